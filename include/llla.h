@@ -202,7 +202,9 @@ llla_status llla_decode(const void *q, const void *Kc, const void *Vc, void *o,
 
 /* Same as llla_decode with the kernel family chosen by the caller.  The matrix-core kernels serve bf16 caches with
  * d = 64 or 128, L_max >= 256 and B * H <= 65535 (queries, keys and values must lie in the f16 range, |x| <= 65504);
- * LLLA_PATH_MFMA on any other call returns LLLA_ERR_UNSUPPORTED, LLLA_PATH_AUTO takes the vector kernels there. */
+ * LLLA_PATH_MFMA on any other call returns LLLA_ERR_UNSUPPORTED; LLLA_PATH_AUTO takes the fp32 matrix-core kernels there
+ * (every d, both dtypes, fp32 arithmetic and no value range), which use the workspace to cut long caches into several parts
+ * but do without it when it is NULL or too small, and the key-space kernel for sequences of at most min(d, 64) keys. */
 llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void *o,
                              llla_strides sk, llla_strides sv, const int32_t *seqlens,
                              int B, int H, int L_max, int d, llla_dtype in, llla_dtype out,

@@ -240,7 +240,8 @@ llla_status llla_backward(const void *Q, const void *K, const void *V, const voi
 size_t llla_decode_workspace_bytes(int B, int H, int L_max, int d, llla_dtype in)
 {
     if (B <= 0 || H <= 0 || L_max <= 0 || !dim_supported(d) || !dtype_ok(in)) return 0;
-    return llla::mfma_decode_workspace_bytes(B, H, L_max, d, in);
+    const size_t need = llla::mfma_decode_workspace_bytes(B, H, L_max, d, in);
+    return need ? need : llla::mfma_decode_f32_workspace_bytes(B, H, L_max, d);
 }
 
 llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void *o, llla_strides sk,
@@ -276,8 +277,13 @@ llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void
         if (st != LLLA_OK) return st;
     }
     llla::stage_begin(p.stream);
-    if (!use_mfma) llla::stage_mark(p.stream, "valu_decode");
-    const hipError_t e = use_mfma ? llla::mfma_decode(p) : llla::valu_decode(p);
+    // fp32 caches, d = 16 / 32 and short bf16 caches: the fp32 matrix-core kernels, faster than the vector kernels at every size
+    // measured (1 to 1024 heads x 66 to 8192 keys).  us, vector vs matrix cores: fp32 d = 64, 64 heads of 1024 .. 8192 keys 1243 vs
+    // 87, 1 head x 66 107 vs 17; d = 128, 256 heads x 8192 4234 vs 1210; d = 32 bf16, 256 heads x 4096 252 vs 51; d = 16, 1024 heads x
+    // 8192 980 vs 193.
+    const bool use_f32 = !use_mfma && path == LLLA_PATH_AUTO && llla::mfma_decode_f32_takes(p);
+    if (!use_mfma && !use_f32) llla::stage_mark(p.stream, "valu_decode");
+    const hipError_t e = use_mfma ? llla::mfma_decode(p) : use_f32 ? llla::mfma_decode_f32(p) : llla::valu_decode(p);
     llla::stage_end(p.stream);
     return e == hipSuccess ? LLLA_OK : LLLA_ERR_LAUNCH;
 }

@@ -104,7 +104,12 @@ size_t mfma_decode_workspace_bytes(int B, int H, int L_max, int d, llla_dtype in
 // whether the MFMA decode path serves this call (it needs the full cache length for every sequence)
 bool mfma_decode_takes(const Problem &p);
 hipError_t mfma_decode(const Problem &p);
-// the d = 128 kernels behind the two functions above (a translation unit of their own)
+// fp32 matrix-core decode (llla_mfma_decode_f32.hip): fp32 caches, and bf16 caches that the 16-bit kernels do not serve.  The
+// workspace is optional: a call with less than the size asked for runs one workgroup per head.
+size_t mfma_decode_f32_workspace_bytes(int B, int H, int L_max, int d);
+bool mfma_decode_f32_takes(const Problem &p);
+hipError_t mfma_decode_f32(const Problem &p);
+// the d = 128 kernels behind mfma_decode (a translation unit of their own)
 size_t mfma_decode128_workspace_bytes(int B, int H, int L_max);
 hipError_t mfma_decode128(const Problem &p);
 

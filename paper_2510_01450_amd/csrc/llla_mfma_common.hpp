@@ -265,7 +265,7 @@ __device__ inline void trinv_row(float (&li)[16], float mul)
 
 // Upper Cholesky factor and its inverse for the diagonal tiles of the wave's four queries at once:
 // lane 16q + r owns row r of query q's symmetric 16x16 tile (a[c] = T[r][c]).  On return
-// li[c] = -(L^{-1})[r][c] with T = L L^T (zero above the diagonal); the sign is the one factorise_wave wants.
+// li[c] = -(L^{-1})[r][c] with T = L L^T (zero above the diagonal); the sign is the one factorise_one wants.
 // pivot_floor: every pivot of the Cholesky factorisation of (a positive semi-definite matrix + lambda I) is
 // at least lambda in exact arithmetic; a computed pivot below the floor (half of lambda) is a rounding
 // artefact of an ill-conditioned early row and is raised to it, which keeps the factorisation finite.
@@ -356,75 +356,63 @@ __device__ inline void dma16_base_nt_off(const void *sbase, unsigned voff, unsig
 #pragma clang diagnostic pop
 __device__ inline void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Blocked factorisation of the wave's QW systems, all in registers / wave-private LDS scratch (the first half of the
-// per-query solve; the substitutions are solve_wave_q4 at d = 64 and solve_wave_v1 at d = 128):
-//   in : acc[q][tix(I,J)]  upper-triangular 16x16 tiles of T_q = -(Sigma~_q + lambda I) (MFMA accumulator layout)
-//        scw               >= QW*16*SC_PITCH floats of LDS owned by this wave
-//        pivot_floor       per lane: half the ridge of the query of the lane's group (see chol_inv16)
+// index of tile (I, J), I <= J, among the upper-triangular 16x16 tiles of a matrix of NB 16-wide blocks (row by row)
+template <int NB>
+__host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I * (I - 1) / 2 + (J - I); }
+
+// Blocked factorisation of ONE system per wave, all in registers / wave-private LDS scratch (the first half of solve_one;
+// solve_wave_q4 has its own for four systems at d = 64):
+//   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I) (MFMA accumulator layout)
+//        scw                   >= 16*SC_PITCH floats of LDS owned by this wave
+//        pivot_floor           half the ridge of the row (see chol_inv16)
 //   out: acc(P,J), P < J, holds U(P,J) and acc(P,P) holds N_P = -U(P,P)^{-1}, with Sigma~ + lambda I = U^T U.
-// 16-blocked upper Cholesky whose block products are C += A^T B on fp32 MFMA; the diagonal tiles of the QW queries
-// are factorised together in (query, row) lanes with DPP row broadcasts.  The matrix cores only add products, so
-// everything that the textbook recursion subtracts is carried negated instead: the trailing matrix (T), the inverse
-// diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on the
-// vector ALU.
-template <int DD>
-__device__ __forceinline__ void factorise_wave(f32x4 (&acc)[Shape<DD>::QW][Shape<DD>::NTILE], float *scw, int g, int nn,
-                                               float pivot_floor)
+// 16-blocked upper Cholesky whose block products are C += A^T B on fp32 MFMA; the diagonal tile is factorised with one
+// row per lane and DPP row broadcasts (the four lane groups of the wave hold four copies).  The matrix cores only add
+// products, so everything that the textbook recursion subtracts is carried negated instead: the trailing matrix (T), the
+// inverse diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on
+// the vector ALU.
+template <int NB>
+__device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor)
 {
-    using S = Shape<DD>;
-    constexpr int QW = S::QW, NB = S::NB;
-    const int gq = (g < QW) ? g : QW - 1;       // lane groups beyond the wave's queries shadow the last one
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
-        // diagonal tiles -> (query, row) lanes, symmetrised
+        // diagonal tile -> one row per lane, symmetrised
 #pragma unroll
-        for (int q = 0; q < QW; ++q)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) scw[q * 16 * SC_PITCH + (4 * g + t) * SC_PITCH + nn] = acc[q][S::tix(P, P)][t];
+        for (int t = 0; t < 4; ++t) scw[(4 * g + t) * SC_PITCH + nn] = acc[upper_tile<NB>(P, P)][t];
         wave_sync();
         float a[16], li[16];
-        {
-            const float *my = scw + gq * 16 * SC_PITCH;
 #pragma unroll
-            for (int c4 = 0; c4 < 4; ++c4) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(my + nn * SC_PITCH + 4 * c4);
+        for (int c4 = 0; c4 < 4; ++c4) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) a[4 * c4 + t] = v[t];
-            }
-#pragma unroll
-            for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + my[c * SC_PITCH + nn]);    // -T, symmetrised
+            for (int t = 0; t < 4; ++t) a[4 * c4 + t] = v[t];
         }
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
         wave_sync();
         chol_inv16(a, li, nn, pivot_floor);
-        if (g < QW) {
-            float *my = scw + g * 16 * SC_PITCH;
+        if (g == 0) {
 #pragma unroll
             for (int c4 = 0; c4 < 4; ++c4)
-                *reinterpret_cast<f32x4 *>(my + nn * SC_PITCH + 4 * c4) = f32x4{li[4 * c4], li[4 * c4 + 1], li[4 * c4 + 2], li[4 * c4 + 3]};
+                *reinterpret_cast<f32x4 *>(scw + nn * SC_PITCH + 4 * c4) = f32x4{li[4 * c4], li[4 * c4 + 1], li[4 * c4 + 2], li[4 * c4 + 3]};
         }
         wave_sync();
+        // N_P in tile layout: reg t = N[4g+t][nn] = -Linv[nn][4g+t]; it replaces the consumed diagonal tile;
+        // U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
+        const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * g);
+        acc[upper_tile<NB>(P, P)] = ui;
 #pragma unroll
-        for (int q = 0; q < QW; ++q) {
-            // N_P in tile layout: reg t = N[4g+t][nn] = -Linv[nn][4g+t]; it replaces the consumed diagonal tile;
-            // U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
-            const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + q * 16 * SC_PITCH + nn * SC_PITCH + 4 * g);
-            acc[q][S::tix(P, P)] = ui;
+        for (int J = P + 1; J < NB; ++J) acc[upper_tile<NB>(P, J)] = tile_atb(zero, ui, acc[upper_tile<NB>(P, J)]);
 #pragma unroll
-            for (int J = P + 1; J < NB; ++J) acc[q][S::tix(P, J)] = tile_atb(zero, ui, acc[q][S::tix(P, J)]);
+        for (int I = P + 1; I < NB; ++I)
 #pragma unroll
-            for (int I = P + 1; I < NB; ++I)
-#pragma unroll
-                for (int J = I; J < NB; ++J) acc[q][S::tix(I, J)] = tile_atb(acc[q][S::tix(I, J)], acc[q][S::tix(P, I)], acc[q][S::tix(P, J)]);
-            // one query at a time: its own tile products give the matrix cores enough independent work, and
-            // interleaving the queries only inflates the number of live registers
-            __builtin_amdgcn_sched_barrier(0);
-        }
+            for (int J = I; J < NB; ++J)
+                acc[upper_tile<NB>(I, J)] = tile_atb(acc[upper_tile<NB>(I, J)], acc[upper_tile<NB>(P, I)], acc[upper_tile<NB>(P, J)]);
+        __builtin_amdgcn_sched_barrier(0);
         wave_sync();
     }
-
 }
-
 
 }  // namespace mfma
 }  // namespace llla

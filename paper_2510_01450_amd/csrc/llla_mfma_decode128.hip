@@ -513,23 +513,23 @@ __global__ __launch_bounds__(NT, 1) void decode128_merge_kernel(const bf16_t *__
     __syncthreads();
 
     if (wave == 0) {   // phase 2 (scalar branch: the block contains MFMAs)
-        f32x4 acc[1][NSIG], rhs[1][NB];
-        float om4[1] = {oms}, y0v[1];
+        f32x4 acc[NSIG], rhs[NB];
+        float y0;
 #pragma unroll
-        for (int t = 0; t < NSIG; ++t) acc[0][t] = -*reinterpret_cast<const f32x4 *>(&merged[t][lane * 4]);
+        for (int t = 0; t < NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&merged[t][lane * 4]);
 #pragma unroll
         for (int P = 0; P < NB; ++P)        // the solve takes -(Sigma~ + lambda I)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[0][S128::tix(P, P)][t] -= (nn == 4 * g + t) ? lambda : 0.f;
-        solve_wave_v1<128>(acc, rhs, y0v, om4, scw, g, nn, 0.5f * lambda, [&](int P, float &m, float &q, float &e) {
+            for (int t = 0; t < 4; ++t) acc[S128::tix(P, P)][t] -= (nn == 4 * g + t) ? lambda : 0.f;
+        solve_one<NB>(acc, rhs, y0, oms, scw, g, nn, 0.5f * lambda, [&](int P, float &m, float &q, float &e) {
             m = -mus[16 * P + nn];
             q = -bf16_to_f32(qg[(size_t)bh * D + 16 * P + nn]);
             (void)e;
         });
         if (nn == 0) {
 #pragma unroll
-            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[0][P];
-            if (g == 0) ys[D] = y0v[0];
+            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[P];
+            if (g == 0) ys[D] = y0;
         }
     }
     __syncthreads();

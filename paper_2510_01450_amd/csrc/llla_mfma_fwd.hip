@@ -425,7 +425,7 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
     for (int q = 0; q < QW; ++q)
 #pragma unroll
         for (int t = 0; t < NTILE; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // The tiles accumulate T = -(Sigma~ + lambda I), the sign the solve works in (see factorise_wave): the ridge is
+    // The tiles accumulate T = -(Sigma~ + lambda I), the sign the solve works in (see factorise_one): the ridge is
     // the starting value of the diagonal, and the scaled MFMA operand carries a minus sign that costs nothing.
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
@@ -920,19 +920,19 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
 #pragma unroll
         for (int q = 0; q < QW; ++q) r0v[q] = Rg[((size_t)bh * n + min(i0 + QW * wave + q, n - 1)) * YP + DD];
     }
-    // one query per wave: factorisation on the matrix cores, substitutions on the vector ALU (solve_wave_v1)
+    // one query per wave: factorisation on the matrix cores, substitutions on the vector ALU (solve_one)
     static_assert(QW == 1, "the general path serves d = 128, one query per wave");
     {
         const int row = min(i0 + wave, n - 1);
         const bf16_t *qrow = Qh + (int64_t)row * sq.seq;
         const float *rrow = WITH_U ? Rg + ((size_t)bh * n + row) * YP : nullptr;
-        solve_wave_v1<DD, WITH_U>(acc, rhs, y0v, om4, &sc[wave][0][0], g, nn, pivot_floor,
+        solve_one<NB, WITH_U>(acc[0], rhs[0], y0v[0], om4[0], &sc[wave][0][0], g, nn, pivot_floor,
                                   [&](int P, float &m, float &q, float &e) {
                                       m = mus[wave][16 * P + nn];                 // mus holds -mu~
                                       q = -bf16_to_f32(qrow[16 * P + nn]);
                                       if constexpr (WITH_U) e = -rrow[16 * P + nn];
                                   },
-                                  r0v, u0v);
+                                  WITH_U ? r0v[0] : 0.f, u0v);
     }
 
 #pragma unroll

@@ -1,5 +1,6 @@
-// Exact solve of ONE augmented system per wave (head dimension 128, one query per wave): the 16-blocked Cholesky
-// factorisation (factorise_wave) on the matrix cores, forward and back substitutions on the vector ALU.
+// Exact solve of ONE augmented system per wave (the moments kernel at head dimension 128, one query per wave; every decode
+// merge): the 16-blocked Cholesky factorisation (factorise_one) on the matrix cores, forward and back substitutions on the
+// vector ALU.
 //
 // Why.  With one query per wave a substitution step is a 16x16 tile times two or three right-hand-side columns; as a
 // 16x16x16 fp32 tile product it occupies the matrix cores for 128 cycles and uses two or three of sixteen output
@@ -13,7 +14,7 @@
 //     the wave), which gives C;  X v (back substitution: U x = z) takes v in C, multiplies per lane and sums over n (the
 //     16 lanes of a row), which gives R;
 //   * C <-> R goes through the wave's scratch tile in LDS (16 floats per vector).
-// The sign conventions are factorise_wave's: tiles hold T = -(Sigma~ + lambda I) factorised as U^T U with acc(P,P) = N_P =
+// The sign conventions are factorise_one's: tiles hold T = -(Sigma~ + lambda I) factorised as U^T U with acc(P,P) = N_P =
 // -U(P,P)^{-1}, right-hand sides come in negated.
 #pragma once
 
@@ -31,24 +32,19 @@ __device__ inline float rows_allsum(float x)
     return x;
 }
 
-//   in : acc[0][tix(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I), accumulator layout (destroyed)
+//   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I), accumulator layout (destroyed)
 //        load_rhs(P, m, q, e)  element 16P + n (n = the lane's position in its row) of -mu~, -q and, WITH_U, -r1
-//        om4[0] = omega; scw: >= 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor as in chol_inv16
-//        WITH_U: r0v[0] = r0
-//   out: rhs[0][P] register t = y1[16P + 4g + t] (every lane; WITH_U: lanes n == 1 hold u1 instead), y0v[0] = y0,
-//        u0v[0] = u0
+//        omega; scw: >= 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor as in chol_inv16
+//        WITH_U: r0
+//   out: rhs[P] register t = y1[16P + 4g + t] (every lane; WITH_U: lanes n == 1 hold u1 instead), y0, u0
 // with [omega mu~^T; mu~ Sigma~ + lambda I] [y0; y1] = [1; q] and, WITH_U, the same matrix times [u0; u1] = [r0; r1].
-template <int DD, bool WITH_U = false, class LoadRhs>
-__device__ __forceinline__ void solve_wave_v1(f32x4 (&acc)[1][Shape<DD>::NTILE], f32x4 (&rhs)[1][Shape<DD>::NB],
-                                              float (&y0v)[1], const float (&om4)[1], float *scw, int g, int nn,
-                                              float pivot_floor, LoadRhs load_rhs, const float *r0v = nullptr,
-                                              float *u0v = nullptr)
+template <int NB, bool WITH_U = false, class LoadRhs>
+__device__ __forceinline__ void solve_one(f32x4 (&acc)[NB * (NB + 1) / 2], f32x4 (&rhs)[NB], float &y0, float omega, float *scw,
+                                          int g, int nn, float pivot_floor, LoadRhs load_rhs, float r0 = 0.f, float *u0_out = nullptr)
 {
-    using S = Shape<DD>;
-    constexpr int NB = S::NB, NS = WITH_U ? 3 : 2;
-    static_assert(S::QW == 1, "one query per wave");
+    constexpr int NS = WITH_U ? 3 : 2;
 
-    factorise_wave<DD>(acc, scw, g, nn, pivot_floor);
+    factorise_one<NB>(acc, scw, g, nn, pivot_floor);
 
     // C -> R and R -> C for NV vectors at once through the scratch tile (vector v at scw + 16 v)
     auto c_to_r = [&](const float (&c)[NS], f32x4 (&r)[NS], int nv) {
@@ -91,7 +87,7 @@ __device__ __forceinline__ void solve_wave_v1(f32x4 (&acc)[1][Shape<DD>::NTILE],
 #pragma unroll
         for (int v = 0; v < NS; ++v) tc[v] = P == 0 ? tv[v][P] : tv[v][P] + rows_allsum(part[v][P]);
         c_to_r(tc, tr, NS);
-        const f32x4 np = acc[0][S::tix(P, P)];
+        const f32x4 np = acc[upper_tile<NB>(P, P)];
         float ac[NS];
 #pragma unroll
         for (int v = 0; v < NS; ++v) {
@@ -102,7 +98,7 @@ __device__ __forceinline__ void solve_wave_v1(f32x4 (&acc)[1][Shape<DD>::NTILE],
             c_to_r(ac, ar, NS);
 #pragma unroll
             for (int I = P + 1; I < NB; ++I) {
-                const f32x4 u = acc[0][S::tix(P, I)];
+                const f32x4 u = acc[upper_tile<NB>(P, I)];
 #pragma unroll
                 for (int v = 0; v < NS; ++v) part[v][I] += dot4(u, ar[v]);
             }
@@ -120,14 +116,13 @@ __device__ __forceinline__ void solve_wave_v1(f32x4 (&acc)[1][Shape<DD>::NTILE],
     }
     saa = row_allsum(saa);
     sac = row_allsum(sac);
-    const float dinv = 1.f / (om4[0] - saa);
-    const float y0 = (1.f - sac) * dinv;
-    y0v[0] = y0;
+    const float dinv = 1.f / (omega - saa);
+    y0 = (1.f - sac) * dinv;
     float u0 = 0.f;
     if constexpr (WITH_U) {
         sae = row_allsum(sae);
-        u0 = (r0v[0] - sae) * dinv;
-        u0v[0] = u0;
+        u0 = (r0 - sae) * dinv;
+        *u0_out = u0;
     }
     constexpr int NZ = WITH_U ? 2 : 1;       // systems of the back substitution
     float zc[NZ][NB], xc[NZ][NB];            // C layout
@@ -150,7 +145,7 @@ __device__ __forceinline__ void solve_wave_v1(f32x4 (&acc)[1][Shape<DD>::NTILE],
             for (int t = 0; t < 4; ++t) p[t] = (nn == 4 * g + t) ? zc[v][P] : 0.f;
 #pragma unroll
             for (int J = P + 1; J < NB; ++J) {
-                const f32x4 u = acc[0][S::tix(P, J)];
+                const f32x4 u = acc[upper_tile<NB>(P, J)];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) p[t] = fmaf(u[t], xc[v][J], p[t]);
             }
@@ -158,13 +153,13 @@ __device__ __forceinline__ void solve_wave_v1(f32x4 (&acc)[1][Shape<DD>::NTILE],
             for (int t = 0; t < 4; ++t) ir[v][t] = row_allsum(p[t]);
         }
         r_to_c(ir, ic, NZ);
-        const f32x4 np = acc[0][S::tix(P, P)];
+        const f32x4 np = acc[upper_tile<NB>(P, P)];
 #pragma unroll
         for (int v = 0; v < NZ; ++v)
 #pragma unroll
             for (int t = 0; t < 4; ++t) xr[v][t] = row_allsum(np[t] * ic[v]);
-        rhs[0][P] = xr[0];
-        if constexpr (WITH_U) rhs[0][P] = (nn == 1) ? xr[1] : xr[0];
+        rhs[P] = xr[0];
+        if constexpr (WITH_U) rhs[P] = (nn == 1) ? xr[1] : xr[0];
         if (P > 0) {
             float c[NS];
             r_to_c(xr, c, NZ);

@@ -1,0 +1,89 @@
+"""Decode on the fp32 matrix-core kernels (path='auto' for fp32 caches, and for bf16 caches that the 16-bit kernels do not
+serve): step and tile remainders, splits of a cache over several workgroups, per-sequence lengths, strided and poisoned caches,
+a call without scratch, both output types.  All outputs against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_01450_amd as llla
+import workloads
+from parity import check
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _case(B, H, L, d, dtype, index, values="normal"):
+    tol = 1e-4                       # fp32 arithmetic for either input type (bf16 widens exactly)
+    w = workloads.C5.with_shape(name="decf32", B=B, H=H, n=L, d=d, dtype=dtype, index=index, values=values, tol=tol,
+                                scale=d ** -0.5)
+    return w, workloads.make_inputs(w)
+
+
+# bf16 at d = 64 / 128 comes here below 256 cached rows only
+@pytest.mark.parametrize("d,dtype,L,BH", [
+    (16, "f32", 65, (2, 3)), (16, "bf16", 4097, (1, 2)), (32, "f32", 33, (3, 1)), (32, "bf16", 3000, (2, 2)),
+    (32, "bf16", 256, (40, 16)), (64, "f32", 257, (2, 2)), (64, "f32", 5003, (1, 3)), (64, "f32", 1030, (70, 8)),
+    (64, "bf16", 255, (2, 3)), (128, "f32", 129, (2, 2)), (128, "f32", 4100, (1, 2)), (128, "f32", 700, (37, 8)),
+    (128, "bf16", 130, (3, 2))])
+def test_full_length(d, dtype, L, BH):
+    B, H = BH
+    w, (q, Kc, Vc) = _case(B, H, L, d, dtype, 2100 + d + L)
+    nb = min(B, 3)
+    ref = oracle.decode(q[:nb], Kc[:nb], Vc[:nb], w.lam, w.scale)
+    qd, Kd, Vd = q.to(DEV), Kc.to(DEV), Vc.to(DEV)
+    got = llla.llla_decode(qd, Kd, Vd, w.lam, w.scale)
+    print(check(got[:nb].cpu().numpy()[:, :, None], ref[:, :, None], np.array([L - 1]), d, w.tol, "L=%d d=%d" % (L, d)))
+    again = llla.llla_decode(qd, Kd, Vd, w.lam, w.scale)
+    assert torch.equal(got, again)
+    half = llla.llla_decode(qd, Kd, Vd, w.lam, w.scale, out_dtype=torch.bfloat16)
+    assert torch.equal(half, got.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("d,dtype", [(16, "f32"), (16, "bf16"), (32, "f32"), (32, "bf16"), (64, "f32"), (128, "f32")])
+def test_lengths_of_their_own_strided_and_poisoned(d, dtype):
+    """Lengths on both sides of the key-space limit, of a step (8 to 32 keys) and of a workgroup's share, in a cache whose rows
+    are 2 d apart and whose tail is NaN."""
+    k = min(d, 64)
+    lens = [1, k, k + 1, k + 7, 2 * d + 9, 4 * d, 4 * d + 1, 1111, 2047, 2048]
+    w, (q, Kc, Vc) = _case(len(lens), 2, 2048, d, dtype, 2200 + d)
+    ref = oracle.decode(q, Kc, Vc, w.lam, w.scale, seqlens=lens)
+    wide = torch.full((len(lens), 2, 2048, 2 * d), float("nan"), dtype=Kc.dtype)
+    Kw, Vw = wide.clone(), wide.clone()
+    Kw[..., :d] = Kc
+    Vw[..., d:] = Vc
+    for b, L in enumerate(lens):
+        Kw[b, :, L:] = float("nan")
+        Vw[b, :, L:] = float("nan")
+    sl = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    got = llla.llla_decode(q.to(DEV), Kw.to(DEV)[..., :d], Vw.to(DEV)[..., d:], w.lam, w.scale, seqlens=sl).cpu().numpy()
+    for b, L in enumerate(lens):
+        print(L, check(got[b:b + 1, :, None], ref[b:b + 1, :, None], np.array([L - 1]), d, w.tol, "seqlen %d d=%d" % (L, d)))
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_without_scratch_and_static(d):
+    """The scratch is optional here (one workgroup per head without it), and llla_decode_static runs the same kernels."""
+    L = 3001
+    w, (q, Kc, Vc) = _case(1, 3, L, d, "f32", 2300 + d, values="l2")
+    ref = oracle.decode(q, Kc, Vc, w.lam, w.scale)
+    qd, Kd, Vd = q.to(DEV), Kc.to(DEV), Vc.to(DEV)
+    assert llla.decode_workspace_bytes(1, 3, L, d, torch.float32) > 0
+    bare = llla.llla_decode(qd, Kd, Vd, w.lam, w.scale, workspace=torch.empty(16, dtype=torch.uint8, device=DEV))
+    full = llla.llla_decode(qd, Kd, Vd, w.lam, w.scale)
+    static = llla.llla_decode_static(qd, Kd, Vd, w.lam, w.scale, torch.empty((1, 3, d), device=DEV))
+    assert torch.equal(full, static)
+    for got in (bare, full):
+        print(check(got.cpu().numpy()[:, :, None], ref[:, :, None], np.array([L - 1]), d, w.tol, "scratch d=%d" % d))
+
+
+@pytest.mark.parametrize("scale", [40.0, -30.0, 0.0])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_reference_exponent_moves(d, scale):
+    """Logits that span far more than 2^8 move the reference exponent during the sweep; with scale 0 all weights are equal."""
+    L = 900
+    w, (q, Kc, Vc) = _case(2, 2, L, d, "f32", 2400 + d, values="l2")
+    ref = oracle.decode(q, Kc, Vc, w.lam, scale)
+    got = llla.llla_decode(q.to(DEV), Kc.to(DEV), Vc.to(DEV), w.lam, scale).cpu().numpy()
+    print(check(got[:, :, None], ref[:, :, None], np.array([L - 1]), d, w.tol, "scale %g d=%d" % (scale, d)))
