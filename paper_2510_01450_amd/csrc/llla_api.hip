@@ -240,7 +240,7 @@ llla_status llla_backward(const void *Q, const void *K, const void *V, const voi
 size_t llla_decode_workspace_bytes(int B, int H, int L_max, int d, llla_dtype in)
 {
     if (B <= 0 || H <= 0 || L_max <= 0 || !dim_supported(d) || !dtype_ok(in)) return 0;
-    const size_t need = llla::mfma_decode_workspace_bytes(B, H, L_max, d, in);
+    const size_t need = llla::mfma_decode_wanted_bytes(B, H, L_max, d, in);
     return need ? need : llla::mfma_decode_f32_workspace_bytes(B, H, L_max, d);
 }
 

@@ -100,7 +100,8 @@ hipError_t padded_backward(const BackwardProblem &p);
 size_t mfma_forward_cg_workspace_bytes(int B, int H, int n, int d, llla_dtype in);
 hipError_t mfma_forward_cg(const Problem &p, int T, float eps, int32_t *iters);
 bool mfma_decode_supported(int d, llla_dtype in);
-size_t mfma_decode_workspace_bytes(int B, int H, int L_max, int d, llla_dtype in);
+size_t mfma_decode_workspace_bytes(int B, int H, int L_max, int d, llla_dtype in);      // what a call must have
+size_t mfma_decode_wanted_bytes(int B, int H, int L_max, int d, llla_dtype in);         // and what it can make use of (at least that)
 // whether the MFMA decode path serves this call (it needs the full cache length for every sequence)
 bool mfma_decode_takes(const Problem &p);
 hipError_t mfma_decode(const Problem &p);
@@ -111,6 +112,7 @@ bool mfma_decode_f32_takes(const Problem &p);
 hipError_t mfma_decode_f32(const Problem &p);
 // the d = 128 kernels behind mfma_decode (a translation unit of their own)
 size_t mfma_decode128_workspace_bytes(int B, int H, int L_max);
+size_t mfma_decode128_flat_bytes(int B, int H, int L_max);
 hipError_t mfma_decode128(const Problem &p);
 
 // ---- stage hooks ---------------------------------------------------------------------------------

@@ -1,0 +1,377 @@
+// What the matrix-core decode kernels have in common after (and before) their pass over the cache: how a cache is cut into the
+// shares of workgroups, the merge of the waves of a workgroup, the record a workgroup leaves, the merge of a head's records, and the
+// solve and output of a head.
+//
+// Moments of a head: omega, mu~, sum w v, and 16x16 tiles in the MFMA accumulator layout -- Sigma~ (upper triangle, row by row), then
+// G~ = sum w k v^T row-major -- all relative to 2^m.  PERM: element n of feature block I is feature NB n + I instead of 16 I + n (the
+// order in which the fp32 kernels load their operands).
+#pragma once
+
+#include "llla_mfma_common.hpp"
+#include "llla_mfma_solve128.hpp"
+#include <algorithm>
+
+namespace llla {
+namespace mfma {
+
+constexpr int DEC_NT = 256;                               // threads of every decode workgroup
+
+template <int D>
+struct DecShape {
+    static constexpr int NB = D / 16;                     // 16-wide feature blocks
+    static constexpr int NSIG = NB * (NB + 1) / 2;
+    static constexpr int NTILES = NSIG + NB * NB;
+    static constexpr int HDR = 64 + 2 * D;                // record: [m, omega, ..], mu~ at 64, sum w v at 64 + D, tiles at HDR
+    static constexpr int REC_F = HDR + NTILES * 256;
+};
+
+// ---- shares ----------------------------------------------------------------------------------------------------------
+// Even (slots == 0): every (batch, head) gets nsplit workgroups, grid (nsplit, B H); a sequence's own length is divided evenly
+// over them.  With nsplit == 1 a workgroup solves its head and writes the output itself.
+// Flat (slots > 0), grid (slots, H): the keys of all sequences of a head index, one sequence behind the other, are cut into slots
+// equal shares; a workgroup walks through the one or more sequences that its share touches and leaves a record for each.
+// Lengths that differ, or a number of heads that does not divide the GPU's slots, then leave no workgroup idle: with even
+// parts a batch with lengths uniform in [L/8, L] takes as long as if all had length L (1.8 times its keys' worth).
+// Positions are counted in units of `unit` keys, sequences padded to whole units, so that no piece is smaller than a unit.
+struct DecSplit {
+    const int32_t *seqlens;
+    int B, H, L_max;
+    int nsplit;            // even: workgroups per head
+    int slots;             // flat: workgroups per head index
+    int unit;              // flat: keys per unit
+    int units_min;         // flat: fewest units worth a workgroup
+    int max_split;         // flat: most pieces of a sequence (about)
+};
+
+constexpr int FLAT_MAX_B = 256;                           // more sequences with lengths of their own: the even cut
+
+struct DecPiece {
+    int b, h, bh, L;       // sequence, head, length
+    int k0, k1;            // keys [k0, k1) of it
+    int rec;               // index of the record
+};
+
+// Start of sequence b (in units), the sum of all and the share of a workgroup
+struct FlatPlan { int start, total, share; };
+
+__device__ inline int seq_len(const DecSplit &s, int b) { return s.seqlens ? min(max(s.seqlens[b], 1), s.L_max) : s.L_max; }
+__device__ inline int seq_units(const DecSplit &s, int b) { return (seq_len(s, b) + s.unit - 1) / s.unit; }
+
+__device__ inline int flat_share(const DecSplit &s, int total, int longest)
+{
+    const int even = (total + s.slots - 1) / s.slots, cap = (longest + s.max_split - 1) / s.max_split;
+    return max(max(even, cap), s.units_min);
+}
+
+// `b_of`: the sequence whose start is asked for, or -1 for the one that holds position pos(share)
+template <class Pos>
+__device__ inline FlatPlan flat_plan(const DecSplit &s, int &b_of, Pos pos)
+{
+    FlatPlan r;
+    if (s.seqlens == nullptr) {
+        const int u = (s.L_max + s.unit - 1) / s.unit;
+        r.total = u * s.B;
+        r.share = flat_share(s, r.total, u);
+        if (b_of < 0) b_of = min(pos(r.share) / u, s.B - 1);
+        r.start = b_of * u;
+        return r;
+    }
+    const int lane = threadIdx.x % 64;
+    int u[FLAT_MAX_B / 64], incl[FLAT_MAX_B / 64], total = 0, longest = 0;
+#pragma unroll
+    for (int c = 0; c < FLAT_MAX_B / 64; ++c) {
+        u[c] = incl[c] = 0;
+        if (64 * c < s.B) {                               // wave-uniform
+            const int b = 64 * c + lane;
+            u[c] = b < s.B ? seq_units(s, b) : 0;
+            int x = u[c];
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int y = __shfl_up(x, off);
+                if (lane >= off) x += y;
+            }
+            incl[c] = total + x;
+            longest = max(longest, u[c]);
+            total = __builtin_amdgcn_readlane(incl[c], 63);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
+    r.total = total;
+    r.share = __builtin_amdgcn_readfirstlane(flat_share(s, total, longest));
+    if (b_of < 0) {                                       // the first sequence that ends beyond the position
+        const int at = pos(r.share);
+        int b = 0;
+#pragma unroll
+        for (int c = 0; c < FLAT_MAX_B / 64; ++c)
+            if (64 * c < s.B) b += __builtin_popcountll(__builtin_amdgcn_ballot_w64(64 * c + lane < s.B && incl[c] <= at));
+        b_of = min(b, s.B - 1);
+    }
+    r.start = 0;
+#pragma unroll
+    for (int c = 0; c < FLAT_MAX_B / 64; ++c)
+        if ((b_of >> 6) == c) r.start = __builtin_amdgcn_readlane(incl[c] - u[c], b_of & 63);
+    return r;
+}
+
+// Calls body(piece) for every piece of this workgroup's share, with a barrier between two of them (the body owns the workgroup's
+// LDS).  Everything that decides the control flow is wave-uniform and the same in all waves.  ONE: even cut, one piece.
+template <bool ONE, class Body>
+__device__ __forceinline__ void for_pieces(const DecSplit &s, Body body)
+{
+    DecPiece pc;
+    const bool flat = !ONE && s.slots != 0;
+    int start = 0, stop = 0, end = 0;
+    if (!flat) {
+        pc.bh = blockIdx.y;
+        pc.b = pc.bh / s.H;
+        pc.h = pc.bh % s.H;
+        pc.L = __builtin_amdgcn_readfirstlane(seq_len(s, pc.b));
+        const int part = (pc.L + s.nsplit - 1) / s.nsplit;
+        pc.k0 = min((int)blockIdx.x * part, pc.L);
+        pc.k1 = min(pc.k0 + part, pc.L);
+        pc.rec = pc.bh * s.nsplit + blockIdx.x;
+    } else {
+        int b = -1;
+        const FlatPlan plan = flat_plan(s, b, [](int share) { return (int)blockIdx.x * share; });
+        pc.b = __builtin_amdgcn_readfirstlane(b);
+        pc.h = blockIdx.y;
+        const int share = __builtin_amdgcn_readfirstlane(plan.share), at = (int)blockIdx.x * share;
+        end = min(at + share, __builtin_amdgcn_readfirstlane(plan.total));
+        if (at >= end) return;
+        start = __builtin_amdgcn_readfirstlane(plan.start);
+        pc.L = __builtin_amdgcn_readfirstlane(seq_len(s, pc.b));
+        stop = min(end, start + (pc.L + s.unit - 1) / s.unit);
+        pc.k0 = (at - start) * s.unit;
+        pc.k1 = min((stop - start) * s.unit, pc.L);
+        pc.bh = pc.b * s.H + pc.h;
+        pc.rec = (int)blockIdx.y * (s.slots + s.B) + (int)blockIdx.x + pc.b;
+    }
+    for (;;) {
+        body(pc);
+        if (ONE || stop == end) break;
+        __syncthreads();
+        start = stop;
+        ++pc.b;
+        ++pc.rec;
+        pc.bh += s.H;
+        pc.L = __builtin_amdgcn_readfirstlane(seq_len(s, pc.b));
+        stop = min(end, start + (pc.L + s.unit - 1) / s.unit);
+        pc.k0 = 0;
+        pc.k1 = min((stop - start) * s.unit, pc.L);
+    }
+}
+
+// The lane index as a value of its own for every piece: what a body derives from it would otherwise be kept in registers across
+// the pieces (the d = 128 kernel spilled 64 registers that way).
+__device__ inline int piece_lane()
+{
+    int lane = threadIdx.x % 64;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+struct DecRecords { int first, count; };
+__device__ inline DecRecords dec_records(const DecSplit &s, int bh)
+{
+    if (s.slots == 0) return DecRecords{bh * s.nsplit, s.nsplit};
+    int b = bh / s.H;
+    const int h = bh % s.H;
+    const FlatPlan plan = flat_plan(s, b, [](int) { return 0; });
+    const int x0 = plan.start / plan.share, x1 = (plan.start + seq_units(s, b) - 1) / plan.share;
+    return DecRecords{__builtin_amdgcn_readfirstlane(h * (s.slots + s.B) + x0 + b), __builtin_amdgcn_readfirstlane(x1 - x0 + 1)};
+}
+
+// Host side.  Which cut a call takes: room = records that the scratch holds; gpu_slots = workgroups the GPU holds at once.
+// Flat where the lengths differ, or where the even cut's last round would leave more than a fifth of the slots idle.
+inline DecSplit choose_split(const Problem &p, int nsplit, size_t room, int gpu_slots, int unit, int keys_min, int max_split)
+{
+    const int bh = p.B * p.H;
+    DecSplit s{p.seqlens, p.B, p.H, p.n, nsplit, 0, unit, std::max(keys_min / unit, 1), max_split};
+    const int slots = std::max(gpu_slots / p.H, 1);
+    const bool fits = p.B >= 2 && (size_t)(slots + p.B) * p.H <= room && (long long)p.B * (p.n / keys_min) > 1;
+    const long long wgs = (long long)bh * nsplit, rounds = (wgs + gpu_slots - 1) / gpu_slots;
+    const bool uneven = wgs > gpu_slots && 5 * wgs < 4 * rounds * gpu_slots;
+    if (fits && (p.seqlens ? p.B <= FLAT_MAX_B : uneven)) s.slots = slots;
+    return s;
+}
+inline size_t flat_records(int B, int H, int gpu_slots) { return (size_t)(std::max(gpu_slots / H, 1) + B) * H; }
+
+// ---- merge, solve, output ----------------------------------------------------------------------------------------------
+struct HeadOut {
+    const void *q;
+    void *o;
+    int out_bf16;
+    float lambda;
+};
+
+// LDS of one head: NBUF copies of the tiles (the merge of a workgroup's waves), NW copies of the vectors
+template <int D, int NBUF, int NW>
+struct HeadLds {
+    float tiles[NBUF][DecShape<D>::NTILES * 256];
+    float mu[NW][D], yv[NW][D];
+    float sc[16 * SC_PITCH];
+    float ys[D + 4];
+    float mw[4], om[4];
+};
+
+// Solve and output of one head whose merged moments lie in lds.tiles[0], lds.mu[0], lds.yv[0], lds.om[0].  Called by all four
+// waves after a barrier.
+template <int D, typename TI, bool PERM, class Lds>
+__device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
+{
+    using S = DecShape<D>;
+    constexpr int NB = S::NB;
+    const int g = lane / 16, nn = lane % 16;
+    if (wave == 0) {                                      // scalar branch: the block contains MFMAs
+        f32x4 acc[S::NSIG], rhs[NB];
+        float y0;
+#pragma unroll
+        for (int t = 0; t < S::NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][t * 256 + lane * 4]);
+#pragma unroll
+        for (int P = 0; P < NB; ++P)                      // the solve takes -(Sigma~ + lambda I)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[upper_tile<NB>(P, P)][t] -= (nn == 4 * g + t) ? out.lambda : 0.f;
+        const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
+        solve_one<NB>(acc, rhs, y0, lds.om[0], lds.sc, g, nn, 0.5f * out.lambda, [&](int P, float &m, float &q, float &e) {
+            m = -lds.mu[0][16 * P + nn];
+            const TI v = qp[PERM ? NB * nn + P : 16 * P + nn];
+            if constexpr (sizeof(TI) == 2) q = -bf16_to_f32(v);
+            else q = -v;
+            (void)e;
+        });
+        if (nn == 0) {
+#pragma unroll
+            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&lds.ys[16 * P + 4 * g]) = rhs[P];
+            if (g == 0) lds.ys[D] = y0;
+        }
+    }
+    __syncthreads();
+    const float y0 = lds.ys[D];
+    for (int J = wave; J < NB; J += 4) {
+        float s = 0.f;
+#pragma unroll
+        for (int I = 0; I < NB; ++I) {
+            const f32x4 gv = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * I + J) * 256 + lane * 4]);
+            const f32x4 y1 = *reinterpret_cast<const f32x4 *>(&lds.ys[16 * I + 4 * g]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s = fmaf(gv[t], y1[t], s);        // G~[16I+4g+t][16J+nn] y1[16I+4g+t]
+        }
+        s = rows_allsum(s);
+        const float o = fmaf(y0, lds.yv[0][16 * J + nn], s);
+        if (g == 0) {
+            const size_t at = (size_t)bh * D + (PERM ? NB * nn + J : 16 * J + nn);
+            if (out.out_bf16) static_cast<bf16_t *>(out.o)[at] = f32_to_bf16(o);
+            else static_cast<float *>(out.o)[at] = o;
+        }
+    }
+}
+
+// The four waves of a workgroup, each with moments of its own share of the keys, become one set of moments: in the workgroup's
+// record R, or (FUSED: one workgroup per head) in LDS, from where the head is solved and its output written.  Summed in a fixed
+// order through NBUF LDS copies of the tiles.  A record per wave instead cost four times the traffic (27 KB each at d = 64).
+//   mref: the exponent the wave's moments refer to; mtrue: the largest logit of its keys (both wave-uniform, -inf without keys)
+//   om: sum of the wave's weights; mu[J], yv[J]: element n of block J, in the lanes of group 0 at least
+template <int D, typename TI, bool PERM, bool FUSED, int NBUF, class Lds>
+__device__ __forceinline__ void finish_workgroup(Lds &lds, f32x4 (&acc)[DecShape<D>::NTILES], float (&mu)[DecShape<D>::NB],
+                                                 float (&yv)[DecShape<D>::NB], float om, float mref, float mtrue, float *R,
+                                                 const HeadOut &out, int bh, int wave, int lane)
+{
+    using S = DecShape<D>;
+    constexpr int NB = S::NB, NTILES = S::NTILES;
+    static_assert(NBUF == 2 || NBUF == 4, "two or four copies of the tiles");
+    const int nn = lane % 16, tid = wave * 64 + lane;
+    if (lane == 0) lds.mw[wave] = mtrue;
+    __syncthreads();
+    const float mall = fmaxf(fmaxf(lds.mw[0], lds.mw[1]), fmaxf(lds.mw[2], lds.mw[3]));
+    const float f = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - mall);
+    auto put = [&](float *dst, bool add) {
+#pragma unroll
+        for (int t = 0; t < NTILES; ++t) {
+            f32x4 *p = reinterpret_cast<f32x4 *>(dst + t * 256 + lane * 4);
+            *p = add ? *p + f * acc[t] : f * acc[t];
+        }
+    };
+    if (lane < 16) {
+#pragma unroll
+        for (int J = 0; J < NB; ++J) { lds.mu[wave][16 * J + nn] = f * mu[J]; lds.yv[wave][16 * J + nn] = f * yv[J]; }
+    }
+    if (lane == 0) lds.om[wave] = f * om;
+    if (wave < NBUF) put(lds.tiles[wave & (NBUF - 1)], false);
+    __syncthreads();
+    if constexpr (NBUF == 2) {
+        if (wave >= 2) put(lds.tiles[wave - 2], true);
+        __syncthreads();
+    }
+    for (int i = tid; i < NTILES * 64; i += DEC_NT) {
+        f32x4 v = reinterpret_cast<const f32x4 *>(lds.tiles[0])[i];
+#pragma unroll
+        for (int bf = 1; bf < NBUF; ++bf) v += reinterpret_cast<const f32x4 *>(lds.tiles[bf])[i];
+        if constexpr (FUSED) reinterpret_cast<f32x4 *>(lds.tiles[0])[i] = v;
+        else *reinterpret_cast<f32x4 *>(R + S::HDR + 4 * i) = v;
+    }
+    if (tid < 2 * D) {
+        float *src = tid < D ? &lds.mu[0][tid] : &lds.yv[0][tid - D];
+        const float v = (src[0] + src[D]) + (src[2 * D] + src[3 * D]);
+        if constexpr (FUSED) src[0] = v;
+        else R[64 + tid] = v;
+    }
+    const float oall = (lds.om[0] + lds.om[1]) + (lds.om[2] + lds.om[3]);
+    if constexpr (FUSED) {
+        __syncthreads();
+        if (tid == 0) lds.om[0] = oall;
+        __syncthreads();
+        solve_and_store<D, TI, PERM>(lds, out, bh, wave, lane);
+    } else if (tid == 0) {
+        R[0] = mall;
+        R[1] = oall;
+    }
+}
+
+// Merge of a head's records (max-rescaled sum), solve, output: one head per workgroup.  The records are fetched eight at a time,
+// every thread owning the same 16 bytes of each, so a head's records are in after one or two round trips to memory.
+template <int D, typename TI, bool PERM>
+__global__ __launch_bounds__(DEC_NT, 1) void decode_merge_kernel(DecSplit split, HeadOut out, const float *__restrict__ parts)
+{
+    using S = DecShape<D>;
+    __shared__ __align__(16) HeadLds<D, 1, 1> lds;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, bh = blockIdx.x;
+    const DecRecords rec = dec_records(split, bh);
+    const int np = rec.count;
+    const float *P0 = parts + (size_t)rec.first * S::REC_F;
+    constexpr int PG = 8;
+    const float mstar = wave_max_strided(P0, 0, np, S::REC_F, lane);
+    constexpr int N4 = (S::NTILES * 64 + DEC_NT - 1) / DEC_NT;
+    f32x4 acc[N4];
+#pragma unroll
+    for (int i = 0; i < N4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float hv = 0.f, om = 0.f;
+    for (int pb = 0; pb < np; pb += PG) {
+        float fk[PG];
+#pragma unroll
+        for (int k = 0; k < PG; ++k) {
+            const float *P = P0 + (size_t)min(pb + k, np - 1) * S::REC_F;            // past the end: factor 0
+            const float m = P[0];
+            fk[k] = (pb + k >= np || m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mstar);
+            om = fmaf(fk[k], P[1], om);
+            if (tid < 2 * D) hv = fmaf(fk[k], P[64 + tid], hv);
+        }
+#pragma unroll
+        for (int i = 0; i < N4; ++i) {
+            const int at = min(tid + DEC_NT * i, S::NTILES * 64 - 1);
+#pragma unroll
+            for (int k = 0; k < PG; ++k)
+                acc[i] += fk[k] * *reinterpret_cast<const f32x4 *>(P0 + (size_t)min(pb + k, np - 1) * S::REC_F + S::HDR + 4 * at);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N4; ++i)
+        if (tid + DEC_NT * i < S::NTILES * 64) reinterpret_cast<f32x4 *>(lds.tiles[0])[tid + DEC_NT * i] = acc[i];
+    if (tid < 2 * D) (tid < D ? lds.mu[0] : lds.yv[0])[tid & (D - 1)] = hv;
+    if (tid == 0) lds.om[0] = om;
+    __syncthreads();
+    solve_and_store<D, TI, PERM>(lds, out, bh, wave, lane);
+}
+
+}  // namespace mfma
+}  // namespace llla

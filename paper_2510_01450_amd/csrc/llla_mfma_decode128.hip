@@ -1,5 +1,5 @@
 // Matrix-core decode path of Local Linear Attention for gfx950 at head dimension 128: bf16 caches, cache
-// capacity L_max >= 1024, optional per-sequence lengths.  The method is the one of the d = 64 kernel (a single
+// capacity L_max >= 256, optional per-sequence lengths.  The method is the one of the d = 64 kernel (a single
 // pass over the cache that accumulates omega, mu~, Sigma~ of Eq. (tilded_form) and the value moments sum w v,
 // G~ = sum w k v^T relative to a running maximum as in Algorithm 1, then one solve per head and
 // o = y0 * sum w v + G~^T y1, which is Eq. (lla) with the sum over keys taken first).
@@ -15,8 +15,7 @@
 // A step's K and V tiles (16 KB) come into LDS in 16 transfers, five by each of the three other waves and one by the
 // weight wave; a wave converts what it brought from bf16 to f16 in place; four stages rotate with one workgroup
 // barrier per step.
-#include "llla_mfma_common.hpp"
-#include "llla_mfma_solve128.hpp"
+#include "llla_decode_tail.hpp"
 #include <type_traits>
 
 namespace llla {
@@ -25,14 +24,14 @@ namespace {
 using namespace mfma;
 
 using S128 = Shape<128>;
-constexpr int D = 128, NB = 8, NT = 256;
+constexpr int D = 128, NB = 8, NT = DEC_NT;
 constexpr int STEP = 32;                       // keys per MFMA step
 constexpr int NSTAGE = 4;                      // LDS stages per workgroup: two being read, two being filled
 constexpr int TILE_H = STEP * D;               // halves of one natural [32 keys][128] tile (8 KB)
 constexpr int STAGE_H = 2 * TILE_H;            // K tile + V tile
-constexpr int NSIG = 36, NTILES = 100;         // Sigma~ upper triangle, then G~ row-major [I][J]
-constexpr int HDR = 3 * D;                     // [m, omega, ..pad], mu~ at [D, 2D), sum w v at [2D, 3D)
-constexpr int PART_F = HDR + NTILES * 256;     // floats per partial record
+constexpr int NSIG = DecShape<D>::NSIG, HDR = DecShape<D>::HDR, REC_F = DecShape<D>::REC_F;      // record layout
+constexpr int KEYS_MIN = 8 * STEP;             // fewest keys worth a workgroup
+constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MIN_L = 256;                     // shorter caches go to the vector path
 constexpr int MAX_SPLIT = 32;
 constexpr int PRECISE_L = 4 * D;               // sequences up to this length take the two-term weights
@@ -47,19 +46,11 @@ typedef __attribute__((address_space(3))) const half8 *lds_half8_ptr;
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint4v *lds_uint4_ptr;
 
-struct Split {
-    int nsplit;          // workgroups (= partial records) per head
-};
-
-Split make_split(int bh, int L)
+int make_split(int bh, int L)                     // workgroups (= records) per head
 {
-    Split s;
-    int want = (512 + bh - 1) / bh;                  // two workgroups per compute unit are resident
-    int most = L / (8 * STEP);                       // at least 8 steps per workgroup
-    if (most < 1) most = 1;
-    s.nsplit = want < 1 ? 1 : (want > most ? most : want);
-    if (s.nsplit > MAX_SPLIT) s.nsplit = MAX_SPLIT;
-    return s;
+    const int want = (SLOTS + bh - 1) / bh, most = L / KEYS_MIN;
+    const int n = want > most ? most : want;
+    return n < 1 ? 1 : n > MAX_SPLIT ? MAX_SPLIT : n;
 }
 
 // two bf16 packed in a dword -> two f16 packed (exact for values in the f16 range)
@@ -94,15 +85,14 @@ __host__ __device__ constexpr int tix4(int i, int j) { return i * 4 - i * (i - 1
 struct PartialArgs {
     const bf16_t *qg, *Kg, *Vg;
     llla_strides sk, sv;
-    const int32_t *seqlens;
-    int H, L_max, nparts;
+    DecSplit split;
     float cscale;
     float *parts;
 };
 
 // The share of wave (WA, WB): rows 4 WA .. 4 WA + 3 (feature blocks), columns 4 WB .. 4 WB + 3.
 template <int WA, int WB, bool PRECISE>
-__device__ __forceinline__ void partial_body(const PartialArgs &a, bf16_t *stage, float *xrec, int wave, int lane)
+__device__ __forceinline__ void partial_body(const PartialArgs &a, const DecPiece &pc, bf16_t *stage, float *xrec, int wave, int lane)
 {
     constexpr bool SIG_DIAG = (WA == WB);                 // 10 tiles of a diagonal quarter of Sigma~
     constexpr bool SIG_FULL = (WA == 0 && WB == 1);       // the 16 tiles of the upper-right quarter
@@ -113,13 +103,9 @@ __device__ __forceinline__ void partial_body(const PartialArgs &a, bf16_t *stage
     constexpr bool HAS_YV = (WA == 0);                    // (sum w v) blocks 4 WB .. 4 WB + 3
 
     const int g = lane / 16, nn = lane % 16;
-    const int bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
-    const int part = blockIdx.x;
-    // the sequence's own length decides the share of each workgroup; rows at and beyond L are never read
-    const int L = a.seqlens ? min(max(a.seqlens[b], 1), a.L_max) : a.L_max;
-    const int keys_per_part = ((L + a.nparts - 1) / a.nparts + STEP - 1) / STEP * STEP;
-    const int r0 = part * keys_per_part;
-    const int r1 = min(r0 + keys_per_part, L);
+    // rows at and beyond L are never read
+    const int bh = pc.bh, b = pc.b, h = pc.h, part = (int)blockIdx.x, L = pc.L;
+    const int r0 = pc.k0, r1 = pc.k1;
     const int nsteps = __builtin_amdgcn_readfirstlane(r1 > r0 ? (r1 - r0 + STEP - 1) / STEP : 0);
     // Short sequences are the ill-conditioned ones (fewer keys than features leave directions that only the ridge
     // holds, and a relative error of 2^-11 in w k is then not small against the ridge): they take the weights in
@@ -424,13 +410,13 @@ __device__ __forceinline__ void partial_body(const PartialArgs &a, bf16_t *stage
 
     om += __shfl_xor(om, 16);
     om += __shfl_xor(om, 32);
-    float *P = a.parts + ((size_t)bh * a.nparts + part) * PART_F;
+    float *P = a.parts + (size_t)pc.rec * REC_F;
     if (WA == 0 && WB == 0 && lane == 0) { P[0] = m; P[1] = om; }
     if (g == 0) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if constexpr (HAS_MU) P[D + 64 * WA + 16 * j + nn] = muacc[j][0];
-            if constexpr (HAS_YV) P[2 * D + 64 * WB + 16 * j + nn] = yvacc[j][0];
+            if constexpr (HAS_MU) P[64 + 64 * WA + 16 * j + nn] = muacc[j][0];
+            if constexpr (HAS_YV) P[64 + D + 64 * WB + 16 * j + nn] = yvacc[j][0];
         }
     }
 #pragma unroll
@@ -451,111 +437,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 {
     __shared__ __align__(16) bf16_t stage[NSTAGE * STAGE_H];       // 4 stages x 16 KB
     __shared__ __align__(16) float xrec[2][XREC_F];                // the weights of a step, from the wave that forms them to all four
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     // Scalar branches: each wave runs the loop of its own share; all of them meet at the same barriers.  The shares
     // differ in work (16 tiles plus the weights, 30 to 36 tiles), and wave w of every workgroup runs on SIMD w of its compute unit; the shares
     // therefore rotate with the workgroup index, so that no SIMD gets the heaviest share from both of its workgroups.
-    const int b = (int)blockIdx.y / a.H;
-    const int L = a.seqlens ? min(max(a.seqlens[b], 1), a.L_max) : a.L_max;
     const int role = (wave + (int)blockIdx.x + (int)blockIdx.y) & 3;
-    if (__builtin_amdgcn_readfirstlane(L <= PRECISE_L ? 1 : 0)) {
-        if (role == 0) partial_body<0, 0, true>(a, stage, &xrec[0][0], wave, lane);
-        else if (role == 1) partial_body<0, 1, true>(a, stage, &xrec[0][0], wave, lane);
-        else if (role == 2) partial_body<1, 0, true>(a, stage, &xrec[0][0], wave, lane);
-        else partial_body<1, 1, true>(a, stage, &xrec[0][0], wave, lane);
-    } else {
-        if (role == 0) partial_body<0, 0, false>(a, stage, &xrec[0][0], wave, lane);
-        else if (role == 1) partial_body<0, 1, false>(a, stage, &xrec[0][0], wave, lane);
-        else if (role == 2) partial_body<1, 0, false>(a, stage, &xrec[0][0], wave, lane);
-        else partial_body<1, 1, false>(a, stage, &xrec[0][0], wave, lane);
-    }
-}
-
-// Merge, solve, output for one head per workgroup (4 waves):
-//   phase 1  wave w sums tiles w, w + 4, .. of the head's partial records with the max-rescale factors
-//            2^(m_p - m*) into LDS (the merge step of Algorithm 1's running maximum);
-//   phase 2  wave 0 solves the augmented system;
-//   phase 3  wave w forms o = y0 * (sum w v) + G~^T y1 for the value blocks 2w and 2w + 1.
-__global__ __launch_bounds__(NT, 1) void decode128_merge_kernel(const bf16_t *__restrict__ qg, const float *__restrict__ parts,
-                                                                int nparts, float lambda, void *__restrict__ og, int out_bf16)
-{
-    constexpr int TPW = NTILES / 4;                                 // tiles per wave in phase 1
-    __shared__ __align__(16) float merged[NTILES][256];
-    __shared__ __align__(16) float scw[16 * SC_PITCH];
-    __shared__ __align__(16) float mus[D], yvs[D], ys[D + 4];
-    __shared__ float oms;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16,
-              nn = lane % 16;
-    const int bh = blockIdx.x;
-    const float *P0 = parts + (size_t)bh * nparts * PART_F;
-
-    {   // phase 1
-        const float mstar = wave_max_strided(P0, 0, nparts, PART_F, lane);
-        float om = 0.f, hv = 0.f;
-        f32x4 acc[TPW];
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < nparts; ++p) {
-            const float *P = P0 + (size_t)p * PART_F;
-            const float mp = P[0];
-            const float f = (mp == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mp - mstar);
-            om = fmaf(f, P[1], om);
-            hv = fmaf(f, P[D + tid], hv);                           // mu~ (threads 0..127), sum w v (128..255)
-#pragma unroll
-            for (int t = 0; t < TPW; ++t)
-                acc[t] += f * *reinterpret_cast<const f32x4 *>(P + HDR + (4 * t + wave) * 256 + lane * 4);
+    for_pieces<false>(a.split, [&](const DecPiece &pc) {
+        if (__builtin_amdgcn_readfirstlane(pc.L <= PRECISE_L ? 1 : 0)) {
+            if (role == 0) partial_body<0, 0, true>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+            else if (role == 1) partial_body<0, 1, true>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+            else if (role == 2) partial_body<1, 0, true>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+            else partial_body<1, 1, true>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+        } else {
+            if (role == 0) partial_body<0, 0, false>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+            else if (role == 1) partial_body<0, 1, false>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+            else if (role == 2) partial_body<1, 0, false>(a, pc, stage, &xrec[0][0], wave, piece_lane());
+            else partial_body<1, 1, false>(a, pc, stage, &xrec[0][0], wave, piece_lane());
         }
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) *reinterpret_cast<f32x4 *>(&merged[4 * t + wave][lane * 4]) = acc[t];
-        if (tid < D) mus[tid] = hv; else yvs[tid - D] = hv;
-        if (tid == 0) oms = om;
-    }
-    __syncthreads();
-
-    if (wave == 0) {   // phase 2 (scalar branch: the block contains MFMAs)
-        f32x4 acc[NSIG], rhs[NB];
-        float y0;
-#pragma unroll
-        for (int t = 0; t < NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&merged[t][lane * 4]);
-#pragma unroll
-        for (int P = 0; P < NB; ++P)        // the solve takes -(Sigma~ + lambda I)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[S128::tix(P, P)][t] -= (nn == 4 * g + t) ? lambda : 0.f;
-        solve_one<NB>(acc, rhs, y0, oms, scw, g, nn, 0.5f * lambda, [&](int P, float &m, float &q, float &e) {
-            m = -mus[16 * P + nn];
-            q = -bf16_to_f32(qg[(size_t)bh * D + 16 * P + nn]);
-            (void)e;
-        });
-        if (nn == 0) {
-#pragma unroll
-            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[P];
-            if (g == 0) ys[D] = y0;
-        }
-    }
-    __syncthreads();
-
-    {   // phase 3
-        const float y0 = ys[D];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int J = 2 * wave + jj;
-            float s = 0.f;
-#pragma unroll
-            for (int I = 0; I < NB; ++I) {
-                const f32x4 gv = *reinterpret_cast<const f32x4 *>(&merged[NSIG + NB * I + J][lane * 4]);
-                const f32x4 y1 = *reinterpret_cast<const f32x4 *>(&ys[16 * I + 4 * g]);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) s = fmaf(gv[t], y1[t], s);      // G~[16I+4g+t][16J+nn] y1[16I+4g+t]
-            }
-            s += __shfl_xor(s, 16);
-            s += __shfl_xor(s, 32);
-            const float o = fmaf(y0, yvs[16 * J + nn], s);
-            if (g == 0) {
-                if (out_bf16) ((bf16_t *)og)[(size_t)bh * D + 16 * J + nn] = f32_to_bf16(o);
-                else ((float *)og)[(size_t)bh * D + 16 * J + nn] = o;
-            }
-        }
-    }
+    });
 }
 
 }  // namespace
@@ -563,31 +462,32 @@ __global__ __launch_bounds__(NT, 1) void decode128_merge_kernel(const bf16_t *__
 size_t mfma_decode128_workspace_bytes(int B, int H, int L_max)
 {
     if (L_max < MIN_L) return 0;
-    const Split s = make_split(B * H, L_max);
-    return round_up((size_t)B * H * s.nsplit * PART_F * sizeof(float), 256);
+    return round_up((size_t)B * H * make_split(B * H, L_max) * REC_F * sizeof(float), 256);
+}
+
+size_t mfma_decode128_flat_bytes(int B, int H, int L_max)
+{
+    if (L_max < MIN_L || B < 2) return 0;
+    return round_up(flat_records(B, H, SLOTS) * REC_F * sizeof(float), 256);
 }
 
 hipError_t mfma_decode128(const Problem &p)
 {
     const int bh = p.B * p.H;
-    const Split s = make_split(bh, p.n);
     PartialArgs a;
     a.qg = (const bf16_t *)p.Q;
     a.Kg = (const bf16_t *)p.K;
     a.Vg = (const bf16_t *)p.V;
     a.sk = p.sk;
     a.sv = p.sv;
-    a.seqlens = p.seqlens;
-    a.H = p.H;
-    a.L_max = p.n;
-    a.nparts = s.nsplit;
+    a.split = choose_split(p, make_split(bh, p.n), p.ws_bytes / (REC_F * sizeof(float)), SLOTS, STEP, KEYS_MIN, MAX_SPLIT);
     a.cscale = p.scale * LOG2E;
     a.parts = static_cast<float *>(p.ws);
+    const HeadOut out{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
     stage_mark(p.stream, "decode_partial");
-    hipLaunchKernelGGL(decode128_partial_kernel, dim3(s.nsplit, bh), dim3(NT), 0, p.stream, a);
+    hipLaunchKernelGGL(decode128_partial_kernel, a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT), 0, p.stream, a);
     stage_mark(p.stream, "decode_merge");
-    hipLaunchKernelGGL(decode128_merge_kernel, dim3(bh), dim3(NT), 0, p.stream, (const bf16_t *)p.Q, (const float *)a.parts,
-                       s.nsplit, p.lambda, p.O, p.out == LLLA_BF16 ? 1 : 0);
+    hipLaunchKernelGGL((decode_merge_kernel<D, bf16_t, false>), dim3(bh), dim3(NT), 0, p.stream, a.split, out, (const float *)a.parts);
     return hipGetLastError();
 }
 

@@ -17,32 +17,27 @@
 // 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
 // wave W owns row blocks W and 7 - W, 25 tiles whatever W; every wave loads the whole rows (the first-level cache serves three
 // of the four) and forms the weights for itself, so there is no exchange at all.
-#include "llla_mfma_common.hpp"
-#include "llla_mfma_solve128.hpp"
+#include "llla_decode_tail.hpp"
 
 namespace llla {
 namespace {
 
 using namespace mfma;
 
-constexpr int NT = 256;
+constexpr int NT = DEC_NT;
 constexpr float REF_SLACK = 8.f;        // the reference exponent moves when a logit exceeds it by more than 2^8 (weights stay <= 256)
 
 template <int D>
-struct F32Shape {
-    static constexpr int NB = D / 16;                     // 16-wide feature blocks = features per lane
-    static constexpr int NSIG = NB * (NB + 1) / 2;
-    static constexpr int NTILES = NSIG + NB * NB;         // Sigma~ (upper) then G~
-    static constexpr int REC_F = 64 + 2 * D + NTILES * 256;   // record: [m, omega, ..], mu~ at 64, sum w v at 64 + D, tiles
-    static constexpr int HDR = 64 + 2 * D;
+struct F32Shape : DecShape<D> {
     static constexpr bool TEAM = D == 128;                // four waves share one key stream
     static constexpr int NC = TEAM ? 2 : 4;               // chunks of four keys whose logits are reduced together
     static constexpr int NG = D == 16 ? 2 : 1;            // such groups per step
     static constexpr int STEP = 4 * NC * NG;              // keys per step
-    static constexpr int NR = TEAM ? 2 : NB;              // row blocks of a wave
+    static constexpr int NR = TEAM ? 2 : D / 16;          // row blocks of a wave
     static constexpr int NBUF = D <= 32 ? 4 : TEAM ? 1 : 2;   // LDS copies of the tiles in the merge of a workgroup's waves
     static constexpr int KEYS_MIN = TEAM ? 128 : 256;     // fewest keys worth a workgroup (its record is read back by the merge)
     static constexpr int SLOTS = D <= 32 ? 1024 : 512;    // workgroups the GPU holds at once
+    static constexpr int MAX_SPLIT = 32;
 };
 
 template <typename TI, int NB>
@@ -123,96 +118,28 @@ __device__ __forceinline__ float wave_max_dpp(float x)    // maximum over the wa
 }
 
 struct F32Args {
-    const void *q, *K, *V;
+    const void *K, *V;
     llla_strides sk, sv;
-    const int32_t *seqlens;
-    int H, L_max, nsplit;
-    float cscale, lambda;
+    DecSplit split;
+    HeadOut out;
+    float cscale;
     float *parts;
-    void *o;
-    int out_bf16;
 };
-
-// LDS of the merge / solve / output phases of one head
-template <int D>
-struct HeadLds {
-    using S = F32Shape<D>;
-    float tiles[S::NBUF][S::NTILES * 256];
-    float mu[S::TEAM ? 1 : 4][D], yv[S::TEAM ? 1 : 4][D];
-    float sc[16 * SC_PITCH];
-    float ys[D + 4];
-    float mw[4], om[4];
-};
-
-// Solve and output of one head whose merged moments lie in lds.tiles[0], lds.mu[0], lds.yv[0], lds.om[0].  Called by all four
-// waves after a barrier.
-template <int D, typename TI>
-__device__ __forceinline__ void solve_and_store(HeadLds<D> &lds, const F32Args &a, int bh, int wave, int lane)
-{
-    using S = F32Shape<D>;
-    constexpr int NB = S::NB;
-    const int g = lane / 16, nn = lane % 16;
-    if (wave == 0) {                                      // scalar branch: the block contains MFMAs
-        f32x4 acc[S::NSIG], rhs[NB];
-        float y0;
-#pragma unroll
-        for (int t = 0; t < S::NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][t * 256 + lane * 4]);
-#pragma unroll
-        for (int P = 0; P < NB; ++P)                      // the solve takes -(Sigma~ + lambda I)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[upper_tile<NB>(P, P)][t] -= (nn == 4 * g + t) ? a.lambda : 0.f;
-        const TI *qp = static_cast<const TI *>(a.q) + (size_t)bh * D;
-        solve_one<NB>(acc, rhs, y0, lds.om[0], lds.sc, g, nn, 0.5f * a.lambda, [&](int P, float &m, float &q, float &e) {
-            m = -lds.mu[0][16 * P + nn];
-            const TI v = qp[NB * nn + P];
-            if constexpr (sizeof(TI) == 2) q = -bf16_to_f32(v);
-            else q = -v;
-            (void)e;
-        });
-        if (nn == 0) {
-#pragma unroll
-            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&lds.ys[16 * P + 4 * g]) = rhs[P];
-            if (g == 0) lds.ys[D] = y0;
-        }
-    }
-    __syncthreads();
-    const float y0 = lds.ys[D];
-    for (int J = wave; J < NB; J += 4) {
-        float s = 0.f;
-#pragma unroll
-        for (int I = 0; I < NB; ++I) {
-            const f32x4 gv = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * I + J) * 256 + lane * 4]);
-            const f32x4 y1 = *reinterpret_cast<const f32x4 *>(&lds.ys[16 * I + 4 * g]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) s = fmaf(gv[t], y1[t], s);        // G~[16I+4g+t][16J+nn] y1[16I+4g+t]
-        }
-        s = rows_allsum(s);
-        const float o = fmaf(y0, lds.yv[0][16 * J + nn], s);
-        if (g == 0) {
-            const size_t at = (size_t)bh * D + NB * nn + J;
-            if (a.out_bf16) static_cast<bf16_t *>(a.o)[at] = f32_to_bf16(o);
-            else static_cast<float *>(a.o)[at] = o;
-        }
-    }
-}
 
 // The stream of one wave and what becomes of its moments.  W: the wave's share of the tiles (TEAM), else 0.
 // FUSED: one workgroup per head; it solves and writes the output itself.
-template <int D, typename TI, bool FUSED, int W>
-__device__ __forceinline__ void decode_f32_body(const F32Args &a, HeadLds<D> &lds, int wave, int lane)
+template <int D, typename TI, bool FUSED, int W, class Lds>
+__device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece &pc, Lds &lds, int wave, int lane)
 {
     using S = F32Shape<D>;
     constexpr int NB = S::NB, NC = S::NC, NG = S::NG, NR = S::NR, STEP = S::STEP, CH = NC * NG;
     constexpr int row[4] = {S::TEAM ? W : 0, S::TEAM ? 7 - W : 1, 2, 3};      // row blocks of this wave: row[0..NR-1]
     const int g = lane / 16, nn = lane % 16;
-    const int bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
-    // the sequence's own length is divided over the streams of its head; rows at and beyond it are never read
-    const int L = a.seqlens ? min(max(a.seqlens[b], 1), a.L_max) : a.L_max;
-    const int nstream = S::TEAM ? a.nsplit : 4 * a.nsplit;
-    const int stream = S::TEAM ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
-    const int share = ((L + nstream - 1) / nstream + STEP - 1) / STEP * STEP;
-    const int r0 = __builtin_amdgcn_readfirstlane(min(stream * share, L));
-    const int r1 = __builtin_amdgcn_readfirstlane(min(r0 + share, L));
+    // the piece is divided over the four waves (TEAM: walked by all four together); rows at and beyond L are never read
+    const int L = pc.L, b = pc.b, h = pc.h, bh = pc.bh;
+    const int share = S::TEAM ? pc.k1 - pc.k0 : ((pc.k1 - pc.k0 + 3) / 4 + STEP - 1) / STEP * STEP;
+    const int r0 = __builtin_amdgcn_readfirstlane(min(pc.k0 + (S::TEAM ? 0 : wave * share), pc.k1));
+    const int r1 = __builtin_amdgcn_readfirstlane(min(r0 + share, pc.k1));
     const int nsteps = (r1 - r0 + STEP - 1) / STEP;
     const char *Kh = reinterpret_cast<const char *>(static_cast<const TI *>(a.K) + b * a.sk.batch + h * a.sk.head);
     const char *Vh = reinterpret_cast<const char *>(static_cast<const TI *>(a.V) + b * a.sv.batch + h * a.sv.head);
@@ -221,7 +148,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, HeadLds<D> &ld
 
     float q[NB];
     {
-        const TI *qp = static_cast<const TI *>(a.q) + (size_t)bh * D + NB * nn;
+        const TI *qp = static_cast<const TI *>(a.out.q) + (size_t)bh * D + NB * nn;
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             if constexpr (sizeof(TI) == 2) q[i] = bf16_to_f32(qp[i]) * a.cscale;
@@ -229,14 +156,21 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, HeadLds<D> &ld
         }
     }
 
-    f32x4 sig[NR][NB], gt[NR][NB];                        // sig[i][J]: J >= row[i] only
+    f32x4 acc[S::NTILES];                                 // (TEAM: the tiles of row blocks row[0] and row[1] only)
     float mu[NR], yv[NR];
 #pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        mu[i] = 0.f; yv[i] = 0.f;
+    for (int t = 0; t < S::NTILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int J = 0; J < NB; ++J) { sig[i][J] = f32x4{0.f, 0.f, 0.f, 0.f}; gt[i][J] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    }
+    for (int i = 0; i < NR; ++i) { mu[i] = 0.f; yv[i] = 0.f; }
+    auto for_tiles = [&](auto fn) {                       // the tiles of this wave
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+#pragma unroll
+            for (int J = row[i]; J < NB; ++J) fn(upper_tile<NB>(row[i], J));
+#pragma unroll
+            for (int J = 0; J < NB; ++J) fn(S::NSIG + NB * row[i] + J);
+        }
+    };
     float om = 0.f, mref = -INFINITY, mtrue = -INFINITY;
 
     typedef RowFrag<TI, NB> Frag;
@@ -279,11 +213,8 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, HeadLds<D> &ld
                 mref = mnew;
                 om *= alpha;
 #pragma unroll
-                for (int i = 0; i < NR; ++i) {
-                    mu[i] *= alpha; yv[i] *= alpha;
-#pragma unroll
-                    for (int J = 0; J < NB; ++J) { if (J >= row[i]) sig[i][J] *= alpha; gt[i][J] *= alpha; }
-                }
+                for (int i = 0; i < NR; ++i) { mu[i] *= alpha; yv[i] *= alpha; }
+                for_tiles([&](int t) { acc[t] *= alpha; });
             }
             mtrue = fmaxf(mtrue, t);
             const float w = __builtin_amdgcn_exp2f(t - mref);         // exp2(-inf) = 0 masks the tail
@@ -301,10 +232,15 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, HeadLds<D> &ld
                     mu[i] += wk;
                     yv[i] = fmaf(wc, vx[row[i]], yv[i]);
 #pragma unroll
-                    for (int J = 0; J < NB; ++J)
-                        if (J >= row[i]) sig[i][J] = __builtin_amdgcn_mfma_f32_16x16x4f32(wk, kx[J], sig[i][J], 0, 0, 0);
+                    for (int J = row[i]; J < NB; ++J) {
+                        f32x4 &t = acc[upper_tile<NB>(row[i], J)];
+                        t = __builtin_amdgcn_mfma_f32_16x16x4f32(wk, kx[J], t, 0, 0, 0);
+                    }
 #pragma unroll
-                    for (int J = 0; J < NB; ++J) gt[i][J] = __builtin_amdgcn_mfma_f32_16x16x4f32(wk, vx[J], gt[i][J], 0, 0, 0);
+                    for (int J = 0; J < NB; ++J) {
+                        f32x4 &t = acc[S::NSIG + NB * row[i] + J];
+                        t = __builtin_amdgcn_mfma_f32_16x16x4f32(wk, vx[J], t, 0, 0, 0);
+                    }
                 }
             };
             chunk(std::integral_constant<int, 0>{});
@@ -326,160 +262,58 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, HeadLds<D> &ld
         }
     }
 
-    // ---- the wave's moments relative to its true maximum (TEAM) or the workgroup's ---------------------------------------
     mtrue = wave_max_dpp(mtrue);
     om += dpp_f<0xB1>(om);
     if constexpr (NC == 4) om += dpp_f<0x4E>(om);
     om = rows_allsum(om);
-    float mall = mtrue;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) { mu[i] = rows_allsum(mu[i]); yv[i] = rows_allsum(yv[i]); }
+    float *R = a.parts + (size_t)pc.rec * S::REC_F;       // this workgroup's record (not FUSED)
     if constexpr (!S::TEAM) {
-        if (lane == 0) lds.mw[wave] = mtrue;
-        __syncthreads();
-        mall = fmaxf(fmaxf(lds.mw[0], lds.mw[1]), fmaxf(lds.mw[2], lds.mw[3]));
-    }
-    const float f = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - mall);
-    om *= f;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        mu[i] = rows_allsum(mu[i]) * f;
-        yv[i] = rows_allsum(yv[i]) * f;
-#pragma unroll
-        for (int J = 0; J < NB; ++J) { if (J >= row[i]) sig[i][J] *= f; gt[i][J] *= f; }
-    }
-    float *R = a.parts + ((size_t)bh * a.nsplit + blockIdx.x) * S::REC_F;      // this workgroup's record (not FUSED)
-
-    if constexpr (S::TEAM) {
-        float *tiles = FUSED ? lds.tiles[0] : R + S::HDR;
-        float *mud = FUSED ? lds.mu[0] : R + 64, *yvd = FUSED ? lds.yv[0] : R + 64 + D;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            if (g == 0) { mud[16 * row[i] + nn] = mu[i]; yvd[16 * row[i] + nn] = yv[i]; }
-#pragma unroll
-            for (int J = 0; J < NB; ++J) {
-                if (J >= row[i]) *reinterpret_cast<f32x4 *>(tiles + upper_tile<NB>(row[i], J) * 256 + lane * 4) = sig[i][J];
-                *reinterpret_cast<f32x4 *>(tiles + (S::NSIG + NB * row[i] + J) * 256 + lane * 4) = gt[i][J];
-            }
-        }
-        if (W == 0 && lane == 0) {
-            if (FUSED) lds.om[0] = om;
-            else { R[0] = mall; R[1] = om; }
-        }
-        if constexpr (FUSED) __syncthreads();
-    } else {
-        // sum over the four waves through LDS, in a fixed order: NBUF copies of the tiles, then the sum of the copies
-        auto put = [&](float *dst, bool add) {
-#pragma unroll
-            for (int i = 0; i < NR; ++i)
-#pragma unroll
-                for (int J = 0; J < NB; ++J) {
-                    if (J >= row[i]) {
-                        f32x4 *p = reinterpret_cast<f32x4 *>(dst + upper_tile<NB>(row[i], J) * 256 + lane * 4);
-                        *p = add ? *p + sig[i][J] : sig[i][J];
-                    }
-                    f32x4 *p = reinterpret_cast<f32x4 *>(dst + (S::NSIG + NB * row[i] + J) * 256 + lane * 4);
-                    *p = add ? *p + gt[i][J] : gt[i][J];
-                }
-        };
+        finish_workgroup<D, TI, true, FUSED, S::NBUF>(lds, acc, mu, yv, om, mref, mtrue, R, a.out, bh, wave, lane);
+    } else {                                              // every wave's own tiles, relative to the true maximum
+        const float f = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - mtrue);
+        float *tiles, *mud, *yvd;
+        if constexpr (FUSED) { tiles = lds.tiles[0]; mud = lds.mu[0]; yvd = lds.yv[0]; }
+        else { tiles = R + S::HDR; mud = R + 64; yvd = R + 64 + D; }
+        for_tiles([&](int t) { *reinterpret_cast<f32x4 *>(tiles + t * 256 + lane * 4) = f * acc[t]; });
         if (g == 0) {
 #pragma unroll
-            for (int i = 0; i < NR; ++i) { lds.mu[wave][16 * row[i] + nn] = mu[i]; lds.yv[wave][16 * row[i] + nn] = yv[i]; }
+            for (int i = 0; i < NR; ++i) { mud[16 * row[i] + nn] = f * mu[i]; yvd[16 * row[i] + nn] = f * yv[i]; }
         }
-        if (lane == 0) lds.om[wave] = om;
-        if (wave < S::NBUF) put(lds.tiles[wave < S::NBUF ? wave : 0], false);
-        __syncthreads();
-        if constexpr (S::NBUF == 2) {
-            if (wave >= 2) put(lds.tiles[wave - 2], true);
+        if (W == 0 && lane == 0) {
+            if constexpr (FUSED) lds.om[0] = f * om;
+            else { R[0] = mtrue; R[1] = f * om; }
+        }
+        if constexpr (FUSED) {
             __syncthreads();
+            solve_and_store<D, TI, true>(lds, a.out, bh, wave, lane);
         }
-        const int tid = wave * 64 + lane;
-        for (int i = tid; i < S::NTILES * 64; i += NT) {
-            f32x4 v = reinterpret_cast<const f32x4 *>(lds.tiles[0])[i];
-#pragma unroll
-            for (int bf = 1; bf < S::NBUF; ++bf) v += reinterpret_cast<const f32x4 *>(lds.tiles[bf])[i];
-            if constexpr (FUSED) reinterpret_cast<f32x4 *>(lds.tiles[0])[i] = v;
-            else *reinterpret_cast<f32x4 *>(R + S::HDR + 4 * i) = v;
-        }
-        if (tid < 2 * D) {
-            float *src = tid < D ? &lds.mu[0][tid] : &lds.yv[0][tid - D];
-            const float v = (src[0] + src[D]) + (src[2 * D] + src[3 * D]);
-            if constexpr (FUSED) src[0] = v;
-            else R[64 + tid] = v;
-        }
-        const float oall = (lds.om[0] + lds.om[1]) + (lds.om[2] + lds.om[3]);
-        if constexpr (FUSED) __syncthreads();
-        if (tid == 0) {
-            if constexpr (FUSED) lds.om[0] = oall;
-            else { R[0] = mall; R[1] = oall; }
-        }
-        if constexpr (FUSED) __syncthreads();
     }
-    if constexpr (FUSED) solve_and_store<D, TI>(lds, a, bh, wave, lane);
 }
 
 template <int D, typename TI, bool FUSED>
 __global__ __launch_bounds__(NT, D <= 32 ? 4 : D == 128 && FUSED ? 1 : 2) void decode_f32_kernel(F32Args a)
 {
-    // (the waves of a team write their own parts of the record: only the merge of a head needs the tiles in LDS)
-    __shared__ __align__(16) unsigned char lds_raw[F32Shape<D>::TEAM && !FUSED ? 16 : sizeof(HeadLds<D>)];
-    HeadLds<D> &lds = *reinterpret_cast<HeadLds<D> *>(lds_raw);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-    if constexpr (F32Shape<D>::TEAM) {                    // scalar branches; all four waves meet at the same barriers
-        if (wave == 0) decode_f32_body<D, TI, FUSED, 0>(a, lds, wave, lane);
-        else if (wave == 1) decode_f32_body<D, TI, FUSED, 1>(a, lds, wave, lane);
-        else if (wave == 2) decode_f32_body<D, TI, FUSED, 2>(a, lds, wave, lane);
-        else decode_f32_body<D, TI, FUSED, 3>(a, lds, wave, lane);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    using S = F32Shape<D>;
+    if constexpr (S::TEAM) {                              // scalar branches; all four waves meet at the same barriers
+        // (the waves of a team write their own parts of the record: only the solve needs the tiles in LDS)
+        __shared__ __align__(16) unsigned char raw[FUSED ? sizeof(HeadLds<D, 1, 1>) : 16];
+        HeadLds<D, 1, 1> &lds = *reinterpret_cast<HeadLds<D, 1, 1> *>(raw);
+        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) {
+            if (wave == 0) decode_f32_body<D, TI, FUSED, 0>(a, pc, lds, wave, piece_lane());
+            else if (wave == 1) decode_f32_body<D, TI, FUSED, 1>(a, pc, lds, wave, piece_lane());
+            else if (wave == 2) decode_f32_body<D, TI, FUSED, 2>(a, pc, lds, wave, piece_lane());
+            else decode_f32_body<D, TI, FUSED, 3>(a, pc, lds, wave, piece_lane());
+        });
     } else {
-        decode_f32_body<D, TI, FUSED, 0>(a, lds, wave, lane);
+        __shared__ __align__(16) HeadLds<D, S::NBUF, 4> lds;
+        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, 0>(a, pc, lds, wave, piece_lane()); });
     }
 }
 
-// Merge of a head's records (max-rescaled sum), solve, output: one head per workgroup.
-template <int D, typename TI>
-__global__ __launch_bounds__(NT, 1) void decode_f32_merge_kernel(F32Args a)
-{
-    using S = F32Shape<D>;
-    __shared__ __align__(16) HeadLds<D> lds;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, bh = blockIdx.x;
-    const float *P0 = a.parts + (size_t)bh * a.nsplit * S::REC_F;
-    constexpr int PG = 8;                                 // records fetched together
-    const float mstar = wave_max_strided(P0, 0, a.nsplit, S::REC_F, lane);
-    auto factor = [&](int p) {
-        const float m = P0[(size_t)min(p, a.nsplit - 1) * S::REC_F];
-        return (p >= a.nsplit || m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mstar);
-    };
-    constexpr int N4 = (S::NTILES * 64 + NT - 1) / NT;
-    f32x4 acc[N4];
-#pragma unroll
-    for (int i = 0; i < N4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float hv = 0.f, om = 0.f;
-    for (int pb = 0; pb < a.nsplit; pb += PG) {
-        float fk[PG];
-#pragma unroll
-        for (int k = 0; k < PG; ++k) fk[k] = factor(pb + k);
-#pragma unroll
-        for (int k = 0; k < PG; ++k) {
-            const float *P = P0 + (size_t)min(pb + k, a.nsplit - 1) * S::REC_F;      // past the end: factor 0
-            om = fmaf(fk[k], P[1], om);
-            if (tid < 2 * D) hv = fmaf(fk[k], P[64 + tid], hv);
-        }
-#pragma unroll
-        for (int i = 0; i < N4; ++i) {
-            const int at = min(tid + NT * i, S::NTILES * 64 - 1);
-#pragma unroll
-            for (int k = 0; k < PG; ++k) {
-                const float *P = P0 + (size_t)min(pb + k, a.nsplit - 1) * S::REC_F;
-                acc[i] += fk[k] * *reinterpret_cast<const f32x4 *>(P + S::HDR + 4 * at);
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < N4; ++i)
-        if (tid + NT * i < S::NTILES * 64) reinterpret_cast<f32x4 *>(lds.tiles[0])[tid + NT * i] = acc[i];
-    if (tid < 2 * D) (tid < D ? lds.mu[0] : lds.yv[0])[tid & (D - 1)] = hv;
-    if (tid == 0) lds.om[0] = om;
-    __syncthreads();
-    solve_and_store<D, TI>(lds, a, bh, wave, lane);
-}
+constexpr size_t MAX_RECORD_BYTES = (size_t)64 << 20;     // what llla_decode_static can hold
 
 // Workgroups per head.  Rounds of the GPU's slots times the keys of a workgroup is the time of the pass; a further workgroup per
 // head only pays where it shortens that by more than its record costs (about KEYS_MIN / 4 keys' worth of time).
@@ -489,7 +323,7 @@ int f32_nsplit(int bh, int L, size_t ws_bytes)
     using S = F32Shape<D>;
     int best = 1;
     double best_cost = 1e300;
-    for (int ns = 1; ns <= 32; ++ns) {
+    for (int ns = 1; ns <= S::MAX_SPLIT; ++ns) {
         if (ns > 1 && ((L + ns - 1) / ns < S::KEYS_MIN || (size_t)bh * ns * S::REC_F * sizeof(float) > ws_bytes)) break;
         const double rounds = (double)(((long long)bh * ns + S::SLOTS - 1) / S::SLOTS);
         const double cost = rounds * ((double)L / ns + S::KEYS_MIN / 4) + (ns > 1 ? S::KEYS_MIN / 8 * ns : 0);
@@ -498,40 +332,46 @@ int f32_nsplit(int bh, int L, size_t ws_bytes)
     return best;
 }
 
-constexpr size_t MAX_RECORD_BYTES = (size_t)64 << 20;     // what llla_decode_static can hold
+// Records that the scratch has room for: the even cut's or the flat one's, whichever is more, where that is useful and fits
+template <int D>
+size_t f32_records(int B, int H, int L)
+{
+    using S = F32Shape<D>;
+    const int ns = f32_nsplit<D>(B * H, L, MAX_RECORD_BYTES);
+    size_t n = ns > 1 ? (size_t)B * H * ns : 0;
+    const size_t flat = flat_records(B, H, S::SLOTS);
+    if (B >= 2 && L > S::KEYS_MIN && flat * S::REC_F * sizeof(float) <= MAX_RECORD_BYTES) n = std::max(n, flat);
+    return n;
+}
 
 template <int D>
-size_t f32_workspace(int bh, int L)
-{
-    const int ns = f32_nsplit<D>(bh, L, MAX_RECORD_BYTES);
-    return ns > 1 ? round_up((size_t)bh * ns * F32Shape<D>::REC_F * sizeof(float), 256) : 0;
-}
+size_t f32_workspace(int B, int H, int L) { return round_up(f32_records<D>(B, H, L) * F32Shape<D>::REC_F * sizeof(float), 256); }
 
 template <int D, typename TI>
 hipError_t f32_launch(const Problem &p)
 {
+    using S = F32Shape<D>;
     const int bh = p.B * p.H;
     F32Args a;
-    a.q = p.Q; a.K = p.K; a.V = p.V;
+    a.K = p.K; a.V = p.V;
     a.sk = p.sk; a.sv = p.sv;
-    a.seqlens = p.seqlens;
-    a.H = p.H; a.L_max = p.n;
     // a caller without the scratch that the records need gets one workgroup per head
-    a.nsplit = f32_nsplit<D>(bh, p.n, p.ws != nullptr && (reinterpret_cast<uintptr_t>(p.ws) & 255u) == 0
-                                          ? (p.ws_bytes < MAX_RECORD_BYTES ? p.ws_bytes : MAX_RECORD_BYTES) : 0);
+    const size_t records = f32_records<D>(p.B, p.H, p.n);
+    const bool scratch = p.ws != nullptr && (reinterpret_cast<uintptr_t>(p.ws) & 255u) == 0 && p.ws_bytes >= records * S::REC_F * sizeof(float);
+    a.split = choose_split(p, scratch ? f32_nsplit<D>(bh, p.n, MAX_RECORD_BYTES) : 1, scratch ? records : 0, S::SLOTS, 4 * S::STEP,
+                           S::KEYS_MIN, S::MAX_SPLIT);
+    a.out = HeadOut{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
     a.cscale = p.scale * LOG2E;
-    a.lambda = p.lambda;
     a.parts = static_cast<float *>(p.ws);
-    a.o = p.O;
-    a.out_bf16 = p.out == LLLA_BF16 ? 1 : 0;
-    if (a.nsplit == 1) {
+    if (a.split.nsplit == 1 && a.split.slots == 0) {
         stage_mark(p.stream, "decode_f32");
         hipLaunchKernelGGL((decode_f32_kernel<D, TI, true>), dim3(1, bh), dim3(NT), 0, p.stream, a);
     } else {
         stage_mark(p.stream, "decode_partial");
-        hipLaunchKernelGGL((decode_f32_kernel<D, TI, false>), dim3(a.nsplit, bh), dim3(NT), 0, p.stream, a);
+        hipLaunchKernelGGL((decode_f32_kernel<D, TI, false>), a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT),
+                           0, p.stream, a);
         stage_mark(p.stream, "decode_merge");
-        hipLaunchKernelGGL((decode_f32_merge_kernel<D, TI>), dim3(bh), dim3(NT), 0, p.stream, a);
+        hipLaunchKernelGGL((decode_merge_kernel<D, TI, true>), dim3(bh), dim3(NT), 0, p.stream, a.split, a.out, (const float *)a.parts);
     }
     return hipGetLastError();
 }
@@ -546,12 +386,11 @@ hipError_t f32_by_dtype(const Problem &p)
 
 size_t mfma_decode_f32_workspace_bytes(int B, int H, int L_max, int d)
 {
-    const int bh = B * H;
     switch (d) {
-        case 16: return f32_workspace<16>(bh, L_max);
-        case 32: return f32_workspace<32>(bh, L_max);
-        case 64: return f32_workspace<64>(bh, L_max);
-        case 128: return f32_workspace<128>(bh, L_max);
+        case 16: return f32_workspace<16>(B, H, L_max);
+        case 32: return f32_workspace<32>(B, H, L_max);
+        case 64: return f32_workspace<64>(B, H, L_max);
+        case 128: return f32_workspace<128>(B, H, L_max);
         default: return 0;
     }
 }

@@ -33,22 +33,27 @@ void *scratch_on_current_device()
     return g_scratch_ptr[dev];
 }
 
+bool shape_ok(int B, int H, int L_max, int d, llla_dtype in)
+{
+    return B > 0 && H > 0 && L_max > 0 && (d == 16 || d == 32 || d == 64 || d == 128) && (in == LLLA_F32 || in == LLLA_BF16);
+}
+
 }  // namespace
 
 extern "C" llla_status llla_decode_static(const void *q, const void *Kc, const void *Vc, void *o, llla_strides sk,
                                           llla_strides sv, const int32_t *seqlens, int B, int H, int L_max, int d,
                                           llla_dtype in, llla_dtype out, float lambda, float scale, void *stream)
 {
-    // what llla_decode would ask of a workspace for this call (0 for shapes the vector kernels serve, and for bad
-    // shapes, which the call below then refuses with their own status)
-    const size_t need = llla_decode_workspace_bytes(B, H, L_max, d, in);
+    // what llla_decode must have for this call (0 for bad shapes, which the call below refuses with their own status); the
+    // fp32 kernels and the cut for sequences of different lengths take what is there
+    const size_t need = shape_ok(B, H, L_max, d, in) ? llla::mfma_decode_workspace_bytes(B, H, L_max, d, in) : 0;
     if (need > kScratchBytes) return LLLA_ERR_WORKSPACE;
     void *ptr = nullptr;
-    if (need > 0) {
+    if (shape_ok(B, H, L_max, d, in) && llla_decode_workspace_bytes(B, H, L_max, d, in) > 0) {
         ptr = scratch_on_current_device();
         if (ptr == nullptr) return LLLA_ERR_LAUNCH;
     }
     // nothing in the records has to start at zero: every record a call reads is written by that call first
-    return llla_decode(q, Kc, Vc, o, sk, sv, seqlens, B, H, L_max, d, in, out, lambda, scale, ptr, need ? kScratchBytes : 0,
+    return llla_decode(q, Kc, Vc, o, sk, sv, seqlens, B, H, L_max, d, in, out, lambda, scale, ptr, ptr ? kScratchBytes : 0,
                        stream);
 }
