@@ -193,7 +193,7 @@ llla_status llla_forward_cg(const void *Q, const void *K, const void *V, void *O
 size_t llla_backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in)
 {
     if (B <= 0 || H <= 0 || n <= 0 || !dim_supported(d) || !dtype_ok(in)) return 0;
-    const size_t a = llla::backward_workspace_bytes(B, H, n, d, in, LLLA_PATH_AUTO);
+    const size_t a = llla::backward_wanted_bytes(B, H, n, d, in);
     const size_t b = llla::padded_backward_workspace_bytes(B, H, n, d, in);
     return a > b ? a : b;
 }

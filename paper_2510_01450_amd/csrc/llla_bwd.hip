@@ -745,13 +745,24 @@ size_t backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in, llla_
     return path == LLLA_PATH_MFMA ? m : (m > v ? m : v);
 }
 
+size_t backward_wanted_bytes(int B, int H, int n, int d, llla_dtype in)
+{
+    const size_t need = backward_workspace_bytes(B, H, n, d, in, LLLA_PATH_AUTO);
+    const size_t f = mfma_backward_f32_supported(n, d, in) ? mfma_backward_f32_workspace_bytes(B, H, n, d) : 0;
+    return f > need ? f : need;
+}
+
 hipError_t backward(const BackwardProblem &p, llla_path path)
 {
     // the matrix-core sweeps put their 64-row blocks on grid.y (at most 65535 of them, i.e. n <= 4 194 240)
     const bool use_mfma = path != LLLA_PATH_VALU && mfma_forward_supported(p.d, p.in, true) && (p.n + 63) / 64 <= 65535;
     stage_begin(p.stream);
     hipError_t err;
-    if (!use_mfma) err = valu_backward(p);
+    // fp32, d = 64: the vector kernels only on request, or where the caller brought no more workspace than they need
+    const bool use_f32 = path == LLLA_PATH_AUTO && mfma_backward_f32_supported(p.n, p.d, p.in) &&
+                         p.ws_bytes >= mfma_backward_f32_workspace_bytes(p.B, p.H, p.n, p.d);
+    if (use_f32) err = mfma_backward_f32(p);
+    else if (!use_mfma) err = valu_backward(p);
     else err = launch_backward_mfma(p);
     stage_end(p.stream);
     return err;

@@ -76,7 +76,14 @@ hipError_t mfma_backward_solve(const BackwardProblem &p, const BackwardLayout &L
 hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int first_row);   // r rows, argmax; rows >= first_row
 hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int first_row);  // dQ, dlambda, row scalars; rows >= first_row
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
-size_t backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in, llla_path path);
+// the same for fp32 inputs (d = 64): fp32 matrix cores throughout (llla_mfma_bwd_f32.hip); its moments kernel is the
+// forward's, with the row maxima M given and the rows r replaced by u
+bool mfma_backward_f32_supported(int n, int d, llla_dtype in);
+size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d);
+hipError_t mfma_backward_f32(const BackwardProblem &p);
+hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU);
+size_t backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in, llla_path path);     // what a call must have
+size_t backward_wanted_bytes(int B, int H, int n, int d, llla_dtype in);                        // and what it can make use of
 hipError_t backward(const BackwardProblem &p, llla_path path);
 
 // MFMA (matrix-core) paths; *_supported() says whether one exists for the shape and dtype.

@@ -1,0 +1,437 @@
+// Matrix-core backward pass for fp32 inputs, d = 64: every contraction on v_mfma_f32_16x16x4_f32, fp32 operands and fp32
+// accumulation, so the accuracy is that of the vector kernels of llla_bwd.hip (whose notation is used here).
+//
+//   r sweep   r_i = sum_j w_ij gamma_ij [1; k_j], the row maximum m_i and the first key that attains it;
+//   moments   the forward's fp32 moments kernel with m_i given and a second right-hand side in its solve: y_i and u_i;
+//   dQ sweep  p^_ij, dQ_i, dlambda_i and the scalars of row i that the key sweep reads;
+//   key sweep dK_j, dV_j.
+//
+// What bounds it: the fp32 matrix rate (1/16 of the 16-bit one).  A tile of 16 queries x 16 keys costs 48 + 656 + 80 + 128
+// MFMAs of 32 cycles in the four stages, and the factorisations come on top.  The vector kernels spend d^2 multiply-adds per
+// pair on the vector ALU, at less than half the matrix rate and out of LDS, and eliminate a (d+1)^2 system with one barrier
+// per pivot.  16 heads x 1024 rows: 2811 us on the vector kernels, 727 here; 2 x 128: 207 and 82; 4 x 2000: 2637 and 1096.
+//
+// The three sweeps share one shape: 32 rows per workgroup, four waves = 2 groups of 16 rows x 2 halves of every 32-row step
+// of the other side, the halves' sums added through LDS at the end.  (64 rows per workgroup without the split leave a
+// 1024-row head with 16 workgroups whose longest is twice the mean.)  Tiles arrive by DMA one step ahead, two buffers, one
+// barrier per step; 16-byte chunks are XOR-swizzled with the row, so that rows are read 16 bytes per lane (operand with the
+// features as contraction index) and columns 4 bytes per lane (operand with the rows as contraction index) from one copy.
+#include "llla_mfma_common.hpp"
+
+namespace llla {
+namespace {
+
+using namespace mfma;
+
+constexpr int RT = 32;                 // rows per workgroup and rows per step
+constexpr float LAZY_BITS = 64.f;      // as in the forward: the reference exponent moves when a tile exceeds it by more
+
+// 32 rows of DD floats -> LDS, chunk c of row r at c ^ (r & 7); rows past `last` repeat it
+template <int DD>
+__device__ inline void dma_tile(const float *src, int64_t pitch, int row0, int last, float *dst, int wave, int lane)
+{
+    constexpr int CH = DD / 4, RPT = 64 / CH, NTR = RT / RPT / 4;     // 16-byte chunks per row, rows and number of a wave's transfers
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
+        const int r0 = (wave * NTR + t) * RPT, row = r0 + lane / CH;
+        const int j = min(row0 + row, last);
+        dma16(src + (int64_t)j * pitch + 4 * ((lane % CH) ^ (row & 7)), dst + r0 * DD);
+    }
+}
+
+// C += T R^T over the features: T = 16 rows of a tile (tile row nn of the lane), R = a row per lane in registers; contraction
+// slot (s, g) stands for feature DD/4 g + s on both sides
+template <int DD>
+__device__ inline f32x4 row_chunk(const float *trow, int g, int v, int nn)
+{
+    return *reinterpret_cast<const f32x4 *>(trow + 4 * ((DD / 16 * g + v) ^ (nn & 7)));
+}
+
+template <int DD>
+__device__ inline void load_row(const float *row, int g, float (&x)[DD / 4])
+{
+#pragma unroll
+    for (int v = 0; v < DD / 16; ++v) {
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(row + DD / 4 * g + 4 * v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * v + e] = a[e];
+    }
+}
+
+// ---- row sweeps ---------------------------------------------------------------------------------------------
+// MODE 0: the r sweep; MODE 1: the dQ sweep.  S^T = K Q^T and the like come out as (lane (g, nn): keys 4g + r, query nn),
+// which is the A operand of the product that contracts over keys when slot g of step r stands for key 4g + r.
+template <int DD, int MODE>
+__global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
+    const float *__restrict__ Qg, const float *__restrict__ Kg, const float *__restrict__ Vg, const float *__restrict__ Gg,
+    llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n, int npad, float scale, float lambda,
+    const float *__restrict__ LamRows, float *__restrict__ Mg, const float *__restrict__ Yg, const float *Ug, float *Rv,
+    float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam)
+{
+    constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = Shape<DD>::YP, RP = DD + 4;
+    __shared__ __align__(16) float tiles[2][2][RT * DD];
+    __shared__ float rbest[4][16], rref[4][16], rsum[4][16];
+    __shared__ int rarg[4][16];
+    static_assert(4 * 16 * RP <= 4 * RT * DD, "the final sums reuse the tiles");
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
+    const int rg = wave & 1, ks = wave >> 1;
+    // head on blockIdx.x (dispatched fastest), row block on y, longest rows first
+    const int bh = blockIdx.x, b = bh / H, h = bh % H;
+    const int i0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * RT;
+    const int iq = min(i0 + 16 * rg + nn, n - 1);           // rows past the end repeat the last one and are not stored
+    const int wlast = min(i0 + 16 * rg + 15, n - 1);
+    const size_t row = (size_t)bh * n + iq;
+    const float *Kh = Kg + b * sk.batch + h * sk.head;
+    const float *Vh = Vg + b * sv.batch + h * sv.head;
+    const float cscale = scale * LOG2E;
+
+    float qr[NS], gr[NS], yr[MODE ? NS : 1], ur[MODE ? NS : 1];
+    load_row<DD>(Qg + b * sq.batch + h * sq.head + (int64_t)iq * sq.seq, g, qr);
+    load_row<DD>(Gg + b * sg.batch + h * sg.head + (int64_t)iq * sg.seq, g, gr);
+    float mh = -INFINITY, y0 = 0.f, u0 = 0.f, corr = 0.f;
+    int jstar = 0;
+    if constexpr (MODE == 1) {
+        load_row<DD>(Yg + row * YP, g, yr);
+        load_row<DD>(Ug + row * YP, g, ur);
+        y0 = Yg[row * YP + DD];
+        u0 = Ug[row * YP + DD];
+        jstar = __float_as_int(Ug[row * YP + DD + 1]);
+        mh = Mg[(size_t)bh * npad + iq];
+        float dl = 0.f;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) dl = fmaf(-ur[s], yr[s], dl);
+        dl += __shfl_xor(dl, 16);
+        dl += __shfl_xor(dl, 32);
+        corr = (LamRows ? LamRows[row] : lambda) * dl;
+        if (ks == 0 && g == 0 && i0 + 16 * rg + nn < n) {
+            float *sc = Sc + row * 8;
+            *reinterpret_cast<f32x4 *>(sc) = f32x4{y0, u0, mh, corr};
+            sc[4] = __int_as_float(jstar);
+            if (dLam) dLam[row] = dl;
+        }
+    }
+    f32x4 acc[NB];
+#pragma unroll
+    for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float csum = 0.f, best = -INFINITY;
+    int arg = 0;
+
+    const int nblk = min(i0 + RT - 1, n - 1) / RT + 1;
+    auto issue = [&](int c) {
+        dma_tile<DD>(Kh, sk.seq, c * RT, n - 1, tiles[c & 1][0], wave, lane);
+        dma_tile<DD>(Vh, sv.seq, c * RT, n - 1, tiles[c & 1][1], wave, lane);
+    };
+    issue(0);
+    for (int c = 0; c < nblk; ++c) {
+        dma_wait();
+        __syncthreads();                                     // step c has arrived, step c - 1 is consumed
+        if (c + 1 < nblk) issue(c + 1);
+        const int jb = c * RT + 16 * ks;
+        if (jb > wlast) continue;                            // no query of this wave sees these keys
+        const float *kt = &tiles[c & 1][0][16 * ks * DD], *vt = &tiles[c & 1][1][16 * ks * DD];
+        f32x4 z = {0.f, 0.f, 0.f, 0.f}, gm = z, at = {y0, y0, y0, y0}, bt = {u0, u0, u0, u0};
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const f32x4 kv = row_chunk<DD>(kt + nn * DD, g, v, nn), vv = row_chunk<DD>(vt + nn * DD, g, v, nn);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qr[4 * v + e], z, 0, 0, 0);
+                gm = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], gr[4 * v + e], gm, 0, 0, 0);
+                if constexpr (MODE == 1) {
+                    at = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], yr[4 * v + e], at, 0, 0, 0);
+                    bt = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], ur[4 * v + e], bt, 0, 0, 0);
+                }
+            }
+        }
+        float zs[4], cf[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) zs[r] = z[r] * cscale;
+        if constexpr (MODE == 0) {
+            float pm = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = jb + 4 * g + r;
+                if (j <= iq) {
+                    pm = fmaxf(pm, zs[r]);
+                    if (zs[r] > best) { best = zs[r]; arg = j; }
+                }
+            }
+            pm = fmaxf(pm, __shfl_xor(pm, 16));
+            pm = fmaxf(pm, __shfl_xor(pm, 32));
+            const bool moves = pm > mh + LAZY_BITS || (mh == -INFINITY && pm > -INFINITY);
+            if (__any(moves)) {
+                const float rsc = !moves ? 1.f : mh == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mh - pm);
+                if (moves) mh = pm;
+                csum *= rsc;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float f = __shfl(rsc, 4 * g + r);
+#pragma unroll
+                    for (int J = 0; J < NB; ++J) acc[J][r] *= f;
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = jb + 4 * g + r;
+            const float w = __builtin_amdgcn_exp2f(zs[r] - mh);
+            if constexpr (MODE == 0) {
+                cf[r] = j <= iq ? w * gm[r] : 0.f;
+                csum += cf[r];
+            } else {
+                const float pv = w * at[r] * (gm[r] - bt[r]);
+                cf[r] = j <= iq ? (j == jstar ? pv + corr : pv) : 0.f;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int kr = 4 * g + r;
+            const float *krow = kt + kr * DD + (nn & 3);
+#pragma unroll
+            for (int J = 0; J < NB; ++J)
+                acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], krow[4 * ((4 * J + (nn >> 2)) ^ (kr & 7))], acc[J], 0, 0, 0);
+        }
+    }
+
+    // ---- the two halves of a row's keys meet in LDS ---------------------------------------------------------------
+    float fac[4] = {1.f, 1.f, 1.f, 1.f};
+    if constexpr (MODE == 0) {
+        csum += __shfl_xor(csum, 16);
+        csum += __shfl_xor(csum, 32);
+#pragma unroll
+        for (int sft = 16; sft <= 32; sft <<= 1) {
+            const float ob = __shfl_xor(best, sft);
+            const int oa = __shfl_xor(arg, sft);
+            const bool take = ob > best || (ob == best && oa < arg);
+            best = take ? ob : best;
+            arg = take ? oa : arg;
+        }
+        if (g == 0) {
+            rbest[wave][nn] = best;
+            rarg[wave][nn] = arg;
+            rref[wave][nn] = mh;
+            rsum[wave][nn] = csum;
+        }
+    }
+    __syncthreads();                                         // (also: every wave is done with the tiles)
+    if constexpr (MODE == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {                        // from the reference exponent to the row maximum; a half
+            const int q = 4 * g + r;                         // that saw no key holds zeros
+            const float ref = rref[wave][q], m = fmaxf(rbest[rg][q], rbest[rg + 2][q]);
+            fac[r] = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref - m);
+        }
+    }
+    float *red = &tiles[0][0][0];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int J = 0; J < NB; ++J) red[(wave * 16 + 4 * g + r) * RP + 16 * J + nn] = acc[J][r] * fac[r];
+    __syncthreads();
+    for (int idx = tid; idx < RT * (DD / 4); idx += 256) {
+        const int rw = idx / (DD / 4), c = 4 * (idx % (DD / 4));
+        if (i0 + rw >= n) continue;
+        const size_t ro = (size_t)bh * n + i0 + rw;
+        const f32x4 s = *reinterpret_cast<const f32x4 *>(red + rw * RP + c) + *reinterpret_cast<const f32x4 *>(red + (RT + rw) * RP + c);
+        if constexpr (MODE == 0) {
+            *reinterpret_cast<f32x4 *>(Rv + ro * YP + c) = s;
+        } else {
+            const f32x4 u = *reinterpret_cast<const f32x4 *>(Ug + ro * YP + c);
+            f32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(scale, s[e], u[e]);
+            *reinterpret_cast<f32x4 *>(dQ + ro * DD + c) = o;
+        }
+    }
+    if (MODE == 0 && tid < RT && i0 + tid < n) {
+        const int w0 = tid / 16, q = tid % 16, w1 = w0 + 2;
+        const size_t ro = (size_t)bh * n + i0 + tid;
+        const float b0 = rbest[w0][q], b1 = rbest[w1][q], m = fmaxf(b0, b1);
+        float r0 = rref[w0][q] == -INFINITY ? 0.f : rsum[w0][q] * __builtin_amdgcn_exp2f(rref[w0][q] - m);
+        r0 += rref[w1][q] == -INFINITY ? 0.f : rsum[w1][q] * __builtin_amdgcn_exp2f(rref[w1][q] - m);
+        const int a = b1 > b0 || (b1 == b0 && rarg[w1][q] < rarg[w0][q]) ? rarg[w1][q] : rarg[w0][q];
+        Rv[ro * YP + DD] = r0;
+        Rv[ro * YP + DD + 1] = __int_as_float(a);
+        Mg[(size_t)bh * npad + i0 + tid] = m;
+    }
+}
+
+// ---- key sweep ------------------------------------------------------------------------------------------------
+// Mirror image: rows of Q, dO, y1, u1 pass through LDS, the keys' rows of K and V stay in registers; the coefficient tiles
+// (lane (g, nn): queries 4g + r, key nn) are the A operands of the products that contract over the queries.
+template <int DD>
+__global__ __launch_bounds__(256, DD == 64 ? 2 : 1) void bwd_keys_f32_kernel(
+    const float *__restrict__ Qg, const float *__restrict__ Kg, const float *__restrict__ Vg, const float *__restrict__ Gg,
+    llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n, float scale, const float *__restrict__ Yg,
+    const float *__restrict__ Ug, const float *__restrict__ Sc, float *__restrict__ dK, float *__restrict__ dV)
+{
+    constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = Shape<DD>::YP, RP = DD + 4;
+    __shared__ __align__(16) float tiles[2][4][RT * DD];
+    __shared__ __align__(16) float scal[2][RT * 8];
+    static_assert(2 * 4 * 16 * RP <= 8 * RT * DD, "the final sums reuse the tiles");
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
+    const int kg = wave & 1, qs = wave >> 1;
+    // head on blockIdx.x (dispatched fastest); low key blocks see the most rows: they go first for every head
+    const int bh = blockIdx.x, b = bh / H, h = bh % H;
+    const int j0 = (int)blockIdx.y * RT;
+    const int jk = min(j0 + 16 * kg + nn, n - 1);            // keys past the end repeat the last one and are not stored
+    const float *Qh = Qg + b * sq.batch + h * sq.head;
+    const float *Gh = Gg + b * sg.batch + h * sg.head;
+    const float *Yh = Yg + (size_t)bh * n * YP, *Uh = Ug + (size_t)bh * n * YP, *Sh = Sc + (size_t)bh * n * 8;
+    const float cscale = scale * LOG2E;
+
+    float kr[NS], vr[NS];
+    load_row<DD>(Kg + b * sk.batch + h * sk.head + (int64_t)jk * sk.seq, g, kr);
+    load_row<DD>(Vg + b * sv.batch + h * sv.head + (int64_t)jk * sv.seq, g, vr);
+    f32x4 dk[NB], dv[NB];
+#pragma unroll
+    for (int J = 0; J < NB; ++J) dk[J] = dv[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto issue = [&](int buf, int it0) {
+        dma_tile<DD>(Qh, sq.seq, it0, n - 1, tiles[buf][0], wave, lane);
+        dma_tile<DD>(Gh, sg.seq, it0, n - 1, tiles[buf][1], wave, lane);
+        dma_tile<DD>(Yh, YP, it0, n - 1, tiles[buf][2], wave, lane);
+        dma_tile<DD>(Uh, YP, it0, n - 1, tiles[buf][3], wave, lane);
+        if (wave == 0) dma16(Sh + (size_t)min(it0 + (lane >> 1), n - 1) * 8 + 4 * (lane & 1), scal[buf]);
+    };
+    issue(0, j0);
+    for (int it0 = j0, c = 0; it0 < n; it0 += RT, ++c) {
+        dma_wait();
+        __syncthreads();                                     // step c has arrived, step c - 1 is consumed
+        if (it0 + RT < n) issue((c + 1) & 1, it0 + RT);
+        const int ib = it0 + 16 * qs;
+        if (ib >= n || ib + 15 < j0 + 16 * kg) continue;     // no pair of this wave in the step
+        const float *qt = &tiles[c & 1][0][16 * qs * DD], *gt = &tiles[c & 1][1][16 * qs * DD];
+        const float *yt = &tiles[c & 1][2][16 * qs * DD], *ut = &tiles[c & 1][3][16 * qs * DD];
+        const float *st = &scal[c & 1][16 * qs * 8];
+        f32x4 z = {0.f, 0.f, 0.f, 0.f}, gm = z, at = z, bt = z;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const f32x4 qv = row_chunk<DD>(qt + nn * DD, g, v, nn), gv = row_chunk<DD>(gt + nn * DD, g, v, nn);
+            const f32x4 yv = row_chunk<DD>(yt + nn * DD, g, v, nn), uv = row_chunk<DD>(ut + nn * DD, g, v, nn);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                z = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[e], kr[4 * v + e], z, 0, 0, 0);
+                gm = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[e], vr[4 * v + e], gm, 0, 0, 0);
+                at = __builtin_amdgcn_mfma_f32_16x16x4f32(yv[e], kr[4 * v + e], at, 0, 0, 0);
+                bt = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[e], kr[4 * v + e], bt, 0, 0, 0);
+            }
+        }
+        float cs[4], ce[4], cp[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int qrow = 4 * g + r, i = ib + qrow;
+            const f32x4 s4 = *reinterpret_cast<const f32x4 *>(st + qrow * 8);      // y0, u0, m, correction
+            const int jstar = __float_as_int(st[qrow * 8 + 4]);
+            const bool valid = jk <= i && i < n;
+            const float w = __builtin_amdgcn_exp2f(z[r] * cscale - s4[2]);
+            const float a = s4[0] + at[r];
+            const float ev = w * (gm[r] - (s4[1] + bt[r]));
+            const float pv = jk == jstar ? fmaf(a, ev, s4[3]) : a * ev;
+            cs[r] = valid ? w * a : 0.f;
+            ce[r] = valid ? ev : 0.f;
+            cp[r] = valid ? scale * pv : 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int qrow = 4 * g + r;
+            int off[NB];
+#pragma unroll
+            for (int J = 0; J < NB; ++J) off[J] = qrow * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ (qrow & 7));
+#pragma unroll
+            for (int J = 0; J < NB; ++J) dv[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cs[r], gt[off[J]], dv[J], 0, 0, 0);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) dk[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(ce[r], yt[off[J]], dk[J], 0, 0, 0);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) dk[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(-cs[r], ut[off[J]], dk[J], 0, 0, 0);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) dk[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cp[r], qt[off[J]], dk[J], 0, 0, 0);
+        }
+    }
+    __syncthreads();
+    float *rk = &tiles[0][0][0], *rv = rk + 4 * 16 * RP;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int J = 0; J < NB; ++J) {
+            const int o = (wave * 16 + 4 * g + r) * RP + 16 * J + nn;
+            rk[o] = dk[J][r];
+            rv[o] = dv[J][r];
+        }
+    __syncthreads();
+    for (int idx = tid; idx < RT * (DD / 4); idx += 256) {
+        const int rw = idx / (DD / 4), c = 4 * (idx % (DD / 4));
+        if (j0 + rw >= n) continue;
+        const size_t o = ((size_t)bh * n + j0 + rw) * DD + c;
+        *reinterpret_cast<f32x4 *>(dK + o) =
+            *reinterpret_cast<const f32x4 *>(rk + rw * RP + c) + *reinterpret_cast<const f32x4 *>(rk + (RT + rw) * RP + c);
+        *reinterpret_cast<f32x4 *>(dV + o) =
+            *reinterpret_cast<const f32x4 *>(rv + rw * RP + c) + *reinterpret_cast<const f32x4 *>(rv + (RT + rw) * RP + c);
+    }
+}
+
+struct BwdF32Layout {
+    size_t m, y, ru, sc, total;
+    int npad;
+};
+
+// The rows of r are overwritten by those of u (the workgroup of the moments kernel that reads r_i writes u_i); the scalars
+// of a row follow its vector: r0, later u0, and the key of the row maximum.
+BwdF32Layout make_bwd_f32_layout(int B, int H, int n, int d)
+{
+    BwdF32Layout L{};
+    const size_t bh = (size_t)B * H;
+    const int yp = d + 16;
+    L.npad = (n + 63) / 64 * 64;
+    size_t off = 0;
+    L.m = off;  off += round_up(bh * L.npad * 4, 256);
+    L.y = off;  off += round_up(bh * (size_t)n * yp * 4, 256);
+    L.ru = off; off += round_up(bh * (size_t)n * yp * 4, 256);
+    L.sc = off; off += round_up(bh * (size_t)n * 8 * 4, 256);
+    L.total = off;
+    return L;
+}
+
+template <int DD, int MODE>
+hipError_t launch_rows(const BackwardProblem &p, const BwdF32Layout &L)
+{
+    char *ws = static_cast<char *>(p.ws);
+    float *M = reinterpret_cast<float *>(ws + L.m), *Y = reinterpret_cast<float *>(ws + L.y);
+    float *RU = reinterpret_cast<float *>(ws + L.ru), *Sc = reinterpret_cast<float *>(ws + L.sc);
+    hipLaunchKernelGGL((bwd_rows_f32_kernel<DD, MODE>), dim3(p.B * p.H, (p.n + RT - 1) / RT), dim3(256), 0, p.stream,
+                       static_cast<const float *>(p.Q), static_cast<const float *>(p.K), static_cast<const float *>(p.V),
+                       static_cast<const float *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, L.npad, p.scale, p.lambda,
+                       p.lambda_rows, M, (const float *)Y, (const float *)RU, RU, Sc, p.dQ, p.dlambda);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool mfma_backward_f32_supported(int n, int d, llla_dtype in) { return in == LLLA_F32 && d == 64 && (n + RT - 1) / RT <= 65535; }
+
+size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d) { return make_bwd_f32_layout(B, H, n, d).total; }
+
+hipError_t mfma_backward_f32(const BackwardProblem &p)
+{
+    const BwdF32Layout L = make_bwd_f32_layout(p.B, p.H, p.n, p.d);
+    char *ws = static_cast<char *>(p.ws);
+    const float *Y = reinterpret_cast<const float *>(ws + L.y), *U = reinterpret_cast<const float *>(ws + L.ru);
+    const float *Sc = reinterpret_cast<const float *>(ws + L.sc);
+    stage_mark(p.stream, "backward_r");
+    hipError_t e = launch_rows<64, 0>(p, L);
+    if (e != hipSuccess) return e;
+    stage_mark(p.stream, "moments");
+    e = mfma_moments_f32_given(p, L.npad, reinterpret_cast<float *>(ws + L.m), reinterpret_cast<float *>(ws + L.y),
+                               reinterpret_cast<float *>(ws + L.ru));
+    if (e != hipSuccess) return e;
+    stage_mark(p.stream, "backward_dq");
+    e = launch_rows<64, 1>(p, L);
+    if (e != hipSuccess) return e;
+    stage_mark(p.stream, "backward_keys");
+    hipLaunchKernelGGL((bwd_keys_f32_kernel<64>), dim3(p.B * p.H, (p.n + RT - 1) / RT), dim3(256), 0, p.stream,
+                       static_cast<const float *>(p.Q), static_cast<const float *>(p.K), static_cast<const float *>(p.V),
+                       static_cast<const float *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, p.scale, Y, U, Sc, p.dK, p.dV);
+    return hipGetLastError();
+}
+
+}  // namespace llla

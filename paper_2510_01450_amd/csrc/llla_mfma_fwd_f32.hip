@@ -65,12 +65,15 @@ struct F32Shared {
 
 // LIVE: feature blocks of 16 that can be non-zero (4, except for calls at d = 16 / 32 that run here on zero-padded
 // copies: the tiles, scaled operands and solve blocks of padded feature blocks are skipped, see moments_body).
-template <int LIVE>
+// BWD (the backward pass, llla_mfma_bwd_f32.hip): Mg holds the row maxima already, so nothing is ever rescaled and one of
+// the three barriers per block goes; RUg holds r1 and r0 of every row (pitch YP, r0 at [FD]) and receives u1, u0 in their
+// place -- the right-hand sides are read before the solve by the lanes that store its result.
+template <int LIVE, bool BWD = false>
 __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__restrict__ Qg, const float *__restrict__ Kg,
                                                             llla_strides sq, llla_strides sk, int H, int n, int npad,
                                                             float cscale, float lambda, const float *__restrict__ lam_rows,
                                                             float *__restrict__ Mg, float *__restrict__ LFg,
-                                                            float *__restrict__ Yg, int causal)
+                                                            float *__restrict__ Yg, float *__restrict__ RUg, int causal)
 {
     using S = Shape<FD>;
     constexpr int NB = 4, QW = 4, QB = 16, YP = S::YP;
@@ -105,6 +108,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     f32x4 mu_acc = {0.f, 0.f, 0.f, 0.f};
     float om_part = 0.f;                   // this lane's share of -omega' of query nn (its keys: 4 g + r of every wave block)
     float mh = -INFINITY, mtrue = -INFINITY;   // reference exponent and true maximum of query nn (log2 units)
+    if constexpr (BWD) mh = Mg[(size_t)bh * npad + min(iq, n - 1)];
 
     // DMA of one K block: 16 KB = 16 wave transfers of 1 KB, four per wave; transfer t of wave w fills key rows
     // 16 w + 4 t .. + 3; lane l of it writes row 16 w + 4 t + l / 16, stored chunk l % 16
@@ -154,26 +158,30 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                 for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qv[e], z, 0, 0, 0);
             }
         }
-        float zs[4], pmx = -INFINITY;
+        float zs[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = c * FKB + 16 * wave + 4 * g + r;
-            zs[r] = z[r] * cscale;
-            pmx = (q_live && j <= jlim) ? fmaxf(pmx, zs[r]) : pmx;
+        for (int r = 0; r < 4; ++r) zs[r] = z[r] * cscale;
+        if constexpr (!BWD) {
+            float pmx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = c * FKB + 16 * wave + 4 * g + r;
+                pmx = (q_live && j <= jlim) ? fmaxf(pmx, zs[r]) : pmx;
+            }
+            pmx = fmaxf(pmx, __shfl_xor(pmx, 16));
+            pmx = fmaxf(pmx, __shfl_xor(pmx, 32));
+            if (g == 0) sm.pm[wave][nn] = pmx;
+            __syncthreads();
+            const float bmx = fmaxf(fmaxf(sm.pm[0][nn], sm.pm[1][nn]), fmaxf(sm.pm[2][nn], sm.pm[3][nn]));
+            mtrue = fmaxf(mtrue, bmx);
+            float rsc = 1.f;
+            if (bmx > mh + LAZY_BITS || (mh == -INFINITY && bmx > -INFINITY)) {       // the reference moves (first block: always)
+                rsc = (mh == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mh - bmx);
+                mh = bmx;
+            }
+            if (wave == 0 && g == 0) sm.rs[nn] = rsc;
+            om_part *= rsc;
         }
-        pmx = fmaxf(pmx, __shfl_xor(pmx, 16));
-        pmx = fmaxf(pmx, __shfl_xor(pmx, 32));
-        if (g == 0) sm.pm[wave][nn] = pmx;
-        __syncthreads();
-        const float bmx = fmaxf(fmaxf(sm.pm[0][nn], sm.pm[1][nn]), fmaxf(sm.pm[2][nn], sm.pm[3][nn]));
-        mtrue = fmaxf(mtrue, bmx);
-        float rsc = 1.f;
-        if (bmx > mh + LAZY_BITS || (mh == -INFINITY && bmx > -INFINITY)) {       // the reference moves (first block: always)
-            rsc = (mh == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mh - bmx);
-            mh = bmx;
-        }
-        if (wave == 0 && g == 0) sm.rs[nn] = rsc;
-        om_part *= rsc;
         {
             float wf[4];
 #pragma unroll
@@ -189,7 +197,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
         if (c + 1 < nblk) issue_dma(c + 1);
 
         // ---- rescale what has been accumulated (factors are 1 unless a reference exponent moved) -------------------
-        {
+        if constexpr (!BWD) {
             const f32x4 r4 = *reinterpret_cast<const f32x4 *>(&sm.rs[4 * g]);        // rows 4 g + r of mu~
 #pragma unroll
             for (int r = 0; r < 4; ++r) mu_acc[r] *= r4[r];
@@ -245,10 +253,10 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     om_part += __shfl_xor(om_part, 16);
     om_part += __shfl_xor(om_part, 32);
     if (g == 0) sm.pm[wave][nn] = om_part;
-    const float lf = q_live ? mtrue - mh : 0.f;                          // log2 F
+    const float lf = (q_live && !BWD) ? mtrue - mh : 0.f;                // log2 F
     if (wave == 0 && g == 0) {
         sm.fsc[nn] = __builtin_amdgcn_exp2f(lf);
-        if (q_live) {
+        if (q_live && !BWD) {
             Mg[(size_t)bh * npad + iq] = mh;
             LFg[(size_t)bh * npad + iq] = lf;
         }
@@ -278,12 +286,25 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
         tq[P] = -qrow[16 * P + nn];
         te[P] = 0.f; y1[P] = 0.f; u1[P] = 0.f;
     }
-    solve_wave_q4<false, LIVE>(acc, tmu, tq, te, 0.f, sm.oms[qi], &sm.sc[wave][0][0], g, nn, pivot_floor, y1, y0, u1, u0);
+    float r0 = 0.f;
+    if constexpr (BWD) {
+        const float *rr = RUg + ((size_t)bh * n + row) * YP;
+#pragma unroll
+        for (int P = 0; P < NB; ++P) te[P] = -rr[16 * P + nn];
+        r0 = rr[FD];
+    }
+    solve_wave_q4<BWD, LIVE>(acc, tmu, tq, te, r0, sm.oms[qi], &sm.sc[wave][0][0], g, nn, pivot_floor, y1, y0, u1, u0);
     if (i0 + qi < n) {
         float *yr = Yg + ((size_t)bh * n + row) * YP;
 #pragma unroll
         for (int P = 0; P < NB; ++P) yr[16 * P + nn] = y1[P];
         if (nn == 0) yr[FD] = y0;
+        if constexpr (BWD) {
+            float *ur = RUg + ((size_t)bh * n + row) * YP;
+#pragma unroll
+            for (int P = 0; P < NB; ++P) ur[16 * P + nn] = u1[P];
+            if (nn == 0) ur[FD] = u0;
+        }
     }
 }
 
@@ -437,13 +458,13 @@ hipError_t mfma_forward_f32(const Problem &p)
     const dim3 grid((p.n + S::QB - 1) / S::QB, bh);
     if (live == 1)
         hipLaunchKernelGGL(moments_f32_kernel<1>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, p.causal);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal);
     else if (live == 2)
         hipLaunchKernelGGL(moments_f32_kernel<2>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, p.causal);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal);
     else
         hipLaunchKernelGGL(moments_f32_kernel<4>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, p.causal);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal);
     if (p.rho != nullptr || p.delta != nullptr) {
         stage_mark(p.stream, "statistics");
         hipLaunchKernelGGL(stats_f32_kernel, dim3((p.n + 3) / 4, bh), dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, L.npad,
@@ -458,6 +479,14 @@ hipError_t mfma_forward_f32(const Problem &p)
     // rows that see at most 64 keys: fp64 in key space (their output weights cancel to three digits in fp32)
     stage_mark(p.stream, "few_key_rows");
     return dual_forward(p);
+}
+
+hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU)
+{
+    const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K);
+    hipLaunchKernelGGL((moments_f32_kernel<4, true>), dim3((p.n + Shape<FD>::QB - 1) / Shape<FD>::QB, p.B * p.H), dim3(256), 0,
+                       p.stream, Q, K, p.sq, p.sk, p.H, p.n, npad, p.scale * LOG2E, p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1);
+    return hipGetLastError();
 }
 
 }  // namespace llla

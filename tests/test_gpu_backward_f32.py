@@ -1,0 +1,46 @@
+"""fp32 backward on the fp32 matrix cores (d = 64): the edges of its 32-row tiles and of the halves they are split into,
+against the backward oracle, with the fp32 gate of the other backward tests (parity.check_grad, 1e-3)."""
+import pytest
+import torch
+
+import paper_2510_01450_amd as llla
+import workloads
+from oracle import backward as ob
+from test_gpu_backward import DEV, _backward, _case, _compare, _floor, _upstream
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 97, 130, 257])
+def test_edges_of_the_tiles(n):
+    w = _case(1, 3, n, 64, "f32", index=540 + n)
+    Q, K, V = workloads.make_inputs(w)
+    G = _upstream(w, 40 + n)
+    _compare(w, _backward(w, Q, K, V, G, w.lam), ob.backward(Q, K, V, G, w.lam, w.scale), "n=%d" % n, _floor(V, G, w.lam))
+
+
+@pytest.mark.parametrize("factor", [-1.0, 40.0])
+def test_reference_exponent(factor):
+    """Logits of growing size: the running reference exponent moves by more than its slack of 64 bits inside a row
+    (factor 40: logits of several hundred), and a negative scale."""
+    w = _case(1, 2, 150, 64, "f32", index=900)
+    Q, K, V = workloads.make_inputs(w)
+    if factor > 1:
+        K = K * torch.linspace(0.5, 8.0, w.n)[None, None, :, None]
+        Q = Q * factor
+    w = w.with_shape(scale=w.scale * (-1.0 if factor < 0 else 1.0))
+    G = _upstream(w, 41)
+    _compare(w, _backward(w, Q, K, V, G, w.lam), ob.backward(Q, K, V, G, w.lam, w.scale), "factor %g" % factor, _floor(V, G, w.lam))
+
+
+def test_workspace_of_the_vector_kernels_is_enough():
+    """A caller that brings only what the vector kernels need gets their result."""
+    w = _case(1, 2, 70, 64, "f32", index=901)
+    Q, K, V = (t.to(DEV) for t in workloads.make_inputs(w))
+    G = _upstream(w, 42).to(DEV)
+    small = (w.B * w.H * w.n * (2 * w.d + 8) * 4 + 255) // 256 * 256
+    assert small < llla.backward_workspace_bytes(w.B, w.H, w.n, w.d, torch.float32)
+    ws = torch.empty(small, dtype=torch.uint8, device=DEV)
+    got = llla.llla_backward(Q, K, V, G, w.lam, w.scale, return_dlambda=True, workspace=ws)
+    want = llla.llla_backward(Q, K, V, G, w.lam, w.scale, return_dlambda=True, path="valu")
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
