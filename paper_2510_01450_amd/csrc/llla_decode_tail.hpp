@@ -210,19 +210,88 @@ template <int D, int NBUF, int NW>
 struct HeadLds {
     float tiles[NBUF][DecShape<D>::NTILES * 256];
     float mu[NW][D], yv[NW][D];
-    float sc[16 * SC_PITCH];
-    float ys[D + 4];
     float mw[4], om[4];
+    static_assert((DecShape<D>::NB < 4 ? DecShape<D>::NB : 4) * 16 * SC_PITCH <= DecShape<D>::NTILES * 256, "the solve's scratch reuses the tiles");
 };
 
 // Solve and output of one head whose merged moments lie in lds.tiles[0], lds.mu[0], lds.yv[0], lds.om[0].  Called by all four
-// waves after a barrier.
+// waves after a barrier; overwrites lds.tiles[0].
+// With Sigma~ + lambda I = U^T U, a = U^{-T} mu~, c = U^{-T} q and W = U^{-T} G~ the output is y0 sum w v + W^T (c - a y0), y0 =
+// (1 - a.c) / (omega - a.a): no back substitution.  mu~, q and G~ are further block columns of the factorisation; wave W
+// carries column W of G~ and repeats the factorisation itself (every wave has a SIMD of its own, and an exchange
+// of tiles would cost the barriers that this saves).  What bounds it is the serial chain of the diagonal tiles.  One wave with both
+// substitutions on the vector ALU: 64 heads of 1024 to 8192 fp32 keys, d = 64, 86.7 instead of 81.2 us; 256 heads x 4096 bf16
+// keys, d = 32, 53.7 instead of 51.5.
 template <int D, typename TI, bool PERM, class Lds>
 __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
 {
     using S = DecShape<D>;
+    constexpr int NB = S::NB, NX = 1;
+    static_assert(NB <= 4, "a column of G~ per wave");
+    const int g = lane / 16, nn = lane % 16;
+    f32x4 acc[S::NSIG], x[NX + 1][NB];
+    if (wave < NB) {                                      // scalar branches: the second one contains MFMAs
+#pragma unroll
+        for (int t = 0; t < S::NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][t * 256 + lane * 4]);
+        const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
+#pragma unroll
+        for (int P = 0; P < NB; ++P) {
+#pragma unroll
+            for (int v = 0; v < NX; ++v)
+                x[v][P] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * P + wave + 4 * v) * 256 + lane * 4]);
+            const f32x4 m = *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                acc[upper_tile<NB>(P, P)][t] -= (nn == 4 * g + t) ? out.lambda : 0.f;
+                const TI qv = qp[PERM ? NB * (4 * g + t) + P : 16 * P + 4 * g + t];
+                float q;
+                if constexpr (sizeof(TI) == 2) q = bf16_to_f32(qv);
+                else q = qv;
+                x[NX][P][t] = nn == 0 ? -m[t] : nn == 1 ? -q : 0.f;       // columns 0 and 1: mu~ and q
+            }
+        }
+    }
+    __syncthreads();                                      // the tiles become the waves' scratch
+    if (wave < NB) {
+        factorise_one<NB, NX + 1>(acc, lds.tiles[0] + wave * 16 * SC_PITCH, g, nn, 0.5f * out.lambda, x);
+        float av[4 * NB], cv[4 * NB], saa = 0.f, sac = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4 * NB; ++i) {
+            av[i] = row_bcast<0>(x[NX][i / 4][i % 4]);
+            cv[i] = row_bcast<1>(x[NX][i / 4][i % 4]);
+            saa = fmaf(av[i], av[i], saa);
+            sac = fmaf(av[i], cv[i], sac);
+        }
+        saa = rows_allsum(saa);
+        sac = rows_allsum(sac);
+        const float y0 = (1.f - sac) / (lds.om[0] - saa);
+#pragma unroll
+        for (int v = 0; v < NX; ++v) {
+            const int J = wave + 4 * v;
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[v][i / 4][i % 4], fmaf(-av[i], y0, cv[i]), s);
+            s = rows_allsum(s);
+            const float o = fmaf(y0, lds.yv[0][16 * J + nn], s);
+            if (g == 0) {
+                const size_t at = (size_t)bh * D + (PERM ? NB * nn + J : 16 * J + nn);
+                if (out.out_bf16) static_cast<bf16_t *>(out.o)[at] = f32_to_bf16(o);
+                else static_cast<float *>(out.o)[at] = o;
+            }
+        }
+    }
+}
+
+// The same at d = 128, where the further block columns would be 108 of 220 tile products per wave (merge kernel 56 us instead of
+// 49): one wave factorises and substitutes on the vector ALU, all waves form the output.
+template <int D, typename TI, bool PERM, class Lds>
+__device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
+{
+    using S = DecShape<D>;
     constexpr int NB = S::NB;
     const int g = lane / 16, nn = lane % 16;
+    float *scratch = lds.tiles[0], *ys = scratch + 16 * SC_PITCH;         // tiles of Sigma~, consumed before they are written
+    static_assert(16 * SC_PITCH + D + 4 <= S::NSIG * 256, "scratch and solution fit the tiles of Sigma~");
     if (wave == 0) {                                      // scalar branch: the block contains MFMAs
         f32x4 acc[S::NSIG], rhs[NB];
         float y0;
@@ -233,7 +302,7 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[upper_tile<NB>(P, P)][t] -= (nn == 4 * g + t) ? out.lambda : 0.f;
         const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
-        solve_one<NB>(acc, rhs, y0, lds.om[0], lds.sc, g, nn, 0.5f * out.lambda, [&](int P, float &m, float &q, float &e) {
+        solve_one<NB>(acc, rhs, y0, lds.om[0], scratch, g, nn, 0.5f * out.lambda, [&](int P, float &m, float &q, float &e) {
             m = -lds.mu[0][16 * P + nn];
             const TI v = qp[PERM ? NB * nn + P : 16 * P + nn];
             if constexpr (sizeof(TI) == 2) q = -bf16_to_f32(v);
@@ -242,18 +311,18 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
         });
         if (nn == 0) {
 #pragma unroll
-            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&lds.ys[16 * P + 4 * g]) = rhs[P];
-            if (g == 0) lds.ys[D] = y0;
+            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[P];
+            if (g == 0) ys[D] = y0;
         }
     }
     __syncthreads();
-    const float y0 = lds.ys[D];
+    const float y0 = ys[D];
     for (int J = wave; J < NB; J += 4) {
         float s = 0.f;
 #pragma unroll
         for (int I = 0; I < NB; ++I) {
             const f32x4 gv = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * I + J) * 256 + lane * 4]);
-            const f32x4 y1 = *reinterpret_cast<const f32x4 *>(&lds.ys[16 * I + 4 * g]);
+            const f32x4 y1 = *reinterpret_cast<const f32x4 *>(&ys[16 * I + 4 * g]);
 #pragma unroll
             for (int t = 0; t < 4; ++t) s = fmaf(gv[t], y1[t], s);        // G~[16I+4g+t][16J+nn] y1[16I+4g+t]
         }
@@ -265,6 +334,13 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
             else static_cast<float *>(out.o)[at] = o;
         }
     }
+}
+
+template <int D, typename TI, bool PERM, class Lds>
+__device__ __forceinline__ void solve_head(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
+{
+    if constexpr (D == 128) solve_and_store_128<D, TI, PERM>(lds, out, bh, wave, lane);
+    else solve_and_store<D, TI, PERM>(lds, out, bh, wave, lane);
 }
 
 // The four waves of a workgroup, each with moments of its own share of the keys, become one set of moments: in the workgroup's
@@ -321,7 +397,7 @@ __device__ __forceinline__ void finish_workgroup(Lds &lds, f32x4 (&acc)[DecShape
         __syncthreads();
         if (tid == 0) lds.om[0] = oall;
         __syncthreads();
-        solve_and_store<D, TI, PERM>(lds, out, bh, wave, lane);
+        solve_head<D, TI, PERM>(lds, out, bh, wave, lane);
     } else if (tid == 0) {
         R[0] = mall;
         R[1] = oall;
@@ -370,7 +446,7 @@ __global__ __launch_bounds__(DEC_NT, 1) void decode_merge_kernel(DecSplit split,
     if (tid < 2 * D) (tid < D ? lds.mu[0] : lds.yv[0])[tid & (D - 1)] = hv;
     if (tid == 0) lds.om[0] = om;
     __syncthreads();
-    solve_and_store<D, TI, PERM>(lds, out, bh, wave, lane);
+    solve_head<D, TI, PERM>(lds, out, bh, wave, lane);
 }
 
 }  // namespace mfma

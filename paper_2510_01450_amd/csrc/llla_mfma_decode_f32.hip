@@ -287,7 +287,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         }
         if constexpr (FUSED) {
             __syncthreads();
-            solve_and_store<D, TI, true>(lds, a.out, bh, wave, lane);
+            solve_head<D, TI, true>(lds, a.out, bh, wave, lane);
         }
     }
 }
