@@ -222,6 +222,13 @@ __global__ __launch_bounds__(NT) void bwd_rows_kernel(const TI *__restrict__ Qg,
         for (int c = r; c < D; c += TPQ) S[(c + 1) * LS + P] = qs[slot * D + c];
 
         // ---- elimination with two right-hand sides (the matrix is symmetric positive definite) -------
+        if constexpr (D <= 32) {
+            __syncthreads();
+            float y[2], y0[2];
+            solve_in_registers<D, 2>(S, LS, r, y, y0);
+            if (r == 0) { y0s[slot] = y0[0]; u0s[slot] = y0[1]; }
+            if (r < D) { y1s[slot * D + r] = y[0]; u1s[slot * D + r] = y[1]; }
+        } else {
         for (int k = 0; k < P; ++k) {
             __syncthreads();
             const float pinv = 1.f / S[k * LS + k];
@@ -248,6 +255,7 @@ __global__ __launch_bounds__(NT) void bwd_rows_kernel(const TI *__restrict__ Qg,
                 S[row * LS + P] = fmaf(-S[row * LS + k], yk, S[row * LS + P]);
                 S[row * LS + P + 1] = fmaf(-S[row * LS + k], uk, S[row * LS + P + 1]);
             }
+        }
         }
         __syncthreads();
     }

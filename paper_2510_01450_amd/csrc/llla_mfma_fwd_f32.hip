@@ -5,7 +5,8 @@
 //   moments  per block of 16 queries: weights, omega_i, mu~_i and Sigma~_i (Eq. (tilded_form)) on chip, the ten upper
 //            16x16 tiles of Sigma~_i per query in MFMA accumulators, then the exact per-query solve (solve_wave_q4);
 //   output   third loop of Algorithm 1 as a flash-style sweep, its three products on fp32 MFMA as well;
-//   rows that see at most 64 keys are rewritten by the fp64 key-space kernel (llla_dual.hip).
+//   rows that see at most 64 keys are served in fp64 and key space (llla_dual.hpp) by further workgroups of the moments kernel:
+//            serial chains that share a compute unit with the matrix-core workgroups instead of running alone at the end.
 //
 // Running maximum.  There is no separate sweep for the row maxima.  fp32 weights have 2^127 of headroom, so the
 // weights are taken relative to a reference exponent mh_i that only moves when a block's largest logit exceeds it by
@@ -14,6 +15,7 @@
 // moment is F_i times the max-normalised one, so the system solved is the max-normalised one times F_i:
 // [omega' mu~'^T; mu~' Sigma~' + lambda F I] y' = [1; q], and the output weights w'_ij (y0' + k_j . y1') equal those of
 // Eq. (lla).  mh_i and y'_i go to the output sweep; delta_i = delta'_i / F_i (rho_i needs no correction).
+#include "llla_dual.hpp"
 #include "llla_mfma_common.hpp"
 #include "llla_mfma_solve64.hpp"
 
@@ -73,15 +75,28 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                                                             llla_strides sq, llla_strides sk, int H, int n, int npad,
                                                             float cscale, float lambda, const float *__restrict__ lam_rows,
                                                             float *__restrict__ Mg, float *__restrict__ LFg,
-                                                            float *__restrict__ Yg, float *__restrict__ RUg, int causal)
+                                                            float *__restrict__ Yg, float *__restrict__ RUg, int causal, int nqb,
+                                                            dual::DualArgs da, int out_bf16)
 {
+    // nqb: blocks of 16 query rows the sequence has; rows [0, da.nrows), a multiple of 16 or all, are the key-space workgroups',
+    // which follow the others of their head
     using S = Shape<FD>;
     constexpr int NB = 4, QW = 4, QB = 16, YP = S::YP;
     __shared__ __align__(16) F32Shared sm;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     const BlockMap bm = xcd_block_map();
     const int bh = bm.bh, b = bh / H, h = bh % H;
-    const int nqb = gridDim.x;
+    if constexpr (!BWD) {
+        const int own = nqb - (da.nrows + QB - 1) / QB;
+        if (bm.blk >= own) {
+            static_assert(sizeof(dual::DualShared<FD>) <= sizeof(F32Shared), "a key-space row fits the workgroup's LDS");
+            auto &ds = *reinterpret_cast<dual::DualShared<FD> *>(&sm);
+            const int i = da.nrows - 1 - (bm.blk - own);
+            if (out_bf16) dual::dual_forward_row<FD, float, bf16_t>(ds, da, bh, i);
+            else dual::dual_forward_row<FD, float, float>(ds, da, bh, i);
+            return;
+        }
+    }
     const int i0 = (nqb - 1 - bm.blk) * QB;                           // long rows first
     const int ilast = min(i0 + QB - 1, n - 1);
     const int nblk = causal ? ilast / FKB + 1 : (n + FKB - 1) / FKB;
@@ -211,9 +226,10 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
             }
         }
 
-        // ---- moments of block c: 16 steps of 4 keys ------------------------------------------------------------
+        // ---- moments of block c: 16 steps of 4 keys, up to the last key a query of the workgroup sees -------------
+        const int s4n = causal ? min(4, (ilast - c * FKB) / 16 + 1) : 4;
 #pragma unroll 1
-        for (int s4 = 0; s4 < 4; ++s4) {
+        for (int s4 = 0; s4 < s4n; ++s4) {
             // weights of keys 4 s + g, s = 4 s4 .. 4 s4 + 3: for this wave's queries (scaling) and for all 16 (mu~)
             f32x4 wq[QW];
 #pragma unroll
@@ -323,14 +339,16 @@ __global__ __launch_bounds__(256, 2) void output_f32_kernel(const float *__restr
                                                          const float *__restrict__ Vg, llla_strides sq, llla_strides sk,
                                                          llla_strides sv, int H, int n, int npad, float cscale,
                                                          const float *__restrict__ Mg, const float *__restrict__ Yg,
-                                                         void *__restrict__ Og, llla_strides so, int out_bf16, int causal)
+                                                         void *__restrict__ Og, llla_strides so, int out_bf16, int causal, int skip)
 {
+    // rows [0, skip) -- 64, or all -- are the key-space workgroups' of the moments kernel
     constexpr int YP = Shape<FD>::YP, NB = 4;
     __shared__ __align__(16) OutShared sm;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     // head on blockIdx.x (dispatched fastest), query block on y, longest rows first
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
     const int i0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * 64;
+    if (i0 < skip) return;
     const int iq = i0 + wave * 16 + nn, iqc = min(iq, n - 1);
     const int jlim = causal ? iq : n - 1;
     const float *Kh = Kg + b * sk.batch + h * sk.head;
@@ -421,11 +439,11 @@ __global__ __launch_bounds__(256, 2) void output_f32_kernel(const float *__restr
 // Statistics of Eq. (lla) from y' and F: 1/delta' = y0' + q . y1', delta = delta' / F, rho = -delta' y1'.  One wave per row.
 __global__ __launch_bounds__(256) void stats_f32_kernel(const float *__restrict__ Qg, llla_strides sq, int H, int n, int npad,
                                                         const float *__restrict__ Yg, const float *__restrict__ LFg,
-                                                        float *__restrict__ rho, float *__restrict__ delta)
+                                                        float *__restrict__ rho, float *__restrict__ delta, int skip)
 {
     constexpr int YP = Shape<FD>::YP;
     const int lane = threadIdx.x % 64, i = blockIdx.x * 4 + threadIdx.x / 64, bh = blockIdx.y;
-    if (i >= n) return;
+    if (i >= n || i < skip) return;
     const float *qrow = Qg + (bh / H) * sq.batch + (bh % H) * sq.head + (int64_t)i * sq.seq;
     const float *yr = Yg + ((size_t)bh * n + i) * YP;
     const float y1 = yr[lane];
@@ -455,37 +473,36 @@ hipError_t mfma_forward_f32(const Problem &p)
     const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K);
     stage_mark(p.stream, "moments");
     const int live = p.live_d > 0 ? (p.live_d + 15) / 16 : 4;      // a d = 16 / 32 call on zero-padded copies: 1 or 2
-    const dim3 grid((p.n + S::QB - 1) / S::QB, bh);
+    const dual::DualArgs da = dual::dual_args(p);
+    const int nqb = (p.n + S::QB - 1) / S::QB, obf = p.out == LLLA_BF16 ? 1 : 0;
+    const dim3 grid(nqb - (da.nrows + S::QB - 1) / S::QB + da.nrows, bh);
     if (live == 1)
         hipLaunchKernelGGL(moments_f32_kernel<1>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);
     else if (live == 2)
         hipLaunchKernelGGL(moments_f32_kernel<2>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);
     else
         hipLaunchKernelGGL(moments_f32_kernel<4>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);
     if (p.rho != nullptr || p.delta != nullptr) {
         stage_mark(p.stream, "statistics");
         hipLaunchKernelGGL(stats_f32_kernel, dim3((p.n + 3) / 4, bh), dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, L.npad,
-                           (const float *)Y, (const float *)LF, p.rho, p.delta);
+                           (const float *)Y, (const float *)LF, p.rho, p.delta, da.nrows);
     }
     stage_mark(p.stream, "output");
     hipLaunchKernelGGL(output_f32_kernel, dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, static_cast<const float *>(p.V),
                        p.sq, p.sk, p.sv, p.H, p.n, L.npad, p.scale * LOG2E, (const float *)M, (const float *)Y, p.O, p.so,
-                       p.out == LLLA_BF16 ? 1 : 0, p.causal);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // rows that see at most 64 keys: fp64 in key space (their output weights cancel to three digits in fp32)
-    stage_mark(p.stream, "few_key_rows");
-    return dual_forward(p);
+                       obf, p.causal, da.nrows);
+    return hipGetLastError();
 }
 
 hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU)
 {
     const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K);
     hipLaunchKernelGGL((moments_f32_kernel<4, true>), dim3((p.n + Shape<FD>::QB - 1) / Shape<FD>::QB, p.B * p.H), dim3(256), 0,
-                       p.stream, Q, K, p.sq, p.sk, p.H, p.n, npad, p.scale * LOG2E, p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1);
+                       p.stream, Q, K, p.sq, p.sk, p.H, p.n, npad, p.scale * LOG2E, p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1,
+                       (p.n + Shape<FD>::QB - 1) / Shape<FD>::QB, dual::DualArgs{}, 0);
     return hipGetLastError();
 }
 

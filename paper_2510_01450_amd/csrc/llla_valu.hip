@@ -16,6 +16,7 @@
 //       the relmm-style product K y1 followed by S V.
 // The running row maximum and the rescaling of the moments across key tiles are those of
 // Algorithm 1 (lines computing m, alpha and the updates of omega and M).
+#include "llla_dual.hpp"
 #include "llla_valu_common.hpp"
 
 namespace llla {
@@ -27,6 +28,8 @@ using namespace valu;
 //          DECODE = true : grid.x = B*H; all slots share the query and split the keys.
 //          GIVEN  = true : (forward only) the per-row solution y and row maximum are read from
 //                          device memory (written by the MFMA moments kernel); only sweep 3 runs.
+// A full forward also carries the key-space rows (llla_dual.hpp) as further workgroups behind its nqb * B*H own: they are
+// serial chains that would otherwise run alone after it (1 head x 128 rows, d = 16: 14 us behind 31).
 template <int D, typename TI, typename TO, bool DECODE, bool GIVEN = false>
 __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, const TI *__restrict__ Kg,
                                                   const TI *__restrict__ Vg, TO *__restrict__ Og,
@@ -36,8 +39,10 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
                                                   const float *__restrict__ Mg = nullptr, int mpitch = 0,
                                                   const float *__restrict__ Yg = nullptr, int ypitch = 0,
                                                   const float *__restrict__ LamRows = nullptr,
-                                                  float *__restrict__ Rho = nullptr, float *__restrict__ Delta = nullptr)
+                                                  float *__restrict__ Rho = nullptr, float *__restrict__ Delta = nullptr,
+                                                  int nqb = 0, int skip = 0, dual::DualArgs dual_args = {})
 {
+    // nqb: blocks of query rows the sequence has; rows [0, skip) are the key-space workgroups'
     using C = Cfg<D>;
     constexpr int TS = C::TS, TG = C::TG, TPQ = C::TPQ, QB = C::QB, LDK = C::LDK, P = C::P,
                   LS = C::LDS_SYS;
@@ -45,7 +50,8 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
     constexpr int NSYS = DECODE ? 1 : QB;
     constexpr int TILE_F = 2 * KROWS * LDK + 2 * QB * KT;   // ks, vs, logits, weights
     constexpr int SYS_F = NSYS * P * LS;
-    constexpr int UNION_F = (TILE_F > SYS_F) ? TILE_F : SYS_F;
+    constexpr int UNION_F = (GIVEN || TILE_F > SYS_F) ? TILE_F : SYS_F;   // (a given solution needs no system: 18
+                                                            // instead of 70 KB at d = 64, eight workgroups per compute unit)
 
     __shared__ __align__(16) float smem[UNION_F + QB * D + QB * (P + 3) + 4 * QB];
     float *ks = smem;                                     // [KROWS][LDK]
@@ -60,6 +66,16 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
     float *fs = al + QB;                                  // [QB] decode merge factors
     float *red = fs + QB;                                 // [QB] spare
 
+    if constexpr (!DECODE && !GIVEN) {
+        static_assert(sizeof(dual::DualShared<D>) <= sizeof(smem), "a key-space row fits the workgroup's LDS");
+        const unsigned own = (unsigned)(nqb - skip / QB) * (unsigned)nbh;
+        if (blockIdx.x >= own) {
+            const unsigned id = blockIdx.x - own;
+            dual::dual_forward_row<D, TI, TO>(*reinterpret_cast<dual::DualShared<D> *>(smem), dual_args, (int)(id % (unsigned)nbh),
+                                              dual_args.nrows - 1 - (int)(id / (unsigned)nbh));
+            return;
+        }
+    }
     const int tid = threadIdx.x;
     const int slot = tid / TPQ;
     const int r = tid % TPQ;
@@ -79,7 +95,7 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
         nkeys = nkeys < 1 ? 1 : (nkeys > n ? n : nkeys);
     } else {
         nkeys = n;
-        const int nqb = (int)(gridDim.x / (unsigned)nbh);
+        if (GIVEN) nqb = (int)(gridDim.x / (unsigned)nbh);
         i0 = (nqb - 1 - (int)(blockIdx.x / (unsigned)nbh)) * QB;          // long rows are scheduled first
     }
     const int my_i = DECODE ? nkeys - 1 : i0 + slot;    // query row of this slot
@@ -250,7 +266,15 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
         }
 
         // ---- exact solve by elimination (the matrix is symmetric positive definite) -----------------
-        {
+        if constexpr (!DECODE && D <= 32) {
+            static_assert(TPQ == (D == 16 ? 16 : 64), "a lane owns a row");
+            __syncthreads();
+            float y[1], y0[1];
+            solve_in_registers<D, 1>(sys + slot * P * LS, LS, r, y, y0);
+            float *yv = ys + slot * (P + 3);
+            if (r == 0) yv[0] = y0[0];
+            if (r < D) yv[1 + r] = y[0];
+        } else {
             float *S = DECODE ? sys : sys + slot * P * LS;
             const int gt = DECODE ? tid : r;
             constexpr int GS = DECODE ? NT : TPQ;
@@ -274,7 +298,7 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
 
         // ---- optional statistics of Eq. (lla): with y1 = -rho/delta and y0 = (1 + q.rho)/delta,
         //      1/delta = y0 + q.y1 and rho = -delta y1 ---------------------------------------------------
-        if (!DECODE && (Rho != nullptr || Delta != nullptr) && slot_live) {
+        if (!DECODE && (Rho != nullptr || Delta != nullptr) && slot_live && my_i >= skip) {
             const float *ysl = ys + slot * (P + 3);
             float qy = 0.f;
             for (int c = 0; c < D; ++c) qy = fmaf(qs[slot * D + c], ysl[1 + c], qy);
@@ -328,42 +352,45 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
             __syncthreads();
         }
         for (int c = tid; c < D; c += NT) Io<TO>::store1(Og + (int64_t)bh * D + c, osum[c]);
-    } else if (slot_live && r < D) {
+    } else if (slot_live && my_i >= skip && r < D) {
         TO *op = Og + b * so.batch + h * so.head + (int64_t)my_i * so.seq;
         Io<TO>::store1(op + r, o);
     }
 }
 
-// nrows: the forward kernel serves query rows [0, nrows) only (nrows = n for a full forward)
 template <int D, typename TI, typename TO, bool DECODE>
-hipError_t launch(const Problem &p, int nrows)
+hipError_t launch(const Problem &p)
 {
     using C = Cfg<D>;
-    dim3 grid((DECODE ? 1 : (nrows + C::QB - 1) / C::QB) * p.B * p.H);
+    const int nbh = p.B * p.H, nqb = (p.n + C::QB - 1) / C::QB;
+    dual::DualArgs da{};
+    if (!DECODE) da = dual::dual_args(p);
+    const int skip = da.nrows;
+    dim3 grid(DECODE ? nbh : (nqb - skip / C::QB + skip) * nbh);
     hipLaunchKernelGGL((valu_kernel<D, TI, TO, DECODE>), grid, dim3(NT), 0, p.stream,
                        (const TI *)p.Q, (const TI *)p.K, (const TI *)p.V, (TO *)p.O, p.sq, p.sk, p.sv,
-                       p.so, p.seqlens, p.H, p.B * p.H, p.n, p.causal, p.lambda, p.scale, (const float *)nullptr, 0,
+                       p.so, p.seqlens, p.H, nbh, p.n, p.causal, p.lambda, p.scale, (const float *)nullptr, 0,
                        (const float *)nullptr, 0, DECODE ? nullptr : p.lambda_rows, DECODE ? nullptr : p.rho,
-                       DECODE ? nullptr : p.delta);
+                       DECODE ? nullptr : p.delta, nqb, skip, da);
     return hipGetLastError();
 }
 
 template <int D, bool DECODE>
-hipError_t by_dtype(const Problem &p, int nrows)
+hipError_t by_dtype(const Problem &p)
 {
     if (p.in == LLLA_F32)
-        return p.out == LLLA_F32 ? launch<D, float, float, DECODE>(p, nrows) : launch<D, float, bf16_t, DECODE>(p, nrows);
-    return p.out == LLLA_F32 ? launch<D, bf16_t, float, DECODE>(p, nrows) : launch<D, bf16_t, bf16_t, DECODE>(p, nrows);
+        return p.out == LLLA_F32 ? launch<D, float, float, DECODE>(p) : launch<D, float, bf16_t, DECODE>(p);
+    return p.out == LLLA_F32 ? launch<D, bf16_t, float, DECODE>(p) : launch<D, bf16_t, bf16_t, DECODE>(p);
 }
 
 template <bool DECODE>
-hipError_t by_dim(const Problem &p, int nrows)
+hipError_t by_dim(const Problem &p)
 {
     switch (p.d) {
-        case 16: return by_dtype<16, DECODE>(p, nrows);
-        case 32: return by_dtype<32, DECODE>(p, nrows);
-        case 64: return by_dtype<64, DECODE>(p, nrows);
-        case 128: return by_dtype<128, DECODE>(p, nrows);
+        case 16: return by_dtype<16, DECODE>(p);
+        case 32: return by_dtype<32, DECODE>(p);
+        case 64: return by_dtype<64, DECODE>(p);
+        case 128: return by_dtype<128, DECODE>(p);
         default: return hipErrorInvalidValue;
     }
 }
@@ -399,18 +426,14 @@ hipError_t valu_forward_given(const Problem &p, int nrows, const float *M, int m
 
 hipError_t valu_forward(const Problem &p)
 {
-    if (dual_forward_rows(p) < p.n) {
-        const hipError_t e = by_dim<false>(p, p.n);
-        if (e != hipSuccess) return e;
-    }
-    return dual_forward(p);
+    return dual_forward_rows(p) < p.n ? by_dim<false>(p) : dual_forward(p);
 }
 
 hipError_t valu_decode(const Problem &p)
 {
     const bool all_short = p.n <= dual_max_keys(p.d);
     if (!all_short) {
-        const hipError_t e = by_dim<true>(p, 1);
+        const hipError_t e = by_dim<true>(p);
         if (e != hipSuccess || p.seqlens == nullptr) return e;      // without lengths every sequence is long
     }
     return dual_decode(p);

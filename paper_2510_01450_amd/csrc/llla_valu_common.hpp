@@ -2,6 +2,8 @@
 // fp32 / bf16 rows (bf16 is widened exactly), LDS tile staging, LDS dot products.
 #pragma once
 
+#include <utility>
+
 #include "llla_common.hpp"
 
 namespace llla {
@@ -84,6 +86,76 @@ __device__ inline float dot_lds(const float *a, const float *b)
         s2 = fmaf(x.z, y.z, s2); s3 = fmaf(x.w, y.w, s3);
     }
     return (s0 + s1) + (s2 + s3);
+}
+
+// Elimination of the augmented (D+1)x(D+1) system of a slot with NR right-hand sides, d = 16 and 32: a lane owns a row, in
+// registers, and the pivot row reaches the others by row broadcasts (d = 16: 16 lanes per slot, DPP) or through scalar
+// registers (d = 32: one wave per slot).  Through LDS, with a barrier per pivot, every element was a read-modify-write of LDS
+// behind the one before it: half the time of a call of 128 rows.  Same operations in the same order.
+//   S: [At | right-hand sides] in LDS, pitch LS, complete and synchronised; r: the lane's place in its slot
+//   y[j]: element 1 + r of solution j (r < D); y0[j]: its element 0
+template <int D, int K>
+__device__ __forceinline__ float row_value(float x)           // of lane K of the slot
+{
+    const int v = __builtin_bit_cast(int, x);
+    if constexpr (D == 16) return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xf, 0xf, true));
+    else return __builtin_bit_cast(float, __builtin_amdgcn_readlane(v, K));
+}
+
+template <int D, int K, int NR>
+__device__ __forceinline__ void eliminate_from(float (&a)[D], float (&b)[NR], int r)
+{
+    if constexpr (K < D - 1) {
+        const float pinv = 1.f / row_value<D, K>(a[K]);
+        const float f = r > K ? a[K] * pinv : 0.f;
+#pragma unroll
+        for (int c = K + 1; c < D; ++c) a[c] = fmaf(-f, row_value<D, K>(a[c]), a[c]);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) b[j] = fmaf(-f, row_value<D, K>(b[j]), b[j]);
+        eliminate_from<D, K + 1, NR>(a, b, r);
+    }
+}
+
+template <int D, int K, int NR>
+__device__ __forceinline__ void substitute_from(const float (&a)[D], float mu, float (&b)[NR], float (&b0)[NR], float (&y)[NR], int r)
+{
+    const float pivot = row_value<D, K>(a[K]), muk = row_value<D, K>(mu);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const float yk = row_value<D, K>(b[j]) / pivot;
+        y[j] = r == K ? yk : y[j];
+        b[j] = r < K ? fmaf(-a[K], yk, b[j]) : b[j];
+        b0[j] = fmaf(-muk, yk, b0[j]);
+    }
+    if constexpr (K > 0) substitute_from<D, K - 1, NR>(a, mu, b, b0, y, r);
+}
+
+template <int D, int... C>
+__device__ __forceinline__ void eliminate_intercept(float (&a)[D], float f, float mu, std::integer_sequence<int, C...>)
+{
+    ((a[C] = fmaf(-f, row_value<D, C>(mu), a[C])), ...);
+}
+
+template <int D, int NR>
+__device__ __forceinline__ void solve_in_registers(const float *S, int LS, int r, float (&y)[NR], float (&y0)[NR])
+{
+    constexpr int P = D + 1;
+    const int rr = r < D ? r : D - 1;
+    float a[D], b[NR], b0[NR];
+    const float *row = S + (1 + rr) * LS;
+    const float mu = row[0], omega = S[0];
+#pragma unroll
+    for (int c = 0; c < D; ++c) a[c] = row[1 + c];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) { b[j] = row[P + j]; b0[j] = S[P + j]; y[j] = 0.f; }
+    const float f = mu * (1.f / omega);
+    eliminate_intercept<D>(a, f, mu, std::make_integer_sequence<int, D>{});
+#pragma unroll
+    for (int j = 0; j < NR; ++j) b[j] = fmaf(-f, b0[j], b[j]);
+    eliminate_from<D, 0, NR>(a, b, r);
+    substitute_from<D, D - 1, NR>(a, mu, b, b0, y, r);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) y0[j] = b0[j] / omega;
 }
 
 }  // namespace valu
