@@ -321,8 +321,8 @@ __global__ __launch_bounds__(NT) void bwd_rows_kernel(const TI *__restrict__ Qg,
 // conditioned, u_i and the coefficients are large and cancel (dQ_0 is exactly 0 as the difference of two large
 // terms), and a 16-bit coefficient split is not enough there.  Those rows take these fp32 sweeps:
 //   MODE 0 (before the solve): r_i = sum_j w_ij gamma_ij [1; k_j] and the key that holds the row maximum;
-//   MODE 1 (after it):         dL/dlambda_i, the correction, dQ_i = u1_i + scale sum_j p^_ij k_j, and the row scalars
-//                              the key sweep reads.
+//   MODE 1 (after it):         dL/dlambda_i, the correction, dQ_i = u1_i + scale sum_j p^_ij k_j, and what the key sweep reads:
+//                              the row scalars, and y1 and -u1 as bf16 hi + lo in the place of the fp32 rows.
 // The row maxima come from the matrix-core sweep (log2 units), so that all kernels normalise a row alike.
 template <int D>
 struct RowCfg {
@@ -342,8 +342,7 @@ __global__ __launch_bounds__(NT) void bwd_rowsweep_kernel(const TI *__restrict__
                                                           llla_strides sg, int H, int n, int nrows, float scale,
                                                           float lambda, const float *__restrict__ LamRows,
                                                           const float *__restrict__ M, int mpitch,
-                                                          const float *__restrict__ Yv, const float *__restrict__ Uv,
-                                                          float *__restrict__ Rv, int vpitch, float *__restrict__ Sc,
+                                                          float *Yv, float *Uv, float *__restrict__ Rv, int vpitch, float *__restrict__ Sc,
                                                           float *__restrict__ dQ, float *__restrict__ dLam)
 {
     using C = RowCfg<D>;
@@ -395,7 +394,7 @@ __global__ __launch_bounds__(NT) void bwd_rowsweep_kernel(const TI *__restrict__
             rs[tid * 8 + 4] = jbits;
             if (i0 + tid < nrows) {
                 float *sc = Sc + row * 8;
-                sc[0] = y0; sc[1] = u0; sc[2] = m; sc[3] = corr; sc[4] = jbits;
+                sc[0] = y0; sc[1] = u0; sc[2] = M[(size_t)bh * mpitch + i]; sc[3] = corr; sc[4] = jbits;
                 if (dLam) dLam[row] = dl;
             }
         } else {
@@ -506,6 +505,20 @@ __global__ __launch_bounds__(NT) void bwd_rowsweep_kernel(const TI *__restrict__
                 *reinterpret_cast<float4 *>(qr + bc + x) =
                     make_float4(fmaf(scale, acc[x], u1s[bi * LDK + bc + x]), fmaf(scale, acc[x + 1], u1s[bi * LDK + bc + x + 1]),
                                 fmaf(scale, acc[x + 2], u1s[bi * LDK + bc + x + 2]), fmaf(scale, acc[x + 3], u1s[bi * LDK + bc + x + 3]));
+        }
+    }
+    if (MODE == 1) {                                     // (only this workgroup reads these rows of Yv and Uv: into LDS, above)
+        for (int idx = tid; idx < QT * D; idx += NT) {
+            const int rw = idx / D, c = idx % D;
+            if (i0 + rw >= nrows) continue;
+            const size_t row = (size_t)bh * n + i0 + rw;
+            bf16_t *yr = reinterpret_cast<bf16_t *>(Yv + row * vpitch), *ur = reinterpret_cast<bf16_t *>(Uv + row * vpitch);
+            const float y = y1s[rw * LDK + c], u = -u1s[rw * LDK + c];
+            const bf16_t yh = f32_to_bf16(y), uh = f32_to_bf16(u);
+            yr[c] = yh;
+            yr[D + c] = f32_to_bf16(y - bf16_to_f32(yh));
+            ur[c] = uh;
+            ur[D + c] = f32_to_bf16(u - bf16_to_f32(uh));
         }
     }
 }
@@ -691,8 +704,8 @@ hipError_t launch_early_rows(const BackwardProblem &p, const BackwardLayout &L, 
     using TI = bf16_t;
     char *base = static_cast<char *>(p.ws);
     const float *M = reinterpret_cast<const float *>(base + L.fwd + L.m);
-    const float *Y = reinterpret_cast<const float *>(base + L.fwd + L.y);
-    const float *U = reinterpret_cast<const float *>(base + L.u);
+    float *Y = reinterpret_cast<float *>(base + L.fwd + L.y);
+    float *U = reinterpret_cast<float *>(base + L.u);
     float *R = reinterpret_cast<float *>(base + L.r);
     float *Sc = reinterpret_cast<float *>(base + L.sc);
     dim3 grid((first + RowCfg<D>::QT - 1) / RowCfg<D>::QT, p.B * p.H);

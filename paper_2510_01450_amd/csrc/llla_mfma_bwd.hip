@@ -5,7 +5,8 @@
 // A wave owns 16 keys and walks over the query rows in steps of 32.  Per step, with C = A B on 16x16x32 bf16 MFMA:
 //   * four products of a [16 queries x d] row tile with the wave's key (or value) fragments give, in the accumulator
 //     layout (lane (g, nn): queries 4g..4g+3, key nn), the logits q_i.k_j, the linear forms y1_i.k_j and u1_i.k_j
-//     (y1, u1 as bf16 hi + lo) and gamma_ij = dO_i.v_j;
+//     (y1, u1 as bf16 hi + lo) and gamma_ij = dO_i.v_j; y0 and -u0 are the accumulators' starting values, and gamma joins
+//     the chain of -u1.k, so that w a and w (gamma - b) are one product each;
 //   * the vector ALU turns them into the three coefficient tiles s_ij, e_ij, scale p^_ij and splits each into
 //     bf16 hi + lo;
 //   * those registers are already the A operand of the second product family, whose contraction index is the query
@@ -13,6 +14,12 @@
 //     are the same row tiles read transposed by ds_read_tr16_b64 (lane nn gets four consecutive queries of feature
 //     16J+nn), so no tile is stored twice.
 // Accumulators stay in registers for the whole sweep; every output element is written once (no atomics).
+//
+// What bounds it: 64 MFMAs (1024 cycles) and some 200 vector instructions per step and wave, in a chain products -> coefficients ->
+// products, so the rest has to stay out of the way.  The dQ sweep leaves y1 and -u1 of every row split into bf16 hi and lo, in the
+// place of the fp32 rows (one split per row instead of one per row and block of 64 keys), which lets all six tiles of a step
+// arrive by DMA, at d = 64 one step ahead into a second buffer with one barrier per step.  Mask and correction of the maximum are
+// scalar branches.
 #include "llla_mfma_common.hpp"
 
 namespace llla {
@@ -36,10 +43,30 @@ __device__ inline bf16x8 tr_frag(const bf16_t *tile, int addr, int pitch)
     return __builtin_bit_cast(bf16x8, make_uint4(au.x, au.y, bu.x, bu.y));
 }
 
-__device__ inline void split_bf16(float x, __bf16 &hi, __bf16 &lo)
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+
+// x = hi + lo with both halves bf16, two values per conversion instruction
+__device__ inline void split_bf16(const float (&x)[8], bf16x8 &hi, bf16x8 &lo)
 {
-    hi = (__bf16)x;
-    lo = (__bf16)(x - (float)hi);
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+        const bf16x2v h = __builtin_convertvector(float2v{x[t], x[t + 1]}, bf16x2v);
+        const bf16x2v l = __builtin_convertvector(float2v{x[t] - (float)h[0], x[t + 1] - (float)h[1]}, bf16x2v);
+        hi[t] = h[0]; hi[t + 1] = h[1];
+        lo[t] = l[0]; lo[t + 1] = l[1];
+    }
+}
+
+// The tiles of the key sweep: rows of DD halves without padding (the DMA writes whole 1 KB wave rows), 16-byte chunk c of row r at
+// c ^ row_swizzle(r).  Sixteen rows read at one chunk land on 16 different chunk positions of the 64 banks (d = 64: two rows per
+// 256 bytes, so 8 positions for the rows of one parity), and the chunk pairs that a half-wave of a transposing read takes from 8
+// rows are disjoint.  Rows 16 apart share their swizzle.
+template <int DD>
+__device__ inline int row_swizzle(int r)
+{
+    if (DD == 64) { const int k = (r >> 1) & 7; return ((k & 3) << 1) | (k >> 2); }
+    return ((r & 7) << 1) | ((r >> 3) & 1);
 }
 
 template <int DD>
@@ -51,13 +78,13 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
 {
     using S = Shape<DD>;
     constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
-    // halves per row of an LDS tile: 32 B of padding, i.e. a row pitch of 40 (d = 64) or 72 (d = 128) banks, keeps the
-    // transposing reads of a half-wave (8 rows x 8 banks) on distinct banks; with 16 B of padding they collided and
-    // 42 % of the kernel's LDS cycles were bank conflicts
-    constexpr int P = DD + 16;
     constexpr int CH = DD / 8;                           // 16-byte chunks per row
-    __shared__ __align__(16) bf16_t qt[QS * P], gt[QS * P], yh[QS * P], yl[QS * P], uh[QS * P], ul[QS * P];
-    __shared__ float rs[QS][9];                          // y0, u0, m, correction, argmax of the step's rows (odd pitch)
+    constexpr int TILE = QS * DD;                        // halves
+    constexpr int NBUF = DD == 64 ? 2 : 1;               // three workgroups per compute unit with 50 KB each, or two (d = 128)
+    constexpr int RPT = 64 / CH, NTR = QS / RPT / 4;     // rows and number of a wave's transfers per tile
+    enum { TQ, TG, TYH, TYL, TUH, TUL, NTILE };          // u: -u1, both uses subtract it
+    __shared__ __align__(16) bf16_t tiles[NBUF][NTILE][TILE];
+    __shared__ __align__(16) float rs[NBUF][QS * 8];     // y0, u0, m (log2 units), correction, argmax of the step's rows
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     // A low key block sees the most rows (up to n/32 steps), the last one two steps.  Workgroups are dispatched
@@ -66,9 +93,11 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
     const int j0 = (int)blockIdx.y * 64;
     const int jk = j0 + 16 * wave + nn, jkc = min(jk, n - 1);
-    const bf16_t *Qh = Qg + b * sq.batch + h * sq.head;
-    const bf16_t *Gh = Gg + b * sg.batch + h * sg.head;
-    const float *Yh = Yg + (size_t)bh * n * YP, *Uh = Ug + (size_t)bh * n * YP, *Sh = Sc + (size_t)bh * n * 8;
+    const char *Qh = reinterpret_cast<const char *>(Qg + b * sq.batch + h * sq.head);
+    const char *Gh = reinterpret_cast<const char *>(Gg + b * sg.batch + h * sg.head);
+    const char *Yh = reinterpret_cast<const char *>(Yg + (size_t)bh * n * YP), *Uh = reinterpret_cast<const char *>(Ug + (size_t)bh * n * YP);
+    const float *Sh = Sc + (size_t)bh * n * 8;
+    const float cscale = scale * LOG2E;
 
     bf16x8 kf[NF], vf[NF];
     {
@@ -83,102 +112,127 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
     f32x4 dv[NB], dk[NB];
 #pragma unroll
     for (int J = 0; J < NB; ++J) dv[J] = dk[J] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int tr_addr = (4 * g + (nn >> 2)) * P + 4 * (nn & 3);      // + 16 J
-
-    for (int it0 = j0; it0 < n; it0 += QS) {
-        __syncthreads();                                 // the previous step's tiles are consumed
-        for (int idx = tid; idx < QS * CH; idx += 256) {
-            const int row = idx / CH, ch = (idx % CH) * 8, i = it0 + row;
-            u32x4 qv = {0u, 0u, 0u, 0u}, gv = qv;
-            f32x4 ya = {0.f, 0.f, 0.f, 0.f}, yb = ya, ua = ya, ub = ya;
-            if (i < n) {
-                qv = *reinterpret_cast<const u32x4 *>(Qh + (int64_t)i * sq.seq + ch);
-                gv = *reinterpret_cast<const u32x4 *>(Gh + (int64_t)i * sg.seq + ch);
-                ya = *reinterpret_cast<const f32x4 *>(Yh + (size_t)i * YP + ch);
-                yb = *reinterpret_cast<const f32x4 *>(Yh + (size_t)i * YP + ch + 4);
-                ua = *reinterpret_cast<const f32x4 *>(Uh + (size_t)i * YP + ch);
-                ub = *reinterpret_cast<const f32x4 *>(Uh + (size_t)i * YP + ch + 4);
-            }
-            bf16x8 y_hi, y_lo, u_hi, u_lo;
+    int row_addr[NF], tr_addr[NB];                       // operand reads: rows (+ 16 s DD), columns
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                __bf16 hi, lo;
-                split_bf16(t < 4 ? ya[t & 3] : yb[t & 3], hi, lo);
-                y_hi[t] = hi; y_lo[t] = lo;
-                split_bf16(-(t < 4 ? ua[t & 3] : ub[t & 3]), hi, lo);      // the tiles hold -u1: both uses subtract it
-                u_hi[t] = hi; u_lo[t] = lo;
-            }
-            *reinterpret_cast<u32x4 *>(&qt[row * P + ch]) = qv;
-            *reinterpret_cast<u32x4 *>(&gt[row * P + ch]) = gv;
-            *reinterpret_cast<bf16x8 *>(&yh[row * P + ch]) = y_hi;
-            *reinterpret_cast<bf16x8 *>(&yl[row * P + ch]) = y_lo;
-            *reinterpret_cast<bf16x8 *>(&uh[row * P + ch]) = u_hi;
-            *reinterpret_cast<bf16x8 *>(&ul[row * P + ch]) = u_lo;
+    for (int f = 0; f < NF; ++f) row_addr[f] = nn * DD + (((g + 4 * f) ^ row_swizzle<DD>(nn)) * 8);
+    {
+        const int r = 4 * g + (nn >> 2);
+#pragma unroll
+        for (int J = 0; J < NB; ++J) tr_addr[J] = r * DD + (((2 * J + ((nn & 3) >> 1)) ^ row_swizzle<DD>(r)) * 8) + (nn & 1) * 4;
+    }
+
+    // transfer t of wave w fills rows RPT (NTR w + t) ..; rows past the end repeat the last one (their coefficients are zero)
+    auto issue = [&](int buf, int it0) {
+#pragma unroll
+        for (int t = 0; t < NTR; ++t) {
+            const int r0 = RPT * (NTR * wave + t), r = r0 + lane / CH;
+            const int64_t i = min(it0 + r, n - 1);
+            const int col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+            const char *y = Yh + i * (YP * 4) + col, *u = Uh + i * (YP * 4) + col;
+            dma16(Qh + i * sq.seq * 2 + col, &tiles[buf][TQ][r0 * DD]);
+            dma16(Gh + i * sg.seq * 2 + col, &tiles[buf][TG][r0 * DD]);
+            dma16(y, &tiles[buf][TYH][r0 * DD]);
+            dma16(y + 2 * DD, &tiles[buf][TYL][r0 * DD]);
+            dma16(u, &tiles[buf][TUH][r0 * DD]);
+            dma16(u + 2 * DD, &tiles[buf][TUL][r0 * DD]);
         }
-        {
-            const int row = tid / 8, c = tid % 8;
-            rs[row][c] = (it0 + row < n && c < 5) ? Sh[(size_t)(it0 + row) * 8 + c] : 0.f;
+        if (wave == 0) dma16(Sh + (size_t)min(it0 + (lane >> 1), n - 1) * 8 + 4 * (lane & 1), rs[buf]);
+    };
+
+    if (NBUF == 2) issue(0, j0);
+    for (int it0 = j0, c = 0; it0 < n; it0 += QS, ++c) {
+        const int buf = NBUF == 2 ? c & 1 : 0;
+        if (NBUF == 1) {
+            __syncthreads();                             // the previous step's tiles are consumed
+            issue(0, it0);
         }
-        __syncthreads();
+        dma_wait();
+        __syncthreads();                                 // this step has arrived (NBUF 2: and the previous one is consumed)
+        if (NBUF == 2 && it0 + QS < n) issue(buf ^ 1, it0 + QS);
+        const bf16_t *qt = tiles[buf][TQ], *gt = tiles[buf][TG], *yh = tiles[buf][TYH], *yl = tiles[buf][TYL];
+        const bf16_t *uh = tiles[buf][TUH], *ul = tiles[buf][TUL];
 
         // ---- coefficients: lane (g, nn) holds the pairs (query it0 + 16s + 4g + r, key jk) --------------------
-        bf16x8 s_hi, s_lo, e_hi, e_lo, p_hi, p_lo;
+        const bool masked = it0 < j0 + 16 * wave + 15 || it0 + QS > n;
+        float sv_[8], ev_[8], pv_[8];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            f32x4 st = {0.f, 0.f, 0.f, 0.f}, at = st, bt = st, gm = st;
-            const int arow = (16 * s + nn) * P + 8 * g;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const bf16x8 qf = *reinterpret_cast<const bf16x8 *>(&qt[arow + 32 * f]);
-                const bf16x8 gf = *reinterpret_cast<const bf16x8 *>(&gt[arow + 32 * f]);
-                const bf16x8 yhf = *reinterpret_cast<const bf16x8 *>(&yh[arow + 32 * f]);
-                const bf16x8 ylf = *reinterpret_cast<const bf16x8 *>(&yl[arow + 32 * f]);
-                const bf16x8 uhf = *reinterpret_cast<const bf16x8 *>(&uh[arow + 32 * f]);
-                const bf16x8 ulf = *reinterpret_cast<const bf16x8 *>(&ul[arow + 32 * f]);
-                st = mfma_bf16(qf, kf[f], st);
-                gm = mfma_bf16(gf, vf[f], gm);
-                at = mfma_bf16(ylf, kf[f], at);
-                at = mfma_bf16(yhf, kf[f], at);
-                bt = mfma_bf16(ulf, kf[f], bt);
-                bt = mfma_bf16(uhf, kf[f], bt);
-            }
+            f32x4 st = {0.f, 0.f, 0.f, 0.f}, at, et;
+            float m[4], corr[4];
+            int jstar[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int qr = 16 * s + 4 * g + r, i = it0 + qr;
-                const float y0 = rs[qr][0], u0 = rs[qr][1], m = rs[qr][2], corr = rs[qr][3];
-                const int jstar = __float_as_int(rs[qr][4]);
-                const bool valid = (jk <= i) && (i < n);
-                const float w = __builtin_amdgcn_exp2f((scale * st[r] - m) * LOG2E);
-                const float a = y0 + at[r];
-                const float ev = w * (gm[r] - u0 + bt[r]);       // bt = -u1.k
-                float pv = a * ev;
-                pv = (jk == jstar) ? pv + corr : pv;
-                __bf16 hi, lo;
-                split_bf16(valid ? w * a : 0.f, hi, lo);
-                s_hi[4 * s + r] = hi; s_lo[4 * s + r] = lo;
-                split_bf16(valid ? ev : 0.f, hi, lo);
-                e_hi[4 * s + r] = hi; e_lo[4 * s + r] = lo;
-                split_bf16(valid ? scale * pv : 0.f, hi, lo);
-                p_hi[4 * s + r] = hi; p_lo[4 * s + r] = lo;
+                const float *row = &rs[buf][(16 * s + 4 * g + r) * 8];
+                const f32x4 s4 = *reinterpret_cast<const f32x4 *>(row);
+                at[r] = s4[0];
+                et[r] = -s4[1];
+                m[r] = s4[2];
+                corr[r] = s4[3];
+                jstar[r] = __float_as_int(row[4]);
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const int ar = row_addr[f] + 16 * s * DD;
+                const bf16x8 qf = *reinterpret_cast<const bf16x8 *>(qt + ar);
+                const bf16x8 gf = *reinterpret_cast<const bf16x8 *>(gt + ar);
+                const bf16x8 yhf = *reinterpret_cast<const bf16x8 *>(yh + ar);
+                const bf16x8 ylf = *reinterpret_cast<const bf16x8 *>(yl + ar);
+                const bf16x8 uhf = *reinterpret_cast<const bf16x8 *>(uh + ar);
+                const bf16x8 ulf = *reinterpret_cast<const bf16x8 *>(ul + ar);
+                st = mfma_bf16(qf, kf[f], st);
+                at = mfma_bf16(ylf, kf[f], at);
+                et = mfma_bf16(ulf, kf[f], et);
+                at = mfma_bf16(yhf, kf[f], at);
+                et = mfma_bf16(uhf, kf[f], et);
+                et = mfma_bf16(gf, vf[f], et);           // gamma - u0 - u1.k
+            }
+            bool star = false;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float w = __builtin_amdgcn_exp2f(fmaf(st[r], cscale, -m[r]));
+                sv_[4 * s + r] = w * at[r];
+                ev_[4 * s + r] = w * et[r];
+                pv_[4 * s + r] = sv_[4 * s + r] * et[r];
+                star = star || jk == jstar[r];
+            }
+            if (__any(star)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pv_[4 * s + r] += jk == jstar[r] ? corr[r] : 0.f;
             }
         }
+        if (masked) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int i = it0 + 16 * (t >> 2) + 4 * g + (t & 3);
+                const bool valid = jk <= i && i < n;
+                sv_[t] = valid ? sv_[t] : 0.f;
+                ev_[t] = valid ? ev_[t] : 0.f;
+                pv_[t] = valid ? pv_[t] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) pv_[t] *= scale;
+        bf16x8 s_hi, s_lo, e_hi, e_lo, p_hi, p_lo;
+        split_bf16(sv_, s_hi, s_lo);
+        split_bf16(ev_, e_hi, e_lo);
+        split_bf16(pv_, p_hi, p_lo);
 
         // ---- accumulate over the step's 32 queries --------------------------------------------------------------
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
-            const int ta = tr_addr + 16 * J;
-            const bf16x8 gT = tr_frag(gt, ta, P);
+            const int ta = tr_addr[J];
+            const bf16x8 gT = tr_frag(gt, ta, DD);
             dv[J] = mfma_bf16(s_lo, gT, dv[J]);
-            dv[J] = mfma_bf16(s_hi, gT, dv[J]);
-            const bf16x8 yhT = tr_frag(yh, ta, P), ylT = tr_frag(yl, ta, P);
+            const bf16x8 yhT = tr_frag(yh, ta, DD), ylT = tr_frag(yl, ta, DD);
             dk[J] = mfma_bf16(e_lo, yhT, dk[J]);
+            dv[J] = mfma_bf16(s_hi, gT, dv[J]);
             dk[J] = mfma_bf16(e_hi, ylT, dk[J]);
             dk[J] = mfma_bf16(e_hi, yhT, dk[J]);
-            const bf16x8 uhT = tr_frag(uh, ta, P), ulT = tr_frag(ul, ta, P);
+            const bf16x8 uhT = tr_frag(uh, ta, DD), ulT = tr_frag(ul, ta, DD);
             dk[J] = mfma_bf16(s_lo, uhT, dk[J]);
             dk[J] = mfma_bf16(s_hi, ulT, dk[J]);
             dk[J] = mfma_bf16(s_hi, uhT, dk[J]);
-            const bf16x8 qT = tr_frag(qt, ta, P);
+            const bf16x8 qT = tr_frag(qt, ta, DD);
             dk[J] = mfma_bf16(p_lo, qT, dk[J]);
             dk[J] = mfma_bf16(p_hi, qT, dk[J]);
         }
@@ -206,8 +260,9 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
 // which is the A operand of a product that contracts over keys, with the K tile read transposed as B.
 //   MODE 0 (before the solve): c_ij = w_ij gamma_ij;  r1_i = sum_j c_ij k_j, r0_i = sum_j c_ij, and the first key that
 //                              attains the row maximum (the logits are produced exactly as in the row-maximum sweep);
-//   MODE 1 (after it):         dL/dlambda_i = -u1_i.y1_i, c_ij = p^_ij;  dQ_i = u1_i + scale sum_j c_ij k_j, and the row
-//                              scalars (y0, u0, m, correction, argmax) the key sweep reads.
+//   MODE 1 (after it):         dL/dlambda_i = -u1_i.y1_i, c_ij = p^_ij;  dQ_i = u1_i + scale sum_j c_ij k_j, and what the key
+//                              sweep reads: the row scalars (y0, u0, m in log2 units, correction, argmax) and, in the place of the
+//                              fp32 rows, y1 and -u1 as bf16 hi (DD halves) and lo.
 // Rows [first_row, n) only: the first rows of a sequence take fp32 sweeps (their coefficients cancel too strongly for
 // a 16-bit split).
 template <int DD, int MODE>
@@ -215,12 +270,13 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
     int first_row, int mpitch, float scale, float lambda, const float *__restrict__ LamRows, const float *__restrict__ Mg,
-    const float *__restrict__ Yg, const float *__restrict__ Ug, float *__restrict__ Rv, float *__restrict__ Sc,
-    float *__restrict__ dQ, float *__restrict__ dLam)
+    float *Yg, float *Ug, float *__restrict__ Rv, float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam)
 {
     using S = Shape<DD>;
     constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
-    constexpr int P = DD + 16, CH = DD / 8;          // row pitch as in the key sweep
+    // halves per row of an LDS tile: 32 B of padding, i.e. a row pitch of 40 (d = 64) or 72 (d = 128) banks, keeps the
+    // transposing reads of a half-wave (8 rows x 8 banks) on distinct banks
+    constexpr int P = DD + 16, CH = DD / 8;
     __shared__ __align__(16) bf16_t kt[KB * P], vt[KB * P];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
@@ -253,23 +309,24 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
         jstar = __float_as_int(Rv[row * YP + DD + 1]);
         float dl = 0.f;
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
+        for (int f = 0; f < NF; ++f) {
+            float yv[8], uv[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const float yv = yr[32 * f + 8 * g + t], uv = ur[32 * f + 8 * g + t];
-                dl = fmaf(-uv, yv, dl);
-                __bf16 hi, lo;
-                split_bf16(yv, hi, lo);
-                yhf[f][t] = hi; ylf[f][t] = lo;
-                split_bf16(uv, hi, lo);
-                uhf[f][t] = hi; ulf[f][t] = lo;
+                yv[t] = yr[32 * f + 8 * g + t];
+                const float u = ur[32 * f + 8 * g + t];
+                dl = fmaf(-u, yv[t], dl);
+                uv[t] = -u;
             }
+            split_bf16(yv, yhf[f], ylf[f]);
+            split_bf16(uv, uhf[f], ulf[f]);
+        }
         dl += __shfl_xor(dl, 16);
         dl += __shfl_xor(dl, 32);
         corr = (LamRows ? LamRows[row] : lambda) * dl;
         if (g == 0 && iq < n) {
             float *sc = Sc + row * 8;
-            sc[0] = y0; sc[1] = u0; sc[2] = mrow * 0.6931471805599453f; sc[3] = corr; sc[4] = __int_as_float(jstar);
+            sc[0] = y0; sc[1] = u0; sc[2] = mrow; sc[3] = corr; sc[4] = __int_as_float(jstar);
             if (dLam) dLam[row] = dl;
         }
     }
@@ -277,6 +334,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
 #pragma unroll
     for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
     float csum = 0.f, best = -INFINITY;
+    const float near = mrow - (1e-4f * fabsf(mrow) + 1e-30f);
     int arg = 0;
     const int tr_addr = (4 * g + (nn >> 2)) * P + 4 * (nn & 3);
 
@@ -306,49 +364,60 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
         }
         __syncthreads();
         if (c + 1 < nblk) fetch(c + 1);
-        bf16x8 c_hi, c_lo;
+        // only the blocks that reach past the wave's first query need the causal mask
+        const bool masked = c * KB + KB - 1 > i0 + 16 * wave;
+        float cv[8];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            f32x4 st = {0.f, 0.f, 0.f, 0.f}, gm = st, at = st, bt = st;
+            f32x4 st = {0.f, 0.f, 0.f, 0.f}, et = {-u0, -u0, -u0, -u0}, at = {y0, y0, y0, y0};      // MODE 0: y0 = u0 = 0
             const int arow = (16 * s + nn) * P + 8 * g;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 const bf16x8 kfr = *reinterpret_cast<const bf16x8 *>(&kt[arow + 32 * f]);
                 const bf16x8 vfr = *reinterpret_cast<const bf16x8 *>(&vt[arow + 32 * f]);
                 st = mfma_bf16(kfr, qf[f], st);
-                gm = mfma_bf16(vfr, gf[f], gm);
                 if (MODE == 1) {
                     at = mfma_bf16(kfr, ylf[f], at);
+                    et = mfma_bf16(kfr, ulf[f], et);
                     at = mfma_bf16(kfr, yhf[f], at);
-                    bt = mfma_bf16(kfr, ulf[f], bt);
-                    bt = mfma_bf16(kfr, uhf[f], bt);
+                    et = mfma_bf16(kfr, uhf[f], et);
                 }
+                et = mfma_bf16(vfr, gf[f], et);
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int j = c * KB + 16 * s + 4 * g + r;
-                const bool valid = (j <= iq) && (iq < n);
-                const float lg = st[r] * cscale;
-                const float w = __builtin_amdgcn_exp2f(lg - mrow);
-                float cv;
-                if (MODE == 0) {
-                    if (valid && lg > best) {
-                        best = lg;
-                        arg = j;
+                const float w = __builtin_amdgcn_exp2f(fmaf(st[r], cscale, -mrow));
+                cv[4 * s + r] = MODE == 0 ? w * et[r] : w * at[r] * et[r];
+            }
+            const int jb = c * KB + 16 * s + 4 * g;
+            if (MODE == 0) {
+                // the first key at the row maximum: only a tile that comes near the maximum is looked at
+                const float top = fmaxf(fmaxf(st[0] * cscale, st[1] * cscale), fmaxf(st[2] * cscale, st[3] * cscale));
+                if (__any(top >= near)) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float lg = st[r] * cscale;
+                        if (jb + r <= iq && iq < n && lg > best) {
+                            best = lg;
+                            arg = jb + r;
+                        }
                     }
-                    cv = valid ? w * gm[r] : 0.f;
-                    csum += cv;
-                } else {
-                    cv = w * (y0 + at[r]) * (gm[r] - u0 - bt[r]);
-                    cv = (j == jstar) ? cv + corr : cv;
-                    cv = valid ? cv : 0.f;
                 }
-                __bf16 hi, lo;
-                split_bf16(cv, hi, lo);
-                c_hi[4 * s + r] = hi;
-                c_lo[4 * s + r] = lo;
+            } else if (__any((unsigned)(jstar - jb) < 4u)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) cv[4 * s + r] += jb + r == jstar ? corr : 0.f;
             }
         }
+        if (masked) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) cv[t] = c * KB + 16 * (t >> 2) + 4 * g + (t & 3) <= iq ? cv[t] : 0.f;
+        }
+        if (MODE == 0) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) csum += cv[t];
+        }
+        bf16x8 c_hi, c_lo;
+        split_bf16(cv, c_hi, c_lo);
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
             const bf16x8 kT = tr_frag(kt, tr_addr + 16 * J, P);
@@ -387,6 +456,19 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
             }
         }
     }
+    if (MODE == 1) {
+        __syncthreads();                                 // the fp32 rows have been read for the last time
+        if (iq < n) {
+            bf16_t *yr = reinterpret_cast<bf16_t *>(Yg + row * YP), *ur = reinterpret_cast<bf16_t *>(Ug + row * YP);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                *reinterpret_cast<bf16x8 *>(yr + 32 * f + 8 * g) = yhf[f];
+                *reinterpret_cast<bf16x8 *>(yr + DD + 32 * f + 8 * g) = ylf[f];
+                *reinterpret_cast<bf16x8 *>(ur + 32 * f + 8 * g) = uhf[f];
+                *reinterpret_cast<bf16x8 *>(ur + DD + 32 * f + 8 * g) = ulf[f];
+            }
+        }
+    }
 }
 
 template <int DD, int MODE>
@@ -394,8 +476,8 @@ hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int fi
 {
     char *base = static_cast<char *>(p.ws);
     const float *M = reinterpret_cast<const float *>(base + L.fwd + L.m);
-    const float *Y = reinterpret_cast<const float *>(base + L.fwd + L.y);
-    const float *U = reinterpret_cast<const float *>(base + L.u);
+    float *Y = reinterpret_cast<float *>(base + L.fwd + L.y);
+    float *U = reinterpret_cast<float *>(base + L.u);
     float *R = reinterpret_cast<float *>(base + L.r);
     float *Sc = reinterpret_cast<float *>(base + L.sc);
     hipLaunchKernelGGL((bwd_rows_mfma_kernel<DD, MODE>), dim3(p.B * p.H, (p.n - first_row + 63) / 64), dim3(256), 0, p.stream,
