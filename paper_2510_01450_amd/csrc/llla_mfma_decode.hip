@@ -31,7 +31,7 @@ constexpr int TILE_H = STEP * D;               // halves of one natural [32 keys
 constexpr int STAGE_H = 2 * TILE_H;            // K tile + V tile
 constexpr int DMA_PER_STAGE = 8;
 constexpr int REC_F = DecShape<D>::REC_F;      // floats per record
-constexpr int KEYS_MIN = 256;                  // fewest keys worth a workgroup
+constexpr int KEYS_FEW = 256, KEYS_MIN = 512;  // fewest keys worth a workgroup (see make_split)
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MAX_SPLIT = 16;                  // most workgroups per head
 constexpr int MIN_L = 256;                     // shorter caches go to the vector path
@@ -51,11 +51,17 @@ int record_room(int bh, int L)
     return nparts > 16 ? nparts + (nparts + group - 1) / group : nparts;
 }
 
-// Workgroups per head: as many as fill the GPU in one round, none with fewer than KEYS_MIN keys
+// Workgroups per head.  A record costs the merge half a microsecond (one workgroup reads a head's records, 27 KB each), 256 further
+// keys cost a workgroup 1.2, and two workgroups on a compute unit slow each other down: as many as fill the GPU, with 256 keys or
+// more, but 512 or more where there would be more than eight per head or more than one per compute unit; below 1024 keys one,
+// which solves the head itself.  us with 256 / 512 keys: 16 heads x 4096 31.2 / 28.4 (1024 keys: 32.9), 32 x 4096 37.2 / 30.1,
+// 64 x 2048 33.1 / 29.8, 128 x 1024 32.8 / 29.7; 4 x 2048 23.3 / 25.0, 16 x 1024 23.1 / 24.8; 32 x 600 24.6, one workgroup 20.8.
 int make_split(int bh, int L)
 {
-    const int want = (SLOTS + bh - 1) / bh, most = std::max(L / KEYS_MIN, 1);
-    return std::min(std::min(want, most), std::min(MAX_SPLIT, record_room(bh, L)));
+    const int want = (SLOTS + bh - 1) / bh, room = std::min(MAX_SPLIT, record_room(bh, L));
+    int n = std::min(std::min(want, L / KEYS_FEW), room);
+    if (n > 8 || n * bh > SLOTS / 2 || L < 2 * KEYS_MIN) n = std::min(n, L / KEYS_MIN);
+    return std::max(n, 1);
 }
 
 // two bf16 packed in a dword -> two f16 packed (exact for values in the f16 range)
