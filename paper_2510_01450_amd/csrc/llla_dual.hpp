@@ -59,7 +59,9 @@ template <int D, int MAX_KEYS = (D < DUAL_MAX_KEYS ? D : DUAL_MAX_KEYS)>
 struct DualShared {
     static constexpr int MK = MAX_KEYS;
     double G[MK * (MK + 1) / 2];                   // lower triangle of G' + lambda I, then its Cholesky factor
-    double u[64], kq[MK + 1], rd[MK];
+    double u[64], kq[MK + 1];
+    double y[MK];                                  // u as one more row of the factorisation: L^{-1} u
+    double rd[MK], ld[MK / 4][6];                  // diagonal blocks of L: reciprocal diagonal, entries 10, 20, 30, 21, 31, 32
     double ut;
     float ks[(MK + 1) * (D + 1)];                  // visible keys, pitch D + 1; the query as one more row
 };
@@ -89,6 +91,7 @@ __device__ __forceinline__ void dual_row(Shared &sm, const TI *qrow, const TI *K
     auto &u = sm.u;
     auto &kq = sm.kq;
     auto &rd = sm.rd;
+    auto &y = sm.y;
     const int tid = threadIdx.x;
     const int m4 = (m + 3) & ~3;                   // the system is padded with identity rows to a multiple of 4
     constexpr int pitch = d + 1;
@@ -166,11 +169,12 @@ __device__ __forceinline__ void dual_row(Shared &sm, const TI *qrow, const TI *K
             }
             G[tri(j, l)] = g;
         }
+    if (tid < MK) y[tid] = u[tid];                 // zero from m on
     __syncthreads();
 
-    // Cholesky G' + lambda I = L L^T in place, four columns per step (two barriers per step instead of per column):
-    // every thread factorises the 4 x 4 diagonal block in registers and inverts its factor; one thread per row below
-    // solves the row's four entries of the panel; all threads share the rank-4 update of what is left.
+    // Cholesky G' + lambda I = L L^T in place, four columns per step (two barriers per step): every thread factorises the 4 x 4
+    // diagonal block in registers; one thread per row below solves the row's four entries of the panel; all threads share
+    // the rank-4 update of what is left.  u rides along as one more row, which turns it into L^{-1} u.
     for (int k0 = 0; k0 < m4; k0 += 4) {
         double a00 = G[tri(k0, k0)], a10 = G[tri(k0 + 1, k0)], a11 = G[tri(k0 + 1, k0 + 1)], a20 = G[tri(k0 + 2, k0)],
                a21 = G[tri(k0 + 2, k0 + 1)], a22 = G[tri(k0 + 2, k0 + 2)], a30 = G[tri(k0 + 3, k0)],
@@ -186,20 +190,22 @@ __device__ __forceinline__ void dual_row(Shared &sm, const TI *qrow, const TI *K
         const double l32 = a32 * r2;
         a33 -= l32 * l32;
         const double r3 = rsqrt_f64(a33);
-        __syncthreads();                           // everybody has read the diagonal block
         if (tid == 0) {
             rd[k0] = r0; rd[k0 + 1] = r1; rd[k0 + 2] = r2; rd[k0 + 3] = r3;
-            G[tri(k0 + 1, k0)] = l10; G[tri(k0 + 2, k0)] = l20; G[tri(k0 + 3, k0)] = l30;
-            G[tri(k0 + 2, k0 + 1)] = l21; G[tri(k0 + 3, k0 + 1)] = l31; G[tri(k0 + 3, k0 + 2)] = l32;
+            double *ld = sm.ld[k0 / 4];
+            ld[0] = l10; ld[1] = l20; ld[2] = l30; ld[3] = l21; ld[4] = l31; ld[5] = l32;
         }
         // panel: row j of L in columns k0..k0+3 solves x L_d^T = G[j][k0..k0+3] (forward substitution along the row)
-        for (int j = k0 + 4 + tid; j < m4; j += DUAL_NT) {
-            const double g0 = G[tri(j, k0)], g1 = G[tri(j, k0 + 1)], g2 = G[tri(j, k0 + 2)], g3 = G[tri(j, k0 + 3)];
+        const int j = k0 + 4 + tid;                // m4 - k0 - 4 <= 60 rows, and the row of u
+        if (j < m4 || tid == DUAL_NT - 1) {
+            const bool border = tid == DUAL_NT - 1;
+            double *row = border ? &y[k0] : &G[tri(j, k0)];
+            const double g0 = row[0], g1 = row[1], g2 = row[2], g3 = row[3];
             const double x0 = g0 * r0;
             const double x1 = (g1 - x0 * l10) * r1;
             const double x2 = (g2 - x0 * l20 - x1 * l21) * r2;
             const double x3 = (g3 - x0 * l30 - x1 * l31 - x2 * l32) * r3;
-            G[tri(j, k0)] = x0; G[tri(j, k0 + 1)] = x1; G[tri(j, k0 + 2)] = x2; G[tri(j, k0 + 3)] = x3;
+            row[0] = x0; row[1] = x1; row[2] = x2; row[3] = x3;
         }
         __syncthreads();
         for (int j = k0 + 4 + ty; j < m4; j += 16) {
@@ -207,24 +213,28 @@ __device__ __forceinline__ void dual_row(Shared &sm, const TI *qrow, const TI *K
             for (int l = k0 + 4 + tx; l <= j; l += 16)
                 G[tri(j, l)] -= j0 * G[tri(l, k0)] + j1 * G[tri(l, k0 + 1)] + j2 * G[tri(l, k0 + 2)] + j3 * G[tri(l, k0 + 3)];
         }
+        if (ty == 15) {
+            for (int l = k0 + 4 + tx; l < m4; l += 16)
+                y[l] -= y[k0] * G[tri(l, k0)] + y[k0 + 1] * G[tri(l, k0 + 1)] + y[k0 + 2] * G[tri(l, k0 + 2)] + y[k0 + 3] * G[tri(l, k0 + 3)];
+        }
         __syncthreads();
     }
 
-    // t = (L L^T)^{-1} u.  Both substitutions in the first wave, lane j owning element j (m4 <= 64): at step k the owner
-    // of element k finishes it (a scalar broadcast of its value) and every later (earlier) element takes its update,
-    // one column of L per step; the other waves wait at the barrier below.
+    // L^T t = y in the first wave, lane j owning element j (m4 <= 64), four elements per step: every lane solves the diagonal block
+    // for the four values (scalar broadcasts), every earlier element takes its update.
     if (tid < 64) {
         const int j = tid;
-        double s = (j < m) ? u[j] : 0.0;
-        for (int k = 0; k < m4; ++k) {                      // L y = u
-            const double yk = lane_value(s, k) * rd[k];
-            if (j == k) s = yk;
-            else if (j > k && j < m4) s -= G[tri(j, k)] * yk;
-        }
-        for (int k = m4 - 1; k >= 0; --k) {                 // L^T t = y
-            const double tk = lane_value(s, k) * rd[k];
-            if (j == k) s = tk;
-            else if (j < k) s -= G[tri(k, j)] * tk;
+        double s = (j < m4) ? y[j] : 0.0;
+        for (int k0 = m4 - 4; k0 >= 0; k0 -= 4) {
+            const double *ld = sm.ld[k0 / 4];
+            const int jj = j < k0 ? j : 0;
+            const double g0 = G[tri(k0, jj)], g1 = G[tri(k0 + 1, jj)], g2 = G[tri(k0 + 2, jj)], g3 = G[tri(k0 + 3, jj)];
+            const double t3 = lane_value(s, k0 + 3) * rd[k0 + 3];
+            const double t2 = (lane_value(s, k0 + 2) - ld[5] * t3) * rd[k0 + 2];
+            const double t1 = (lane_value(s, k0 + 1) - ld[3] * t2 - ld[4] * t3) * rd[k0 + 1];
+            const double t0 = (lane_value(s, k0) - ld[0] * t1 - ld[1] * t2 - ld[2] * t3) * rd[k0];
+            if (j < k0) s -= g0 * t0 + g1 * t1 + g2 * t2 + g3 * t3;
+            else if (j < k0 + 4) s = j == k0 ? t0 : j == k0 + 1 ? t1 : j == k0 + 2 ? t2 : t3;
         }
         const double ujt = (j < m) ? u[j] * s : 0.0;        // u_j t_j: output weight s_j = u_j t_j / (u . t)
         double ut = ujt;
