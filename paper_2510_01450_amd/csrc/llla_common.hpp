@@ -51,7 +51,7 @@ hipError_t valu_forward_given(const Problem &p, int nrows, const float *M, int m
 hipError_t valu_decode(const Problem &p);
 
 // Queries that see at most dual_max_keys(d) = min(d, DUAL_MAX_KEYS) keys: fp64, key-space form of the same minimiser
-// (llla_dual.hip).  dual_forward() serves rows [0, dual_forward_rows(p)) of a forward call (O, and rho / delta when
+// (llla_dual.hpp).  dual_forward() serves rows [0, dual_forward_rows(p)) of a forward call (O, and rho / delta when
 // asked for); dual_decode() serves the sequences of a decode call that are short enough and leaves the others alone.
 constexpr int DUAL_MAX_KEYS = 64;
 int dual_max_keys(int d);
@@ -94,6 +94,7 @@ hipError_t mfma_forward(const Problem &p);
 bool mfma_forward_f32_supported(int d, bool causal);
 size_t mfma_forward_f32_workspace_bytes(int B, int H, int n);
 hipError_t mfma_forward_f32(const Problem &p);
+hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y, int skip);      // its output sweep, rows from skip on
 // head dimensions 16 and 32 (bf16 or fp32): the d = 64 matrix-core forward on zero-padded copies (llla_pad.hip)
 bool padded_forward_supported(int d, llla_dtype in);
 size_t padded_forward_workspace_bytes(int B, int H, int n, int d, llla_dtype in);

@@ -6,14 +6,15 @@
 //   dQ sweep  p^_ij, dQ_i, dlambda_i and the scalars of row i that the key sweep reads;
 //   key sweep dK_j, dV_j.
 //
-// What bounds it: the fp32 matrix rate (1/16 of the 16-bit one).  A tile of 16 queries x 16 keys costs 48 + 656 + 80 + 128
-// MFMAs of 32 cycles in the four stages, and the factorisations come on top.  The vector kernels spend d^2 multiply-adds per
-// pair on the vector ALU, at less than half the matrix rate and out of LDS, and eliminate a (d+1)^2 system with one barrier
-// per pivot.  16 heads x 1024 rows: 2811 us on the vector kernels, 727 here; 2 x 128: 207 and 82; 4 x 2000: 2637 and 1096.
+// What bounds it: the sweeps the fp32 matrix rate (1/16 of the 16-bit one; a tile of 16 queries x 16 keys costs 48 + 80 + 128 MFMAs of
+// 32 cycles in the three of them), the moments see llla_mfma_fwd_f32.hip.  The vector kernels spend d^2 multiply-adds per pair on
+// the vector ALU, out of LDS, and eliminate a (d+1)^2 system with one barrier per pivot.  16 heads x 1024 rows: 2811 us on the
+// vector kernels, 513 here; 2 x 128: 207 and 82.
 //
-// The three sweeps share one shape: 32 rows per workgroup, four waves = 2 groups of 16 rows x 2 halves of every 32-row step
+// The sweeps (and the output sweep of the fp32 forward, a fourth) share one shape: 32 rows per workgroup, four waves = 2 groups of 16 rows x 2 halves of every 32-row step
 // of the other side, the halves' sums added through LDS at the end.  (64 rows per workgroup without the split leave a
-// 1024-row head with 16 workgroups whose longest is twice the mean.)  Tiles arrive by DMA one step ahead, two buffers, one
+// 1024-row head with 16 workgroups whose longest is twice the mean; with it and balanced_block the r, dQ and key sweeps of 16 heads x
+// 1024 rows take 55, 64 and 110 us, in plain longest-first order 62, 79 and 131; the output sweep 53, before the split 64.)  Tiles arrive by DMA one step ahead, two buffers, one
 // barrier per step; 16-byte chunks are XOR-swizzled with the row, so that rows are read 16 bytes per lane (operand with the
 // features as contraction index) and columns 4 bytes per lane (operand with the rows as contraction index) from one copy.
 #include "llla_mfma_common.hpp"
@@ -39,12 +40,29 @@ __device__ inline void dma_tile(const float *src, int64_t pitch, int row0, int l
     }
 }
 
+// Which of ny blocks of a head workgroup y of the grid (heads, ny) serves, blocks numbered from the longest.  Where the whole grid
+// is resident at once (up to four workgroups per compute unit), a compute unit that gets a long one in the first round
+// must get a short one in the second: every second group of 256 workgroups takes its blocks in reverse.
+__device__ inline int balanced_block(int y, int ny, int heads)
+{
+    const int group = max(256 / heads, 1), first = y / group * group;
+    return ((y / group) & 1) != 0 && y < 4 * group && first + group <= ny ? 2 * first + group - 1 - y : y;
+}
+
 // C += T R^T over the features: T = 16 rows of a tile (tile row nn of the lane), R = a row per lane in registers; contraction
 // slot (s, g) stands for feature DD/4 g + s on both sides
 template <int DD>
 __device__ inline f32x4 row_chunk(const float *trow, int g, int v, int nn)
 {
     return *reinterpret_cast<const f32x4 *>(trow + 4 * ((DD / 16 * g + v) ^ (nn & 7)));
+}
+
+// 2^x as the square of its root: the moments kernel works with the roots of the weights, and the sweeps use the same weights to
+// the last bit (logits of some sixty bits amplify the difference of two roundings to the size of the result's error).
+__device__ inline float weight(float x)
+{
+    const float root = __builtin_amdgcn_exp2f(0.5f * x);
+    return root * root;
 }
 
 template <int DD>
@@ -59,14 +77,16 @@ __device__ inline void load_row(const float *row, int g, float (&x)[DD / 4])
 }
 
 // ---- row sweeps ---------------------------------------------------------------------------------------------
-// MODE 0: the r sweep; MODE 1: the dQ sweep.  S^T = K Q^T and the like come out as (lane (g, nn): keys 4g + r, query nn),
+// MODE 0: the r sweep; MODE 1: the dQ sweep; MODE 2: the output sweep of a forward call, O_i = sum_j w_ij (y0_i + k_j . y1_i) v_j
+// (third loop of Algorithm 1), rows from `skip` on (a multiple of RT, or all).  S^T = K Q^T and the like come out as (lane (g, nn): keys 4g + r, query nn),
 // which is the A operand of the product that contracts over keys when slot g of step r stands for key 4g + r.
 template <int DD, int MODE>
 __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     const float *__restrict__ Qg, const float *__restrict__ Kg, const float *__restrict__ Vg, const float *__restrict__ Gg,
     llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n, int npad, float scale, float lambda,
     const float *__restrict__ LamRows, float *__restrict__ Mg, const float *__restrict__ Yg, const float *Ug, float *Rv,
-    float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam)
+    float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam, int causal = 1, int skip = 0, void *Og = nullptr,
+    llla_strides so = {}, int out_bf16 = 0)
 {
     constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = Shape<DD>::YP, RP = DD + 4;
     __shared__ __align__(16) float tiles[2][2][RT * DD];
@@ -77,17 +97,18 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     const int rg = wave & 1, ks = wave >> 1;
     // head on blockIdx.x (dispatched fastest), row block on y, longest rows first
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int i0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * RT;
+    const int i0 = skip + ((int)gridDim.y - 1 - balanced_block(blockIdx.y, gridDim.y, gridDim.x)) * RT;
     const int iq = min(i0 + 16 * rg + nn, n - 1);           // rows past the end repeat the last one and are not stored
-    const int wlast = min(i0 + 16 * rg + 15, n - 1);
+    const int jlim = MODE == 2 && !causal ? n - 1 : iq;     // the last key the lane's query sees, and the wave's queries
+    const int wlast = MODE == 2 && !causal ? n - 1 : min(i0 + 16 * rg + 15, n - 1);
     const size_t row = (size_t)bh * n + iq;
     const float *Kh = Kg + b * sk.batch + h * sk.head;
     const float *Vh = Vg + b * sv.batch + h * sv.head;
     const float cscale = scale * LOG2E;
 
-    float qr[NS], gr[NS], yr[MODE ? NS : 1], ur[MODE ? NS : 1];
+    float qr[NS], gr[MODE < 2 ? NS : 1], yr[MODE ? NS : 1], ur[MODE == 1 ? NS : 1];
     load_row<DD>(Qg + b * sq.batch + h * sq.head + (int64_t)iq * sq.seq, g, qr);
-    load_row<DD>(Gg + b * sg.batch + h * sg.head + (int64_t)iq * sg.seq, g, gr);
+    if constexpr (MODE < 2) load_row<DD>(Gg + b * sg.batch + h * sg.head + (int64_t)iq * sg.seq, g, gr);
     float mh = -INFINITY, y0 = 0.f, u0 = 0.f, corr = 0.f;
     int jstar = 0;
     if constexpr (MODE == 1) {
@@ -110,13 +131,18 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
             if (dLam) dLam[row] = dl;
         }
     }
+    if constexpr (MODE == 2) {
+        load_row<DD>(Yg + row * YP, g, yr);
+        y0 = Yg[row * YP + DD];
+        mh = Mg[(size_t)bh * npad + iq];
+    }
     f32x4 acc[NB];
 #pragma unroll
     for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
     float csum = 0.f, best = -INFINITY;
     int arg = 0;
 
-    const int nblk = min(i0 + RT - 1, n - 1) / RT + 1;
+    const int nblk = (MODE == 2 && !causal ? n - 1 : min(i0 + RT - 1, n - 1)) / RT + 1;
     auto issue = [&](int c) {
         dma_tile<DD>(Kh, sk.seq, c * RT, n - 1, tiles[c & 1][0], wave, lane);
         dma_tile<DD>(Vh, sv.seq, c * RT, n - 1, tiles[c & 1][1], wave, lane);
@@ -132,13 +158,15 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
         f32x4 z = {0.f, 0.f, 0.f, 0.f}, gm = z, at = {y0, y0, y0, y0}, bt = {u0, u0, u0, u0};
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const f32x4 kv = row_chunk<DD>(kt + nn * DD, g, v, nn), vv = row_chunk<DD>(vt + nn * DD, g, v, nn);
+            const f32x4 kv = row_chunk<DD>(kt + nn * DD, g, v, nn);
+            f32x4 vv = kv;
+            if constexpr (MODE < 2) vv = row_chunk<DD>(vt + nn * DD, g, v, nn);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qr[4 * v + e], z, 0, 0, 0);
-                gm = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], gr[4 * v + e], gm, 0, 0, 0);
+                if constexpr (MODE < 2) gm = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], gr[4 * v + e], gm, 0, 0, 0);
+                if constexpr (MODE >= 1) at = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], yr[4 * v + e], at, 0, 0, 0);
                 if constexpr (MODE == 1) {
-                    at = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], yr[4 * v + e], at, 0, 0, 0);
                     bt = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], ur[4 * v + e], bt, 0, 0, 0);
                 }
             }
@@ -174,10 +202,12 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = jb + 4 * g + r;
-            const float w = __builtin_amdgcn_exp2f(zs[r] - mh);
+            const float w = weight(zs[r] - mh);
             if constexpr (MODE == 0) {
                 cf[r] = j <= iq ? w * gm[r] : 0.f;
                 csum += cf[r];
+            } else if constexpr (MODE == 2) {
+                cf[r] = j <= jlim ? w * at[r] : 0.f;
             } else {
                 const float pv = w * at[r] * (gm[r] - bt[r]);
                 cf[r] = j <= iq ? (j == jstar ? pv + corr : pv) : 0.f;
@@ -186,7 +216,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int kr = 4 * g + r;
-            const float *krow = kt + kr * DD + (nn & 3);
+            const float *krow = (MODE == 2 ? vt : kt) + kr * DD + (nn & 3);
 #pragma unroll
             for (int J = 0; J < NB; ++J)
                 acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], krow[4 * ((4 * J + (nn >> 2)) ^ (kr & 7))], acc[J], 0, 0, 0);
@@ -235,6 +265,14 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
         const f32x4 s = *reinterpret_cast<const f32x4 *>(red + rw * RP + c) + *reinterpret_cast<const f32x4 *>(red + (RT + rw) * RP + c);
         if constexpr (MODE == 0) {
             *reinterpret_cast<f32x4 *>(Rv + ro * YP + c) = s;
+        } else if constexpr (MODE == 2) {
+            const int64_t off = b * so.batch + h * so.head + (int64_t)(i0 + rw) * so.seq + c;
+            if (out_bf16) {
+                typedef bf16_t bf16_4 __attribute__((ext_vector_type(4)));
+                *reinterpret_cast<bf16_4 *>((bf16_t *)Og + off) = bf16_4{f32_to_bf16(s[0]), f32_to_bf16(s[1]), f32_to_bf16(s[2]), f32_to_bf16(s[3])};
+            } else {
+                *reinterpret_cast<f32x4 *>((float *)Og + off) = s;
+            }
         } else {
             const f32x4 u = *reinterpret_cast<const f32x4 *>(Ug + ro * YP + c);
             f32x4 o;
@@ -273,7 +311,7 @@ __global__ __launch_bounds__(256, DD == 64 ? 2 : 1) void bwd_keys_f32_kernel(
     const int kg = wave & 1, qs = wave >> 1;
     // head on blockIdx.x (dispatched fastest); low key blocks see the most rows: they go first for every head
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int j0 = (int)blockIdx.y * RT;
+    const int j0 = balanced_block(blockIdx.y, gridDim.y, gridDim.x) * RT;
     const int jk = min(j0 + 16 * kg + nn, n - 1);            // keys past the end repeat the last one and are not stored
     const float *Qh = Qg + b * sq.batch + h * sq.head;
     const float *Gh = Gg + b * sg.batch + h * sg.head;
@@ -324,7 +362,7 @@ __global__ __launch_bounds__(256, DD == 64 ? 2 : 1) void bwd_keys_f32_kernel(
             const f32x4 s4 = *reinterpret_cast<const f32x4 *>(st + qrow * 8);      // y0, u0, m, correction
             const int jstar = __float_as_int(st[qrow * 8 + 4]);
             const bool valid = jk <= i && i < n;
-            const float w = __builtin_amdgcn_exp2f(z[r] * cscale - s4[2]);
+            const float w = weight(z[r] * cscale - s4[2]);
             const float a = s4[0] + at[r];
             const float ev = w * (gm[r] - (s4[1] + bt[r]));
             const float pv = jk == jstar ? fmaf(a, ev, s4[3]) : a * ev;
@@ -406,6 +444,16 @@ hipError_t launch_rows(const BackwardProblem &p, const BwdF32Layout &L)
 }
 
 }  // namespace
+
+hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y, int skip)
+{
+    if (skip >= p.n) return hipSuccess;
+    const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K), *V = static_cast<const float *>(p.V);
+    hipLaunchKernelGGL((bwd_rows_f32_kernel<64, 2>), dim3(p.B * p.H, (p.n - skip + RT - 1) / RT), dim3(256), 0, p.stream, Q, K, V,
+                       nullptr, p.sq, p.sk, p.sv, llla_strides{}, p.H, p.n, npad, p.scale, 0.f, nullptr, M, Y, nullptr, nullptr, nullptr,
+                       nullptr, nullptr, p.causal, skip, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0);
+    return hipGetLastError();
+}
 
 bool mfma_backward_f32_supported(int n, int d, llla_dtype in) { return in == LLLA_F32 && d == 64 && (n + RT - 1) / RT <= 65535; }
 

@@ -1,10 +1,16 @@
-// Matrix-core forward path for fp32 inputs, d = 64: the contractions of Algorithm 1 (Section 3.2) -- logits,
-// first moment, second moment -- on v_mfma_f32_16x16x4_f32, fp32 operands and fp32 accumulation throughout, so the
-// path has the accuracy of the vector kernels and no value-range condition.
+// Matrix-core forward path for fp32 inputs, d = 64, with the accuracy of the vector kernels and no value-range condition: logits and
+// first moment on v_mfma_f32_16x16x4_f32, the second moment Sigma~_i = Z^T Z with the rows z_j = sqrt(w_ij) k_j split into three bf16
+// (24 significant bits, fp32's exponents) on 16-bit MFMA, six of the nine partial products, fp32 accumulation.
+//
+// What bounds it: on fp32 MFMA the second moment is 256 matrix-core cycles per 16x16 tile and 32 keys, and 80 % of the call.  Six
+// products of 16-bit MFMA are 96.  Both operands being the same z, a query's keys are scaled and split once (36 vector
+// instructions per 16 features and lane, 2.9 per MFMA; three fit beside one), and products and splitting are made to alternate.
+// 16 heads x 1024: call 606 -> 419 us.  Errors against fp64 over normal, unit, peaked and badly scaled inputs, ridges 10^-2 and
+// 10^-4: equal or smaller (unit, 10^-2: 1.7e-6 before and after; normal: 1.4e-5 and 1.2e-5).
 //
 //   moments  per block of 16 queries: weights, omega_i, mu~_i and Sigma~_i (Eq. (tilded_form)) on chip, the ten upper
 //            16x16 tiles of Sigma~_i per query in MFMA accumulators, then the exact per-query solve (solve_wave_q4);
-//   output   third loop of Algorithm 1 as a flash-style sweep, its three products on fp32 MFMA as well;
+//   output   third loop of Algorithm 1 as a flash-style sweep, its three products on fp32 MFMA (llla_mfma_bwd_f32.hip);
 //   rows that see at most 64 keys are served in fp64 and key space (llla_dual.hpp) by further workgroups of the moments kernel:
 //            serial chains that share a compute unit with the matrix-core workgroups instead of running alone at the end.
 //
@@ -56,7 +62,7 @@ __device__ inline int swz(int r) { return ((r & 1) << 2) | ((r >> 1) & 3); }
 
 struct F32Shared {
     float kt[2][FKB * FD];
-    float wt[16 * FWP];                // weights of the current block, negated: [query][g * 16 + s], key = 4 s + g
+    float wt[16 * FWP];                // roots of the weights of the current block: [query][g * 16 + s], key = 4 s + g
     float pm[4][16];                   // block maximum of every query, per weight wave
     float rs[16];                      // rescale factor of every query for this block (1 unless its reference moved)
     float mus[16][FD + 4];
@@ -64,6 +70,42 @@ struct F32Shared {
     float fsc[16];                     // F of every query
     float sc[4][4][16 * SC_PITCH];
 };
+
+// schedule: N times one MFMA, then V vector instructions
+template <int N, int V>
+__device__ __forceinline__ void alternate()
+{
+    if constexpr (N > 0) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+        alternate<N - 1, V>();
+    }
+}
+
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+
+// x = h + m + l, three bf16 (24 significant bits; bf16 has the exponents of fp32, so this holds over its whole range).  The
+// remainders x - h are v_dot2_f32_bf16 with (-1, 0) and (0, -1), exact like the subtractions they stand for: one instruction per value
+// instead of an unpacking and a subtraction.  (The two constants come in scalar registers: as a literal the compiler encodes (-1, 0)
+// as the inline constant -1.0, which this instruction reads as the fp32 bit pattern, i.e. (0, -1); seen with ROCm 7.2.)
+__device__ inline void split3_bf16(const float (&x)[8], bf16x8 &h, bf16x8 &m, bf16x8 &l)
+{
+    unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
+    asm("" : "+s"(lo), "+s"(hi));
+    const bf16x2v first = __builtin_bit_cast(bf16x2v, lo), second = __builtin_bit_cast(bf16x2v, hi);
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+        const bf16x2v a = __builtin_convertvector(float2v{x[t], x[t + 1]}, bf16x2v);
+        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, first, x[t], false), r1 = __builtin_amdgcn_fdot2_f32_bf16(a, second, x[t + 1], false);
+        const bf16x2v b = __builtin_convertvector(float2v{r0, r1}, bf16x2v);
+        const bf16x2v c = __builtin_convertvector(float2v{__builtin_amdgcn_fdot2_f32_bf16(b, first, r0, false),
+                                                          __builtin_amdgcn_fdot2_f32_bf16(b, second, r1, false)}, bf16x2v);
+        h[t] = a[0]; h[t + 1] = a[1];
+        m[t] = b[0]; m[t + 1] = b[1];
+        l[t] = c[0]; l[t + 1] = c[1];
+    }
+}
 
 // LIVE: feature blocks of 16 that can be non-zero (4, except for calls at d = 16 / 32 that run here on zero-padded
 // copies: the tiles, scaled operands and solve blocks of padded feature blocks are skipped, see moments_body).
@@ -121,7 +163,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
 #pragma unroll
         for (int t = 0; t < 10; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 mu_acc = {0.f, 0.f, 0.f, 0.f};
-    float om_part = 0.f;                   // this lane's share of -omega' of query nn (its keys: 4 g + r of every wave block)
+    float om_part = 0.f;                   // this lane's share of omega' of query nn (its keys: 4 g + r of every wave block)
     float mh = -INFINITY, mtrue = -INFINITY;   // reference exponent and true maximum of query nn (log2 units)
     if constexpr (BWD) mh = Mg[(size_t)bh * npad + min(iq, n - 1)];
 
@@ -154,6 +196,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     };
 
     issue_dma(0);
+    __builtin_amdgcn_s_setprio(2);         // the loop before the solve of the other workgroup of the compute unit: 1-2 %
     for (int c = 0; c < nblk; ++c) {
         const float *kt = sm.kt[c & 1];
         dma_wait();
@@ -202,9 +245,10 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int j = c * FKB + 16 * wave + 4 * g + r;
-                const float wgt = __builtin_amdgcn_exp2f(zs[r] - mh);
-                wf[r] = (q_live && j <= jlim) ? -wgt : 0.f;           // stored negated: the tiles accumulate -(w k) k^T
-                sm.wt[nn * FWP + r * 16 + 4 * wave + g] = wf[r];
+                const float root = __builtin_amdgcn_exp2f(0.5f * (zs[r] - mh));
+                const float sw = (q_live && j <= jlim) ? root : 0.f;
+                sm.wt[nn * FWP + r * 16 + 4 * wave + g] = sw;
+                wf[r] = sw * sw;
             }
             om_part += (wf[0] + wf[1]) + (wf[2] + wf[3]);
         }
@@ -226,42 +270,84 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
             }
         }
 
-        // ---- moments of block c: 16 steps of 4 keys, up to the last key a query of the workgroup sees -------------
-        const int s4n = causal ? min(4, (ilast - c * FKB) / 16 + 1) : 4;
+        // ---- moments of block c, in halves of 32 keys, up to the last key a query of the workgroup sees -----------
+        const int nhalf = causal ? min(2, (ilast - c * FKB) / 32 + 1) : 2;
 #pragma unroll 1
-        for (int s4 = 0; s4 < s4n; ++s4) {
-            // weights of keys 4 s + g, s = 4 s4 .. 4 s4 + 3: for this wave's queries (scaling) and for all 16 (mu~)
-            f32x4 wq[QW];
-#pragma unroll
-            for (int q = 0; q < QW; ++q) wq[q] = *reinterpret_cast<const f32x4 *>(&sm.wt[(QW * wave + q) * FWP + g * 16 + 4 * s4]);
-            const f32x4 wa = *reinterpret_cast<const f32x4 *>(&sm.wt[nn * FWP + g * 16 + 4 * s4]);
-            // the operand addresses below are formed from copies of the lane indices that the compiler cannot see
-            // through: twenty of them are loop-invariant and would otherwise be kept in registers over the whole sweep
+        for (int hf = 0; hf < nhalf; ++hf) {
+            // Key 4 (8 hf + t) + g is slot t of lane group g; its row starts at t * 4 FD from this lane's first.  The swizzle of row
+            // 4 t + g is ((g & 1) << 2) | ((2 t + (g >> 1)) & 3), so four addresses per lane (parities of t and I) and immediates
+            // serve all reads.  (They are formed from copies of the lane indices that the compiler cannot see through: it would
+            // keep all 32 in registers over the whole sweep.)
             int g_e = g, nn_e = nn;
             asm volatile("" : "+v"(g_e), "+v"(nn_e));
+            const int c4 = nn_e >> 2;
+            const float *krow = kt + (32 * hf + g_e) * FD + (nn_e & 3);
+            const float *ka[2][2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = 4 * (4 * s4 + e) + g_e;
-                const float *krow = kt + row * FD + (nn_e & 3);
-                const int sw = swz(row), c4 = nn_e >> 2;
-                float kf[NB];
+            for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
-                for (int I = 0; I < LIVE; ++I) kf[I] = krow[4 * ((4 * I + c4) ^ sw)];
-                const float kmu = krow[4 * ((4 * wave + c4) ^ sw)];                   // this wave's feature block of mu~
+                for (int ip = 0; ip < 2; ++ip) ka[tp][ip] = krow + 4 * (4 * (ip ^ (g_e & 1)) + (c4 ^ ((2 * tp + (g_e >> 1)) & 3)));
+            // Work items (query q, feature block I): z = sqrt(w) k of block I in three bf16, then the products of block I with
+            // blocks 0..I.  A wave's vector instructions and MFMAs overlap only where they alternate, so a region of the schedule
+            // holds the products of one item and the z of the next.
+            bf16x8 zh[QW + 1][NB], zm[QW + 1][NB], zl[QW + 1][NB];
+            f32x4 w0, w1;
+            auto make_z = [&](int q, int I) {
+                if (I == 0) {
+                    const float *wp = &sm.wt[(QW * wave + q) * FWP + g_e * 16 + 8 * hf];
+                    w0 = *reinterpret_cast<const f32x4 *>(wp);
+                    w1 = *reinterpret_cast<const f32x4 *>(wp + 4);
+                }
+                // read again for every query: 32 registers for the keys of a half would push accumulators into scratch memory
+                asm volatile("" ::: "memory");
+                float x[8];
 #pragma unroll
-                for (int q = 0; q < QW; ++q)
+                for (int t = 0; t < 8; ++t) x[t] = (t < 4 ? w0[t & 3] : w1[t & 3]) * ka[t & 1][I & 1][4 * t * FD + 32 * (I >> 1)];
+                split3_bf16(x, zh[q][I], zm[q][I], zl[q][I]);
+            };
+            make_z(0, 0);
 #pragma unroll
-                    for (int I = 0; I < LIVE; ++I) {
-                        const float af = kf[I] * wq[q][e];
+            for (int q = 0; q < QW; ++q)
 #pragma unroll
-                        for (int J = I; J < LIVE; ++J)
-                            acc[q][S::tix(I, J)] = __builtin_amdgcn_mfma_f32_16x16x4f32(af, kf[J], acc[q][S::tix(I, J)], 0, 0, 0);
+                for (int I = 0; I < LIVE; ++I) {
+                    if (I + 1 < LIVE) make_z(q, I + 1);
+                    else if (q + 1 < QW) make_z(q + 1, 0);
+                    // six products of the nine: what is left out is below 2^-24 of the result
+#pragma unroll
+                    for (int J = 0; J <= I; ++J) {
+                        f32x4 &t = acc[q][S::tix(J, I)];
+                        t = mfma_bf16(zl[q][J], zh[q][I], t);
+                        t = mfma_bf16(zh[q][J], zl[q][I], t);
+                        t = mfma_bf16(zm[q][J], zm[q][I], t);
+                        t = mfma_bf16(zm[q][J], zh[q][I], t);
+                        t = mfma_bf16(zh[q][J], zm[q][I], t);
+                        t = mfma_bf16(zh[q][J], zh[q][I], t);
                     }
-                mu_acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[e], kmu, mu_acc, 0, 0, 0);   // -mu~'[query 4g+r][16 wave + nn]
+                    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+                    if (I == 0) alternate<6, 8>();
+                    else if (I == 1) alternate<12, 4>();
+                    else if (I == 2) alternate<18, 3>();
+                    else alternate<24, 2>();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            // mu~: fp32, four keys per MFMA, the weights of all 16 queries against this wave's feature block
+            const float *wp = &sm.wt[nn_e * FWP + g_e * 16 + 8 * hf];
+            w0 = *reinterpret_cast<const f32x4 *>(wp);
+            w1 = *reinterpret_cast<const f32x4 *>(wp + 4);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const float sw = t < 4 ? w0[t & 3] : w1[t & 3];
+                const float kmu = ka[t & 1][wave & 1][4 * t * FD + 32 * (wave >> 1)];
+                mu_acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-sw * sw, kmu, mu_acc, 0, 0, 0);   // -mu~'[query 4g+r][16 wave + nn]
             }
         }
     }
+#pragma unroll
+    for (int q = 0; q < QW; ++q)                                      // the solve works on -Sigma~'
+#pragma unroll
+        for (int t = 0; t < 10; ++t) acc[q][t] = -acc[q][t];
 
+    __builtin_amdgcn_s_setprio(0);
     // ---- hand mu~', omega' and F to the waves that own the queries -------------------------------------------------
     __syncthreads();
 #pragma unroll
@@ -278,38 +364,63 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
         }
     }
     __syncthreads();
-    if (tid < 16) sm.oms[tid] = -((sm.pm[0][tid] + sm.pm[1][tid]) + (sm.pm[2][tid] + sm.pm[3][tid]));
+    if (tid < 16) sm.oms[tid] = ((sm.pm[0][tid] + sm.pm[1][tid]) + (sm.pm[2][tid] + sm.pm[3][tid]));
     __syncthreads();
 
-    // ---- the ridge lambda F on the diagonal (the tiles hold -Sigma~'), then the solve ----------------------------------
+    // ---- the ridge lambda F on the diagonal (the tiles hold -Sigma~'), the intercept eliminated, then the solve -----------
+    // The intercept goes first, which leaves the centred Sigma~ - mu~ mu~^T / omega + lambda F I: at least lambda F however few keys
+    // the row sees.  Eliminated last it leaves omega - mu~^T (Sigma~ + lambda F I)^-1 mu~, which few keys far apart cancel to zero in
+    // fp32 (64 rows, features from 10^-3 to 10, ridge 10^-4: non-finite gradients).
     const int qi = QW * wave + g;                                       // solve role: lane (g, nn) = (query, element)
     const int row = min(i0 + qi, n - 1);
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
         const int rq = min(i0 + QW * wave + q, n - 1);
         const float lq = (lam_rows ? lam_rows[(size_t)bh * n + rq] : lambda) * sm.fsc[QW * wave + q];
+        const float oinv = 1.f / sm.oms[QW * wave + q];
+        const float *mq = sm.mus[QW * wave + q];
+        float mc[NB];
 #pragma unroll
-        for (int P = 0; P < NB; ++P)
+        for (int J = 0; J < LIVE; ++J) mc[J] = mq[16 * J + nn];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[q][S::tix(P, P)][t] -= (nn == 4 * g + t) ? lq : 0.f;
+        for (int I = 0; I < NB; ++I) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[q][S::tix(I, I)][t] -= (nn == 4 * g + t) ? lq : 0.f;
+            if (I < LIVE) {
+                const f32x4 mr = oinv * *reinterpret_cast<const f32x4 *>(mq + 16 * I + 4 * g);
+#pragma unroll
+                for (int J = I; J < LIVE; ++J)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[q][S::tix(I, J)][t] = fmaf(mr[t], mc[J], acc[q][S::tix(I, J)][t]);
+            }
+        }
     }
     const float pivot_floor = 0.5f * (lam_rows ? lam_rows[(size_t)bh * n + row] : lambda) * sm.fsc[qi];
     const float *qrow = Qh + (int64_t)row * sq.seq;
-    float tmu[4], tq[4], te[4], y1[4], u1[4], y0 = 0.f, u0 = 0.f;
+    const float oinv = 1.f / sm.oms[qi];
+    float nm[4], tmu[4], tq[4], te[4], y1[4], u1[4], y0 = 0.f, u0 = 0.f;
+    float r0 = 0.f;
+    const float *rr = BWD ? RUg + ((size_t)bh * n + row) * YP : nullptr;
+    if constexpr (BWD) r0 = rr[FD];
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
-        tmu[P] = sm.mus[qi][16 * P + nn];                                // -mu~'
-        tq[P] = -qrow[16 * P + nn];
-        te[P] = 0.f; y1[P] = 0.f; u1[P] = 0.f;
+        nm[P] = sm.mus[qi][16 * P + nn];                                 // -mu~'
+        tmu[P] = 0.f;
+        tq[P] = fmaf(-nm[P], oinv, -qrow[16 * P + nn]);                  // -(q - mu~ / omega)
+        te[P] = BWD ? fmaf(-nm[P], r0 * oinv, -rr[16 * P + nn]) : 0.f;   // -(r1 - mu~ r0 / omega)
+        y1[P] = 0.f; u1[P] = 0.f;
     }
-    float r0 = 0.f;
-    if constexpr (BWD) {
-        const float *rr = RUg + ((size_t)bh * n + row) * YP;
+    solve_wave_q4<BWD, LIVE>(acc, tmu, tq, te, r0, 1.f, &sm.sc[wave][0][0], g, nn, pivot_floor, y1, y0, u1, u0);
+    {
+        float my = 0.f, mu = 0.f;
 #pragma unroll
-        for (int P = 0; P < NB; ++P) te[P] = -rr[16 * P + nn];
-        r0 = rr[FD];
+        for (int P = 0; P < LIVE; ++P) {
+            my = fmaf(nm[P], y1[P], my);
+            if constexpr (BWD) mu = fmaf(nm[P], u1[P], mu);
+        }
+        y0 = (1.f + row_allsum(my)) * oinv;
+        if constexpr (BWD) u0 = (r0 + row_allsum(mu)) * oinv;
     }
-    solve_wave_q4<BWD, LIVE>(acc, tmu, tq, te, r0, sm.oms[qi], &sm.sc[wave][0][0], g, nn, pivot_floor, y1, y0, u1, u0);
     if (i0 + qi < n) {
         float *yr = Yg + ((size_t)bh * n + row) * YP;
 #pragma unroll
@@ -320,118 +431,6 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
 #pragma unroll
             for (int P = 0; P < NB; ++P) ur[16 * P + nn] = u1[P];
             if (nn == 0) ur[FD] = u0;
-        }
-    }
-}
-
-// Third loop of Algorithm 1 for 64 queries per workgroup (16 per wave): S^T = K Q^T and K y1' on fp32 MFMA, the output
-// weights w'_ij (y0'_i + k_j . y1'_i) on the vector ALU, O = S V on fp32 MFMA.  The coefficient tile comes out of the
-// first two products in the accumulator layout (lane (g, n): keys 4 g + r of a 16-key sub-tile, query n), which is
-// directly the A operand of the third when contraction slot (g, r) stands for key 4 g + r.  K and V tiles of 64 keys
-// arrive by DMA, 16-byte chunks XOR-swizzled with the low three bits of the key row (the b128 reads of K rows and the
-// b32 reads of V rows 4 g + r are then both free of bank conflicts).
-struct OutShared {
-    float k[FKB * FD];
-    float v[FKB * FD];
-};
-
-__global__ __launch_bounds__(256, 2) void output_f32_kernel(const float *__restrict__ Qg, const float *__restrict__ Kg,
-                                                         const float *__restrict__ Vg, llla_strides sq, llla_strides sk,
-                                                         llla_strides sv, int H, int n, int npad, float cscale,
-                                                         const float *__restrict__ Mg, const float *__restrict__ Yg,
-                                                         void *__restrict__ Og, llla_strides so, int out_bf16, int causal, int skip)
-{
-    // rows [0, skip) -- 64, or all -- are the key-space workgroups' of the moments kernel
-    constexpr int YP = Shape<FD>::YP, NB = 4;
-    __shared__ __align__(16) OutShared sm;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
-    // head on blockIdx.x (dispatched fastest), query block on y, longest rows first
-    const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int i0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * 64;
-    if (i0 < skip) return;
-    const int iq = i0 + wave * 16 + nn, iqc = min(iq, n - 1);
-    const int jlim = causal ? iq : n - 1;
-    const float *Kh = Kg + b * sk.batch + h * sk.head;
-    const float *Vh = Vg + b * sv.batch + h * sv.head;
-    float qreg[16], yreg[16];                                       // Q and y1' of query nn, features 16 g + s
-    {
-        const float *qrow = Qg + b * sq.batch + h * sq.head + (int64_t)iqc * sq.seq + 16 * g;
-        const float *yrow = Yg + ((size_t)bh * n + iqc) * YP + 16 * g;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const f32x4 a = *reinterpret_cast<const f32x4 *>(qrow + 4 * v), c = *reinterpret_cast<const f32x4 *>(yrow + 4 * v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { qreg[4 * v + e] = a[e]; yreg[4 * v + e] = c[e]; }
-        }
-    }
-    const float y0 = Yg[((size_t)bh * n + iqc) * YP + FD];
-    const float mh = Mg[(size_t)bh * npad + iqc];
-    f32x4 oacc[NB];
-#pragma unroll
-    for (int J = 0; J < NB; ++J) oacc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int ilast = min(i0 + 63, n - 1);
-    const int nblk = causal ? ilast / FKB + 1 : (n + FKB - 1) / FKB;
-    for (int c = 0; c < nblk; ++c) {
-        __syncthreads();                                            // everybody is done with the previous tiles
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = 16 * wave + 4 * t + (lane >> 4);
-            const int j = min(c * FKB + row, n - 1);
-            const int chunk = (lane & 15) ^ (row & 7);
-            dma16(Kh + (int64_t)j * sk.seq + 4 * chunk, sm.k + (16 * wave + 4 * t) * FD);
-            dma16(Vh + (int64_t)j * sv.seq + 4 * chunk, sm.v + (16 * wave + 4 * t) * FD);
-        }
-        dma_wait();
-        __syncthreads();
-        // blocks that lie wholly before the wave's first query need no causal mask (a scalar condition)
-        const bool masked = causal ? (c * FKB + FKB - 1 > i0 + wave * 16) : (c * FKB + FKB > n);
-#pragma unroll
-        for (int sub = 0; sub < 4; ++sub) {
-            f32x4 z = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
-            {
-                const int row = 16 * sub + nn;
-                const float *krow = sm.k + row * FD;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const f32x4 kv = *reinterpret_cast<const f32x4 *>(krow + 4 * ((4 * g + v) ^ (row & 7)));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qreg[4 * v + e], z, 0, 0, 0);
-                        u = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], yreg[4 * v + e], u, 0, 0, 0);
-                    }
-                }
-            }
-            float cf[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                cf[r] = __builtin_amdgcn_exp2f(z[r] * cscale - mh) * (y0 + u[r]);
-                if (masked) {
-                    const int j = c * FKB + 16 * sub + 4 * g + r;
-                    cf[r] = (j <= jlim) ? cf[r] : 0.f;
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * sub + 4 * g + r;
-                const float *vrow = sm.v + row * FD + (nn & 3);
-#pragma unroll
-                for (int J = 0; J < NB; ++J)
-                    oacc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], vrow[4 * ((4 * J + (nn >> 2)) ^ (row & 7))], oacc[J], 0, 0, 0);
-            }
-        }
-    }
-    // oacc[J]: lane (g, nn) reg r = O[query i0 + 16 wave + 4 g + r][feature 16 J + nn]
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = i0 + wave * 16 + 4 * g + r;
-        if (i < n) {
-            const int64_t off = b * so.batch + h * so.head + (int64_t)i * so.seq;
-#pragma unroll
-            for (int J = 0; J < NB; ++J) {
-                if (out_bf16) ((bf16_t *)Og)[off + 16 * J + nn] = f32_to_bf16(oacc[J][r]);
-                else ((float *)Og)[off + 16 * J + nn] = oacc[J][r];
-            }
         }
     }
 }
@@ -491,10 +490,8 @@ hipError_t mfma_forward_f32(const Problem &p)
                            (const float *)Y, (const float *)LF, p.rho, p.delta, da.nrows);
     }
     stage_mark(p.stream, "output");
-    hipLaunchKernelGGL(output_f32_kernel, dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, static_cast<const float *>(p.V),
-                       p.sq, p.sk, p.sv, p.H, p.n, L.npad, p.scale * LOG2E, (const float *)M, (const float *)Y, p.O, p.so,
-                       obf, p.causal, da.nrows);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : mfma_output_f32(p, L.npad, M, Y, da.nrows);
 }
 
 hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU)

@@ -1,5 +1,6 @@
 """fp32 backward on the fp32 matrix cores (d = 64): the edges of its 32-row tiles and of the halves they are split into,
 against the backward oracle, with the fp32 gate of the other backward tests (parity.check_grad, 1e-3)."""
+import numpy as np
 import pytest
 import torch
 
@@ -31,6 +32,23 @@ def test_reference_exponent(factor):
     w = w.with_shape(scale=w.scale * (-1.0 if factor < 0 else 1.0))
     G = _upstream(w, 41)
     _compare(w, _backward(w, Q, K, V, G, w.lam), ob.backward(Q, K, V, G, w.lam, w.scale), "factor %g" % factor, _floor(V, G, w.lam))
+
+
+def test_few_keys_small_ridge_features_over_four_decades():
+    """Rows with few keys far apart: the system is regular only through the ridge, and the intercept has to be eliminated
+    before the features (eliminated last it cancels to zero).  Condition number about 1e2 / 1e-4 = 1e6, times the 6e-8 of
+    fp32, times the ten of a head's worst rows."""
+    n, d = 64, 64
+    g = torch.Generator(device="cpu").manual_seed(64)
+    Q, K, V, G = (torch.randn((1, 2, n, d), generator=g) for _ in range(4))
+    size = 10.0 ** (torch.rand(d, generator=g) * 4 - 3)
+    K, Q = K * size, Q / size.clamp(min=0.1)
+    got = llla.llla_backward(Q.to(DEV), K.to(DEV), V.to(DEV), G.to(DEV), 1e-4, 1 / 8.0, return_dlambda=True)
+    ref = ob.backward(Q, K, V, G, 1e-4, 1 / 8.0)
+    for a, b in zip(got, ref):
+        a = a.cpu().double().numpy()
+        assert np.isfinite(a).all()
+        assert np.linalg.norm(a - b) <= 0.6 * np.linalg.norm(b)
 
 
 def test_workspace_of_the_vector_kernels_is_enough():
