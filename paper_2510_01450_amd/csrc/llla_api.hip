@@ -279,7 +279,7 @@ llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void
     llla::stage_begin(p.stream);
     // fp32 caches, d = 16 / 32 and short bf16 caches: the fp32 matrix-core kernels, faster than the vector kernels at every size
     // measured (1 to 1024 heads x 66 to 8192 keys).  us, vector vs matrix cores: fp32 d = 64, 64 heads of 1024 .. 8192 keys 1243 vs
-    // 87, 1 head x 66 107 vs 17; d = 128, 256 heads x 8192 4234 vs 1210; d = 32 bf16, 256 heads x 4096 252 vs 51; d = 16, 1024 heads x
+    // 87, 1 head x 66 107 vs 17; d = 128, 256 heads x 8192 4234 vs 1210; d = 32 bf16, 256 heads x 4096 252 vs 36; d = 16, 1024 heads x
     // 8192 980 vs 193.
     const bool use_f32 = !use_mfma && path == LLLA_PATH_AUTO && llla::mfma_decode_f32_takes(p);
     if (!use_mfma && !use_f32) llla::stage_mark(p.stream, "valu_decode");

@@ -7,6 +7,7 @@
 // order in which the fp32 kernels load their operands).
 #pragma once
 
+#include "llla_dual.hpp"
 #include "llla_mfma_common.hpp"
 #include "llla_mfma_solve128.hpp"
 #include <algorithm>
@@ -406,11 +407,25 @@ __device__ __forceinline__ void finish_workgroup(Lds &lds, f32x4 (&acc)[DecShape
 
 // Merge of a head's records (max-rescaled sum), solve, output: one head per workgroup.  The records are fetched eight at a time,
 // every thread owning the same 16 bytes of each, so a head's records are in after one or two round trips to memory.
-template <int D, typename TI, bool PERM>
-__global__ __launch_bounds__(DEC_NT, 1) void decode_merge_kernel(DecSplit split, HeadOut out, const float *__restrict__ parts)
+// DUAL: a call whose sequences of at most 64 keys are served in key space has one more workgroup per head for that, in the same
+// launch; which of the two writes the head follows from its length.
+template <int D, typename TI, bool PERM, bool DUAL = false>
+__global__ __launch_bounds__(DEC_NT, 1) void decode_merge_kernel(DecSplit split, HeadOut out, const float *__restrict__ parts,
+                                                                 dual::DualArgs da = {}, int heads = 0)
 {
     using S = DecShape<D>;
-    __shared__ __align__(16) HeadLds<D, 1, 1> lds;
+    using Dual = dual::DualShared<D, DUAL_MAX_KEYS>;
+    constexpr size_t LDS_B = sizeof(HeadLds<D, 1, 1>) > sizeof(Dual) || !DUAL ? sizeof(HeadLds<D, 1, 1>) : sizeof(Dual);
+    __shared__ __align__(16) unsigned char raw[LDS_B];
+    if constexpr (DUAL) {
+        if ((int)blockIdx.x >= heads) {
+            if (out.out_bf16) dual::dual_decode_head<D, TI, bf16_t>(*reinterpret_cast<Dual *>(raw), da, split.seqlens, blockIdx.x - heads);
+            else dual::dual_decode_head<D, TI, float>(*reinterpret_cast<Dual *>(raw), da, split.seqlens, blockIdx.x - heads);
+            return;
+        }
+        if (seq_len(split, blockIdx.x / split.H) <= DUAL_MAX_KEYS) return;
+    }
+    HeadLds<D, 1, 1> &lds = *reinterpret_cast<HeadLds<D, 1, 1> *>(raw);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, bh = blockIdx.x;
     const DecRecords rec = dec_records(split, bh);
     const int np = rec.count;

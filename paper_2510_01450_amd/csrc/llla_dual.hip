@@ -18,13 +18,7 @@ template <int D, typename TI, typename TO>
 __global__ __launch_bounds__(DUAL_NT) void dual_decode_kernel(DualArgs a, const int32_t *__restrict__ seqlens)
 {
     __shared__ DualShared<D, DUAL_MAX_KEYS> sm;
-    const int bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
-    int m = seqlens ? seqlens[b] : a.n;
-    m = m < 1 ? 1 : (m > a.n ? a.n : m);
-    if (m > DUAL_MAX_KEYS) return;                        // the whole workgroup
-    dual_row<D, TI, TO>(sm, (const TI *)a.Q + (int64_t)bh * D, (const TI *)a.K + b * a.sk.batch + h * a.sk.head,
-                        (const TI *)a.V + b * a.sv.batch + h * a.sv.head, a.sk.seq, a.sv.seq, m, (double)a.lambda, a.scale,
-                        (TO *)a.O + (int64_t)bh * D, nullptr, nullptr);
+    dual_decode_head<D, TI, TO>(sm, a, seqlens, blockIdx.y);
 }
 
 template <int D, typename TI, typename TO>

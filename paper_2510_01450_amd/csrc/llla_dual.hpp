@@ -275,6 +275,19 @@ __device__ __forceinline__ void dual_forward_row(DualShared<D> &sm, const DualAr
                         a.Delta ? a.Delta + row : nullptr);
 }
 
+// The sequence of (batch, head) bh of a decode call (q, o contiguous); returns at once if it is longer than 64 keys
+template <int D, typename TI, typename TO>
+__device__ __forceinline__ void dual_decode_head(DualShared<D, DUAL_MAX_KEYS> &sm, const DualArgs &a, const int32_t *seqlens, int bh)
+{
+    const int b = bh / a.H, h = bh % a.H;
+    int m = seqlens ? seqlens[b] : a.n;
+    m = m < 1 ? 1 : (m > a.n ? a.n : m);
+    if (m > DUAL_MAX_KEYS) return;                            // the whole workgroup
+    dual_row<D, TI, TO>(sm, (const TI *)a.Q + (int64_t)bh * D, (const TI *)a.K + b * a.sk.batch + h * a.sk.head,
+                        (const TI *)a.V + b * a.sv.batch + h * a.sv.head, a.sk.seq, a.sv.seq, m, (double)a.lambda, a.scale,
+                        (TO *)a.O + (int64_t)bh * D, nullptr, nullptr);
+}
+
 inline DualArgs dual_args(const Problem &p)
 {
     return DualArgs{p.Q, p.K, p.V, p.O, p.sq, p.sk, p.sv, p.so, p.H, p.n, p.causal, p.lambda, p.scale, p.lambda_rows, p.rho, p.delta,

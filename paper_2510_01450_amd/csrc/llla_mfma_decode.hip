@@ -346,7 +346,7 @@ hipError_t mfma_decode(const Problem &p)
         hipLaunchKernelGGL((decode_partial_kernel<false>), grid, dim3(NT), 0, p.stream, split, out, (const bf16_t *)p.K,
                            (const bf16_t *)p.V, p.sk, p.sv, cscale, parts);
         stage_mark(p.stream, "decode_merge");
-        hipLaunchKernelGGL((decode_merge_kernel<D, bf16_t, false>), dim3(p.B * p.H), dim3(NT), 0, p.stream, split, out, (const float *)parts);
+        hipLaunchKernelGGL((decode_merge_kernel<D, bf16_t, false>), dim3(p.B * p.H), dim3(NT), 0, p.stream, split, out, (const float *)parts, dual::DualArgs{}, 0);
     }
     return hipGetLastError();
 }

@@ -12,8 +12,12 @@
 // The logits of 4 keys x 4 chunks are reduced over the 16 lanes of a row by two exchange stages that leave chunk (n & 3) in
 // lane n, so a lane forms ONE exponential per 16 keys; the weights go back to the row as DPP broadcasts.
 //
+// bf16 caches at d = 16 / 32 leave the fp32 MFMA rate behind: slot (g, t) of a 16x16x32 MFMA stands for key 4 t + g, so the registers
+// of eight chunks are its operands as they are; k and v are bf16 already, and w k is split into three (24 significant bits), three
+// products instead of eight fp32 ones of twice the cycles.
+//
 // What bounds it: 26 tiles of 16x16x4 per four keys at d = 64 are 832 matrix-core cycles for 2 KB of fp32 cache, 6 TB/s at 2.4 GHz,
-// i.e. the fp32 matrix cores and HBM meet (d = 32: 7 tiles, bf16 5.6 TB/s; d = 16: 2 tiles); at d = 128 it is 100 tiles,
+// i.e. the fp32 matrix cores and HBM meet (d = 16 / 32 in bf16: HBM); at d = 128 it is 100 tiles,
 // 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
 // wave W owns row blocks W and 7 - W, 25 tiles whatever W; every wave loads the whole rows (the first-level cache serves three
 // of the four) and forms the weights for itself, so there is no exchange at all.
@@ -36,7 +40,7 @@ struct F32Shape : DecShape<D> {
     static constexpr int NR = TEAM ? 2 : D / 16;          // row blocks of a wave
     static constexpr int NBUF = D <= 32 ? 4 : TEAM ? 1 : 2;   // LDS copies of the tiles in the merge of a workgroup's waves
     static constexpr int KEYS_MIN = TEAM ? 128 : 256;     // fewest keys worth a workgroup (its record is read back by the merge)
-    static constexpr int SLOTS = D <= 32 ? 1024 : 512;    // workgroups the GPU holds at once
+    static constexpr int SLOTS = D <= 16 ? 1024 : 512;    // workgroups worth having at once
     static constexpr int MAX_SPLIT = 32;
 };
 
@@ -132,7 +136,8 @@ template <int D, typename TI, bool FUSED, int W, class Lds>
 __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece &pc, Lds &lds, int wave, int lane)
 {
     using S = F32Shape<D>;
-    constexpr int NB = S::NB, NC = S::NC, NG = S::NG, NR = S::NR, STEP = S::STEP, CH = NC * NG;
+    constexpr bool SPLIT = sizeof(TI) == 2 && D <= 32;    // w k in three bf16 on 16-bit MFMA, eight chunks at a time
+    constexpr int NB = S::NB, NC = S::NC, NG = SPLIT ? 2 : S::NG, NR = S::NR, CH = NC * NG, STEP = 4 * CH;
     constexpr int row[4] = {S::TEAM ? W : 0, S::TEAM ? 7 - W : 1, 2, 3};      // row blocks of this wave: row[0..NR-1]
     const int g = lane / 16, nn = lane % 16;
     // the piece is divided over the four waves (TEAM: walked by all four together); rows at and beyond L are never read
@@ -193,7 +198,71 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             }
         }
     };
-    auto compute = [&](const Step &st, int s) {
+    auto compute_split = [&](const auto &st, int s) {
+        const int j0 = r0 + s * STEP;
+        float t[2], w[2];
+#pragma unroll
+        for (int grp = 0; grp < 2; ++grp) {
+            float p[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                p[c] = 0.f;
+#pragma unroll
+                for (int i = 0; i < NB; ++i) p[c] = fmaf(q[i], frag_f32<TI, NB>(st.k[grp * NC + c], i), p[c]);
+            }
+            t[grp] = reduce_chunks<NC>(p, nn);                        // logit (log2 units) of key 4 (n % NC) + g of the group
+            t[grp] = j0 + grp * 4 * NC + 4 * (nn & (NC - 1)) + g < r1 ? t[grp] : -INFINITY;
+        }
+        const float top = fmaxf(t[0], t[1]);
+        if (__builtin_amdgcn_ballot_w64(top > mref + REF_SLACK) != 0) {
+            const float mnew = wave_max_dpp(top);
+            const float alpha = mref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mref - mnew);
+            mref = mnew;
+            om *= alpha;
+#pragma unroll
+            for (int i = 0; i < NR; ++i) { mu[i] *= alpha; yv[i] *= alpha; }
+            for_tiles([&](int t) { acc[t] *= alpha; });
+        }
+        mtrue = fmaxf(mtrue, top);
+#pragma unroll
+        for (int grp = 0; grp < 2; ++grp) {
+            w[grp] = __builtin_amdgcn_exp2f(t[grp] - mref);           // exp2(-inf) = 0 masks the tail
+            om += w[grp];
+        }
+        const float wc[8] = {row_bcast<0>(w[0]), row_bcast<1>(w[0]), row_bcast<2>(w[0]), row_bcast<3>(w[0]),
+                             row_bcast<0>(w[1]), row_bcast<1>(w[1]), row_bcast<2>(w[1]), row_bcast<3>(w[1])};
+        // element I of eight chunks as an MFMA operand: bf16 bits as loaded
+        auto operand = [](const auto &f, int I) {
+            uint4v u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const unsigned a = f[2 * c].u[I >> 1], b = f[2 * c + 1].u[I >> 1];
+                u[c] = (I & 1) ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
+            }
+            return __builtin_bit_cast(bf16x8, u);
+        };
+        bf16x8 kb[NB], vb[NB];
+#pragma unroll
+        for (int J = 0; J < NB; ++J) { kb[J] = operand(st.k, J); vb[J] = operand(st.v, J); }
+#pragma unroll
+        for (int I = 0; I < NB; ++I) {
+            float x[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                x[c] = wc[c] * frag_f32<TI, NB>(st.k[c], I);
+                mu[I] += x[c];
+                yv[I] = fmaf(wc[c], frag_f32<TI, NB>(st.v[c], I), yv[I]);
+            }
+            bf16x8 h, m, l;
+            split3_bf16(x, h, m, l);
+            auto product = [&](f32x4 &t, bf16x8 b) { t = mfma_bf16(h, b, mfma_bf16(m, b, mfma_bf16(l, b, t))); };
+#pragma unroll
+            for (int J = I; J < NB; ++J) product(acc[upper_tile<NB>(I, J)], kb[J]);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) product(acc[S::NSIG + NB * I + J], vb[J]);
+        }
+    };
+    auto compute_f32 = [&](const Step &st, int s) {
         const int j0 = r0 + s * STEP;
 #pragma unroll
         for (int grp = 0; grp < NG; ++grp) {
@@ -251,6 +320,10 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             }
         }
     };
+    auto compute = [&](const Step &st, int s) {
+        if constexpr (SPLIT) compute_split(st, s);
+        else compute_f32(st, s);
+    };
     if (nsteps > 0) {
         Step sa, sb;
         load(sa, 0);
@@ -292,8 +365,10 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     }
 }
 
+// Two waves per SIMD for the split form at d = 32: four leave 128 registers, 24 too few, and three are still slower (256 heads x 4096
+// keys: 53.9, 38.4 and 35.9 us with 1024, 768 and 512 workgroups; on fp32 MFMA 52.6; 512 x 16384: 254, 201, 191 and 303).
 template <int D, typename TI, bool FUSED>
-__global__ __launch_bounds__(NT, D <= 32 ? 4 : D == 128 && FUSED ? 1 : 2) void decode_f32_kernel(F32Args a)
+__global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : D == 128 && FUSED ? 1 : 2) void decode_f32_kernel(F32Args a)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     using S = F32Shape<D>;
@@ -366,12 +441,20 @@ hipError_t f32_launch(const Problem &p)
     if (a.split.nsplit == 1 && a.split.slots == 0) {
         stage_mark(p.stream, "decode_f32");
         hipLaunchKernelGGL((decode_f32_kernel<D, TI, true>), dim3(1, bh), dim3(NT), 0, p.stream, a);
+        // without lengths every sequence is long; with them, those of at most 64 keys are served in key space
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess || p.seqlens == nullptr ? e : dual_decode(p);
     } else {
         stage_mark(p.stream, "decode_partial");
         hipLaunchKernelGGL((decode_f32_kernel<D, TI, false>), a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT),
                            0, p.stream, a);
         stage_mark(p.stream, "decode_merge");
-        hipLaunchKernelGGL((decode_merge_kernel<D, TI, true>), dim3(bh), dim3(NT), 0, p.stream, a.split, a.out, (const float *)a.parts);
+        if (p.seqlens == nullptr)
+            hipLaunchKernelGGL((decode_merge_kernel<D, TI, true>), dim3(bh), dim3(NT), 0, p.stream, a.split, a.out, (const float *)a.parts,
+                               dual::DualArgs{}, 0);
+        else
+            hipLaunchKernelGGL((decode_merge_kernel<D, TI, true, true>), dim3(2 * bh), dim3(NT), 0, p.stream, a.split, a.out,
+                               (const float *)a.parts, dual::dual_args(p), bh);
     }
     return hipGetLastError();
 }
@@ -404,17 +487,13 @@ bool mfma_decode_f32_takes(const Problem &p)
 
 hipError_t mfma_decode_f32(const Problem &p)
 {
-    hipError_t e = hipErrorInvalidValue;
     switch (p.d) {
-        case 16: e = f32_by_dtype<16>(p); break;
-        case 32: e = f32_by_dtype<32>(p); break;
-        case 64: e = f32_by_dtype<64>(p); break;
-        case 128: e = f32_by_dtype<128>(p); break;
-        default: break;
+        case 16: return f32_by_dtype<16>(p);
+        case 32: return f32_by_dtype<32>(p);
+        case 64: return f32_by_dtype<64>(p);
+        case 128: return f32_by_dtype<128>(p);
+        default: return hipErrorInvalidValue;
     }
-    // without lengths every sequence is long; with them, those of at most min(d, 64) keys are served in key space
-    if (e != hipSuccess || p.seqlens == nullptr) return e;
-    return dual_decode(p);
 }
 
 }  // namespace llla

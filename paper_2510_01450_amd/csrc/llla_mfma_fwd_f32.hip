@@ -82,31 +82,6 @@ __device__ __forceinline__ void alternate()
     }
 }
 
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-
-// x = h + m + l, three bf16 (24 significant bits; bf16 has the exponents of fp32, so this holds over its whole range).  The
-// remainders x - h are v_dot2_f32_bf16 with (-1, 0) and (0, -1), exact like the subtractions they stand for: one instruction per value
-// instead of an unpacking and a subtraction.  (The two constants come in scalar registers: as a literal the compiler encodes (-1, 0)
-// as the inline constant -1.0, which this instruction reads as the fp32 bit pattern, i.e. (0, -1); seen with ROCm 7.2.)
-__device__ inline void split3_bf16(const float (&x)[8], bf16x8 &h, bf16x8 &m, bf16x8 &l)
-{
-    unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
-    asm("" : "+s"(lo), "+s"(hi));
-    const bf16x2v first = __builtin_bit_cast(bf16x2v, lo), second = __builtin_bit_cast(bf16x2v, hi);
-#pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-        const bf16x2v a = __builtin_convertvector(float2v{x[t], x[t + 1]}, bf16x2v);
-        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, first, x[t], false), r1 = __builtin_amdgcn_fdot2_f32_bf16(a, second, x[t + 1], false);
-        const bf16x2v b = __builtin_convertvector(float2v{r0, r1}, bf16x2v);
-        const bf16x2v c = __builtin_convertvector(float2v{__builtin_amdgcn_fdot2_f32_bf16(b, first, r0, false),
-                                                          __builtin_amdgcn_fdot2_f32_bf16(b, second, r1, false)}, bf16x2v);
-        h[t] = a[0]; h[t + 1] = a[1];
-        m[t] = b[0]; m[t + 1] = b[1];
-        l[t] = c[0]; l[t + 1] = c[1];
-    }
-}
-
 // LIVE: feature blocks of 16 that can be non-zero (4, except for calls at d = 16 / 32 that run here on zero-padded
 // copies: the tiles, scaled operands and solve blocks of padded feature blocks are skipped, see moments_body).
 // BWD (the backward pass, llla_mfma_bwd_f32.hip): Mg holds the row maxima already, so nothing is ever rescaled and one of
