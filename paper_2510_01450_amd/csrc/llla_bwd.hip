@@ -229,33 +229,33 @@ __global__ __launch_bounds__(NT) void bwd_rows_kernel(const TI *__restrict__ Qg,
             if (r == 0) { y0s[slot] = y0[0]; u0s[slot] = y0[1]; }
             if (r < D) { y1s[slot * D + r] = y[0]; u1s[slot * D + r] = y[1]; }
         } else {
-        for (int k = 0; k < P; ++k) {
-            __syncthreads();
-            const float pinv = 1.f / S[k * LS + k];
-            for (int row = k + 1 + r; row < P; row += TPQ) {
-                const float f = S[row * LS + k] * pinv;
-                for (int c = k + 1; c <= P + 1; ++c) S[row * LS + c] = fmaf(-f, S[k * LS + c], S[row * LS + c]);
-            }
-        }
-        for (int k = P - 1; k >= 0; --k) {
-            __syncthreads();
-            const float pinv = 1.f / S[k * LS + k];
-            const float yk = S[k * LS + P] * pinv;
-            const float uk = S[k * LS + P + 1] * pinv;
-            if (r == 0) {
-                if (k == 0) {
-                    y0s[slot] = yk;
-                    u0s[slot] = uk;
-                } else {
-                    y1s[slot * D + k - 1] = yk;
-                    u1s[slot * D + k - 1] = uk;
+            for (int k = 0; k < P; ++k) {
+                __syncthreads();
+                const float pinv = 1.f / S[k * LS + k];
+                for (int row = k + 1 + r; row < P; row += TPQ) {
+                    const float f = S[row * LS + k] * pinv;
+                    for (int c = k + 1; c <= P + 1; ++c) S[row * LS + c] = fmaf(-f, S[k * LS + c], S[row * LS + c]);
                 }
             }
-            for (int row = r; row < k; row += TPQ) {
-                S[row * LS + P] = fmaf(-S[row * LS + k], yk, S[row * LS + P]);
-                S[row * LS + P + 1] = fmaf(-S[row * LS + k], uk, S[row * LS + P + 1]);
+            for (int k = P - 1; k >= 0; --k) {
+                __syncthreads();
+                const float pinv = 1.f / S[k * LS + k];
+                const float yk = S[k * LS + P] * pinv;
+                const float uk = S[k * LS + P + 1] * pinv;
+                if (r == 0) {
+                    if (k == 0) {
+                        y0s[slot] = yk;
+                        u0s[slot] = uk;
+                    } else {
+                        y1s[slot * D + k - 1] = yk;
+                        u1s[slot * D + k - 1] = uk;
+                    }
+                }
+                for (int row = r; row < k; row += TPQ) {
+                    S[row * LS + P] = fmaf(-S[row * LS + k], yk, S[row * LS + P]);
+                    S[row * LS + P + 1] = fmaf(-S[row * LS + k], uk, S[row * LS + P + 1]);
+                }
             }
-        }
         }
         __syncthreads();
     }
