@@ -254,7 +254,7 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
     }
     __syncthreads();                                      // the tiles become the waves' scratch
     if (wave < NB) {
-        factorise_one<NB, NX + 1>(acc, lds.tiles[0] + wave * 16 * SC_PITCH, g, nn, 0.5f * out.lambda, x);
+        factorise_columns<NB, NX + 1>(acc, lds.tiles[0] + wave * 16 * SC_PITCH, g, nn, 0.5f * out.lambda, x);
         float av[4 * NB], cv[4 * NB], saa = 0.f, sac = 0.f;
 #pragma unroll
         for (int i = 0; i < 4 * NB; ++i) {

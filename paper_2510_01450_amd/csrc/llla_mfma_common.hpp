@@ -385,21 +385,67 @@ __device__ inline void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memor
 template <int NB>
 __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I * (I - 1) / 2 + (J - I); }
 
-// Blocked factorisation of ONE system per wave, all in registers / wave-private LDS scratch (the first half of solve_one and
-// of the decode tail's solve; solve_wave_q4 has its own for four systems at d = 64):
+// Blocked factorisation of ONE system per wave, all in registers / wave-private LDS scratch (the first half of solve_one;
+// solve_wave_q4 has its own for four systems at d = 64):
 //   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I) (MFMA accumulator layout)
-//        x[v][P]               NX further block columns, negated right-hand sides -B in the same layout
 //        scw                   >= 16*SC_PITCH floats of LDS owned by this wave
 //        pivot_floor           half the ridge of the row (see chol_inv16)
-//   out: acc(P,J), P < J, holds U(P,J) and acc(P,P) holds N_P = -U(P,P)^{-1}, with Sigma~ + lambda I = U^T U; x = U^{-T} B.
+//   out: acc(P,J), P < J, holds U(P,J) and acc(P,P) holds N_P = -U(P,P)^{-1}, with Sigma~ + lambda I = U^T U.
 // 16-blocked upper Cholesky whose block products are C += A^T B on fp32 MFMA; the diagonal tile is factorised with one
 // row per lane and DPP row broadcasts (the four lane groups of the wave hold four copies).  The matrix cores only add
 // products, so everything that the textbook recursion subtracts is carried negated instead: the trailing matrix (T), the
 // inverse diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on
-// the vector ALU.  The next diagonal tile is updated first and on its way through LDS while the other products issue.
-template <int NB, int NX = 0>
-__device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor,
-                                              f32x4 (*x)[NB] = nullptr)
+// the vector ALU.
+template <int NB>
+__device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor)
+{
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int P = 0; P < NB; ++P) {
+        // diagonal tile -> one row per lane, symmetrised
+#pragma unroll
+        for (int t = 0; t < 4; ++t) scw[(4 * g + t) * SC_PITCH + nn] = acc[upper_tile<NB>(P, P)][t];
+        wave_sync();
+        float a[16], li[16];
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[4 * c4 + t] = v[t];
+        }
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
+        wave_sync();
+        chol_inv16(a, li, nn, pivot_floor);
+        if (g == 0) {
+#pragma unroll
+            for (int c4 = 0; c4 < 4; ++c4)
+                *reinterpret_cast<f32x4 *>(scw + nn * SC_PITCH + 4 * c4) = f32x4{li[4 * c4], li[4 * c4 + 1], li[4 * c4 + 2], li[4 * c4 + 3]};
+        }
+        wave_sync();
+        // N_P in tile layout: reg t = N[4g+t][nn] = -Linv[nn][4g+t]; it replaces the consumed diagonal tile;
+        // U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
+        const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * g);
+        acc[upper_tile<NB>(P, P)] = ui;
+#pragma unroll
+        for (int J = P + 1; J < NB; ++J) acc[upper_tile<NB>(P, J)] = tile_atb(zero, ui, acc[upper_tile<NB>(P, J)]);
+#pragma unroll
+        for (int I = P + 1; I < NB; ++I)
+#pragma unroll
+            for (int J = I; J < NB; ++J)
+                acc[upper_tile<NB>(I, J)] = tile_atb(acc[upper_tile<NB>(I, J)], acc[upper_tile<NB>(P, I)], acc[upper_tile<NB>(P, J)]);
+        __builtin_amdgcn_sched_barrier(0);
+        wave_sync();
+    }
+}
+
+// The same with further block columns (the decode tail's solve at d <= 64):
+//   in : x[v][P]               NX further block columns, negated right-hand sides -B in the same layout
+//   out: x = U^{-T} B
+// The next diagonal tile is updated first and on its way through LDS while the other products issue.
+template <int NB, int NX>
+__device__ __forceinline__ void factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor,
+                                                  f32x4 (&x)[NX][NB])
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     auto put_diagonal = [&](int P) {

@@ -31,6 +31,7 @@ constexpr int TILE_H = STEP * D;               // halves of one natural [32 keys
 constexpr int STAGE_H = 2 * TILE_H;            // K tile + V tile
 constexpr int NSIG = DecShape<D>::NSIG, HDR = DecShape<D>::HDR, REC_F = DecShape<D>::REC_F;      // record layout
 constexpr int KEYS_MIN = 8 * STEP;             // fewest keys worth a workgroup
+constexpr int FLAT_KEYS = 2048;                // keys per workgroup of the even cut from which the flat one is taken
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MIN_L = 256;                     // shorter caches go to the vector path
 constexpr int MAX_SPLIT = 32;
@@ -480,7 +481,12 @@ hipError_t mfma_decode128(const Problem &p)
     a.Vg = (const bf16_t *)p.V;
     a.sk = p.sk;
     a.sv = p.sv;
-    a.split = choose_split(p, make_split(bh, p.n), p.ws_bytes / (REC_F * sizeof(float)), SLOTS, STEP, KEYS_MIN, MAX_SPLIT);
+    // The flat cut leaves more records of 100 KB for the merge than it saves keys for the pass unless a workgroup's share is long: us,
+    // lengths uniform in [L/8, L], even and flat cut: 32 heads x 8192 76 / 90, 256 x 2048 78 / 97, 72 x 5147 80 / 89, but 256 x 16384
+    // 309 / 284.  Without room for records (0) choose_split takes the even one.
+    const int nsplit = make_split(bh, p.n);
+    const size_t room = p.n / nsplit >= FLAT_KEYS ? p.ws_bytes / (REC_F * sizeof(float)) : 0;
+    a.split = choose_split(p, nsplit, room, SLOTS, STEP, KEYS_MIN, MAX_SPLIT);
     a.cscale = p.scale * LOG2E;
     a.parts = static_cast<float *>(p.ws);
     const HeadOut out{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
