@@ -206,20 +206,32 @@ struct HeadOut {
     float lambda;
 };
 
-// LDS of one head: NBUF copies of the tiles (the merge of a workgroup's waves), NW copies of the vectors
+// LDS of one head: NBUF copies of the tiles (the merge of a workgroup's waves), NW copies of the vectors, the solve's scratch
 template <int D, int NBUF, int NW>
 struct HeadLds {
     float tiles[NBUF][DecShape<D>::NTILES * 256];
     float mu[NW][D], yv[NW][D];
     float mw[4], om[4];
-    static_assert((DecShape<D>::NB < 4 ? DecShape<D>::NB : 4) * 16 * SC_PITCH <= DecShape<D>::NTILES * 256, "the solve's scratch reuses the tiles");
+    float sc[D == 128 ? 16 * SC_PITCH + D + 4 : DecShape<D>::NB * 16 * SC_PITCH];
 };
 
+// The ridge of attempt a at a solve: lambda + eta S~_ii.  The centred matrix carries the rounding of moments of the size of |k|^2: some
+// 2^-24 of them, or 2^-11 where the weighted keys are 16-bit floats.  Where that exceeds lambda a pivot comes out below lambda / 2,
+// and a factorisation that only raises such pivots amplifies the noise of their columns block by block until it overflows (a common
+// offset of 100 in 64 features: 23 of 48 outputs not finite).  The solve is then repeated with a ridge of the size of that noise, feature by
+// feature; the last one dominates any.  All arithmetic before the first such pivot is that of lambda alone.
+constexpr int SOLVE_TRIES = 5;
+__device__ inline float noise_ridge(int attempt) { return attempt == 0 ? 0.f : __builtin_ldexpf(1.f, 6 * attempt - 28); }
+
 // Solve and output of one head whose merged moments lie in lds.tiles[0], lds.mu[0], lds.yv[0], lds.om[0].  Called by all four
-// waves after a barrier; overwrites lds.tiles[0].
-// With Sigma~ + lambda I = U^T U, a = U^{-T} mu~, c = U^{-T} q and W = U^{-T} G~ the output is y0 sum w v + W^T (c - a y0), y0 =
-// (1 - a.c) / (omega - a.a): no back substitution.  mu~, q and G~ are further block columns of the factorisation; wave W
-// carries column W of G~ and repeats the factorisation itself (every wave has a SIMD of its own, and an exchange
+// waves after a barrier.
+// The intercept is eliminated first: with the centred Sigma_c = Sigma~ - mu~ mu~^T / omega, q_c = q - mu~ / omega, G_c = G~ -
+// mu~ (sum w v)^T / omega and Sigma_c + lambda I = U^T U the output is sum w v / omega + (U^{-T} G_c)^T U^{-T} q_c: every pivot is
+// lambda or more however few keys the head sees.  Eliminated last it leaves omega - mu~^T (Sigma~ + lambda I)^{-1} mu~, which cancels
+// to zero in fp32 where one key far from the origin holds nearly all the weight (a common offset of 100 in the 32 features of 1000
+// fp32 keys, ridge 10^-2: 14 of 48 outputs were not finite).
+// q_c and the columns of G_c are further block columns of the factorisation, so there is no back substitution; wave W
+// carries column W of G_c and repeats the factorisation itself (every wave has a SIMD of its own, and an exchange
 // of tiles would cost the barriers that this saves).  What bounds it is the serial chain of the diagonal tiles.  One wave with both
 // substitutions on the vector ALU: 64 heads of 1024 to 8192 fp32 keys, d = 64, 86.7 instead of 81.2 us; 256 heads x 4096 bf16
 // keys, d = 32, 53.7 instead of 51.5.
@@ -227,89 +239,115 @@ template <int D, typename TI, bool PERM, class Lds>
 __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
 {
     using S = DecShape<D>;
-    constexpr int NB = S::NB, NX = 1;
-    static_assert(NB <= 4, "a column of G~ per wave");
+    constexpr int NB = S::NB;
+    static_assert(NB <= 4, "a column of G_c per wave");
     const int g = lane / 16, nn = lane % 16;
-    f32x4 acc[S::NSIG], x[NX + 1][NB];
-    if (wave < NB) {                                      // scalar branches: the second one contains MFMAs
+    if (wave >= NB) return;                               // (scalar branches: what follows contains MFMAs)
+    const float oinv = 1.f / lds.om[0], yc = lds.yv[0][16 * wave + nn], floor = 0.5f * out.lambda;
+    const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
+    f32x4 acc[S::NSIG], x[2][NB];                         // x: the wave's column of G_c; q_c in column 0
+    for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
+        const float eta = noise_ridge(attempt);
+        float mc[NB];
 #pragma unroll
-        for (int t = 0; t < S::NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][t * 256 + lane * 4]);
-        const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
+        for (int J = 0; J < NB; ++J) mc[J] = lds.mu[0][16 * J + nn];
 #pragma unroll
         for (int P = 0; P < NB; ++P) {
+            const f32x4 mr = oinv * *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
+            const f32x4 gt = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * P + wave) * 256 + lane * 4]);
 #pragma unroll
-            for (int v = 0; v < NX; ++v)
-                x[v][P] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * P + wave + 4 * v) * 256 + lane * 4]);
-            const f32x4 m = *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
+            for (int J = P; J < NB; ++J) {
+                const f32x4 st = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][upper_tile<NB>(P, J) * 256 + lane * 4]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    float v = fmaf(mr[t], mc[J], -st[t]);
+                    if (J == P) v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                    acc[upper_tile<NB>(P, J)][t] = v;
+                }
+            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                acc[upper_tile<NB>(P, P)][t] -= (nn == 4 * g + t) ? out.lambda : 0.f;
+                x[0][P][t] = fmaf(mr[t], yc, -gt[t]);
                 const TI qv = qp[PERM ? NB * (4 * g + t) + P : 16 * P + 4 * g + t];
                 float q;
                 if constexpr (sizeof(TI) == 2) q = bf16_to_f32(qv);
                 else q = qv;
-                x[NX][P][t] = nn == 0 ? -m[t] : nn == 1 ? -q : 0.f;       // columns 0 and 1: mu~ and q
+                x[1][P][t] = nn == 0 ? mr[t] - q : 0.f;
             }
         }
+        const float low = factorise_columns<NB, 2>(acc, lds.sc + wave * 16 * SC_PITCH, g, nn, floor, x);
+        if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;
     }
-    __syncthreads();                                      // the tiles become the waves' scratch
-    if (wave < NB) {
-        factorise_columns<NB, NX + 1>(acc, lds.tiles[0] + wave * 16 * SC_PITCH, g, nn, 0.5f * out.lambda, x);
-        float av[4 * NB], cv[4 * NB], saa = 0.f, sac = 0.f;
+    float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4 * NB; ++i) {
-            av[i] = row_bcast<0>(x[NX][i / 4][i % 4]);
-            cv[i] = row_bcast<1>(x[NX][i / 4][i % 4]);
-            saa = fmaf(av[i], av[i], saa);
-            sac = fmaf(av[i], cv[i], sac);
-        }
-        saa = rows_allsum(saa);
-        sac = rows_allsum(sac);
-        const float y0 = (1.f - sac) / (lds.om[0] - saa);
-#pragma unroll
-        for (int v = 0; v < NX; ++v) {
-            const int J = wave + 4 * v;
-            float s = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[v][i / 4][i % 4], fmaf(-av[i], y0, cv[i]), s);
-            s = rows_allsum(s);
-            const float o = fmaf(y0, lds.yv[0][16 * J + nn], s);
-            if (g == 0) {
-                const size_t at = (size_t)bh * D + (PERM ? NB * nn + J : 16 * J + nn);
-                if (out.out_bf16) static_cast<bf16_t *>(out.o)[at] = f32_to_bf16(o);
-                else static_cast<float *>(out.o)[at] = o;
-            }
-        }
+    for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[0][i / 4][i % 4], row_bcast<0>(x[1][i / 4][i % 4]), s);
+    s = rows_allsum(s);
+    const float o = fmaf(oinv, yc, s);
+    if (g == 0) {
+        const size_t at = (size_t)bh * D + (PERM ? NB * nn + wave : 16 * wave + nn);
+        if (out.out_bf16) static_cast<bf16_t *>(out.o)[at] = f32_to_bf16(o);
+        else static_cast<float *>(out.o)[at] = o;
     }
 }
 
 // The same at d = 128, where the further block columns would be 108 of 220 tile products per wave (merge kernel 56 us instead of
-// 49): one wave factorises and substitutes on the vector ALU, all waves form the output.
+// 49): one wave factorises and substitutes on the vector ALU, all waves form the output as y0 sum w v + G~^T y1, y0 = (1 - mu~ . y1) /
+// omega.
 template <int D, typename TI, bool PERM, class Lds>
 __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
 {
     using S = DecShape<D>;
     constexpr int NB = S::NB;
     const int g = lane / 16, nn = lane % 16;
-    float *scratch = lds.tiles[0], *ys = scratch + 16 * SC_PITCH;         // tiles of Sigma~, consumed before they are written
-    static_assert(16 * SC_PITCH + D + 4 <= S::NSIG * 256, "scratch and solution fit the tiles of Sigma~");
+    float *scratch = lds.sc, *ys = scratch + 16 * SC_PITCH;
     if (wave == 0) {                                      // scalar branch: the block contains MFMAs
         f32x4 acc[S::NSIG], rhs[NB];
-        float y0;
+        const float oinv = 1.f / lds.om[0], floor = 0.5f * out.lambda;
+        for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
+            const float eta = noise_ridge(attempt);
+            float mc[NB];
 #pragma unroll
-        for (int t = 0; t < S::NSIG; ++t) acc[t] = -*reinterpret_cast<const f32x4 *>(&lds.tiles[0][t * 256 + lane * 4]);
+            for (int J = 0; J < NB; ++J) mc[J] = lds.mu[0][16 * J + nn];
 #pragma unroll
-        for (int P = 0; P < NB; ++P)                      // the solve takes -(Sigma~ + lambda I)
+            for (int P = 0; P < NB; ++P) {                // -(Sigma_c + ridge)
+                const f32x4 mr = oinv * *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[upper_tile<NB>(P, P)][t] -= (nn == 4 * g + t) ? out.lambda : 0.f;
+                for (int J = P; J < NB; ++J) {
+                    const f32x4 st = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][upper_tile<NB>(P, J) * 256 + lane * 4]);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        float v = fmaf(mr[t], mc[J], -st[t]);
+                        if (J == P) v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                        acc[upper_tile<NB>(P, J)][t] = v;
+                    }
+                }
+            }
+            float low = INFINITY;
+            factorise_one<NB, true>(acc, scratch, g, nn, floor, &low);
+            if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;
+        }
         const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
-        solve_one<NB>(acc, rhs, y0, lds.om[0], scratch, g, nn, 0.5f * out.lambda, [&](int P, float &m, float &q, float &e) {
-            m = -lds.mu[0][16 * P + nn];
+        float tv[1][NB];                                  // -q_c, U^{-T} q_c, its negative
+#pragma unroll
+        for (int P = 0; P < NB; ++P) {
             const TI v = qp[PERM ? NB * nn + P : 16 * P + nn];
-            if constexpr (sizeof(TI) == 2) q = -bf16_to_f32(v);
-            else q = -v;
-            (void)e;
-        });
+            float q;
+            if constexpr (sizeof(TI) == 2) q = bf16_to_f32(v);
+            else q = v;
+            tv[0][P] = fmaf(lds.mu[0][16 * P + nn], oinv, -q);
+        }
+        substitute_forward<NB, 1>(acc, tv, scratch, g, nn);
+#pragma unroll
+        for (int P = 0; P < NB; ++P) tv[0][P] = -tv[0][P];
+        substitute_back<NB, 1>(acc, tv, rhs, scratch, g, nn);
+        float my = 0.f;
+#pragma unroll
+        for (int P = 0; P < NB; ++P) {
+            const f32x4 m = *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) my = fmaf(m[t], rhs[P][t], my);
+        }
+        const float y0 = (1.f - rows_allsum(my)) * oinv;
         if (nn == 0) {
 #pragma unroll
             for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[P];

@@ -294,7 +294,9 @@ __device__ inline void trinv_row(float (&li)[16], float mul)
 // pivot_floor: every pivot of the Cholesky factorisation of (a positive semi-definite matrix + lambda I) is
 // at least lambda in exact arithmetic; a computed pivot below the floor (half of lambda) is a rounding
 // artefact of an ill-conditioned early row and is raised to it, which keeps the factorisation finite.
-__device__ inline void chol_inv16(float (&a)[16], float (&li)[16], int r, float pivot_floor)
+// LOW: *low becomes the smallest pivot before that, if smaller (NaN pivots are passed over).
+template <bool LOW = false>
+__device__ inline void chol_inv16(float (&a)[16], float (&li)[16], int r, float pivot_floor, float *low = nullptr)
 {
     float nl2[16];      // -L[r][k] / L[k][k]  (column-scaled factor, strictly lower part kept, negated)
     float dinv_own = 0.f;
@@ -303,6 +305,7 @@ __device__ inline void chol_inv16(float (&a)[16], float (&li)[16], int r, float 
         float dk;
         const float ak = a[k];
         LLLA_SWITCH16(k, dk = bcast_settled<KK>(ak));        // diagonal entry of step k, from lane k of the row
+        if constexpr (LOW) *low = fminf(*low, dk);
         dk = fmaxf(dk, pivot_floor);
         float rinv = __builtin_amdgcn_rsqf(dk);
         rinv = rinv * (1.5f - 0.5f * dk * rinv * rinv);      // one Newton step
@@ -396,8 +399,9 @@ __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I *
 // products, so everything that the textbook recursion subtracts is carried negated instead: the trailing matrix (T), the
 // inverse diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on
 // the vector ALU.
-template <int NB>
-__device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor)
+// LOW: low as in chol_inv16, over all pivots.
+template <int NB, bool LOW = false>
+__device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor, float *low = nullptr)
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -416,7 +420,7 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 #pragma unroll
         for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
         wave_sync();
-        chol_inv16(a, li, nn, pivot_floor);
+        chol_inv16<LOW>(a, li, nn, pivot_floor, low);
         if (g == 0) {
 #pragma unroll
             for (int c4 = 0; c4 < 4; ++c4)
@@ -441,12 +445,13 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 
 // The same with further block columns (the decode tail's solve at d <= 64):
 //   in : x[v][P]               NX further block columns, negated right-hand sides -B in the same layout
-//   out: x = U^{-T} B
+//   out: x = U^{-T} B; returns the smallest pivot before it was raised to the floor
 // The next diagonal tile is updated first and on its way through LDS while the other products issue.
 template <int NB, int NX>
-__device__ __forceinline__ void factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor,
-                                                  f32x4 (&x)[NX][NB])
+__device__ __forceinline__ float factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor,
+                                                   f32x4 (&x)[NX][NB])
 {
+    float low = INFINITY;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     auto put_diagonal = [&](int P) {
 #pragma unroll
@@ -467,7 +472,7 @@ __device__ __forceinline__ void factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2
 #pragma unroll
         for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
         wave_sync();
-        chol_inv16(a, li, nn, pivot_floor);
+        chol_inv16<true>(a, li, nn, pivot_floor, &low);
         if (g == 0) {
 #pragma unroll
             for (int c4 = 0; c4 < 4; ++c4)
@@ -499,6 +504,7 @@ __device__ __forceinline__ void factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+    return low;
 }
 
 }  // namespace mfma
