@@ -295,7 +295,9 @@ __device__ inline void trinv_row(float (&li)[16], float mul)
 // at least lambda in exact arithmetic; a computed pivot below the floor (half of lambda) is a rounding
 // artefact of an ill-conditioned early row and is raised to it, which keeps the factorisation finite.
 // LOW: *low becomes the smallest pivot before that, if smaller (NaN pivots are passed over).
-template <bool LOW = false>
+// DROP: such a pivot is not raised but made infinite, which takes its column and its unknown out of the system.  Where the pivot is
+// noise its column is too, of the size of the matrix's rounding: divided by the root of a raised pivot a few such columns in a row overflow.
+template <bool LOW = false, bool DROP = false>
 __device__ inline void chol_inv16(float (&a)[16], float (&li)[16], int r, float pivot_floor, float *low = nullptr)
 {
     float nl2[16];      // -L[r][k] / L[k][k]  (column-scaled factor, strictly lower part kept, negated)
@@ -306,9 +308,10 @@ __device__ inline void chol_inv16(float (&a)[16], float (&li)[16], int r, float 
         const float ak = a[k];
         LLLA_SWITCH16(k, dk = bcast_settled<KK>(ak));        // diagonal entry of step k, from lane k of the row
         if constexpr (LOW) *low = fminf(*low, dk);
-        dk = fmaxf(dk, pivot_floor);
+        if constexpr (!DROP) dk = fmaxf(dk, pivot_floor);
         float rinv = __builtin_amdgcn_rsqf(dk);
         rinv = rinv * (1.5f - 0.5f * dk * rinv * rinv);      // one Newton step
+        if constexpr (DROP) rinv = dk < pivot_floor ? 0.f : rinv;
         const float u = ak * rinv;                           // L[r][k] in rows r >= k; rows above are finished and never read again
         const float nu = -u;
         nl2[k] = (r > k) ? nu * rinv : 0.f;

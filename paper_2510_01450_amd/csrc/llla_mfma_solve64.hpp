@@ -168,13 +168,13 @@ __device__ inline float row_transpose_sum(const float (&p)[16], int nn)
 //        tmu[P], tq[P]     lane (q, r): -mu~_q[16P + r] and -q_q[16P + r]  (both destroyed)
 //        te[P], r0         WITH_U: lane (q, r): -r1_q[16P + r]; r0 of the lane's query
 //        omega             omega of the lane's query (lane group g = query g)
-//        scw               >= 4 * 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor as in chol_inv16
+//        scw               >= 4 * 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor, DROP as in chol_inv16
 //   out: y1[P] = y1_q[16P + r] in lane (q, r), y0 of the lane's query in every lane;  WITH_U: u1[P], u0 likewise
 // with [omega mu~^T; mu~ Sigma~ + lambda I] [y0; y1] = [1; q] and, WITH_U, the same matrix times [u0; u1] = [r0; r1].
 // LIVE < 4 (a call at d = 16 / 32 on zero-padded copies): feature blocks LIVE..3 of every key and query are zero, the
 // matrix is block diagonal with lambda I in those blocks and their right-hand sides are zero, so the solution vanishes
 // there and only blocks 0..LIVE-1 are factorised and substituted.
-template <bool WITH_U, int LIVE = 4>
+template <bool WITH_U, int LIVE = 4, bool DROP = false>
 __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[4], float (&tq)[4], float (&te)[4], float r0,
                                               float omega, float *scw, int g, int nn, float pivot_floor, float (&y1)[4],
                                               float &y0, float (&u1)[4], float &u0)
@@ -205,7 +205,7 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
             for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + my[c * SC_PITCH + nn]);    // -T, symmetrised
         }
         wave_sync();
-        chol_inv16(a, li, nn, pivot_floor);
+        chol_inv16<false, DROP>(a, li, nn, pivot_floor);
         {
             float *my = scw + g * 16 * SC_PITCH;
 #pragma unroll

@@ -62,3 +62,15 @@ def test_workspace_of_the_vector_kernels_is_enough():
     got = llla.llla_backward(Q, K, V, G, w.lam, w.scale, return_dlambda=True, workspace=ws)
     want = llla.llla_backward(Q, K, V, G, w.lam, w.scale, return_dlambda=True, path="valu")
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("n,offset", [(500, 30.0), (130, 100.0), (64, 100.0)])
+def test_common_offset_stays_finite(n, offset):
+    """Keys and queries far from the origin: the rounding of moments of the size of |k|^2 exceeds the ridge, pivots of the centred
+    matrix come out negative, and what they would be divided into must not overflow.  (Nothing but finiteness can be asked for:
+    |k|^2 / ridge * 2^-24 is 0.4 and 4.)"""
+    g = torch.Generator(device="cpu").manual_seed(n)
+    Q, K, V, G = (torch.randn((1, 4, n, 64), generator=g).to(DEV) for _ in range(4))
+    Q, K = Q + offset, K + offset
+    for x in (llla.llla_forward(Q, K, V, 1e-2, 1 / 8.0),) + llla.llla_backward(Q, K, V, G, 1e-2, 1 / 8.0, return_dlambda=True):
+        assert bool(torch.isfinite(x).all())
