@@ -49,6 +49,21 @@ __device__ inline int balanced_block(int y, int ny, int heads)
     return ((y / group) & 1) != 0 && y < 4 * group && first + group <= ny ? 2 * first + group - 1 - y : y;
 }
 
+// The blocks of a head on y and z of a grid: y alone ends at 65535, and a forward call is accepted up to 64 times that many rows.
+struct BlockGrid { unsigned y, z; };
+constexpr BlockGrid block_grid(int blocks)
+{
+    const unsigned z = (unsigned)(blocks + 65534) / 65535u;
+    return BlockGrid{((unsigned)blocks + z - 1) / z, z};
+}
+constexpr bool covered(int blocks)
+{
+    return block_grid(blocks).y <= 65535 && block_grid(blocks).y * block_grid(blocks).z >= (unsigned)blocks &&
+           block_grid(blocks).y * (block_grid(blocks).z - 1) < (unsigned)blocks;
+}
+static_assert(covered(1) && covered(65535) && block_grid(65535).z == 1 && covered(65536) && covered(65537) && covered(131070),
+              "row blocks of the longest forward call: 64 x 65535 rows");
+
 // C += T R^T over the features: T = 16 rows of a tile (tile row nn of the lane), R = a row per lane in registers; contraction
 // slot (s, g) stands for feature DD/4 g + s on both sides
 template <int DD>
@@ -95,9 +110,11 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     static_assert(4 * 16 * RP <= 4 * RT * DD, "the final sums reuse the tiles");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     const int rg = wave & 1, ks = wave >> 1;
-    // head on blockIdx.x (dispatched fastest), row block on y, longest rows first
+    // head on blockIdx.x (dispatched fastest), row block on y (and z, see block_grid), longest rows first
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int i0 = skip + ((int)gridDim.y - 1 - balanced_block(blockIdx.y, gridDim.y, gridDim.x)) * RT;
+    const int ny = (n - skip + RT - 1) / RT, yb = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+    if (yb >= ny) return;
+    const int i0 = skip + (ny - 1 - balanced_block(yb, ny, gridDim.x)) * RT;
     const int iq = min(i0 + 16 * rg + nn, n - 1);           // rows past the end repeat the last one and are not stored
     const int jlim = MODE == 2 && !causal ? n - 1 : iq;     // the last key the lane's query sees, and the wave's queries
     const int wlast = MODE == 2 && !causal ? n - 1 : min(i0 + 16 * rg + 15, n - 1);
@@ -449,7 +466,8 @@ hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y,
 {
     if (skip >= p.n) return hipSuccess;
     const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K), *V = static_cast<const float *>(p.V);
-    hipLaunchKernelGGL((bwd_rows_f32_kernel<64, 2>), dim3(p.B * p.H, (p.n - skip + RT - 1) / RT), dim3(256), 0, p.stream, Q, K, V,
+    const BlockGrid grid = block_grid((p.n - skip + RT - 1) / RT);
+    hipLaunchKernelGGL((bwd_rows_f32_kernel<64, 2>), dim3(p.B * p.H, grid.y, grid.z), dim3(256), 0, p.stream, Q, K, V,
                        nullptr, p.sq, p.sk, p.sv, llla_strides{}, p.H, p.n, npad, p.scale, 0.f, nullptr, M, Y, nullptr, nullptr, nullptr,
                        nullptr, nullptr, p.causal, skip, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0);
     return hipGetLastError();

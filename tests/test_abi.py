@@ -198,3 +198,12 @@ def test_small_head_dimensions_dispatch_on_the_host():
     assert _bwd(d=32, din=1, n=64, path=0) == 6                          # backward: padded from 64 rows on at d = 32
     assert _bwd(d=16, din=1, n=64, path=2) == 6
     assert _bwd(d=16, din=0, n=64, path=2) == 7                          # no fp32 matrix-core backward
+
+
+def test_longest_calls_are_accepted():
+    """fp32 forward on the matrix cores: up to 64 x 65535 rows, also where that is more than 65535 blocks of the output sweep's 32 rows
+    (what is missing is the workspace); longer ones are refused there."""
+    for d in (64, 32):
+        assert _fwd(n=2097185, d=d, path=2) == 6
+        assert _fwd(n=64 * 65535, d=d, path=2) == 6
+        assert _fwd(n=64 * 65535 + 1, d=d, path=2) == 7
