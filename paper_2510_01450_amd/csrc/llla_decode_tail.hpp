@@ -11,6 +11,7 @@
 #include "llla_mfma_common.hpp"
 #include "llla_mfma_solve128.hpp"
 #include <algorithm>
+#include <type_traits>
 
 namespace llla {
 namespace mfma {
@@ -172,6 +173,7 @@ __device__ inline int piece_lane()
     return lane;
 }
 
+constexpr int MAX_RECORDS = 64;                           // of a head: a lane each in the merge
 struct DecRecords { int first, count; };
 __device__ inline DecRecords dec_records(const DecSplit &s, int bh)
 {
@@ -197,6 +199,24 @@ inline DecSplit choose_split(const Problem &p, int nsplit, size_t room, int gpu_
     return s;
 }
 inline size_t flat_records(int B, int H, int gpu_slots) { return (size_t)(std::max(gpu_slots / H, 1) + B) * H; }
+
+// ---- exchanges inside a wave ------------------------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+
+__device__ __forceinline__ float wave_max_dpp(float x)    // maximum over the wave, in every lane
+{
+    x = fmaxf(x, dpp_f<0xB1>(x));
+    x = fmaxf(x, dpp_f<0x4E>(x));
+    x = fmaxf(x, dpp_f<0x124>(x));
+    x = fmaxf(x, dpp_f<0x128>(x));
+    x = fmaxf(x, rows_1_3_from_rows_0_2(x));
+    x = fmaxf(x, rows_2_3_from_row_1(x));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
+}
 
 // ---- merge, solve, output ----------------------------------------------------------------------------------------------
 struct HeadOut {
@@ -245,9 +265,11 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
     if (wave >= NB) return;                               // (scalar branches: what follows contains MFMAs)
     const float oinv = 1.f / lds.om[0], yc = lds.yv[0][16 * wave + nn], floor = 0.5f * out.lambda;
     const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
-    f32x4 acc[S::NSIG], x[2][NB];                         // x: the wave's column of G_c; q_c in column 0
+    float o = 0.f;
     for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
+        asm volatile("" ::: "memory");                    // (the moments are read again: not kept in registers for a second attempt)
         const float eta = noise_ridge(attempt);
+        f32x4 acc[S::NSIG], x[2][NB];                     // x: the wave's column of G_c; q_c in column 0
         float mc[NB];
 #pragma unroll
         for (int J = 0; J < NB; ++J) mc[J] = lds.mu[0][16 * J + nn];
@@ -276,13 +298,13 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
             }
         }
         const float low = factorise_columns<NB, 2>(acc, lds.sc + wave * 16 * SC_PITCH, g, nn, floor, x);
-        if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;
-    }
-    float s = 0.f;
+        float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[0][i / 4][i % 4], row_bcast<0>(x[1][i / 4][i % 4]), s);
-    s = rows_allsum(s);
-    const float o = fmaf(oinv, yc, s);
+        for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[0][i / 4][i % 4], row_bcast<0>(x[1][i / 4][i % 4]), s);
+        s = rows_allsum(s);
+        o = fmaf(oinv, yc, s);
+        if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;      // (at the end: nothing but o outlives an attempt)
+    }
     if (g == 0) {
         const size_t at = (size_t)bh * D + (PERM ? NB * nn + wave : 16 * wave + nn);
         if (out.out_bf16) static_cast<bf16_t *>(out.o)[at] = f32_to_bf16(o);
@@ -301,10 +323,14 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
     const int g = lane / 16, nn = lane % 16;
     float *scratch = lds.sc, *ys = scratch + 16 * SC_PITCH;
     if (wave == 0) {                                      // scalar branch: the block contains MFMAs
-        f32x4 acc[S::NSIG], rhs[NB];
         const float oinv = 1.f / lds.om[0], floor = 0.5f * out.lambda;
+        const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
         for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
+            int lane_e = lane;                            // an attempt keeps nothing for the next: neither the moments nor what follows
+            asm volatile("" : "+v"(lane_e) :: "memory");  // from the lane index (registers for both cost 0.5 us)
+            const int g = lane_e / 16, nn = lane_e % 16;
             const float eta = noise_ridge(attempt);
+            f32x4 acc[S::NSIG], rhs[NB];
             float mc[NB];
 #pragma unroll
             for (int J = 0; J < NB; ++J) mc[J] = lds.mu[0][16 * J + nn];
@@ -313,7 +339,7 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
                 const f32x4 mr = oinv * *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
 #pragma unroll
                 for (int J = P; J < NB; ++J) {
-                    const f32x4 st = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][upper_tile<NB>(P, J) * 256 + lane * 4]);
+                    const f32x4 st = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][upper_tile<NB>(P, J) * 256 + lane_e * 4]);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         float v = fmaf(mr[t], mc[J], -st[t]);
@@ -324,34 +350,33 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
             }
             float low = INFINITY;
             factorise_one<NB, true>(acc, scratch, g, nn, floor, &low);
+            float tv[1][NB];                                  // -q_c, U^{-T} q_c, its negative
+#pragma unroll
+            for (int P = 0; P < NB; ++P) {
+                const TI v = qp[PERM ? NB * nn + P : 16 * P + nn];
+                float q;
+                if constexpr (sizeof(TI) == 2) q = bf16_to_f32(v);
+                else q = v;
+                tv[0][P] = fmaf(lds.mu[0][16 * P + nn], oinv, -q);
+            }
+            substitute_forward<NB, 1>(acc, tv, scratch, g, nn);
+#pragma unroll
+            for (int P = 0; P < NB; ++P) tv[0][P] = -tv[0][P];
+            substitute_back<NB, 1>(acc, tv, rhs, scratch, g, nn);
+            float my = 0.f;
+#pragma unroll
+            for (int P = 0; P < NB; ++P) {
+                const f32x4 m = *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) my = fmaf(m[t], rhs[P][t], my);
+            }
+            const float y0 = (1.f - rows_allsum(my)) * oinv;
+            if (nn == 0) {
+#pragma unroll
+                for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[P];
+                if (g == 0) ys[D] = y0;
+            }
             if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;
-        }
-        const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
-        float tv[1][NB];                                  // -q_c, U^{-T} q_c, its negative
-#pragma unroll
-        for (int P = 0; P < NB; ++P) {
-            const TI v = qp[PERM ? NB * nn + P : 16 * P + nn];
-            float q;
-            if constexpr (sizeof(TI) == 2) q = bf16_to_f32(v);
-            else q = v;
-            tv[0][P] = fmaf(lds.mu[0][16 * P + nn], oinv, -q);
-        }
-        substitute_forward<NB, 1>(acc, tv, scratch, g, nn);
-#pragma unroll
-        for (int P = 0; P < NB; ++P) tv[0][P] = -tv[0][P];
-        substitute_back<NB, 1>(acc, tv, rhs, scratch, g, nn);
-        float my = 0.f;
-#pragma unroll
-        for (int P = 0; P < NB; ++P) {
-            const f32x4 m = *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) my = fmaf(m[t], rhs[P][t], my);
-        }
-        const float y0 = (1.f - rows_allsum(my)) * oinv;
-        if (nn == 0) {
-#pragma unroll
-            for (int P = 0; P < NB; ++P) *reinterpret_cast<f32x4 *>(&ys[16 * P + 4 * g]) = rhs[P];
-            if (g == 0) ys[D] = y0;
         }
     }
     __syncthreads();
@@ -443,12 +468,18 @@ __device__ __forceinline__ void finish_workgroup(Lds &lds, f32x4 (&acc)[DecShape
     }
 }
 
-// Merge of a head's records (max-rescaled sum), solve, output: one head per workgroup.  The records are fetched eight at a time,
-// every thread owning the same 16 bytes of each, so a head's records are in after one or two round trips to memory.
+// Merge of a head's records (max-rescaled sum), solve, output: one head per workgroup.  Every thread owns the same 16 bytes of each tile
+// of every record.  What bounds it is the number of round trips to memory in front of the solve: lane l fetches maximum and weight sum of
+// record l, one trip for all of them; header vectors and tiles come in groups of records, unconditionally and all in flight together
+// (a load under a condition, or behind the scalar load of its record's maximum, was waited for by itself: 16 trips per eight records),
+// and only records that there are (three of 100 KB cost eight).  Four records at a time; one at d = 128, where it is 25 loads per
+// thread and a compute unit takes 1 us for it however many are requested together.  Eight (at d = 64) take more registers than two workgroups on
+// a compute unit have: 512 heads x 8192 170 instead of 164 us.  us of a call, eight at a time and so: d = 128, 8 heads x 1000 keys 48.7 / 44.1,
+// 16 x 4096 69.5 / 63.9; d = 64, 16 x 4096 28.4 / 26.1; fp32, 16 x 4096 40.0 / 35.6; d = 16, fp32, 64 heads of 512 .. 4096 24.9 / 20.5.
 // DUAL: a call whose sequences of at most 64 keys are served in key space has one more workgroup per head for that, in the same
 // launch; which of the two writes the head follows from its length.
 template <int D, typename TI, bool PERM, bool DUAL = false>
-__global__ __launch_bounds__(DEC_NT, 1) void decode_merge_kernel(DecSplit split, HeadOut out, const float *__restrict__ parts,
+__global__ __launch_bounds__(DEC_NT, D == 128 ? 1 : 2) void decode_merge_kernel(DecSplit split, HeadOut out, const float *__restrict__ parts,
                                                                  dual::DualArgs da = {}, int heads = 0)
 {
     using S = DecShape<D>;
@@ -468,29 +499,53 @@ __global__ __launch_bounds__(DEC_NT, 1) void decode_merge_kernel(DecSplit split,
     const DecRecords rec = dec_records(split, bh);
     const int np = rec.count;
     const float *P0 = parts + (size_t)rec.first * S::REC_F;
-    constexpr int PG = 8;
-    const float mstar = wave_max_strided(P0, 0, np, S::REC_F, lane);
+    float f, om;                                          // factor and weights of record `lane`
+    {
+        const float *P = P0 + (size_t)min(lane, np - 1) * S::REC_F;
+        const float mp = P[0], o = P[1], m = lane < np ? mp : -INFINITY;
+        const float top = wave_max_dpp(m);                // (all lanes take part)
+        f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top);
+        om = rows_allsum(row_allsum(f * o));
+    }
     constexpr int N4 = (S::NTILES * 64 + DEC_NT - 1) / DEC_NT;
     f32x4 acc[N4];
 #pragma unroll
     for (int i = 0; i < N4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float hv = 0.f, om = 0.f;
-    for (int pb = 0; pb < np; pb += PG) {
-        float fk[PG];
+    float hv = 0.f;
+    struct Part { float h; f32x4 v[N4]; };                // what a thread owns of a record
+    constexpr int LAST = S::NTILES * 64 - DEC_NT * (N4 - 1);          // threads that own a piece of the last round
+    // (scalar base and unsigned byte offset per lane: one address register for all loads)
+    const unsigned hoff = 4u * (unsigned)min(tid, 2 * D - 1), toff = 16u * (unsigned)tid, tlast = 16u * (unsigned)min(tid, LAST - 1);
+    auto fetch = [&](Part &r, int p) {
+        const char *P = reinterpret_cast<const char *>(P0 + (size_t)min(p, np - 1) * S::REC_F);
+        r.h = *reinterpret_cast<const float *>(P + 256 + hoff);
 #pragma unroll
-        for (int k = 0; k < PG; ++k) {
-            const float *P = P0 + (size_t)min(pb + k, np - 1) * S::REC_F;            // past the end: factor 0
-            const float m = P[0];
-            fk[k] = (pb + k >= np || m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mstar);
-            om = fmaf(fk[k], P[1], om);
-            if (tid < 2 * D) hv = fmaf(fk[k], P[64 + tid], hv);
-        }
+        for (int i = 0; i < N4; ++i) r.v[i] = *reinterpret_cast<const f32x4 *>(P + 4 * S::HDR + 16 * DEC_NT * i + (i + 1 < N4 ? toff : tlast));
+    };
+    auto add = [&](const Part &r, int p) {
+        const float fp = p < np ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f), p)) : 0.f;
+        hv = fmaf(fp, r.h, hv);
 #pragma unroll
-        for (int i = 0; i < N4; ++i) {
-            const int at = min(tid + DEC_NT * i, S::NTILES * 64 - 1);
+        for (int i = 0; i < N4; ++i) acc[i] += fp * r.v[i];
+    };
+    auto group = [&](int pb, auto size) {                 // records pb .. pb + N - 1, those there are
+        constexpr int N = decltype(size)::value;
+        Part r[N];
 #pragma unroll
-            for (int k = 0; k < PG; ++k)
-                acc[i] += fk[k] * *reinterpret_cast<const f32x4 *>(P0 + (size_t)min(pb + k, np - 1) * S::REC_F + S::HDR + 4 * at);
+        for (int k = 0; k < N; ++k) fetch(r[k], pb + k);
+        __builtin_amdgcn_sched_barrier(0);                // all loads first: the scheduler put the first sum, and its wait, between them
+#pragma unroll
+        for (int k = 0; k < N; ++k) add(r[k], pb + k);
+    };
+    // (all branches on np are scalar)
+    if constexpr (D == 128) {
+#pragma unroll 1
+        for (int p = 0; p < np; ++p) group(p, std::integral_constant<int, 1>{});
+    } else {
+        for (int pb = 0; pb < np; pb += 4) {
+            if (np - pb > 2) group(pb, std::integral_constant<int, 4>{});
+            else if (np - pb > 1) group(pb, std::integral_constant<int, 2>{});
+            else group(pb, std::integral_constant<int, 1>{});
         }
     }
 #pragma unroll

@@ -34,6 +34,7 @@ constexpr int REC_F = DecShape<D>::REC_F;      // floats per record
 constexpr int KEYS_FEW = 256, KEYS_MIN = 512;  // fewest keys worth a workgroup (see make_split)
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MAX_SPLIT = 16;                  // most workgroups per head
+static_assert(MAX_SPLIT < MAX_RECORDS, "the flat cut can leave one piece more");
 constexpr int MIN_L = 256;                     // shorter caches go to the vector path
 constexpr int PRECISE_L = 4 * D;               // sequences up to this length take the two-term weights
 

@@ -35,6 +35,7 @@ constexpr int FLAT_KEYS = 2048;                // keys per workgroup of the even
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MIN_L = 256;                     // shorter caches go to the vector path
 constexpr int MAX_SPLIT = 32;
+static_assert(MAX_SPLIT < MAX_RECORDS, "the flat cut can leave one piece more");
 constexpr int PRECISE_L = 4 * D;               // sequences up to this length take the two-term weights
 // Exchange record of one step's weights (floats): [0, 32) the fp32 weights, [32, 48) the same rounded to f16, [48, 64)
 // their f16 tails, [64] the factor by which the moments so far are rescaled before the step is added, [65] the running
@@ -434,6 +435,8 @@ __device__ __forceinline__ void partial_body(const PartialArgs &a, const DecPiec
     }
 }
 
+// EVEN: one piece per workgroup, known to the compiler (0.5 us of a short call)
+template <bool EVEN>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode128_partial_kernel(PartialArgs a)
 {
     __shared__ __align__(16) bf16_t stage[NSTAGE * STAGE_H];       // 4 stages x 16 KB
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // differ in work (16 tiles plus the weights, 30 to 36 tiles), and wave w of every workgroup runs on SIMD w of its compute unit; the shares
     // therefore rotate with the workgroup index, so that no SIMD gets the heaviest share from both of its workgroups.
     const int role = (wave + (int)blockIdx.x + (int)blockIdx.y) & 3;
-    for_pieces<false>(a.split, [&](const DecPiece &pc) {
+    for_pieces<EVEN>(a.split, [&](const DecPiece &pc) {
         if (__builtin_amdgcn_readfirstlane(pc.L <= PRECISE_L ? 1 : 0)) {
             if (role == 0) partial_body<0, 0, true>(a, pc, stage, &xrec[0][0], wave, piece_lane());
             else if (role == 1) partial_body<0, 1, true>(a, pc, stage, &xrec[0][0], wave, piece_lane());
@@ -491,7 +494,8 @@ hipError_t mfma_decode128(const Problem &p)
     a.parts = static_cast<float *>(p.ws);
     const HeadOut out{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
     stage_mark(p.stream, "decode_partial");
-    hipLaunchKernelGGL(decode128_partial_kernel, a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT), 0, p.stream, a);
+    if (a.split.slots) hipLaunchKernelGGL(decode128_partial_kernel<false>, dim3(a.split.slots, p.H), dim3(NT), 0, p.stream, a);
+    else hipLaunchKernelGGL(decode128_partial_kernel<true>, dim3(a.split.nsplit, bh), dim3(NT), 0, p.stream, a);
     stage_mark(p.stream, "decode_merge");
     hipLaunchKernelGGL((decode_merge_kernel<D, bf16_t, false>), dim3(bh), dim3(NT), 0, p.stream, a.split, out, (const float *)a.parts);
     return hipGetLastError();

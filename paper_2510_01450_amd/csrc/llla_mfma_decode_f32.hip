@@ -42,6 +42,7 @@ struct F32Shape : DecShape<D> {
     static constexpr int KEYS_MIN = TEAM ? 128 : 256;     // fewest keys worth a workgroup (its record is read back by the merge)
     static constexpr int SLOTS = D <= 16 ? 1024 : 512;    // workgroups worth having at once
     static constexpr int MAX_SPLIT = 32;
+    static_assert(MAX_SPLIT < MAX_RECORDS, "the flat cut can leave one piece more");
 };
 
 template <typename TI, int NB>
@@ -85,12 +86,6 @@ __device__ __forceinline__ float frag_f32(const RowFrag<TI, NB> &f, int i)
     else return __uint_as_float((i & 1) ? f.u[i >> 1] & 0xffff0000u : f.u[i >> 1] << 16);
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
-
 // sums of p[0..NC-1] over the 16 lanes of a row; lane n receives the sum of p[n & (NC - 1)]
 template <int NC>
 __device__ __forceinline__ float reduce_chunks(const float (&p)[NC], int nn)
@@ -108,17 +103,6 @@ __device__ __forceinline__ float reduce_chunks(const float (&p)[NC], int nn)
     s += dpp_f<0x124>(s);                                 // row_ror:4
     s += dpp_f<0x128>(s);                                 // row_ror:8
     return s;
-}
-
-__device__ __forceinline__ float wave_max_dpp(float x)    // maximum over the wave, in every lane
-{
-    x = fmaxf(x, dpp_f<0xB1>(x));
-    x = fmaxf(x, dpp_f<0x4E>(x));
-    x = fmaxf(x, dpp_f<0x124>(x));
-    x = fmaxf(x, dpp_f<0x128>(x));
-    x = fmaxf(x, rows_1_3_from_rows_0_2(x));
-    x = fmaxf(x, rows_2_3_from_row_1(x));
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
 
 struct F32Args {

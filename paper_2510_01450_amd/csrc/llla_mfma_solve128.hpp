@@ -24,12 +24,16 @@
 namespace llla {
 namespace mfma {
 
-// sum of x over the four 16-lane rows of the wave (same lane position), in every row
+// sum of x over the four 16-lane rows of the wave (same lane position), in every row.  Row swaps on the vector ALU: through __shfl_xor, i.e.
+// LDS, the sums were six LDS round trips of a block step's chain (inline assembly and its s_nop: see rows_transpose4).
 __device__ inline float rows_allsum(float x)
 {
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
-    return x;
+    float a = x, b = x;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));       // rows 0 0 2 2 and 1 1 3 3
+    a += b;
+    b = a;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return a + b;
 }
 
 // C -> R and R -> C for NV vectors at once through the scratch tile (vector v at scw + 16 v)

@@ -87,3 +87,18 @@ def test_reference_exponent_moves(d, scale):
     ref = oracle.decode(q, Kc, Vc, w.lam, scale)
     got = llla.llla_decode(q.to(DEV), Kc.to(DEV), Vc.to(DEV), w.lam, scale).cpu().numpy()
     print(check(got[:, :, None], ref[:, :, None], np.array([L - 1]), d, w.tol, "scale %g d=%d" % (scale, d)))
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_records_of_a_head(d):
+    """Caches cut into one to a few dozen parts, i.e. every size of the last group of records that the merge takes, and as many
+    maxima.  Unit keys and a small scale: the matrix is well conditioned and the output known to some tens of roundings,
+    which a record with a slightly wrong factor (the gate of the other tests is 1e-4) does not keep."""
+    for L in (130, 300, 520, 780, 1030, 1300, 1600, 2100, 2400, 4200, 4700, 8300, 9100):
+        w, (q, Kc, Vc) = _case(1, 2, L, d, "f32", 2500 + d + L, values="l2")
+        Kc = Kc * torch.linspace(0.5, 1.5, L)[None, None, :, None]                 # the maximum differs from part to part
+        ref = oracle.decode(q, Kc, Vc, w.lam, w.scale)
+        got = llla.llla_decode(q.to(DEV), Kc.to(DEV), Vc.to(DEV), w.lam, w.scale).cpu().double().numpy()
+        err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+        # (hardly more keys than features leave directions that the ridge alone holds: condition number 4 / 10^-2 instead of some tens)
+        assert err.max() <= (64 if L >= 4 * d else 640) * 2.0 ** -24, "L=%d: %.2e" % (L, err.max())
