@@ -31,7 +31,7 @@ constexpr int TILE_H = STEP * D;               // halves of one natural [32 keys
 constexpr int STAGE_H = 2 * TILE_H;            // K tile + V tile
 constexpr int NSIG = DecShape<D>::NSIG, HDR = DecShape<D>::HDR, REC_F = DecShape<D>::REC_F;      // record layout
 constexpr int KEYS_MIN = 8 * STEP;             // fewest keys worth a workgroup
-constexpr int FLAT_KEYS = 2048;                // keys per workgroup of the even cut from which the flat one is taken
+constexpr int FLAT_KEYS = 4096;               // keys per workgroup of the even cut from which the flat one is taken
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MIN_L = 256;                     // shorter caches go to the vector path
 constexpr int MAX_SPLIT = 32;
@@ -54,6 +54,12 @@ int make_split(int bh, int L)                     // workgroups (= records) per 
     const int n = want > most ? most : want;
     return n < 1 ? 1 : n > MAX_SPLIT ? MAX_SPLIT : n;
 }
+
+// The flat cut leaves more records of 100 KB for the merge than it saves keys for the pass unless a workgroup's share is long: us,
+// lengths uniform in [L/8, L], even / flat cut: with 2048 keys per workgroup of the even cut 512 heads x 2048 138 / 159, 64 x 16384 123 / 133,
+// 32 x 32768 134 / 145, 128 x 8192 118 / 120; with 4096 256 x 8192 190 / 187, 640 x 4096 279 / 266; with 8192 512 x 8192 337 / 322, 256 x
+// 16384 315 / 273.
+bool flat_pays(int L, int nsplit) { return L / nsplit >= FLAT_KEYS; }
 
 // two bf16 packed in a dword -> two f16 packed (exact for values in the f16 range)
 __device__ inline unsigned bf16x2_to_f16x2(unsigned u)
@@ -484,11 +490,8 @@ hipError_t mfma_decode128(const Problem &p)
     a.Vg = (const bf16_t *)p.V;
     a.sk = p.sk;
     a.sv = p.sv;
-    // The flat cut leaves more records of 100 KB for the merge than it saves keys for the pass unless a workgroup's share is long: us,
-    // lengths uniform in [L/8, L], even and flat cut: 32 heads x 8192 76 / 90, 256 x 2048 78 / 97, 72 x 5147 80 / 89, but 256 x 16384
-    // 309 / 284.  Without room for records (0) choose_split takes the even one.
     const int nsplit = make_split(bh, p.n);
-    const size_t room = p.n / nsplit >= FLAT_KEYS ? p.ws_bytes / (REC_F * sizeof(float)) : 0;
+    const size_t room = flat_pays(p.n, nsplit) ? p.ws_bytes / (REC_F * sizeof(float)) : 0;      // none: choose_split takes the even cut
     a.split = choose_split(p, nsplit, room, SLOTS, STEP, KEYS_MIN, MAX_SPLIT);
     a.cscale = p.scale * LOG2E;
     a.parts = static_cast<float *>(p.ws);
