@@ -477,7 +477,7 @@ size_t mfma_decode128_workspace_bytes(int B, int H, int L_max)
 
 size_t mfma_decode128_flat_bytes(int B, int H, int L_max)
 {
-    if (L_max < MIN_L || B < 2) return 0;
+    if (L_max < MIN_L || B < 2 || !flat_pays(L_max, make_split(B * H, L_max))) return 0;
     return round_up(flat_records(B, H, SLOTS) * REC_F * sizeof(float), 256);
 }
 

@@ -207,3 +207,18 @@ def test_longest_calls_are_accepted():
         assert _fwd(n=2097185, d=d, path=2) == 6
         assert _fwd(n=64 * 65535, d=d, path=2) == 6
         assert _fwd(n=64 * 65535 + 1, d=d, path=2) == 7
+
+
+def test_decode_workspace_holds_the_records_a_call_can_leave():
+    """bf16, d = 128: records of 25920 floats, one per workgroup of the even cut; those of equal shares of all keys are asked for only
+    where such a cut is taken (4096 keys or more per workgroup of the even cut, more than one sequence)."""
+    import torch
+
+    def records(B, H, L):
+        return llla.decode_workspace_bytes(B, H, L, 128, torch.bfloat16) / (25920 * 4)
+
+    for L in (256, 1000, 4095):
+        assert 512 <= records(32, 16, L) < 513                             # one workgroup per head
+    assert 512 <= records(4, 16, 4096) < 513                               # 64 heads, eight workgroups of 512 keys each
+    assert 768 <= records(16, 16, 16384) < 769                             # 512 workgroups and a record more per sequence
+    assert 512 <= records(1, 16, 100000) < 513                             # one sequence: nothing to balance
