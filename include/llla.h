@@ -206,7 +206,8 @@ llla_status llla_decode(const void *q, const void *Kc, const void *Vc, void *o,
  * d = 64 or 128, L_max >= 256 and B * H <= 65535 (queries, keys and values must lie in the f16 range, |x| <= 65504);
  * LLLA_PATH_MFMA on any other call returns LLLA_ERR_UNSUPPORTED; LLLA_PATH_AUTO takes the fp32 matrix-core kernels there
  * (every d, both dtypes, fp32 arithmetic and no value range), which use the workspace to cut long caches into several parts
- * but do without it when it is NULL or too small, and the key-space kernel for sequences of at most min(d, 64) keys. */
+ * but do without it when it is NULL or too small, and the key-space kernel: for caches of at most min(d, 64) rows, and with
+ * lengths for sequences of at most 64 keys. */
 llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void *o,
                              llla_strides sk, llla_strides sv, const int32_t *seqlens,
                              int B, int H, int L_max, int d, llla_dtype in, llla_dtype out,
@@ -217,12 +218,13 @@ llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void
  * llla_decode_static -- llla_decode for callers that cannot allocate device memory and therefore have no workspace
  * to pass: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
  * kernels and bit-identical results; the partial-moment records that llla_decode keeps in `workspace` live in a
- * device array of LLLA_STATIC_SCRATCH_BYTES inside the library instead (one copy per GPU, held from the moment the
+ * device array of twice LLLA_STATIC_SCRATCH_BYTES inside the library instead (one copy per GPU, held from the moment the
  * library is loaded on that GPU until the process ends).  The call allocates and frees nothing and does not
- * synchronise.  A call whose llla_decode_workspace_bytes() exceeds LLLA_STATIC_SCRATCH_BYTES returns
- * LLLA_ERR_WORKSPACE (the decode configuration of 32 x 16 heads x 32768 keys at d = 64 needs 56 MB and fits);
- * LLLA_ERR_LAUNCH if the runtime cannot report the array's address.  Every call on a GPU uses that GPU's one array:
- * calls on the same stream are ordered and safe, calls that overlap on one GPU (different streams, different
+ * synchronise.  A call on the 16-bit kernels (bf16 caches, d = 64 or 128, L_max >= 256) whose records, one per workgroup with
+ * the keys of every head divided evenly, exceed LLLA_STATIC_SCRATCH_BYTES returns LLLA_ERR_WORKSPACE (the decode
+ * configuration of 32 x 16 heads x 32768 keys at d = 64 needs 56 MB and fits); LLLA_ERR_LAUNCH if the runtime cannot report
+ * the array's address.  Every call on a GPU uses that GPU's one array, whatever its type and head dimension: calls on the same
+ * stream are ordered and safe, calls that overlap on one GPU (different streams, different
  * threads) race on it -- unlike every other entry point, this one is not re-entrant per device.
  */
 #define LLLA_STATIC_SCRATCH_BYTES ((size_t)64 << 20)

@@ -12,7 +12,9 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = LLLA_STATIC_SCRATCH_BYTES;
+// What a call may need, and the array: twice that, so that a call whose even cut fits finds room for the flat one too, which llla_decode
+// would take for it (at d = 128 up to 512 + 647 records of 104 KB), and both return the same bits.
+constexpr size_t kMostNeeded = LLLA_STATIC_SCRATCH_BYTES, kScratchBytes = 2 * kMostNeeded;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -47,11 +49,11 @@ extern "C" llla_status llla_decode_static(const void *q, const void *Kc, const v
     // what llla_decode must have for this call (0 for bad shapes, which the call below refuses with their own status); the
     // fp32 kernels and the cut for sequences of different lengths take what is there
     const size_t need = shape_ok(B, H, L_max, d, in) ? llla::mfma_decode_workspace_bytes(B, H, L_max, d, in) : 0;
-    if (need > kScratchBytes) return LLLA_ERR_WORKSPACE;
+    if (need > kMostNeeded) return LLLA_ERR_WORKSPACE;
     void *ptr = nullptr;
     if (shape_ok(B, H, L_max, d, in) && llla_decode_workspace_bytes(B, H, L_max, d, in) > 0) {
         ptr = scratch_on_current_device();
-        if (ptr == nullptr) return LLLA_ERR_LAUNCH;
+        if (ptr == nullptr && need > 0) return LLLA_ERR_LAUNCH;
     }
     // nothing in the records has to start at zero: every record a call reads is written by that call first
     return llla_decode(q, Kc, Vc, o, sk, sv, seqlens, B, H, L_max, d, in, out, lambda, scale, ptr, ptr ? kScratchBytes : 0,

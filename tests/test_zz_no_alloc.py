@@ -76,3 +76,15 @@ def test_a_call_beyond_the_array_is_refused():
     st = llla.lib().llla_decode_static(fake, fake, fake, fake, s, s, 0, B, H, L, d, 1, 0, ctypes.c_float(1e-2),
                                        ctypes.c_float(0.125), 0)
     assert st == 6
+
+
+def test_equal_shares_at_d128_are_the_same_bits():
+    """640 heads x up to 4096 keys with lengths of their own: llla_decode cuts the keys into equal shares, whose records (119 MB) exceed
+    what a call may need of the array (64 MiB; its even cut takes 63), and so does the static call."""
+    B, H, L, d = 40, 16, 4096, 128
+    g = torch.Generator(device=DEV).manual_seed(77)
+    q, Kc, Vc = (torch.randn(s, generator=g, device=DEV, dtype=torch.bfloat16) for s in ((B, H, d), (B, H, L, d), (B, H, L, d)))
+    lens = torch.randint(1, L + 1, (B,), generator=g, device=DEV, dtype=torch.int32)
+    assert llla.decode_workspace_bytes(B, H, L, d, torch.bfloat16) > (64 << 20)
+    got = llla.llla_decode_static(q, Kc, Vc, 1e-2, d ** -0.5, torch.empty((B, H, d), device=DEV), seqlens=lens)
+    assert torch.equal(got, llla.llla_decode(q, Kc, Vc, 1e-2, d ** -0.5, seqlens=lens))
