@@ -171,8 +171,9 @@ llla_status llla_forward_cg(const void *Q, const void *K, const void *V, void *O
  *                 sweeps around it run in fp32 on the vector ALU.  bf16 inputs with d = 16 or 32 run it at d = 64 on
  *                 zero-padded copies, as the forward does (the gradient of a padded feature is zero and is dropped);
  *                 LLLA_PATH_AUTO takes that route for d = 32 from 64 rows on, and for d = 16 from 512 rows on.
- *                 LLLA_PATH_AUTO runs fp32 inputs with d = 64 on the fp32 matrix cores (fp32 arithmetic throughout), or on
- *                 the vector path when the workspace is too small for that but large enough for the vector path.
+ *                 LLLA_PATH_AUTO runs fp32 inputs with d = 64 on the fp32 matrix cores (fp32 arithmetic; the second moment
+ *                 from operands split into three bf16, 24 significant bits), or on the vector path when the workspace is too small
+ *                 for that but large enough for the vector path.
  * Causal only.  Workspace: llla_backward_workspace_bytes (Theta(B H n d); enough for every path).
  */
 size_t llla_backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in);

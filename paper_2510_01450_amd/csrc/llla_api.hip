@@ -13,10 +13,10 @@ constexpr int kMaxGridY = 65535;
 // Measured at 64 heads, bf16, vector vs padded.  Forward, d = 32: 0.028 vs 0.036 ms at n = 16, 0.075 vs 0.037 at 32, 0.19 vs
 // 0.057 at 128, 22.5 vs 1.56 at 4096; d = 16: 0.028 vs 0.036 at n = 16, 0.045 vs 0.038 at 32, 0.064 vs 0.053 at 128, 6.2 vs 1.2 at
 // 4096 -> from 32 rows on.  Backward, d = 32: 0.055 vs 0.057 at n = 32, 0.080 vs 0.070 at 64, 42.5 vs 3.7 at 4096 -> from 64 rows
-// on; d = 16: 0.071 vs 0.106 at n = 128, 0.32 vs 0.21 at 512, 15.1 vs 3.2 at 4096 -> from 512 rows on.  fp32 inputs (fp32 MFMA, a
-// sixteenth of the 16-bit rate; forward only), d = 32: 0.34 vs 0.36 ms at n = 256, 0.73 vs 0.53 at 512, 2.0 vs 1.1 at 1024, 24.3
-// vs 11.1 at 4096, but 0.196 vs 0.217 at 2 heads x 1024 -> from 1024 rows on; d = 16: 0.062 vs 0.30 at n = 128, 0.53 vs 0.77 at 1024,
-// 6.5 vs 6.9 at 4096 -> only when forced.
+// on; d = 16: 0.071 vs 0.106 at n = 128, 0.32 vs 0.21 at 512, 15.1 vs 3.2 at 4096 -> from 512 rows on.  fp32 inputs (forward
+// only), 64 heads, d = 32: 0.16 vs 0.27 ms at n = 256, 0.50 vs 0.39 at 512, 1.6 vs 0.83 at 1024, 23.9 vs 8.9 at 4096; 2 heads 0.079 vs
+// 0.080 at 512, 0.153 vs 0.136 at 1024 -> from 1024 rows on; d = 16: 0.028 vs 0.23 at n = 128, 0.47 vs 0.64 at 1024, 1.6 vs 1.8 at 2048,
+// 6.4 vs 6.3 at 4096, and with 2 heads 0.083 vs 0.074 at 512, 0.62 vs 0.42 at 4096 -> only when forced.
 bool auto_takes_padded(int n, int d, llla_dtype in) { return in == LLLA_BF16 ? n >= 32 : (d == 32 && n >= 1024); }
 bool auto_takes_padded_backward(int n, int d, llla_dtype in) { return in == LLLA_BF16 && n >= (d == 32 ? 64 : 512); }
 
@@ -278,8 +278,8 @@ llla_status llla_decode_path(const void *q, const void *Kc, const void *Vc, void
     }
     llla::stage_begin(p.stream);
     // fp32 caches, d = 16 / 32 and short bf16 caches: the fp32 matrix-core kernels, faster than the vector kernels at every size
-    // measured (1 to 1024 heads x 66 to 8192 keys).  us, vector vs matrix cores: fp32 d = 64, 64 heads of 1024 .. 8192 keys 1243 vs
-    // 87, 1 head x 66 107 vs 17; d = 128, 256 heads x 8192 4234 vs 1210; d = 32 bf16, 256 heads x 4096 252 vs 36; d = 16, 1024 heads x
+    // measured (1 to 1024 heads x 66 to 8192 keys).  us, vector vs matrix cores: fp32 d = 64, 64 heads of 1024 .. 8192 keys 1250 vs
+    // 81, 1 head x 66 107 vs 17; d = 128, 256 heads x 8192 4234 vs 1210; d = 32 bf16, 256 heads x 4096 252 vs 34; d = 16, 1024 heads x
     // 8192 980 vs 193.
     const bool use_f32 = !use_mfma && path == LLLA_PATH_AUTO && llla::mfma_decode_f32_takes(p);
     if (!use_mfma && !use_f32) llla::stage_mark(p.stream, "valu_decode");

@@ -76,7 +76,7 @@ hipError_t mfma_backward_solve(const BackwardProblem &p, const BackwardLayout &L
 hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int first_row);   // r rows, argmax; rows >= first_row
 hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int first_row);  // dQ, dlambda, row scalars; rows >= first_row
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
-// the same for fp32 inputs (d = 64): fp32 matrix cores throughout (llla_mfma_bwd_f32.hip); its moments kernel is the
+// the same for fp32 inputs (d = 64): sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
 // forward's, with the row maxima M given and the rows r replaced by u
 bool mfma_backward_f32_supported(int n, int d, llla_dtype in);
 size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d);
@@ -90,7 +90,7 @@ hipError_t backward(const BackwardProblem &p, llla_path path);
 bool mfma_forward_supported(int d, llla_dtype in, bool causal);
 size_t mfma_forward_workspace_bytes(int B, int H, int n, int d, llla_dtype in);
 hipError_t mfma_forward(const Problem &p);
-// the same for fp32 inputs (d = 64, causal): fp32 MFMA throughout (llla_mfma_fwd_f32.hip)
+// the same for fp32 inputs (d = 64): llla_mfma_fwd_f32.hip
 bool mfma_forward_f32_supported(int d, bool causal);
 size_t mfma_forward_f32_workspace_bytes(int B, int H, int n);
 hipError_t mfma_forward_f32(const Problem &p);

@@ -1,5 +1,7 @@
-// Matrix-core backward pass for fp32 inputs, d = 64: every contraction on v_mfma_f32_16x16x4_f32, fp32 operands and fp32
-// accumulation, so the accuracy is that of the vector kernels of llla_bwd.hip (whose notation is used here).
+// Matrix-core backward pass for fp32 inputs, d = 64.  The sweeps form every contraction on v_mfma_f32_16x16x4_f32, fp32 operands and fp32
+// accumulation; the second moment comes from operands split into three bf16 (24 significant bits) on 16-bit MFMA.  Errors against fp64
+// are those of the vector kernels of llla_bwd.hip (whose notation is used here) or smaller, for inputs whose |k|^2 / ridge is below
+// some 10^5: 500 rows of normal inputs, ridge 10^-2, dQ 8.1e-5 there and 7.0e-5 here; keys of ten times that size 0.15 and 0.22.
 //
 //   r sweep   r_i = sum_j w_ij gamma_ij [1; k_j], the row maximum m_i and the first key that attains it;
 //   moments   the forward's fp32 moments kernel with m_i given and a second right-hand side in its solve: y_i and u_i;

@@ -35,7 +35,7 @@ constexpr int KEYS_FEW = 256, KEYS_MIN = 512;  // fewest keys worth a workgroup 
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
 constexpr int MAX_SPLIT = 16;                  // most workgroups per head
 static_assert(MAX_SPLIT < MAX_RECORDS, "the flat cut can leave one piece more");
-constexpr int MIN_L = 256;                     // shorter caches go to the vector path
+constexpr int MIN_L = 256;                     // shorter caches go to the fp32 kernels (llla_mfma_decode_f32.hip)
 constexpr int PRECISE_L = 4 * D;               // sequences up to this length take the two-term weights
 
 typedef short short4v __attribute__((ext_vector_type(4)));
@@ -52,11 +52,11 @@ int record_room(int bh, int L)
     return nparts > 16 ? nparts + (nparts + group - 1) / group : nparts;
 }
 
-// Workgroups per head.  A record costs the merge half a microsecond (one workgroup reads a head's records, 27 KB each), 256 further
-// keys cost a workgroup 1.2, and two workgroups on a compute unit slow each other down: as many as fill the GPU, with 256 keys or
+// Workgroups per head.  A record costs the merge time (one workgroup reads a head's records, 27 KB each), 256 further keys cost a
+// workgroup 1.2 us, and two workgroups on a compute unit slow each other down: as many as fill the GPU, with 256 keys or
 // more, but 512 or more where there would be more than eight per head or more than one per compute unit; below 1024 keys one,
-// which solves the head itself.  us with 256 / 512 keys: 16 heads x 4096 31.2 / 28.4 (1024 keys: 32.9), 32 x 4096 37.2 / 30.1,
-// 64 x 2048 33.1 / 29.8, 128 x 1024 32.8 / 29.7; 4 x 2048 23.3 / 25.0, 16 x 1024 23.1 / 24.8; 32 x 600 24.6, one workgroup 20.8.
+// which solves the head itself.  us with 256 / 512 keys: 16 heads x 4096 26.8 / 26.3 (1024 keys: 29.3), 32 x 4096 34.0 / 29.0,
+// 64 x 2048 31.2 / 27.5, 128 x 1024 30.2 / 27.4; 4 x 2048 21.5 / 21.7, 16 x 1024 20.5 / 22.4; 32 x 600 21.6, one workgroup 21.7.
 int make_split(int bh, int L)
 {
     const int want = (SLOTS + bh - 1) / bh, room = std::min(MAX_SPLIT, record_room(bh, L));

@@ -33,7 +33,7 @@ constexpr int NSIG = DecShape<D>::NSIG, HDR = DecShape<D>::HDR, REC_F = DecShape
 constexpr int KEYS_MIN = 8 * STEP;             // fewest keys worth a workgroup
 constexpr int FLAT_KEYS = 4096;               // keys per workgroup of the even cut from which the flat one is taken
 constexpr int SLOTS = 512;                     // two workgroups per compute unit are resident
-constexpr int MIN_L = 256;                     // shorter caches go to the vector path
+constexpr int MIN_L = 256;                     // shorter caches go to the fp32 kernels (llla_mfma_decode_f32.hip)
 constexpr int MAX_SPLIT = 32;
 static_assert(MAX_SPLIT < MAX_RECORDS, "the flat cut can leave one piece more");
 constexpr int PRECISE_L = 4 * D;               // sequences up to this length take the two-term weights

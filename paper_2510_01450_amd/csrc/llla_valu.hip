@@ -50,8 +50,9 @@ __global__ __launch_bounds__(NT) void valu_kernel(const TI *__restrict__ Qg, con
     constexpr int NSYS = DECODE ? 1 : QB;
     constexpr int TILE_F = 2 * KROWS * LDK + 2 * QB * KT;   // ks, vs, logits, weights
     constexpr int SYS_F = NSYS * P * LS;
-    constexpr int UNION_F = (GIVEN || TILE_F > SYS_F) ? TILE_F : SYS_F;   // (a given solution needs no system: 18
-                                                            // instead of 70 KB at d = 64, eight workgroups per compute unit)
+    constexpr int UNION_F = (GIVEN || TILE_F > SYS_F) ? TILE_F : SYS_F;   // (a given solution needs no system: 21
+                                                            // instead of 70 KB at d = 64; four workgroups per compute
+                                                            // unit, by registers, instead of two)
 
     __shared__ __align__(16) float smem[UNION_F + QB * D + QB * (P + 3) + 4 * QB];
     float *ks = smem;                                     // [KROWS][LDK]

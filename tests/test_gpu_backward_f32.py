@@ -36,8 +36,8 @@ def test_reference_exponent(factor):
 
 def test_few_keys_small_ridge_features_over_four_decades():
     """Rows with few keys far apart: the system is regular only through the ridge, and the intercept has to be eliminated
-    before the features (eliminated last it cancels to zero).  Condition number about 1e2 / 1e-4 = 1e6, times the 6e-8 of
-    fp32, times the ten of a head's worst rows."""
+    before the features (eliminated last it cancels to zero).  Bounds: four times the errors of the vector kernels, which eliminate in
+    that order too (2.4e-4, 2.0e-5, 2.0e-4, 3.0e-4; here 1.4e-4, 1.9e-5, 1.5e-4, 1.7e-4)."""
     n, d = 64, 64
     g = torch.Generator(device="cpu").manual_seed(64)
     Q, K, V, G = (torch.randn((1, 2, n, d), generator=g) for _ in range(4))
@@ -45,10 +45,10 @@ def test_few_keys_small_ridge_features_over_four_decades():
     K, Q = K * size, Q / size.clamp(min=0.1)
     got = llla.llla_backward(Q.to(DEV), K.to(DEV), V.to(DEV), G.to(DEV), 1e-4, 1 / 8.0, return_dlambda=True)
     ref = ob.backward(Q, K, V, G, 1e-4, 1 / 8.0)
-    for a, b in zip(got, ref):
+    for a, b, bound in zip(got, ref, (1e-3, 8e-5, 8e-4, 1.2e-3)):
         a = a.cpu().double().numpy()
         assert np.isfinite(a).all()
-        assert np.linalg.norm(a - b) <= 0.6 * np.linalg.norm(b)
+        assert np.linalg.norm(a - b) <= bound * np.linalg.norm(b)
 
 
 def test_workspace_of_the_vector_kernels_is_enough():
