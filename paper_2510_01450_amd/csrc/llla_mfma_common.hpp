@@ -2,6 +2,8 @@
 // MFMA wrappers, DPP broadcasts, LDS DMA, and the on-chip exact solve of the per-query system.
 #pragma once
 
+#include <type_traits>
+
 #include "llla_common.hpp"
 
 namespace llla {
@@ -64,17 +66,6 @@ __device__ inline float rows_2_3_from_row_1(float x)
 {
     const int v = __builtin_bit_cast(int, x);
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
-}
-
-// Maximum of x[p * pitch], p in [p0, p1), over a wave: lane l takes p0 + l, p0 + l + 64, .., so the loads of a
-// wave are in flight together (a loop over p in every lane would wait for each load in turn).
-__device__ inline float wave_max_strided(const float *x, int p0, int p1, size_t pitch, int lane)
-{
-    float mv = -INFINITY;
-    for (int p = p0 + lane; p < p1; p += 64) mv = fmaxf(mv, x[(size_t)p * pitch]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mv = fmaxf(mv, __shfl_xor(mv, off));
-    return mv;
 }
 
 __device__ inline void wave_sync()
@@ -156,178 +147,178 @@ __device__ inline f32x4 tile_atb(f32x4 c, f32x4 a, f32x4 b)
 
 constexpr int SC_PITCH = 20;         // floats per row of a 16x16 scratch tile
 
-// Row-broadcast multiply-adds as VOP2 DPP instructions, a_i += (src of lane C_i of the 16-lane row) * mul:
-// the compiler does not fuse a DPP move into an FMA by itself, and these pairs are most of the vector-ALU
-// work of the diagonal-tile factorisation.  A DPP read needs two wait states after a vector-ALU write of the
-// register it reads, and the compiler's hazard handling does not look inside inline assembly; every
-// statement below therefore starts with its own s_nop 1, and all registers it reads through DPP are operands
-// of the statement, so whatever wrote them lies before that s_nop.
-//   fmac_bcastN<C0..>(a0.., src, mul): a_i += bcast_{C_i}(src) * mul        (rank-1 update of a row)
-//   fmac_selfN<C>(a0.., mul):          a_i += bcast_C(a_i) * mul            (triangular-inverse recursion)
-template <int C0>
-__device__ inline void fmac_bcast1(float &a0, float src, float mul)
+// ---- diagonal tiles -----------------------------------------------------------------------------------------------------------
+// Their factorisation is most of the vector work of every solve in the library and is bound by instruction issue (two waves share a
+// SIMD and the matrix cores add nothing to it), so what counts is the number of instructions.  Row-broadcast multiply-adds are VOP2 DPP
+// instructions; the compiler does not fuse a DPP move into an FMA by itself.  A DPP read needs two wait states after a vector-ALU
+// write of the register it reads, and the compiler's hazard handling does not look inside inline assembly: every statement
+// starts with its own s_nop 1, all registers it reads through DPP are operands of the statement (whatever wrote them lies before that
+// s_nop), and what a statement both writes and reads through DPP lies two instructions apart or has an s_nop between.
+#define LLLA_FROM(M, K) LLLA_FROM_##K(M)
+#define LLLA_FROM_15(M) M(15)
+#define LLLA_FROM_14(M) M(14) LLLA_FROM_15(M)
+#define LLLA_FROM_13(M) M(13) LLLA_FROM_14(M)
+#define LLLA_FROM_12(M) M(12) LLLA_FROM_13(M)
+#define LLLA_FROM_11(M) M(11) LLLA_FROM_12(M)
+#define LLLA_FROM_10(M) M(10) LLLA_FROM_11(M)
+#define LLLA_FROM_9(M) M(9) LLLA_FROM_10(M)
+#define LLLA_FROM_8(M) M(8) LLLA_FROM_9(M)
+#define LLLA_FROM_7(M) M(7) LLLA_FROM_8(M)
+#define LLLA_FROM_6(M) M(6) LLLA_FROM_7(M)
+#define LLLA_FROM_5(M) M(5) LLLA_FROM_6(M)
+#define LLLA_FROM_4(M) M(4) LLLA_FROM_5(M)
+#define LLLA_FROM_3(M) M(3) LLLA_FROM_4(M)
+#define LLLA_FROM_2(M) M(2) LLLA_FROM_3(M)
+#define LLLA_FROM_1(M) M(1) LLLA_FROM_2(M)
+#define LLLA_DPP(C) " row_newbcast:" #C " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+
+// max(x of lane K of the caller's 16-lane row, lo); a NaN gives lo
+template <int K>
+__device__ inline float bcast_max(float x, float lo)
 {
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0) : "v"(src), "v"(mul), "n"(C0));
+    float d;
+    asm volatile("s_nop 1\n\tv_max_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(d) : "v"(x), "v"(lo), "n"(K));
+    return d;
 }
-template <int C0, int C1>
-__device__ inline void fmac_bcast2(float &a0, float &a1, float src, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %2, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %1, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0), "+v"(a1) : "v"(src), "v"(mul), "n"(C0), "n"(C1));
-}
-template <int C0, int C1, int C2, int C3>
-__device__ inline void fmac_bcast4(float &a0, float &a1, float &a2, float &a3, float src, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3) : "v"(src), "v"(mul), "n"(C0), "n"(C1), "n"(C2), "n"(C3));
-}
-template <int C0, int C1, int C2, int C3, int C4, int C5, int C6, int C7>
-__device__ inline void fmac_bcast8(float &a0, float &a1, float &a2, float &a3, float &a4, float &a5, float &a6, float &a7, float src, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %8, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %1, %8, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %2, %8, %9 row_newbcast:%12 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %3, %8, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %4, %8, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %5, %8, %9 row_newbcast:%15 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %6, %8, %9 row_newbcast:%16 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %7, %8, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(a4), "+v"(a5), "+v"(a6), "+v"(a7) : "v"(src), "v"(mul), "n"(C0), "n"(C1), "n"(C2), "n"(C3), "n"(C4), "n"(C5), "n"(C6), "n"(C7));
-}
-template <int C>
-__device__ inline void fmac_self1(float &a0, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0) : "v"(mul), "n"(C));
-}
-template <int C>
-__device__ inline void fmac_self2(float &a0, float &a1, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %0, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %1, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0), "+v"(a1) : "v"(mul), "n"(C));
-}
-template <int C>
-__device__ inline void fmac_self4(float &a0, float &a1, float &a2, float &a3, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %0, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3) : "v"(mul), "n"(C));
-}
-template <int C>
-__device__ inline void fmac_self8(float &a0, float &a1, float &a2, float &a3, float &a4, float &a5, float &a6, float &a7, float mul)
-{
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f32_dpp %0, %0, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %1, %1, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %2, %2, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %3, %3, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %4, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %5, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %6, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-                 "v_fmac_f32_dpp %7, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(a4), "+v"(a5), "+v"(a6), "+v"(a7) : "v"(mul), "n"(C));
-}
-template <int C>
+template <int K>
 __device__ inline float bcast_settled(float src)     // row broadcast of a value that inline assembly may have written
 {
     float d;
-    asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-                 : "=v"(d) : "v"(src), "n"(C));
+    asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(d) : "v"(src), "n"(K));
     return d;
 }
-
-// a[K+1..15] += bcast_c(src) * mul for c = K+1..15, in statements of 8, 4, 2 and 1 instructions
+// a[c] -= (v of lane c of the row) * v for c = K+1 .. 15
 template <int K>
-__device__ inline void rank1_row(float (&a)[16], float src, float mul)
+__device__ inline void rank1_row(float (&a)[16], float v)
 {
-    constexpr int N = 15 - K;
-    constexpr int c8 = K + 1, c4 = c8 + (N & 8), c2 = c4 + (N & 4), c1 = c2 + (N & 2);
-    if constexpr ((N & 8) != 0)
-        fmac_bcast8<c8, c8 + 1, c8 + 2, c8 + 3, c8 + 4, c8 + 5, c8 + 6, c8 + 7>(a[c8], a[c8 + 1], a[c8 + 2], a[c8 + 3], a[c8 + 4], a[c8 + 5],
-                                                                                a[c8 + 6], a[c8 + 7], src, mul);
-    if constexpr ((N & 4) != 0) fmac_bcast4<c4, c4 + 1, c4 + 2, c4 + 3>(a[c4], a[c4 + 1], a[c4 + 2], a[c4 + 3], src, mul);
-    if constexpr ((N & 2) != 0) fmac_bcast2<c2, c2 + 1>(a[c2], a[c2 + 1], src, mul);
-    if constexpr ((N & 1) != 0) fmac_bcast1<c1>(a[c1], src, mul);
-}
-// li[0..P] += bcast_P(li[c]) * mul
-template <int P>
-__device__ inline void trinv_row(float (&li)[16], float mul)
-{
-    constexpr int N = P + 1;
-    constexpr int c8 = 0, c4 = c8 + (N & 8), c2 = c4 + (N & 4), c1 = c2 + (N & 2);
-    if constexpr ((N & 8) != 0) fmac_self8<P>(li[c8], li[c8 + 1], li[c8 + 2], li[c8 + 3], li[c8 + 4], li[c8 + 5], li[c8 + 6], li[c8 + 7], mul);
-    if constexpr ((N & 4) != 0) fmac_self4<P>(li[c4], li[c4 + 1], li[c4 + 2], li[c4 + 3], mul);
-    if constexpr ((N & 2) != 0) fmac_self2<P>(li[c2], li[c2 + 1], mul);
-    if constexpr ((N & 1) != 0) fmac_self1<P>(li[c1], mul);
+#define F(C) "v_fmac_f32_dpp %[a" #C "], %[v], -%[v]" LLLA_DPP(C)
+#define O(C) , [a##C] "+v"(a[C])
+#define LLLA_RANK1(K, C) \
+    if constexpr (K == C - 1) asm volatile("s_nop 1\n\t" LLLA_FROM(F, C) : [v] "+v"(v) LLLA_FROM(O, C));
+    LLLA_RANK1(K, 1) LLLA_RANK1(K, 2) LLLA_RANK1(K, 3) LLLA_RANK1(K, 4) LLLA_RANK1(K, 5) LLLA_RANK1(K, 6) LLLA_RANK1(K, 7) LLLA_RANK1(K, 8)
+    LLLA_RANK1(K, 9) LLLA_RANK1(K, 10) LLLA_RANK1(K, 11) LLLA_RANK1(K, 12) LLLA_RANK1(K, 13) LLLA_RANK1(K, 14) LLLA_RANK1(K, 15)
+#undef LLLA_RANK1
+#undef O
+#undef F
 }
 
-#define LLLA_SWITCH16(K, STMT)                                                                          \
-    switch (K) {                                                                                        \
-        case 0: { constexpr int KK = 0; STMT; } break;   case 1: { constexpr int KK = 1; STMT; } break;    \
-        case 2: { constexpr int KK = 2; STMT; } break;   case 3: { constexpr int KK = 3; STMT; } break;    \
-        case 4: { constexpr int KK = 4; STMT; } break;   case 5: { constexpr int KK = 5; STMT; } break;    \
-        case 6: { constexpr int KK = 6; STMT; } break;   case 7: { constexpr int KK = 7; STMT; } break;    \
-        case 8: { constexpr int KK = 8; STMT; } break;   case 9: { constexpr int KK = 9; STMT; } break;    \
-        case 10: { constexpr int KK = 10; STMT; } break; case 11: { constexpr int KK = 11; STMT; } break;  \
-        case 12: { constexpr int KK = 12; STMT; } break; case 13: { constexpr int KK = 13; STMT; } break;  \
-        case 14: { constexpr int KK = 14; STMT; } break; default: { constexpr int KK = 15; STMT; } break;  \
-    }
+// 1 / sqrt(x): the hardware's estimate and one Newton step
+__device__ inline float rsqrt_newton(float x)
+{
+    const float r = __builtin_amdgcn_rsqf(x);
+    return r * (1.5f - 0.5f * x * r * r);
+}
 
-// Upper Cholesky factor and its inverse for the diagonal tiles of the wave's four queries at once:
-// lane 16q + r owns row r of query q's symmetric 16x16 tile (a[c] = T[r][c]).  On return
-// li[c] = -(L^{-1})[r][c] with T = L L^T (zero above the diagonal); the sign is the one factorise_one wants.
-// pivot_floor: every pivot of the Cholesky factorisation of (a positive semi-definite matrix + lambda I) is
-// at least lambda in exact arithmetic; a computed pivot below the floor (half of lambda) is a rounding
-// artefact of an ill-conditioned early row and is raised to it, which keeps the factorisation finite.
-// LOW: *low becomes the smallest pivot before that, if smaller (NaN pivots are passed over).
+// Cholesky factorisation S = L D L^T (L unit lower triangular) of the symmetric tiles of the wave's systems: lane 16 q + r owns row r of
+// system q's tile, a[c] = S[r][c].  On return (a destroyed)
+//   nl[k] = -L[r][k] for r > k, else 0  (k = 0..14);   ndinv = -D[r]^(-1/2).
+// What is subtracted are columns v = D^(1/2) L, the same rounded values on both sides of the product and D^(-1/2) the one that ndinv
+// returns: the rounding errors of L and D then cancel in the products of the tiles.  With L[r][k] on one side and a[k] on the other (no
+// roots on the way, three instructions less per step) the errors of fp32 rows were 0.5-1 % larger, and rows of sharp weights missed their bound.
+// Per tile, inverse included, 520 instructions (690 with a statement and its wait states per 8, 4, 2 and 1 columns and the inverse started
+// from the identity): 96 heads x 1000 rows of the bf16 forward at d = 64 500 -> 482 us, 64 x 4096 2880 -> 2845, decode of 16 x 4096 keys
+// 26.2 -> 24.5.
+// pivot_floor: every pivot D of (a positive semi-definite matrix + lambda I) is at least lambda in exact arithmetic; a computed
+// pivot below the floor (half of lambda) is a rounding artefact of an ill-conditioned row and is raised to it, which keeps the
+// factorisation finite.  LOW: *low becomes the smallest pivot before that, if smaller (NaN pivots are passed over).
 // DROP: such a pivot is not raised but made infinite, which takes its column and its unknown out of the system.  Where the pivot is
-// noise its column is too, of the size of the matrix's rounding: divided by the root of a raised pivot a few such columns in a row overflow.
-template <bool LOW = false, bool DROP = false>
-__device__ inline void chol_inv16(float (&a)[16], float (&li)[16], int r, float pivot_floor, float *low = nullptr)
+// noise its column is too, of the size of the matrix's rounding: divided by the root of a raised pivot a few such columns in a row
+// overflow.
+template <bool LOW, bool DROP>
+__device__ inline void eliminate16(float (&a)[16], float (&nl)[16], float &ndinv, int r, float pivot_floor, float *low)
 {
-    float nl2[16];      // -L[r][k] / L[k][k]  (column-scaled factor, strictly lower part kept, negated)
-    float dinv_own = 0.f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        float dk;
-        const float ak = a[k];
-        LLLA_SWITCH16(k, dk = bcast_settled<KK>(ak));        // diagonal entry of step k, from lane k of the row
-        if constexpr (LOW) *low = fminf(*low, dk);
-        if constexpr (!DROP) dk = fmaxf(dk, pivot_floor);
-        float rinv = __builtin_amdgcn_rsqf(dk);
-        rinv = rinv * (1.5f - 0.5f * dk * rinv * rinv);      // one Newton step
-        if constexpr (DROP) rinv = dk < pivot_floor ? 0.f : rinv;
-        const float u = ak * rinv;                           // L[r][k] in rows r >= k; rows above are finished and never read again
-        const float nu = -u;
-        nl2[k] = (r > k) ? nu * rinv : 0.f;
-        dinv_own = (r == k) ? rinv : dinv_own;
-        if (k < 15) { LLLA_SWITCH16(k, rank1_row<(KK < 15 ? KK : 14)>(a, u, nu)); }      // a[c] -= L[r][k] L[c][k], c > k
-    }
-    // M = (unit lower L'')^{-1}:  M[r][c] = [r==c] - sum_{c<=p<r} L''[r][p] M[p][c]
-#pragma unroll
-    for (int c = 0; c < 16; ++c) li[c] = (r == c) ? 1.f : 0.f;
-#pragma unroll
-    for (int p = 0; p < 15; ++p) { LLLA_SWITCH16(p, trinv_row<(KK < 15 ? KK : 14)>(li, nl2[p])); }
-    const float ndinv = -dinv_own;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) li[c] *= ndinv;             // -L^{-1} = -D^{-1} L''^{-1}
+    float own = 0.f;
+    auto step = [&](auto ktag) {
+        constexpr int K = decltype(ktag)::value;
+        const float ak = a[K];
+        float d;
+        if constexpr (LOW || DROP) d = bcast_settled<K>(ak);
+        if constexpr (LOW) *low = fminf(*low, d);
+        if constexpr (LOW && !DROP) d = fmaxf(d, pivot_floor);
+        if constexpr (!LOW && !DROP) d = bcast_max<K>(ak, pivot_floor);
+        float rinv = rsqrt_newton(d);
+        if constexpr (DROP) rinv = d < pivot_floor ? 0.f : rinv;
+        own = (r == K) ? rinv : own;
+        if constexpr (K < 15) {
+            const float v = ak * rinv;                       // in rows r >= K; the others are finished and never read again
+            nl[K] = (r > K) ? -v * rinv : 0.f;
+            rank1_row<K>(a, v);                              // a[c] -= v[r] v[c], c > K
+        }
+    };
+#define STEP(K) step(std::integral_constant<int, K>{});
+    STEP(0) LLLA_FROM(STEP, 1)
+#undef STEP
+    ndinv = -own;
 }
-#undef LLLA_SWITCH16
+
+// The inverse of what eliminate16 found: li[c] = -(D^(-1/2) L^-1)[r][c], zero above the diagonal (with S = U^T U that is
+// -(U^-T)[r][c]).  M = L^-1: M[r][c] = [r == c] - sum_{c<=p<r} L[r][p] M[p][c]; column p starts as the first term that it takes.
+__device__ inline void invert16(const float (&nl)[16], float ndinv, int r, float (&li)[16])
+{
+#pragma unroll
+    for (int c = 0; c < 15; ++c) li[c] = (r == c) ? 1.f : nl[c];
+    li[15] = (r == 15) ? 1.f : 0.f;
+#define G(C, P) "v_fmac_f32_dpp %[l" #C "], %[l" #C "], %[n" #P "]" LLLA_DPP(P)
+#define R1(P) G(0, P)
+#define R2(P) R1(P) G(1, P)
+#define R3(P) R2(P) G(2, P)
+#define R4(P) R3(P) G(3, P)
+#define R5(P) R4(P) G(4, P)
+#define R6(P) R5(P) G(5, P)
+#define R7(P) R6(P) G(6, P)
+#define R8(P) R7(P) G(7, P)
+#define R9(P) R8(P) G(8, P)
+#define R10(P) R9(P) G(9, P)
+#define R11(P) R10(P) G(10, P)
+#define R12(P) R11(P) G(11, P)
+#define R13(P) R12(P) G(12, P)
+#define R14(P) R13(P) G(13, P)
+#define L(C) [l##C] "+v"(li[C])
+#define N(C) [n##C] "v"(nl[C])
+    asm volatile("s_nop 1\n\t" R1(1) "s_nop 1\n\t" R2(2) "s_nop 0\n\t" R3(3) R4(4) R5(5) R6(6) R7(7)
+                 : L(0), L(1), L(2), L(3), L(4), L(5), L(6)
+                 : N(1), N(2), N(3), N(4), N(5), N(6), N(7));
+    asm volatile("s_nop 1\n\t" R8(8) R9(9) R10(10) R11(11) R12(12) R13(13) R14(14)
+                 : L(0), L(1), L(2), L(3), L(4), L(5), L(6), L(7), L(8), L(9), L(10), L(11), L(12), L(13)
+                 : N(8), N(9), N(10), N(11), N(12), N(13), N(14));
+#undef N
+#undef L
+#undef R14
+#undef R13
+#undef R12
+#undef R11
+#undef R10
+#undef R9
+#undef R8
+#undef R7
+#undef R6
+#undef R5
+#undef R4
+#undef R3
+#undef R2
+#undef R1
+#undef G
+#pragma unroll
+    for (int c = 0; c < 16; ++c) li[c] *= ndinv;
+}
+
+// The same for ONE system, whose tile the four 16-lane rows of the wave hold four copies of: lane (g, r) forms columns 4g..4g+3 of
+// its row only, li[t] = -(D^(-1/2) L^-1)[r][4g+t].  That is 60 multiply-adds instead of 105, and what a lane then holds is the
+// fragment of N = -U^-1 in the accumulator layout (register t = N[4g+t][r]): no exchange through LDS.
+__device__ inline f32x4 invert16_quarter(const float (&nl)[16], float ndinv, int r, int g)
+{
+    float l0 = (r == 4 * g) ? 1.f : 0.f, l1 = (r == 4 * g + 1) ? 1.f : 0.f, l2 = (r == 4 * g + 2) ? 1.f : 0.f, l3 = (r == 4 * g + 3) ? 1.f : 0.f;
+#define G(C, P) "v_fmac_f32_dpp %[l" #C "], %[l" #C "], %[n" #P "]" LLLA_DPP(P)
+#define Q(P) G(0, P) G(1, P) G(2, P) G(3, P)
+#define N(C) [n##C] "v"(nl[C])
+    asm volatile("s_nop 1\n\t" Q(0) Q(1) Q(2) Q(3) Q(4) Q(5) Q(6) Q(7) Q(8) Q(9) Q(10) Q(11) Q(12) Q(13) Q(14)
+                 : [l0] "+v"(l0), [l1] "+v"(l1), [l2] "+v"(l2), [l3] "+v"(l3)
+                 : N(0), N(1), N(2), N(3), N(4), N(5), N(6), N(7), N(8), N(9), N(10), N(11), N(12), N(13), N(14));
+#undef N
+#undef Q
+#undef G
+    return f32x4{l0 * ndinv, l1 * ndinv, l2 * ndinv, l3 * ndinv};
+}
 
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef const __attribute__((address_space(1))) void *glb_void_ptr;
@@ -395,14 +386,14 @@ __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I *
 // solve_wave_q4 has its own for four systems at d = 64):
 //   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I) (MFMA accumulator layout)
 //        scw                   >= 16*SC_PITCH floats of LDS owned by this wave
-//        pivot_floor           half the ridge of the row (see chol_inv16)
+//        pivot_floor           half the ridge of the row (see eliminate16)
 //   out: acc(P,J), P < J, holds U(P,J) and acc(P,P) holds N_P = -U(P,P)^{-1}, with Sigma~ + lambda I = U^T U.
 // 16-blocked upper Cholesky whose block products are C += A^T B on fp32 MFMA; the diagonal tile is factorised with one
 // row per lane and DPP row broadcasts (the four lane groups of the wave hold four copies).  The matrix cores only add
 // products, so everything that the textbook recursion subtracts is carried negated instead: the trailing matrix (T), the
 // inverse diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on
 // the vector ALU.
-// LOW: low as in chol_inv16, over all pivots.
+// LOW: low as in eliminate16, over all pivots.
 template <int NB, bool LOW = false>
 __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor, float *low = nullptr)
 {
@@ -413,7 +404,7 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 #pragma unroll
         for (int t = 0; t < 4; ++t) scw[(4 * g + t) * SC_PITCH + nn] = acc[upper_tile<NB>(P, P)][t];
         wave_sync();
-        float a[16], li[16];
+        float a[16], nl[16], ndinv;
 #pragma unroll
         for (int c4 = 0; c4 < 4; ++c4) {
             const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
@@ -423,16 +414,9 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 #pragma unroll
         for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
         wave_sync();
-        chol_inv16<LOW>(a, li, nn, pivot_floor, low);
-        if (g == 0) {
-#pragma unroll
-            for (int c4 = 0; c4 < 4; ++c4)
-                *reinterpret_cast<f32x4 *>(scw + nn * SC_PITCH + 4 * c4) = f32x4{li[4 * c4], li[4 * c4 + 1], li[4 * c4 + 2], li[4 * c4 + 3]};
-        }
-        wave_sync();
-        // N_P in tile layout: reg t = N[4g+t][nn] = -Linv[nn][4g+t]; it replaces the consumed diagonal tile;
-        // U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
-        const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * g);
+        eliminate16<LOW, false>(a, nl, ndinv, nn, pivot_floor, low);
+        // N_P replaces the consumed diagonal tile; U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
+        const f32x4 ui = invert16_quarter(nl, ndinv, nn, g);
         acc[upper_tile<NB>(P, P)] = ui;
 #pragma unroll
         for (int J = P + 1; J < NB; ++J) acc[upper_tile<NB>(P, J)] = tile_atb(zero, ui, acc[upper_tile<NB>(P, J)]);
@@ -442,7 +426,6 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
             for (int J = I; J < NB; ++J)
                 acc[upper_tile<NB>(I, J)] = tile_atb(acc[upper_tile<NB>(I, J)], acc[upper_tile<NB>(P, I)], acc[upper_tile<NB>(P, J)]);
         __builtin_amdgcn_sched_barrier(0);
-        wave_sync();
     }
 }
 
@@ -465,7 +448,7 @@ __device__ __forceinline__ float factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
         // diagonal tile -> one row per lane, symmetrised
-        float a[16], li[16];
+        float a[16], nl[16], ndinv;
 #pragma unroll
         for (int c4 = 0; c4 < 4; ++c4) {
             const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
@@ -475,18 +458,10 @@ __device__ __forceinline__ float factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 
 #pragma unroll
         for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
         wave_sync();
-        chol_inv16<true>(a, li, nn, pivot_floor, &low);
-        if (g == 0) {
-#pragma unroll
-            for (int c4 = 0; c4 < 4; ++c4)
-                *reinterpret_cast<f32x4 *>(scw + nn * SC_PITCH + 4 * c4) = f32x4{li[4 * c4], li[4 * c4 + 1], li[4 * c4 + 2], li[4 * c4 + 3]};
-        }
-        wave_sync();
-        // N_P in tile layout: reg t = N[4g+t][nn] = -Linv[nn][4g+t]; it replaces the consumed diagonal tile;
-        // U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
-        const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * g);
+        eliminate16<true, false>(a, nl, ndinv, nn, pivot_floor, &low);
+        // N_P replaces the consumed diagonal tile; U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
+        const f32x4 ui = invert16_quarter(nl, ndinv, nn, g);
         acc[upper_tile<NB>(P, P)] = ui;
-        wave_sync();
         if (P + 1 < NB) {
             f32x4 &u = acc[upper_tile<NB>(P, P + 1)], &d = acc[upper_tile<NB>(P + 1, P + 1)];
             u = tile_atb(zero, ui, u);

@@ -144,7 +144,7 @@ __device__ __forceinline__ void substitute_back(const f32x4 (&acc)[NB * (NB + 1)
 
 //   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I), accumulator layout (destroyed)
 //        load_rhs(P, m, q, e)  element 16P + n (n = the lane's position in its row) of -mu~, -q and, WITH_U, -r1
-//        omega; scw: >= 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor as in chol_inv16
+//        omega; scw: >= 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor as in eliminate16
 //        WITH_U: r0
 //   out: rhs[P] register t = y1[16P + 4g + t] (every lane; WITH_U: lanes n == 1 hold u1 instead), y0, u0
 // with [omega mu~^T; mu~ Sigma~ + lambda I] [y0; y1] = [1; q] and, WITH_U, the same matrix times [u0; u1] = [r0; r1].

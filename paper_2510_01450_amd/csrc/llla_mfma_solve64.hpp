@@ -168,7 +168,7 @@ __device__ inline float row_transpose_sum(const float (&p)[16], int nn)
 //        tmu[P], tq[P]     lane (q, r): -mu~_q[16P + r] and -q_q[16P + r]  (both destroyed)
 //        te[P], r0         WITH_U: lane (q, r): -r1_q[16P + r]; r0 of the lane's query
 //        omega             omega of the lane's query (lane group g = query g)
-//        scw               >= 4 * 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor, DROP as in chol_inv16
+//        scw               >= 4 * 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor, DROP as in eliminate16
 //   out: y1[P] = y1_q[16P + r] in lane (q, r), y0 of the lane's query in every lane;  WITH_U: u1[P], u0 likewise
 // with [omega mu~^T; mu~ Sigma~ + lambda I] [y0; y1] = [1; q] and, WITH_U, the same matrix times [u0; u1] = [r0; r1].
 // LIVE < 4 (a call at d = 16 / 32 on zero-padded copies): feature blocks LIVE..3 of every key and query are zero, the
@@ -184,7 +184,7 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
     static_assert(LIVE >= 1 && LIVE <= 4, "four 16-wide blocks");
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 
-    // ---- factorisation (as in factorise_one): acc(P,J), P < J, becomes U(P,J); acc(P,P) becomes N_P = -U(P,P)^{-1} -----
+    // ---- factorisation (as in factorise_one): acc(P,J), P < J, becomes U(P,J); acc(P,P) becomes N_P = -U(P,P)^{-1}, by columns -----
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
 #pragma unroll
@@ -192,7 +192,7 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
 #pragma unroll
             for (int t = 0; t < 4; ++t) scw[q * 16 * SC_PITCH + (4 * g + t) * SC_PITCH + nn] = acc[q][S::tix(P, P)][t];
         wave_sync();
-        float a[16], li[16];
+        float a[16], li[16], nl[16], ndinv;
         {
             const float *my = scw + g * 16 * SC_PITCH;
 #pragma unroll
@@ -205,35 +205,40 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
             for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + my[c * SC_PITCH + nn]);    // -T, symmetrised
         }
         wave_sync();
-        chol_inv16<false, DROP>(a, li, nn, pivot_floor);
-        {
+        eliminate16<false, DROP>(a, nl, ndinv, nn, pivot_floor, nullptr);
+        invert16(nl, ndinv, nn, li);
+        if (P + 1 < NB) {
             float *my = scw + g * 16 * SC_PITCH;
 #pragma unroll
             for (int c4 = 0; c4 < 4; ++c4)
                 *reinterpret_cast<f32x4 *>(my + nn * SC_PITCH + 4 * c4) = f32x4{li[4 * c4], li[4 * c4 + 1], li[4 * c4 + 2], li[4 * c4 + 3]};
+            wave_sync();
         }
-        wave_sync();
+        // what lane (q, r) holds of its own query, li[c] = N_P[c][r], is the form that the substitutions take (see below)
 #pragma unroll
-        for (int q = 0; q < QW; ++q) {
-            const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + q * 16 * SC_PITCH + nn * SC_PITCH + 4 * g);
-            acc[q][S::tix(P, P)] = ui;
+        for (int q = 0; q < QW; ++q) acc[q][S::tix(P, P)] = f32x4{li[4 * q], li[4 * q + 1], li[4 * q + 2], li[4 * q + 3]};
+        if (P + 1 < NB) {
 #pragma unroll
-            for (int J = P + 1; J < NB; ++J) acc[q][S::tix(P, J)] = tile_atb(zero, ui, acc[q][S::tix(P, J)]);
+            for (int q = 0; q < QW; ++q) {
+                const f32x4 ui = *reinterpret_cast<const f32x4 *>(scw + q * 16 * SC_PITCH + nn * SC_PITCH + 4 * g);
 #pragma unroll
-            for (int I = P + 1; I < NB; ++I)
+                for (int J = P + 1; J < NB; ++J) acc[q][S::tix(P, J)] = tile_atb(zero, ui, acc[q][S::tix(P, J)]);
 #pragma unroll
-                for (int J = I; J < NB; ++J) acc[q][S::tix(I, J)] = tile_atb(acc[q][S::tix(I, J)], acc[q][S::tix(P, I)], acc[q][S::tix(P, J)]);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int I = P + 1; I < NB; ++I)
+#pragma unroll
+                    for (int J = I; J < NB; ++J) acc[q][S::tix(I, J)] = tile_atb(acc[q][S::tix(I, J)], acc[q][S::tix(P, I)], acc[q][S::tix(P, J)]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wave_sync();
         }
-        wave_sync();
     }
 
-    // ---- every tile from the accumulator layout to columns: lane (q, r) now holds column r of query q's tile,
+    // ---- the tiles off the diagonal from the accumulator layout to columns: lane (q, r) now holds column r of query q's tile,
     //      element c = 4 g' + t in register acc[g'][tile][t] ---------------------------------------------------------
 #pragma unroll
     for (int I = 0; I < NB; ++I)
 #pragma unroll
-        for (int J = I; J < NB; ++J) {
+        for (int J = I + 1; J < NB; ++J) {
             const int tl = S::tix(I, J);
             rows_transpose4(acc[0][tl], acc[1][tl], acc[2][tl], acc[3][tl]);
         }
