@@ -367,7 +367,8 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
                                              const float *__restrict__ lam_rows, const _Float16 *__restrict__ KT,
                                              const float *__restrict__ Mg, float *__restrict__ Yg,
                                              const float *__restrict__ Rg = nullptr, float *__restrict__ Ug = nullptr,
-                                             int causal = 1)
+                                             int causal = 1, float *__restrict__ rho = nullptr,
+                                             float *__restrict__ delta = nullptr)
 {
     using S = Shape<DD>;
     constexpr int NB = S::NB, NTILE = S::NTILE, NF = S::NF, QW = S::QW, NW = S::NW, QB = S::QB, YP = S::YP;
@@ -901,6 +902,20 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
 #pragma unroll
             for (int P = 0; P < NB; ++P) yr[16 * P + nn] = y1[P];
             if (nn == 0) yr[DD] = y0;
+            if constexpr (!WITH_U) {
+                if (rho != nullptr || delta != nullptr) {                // (a scalar branch)
+                    float qy = 0.f;
+#pragma unroll
+                    for (int P = 0; P < NB; ++P) qy = fmaf(bf16_to_f32(sm.qt[qi][16 * P + nn]), y1[P], qy);
+                    const float dl = 1.f / (y0 + row_allsum(qy));
+                    const size_t at = (size_t)bh * n + row;
+                    if (delta != nullptr && nn == 0) delta[at] = dl;
+                    if (rho != nullptr) {
+#pragma unroll
+                        for (int P = 0; P < NB; ++P) rho[at * DD + 16 * P + nn] = -dl * y1[P];
+                    }
+                }
+            }
             if constexpr (WITH_U) {
                 float *ur = Ug + ((size_t)bh * n + row) * YP;
 #pragma unroll
@@ -938,6 +953,25 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
         const int i = i0 + QW * wave + q;
+        if constexpr (!WITH_U) {
+            if (i < n && (rho != nullptr || delta != nullptr)) {         // (a scalar branch)
+                const bf16_t *qr = Qh + (int64_t)i * sq.seq + 4 * g;
+                float qy = 0.f;
+#pragma unroll
+                for (int P = 0; P < NB; ++P)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) qy = fmaf(bf16_to_f32(qr[16 * P + t]), rhs[q][P][t], qy);
+                const float dl = 1.f / (y0v[q] + rows_allsum(qy));
+                const size_t at = (size_t)bh * n + i;
+                if (delta != nullptr && g == 0 && nn == 0) delta[at] = dl;
+                if (rho != nullptr && nn == 0) {
+#pragma unroll
+                    for (int P = 0; P < NB; ++P)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) rho[at * DD + 16 * P + 4 * g + t] = -dl * rhs[q][P][t];     // (rho is aligned to 4 bytes only)
+                }
+            }
+        }
         if (i < n && nn == 0) {
             float *yr = Yg + ((size_t)bh * n + i) * YP;
 #pragma unroll
@@ -960,18 +994,20 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
 
 // One launch serves every query block: blocks whose rows lie below precise_rows take the precise
 // variant.  The choice depends on blockIdx only, so it is a scalar branch (MFMA ignores EXEC).
+// rho, delta (optional): the statistics of Eq. (lla) from the solved y of every row: with y1 = -rho/delta and y0 = (1 + q.rho)/delta,
+// 1/delta = y0 + q.y1 and rho = -delta y1.  (In a launch of their own, which read Y and Q again, 12 of 493 us at 96 heads x 1000 rows.)
 template <int DD, int LIVE = Shape<DD>::NB>
 __global__ __launch_bounds__(Shape<DD>::NT, DD == 64 ? 2 : 1) void moments_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq, llla_strides sk, int H, int n, int nkb,
     int precise_rows, float cscale, float lambda, const float *__restrict__ lam_rows, const _Float16 *__restrict__ KT,
-    const float *__restrict__ Mg, float *__restrict__ Yg, int causal)
+    const float *__restrict__ Mg, float *__restrict__ Yg, int causal, float *__restrict__ rho, float *__restrict__ delta)
 {
     __shared__ __align__(16) MomentsShared<DD> sm;
     const int i0 = ((int)gridDim.x - 1 - moments_block<DD>().blk) * Shape<DD>::QB;
     if (i0 < precise_rows)
-        moments_body<true, DD, false, LIVE>(sm, Qg, Kg, sq, sk, H, n, nkb, cscale, lambda, lam_rows, KT, Mg, Yg, nullptr, nullptr, causal);
+        moments_body<true, DD, false, LIVE>(sm, Qg, Kg, sq, sk, H, n, nkb, cscale, lambda, lam_rows, KT, Mg, Yg, nullptr, nullptr, causal, rho, delta);
     else
-        moments_body<false, DD, false, LIVE>(sm, Qg, Kg, sq, sk, H, n, nkb, cscale, lambda, lam_rows, KT, Mg, Yg, nullptr, nullptr, causal);
+        moments_body<false, DD, false, LIVE>(sm, Qg, Kg, sq, sk, H, n, nkb, cscale, lambda, lam_rows, KT, Mg, Yg, nullptr, nullptr, causal, rho, delta);
 }
 
 // The same with the backward's second system (see moments_body).
@@ -987,34 +1023,6 @@ __global__ __launch_bounds__(Shape<DD>::NT, DD == 64 ? 2 : 1) void moments_u_ker
         moments_body<true, DD, true, LIVE>(sm, Qg, Kg, sq, sk, H, n, nkb, cscale, lambda, lam_rows, KT, Mg, Yg, Rg, Ug);
     else
         moments_body<false, DD, true, LIVE>(sm, Qg, Kg, sq, sk, H, n, nkb, cscale, lambda, lam_rows, KT, Mg, Yg, Rg, Ug);
-}
-
-// Optional statistics of Eq. (lla) from the solved y of every row: with y1 = -rho/delta and
-// y0 = (1 + q.rho)/delta, 1/delta = y0 + q.y1 and rho = -delta y1.  Sixteen lanes per row, so that a wave has four rows' loads in
-// flight and the sum over a row is four DPP additions (one row per wave and six shuffles: 18 us for 96 heads x 1000 rows).
-template <int DD>
-__global__ __launch_bounds__(256) void stats_kernel(const bf16_t *__restrict__ Qg, llla_strides sq, int H, int n,
-                                                    const float *__restrict__ Yg, float *__restrict__ rho,
-                                                    float *__restrict__ delta)
-{
-    constexpr int YP = Shape<DD>::YP, PER = DD / 16;
-    const int nn = threadIdx.x % 16, i = blockIdx.x * 16 + threadIdx.x / 16, ic = min(i, n - 1), bh = blockIdx.y;
-    const bf16_t *qrow = Qg + (bh / H) * sq.batch + (bh % H) * sq.head + (int64_t)ic * sq.seq;
-    const float *yr = Yg + ((size_t)bh * n + ic) * YP;
-    float y1[PER], qy = 0.f;
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-        y1[t] = yr[nn + 16 * t];
-        qy = fmaf(bf16_to_f32(qrow[nn + 16 * t]), y1[t], qy);
-    }
-    const float dl = 1.f / (yr[DD] + row_allsum(qy));
-    if (i >= n) return;
-    const size_t row = (size_t)bh * n + i;
-    if (delta != nullptr && nn == 0) delta[row] = dl;
-    if (rho != nullptr) {
-#pragma unroll
-        for (int t = 0; t < PER; ++t) rho[row * DD + nn + 16 * t] = -dl * y1[t];
-    }
 }
 
 template <int DD>
@@ -1057,19 +1065,14 @@ hipError_t forward_impl(const Problem &p)
     if constexpr (DD == 64) {
         if (live == 1)
             hipLaunchKernelGGL((moments_kernel<DD, 1>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
-                               L.nkb, first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal);
+                               L.nkb, first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
         else if (live == 2)
             hipLaunchKernelGGL((moments_kernel<DD, 2>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
-                               L.nkb, first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal);
+                               L.nkb, first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
     }
     if (live == S::NB)
         hipLaunchKernelGGL((moments_kernel<DD>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
-                           first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal);
-    if (p.rho != nullptr || p.delta != nullptr) {
-        stage_mark(p.stream, "statistics");
-        hipLaunchKernelGGL((stats_kernel<DD>), dim3((p.n + 15) / 16, bh), dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, Y, p.rho,
-                           p.delta);
-    }
+                           first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
     // output: those rows are evaluated in fp32 on the vector ALUs (their weights y0 + k.y1 cancel
     // to a few digits), the rest by the MFMA sweep
     if (first > 0) {
