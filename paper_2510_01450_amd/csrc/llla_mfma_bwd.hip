@@ -15,11 +15,14 @@
 //     16J+nn), so no tile is stored twice.
 // Accumulators stay in registers for the whole sweep; every output element is written once (no atomics).
 //
-// What bounds it: 64 MFMAs (1024 cycles) and some 200 vector instructions per step and wave, in a chain products -> coefficients ->
-// products, so the rest has to stay out of the way.  The dQ sweep leaves y1 and -u1 of every row split into bf16 hi and lo, in the
-// place of the fp32 rows (one split per row instead of one per row and block of 64 keys), which lets all six tiles of a step
-// arrive by DMA, at d = 64 one step ahead into a second buffer with one barrier per step.  Mask and correction of the maximum are
-// scalar branches.
+// What bounds it: 64 MFMAs (1024 cycles) and some 160 vector instructions per step and 16 keys, in a chain products -> coefficients ->
+// products; the two kinds of work hardly overlap between waves, so the rest has to stay out of the way.  The dQ sweep leaves y1 and -u1
+// of every row split into bf16 hi and lo, in the place of the fp32 rows (one split per row instead of one per row and block of 64
+// keys), which lets all six tiles of a step arrive by DMA, at d = 64 one step ahead into a second buffer with one barrier per step,
+// scalar bases and constant offsets.  Mask and correction of the maximum are one scalar branch each per step.
+// NK = 2 (d = 64): two blocks of 16 keys per wave share every operand fragment (a wave reads 48 KB of LDS per step, with one block
+// 1.5 times what LDS delivers while its products run).  It pays from TWO_KEY_BLOCKS_FROM workgroups of 128 keys on: 64 heads x 4096 rows
+// 1063 -> 942 us (one block 1036), 96 x 1000 130 -> 124; below, the longest workgroup decides: 16 x 4096 318 -> 390, 16 x 1000 57 -> 83.
 #include "llla_mfma_common.hpp"
 
 namespace llla {
@@ -43,16 +46,17 @@ __device__ inline bf16x8 tr_frag(const bf16_t *tile, int addr, int pitch)
     return __builtin_bit_cast(bf16x8, make_uint4(au.x, au.y, bu.x, bu.y));
 }
 
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-
-// x = hi + lo with both halves bf16, two values per conversion instruction
+// x = hi + lo with both halves bf16, two values per conversion instruction and one per remainder (see split3_bf16)
 __device__ inline void split_bf16(const float (&x)[8], bf16x8 &hi, bf16x8 &lo)
 {
+    unsigned c0 = 0x0000bf80u, c1 = 0xbf800000u;
+    asm("" : "+s"(c0), "+s"(c1));
+    const bf16x2v first = __builtin_bit_cast(bf16x2v, c0), second = __builtin_bit_cast(bf16x2v, c1);
 #pragma unroll
     for (int t = 0; t < 8; t += 2) {
         const bf16x2v h = __builtin_convertvector(float2v{x[t], x[t + 1]}, bf16x2v);
-        const bf16x2v l = __builtin_convertvector(float2v{x[t] - (float)h[0], x[t + 1] - (float)h[1]}, bf16x2v);
+        const bf16x2v l = __builtin_convertvector(float2v{__builtin_amdgcn_fdot2_f32_bf16(h, first, x[t], false),
+                                                          __builtin_amdgcn_fdot2_f32_bf16(h, second, x[t + 1], false)}, bf16x2v);
         hi[t] = h[0]; hi[t + 1] = h[1];
         lo[t] = l[0]; lo[t + 1] = l[1];
     }
@@ -69,8 +73,8 @@ __device__ inline int row_swizzle(int r)
     return ((r & 7) << 1) | ((r >> 3) & 1);
 }
 
-template <int DD>
-__global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
+template <int DD, int NK>
+__global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfma_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
     float scale, const float *__restrict__ Yg, const float *__restrict__ Ug, const float *__restrict__ Sc,
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
     constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
     constexpr int CH = DD / 8;                           // 16-byte chunks per row
     constexpr int TILE = QS * DD;                        // halves
-    constexpr int NBUF = DD == 64 ? 2 : 1;               // three workgroups per compute unit with 50 KB each, or two (d = 128)
+    constexpr int NBUF = DD == 64 ? 2 : 1;               // 50 KB per workgroup
     constexpr int RPT = 64 / CH, NTR = QS / RPT / 4;     // rows and number of a wave's transfers per tile
     enum { TQ, TG, TYH, TYL, TUH, TUL, NTILE };          // u: -u1, both uses subtract it
     __shared__ __align__(16) bf16_t tiles[NBUF][NTILE][TILE];
@@ -91,27 +95,30 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
     // with blockIdx.x running fastest, so the head is put there: all heads' longest blocks start first and the
     // shortest ones fill the tail, instead of the last head's longest block running alone at the end.
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int j0 = (int)blockIdx.y * 64;
-    const int jk = j0 + 16 * wave + nn, jkc = min(jk, n - 1);
+    const int j0 = (int)blockIdx.y * (64 * NK), jw = j0 + 16 * NK * wave;       // first key of the workgroup, of the wave
     const char *Qh = reinterpret_cast<const char *>(Qg + b * sq.batch + h * sq.head);
     const char *Gh = reinterpret_cast<const char *>(Gg + b * sg.batch + h * sg.head);
     const char *Yh = reinterpret_cast<const char *>(Yg + (size_t)bh * n * YP), *Uh = reinterpret_cast<const char *>(Ug + (size_t)bh * n * YP);
     const float *Sh = Sc + (size_t)bh * n * 8;
     const float cscale = scale * LOG2E;
 
-    bf16x8 kf[NF], vf[NF];
-    {
+    bf16x8 kf[NK][NF], vf[NK][NF];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const int jkc = min(jw + 16 * k + nn, n - 1);
         const bf16_t *krow = Kg + b * sk.batch + h * sk.head + (int64_t)jkc * sk.seq;
         const bf16_t *vrow = Vg + b * sv.batch + h * sv.head + (int64_t)jkc * sv.seq;
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            kf[f] = *reinterpret_cast<const bf16x8 *>(krow + 32 * f + 8 * g);
-            vf[f] = *reinterpret_cast<const bf16x8 *>(vrow + 32 * f + 8 * g);
+            kf[k][f] = *reinterpret_cast<const bf16x8 *>(krow + 32 * f + 8 * g);
+            vf[k][f] = *reinterpret_cast<const bf16x8 *>(vrow + 32 * f + 8 * g);
         }
     }
-    f32x4 dv[NB], dk[NB];
+    f32x4 dv[NK][NB], dk[NK][NB];
 #pragma unroll
-    for (int J = 0; J < NB; ++J) dv[J] = dk[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+        for (int J = 0; J < NB; ++J) dv[k][J] = dk[k][J] = f32x4{0.f, 0.f, 0.f, 0.f};
     int row_addr[NF], tr_addr[NB];                       // operand reads: rows (+ 16 s DD), columns
 #pragma unroll
     for (int f = 0; f < NF; ++f) row_addr[f] = nn * DD + (((g + 4 * f) ^ row_swizzle<DD>(nn)) * 8);
@@ -121,54 +128,84 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
         for (int J = 0; J < NB; ++J) tr_addr[J] = r * DD + (((2 * J + ((nn & 3) >> 1)) ^ row_swizzle<DD>(r)) * 8) + (nn & 1) * 4;
     }
 
-    // transfer t of wave w fills rows RPT (NTR w + t) ..; rows past the end repeat the last one (their coefficients are zero)
+    // Transfer t of wave w fills rows RPT (NTR w + t) ...  Steps inside the sequence take a scalar base and offsets that never change (no
+    // address arithmetic on the vector ALU); in the last one rows past the end repeat the last row (their coefficients are zero).
+    unsigned q_off[NTR], g_off[NTR], y_off[NTR];
+    const bool small_pitch = sq.seq < (int64_t(1) << 24) && sg.seq < (int64_t(1) << 24);       // the offsets fit 32 bits
+    const int n_whole = small_pitch ? n : 0;
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
+        const int r = RPT * (NTR * wave + t) + lane / CH, col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+        q_off[t] = 2u * (unsigned)(r * (int)sq.seq) + col;
+        g_off[t] = 2u * (unsigned)(r * (int)sg.seq) + col;
+        y_off[t] = (unsigned)(r * (YP * 4) + col);
+    }
+    const unsigned tiles_lds = lds_offset(&tiles[0][0][0]), rs_lds = lds_offset(&rs[0][0]);
     auto issue = [&](int buf, int it0) {
+        const bool whole = it0 + QS <= n_whole;
+        const char *qb = Qh + (int64_t)it0 * sq.seq * 2, *gb = Gh + (int64_t)it0 * sg.seq * 2;
+        const char *yb = Yh + (int64_t)it0 * (YP * 4), *ub = Uh + (int64_t)it0 * (YP * 4);
 #pragma unroll
         for (int t = 0; t < NTR; ++t) {
-            const int r0 = RPT * (NTR * wave + t), r = r0 + lane / CH;
-            const int64_t i = min(it0 + r, n - 1);
-            const int col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
-            const char *y = Yh + i * (YP * 4) + col, *u = Uh + i * (YP * 4) + col;
-            dma16(Qh + i * sq.seq * 2 + col, &tiles[buf][TQ][r0 * DD]);
-            dma16(Gh + i * sg.seq * 2 + col, &tiles[buf][TG][r0 * DD]);
-            dma16(y, &tiles[buf][TYH][r0 * DD]);
-            dma16(y + 2 * DD, &tiles[buf][TYL][r0 * DD]);
-            dma16(u, &tiles[buf][TUH][r0 * DD]);
-            dma16(u + 2 * DD, &tiles[buf][TUL][r0 * DD]);
+            const int r0 = RPT * (NTR * wave + t);
+            const unsigned dst = tiles_lds + 2u * (unsigned)(buf * NTILE * TILE + r0 * DD);
+            if (whole) {
+                dma16_base_off(qb, q_off[t], dst + 2u * (TQ * TILE));
+                dma16_base_off(gb, g_off[t], dst + 2u * (TG * TILE));
+                dma16_base_off(yb, y_off[t], dst + 2u * (TYH * TILE));
+                dma16_base_off(yb + 2 * DD, y_off[t], dst + 2u * (TYL * TILE));
+                dma16_base_off(ub, y_off[t], dst + 2u * (TUH * TILE));
+                dma16_base_off(ub + 2 * DD, y_off[t], dst + 2u * (TUL * TILE));
+            } else {
+                const int r = r0 + lane / CH;
+                const int64_t i = min(it0 + r, n - 1);
+                const int col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+                const char *y = Yh + i * (YP * 4) + col, *u = Uh + i * (YP * 4) + col;
+                dma16(Qh + i * sq.seq * 2 + col, &tiles[buf][TQ][r0 * DD]);
+                dma16(Gh + i * sg.seq * 2 + col, &tiles[buf][TG][r0 * DD]);
+                dma16(y, &tiles[buf][TYH][r0 * DD]);
+                dma16(y + 2 * DD, &tiles[buf][TYL][r0 * DD]);
+                dma16(u, &tiles[buf][TUH][r0 * DD]);
+                dma16(u + 2 * DD, &tiles[buf][TUL][r0 * DD]);
+            }
         }
-        if (wave == 0) dma16(Sh + (size_t)min(it0 + (lane >> 1), n - 1) * 8 + 4 * (lane & 1), rs[buf]);
+        if (wave == 0) {
+            if (whole) dma16_base_off(Sh + (size_t)it0 * 8, 16u * lane, rs_lds + 4u * (unsigned)(buf * QS * 8));
+            else dma16(Sh + (size_t)min(it0 + (lane >> 1), n - 1) * 8 + 4 * (lane & 1), rs[buf]);
+        }
     };
 
-    if (NBUF == 2) issue(0, j0);
-    for (int it0 = j0, c = 0; it0 < n; it0 += QS, ++c) {
-        const int buf = NBUF == 2 ? c & 1 : 0;
+    // one step (buf: with two key blocks a run-time value, since two copies of the loop spill; else a constant, so that the operand
+    // addresses are registers plus immediates)
+    auto step = [&](auto buf, int it0) {
         if (NBUF == 1) {
             __syncthreads();                             // the previous step's tiles are consumed
             issue(0, it0);
         }
         dma_wait();
         __syncthreads();                                 // this step has arrived (NBUF 2: and the previous one is consumed)
-        if (NBUF == 2 && it0 + QS < n) issue(buf ^ 1, it0 + QS);
+        const bool more = NBUF == 2 && it0 + QS < n;
+        if (NK > 1 && more) issue(buf ^ 1, it0 + QS);
+        if (NK > 1 && it0 + QS <= jw) return;            // every row of the step lies before the wave's first key
         const bf16_t *qt = tiles[buf][TQ], *gt = tiles[buf][TG], *yh = tiles[buf][TYH], *yl = tiles[buf][TYL];
         const bf16_t *uh = tiles[buf][TUH], *ul = tiles[buf][TUL];
 
-        // ---- coefficients: lane (g, nn) holds the pairs (query it0 + 16s + 4g + r, key jk) --------------------
-        const bool masked = it0 < j0 + 16 * wave + 15 || it0 + QS > n;
-        float sv_[8], ev_[8], pv_[8];
+        // ---- coefficients: lane (g, nn) holds the pairs (query it0 + 16s + 4g + r, key jw + 16k + nn) ----------
+        float sv_[NK][8], ev_[NK][8], pv_[NK][8];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            f32x4 st = {0.f, 0.f, 0.f, 0.f}, at, et;
-            float m[4], corr[4];
-            int jstar[4];
+            f32x4 st[NK], at[NK], et[NK];
+            float m[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float *row = &rs[buf][(16 * s + 4 * g + r) * 8];
-                const f32x4 s4 = *reinterpret_cast<const f32x4 *>(row);
-                at[r] = s4[0];
-                et[r] = -s4[1];
+                const f32x4 s4 = *reinterpret_cast<const f32x4 *>(&rs[buf][(16 * s + 4 * g + r) * 8]);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    st[k][r] = 0.f;
+                    at[k][r] = s4[0];
+                    et[k][r] = -s4[1];
+                }
                 m[r] = s4[2];
-                corr[r] = s4[3];
-                jstar[r] = __float_as_int(row[4]);
             }
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
@@ -179,78 +216,150 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
                 const bf16x8 ylf = *reinterpret_cast<const bf16x8 *>(yl + ar);
                 const bf16x8 uhf = *reinterpret_cast<const bf16x8 *>(uh + ar);
                 const bf16x8 ulf = *reinterpret_cast<const bf16x8 *>(ul + ar);
-                st = mfma_bf16(qf, kf[f], st);
-                at = mfma_bf16(ylf, kf[f], at);
-                et = mfma_bf16(ulf, kf[f], et);
-                at = mfma_bf16(yhf, kf[f], at);
-                et = mfma_bf16(uhf, kf[f], et);
-                et = mfma_bf16(gf, vf[f], et);           // gamma - u0 - u1.k
-            }
-            bool star = false;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float w = __builtin_amdgcn_exp2f(fmaf(st[r], cscale, -m[r]));
-                sv_[4 * s + r] = w * at[r];
-                ev_[4 * s + r] = w * et[r];
-                pv_[4 * s + r] = sv_[4 * s + r] * et[r];
-                star = star || jk == jstar[r];
+                for (int k = 0; k < NK; ++k) {
+                    st[k] = mfma_bf16(qf, kf[k][f], st[k]);
+                    at[k] = mfma_bf16(ylf, kf[k][f], at[k]);
+                    et[k] = mfma_bf16(ulf, kf[k][f], et[k]);
+                    at[k] = mfma_bf16(yhf, kf[k][f], at[k]);
+                    et[k] = mfma_bf16(uhf, kf[k][f], et[k]);
+                    et[k] = mfma_bf16(gf, vf[k][f], et[k]);          // gamma - u0 - u1.k
+                }
             }
-            if (__any(star)) {
+            // (with one key block behind the first products, so that the reads above do not wait for its scalar work: few heads 3 % faster;
+            // with two 3 % slower)
+            if (NK == 1 && s == 0 && more) issue(buf ^ 1, it0 + QS);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) pv_[4 * s + r] += jk == jstar[r] ? corr[r] : 0.f;
-            }
+            for (int k = 0; k < NK; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float w = __builtin_amdgcn_exp2f(fmaf(st[k][r], cscale, -m[r]));
+                    sv_[k][4 * s + r] = w * at[k][r];
+                    ev_[k][4 * s + r] = w * et[k][r];
+                    pv_[k][4 * s + r] = sv_[k][4 * s + r] * et[k][r];
+                }
         }
-        if (masked) {
+        // the correction of the maximum, where a row of the step attains it at one of the wave's keys (lane l looks at row l % 32)
+        if (__any((unsigned)(__float_as_int(rs[buf][(lane & 31) * 8 + 4]) - jw) < 16u * NK)) {
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const int i = it0 + 16 * (t >> 2) + 4 * g + (t & 3);
-                const bool valid = jk <= i && i < n;
-                sv_[t] = valid ? sv_[t] : 0.f;
-                ev_[t] = valid ? ev_[t] : 0.f;
-                pv_[t] = valid ? pv_[t] : 0.f;
+                const float *row = &rs[buf][(16 * (t >> 2) + 4 * g + (t & 3)) * 8];
+#pragma unroll
+                for (int k = 0; k < NK; ++k) pv_[k][t] += jw + 16 * k + nn == __float_as_int(row[4]) ? row[3] : 0.f;
             }
         }
+        if (it0 < jw + 16 * NK - 1 || it0 + QS > n) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) pv_[t] *= scale;
-        bf16x8 s_hi, s_lo, e_hi, e_lo, p_hi, p_lo;
-        split_bf16(sv_, s_hi, s_lo);
-        split_bf16(ev_, e_hi, e_lo);
-        split_bf16(pv_, p_hi, p_lo);
-
-        // ---- accumulate over the step's 32 queries --------------------------------------------------------------
+            for (int k = 0; k < NK; ++k)
 #pragma unroll
-        for (int J = 0; J < NB; ++J) {
-            const int ta = tr_addr[J];
-            const bf16x8 gT = tr_frag(gt, ta, DD);
-            dv[J] = mfma_bf16(s_lo, gT, dv[J]);
-            const bf16x8 yhT = tr_frag(yh, ta, DD), ylT = tr_frag(yl, ta, DD);
-            dk[J] = mfma_bf16(e_lo, yhT, dk[J]);
-            dv[J] = mfma_bf16(s_hi, gT, dv[J]);
-            dk[J] = mfma_bf16(e_hi, ylT, dk[J]);
-            dk[J] = mfma_bf16(e_hi, yhT, dk[J]);
-            const bf16x8 uhT = tr_frag(uh, ta, DD), ulT = tr_frag(ul, ta, DD);
-            dk[J] = mfma_bf16(s_lo, uhT, dk[J]);
-            dk[J] = mfma_bf16(s_hi, ulT, dk[J]);
-            dk[J] = mfma_bf16(s_hi, uhT, dk[J]);
-            const bf16x8 qT = tr_frag(qt, ta, DD);
-            dk[J] = mfma_bf16(p_lo, qT, dk[J]);
-            dk[J] = mfma_bf16(p_hi, qT, dk[J]);
+                for (int t = 0; t < 8; ++t) {
+                    const int i = it0 + 16 * (t >> 2) + 4 * g + (t & 3);
+                    const bool valid = jw + 16 * k + nn <= i && i < n;
+                    sv_[k][t] = valid ? sv_[k][t] : 0.f;
+                    ev_[k][t] = valid ? ev_[k][t] : 0.f;
+                    pv_[k][t] = valid ? pv_[k][t] : 0.f;
+                }
         }
-    }
 
-    // dv[J], dk[J]: lane (g, nn) reg r = gradient of key j0 + 16 wave + 4g + r, feature 16J + nn
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int key = j0 + 16 * wave + 4 * g + r;
-        if (key < n) {
-            const size_t off = ((size_t)bh * n + key) * DD + nn;
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) pv_[k][t] *= scale;
+
+        // ---- accumulate over the step's 32 queries ----------------------------------------------------------------
+        if constexpr (NK == 1) {
+            bf16x8 s_hi, s_lo, e_hi, e_lo, p_hi, p_lo;
+            split_bf16(sv_[0], s_hi, s_lo);
+            split_bf16(ev_[0], e_hi, e_lo);
+            split_bf16(pv_[0], p_hi, p_lo);
 #pragma unroll
             for (int J = 0; J < NB; ++J) {
-                dK[off + 16 * J] = dk[J][r];
-                dV[off + 16 * J] = dv[J][r];
+                f32x4 &dvj = dv[0][J], &dkj = dk[0][J];
+                const bf16x8 gT = tr_frag(gt, tr_addr[J], DD);
+                dvj = mfma_bf16(s_lo, gT, dvj);
+                const bf16x8 yhT = tr_frag(yh, tr_addr[J], DD), ylT = tr_frag(yl, tr_addr[J], DD);
+                dkj = mfma_bf16(e_lo, yhT, dkj);
+                dvj = mfma_bf16(s_hi, gT, dvj);
+                dkj = mfma_bf16(e_hi, ylT, dkj);
+                dkj = mfma_bf16(e_hi, yhT, dkj);
+                const bf16x8 uhT = tr_frag(uh, tr_addr[J], DD), ulT = tr_frag(ul, tr_addr[J], DD);
+                dkj = mfma_bf16(s_lo, uhT, dkj);
+                dkj = mfma_bf16(s_hi, ulT, dkj);
+                dkj = mfma_bf16(s_hi, uhT, dkj);
+                const bf16x8 qT = tr_frag(qt, tr_addr[J], DD);
+                dkj = mfma_bf16(p_lo, qT, dkj);
+                dkj = mfma_bf16(p_hi, qT, dkj);
+            }
+        } else {
+            // one coefficient after the other: the next one is split beside the products of this one
+            bf16x8 c_hi[NK], c_lo[NK];
+#pragma unroll
+            for (int k = 0; k < NK; ++k) split_bf16(sv_[k], c_hi[k], c_lo[k]);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) {
+                const bf16x8 gT = tr_frag(gt, tr_addr[J], DD), uhT = tr_frag(uh, tr_addr[J], DD), ulT = tr_frag(ul, tr_addr[J], DD);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    dv[k][J] = mfma_bf16(c_lo[k], gT, dv[k][J]);
+                    dk[k][J] = mfma_bf16(c_lo[k], uhT, dk[k][J]);
+                }
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    dv[k][J] = mfma_bf16(c_hi[k], gT, dv[k][J]);
+                    dk[k][J] = mfma_bf16(c_hi[k], ulT, dk[k][J]);
+                }
+#pragma unroll
+                for (int k = 0; k < NK; ++k) dk[k][J] = mfma_bf16(c_hi[k], uhT, dk[k][J]);
+            }
+#pragma unroll
+            for (int k = 0; k < NK; ++k) split_bf16(ev_[k], c_hi[k], c_lo[k]);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) {
+                const bf16x8 yhT = tr_frag(yh, tr_addr[J], DD), ylT = tr_frag(yl, tr_addr[J], DD);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) dk[k][J] = mfma_bf16(c_lo[k], yhT, dk[k][J]);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) dk[k][J] = mfma_bf16(c_hi[k], ylT, dk[k][J]);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) dk[k][J] = mfma_bf16(c_hi[k], yhT, dk[k][J]);
+            }
+#pragma unroll
+            for (int k = 0; k < NK; ++k) split_bf16(pv_[k], c_hi[k], c_lo[k]);
+#pragma unroll
+            for (int J = 0; J < NB; ++J) {
+                const bf16x8 qT = tr_frag(qt, tr_addr[J], DD);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) dk[k][J] = mfma_bf16(c_lo[k], qT, dk[k][J]);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) dk[k][J] = mfma_bf16(c_hi[k], qT, dk[k][J]);
             }
         }
+    };
+    if (NBUF == 2) issue(0, j0);
+    if constexpr (NK == 1) {
+        for (int it0 = j0; it0 < n; it0 += NBUF * QS) {
+            step(std::integral_constant<int, 0>{}, it0);
+            if (NBUF == 2 && it0 + QS < n) step(std::integral_constant<int, NBUF - 1>{}, it0 + QS);
+        }
+    } else {
+        for (int it0 = j0, c = 0; it0 < n; it0 += QS, ++c) step(c & 1, it0);
     }
+
+    // dv[k][J], dk[k][J]: lane (g, nn) reg r = gradient of key jw + 16k + 4g + r, feature 16J + nn
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int key = jw + 16 * k + 4 * g + r;
+            if (key < n) {
+                const size_t off = ((size_t)bh * n + key) * DD + nn;
+#pragma unroll
+                for (int J = 0; J < NB; ++J) {
+                    dK[off + 16 * J] = dk[k][J][r];
+                    dV[off + 16 * J] = dv[k][J][r];
+                }
+            }
+        }
 }
 
 
@@ -265,7 +374,12 @@ __global__ __launch_bounds__(256, DD == 64 ? 3 : 2) void bwd_keys_mfma_kernel(
 //                              fp32 rows, y1 and -u1 as bf16 hi (DD halves) and lo.
 // Rows [first_row, n) only: the first rows of a sequence take fp32 sweeps (their coefficients cancel too strongly for
 // a 16-bit split).
-template <int DD, int MODE>
+// The K and V tiles come by DMA into NST stages as in the key sweep, one barrier per block.  A block is so short (16 and 32 MFMAs) that the
+// transfers' latency shows where they are one block ahead: MODE 1 keeps three on their way (64 heads x 4096: through registers and two
+// barriers 493 us, one block ahead 480, three 434).  MODE 0, bound by its vector work, has two stages and the loop unrolled
+// over them (341 -> 307; three blocks ahead 319), and NQ = 2 blocks of 16 queries per wave from TWO_QUERY_BLOCKS_FROM workgroups of 128
+// rows on (328 -> 310; 64 x 2048 102 -> 106, 96 x 1000 47 -> 55).
+template <int DD, int MODE, int NQ>
 __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
@@ -274,202 +388,283 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
 {
     using S = Shape<DD>;
     constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
-    // halves per row of an LDS tile: 32 B of padding, i.e. a row pitch of 40 (d = 64) or 72 (d = 128) banks, keeps the
-    // transposing reads of a half-wave (8 rows x 8 banks) on distinct banks
-    constexpr int P = DD + 16, CH = DD / 8;
-    __shared__ __align__(16) bf16_t kt[KB * P], vt[KB * P];
+    constexpr int CH = DD / 8, TILE = KB * DD, RPT = 64 / CH, NTR = KB / RPT / 4;     // as in the key sweep
+    constexpr int NST = MODE == 0 ? 2 : 4;               // blocks in LDS: the one in use and NST - 1 on their way
+    __shared__ __align__(16) bf16_t kt[NST][TILE], vt[NST][TILE];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     // head on blockIdx.x (dispatched fastest), row block on y, longest rows first: see bwd_keys_mfma_kernel
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int i0 = first_row + ((int)gridDim.y - 1 - (int)blockIdx.y) * 64;
-    const int iq = i0 + 16 * wave + nn, iqc = min(iq, n - 1);
-    const size_t row = (size_t)bh * n + iqc;
-    const bf16_t *Kh = Kg + b * sk.batch + h * sk.head;
-    const bf16_t *Vh = Vg + b * sv.batch + h * sv.head;
-    const float cscale = scale * LOG2E;
+    const int i0 = first_row + ((int)gridDim.y - 1 - (int)blockIdx.y) * (64 * NQ), iw = i0 + 16 * NQ * wave;   // first row of the workgroup, of the wave
+    const char *Kh = reinterpret_cast<const char *>(Kg + b * sk.batch + h * sk.head);
+    const char *Vh = reinterpret_cast<const char *>(Vg + b * sv.batch + h * sv.head);
+    // MODE 0 compares raw products with the maximum, so the sign of the scale goes into the query operand
+    const float cscale = MODE == 0 ? fabsf(scale * LOG2E) : scale * LOG2E;
+    const unsigned flip = MODE == 0 && scale < 0.f ? 0x80008000u : 0u;
 
-    bf16x8 qf[NF], gf[NF], yhf[NF], ylf[NF], uhf[NF], ulf[NF];
-    {
+    bf16x8 qf[NQ][NF], gf[NQ][NF], yhf[NQ][NF], ylf[NQ][NF], uhf[NQ][NF], ulf[NQ][NF];
+    float mrow[NQ], near[NQ], y0[NQ], u0[NQ], corr[NQ];
+    int jstar[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int iq = iw + 16 * q + nn, iqc = min(iq, n - 1);
+        const size_t row = (size_t)bh * n + iqc;
         const bf16_t *qrow = Qg + b * sq.batch + h * sq.head + (int64_t)iqc * sq.seq;
         const bf16_t *grow = Gg + b * sg.batch + h * sg.head + (int64_t)iqc * sg.seq;
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            qf[f] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * f + 8 * g);
-            gf[f] = *reinterpret_cast<const bf16x8 *>(grow + 32 * f + 8 * g);
+            u32x4 u = *reinterpret_cast<const u32x4 *>(qrow + 32 * f + 8 * g);
+            if (MODE == 0) u ^= flip;
+            qf[q][f] = __builtin_bit_cast(bf16x8, u);
+            gf[q][f] = *reinterpret_cast<const bf16x8 *>(grow + 32 * f + 8 * g);
         }
-    }
-    const float mrow = Mg[(size_t)bh * mpitch + iqc];                     // log2 units
-    float y0 = 0.f, u0 = 0.f, corr = 0.f;
-    int jstar = 0;
-    if (MODE == 1) {
-        const float *yr = Yg + row * YP, *ur = Ug + row * YP;
-        y0 = yr[DD];
-        u0 = ur[DD];
-        jstar = __float_as_int(Rv[row * YP + DD + 1]);
-        float dl = 0.f;
+        mrow[q] = Mg[(size_t)bh * mpitch + iqc];                          // log2 units
+        // a product from here on can be the row's maximum (a zero scale: every one)
+        near[q] = (mrow[q] - (1e-4f * fabsf(mrow[q]) + 1e-30f)) / cscale;
+        y0[q] = u0[q] = corr[q] = 0.f;
+        jstar[q] = 0;
+        if (MODE == 1) {
+            const float *yr = Yg + row * YP, *ur = Ug + row * YP;
+            y0[q] = yr[DD];
+            u0[q] = ur[DD];
+            jstar[q] = __float_as_int(Rv[row * YP + DD + 1]);
+            float dl = 0.f;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            float yv[8], uv[8];
+            for (int f = 0; f < NF; ++f) {
+                float yv[8], uv[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                yv[t] = yr[32 * f + 8 * g + t];
-                const float u = ur[32 * f + 8 * g + t];
-                dl = fmaf(-u, yv[t], dl);
-                uv[t] = -u;
+                for (int t = 0; t < 8; ++t) {
+                    yv[t] = yr[32 * f + 8 * g + t];
+                    const float u = ur[32 * f + 8 * g + t];
+                    dl = fmaf(-u, yv[t], dl);
+                    uv[t] = -u;
+                }
+                split_bf16(yv, yhf[q][f], ylf[q][f]);
+                split_bf16(uv, uhf[q][f], ulf[q][f]);
             }
-            split_bf16(yv, yhf[f], ylf[f]);
-            split_bf16(uv, uhf[f], ulf[f]);
-        }
-        dl += __shfl_xor(dl, 16);
-        dl += __shfl_xor(dl, 32);
-        corr = (LamRows ? LamRows[row] : lambda) * dl;
-        if (g == 0 && iq < n) {
-            float *sc = Sc + row * 8;
-            sc[0] = y0; sc[1] = u0; sc[2] = mrow; sc[3] = corr; sc[4] = __int_as_float(jstar);
-            if (dLam) dLam[row] = dl;
+            dl += __shfl_xor(dl, 16);
+            dl += __shfl_xor(dl, 32);
+            corr[q] = (LamRows ? LamRows[row] : lambda) * dl;
+            if (g == 0 && iq < n) {
+                float *sc = Sc + row * 8;
+                sc[0] = y0[q]; sc[1] = u0[q]; sc[2] = mrow[q]; sc[3] = corr[q]; sc[4] = __int_as_float(jstar[q]);
+                if (dLam) dLam[row] = dl;
+            }
         }
     }
-    f32x4 acc[NB];
+    f32x4 acc[NQ][NB];
+    float csum[NQ], best[NQ];
+    int arg[NQ];
 #pragma unroll
-    for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float csum = 0.f, best = -INFINITY;
-    const float near = mrow - (1e-4f * fabsf(mrow) + 1e-30f);
-    int arg = 0;
-    const int tr_addr = (4 * g + (nn >> 2)) * P + 4 * (nn & 3);
-
-    const int nblk = min(i0 + 63, n - 1) / KB + 1;
-    // the next key tile travels from global memory into registers while the current one is consumed
-    constexpr int NIT = KB * CH / 256;
-    u32x4 pk[NIT], pv[NIT];
-    auto fetch = [&](int c) {
+    for (int q = 0; q < NQ; ++q) {
 #pragma unroll
-        for (int k = 0; k < NIT; ++k) {
-            const int idx = tid + 256 * k, key = idx / CH, ch = (idx % CH) * 8, j = c * KB + key;
-            pk[k] = pv[k] = u32x4{0u, 0u, 0u, 0u};
-            if (j < n) {
-                pk[k] = *reinterpret_cast<const u32x4 *>(Kh + (int64_t)j * sk.seq + ch);
-                pv[k] = *reinterpret_cast<const u32x4 *>(Vh + (int64_t)j * sv.seq + ch);
+        for (int J = 0; J < NB; ++J) acc[q][J] = f32x4{0.f, 0.f, 0.f, 0.f};
+        csum[q] = 0.f;
+        best[q] = -INFINITY;
+        arg[q] = 0;
+    }
+    int row_addr[NF], tr_addr[NB];                       // operand reads: rows (+ 16 s DD), columns
+#pragma unroll
+    for (int f = 0; f < NF; ++f) row_addr[f] = nn * DD + (((g + 4 * f) ^ row_swizzle<DD>(nn)) * 8);
+    {
+        const int r = 4 * g + (nn >> 2);
+#pragma unroll
+        for (int J = 0; J < NB; ++J) tr_addr[J] = r * DD + (((2 * J + ((nn & 3) >> 1)) ^ row_swizzle<DD>(r)) * 8) + (nn & 1) * 4;
+    }
+    // as in the key sweep; keys past the end repeat the last one: no row that is stored sees them
+    unsigned k_off[NTR], v_off[NTR];
+    const int n_whole = sk.seq < (int64_t(1) << 24) && sv.seq < (int64_t(1) << 24) ? n : 0;
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
+        const int r = RPT * (NTR * wave + t) + lane / CH, col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+        k_off[t] = 2u * (unsigned)(r * (int)sk.seq) + col;
+        v_off[t] = 2u * (unsigned)(r * (int)sv.seq) + col;
+    }
+    const unsigned kt_lds = lds_offset(&kt[0][0]), vt_lds = lds_offset(&vt[0][0]);
+    auto issue = [&](int buf, int c) {
+        const bool whole = c * KB + KB <= n_whole;
+        const char *kb = Kh + (int64_t)(c * KB) * sk.seq * 2, *vb = Vh + (int64_t)(c * KB) * sv.seq * 2;
+#pragma unroll
+        for (int t = 0; t < NTR; ++t) {
+            const int r0 = RPT * (NTR * wave + t);
+            if (whole) {
+                dma16_base_off(kb, k_off[t], kt_lds + 2u * (unsigned)(buf * TILE + r0 * DD));
+                dma16_base_off(vb, v_off[t], vt_lds + 2u * (unsigned)(buf * TILE + r0 * DD));
+            } else {
+                const int r = r0 + lane / CH;
+                const int64_t j = min(c * KB + r, n - 1);
+                const int col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+                dma16(Kh + j * sk.seq * 2 + col, &kt[buf][r0 * DD]);
+                dma16(Vh + j * sv.seq * 2 + col, &vt[buf][r0 * DD]);
             }
         }
     };
-    fetch(0);
-    for (int c = 0; c < nblk; ++c) {
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < NIT; ++k) {
-            const int idx = tid + 256 * k, key = idx / CH, ch = (idx % CH) * 8;
-            *reinterpret_cast<u32x4 *>(&kt[key * P + ch]) = pk[k];
-            *reinterpret_cast<u32x4 *>(&vt[key * P + ch]) = pv[k];
+
+    const int nblk = min(i0 + 64 * NQ - 1, n - 1) / KB + 1;
+    auto step = [&](auto buf, int c) {
+        dma_wait_but<2 * NTR * (NST - 2)>();
+        __syncthreads();                                 // this block has arrived, the previous one is consumed
+        const int next = min(c + NST - 1, nblk - 1);     // (past the end: the last block again, so that the count above holds)
+        if (MODE == 1) issue((buf + NST - 1) & (NST - 1), next);
+        if (c * KB > iw + 16 * NQ - 1) {                 // every key of the block lies behind the wave's last row
+            if (MODE == 0) issue((buf + NST - 1) & (NST - 1), next);
+            return;
         }
-        __syncthreads();
-        if (c + 1 < nblk) fetch(c + 1);
-        // only the blocks that reach past the wave's first query need the causal mask
-        const bool masked = c * KB + KB - 1 > i0 + 16 * wave;
-        float cv[8];
+        float cv[NQ][8], lg[NQ][8];                      // coefficients; MODE 0: raw products
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            f32x4 st = {0.f, 0.f, 0.f, 0.f}, et = {-u0, -u0, -u0, -u0}, at = {y0, y0, y0, y0};      // MODE 0: y0 = u0 = 0
-            const int arow = (16 * s + nn) * P + 8 * g;
+            f32x4 st[NQ], et[NQ], at[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                st[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                et[q] = f32x4{-u0[q], -u0[q], -u0[q], -u0[q]};            // MODE 0: y0 = u0 = 0
+                at[q] = f32x4{y0[q], y0[q], y0[q], y0[q]};
+            }
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const bf16x8 kfr = *reinterpret_cast<const bf16x8 *>(&kt[arow + 32 * f]);
-                const bf16x8 vfr = *reinterpret_cast<const bf16x8 *>(&vt[arow + 32 * f]);
-                st = mfma_bf16(kfr, qf[f], st);
-                if (MODE == 1) {
-                    at = mfma_bf16(kfr, ylf[f], at);
-                    et = mfma_bf16(kfr, ulf[f], et);
-                    at = mfma_bf16(kfr, yhf[f], at);
-                    et = mfma_bf16(kfr, uhf[f], et);
+                const bf16x8 kfr = *reinterpret_cast<const bf16x8 *>(&kt[buf][row_addr[f] + 16 * s * DD]);
+                const bf16x8 vfr = *reinterpret_cast<const bf16x8 *>(&vt[buf][row_addr[f] + 16 * s * DD]);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    st[q] = mfma_bf16(kfr, qf[q][f], st[q]);
+                    if (MODE == 1) {
+                        at[q] = mfma_bf16(kfr, ylf[q][f], at[q]);
+                        et[q] = mfma_bf16(kfr, ulf[q][f], et[q]);
+                        at[q] = mfma_bf16(kfr, yhf[q][f], at[q]);
+                        et[q] = mfma_bf16(kfr, uhf[q][f], et[q]);
+                    }
+                    et[q] = mfma_bf16(vfr, gf[q][f], et[q]);
                 }
-                et = mfma_bf16(vfr, gf[f], et);
             }
+            // (MODE 0: behind the first products, so that the reads above do not wait for its scalar work: few heads 8 % faster; MODE 1 7 % slower)
+            if (MODE == 0 && s == 0) issue((buf + NST - 1) & (NST - 1), next);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float w = __builtin_amdgcn_exp2f(fmaf(st[r], cscale, -mrow));
-                cv[4 * s + r] = MODE == 0 ? w * et[r] : w * at[r] * et[r];
-            }
-            const int jb = c * KB + 16 * s + 4 * g;
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float w = __builtin_amdgcn_exp2f(fmaf(st[q][r], cscale, -mrow[q]));
+                    cv[q][4 * s + r] = MODE == 0 ? w * et[q][r] : w * at[q][r] * et[q][r];
+                    lg[q][4 * s + r] = st[q][r];
+                }
+        }
+        // lane (g, nn): cv[q][4s + r] belongs to key 32c + 16s + 4g + r and query iw + 16q + nn
+        const int j0 = c * KB + 4 * g;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
             if (MODE == 0) {
-                // the first key at the row maximum: only a tile that comes near the maximum is looked at
-                const float top = fmaxf(fmaxf(st[0] * cscale, st[1] * cscale), fmaxf(st[2] * cscale, st[3] * cscale));
-                if (__any(top >= near)) {
+                // the first key at the row maximum: only a block that comes near the maximum is looked at
+                float top = fmaxf(lg[q][0], lg[q][1]);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float lg = st[r] * cscale;
-                        if (jb + r <= iq && iq < n && lg > best) {
-                            best = lg;
-                            arg = jb + r;
+                for (int t = 2; t < 8; t += 2) top = fmaxf(fmaxf(top, lg[q][t]), lg[q][t + 1]);
+                if (__any(!(top < near[q]))) {
+                    const int iq = iw + 16 * q + nn;
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const int j = j0 + 16 * (t >> 2) + (t & 3);
+                        const float l = lg[q][t] * cscale;
+                        if (j <= iq && iq < n && l > best[q]) {
+                            best[q] = l;
+                            arg[q] = j;
                         }
                     }
                 }
-            } else if (__any((unsigned)(jstar - jb) < 4u)) {
+            } else if (__any((unsigned)(jstar[q] - c * KB) < (unsigned)KB)) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) cv[4 * s + r] += jb + r == jstar ? corr : 0.f;
+                for (int t = 0; t < 8; ++t) cv[q][t] += j0 + 16 * (t >> 2) + (t & 3) == jstar[q] ? corr[q] : 0.f;
             }
         }
-        if (masked) {
+        if (c * KB + KB - 1 > iw) {                      // only the blocks that reach past the wave's first query need the causal mask
 #pragma unroll
-            for (int t = 0; t < 8; ++t) cv[t] = c * KB + 16 * (t >> 2) + 4 * g + (t & 3) <= iq ? cv[t] : 0.f;
-        }
-        if (MODE == 0) {
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int t = 0; t < 8; ++t) csum += cv[t];
+                for (int t = 0; t < 8; ++t) cv[q][t] = j0 + 16 * (t >> 2) + (t & 3) <= iw + 16 * q + nn ? cv[q][t] : 0.f;
         }
-        bf16x8 c_hi, c_lo;
-        split_bf16(cv, c_hi, c_lo);
+        bf16x8 c_hi[NQ], c_lo[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (MODE == 0) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) csum[q] += cv[q][t];
+            }
+            split_bf16(cv[q], c_hi[q], c_lo[q]);
+        }
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
-            const bf16x8 kT = tr_frag(kt, tr_addr + 16 * J, P);
-            acc[J] = mfma_bf16(c_lo, kT, acc[J]);
-            acc[J] = mfma_bf16(c_hi, kT, acc[J]);
+            const bf16x8 kT = tr_frag(kt[buf], tr_addr[J], DD);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) acc[q][J] = mfma_bf16(c_lo[q], kT, acc[q][J]);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) acc[q][J] = mfma_bf16(c_hi[q], kT, acc[q][J]);
         }
+    };
+#pragma unroll
+    for (int c = 0; c < NST - 1; ++c) issue(c, min(c, nblk - 1));
+    if constexpr (MODE == 0) {
+        for (int c = 0; c < nblk; c += NST) {
+            step(std::integral_constant<int, 0>{}, c);
+            if (c + 1 < nblk) step(std::integral_constant<int, 1>{}, c + 1);
+        }
+    } else {
+        for (int c = 0; c < nblk; ++c) step(c & (NST - 1), c);
     }
+    dma_wait();                                          // no transfer is left when the workgroup's LDS goes to the next one
 
-    if (MODE == 0) {
-        // lanes (g, nn), g = 0..3, hold query nn's partial sums and maxima over disjoint keys
-        csum += __shfl_xor(csum, 16);
-        csum += __shfl_xor(csum, 32);
 #pragma unroll
-        for (int sft = 16; sft <= 32; sft <<= 1) {
-            const float ob = __shfl_xor(best, sft);
-            const int oa = __shfl_xor(arg, sft);
-            const bool take = (ob > best) || (ob == best && oa < arg);
-            best = take ? ob : best;
-            arg = take ? oa : arg;
+    for (int q = 0; q < NQ; ++q) {
+        const int iq = iw + 16 * q + nn;
+        const size_t row = (size_t)bh * n + min(iq, n - 1);
+        if (MODE == 0) {
+            // lanes (g, nn), g = 0..3, hold query nn's partial sums and maxima over disjoint keys
+            csum[q] += __shfl_xor(csum[q], 16);
+            csum[q] += __shfl_xor(csum[q], 32);
+#pragma unroll
+            for (int sft = 16; sft <= 32; sft <<= 1) {
+                const float ob = __shfl_xor(best[q], sft);
+                const int oa = __shfl_xor(arg[q], sft);
+                const bool take = (ob > best[q]) || (ob == best[q] && oa < arg[q]);
+                best[q] = take ? ob : best[q];
+                arg[q] = take ? oa : arg[q];
+            }
+            if (g == 0 && iq < n) {
+                Rv[row * YP + DD] = csum[q];
+                Rv[row * YP + DD + 1] = __int_as_float(arg[q]);
+            }
         }
-        if (g == 0 && iq < n) {
-            Rv[row * YP + DD] = csum;
-            Rv[row * YP + DD + 1] = __int_as_float(arg);
-        }
-    }
-    // acc[J]: lane (g, nn) reg r = sum for query i0 + 16 wave + 4g + r, feature 16J + nn
+        // acc[q][J]: lane (g, nn) reg r = sum for query iw + 16 q + 4g + r, feature 16J + nn
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 16 * wave + 4 * g + r;
-        if (i < n) {
-            const size_t ro = (size_t)bh * n + i;
+        for (int r = 0; r < 4; ++r) {
+            const int i = iw + 16 * q + 4 * g + r;
+            if (i < n) {
+                const size_t ro = (size_t)bh * n + i;
 #pragma unroll
-            for (int J = 0; J < NB; ++J) {
-                if (MODE == 0) Rv[ro * YP + 16 * J + nn] = acc[J][r];
-                else dQ[ro * DD + 16 * J + nn] = fmaf(scale, acc[J][r], Ug[ro * YP + 16 * J + nn]);
+                for (int J = 0; J < NB; ++J) {
+                    if (MODE == 0) Rv[ro * YP + 16 * J + nn] = acc[q][J][r];
+                    else dQ[ro * DD + 16 * J + nn] = fmaf(scale, acc[q][J][r], Ug[ro * YP + 16 * J + nn]);
+                }
             }
         }
     }
     if (MODE == 1) {
         __syncthreads();                                 // the fp32 rows have been read for the last time
-        if (iq < n) {
-            bf16_t *yr = reinterpret_cast<bf16_t *>(Yg + row * YP), *ur = reinterpret_cast<bf16_t *>(Ug + row * YP);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                *reinterpret_cast<bf16x8 *>(yr + 32 * f + 8 * g) = yhf[f];
-                *reinterpret_cast<bf16x8 *>(yr + DD + 32 * f + 8 * g) = ylf[f];
-                *reinterpret_cast<bf16x8 *>(ur + 32 * f + 8 * g) = uhf[f];
-                *reinterpret_cast<bf16x8 *>(ur + DD + 32 * f + 8 * g) = ulf[f];
+        for (int q = 0; q < NQ; ++q) {
+            const int iq = iw + 16 * q + nn;
+            const size_t row = (size_t)bh * n + iq;
+            if (iq < n) {
+                bf16_t *yr = reinterpret_cast<bf16_t *>(Yg + row * YP), *ur = reinterpret_cast<bf16_t *>(Ug + row * YP);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    *reinterpret_cast<bf16x8 *>(yr + 32 * f + 8 * g) = yhf[q][f];
+                    *reinterpret_cast<bf16x8 *>(yr + DD + 32 * f + 8 * g) = ylf[q][f];
+                    *reinterpret_cast<bf16x8 *>(ur + 32 * f + 8 * g) = uhf[q][f];
+                    *reinterpret_cast<bf16x8 *>(ur + DD + 32 * f + 8 * g) = ulf[q][f];
+                }
             }
         }
     }
 }
+
+constexpr long long TWO_QUERY_BLOCKS_FROM = 1536, TWO_KEY_BLOCKS_FROM = 768;
 
 template <int DD, int MODE>
 hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int first_row)
@@ -480,10 +675,19 @@ hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int fi
     float *U = reinterpret_cast<float *>(base + L.u);
     float *R = reinterpret_cast<float *>(base + L.r);
     float *Sc = reinterpret_cast<float *>(base + L.sc);
-    hipLaunchKernelGGL((bwd_rows_mfma_kernel<DD, MODE>), dim3(p.B * p.H, (p.n - first_row + 63) / 64), dim3(256), 0, p.stream,
-                       static_cast<const bf16_t *>(p.Q), static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V),
-                       static_cast<const bf16_t *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, first_row, L.npad, p.scale,
-                       p.lambda, p.lambda_rows, M, Y, U, R, Sc, p.dQ, p.dlambda);
+    auto launch = [&](auto kernel, int rows) {
+        hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (p.n - first_row + rows - 1) / rows), dim3(256), 0, p.stream,
+                           static_cast<const bf16_t *>(p.Q), static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V),
+                           static_cast<const bf16_t *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, first_row, L.npad, p.scale,
+                           p.lambda, p.lambda_rows, M, Y, U, R, Sc, p.dQ, p.dlambda);
+    };
+    if constexpr (DD == 64 && MODE == 0) {
+        if ((long long)p.B * p.H * ((p.n - first_row + 127) / 128) >= TWO_QUERY_BLOCKS_FROM) {
+            launch(bwd_rows_mfma_kernel<64, 0, 2>, 128);
+            return hipGetLastError();
+        }
+    }
+    launch(bwd_rows_mfma_kernel<DD, MODE, 1>, 64);
     return hipGetLastError();
 }
 
@@ -508,13 +712,13 @@ hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L)
     const float *Sc = reinterpret_cast<const float *>(base + L.sc);
     const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K),
                  *V = static_cast<const bf16_t *>(p.V), *G = static_cast<const bf16_t *>(p.dO);
-    dim3 grid(p.B * p.H, (p.n + 63) / 64);
-    if (p.d == 64)
-        hipLaunchKernelGGL((bwd_keys_mfma_kernel<64>), grid, dim3(256), 0, p.stream, Q, K, V, G, p.sq, p.sk, p.sv, p.sdo,
+    auto launch = [&](auto kernel, int keys) {
+        hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (p.n + keys - 1) / keys), dim3(256), 0, p.stream, Q, K, V, G, p.sq, p.sk, p.sv, p.sdo,
                            p.H, p.n, p.scale, Y, U, Sc, p.dK, p.dV);
-    else
-        hipLaunchKernelGGL((bwd_keys_mfma_kernel<128>), grid, dim3(256), 0, p.stream, Q, K, V, G, p.sq, p.sk, p.sv, p.sdo,
-                           p.H, p.n, p.scale, Y, U, Sc, p.dK, p.dV);
+    };
+    if (p.d != 64) launch(bwd_keys_mfma_kernel<128, 1>, 64);
+    else if ((long long)p.B * p.H * ((p.n + 127) / 128) >= TWO_KEY_BLOCKS_FROM) launch(bwd_keys_mfma_kernel<64, 2>, 128);
+    else launch(bwd_keys_mfma_kernel<64, 1>, 64);
     return hipGetLastError();
 }
 

@@ -377,6 +377,9 @@ __device__ inline void dma16_base_nt_off(const void *sbase, unsigned voff, unsig
 }
 #pragma clang diagnostic pop
 __device__ inline void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// all but this wave's N youngest transfers (and loads and stores) have landed
+template <int N>
+__device__ inline void dma_wait_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // index of tile (I, J), I <= J, among the upper-triangular 16x16 tiles of a matrix of NB 16-wide blocks (row by row)
 template <int NB>
