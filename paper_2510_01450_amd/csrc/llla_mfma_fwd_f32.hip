@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                                                             float *__restrict__ Yg, float *__restrict__ RUg, int causal, int nqb,
                                                             dual::DualArgs da, int out_bf16)
 {
-    // nqb: blocks of 16 query rows the sequence has; rows [0, da.nrows), a multiple of 16 or all, are the key-space workgroups',
+    // nqb: blocks of 16 query rows the sequence has; rows [0, da.nrows), a multiple of 16 or all, are the key-space workgroups' (four each),
     // which follow the others of their head
     using S = Shape<FD>;
     constexpr int NB = 4, QW = 4, QB = 16, YP = S::YP;
@@ -106,11 +106,11 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     if constexpr (!BWD) {
         const int own = nqb - (da.nrows + QB - 1) / QB;
         if (bm.blk >= own) {
-            static_assert(sizeof(dual::DualShared<FD>) <= sizeof(F32Shared), "a key-space row fits the workgroup's LDS");
-            auto &ds = *reinterpret_cast<dual::DualShared<FD> *>(&sm);
-            const int i = da.nrows - 1 - (bm.blk - own);
-            if (out_bf16) dual::dual_forward_row<FD, float, bf16_t>(ds, da, bh, i);
-            else dual::dual_forward_row<FD, float, float>(ds, da, bh, i);
+            static_assert(sizeof(dual::DualShared4) <= sizeof(F32Shared), "key-space rows fit the workgroup's LDS");
+            auto &ds = *reinterpret_cast<dual::DualShared4 *>(&sm);
+            const int top = da.nrows - 1 - 4 * (bm.blk - own);
+            if (out_bf16) dual::dual_forward_rows4<bf16_t>(ds, da, bh, top);
+            else dual::dual_forward_rows4<float>(ds, da, bh, top);
             return;
         }
     }
@@ -452,7 +452,7 @@ hipError_t mfma_forward_f32(const Problem &p)
     const int live = p.live_d > 0 ? (p.live_d + 15) / 16 : 4;      // a d = 16 / 32 call on zero-padded copies: 1 or 2
     const dual::DualArgs da = dual::dual_args(p);
     const int nqb = (p.n + S::QB - 1) / S::QB, obf = p.out == LLLA_BF16 ? 1 : 0;
-    const dim3 grid(nqb - (da.nrows + S::QB - 1) / S::QB + da.nrows, bh);
+    const dim3 grid(nqb - (da.nrows + S::QB - 1) / S::QB + (da.nrows + 3) / 4, bh);
     if (live == 1)
         hipLaunchKernelGGL(moments_f32_kernel<1>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
                            p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);

@@ -42,3 +42,22 @@ def test_not_causal(n):
     O = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), w.lam, w.scale, causal=False)
     ref = oracle.forward(Q, K, V, w.lam, w.scale, causal=False)
     check(O.cpu().numpy(), ref, np.full(n, n - 1), 64, w.tol, "not causal n=%d" % n)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 30, 61, 64, 70])
+def test_rows_at_d64_are_exact_to_the_rounding_of_the_result(n):
+    """Four rows per workgroup, one per wave, in fp64: what is left is the rounding of the stored fp32 values (2^-24 per element, and
+    the fp64 arithmetic's 2^-53 times a condition number of at most |k|^2 n / lambda = 5e5).  Keys of norm 8, a ridge per row,
+    strided inputs."""
+    d, B, H = 64, 2, 2
+    g = torch.Generator(device="cpu").manual_seed(7000 + n)
+    Q, K, V = [torch.randn((B, n, H, d), generator=g).transpose(1, 2) for _ in range(3)]
+    lam = 1e-2 * torch.exp(0.5 * torch.randn((B, H, n), generator=g))
+    O, rho, delta = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), lam.to(DEV), 1 / math.sqrt(d), return_stats=True)
+    ref = oracle.forward_ex(Q.contiguous(), K.contiguous(), V.contiguous(), lam, 1 / math.sqrt(d))
+    m = min(n, 64)
+    for x, r in zip((O, rho, delta[..., None]), (ref[0], ref[1], np.asarray(ref[2])[..., None])):
+        x, r = x.cpu().double().numpy()[:, :, :m], np.asarray(r, dtype=np.float64)[:, :, :m]
+        err = np.linalg.norm(x - r, axis=-1) / np.maximum(np.linalg.norm(r, axis=-1), 1e-300)
+        err[np.linalg.norm(r, axis=-1) == 0] = np.abs(x[np.linalg.norm(r, axis=-1) == 0]).max(initial=0.0)
+        assert err.max() < 1e-7, (n, err.max())
