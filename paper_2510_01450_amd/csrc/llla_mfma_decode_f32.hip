@@ -16,9 +16,11 @@
 // of eight chunks are its operands as they are; k and v are bf16 already, and w k is split into three (24 significant bits), three
 // products instead of eight fp32 ones of twice the cycles.
 //
-// What bounds it: 26 tiles of 16x16x4 per four keys at d = 64 are 832 matrix-core cycles for 2 KB of fp32 cache, 6 TB/s at 2.4 GHz,
-// i.e. the fp32 matrix cores and HBM meet (d = 16 / 32 in bf16: HBM); at d = 128 it is 100 tiles,
-// 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
+// fp32 caches at d = 64 do likewise (compute_roots): 26 tiles of 16x16x4 per four keys were 832 matrix-core cycles for 2 KB of cache, 6 TB/s
+// at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 312.
+//
+// What bounds it: HBM at d = 16 / 32; the loads' latency with one wave per SIMD at d = 64 in fp32 (4.7 TB/s at 256 heads x 8192); at d = 128
+// 100 tiles of 16x16x4 per four keys, 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
 // wave W owns row blocks W and 7 - W, 25 tiles whatever W; every wave loads the whole rows (the first-level cache serves three
 // of the four) and forms the weights for itself, so there is no exchange at all.
 #include "llla_decode_tail.hpp"
@@ -30,6 +32,12 @@ using namespace mfma;
 
 constexpr int NT = DEC_NT;
 constexpr float REF_SLACK = 8.f;        // the reference exponent moves when a logit exceeds it by more than 2^8 (weights stay <= 256)
+
+// fp32 caches at d = 64: sqrt(w) k and sqrt(w) v in three bf16 on 16-bit MFMA, one workgroup per compute unit (see compute_roots).  Two
+// workgroups on fp32 MFMA overlap one's merge and solve with the other's pass, which wins where there are many heads of few keys
+// (us, fp32 MFMA / roots: 256 heads x 512 42.8 / 28.1, x 1000 59.7 / 40.6; 512 x 128 29 / 35, x 512 56 / 54, x 1000 85 / 78; 384 x 300 43 / 53,
+// 320 x 777 78 / 82; 1024 x 512 100 / 105, x 1000 162 / 153, x 2048 290 / 257).
+inline bool roots_pay(int bh, int L) { return bh <= 256 || L >= 960; }
 
 template <int D>
 struct F32Shape : DecShape<D> {
@@ -116,12 +124,12 @@ struct F32Args {
 
 // The stream of one wave and what becomes of its moments.  W: the wave's share of the tiles (TEAM), else 0.
 // FUSED: one workgroup per head; it solves and writes the output itself.
-template <int D, typename TI, bool FUSED, int W, class Lds>
+template <int D, typename TI, bool FUSED, bool ROOTS, int W, class Lds>
 __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece &pc, Lds &lds, int wave, int lane)
 {
     using S = F32Shape<D>;
     constexpr bool SPLIT = sizeof(TI) == 2 && D <= 32;    // w k in three bf16 on 16-bit MFMA, eight chunks at a time
-    constexpr int NB = S::NB, NC = S::NC, NG = SPLIT ? 2 : S::NG, NR = S::NR, CH = NC * NG, STEP = 4 * CH;
+    constexpr int NB = S::NB, NC = S::NC, NG = SPLIT || ROOTS ? 2 : S::NG, NR = S::NR, CH = NC * NG, STEP = 4 * CH;
     constexpr int row[4] = {S::TEAM ? W : 0, S::TEAM ? 7 - W : 1, 2, 3};      // row blocks of this wave: row[0..NR-1]
     const int g = lane / 16, nn = lane % 16;
     // the piece is divided over the four waves (TEAM: walked by all four together); rows at and beyond L are never read
@@ -164,27 +172,26 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
 
     typedef RowFrag<TI, NB> Frag;
     struct Step { Frag k[CH], v[CH]; };
-    auto load = [&](Step &st, int s) {
+    auto load_rows = [&](Frag (&f)[CH], const char *base, int64_t pitch, unsigned off, int s) {
         const int j0 = r0 + (s < nsteps ? s : 0) * STEP;              // past the end: the first step again, never used
         if (j0 + STEP <= L) {
-            const char *kb = Kh + j0 * krow, *vb = Vh + j0 * vrow;
+            const char *p = base + j0 * pitch;
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                st.k[c] = load_frag<TI, NB, !S::TEAM>(kb + 4 * c * krow + koff);
-                st.v[c] = load_frag<TI, NB, !S::TEAM>(vb + 4 * c * vrow + voff);
-            }
+            for (int c = 0; c < CH; ++c) f[c] = load_frag<TI, NB, !S::TEAM>(p + 4 * c * pitch + off);
         } else {                                          // rows beyond the sequence: its last row (their weights are 0)
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int j = min(j0 + 4 * c + g, L - 1);
-                st.k[c] = load_frag<TI, NB, !S::TEAM>(Kh + j * krow + NB * nn * (int)sizeof(TI));
-                st.v[c] = load_frag<TI, NB, !S::TEAM>(Vh + j * vrow + NB * nn * (int)sizeof(TI));
-            }
+            for (int c = 0; c < CH; ++c) f[c] = load_frag<TI, NB, !S::TEAM>(base + min(j0 + 4 * c + g, L - 1) * pitch + NB * nn * (int)sizeof(TI));
         }
     };
-    auto compute_split = [&](const auto &st, int s) {
+    auto load = [&](Step &st, int s) {
+        load_rows(st.k, Kh, krow, koff, s);
+        load_rows(st.v, Vh, vrow, voff, s);
+    };
+    // logits of a step's 32 keys, the reference exponent, and half the exponents of the weights (ROOTS) or the exponents: e[grp] belongs to
+    // key 4 (n % 4) + g of group grp
+    auto step_exponents = [&](const auto &k, int s, float (&e)[2]) {
         const int j0 = r0 + s * STEP;
-        float t[2], w[2];
+        float t[2];
 #pragma unroll
         for (int grp = 0; grp < 2; ++grp) {
             float p[NC];
@@ -192,7 +199,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             for (int c = 0; c < NC; ++c) {
                 p[c] = 0.f;
 #pragma unroll
-                for (int i = 0; i < NB; ++i) p[c] = fmaf(q[i], frag_f32<TI, NB>(st.k[grp * NC + c], i), p[c]);
+                for (int i = 0; i < NB; ++i) p[c] = fmaf(q[i], frag_f32<TI, NB>(k[grp * NC + c], i), p[c]);
             }
             t[grp] = reduce_chunks<NC>(p, nn);                        // logit (log2 units) of key 4 (n % NC) + g of the group
             t[grp] = j0 + grp * 4 * NC + 4 * (nn & (NC - 1)) + g < r1 ? t[grp] : -INFINITY;
@@ -209,8 +216,14 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         }
         mtrue = fmaxf(mtrue, top);
 #pragma unroll
+        for (int grp = 0; grp < 2; ++grp) e[grp] = t[grp] - mref;
+    };
+    auto compute_split = [&](const auto &st, int s) {
+        float e[2], w[2];
+        step_exponents(st.k, s, e);
+#pragma unroll
         for (int grp = 0; grp < 2; ++grp) {
-            w[grp] = __builtin_amdgcn_exp2f(t[grp] - mref);           // exp2(-inf) = 0 masks the tail
+            w[grp] = __builtin_amdgcn_exp2f(e[grp]);                  // exp2(-inf) = 0 masks the tail
             om += w[grp];
         }
         const float wc[8] = {row_bcast<0>(w[0]), row_bcast<1>(w[0]), row_bcast<2>(w[0]), row_bcast<3>(w[0]),
@@ -244,6 +257,58 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             for (int J = I; J < NB; ++J) product(acc[upper_tile<NB>(I, J)], kb[J]);
 #pragma unroll
             for (int J = 0; J < NB; ++J) product(acc[S::NSIG + NB * I + J], vb[J]);
+        }
+    };
+    // sqrt(w) k and sqrt(w) v split into three bf16 each, six products per tile of the nine (the rest is below 2^-24), as in the moments
+    // kernel of the forward: 96 matrix-core cycles per tile and 32 keys instead of 256.  One wave per SIMD: with 256 registers 340 are
+    // spilled.  One set of registers for the rows: the next step's keys are requested as soon as these are converted, its values at the end.
+    // 64 heads x 4608 keys: pass 55.7 -> 40.0 us; 256 x 8192: 320 -> 226; 64 heads x 1024 to 8192: call 83.0 -> 64.2.  (Two sets of
+    // registers 66; conversions and products pinned to alternate 66, with two sets 69: part of the registers are then accumulation registers,
+    // read back one by one.)
+    auto compute_roots = [&](Step &st, int s) {
+        float e[2], rt[2];
+        step_exponents(st.k, s, e);
+#pragma unroll
+        for (int grp = 0; grp < 2; ++grp) {
+            rt[grp] = __builtin_amdgcn_exp2f(0.5f * e[grp]);          // exp2(-inf) = 0 masks the tail
+            om = fmaf(rt[grp], rt[grp], om);
+        }
+        const float rc[8] = {row_bcast<0>(rt[0]), row_bcast<1>(rt[0]), row_bcast<2>(rt[0]), row_bcast<3>(rt[0]),
+                             row_bcast<0>(rt[1]), row_bcast<1>(rt[1]), row_bcast<2>(rt[1]), row_bcast<3>(rt[1])};
+        struct Split3 { bf16x8 h, m, l; };
+        auto scaled = [&](const Frag (&f)[CH], int I, float &sum) {
+            float x[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                x[c] = rc[c] * frag_f32<TI, NB>(f[c], I);
+                sum = fmaf(rc[c], x[c], sum);
+            }
+            Split3 r;
+            split3_bf16(x, r.h, r.m, r.l);
+            return r;
+        };
+        auto product = [](f32x4 &t, const Split3 &a, const Split3 &b) {
+            t = mfma_bf16(a.l, b.h, t);
+            t = mfma_bf16(a.h, b.l, t);
+            t = mfma_bf16(a.m, b.m, t);
+            t = mfma_bf16(a.m, b.h, t);
+            t = mfma_bf16(a.h, b.m, t);
+            t = mfma_bf16(a.h, b.h, t);
+        };
+        Split3 z[NB];
+#pragma unroll
+        for (int J = 0; J < NB; ++J) {
+            z[J] = scaled(st.k, J, mu[J]);
+            if (J == NB - 1) load_rows(st.k, Kh, krow, koff, s + 1);
+#pragma unroll
+            for (int I = 0; I <= J; ++I) product(acc[upper_tile<NB>(I, J)], z[I], z[J]);
+        }
+#pragma unroll
+        for (int J = 0; J < NB; ++J) {
+            const Split3 v = scaled(st.v, J, yv[J]);
+            if (J == NB - 1) load_rows(st.v, Vh, vrow, voff, s + 1);
+#pragma unroll
+            for (int I = 0; I < NB; ++I) product(acc[S::NSIG + NB * I + J], z[I], v);
         }
     };
     auto compute_f32 = [&](const Step &st, int s) {
@@ -308,7 +373,14 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         if constexpr (SPLIT) compute_split(st, s);
         else compute_f32(st, s);
     };
-    if (nsteps > 0) {
+    if constexpr (ROOTS) {
+        if (nsteps > 0) {
+            Step st;
+            load(st, 0);
+#pragma unroll 1
+            for (int s = 0; s < nsteps; ++s) compute_roots(st, s);
+        }
+    } else if (nsteps > 0) {
         Step sa, sb;
         load(sa, 0);
         for (int s = 0; s < nsteps; s += 2) {
@@ -351,8 +423,8 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
 
 // Two waves per SIMD for the split form at d = 32: four leave 128 registers, 24 too few, and three are still slower (256 heads x 4096
 // keys: 53.9, 38.4 and 35.9 us with 1024, 768 and 512 workgroups; on fp32 MFMA 52.6; 512 x 16384: 254, 201, 191 and 303).
-template <int D, typename TI, bool FUSED>
-__global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : D == 128 && FUSED ? 1 : 2) void decode_f32_kernel(F32Args a)
+template <int D, typename TI, bool FUSED, bool ROOTS>
+__global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : ROOTS || (D == 128 && FUSED) ? 1 : 2) void decode_f32_kernel(F32Args a)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     using S = F32Shape<D>;
@@ -361,14 +433,14 @@ __global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : 
         __shared__ __align__(16) unsigned char raw[FUSED ? sizeof(HeadLds<D, 1, 1>) : 16];
         HeadLds<D, 1, 1> &lds = *reinterpret_cast<HeadLds<D, 1, 1> *>(raw);
         for_pieces<FUSED>(a.split, [&](const DecPiece &pc) {
-            if (wave == 0) decode_f32_body<D, TI, FUSED, 0>(a, pc, lds, wave, piece_lane());
-            else if (wave == 1) decode_f32_body<D, TI, FUSED, 1>(a, pc, lds, wave, piece_lane());
-            else if (wave == 2) decode_f32_body<D, TI, FUSED, 2>(a, pc, lds, wave, piece_lane());
-            else decode_f32_body<D, TI, FUSED, 3>(a, pc, lds, wave, piece_lane());
+            if (wave == 0) decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, wave, piece_lane());
+            else if (wave == 1) decode_f32_body<D, TI, FUSED, ROOTS, 1>(a, pc, lds, wave, piece_lane());
+            else if (wave == 2) decode_f32_body<D, TI, FUSED, ROOTS, 2>(a, pc, lds, wave, piece_lane());
+            else decode_f32_body<D, TI, FUSED, ROOTS, 3>(a, pc, lds, wave, piece_lane());
         });
     } else {
         __shared__ __align__(16) HeadLds<D, S::NBUF, 4> lds;
-        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, 0>(a, pc, lds, wave, piece_lane()); });
+        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, wave, piece_lane()); });
     }
 }
 
@@ -377,14 +449,14 @@ constexpr size_t MAX_RECORD_BYTES = (size_t)64 << 20;     // what llla_decode_st
 // Workgroups per head.  Rounds of the GPU's slots times the keys of a workgroup is the time of the pass; a further workgroup per
 // head only pays where it shortens that by more than its record costs (about KEYS_MIN / 4 keys' worth of time).
 template <int D>
-int f32_nsplit(int bh, int L, size_t ws_bytes)
+int f32_nsplit(int bh, int L, size_t ws_bytes, int slots = F32Shape<D>::SLOTS)
 {
     using S = F32Shape<D>;
     int best = 1;
     double best_cost = 1e300;
     for (int ns = 1; ns <= S::MAX_SPLIT; ++ns) {
         if (ns > 1 && ((L + ns - 1) / ns < S::KEYS_MIN || (size_t)bh * ns * S::REC_F * sizeof(float) > ws_bytes)) break;
-        const double rounds = (double)(((long long)bh * ns + S::SLOTS - 1) / S::SLOTS);
+        const double rounds = (double)(((long long)bh * ns + slots - 1) / slots);
         const double cost = rounds * ((double)L / ns + S::KEYS_MIN / 4) + (ns > 1 ? S::KEYS_MIN / 8 * ns : 0);
         if (cost < best_cost) { best_cost = cost; best = ns; }
     }
@@ -406,7 +478,7 @@ size_t f32_records(int B, int H, int L)
 template <int D>
 size_t f32_workspace(int B, int H, int L) { return round_up(f32_records<D>(B, H, L) * F32Shape<D>::REC_F * sizeof(float), 256); }
 
-template <int D, typename TI>
+template <int D, typename TI, bool ROOTS>
 hipError_t f32_launch(const Problem &p)
 {
     using S = F32Shape<D>;
@@ -417,20 +489,22 @@ hipError_t f32_launch(const Problem &p)
     // a caller without the scratch that the records need gets one workgroup per head
     const size_t records = f32_records<D>(p.B, p.H, p.n);
     const bool scratch = p.ws != nullptr && (reinterpret_cast<uintptr_t>(p.ws) & 255u) == 0 && p.ws_bytes >= records * S::REC_F * sizeof(float);
-    a.split = choose_split(p, scratch ? f32_nsplit<D>(bh, p.n, MAX_RECORD_BYTES) : 1, scratch ? records : 0, S::SLOTS, 4 * S::STEP,
-                           S::KEYS_MIN, S::MAX_SPLIT);
+    // (by roots a compute unit holds one workgroup; the records' room is that of the other types)
+    constexpr int slots = ROOTS ? 256 : S::SLOTS;
+    const int ns = scratch ? f32_nsplit<D>(bh, p.n, ROOTS ? records * S::REC_F * sizeof(float) : MAX_RECORD_BYTES, slots) : 1;
+    a.split = choose_split(p, ns, scratch ? records : 0, slots, ROOTS ? 128 : 4 * S::STEP, S::KEYS_MIN, S::MAX_SPLIT);
     a.out = HeadOut{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
     a.cscale = p.scale * LOG2E;
     a.parts = static_cast<float *>(p.ws);
     if (a.split.nsplit == 1 && a.split.slots == 0) {
         stage_mark(p.stream, "decode_f32");
-        hipLaunchKernelGGL((decode_f32_kernel<D, TI, true>), dim3(1, bh), dim3(NT), 0, p.stream, a);
+        hipLaunchKernelGGL((decode_f32_kernel<D, TI, true, ROOTS>), dim3(1, bh), dim3(NT), 0, p.stream, a);
         // without lengths every sequence is long; with them, those of at most 64 keys are served in key space
         const hipError_t e = hipGetLastError();
         return e != hipSuccess || p.seqlens == nullptr ? e : dual_decode(p);
     } else {
         stage_mark(p.stream, "decode_partial");
-        hipLaunchKernelGGL((decode_f32_kernel<D, TI, false>), a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT),
+        hipLaunchKernelGGL((decode_f32_kernel<D, TI, false, ROOTS>), a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT),
                            0, p.stream, a);
         stage_mark(p.stream, "decode_merge");
         if (p.seqlens == nullptr)
@@ -446,7 +520,10 @@ hipError_t f32_launch(const Problem &p)
 template <int D>
 hipError_t f32_by_dtype(const Problem &p)
 {
-    return p.in == LLLA_F32 ? f32_launch<D, float>(p) : f32_launch<D, bf16_t>(p);
+    if constexpr (D == 64) {
+        if (p.in == LLLA_F32 && roots_pay(p.B * p.H, p.n)) return f32_launch<D, float, true>(p);
+    }
+    return p.in == LLLA_F32 ? f32_launch<D, float, false>(p) : f32_launch<D, bf16_t, false>(p);
 }
 
 }  // namespace

@@ -102,3 +102,18 @@ def test_records_of_a_head(d):
         err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
         # (hardly more keys than features leave directions that the ridge alone holds: condition number 4 / 10^-2 instead of some tens)
         assert err.max() <= (64 if L >= 4 * d else 640) * 2.0 ** -24, "L=%d: %.2e" % (L, err.max())
+
+
+@pytest.mark.parametrize("L,BH", [(65, (2, 2)), (95, (2, 2)), (96, (2, 2)), (97, (2, 2)), (127, (1, 3)), (129, (1, 3)), (160, (3, 2)), (257, (2, 2)),
+                                  (511, (1, 2)), (1025, (1, 1)), (959, (33, 8)), (960, (33, 8)), (300, (32, 8)), (300, (33, 8))])
+def test_three_term_products_at_d64(L, BH):
+    """fp32 caches at d = 64: steps of 32 keys and their remainders, one workgroup per head and several, and both sides of the rule that
+    chooses between the three-term products and fp32 MFMA (256 heads; 960 keys).  Unit keys.  Bound: 24-bit operands and fp32 sums leave
+    some 2^-24 sqrt(L) of the moments, times the condition number of the system (about 4 from 4 d keys on: a tenth of the usual gate;
+    below, the usual gate)."""
+    B, H = BH
+    w, (q, Kc, Vc) = _case(B, H, L, 64, "f32", 2300 + L, values="l2")
+    nb = min(B, 3)
+    got = llla.llla_decode(q.to(DEV), Kc.to(DEV), Vc.to(DEV), w.lam, w.scale)[:nb].cpu().numpy()
+    ref = oracle.decode(q[:nb], Kc[:nb], Vc[:nb], w.lam, w.scale)
+    check(got[:, :, None], ref[:, :, None], np.array([L - 1]), 64, 1e-5 if L >= 256 else 1e-4, "L=%d heads %d" % (L, B * H))
