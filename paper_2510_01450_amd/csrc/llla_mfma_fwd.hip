@@ -13,7 +13,7 @@
 //   output  s_ij = w_ij (y0_i + k_j . y1_i), O = S V  (Eq. (lla) with y1 = -rho/delta,
 //           y0 = (1 + q.rho)/delta), a flash-style sweep.
 // The first 2d rows of every sequence, whose systems are the worst conditioned, take the "precise" variant of the
-// moments kernel (fp32 weights, the scaled operand as two f16 terms) and an fp32 output sweep on the vector ALU.
+// moments kernel (fp32 weights, the scaled operand as two f16 terms) and an output sweep with three-term operands.
 #include <type_traits>
 
 #include "llla_mfma_common.hpp"
@@ -99,7 +99,10 @@ constexpr int VT_PITCH = KB + 8;     // halves
 
 // LIVE < NB (a d = 16 / 32 call on zero-padded copies): features and value columns from 16 LIVE on are zero, so the
 // contractions over features stop after the chunks that hold live ones and only LIVE output tiles are formed and stored.
-template <bool MAXONLY, int DD, int LIVE = Shape<DD>::NB>
+// TERMS = 3 (the first rows, whose coefficients cancel to a few digits): y1 and the coefficients in three bf16 instead of two, i.e. fp32
+// accuracy, since q, k and v are bf16 already.  (On the vector ALU these rows took 26 of 480 us at 96 heads x 1000 rows and 18 at 64 x 4096,
+// all latency; 6 now.)
+template <bool MAXONLY, int DD, int LIVE = Shape<DD>::NB, int TERMS = 2>
 __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg,
                                                     llla_strides sq, llla_strides sk, int H, int n, int nkb,
                                                     int first_row, float cscale, const bf16_t *__restrict__ VT,
@@ -146,21 +149,27 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
     }
 
     float mrow = -INFINITY, y0 = 0.f;
-    bf16x8 yh[NF], yl[NF];
+    bf16x8 yh[NF], ym[NF], yl[NF];
     f32x4 oacc[NB];
     if (!MAXONLY) {
         mrow = Mg[(size_t)bh * (nkb * KB) + iqc];
         const float *yr = Yg ? Yg + ((size_t)bh * n + iqc) * YP : nullptr;
         y0 = yr ? yr[DD] : 1.f;
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
+        for (int f = 0; f < NF; ++f) {
+            float yv[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const float v = yr ? yr[32 * f + 8 * g + t] : 0.f;
-                const __bf16 hi = (__bf16)v;
-                yh[f][t] = hi;
-                yl[f][t] = (__bf16)(v - (float)hi);
+            for (int t = 0; t < 8; ++t) yv[t] = yr ? yr[32 * f + 8 * g + t] : 0.f;
+            if constexpr (TERMS == 3) split3_bf16(yv, yh[f], ym[f], yl[f]);
+            else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const __bf16 hi = (__bf16)yv[t];
+                    yh[f][t] = hi;
+                    yl[f][t] = (__bf16)(yv[t] - (float)hi);
+                }
             }
+        }
 #pragma unroll
         for (int J = 0; J < NB; ++J) oacc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -221,6 +230,10 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                 f32x4 u = {y0, y0, y0, y0};         // y0 + k . y1: the intercept rides in as the accumulator's initial value
 #pragma unroll
                 for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yl[f], u);
+                if constexpr (TERMS == 3) {
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], ym[f], u);
+                }
 #pragma unroll
                 for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yh[f], u);
                 ut[s] = u;
@@ -244,7 +257,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                     }
             }
         } else {
-            bf16x8 ch, cl;      // output weights as bf16 hi + lo; slot t<4: key 4g+t, t>=4: key 16+4g+t-4
+            bf16x8 ch, cm, cl;  // output weights as bf16 hi + lo; slot t<4: key 4g+t, t>=4: key 16+4g+t-4
             float cv[8];
 #pragma unroll
             for (int s = 0; s < 2; ++s)
@@ -263,14 +276,15 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                 for (int t = 0; t < 8; ++t) csum += cv[t];
             }
             // two values per conversion instruction (v_cvt_pk_bf16_f32)
-            typedef float float2v __attribute__((ext_vector_type(2)));
-            typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+            if constexpr (TERMS == 3) split3_bf16(cv, ch, cm, cl);
+            else {
 #pragma unroll
-            for (int t = 0; t < 8; t += 2) {
-                const bf16x2v hi = __builtin_convertvector(float2v{cv[t], cv[t + 1]}, bf16x2v);
-                const bf16x2v lo = __builtin_convertvector(float2v{cv[t] - (float)hi[0], cv[t + 1] - (float)hi[1]}, bf16x2v);
-                ch[t] = hi[0]; ch[t + 1] = hi[1];
-                cl[t] = lo[0]; cl[t + 1] = lo[1];
+                for (int t = 0; t < 8; t += 2) {
+                    const bf16x2v hi = __builtin_convertvector(float2v{cv[t], cv[t + 1]}, bf16x2v);
+                    const bf16x2v lo = __builtin_convertvector(float2v{cv[t] - (float)hi[0], cv[t + 1] - (float)hi[1]}, bf16x2v);
+                    ch[t] = hi[0]; ch[t + 1] = hi[1];
+                    cl[t] = lo[0]; cl[t + 1] = lo[1];
+                }
             }
 #pragma unroll
             for (int J = 0; J < NB; ++J) {
@@ -280,6 +294,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                 const uint4 pk = make_uint4(lo.x, lo.y, hi.x, hi.y);
                 vf = __builtin_bit_cast(bf16x8, pk);
                 oacc[J] = mfma_bf16(cl, vf, oacc[J]);
+                if constexpr (TERMS == 3) oacc[J] = mfma_bf16(cm, vf, oacc[J]);
                 oacc[J] = mfma_bf16(ch, vf, oacc[J]);
             }
         }
@@ -1073,12 +1088,11 @@ hipError_t forward_impl(const Problem &p)
     if (live == S::NB)
         hipLaunchKernelGGL((moments_kernel<DD>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
                            first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
-    // output: those rows are evaluated in fp32 on the vector ALUs (their weights y0 + k.y1 cancel
-    // to a few digits), the rest by the MFMA sweep
+    // output: those rows by the sweep with fp32 accuracy (their weights y0 + k.y1 cancel to a few digits), the rest by the plain one
     if (first > 0) {
         stage_mark(p.stream, "output_early_rows");
-        const hipError_t e = valu_forward_given(p, first, M, L.npad, Y, S::YP);
-        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((sweep_kernel<false, DD, S::NB, 3>), dim3(bh, (first + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
+                           p.n, L.nkb, 0, cscale, VT, M, Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0, (float *)nullptr, p.causal);
     }
     if (first < p.n) {
         const int nq64b = (p.n - first + 63) / 64;
