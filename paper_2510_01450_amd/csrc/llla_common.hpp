@@ -73,8 +73,8 @@ struct BackwardLayout {
 BackwardLayout mfma_backward_layout(int B, int H, int n, int d);
 hipError_t mfma_backward_rowmax(const BackwardProblem &p, const BackwardLayout &L);   // re-tiling and row maxima
 hipError_t mfma_backward_solve(const BackwardProblem &p, const BackwardLayout &L);    // moments, y and u of every row
-hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int first_row);   // r rows, argmax; rows >= first_row
-hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int first_row);  // dQ, dlambda, row scalars; rows >= first_row
+hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int early);   // r rows, argmax
+hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int early);  // dQ, dlambda, row scalars
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
 // the same for fp32 inputs (d = 64): sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
 // forward's, with the row maxima M given and the rows r replaced by u

@@ -372,15 +372,18 @@ __global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfm
 //   MODE 1 (after it):         dL/dlambda_i = -u1_i.y1_i, c_ij = p^_ij;  dQ_i = u1_i + scale sum_j c_ij k_j, and what the key
 //                              sweep reads: the row scalars (y0, u0, m in log2 units, correction, argmax) and, in the place of the
 //                              fp32 rows, y1 and -u1 as bf16 hi (DD halves) and lo.
-// Rows [first_row, n) only: the first rows of a sequence take fp32 sweeps (their coefficients cancel too strongly for
-// a 16-bit split).
+// Rows [first_row, n).  The first 2d rows of a sequence, a launch of their own, have the worst conditioned systems: u_i and the
+// coefficients are large and cancel (dQ_0 is exactly 0 as the difference of two large terms), and two terms are not enough there.  They
+// take TERMS = 3: y1, u1 and the coefficients in three bf16, i.e. fp32 accuracy, since q, k, v and dO are bf16 already.  (In fp32 on the
+// vector ALU the two modes took 23 + 29 us at 16 heads x 1000 rows, 25 + 33 at 64 x 4096; the calls went from 259 to 223 and from 4420 to 4342, errors of those
+// rows 0.7-1 times the former.)
 // The K and V tiles come by DMA into NST stages as in the key sweep, one barrier per block.  A block is so short (16 and 32 MFMAs) that the
 // transfers' latency shows where they are one block ahead: MODE 1 keeps three on their way (64 heads x 4096: through registers and two
 // barriers 493 us, one block ahead 480, three 434).  MODE 0, bound by its vector work, has two stages and the loop unrolled
 // over them (341 -> 307; three blocks ahead 319), and NQ = 2 blocks of 16 queries per wave from TWO_QUERY_BLOCKS_FROM workgroups of 128
 // rows on (328 -> 310; 64 x 2048 102 -> 106, 96 x 1000 47 -> 55).
-template <int DD, int MODE, int NQ>
-__global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
+template <int DD, int MODE, int NQ, int TERMS = 2>
+__global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
     int first_row, int mpitch, float scale, float lambda, const float *__restrict__ LamRows, const float *__restrict__ Mg,
@@ -402,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
     const float cscale = MODE == 0 ? fabsf(scale * LOG2E) : scale * LOG2E;
     const unsigned flip = MODE == 0 && scale < 0.f ? 0x80008000u : 0u;
 
-    bf16x8 qf[NQ][NF], gf[NQ][NF], yhf[NQ][NF], ylf[NQ][NF], uhf[NQ][NF], ulf[NQ][NF];
+    bf16x8 qf[NQ][NF], gf[NQ][NF], yhf[NQ][NF], ylf[NQ][NF], uhf[NQ][NF], ulf[NQ][NF], y3f[NQ][NF], u3f[NQ][NF];
     float mrow[NQ], near[NQ], y0[NQ], u0[NQ], corr[NQ];
     int jstar[NQ];
 #pragma unroll
@@ -439,8 +442,13 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
                     dl = fmaf(-u, yv[t], dl);
                     uv[t] = -u;
                 }
-                split_bf16(yv, yhf[q][f], ylf[q][f]);
-                split_bf16(uv, uhf[q][f], ulf[q][f]);
+                if constexpr (TERMS == 3) {
+                    split3_bf16(yv, yhf[q][f], ylf[q][f], y3f[q][f]);
+                    split3_bf16(uv, uhf[q][f], ulf[q][f], u3f[q][f]);
+                } else {
+                    split_bf16(yv, yhf[q][f], ylf[q][f]);
+                    split_bf16(uv, uhf[q][f], ulf[q][f]);
+                }
             }
             dl += __shfl_xor(dl, 16);
             dl += __shfl_xor(dl, 32);
@@ -527,6 +535,10 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     st[q] = mfma_bf16(kfr, qf[q][f], st[q]);
+                    if (MODE == 1 && TERMS == 3) {
+                        at[q] = mfma_bf16(kfr, y3f[q][f], at[q]);
+                        et[q] = mfma_bf16(kfr, u3f[q][f], et[q]);
+                    }
                     if (MODE == 1) {
                         at[q] = mfma_bf16(kfr, ylf[q][f], at[q]);
                         et[q] = mfma_bf16(kfr, ulf[q][f], et[q]);
@@ -579,18 +591,23 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
 #pragma unroll
                 for (int t = 0; t < 8; ++t) cv[q][t] = j0 + 16 * (t >> 2) + (t & 3) <= iw + 16 * q + nn ? cv[q][t] : 0.f;
         }
-        bf16x8 c_hi[NQ], c_lo[NQ];
+        bf16x8 c_hi[NQ], c_lo[NQ], c_3[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             if (MODE == 0) {
 #pragma unroll
                 for (int t = 0; t < 8; ++t) csum[q] += cv[q][t];
             }
-            split_bf16(cv[q], c_hi[q], c_lo[q]);
+            if constexpr (TERMS == 3) split3_bf16(cv[q], c_hi[q], c_lo[q], c_3[q]);
+            else split_bf16(cv[q], c_hi[q], c_lo[q]);
         }
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
             const bf16x8 kT = tr_frag(kt[buf], tr_addr[J], DD);
+            if constexpr (TERMS == 3) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) acc[q][J] = mfma_bf16(c_3[q], kT, acc[q][J]);
+            }
 #pragma unroll
             for (int q = 0; q < NQ; ++q) acc[q][J] = mfma_bf16(c_lo[q], kT, acc[q][J]);
 #pragma unroll
@@ -667,7 +684,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_mfma_kernel(
 constexpr long long TWO_QUERY_BLOCKS_FROM = 1536, TWO_KEY_BLOCKS_FROM = 768;
 
 template <int DD, int MODE>
-hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int first_row)
+hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int early)
 {
     char *base = static_cast<char *>(p.ws);
     const float *M = reinterpret_cast<const float *>(base + L.fwd + L.m);
@@ -675,33 +692,33 @@ hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int fi
     float *U = reinterpret_cast<float *>(base + L.u);
     float *R = reinterpret_cast<float *>(base + L.r);
     float *Sc = reinterpret_cast<float *>(base + L.sc);
-    auto launch = [&](auto kernel, int rows) {
-        hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (p.n - first_row + rows - 1) / rows), dim3(256), 0, p.stream,
+    auto launch = [&](auto kernel, int rows, int r0, int r1) {        // rows [r0, r1) in blocks of `rows`; r1 a multiple of 64 or n
+        hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (r1 - r0 + rows - 1) / rows), dim3(256), 0, p.stream,
                            static_cast<const bf16_t *>(p.Q), static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V),
-                           static_cast<const bf16_t *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, first_row, L.npad, p.scale,
+                           static_cast<const bf16_t *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, r0, L.npad, p.scale,
                            p.lambda, p.lambda_rows, M, Y, U, R, Sc, p.dQ, p.dlambda);
+        return hipGetLastError();
     };
+    const hipError_t e = launch(bwd_rows_mfma_kernel<DD, MODE, 1, 3>, 64, 0, early);
+    if (e != hipSuccess || early >= p.n) return e;
     if constexpr (DD == 64 && MODE == 0) {
-        if ((long long)p.B * p.H * ((p.n - first_row + 127) / 128) >= TWO_QUERY_BLOCKS_FROM) {
-            launch(bwd_rows_mfma_kernel<64, 0, 2>, 128);
-            return hipGetLastError();
-        }
+        if ((long long)p.B * p.H * ((p.n - early + 127) / 128) >= TWO_QUERY_BLOCKS_FROM)
+            return launch(bwd_rows_mfma_kernel<64, 0, 2>, 128, early, p.n);
     }
-    launch(bwd_rows_mfma_kernel<DD, MODE, 1>, 64);
-    return hipGetLastError();
+    return launch(bwd_rows_mfma_kernel<DD, MODE, 1>, 64, early, p.n);
 }
 
 }  // namespace
 
-// rows [first_row, n); first_row must be a multiple of 64
-hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int first_row)
+// early: the rows at the beginning that take three-term operands, a multiple of 64 or all
+hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int early)
 {
-    return p.d == 64 ? launch_rows<64, 0>(p, L, first_row) : launch_rows<128, 0>(p, L, first_row);
+    return p.d == 64 ? launch_rows<64, 0>(p, L, early) : launch_rows<128, 0>(p, L, early);
 }
 
-hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int first_row)
+hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int early)
 {
-    return p.d == 64 ? launch_rows<64, 1>(p, L, first_row) : launch_rows<128, 1>(p, L, first_row);
+    return p.d == 64 ? launch_rows<64, 1>(p, L, early) : launch_rows<128, 1>(p, L, early);
 }
 
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L)
