@@ -120,7 +120,9 @@ llla_status llla_forward_ex(const void *Q, const void *K, const void *V, void *O
     p.stream = static_cast<hipStream_t>(stream);
     llla::stage_begin(p.stream);
     if (!use_mfma) llla::stage_mark(p.stream, "valu_forward");
-    const hipError_t e = !use_mfma ? llla::valu_forward(p)
+    const bool by_row = path == LLLA_PATH_AUTO && !use_mfma && llla::short_forward_takes(B * H, n, d, in);
+    const hipError_t e = by_row    ? llla::short_forward(p)
+                         : !use_mfma ? llla::valu_forward(p)
                          : padded  ? llla::padded_forward(p)
                          : f32_mfma ? llla::mfma_forward_f32(p) : llla::mfma_forward(p);
     llla::stage_end(p.stream);

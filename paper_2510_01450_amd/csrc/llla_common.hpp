@@ -47,6 +47,9 @@ struct BackwardProblem {
 hipError_t valu_forward(const Problem &p);
 // sweep 3 only, for query rows [0, nrows): y (pitch ypitch floats: y1 then y0) and the row maxima (log2
 // units) come from device memory
+// fp32 inputs, d = 16 / 32, short sequences: one wave per row (llla_short.hip)
+bool short_forward_takes(int heads, int n, int d, llla_dtype in);
+hipError_t short_forward(const Problem &p);
 hipError_t valu_forward_given(const Problem &p, int nrows, const float *M, int mpitch, const float *Y, int ypitch);
 hipError_t valu_decode(const Problem &p);
 

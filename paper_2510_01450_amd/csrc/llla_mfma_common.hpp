@@ -397,7 +397,7 @@ __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I *
 // inverse diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on
 // the vector ALU.
 // LOW: low as in eliminate16, over all pivots.
-template <int NB, bool LOW = false>
+template <int NB, bool LOW = false, bool DROP = false>
 __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor, float *low = nullptr)
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -417,7 +417,7 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 #pragma unroll
         for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
         wave_sync();
-        eliminate16<LOW, false>(a, nl, ndinv, nn, pivot_floor, low);
+        eliminate16<LOW, DROP>(a, nl, ndinv, nn, pivot_floor, low);
         // N_P replaces the consumed diagonal tile; U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
         const f32x4 ui = invert16_quarter(nl, ndinv, nn, g);
         acc[upper_tile<NB>(P, P)] = ui;

@@ -144,16 +144,16 @@ __device__ __forceinline__ void substitute_back(const f32x4 (&acc)[NB * (NB + 1)
 
 //   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I), accumulator layout (destroyed)
 //        load_rhs(P, m, q, e)  element 16P + n (n = the lane's position in its row) of -mu~, -q and, WITH_U, -r1
-//        omega; scw: >= 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor as in eliminate16
+//        omega; scw: >= 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor, DROP as in eliminate16
 //        WITH_U: r0
 //   out: rhs[P] register t = y1[16P + 4g + t] (every lane; WITH_U: lanes n == 1 hold u1 instead), y0, u0
 // with [omega mu~^T; mu~ Sigma~ + lambda I] [y0; y1] = [1; q] and, WITH_U, the same matrix times [u0; u1] = [r0; r1].
-template <int NB, bool WITH_U = false, class LoadRhs>
+template <int NB, bool WITH_U = false, bool DROP = false, class LoadRhs>
 __device__ __forceinline__ void solve_one(f32x4 (&acc)[NB * (NB + 1) / 2], f32x4 (&rhs)[NB], float &y0, float omega, float *scw,
                                           int g, int nn, float pivot_floor, LoadRhs load_rhs, float r0 = 0.f, float *u0_out = nullptr)
 {
     constexpr int NS = WITH_U ? 3 : 2;
-    factorise_one<NB>(acc, scw, g, nn, pivot_floor);
+    factorise_one<NB, false, DROP>(acc, scw, g, nn, pivot_floor);
     float tv[NS][NB];
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
