@@ -132,6 +132,13 @@ __device__ inline void split3_bf16(const float (&x)[8], bf16x8 &h, bf16x8 &m, bf
     }
 }
 
+// 2 x for finite x of at least 2^-126 in absolute value, by the exponent field (a smaller x becomes x +- 2^-126; infinities are not kept)
+__device__ inline bf16x8 twice_bf16(bf16x8 x)
+{
+    typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, (u16x8)(__builtin_bit_cast(u16x8, x) + (unsigned short)0x80));
+}
+
 __device__ inline f32x4 mfma_f16(half8 a, half8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 __device__ inline f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 

@@ -301,7 +301,14 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             z[J] = scaled(st.k, J, mu[J]);
             if (J == NB - 1) load_rows(st.k, Kh, krow, koff, s + 1);
 #pragma unroll
-            for (int I = 0; I <= J; ++I) product(acc[upper_tile<NB>(I, J)], z[I], z[J]);
+            for (int I = 0; I < J; ++I) product(acc[upper_tile<NB>(I, J)], z[I], z[J]);
+            // diagonal: h^T m and m^T h are each other's transposes, and the solve takes (T + T^T) / 2
+            f32x4 &t = acc[upper_tile<NB>(J, J)];
+            const bf16x8 h2 = twice_bf16(z[J].h);
+            t = mfma_bf16(h2, z[J].l, t);
+            t = mfma_bf16(z[J].m, z[J].m, t);
+            t = mfma_bf16(h2, z[J].m, t);
+            t = mfma_bf16(z[J].h, z[J].h, t);
         }
 #pragma unroll
         for (int J = 0; J < NB; ++J) {

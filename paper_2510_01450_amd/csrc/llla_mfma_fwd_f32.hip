@@ -288,9 +288,10 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                 for (int I = 0; I < LIVE; ++I) {
                     if (I + 1 < LIVE) make_z(q, I + 1);
                     else if (q + 1 < QW) make_z(q + 1, 0);
-                    // six products of the nine: what is left out is below 2^-24 of the result
+                    // six products of the nine: what is left out is below 2^-24 of the result.  In a diagonal tile h^T m and m^T h (and
+                    // h^T l and l^T h) are each other's transposes: (2 h)^T m and (2 h)^T l serve, and the solve's (T + T^T) / 2 does the rest.
 #pragma unroll
-                    for (int J = 0; J <= I; ++J) {
+                    for (int J = 0; J < I; ++J) {
                         f32x4 &t = acc[q][S::tix(J, I)];
                         t = mfma_bf16(zl[q][J], zh[q][I], t);
                         t = mfma_bf16(zh[q][J], zl[q][I], t);
@@ -299,11 +300,19 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                         t = mfma_bf16(zh[q][J], zm[q][I], t);
                         t = mfma_bf16(zh[q][J], zh[q][I], t);
                     }
+                    {
+                        f32x4 &t = acc[q][S::tix(I, I)];
+                        const bf16x8 h2 = twice_bf16(zh[q][I]);
+                        t = mfma_bf16(h2, zl[q][I], t);
+                        t = mfma_bf16(zm[q][I], zm[q][I], t);
+                        t = mfma_bf16(h2, zm[q][I], t);
+                        t = mfma_bf16(zh[q][I], zh[q][I], t);
+                    }
                     __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-                    if (I == 0) alternate<6, 8>();
-                    else if (I == 1) alternate<12, 4>();
-                    else if (I == 2) alternate<18, 3>();
-                    else alternate<24, 2>();
+                    if (I == 0) alternate<4, 11>();
+                    else if (I == 1) alternate<10, 5>();
+                    else if (I == 2) alternate<16, 3>();
+                    else alternate<22, 2>();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             // mu~: fp32, four keys per MFMA, the weights of all 16 queries against this wave's feature block
