@@ -45,11 +45,11 @@ struct BackwardProblem {
 
 // Launchers return hipSuccess or the launch error.  Each lives in its own translation unit.
 hipError_t valu_forward(const Problem &p);
-// sweep 3 only, for query rows [0, nrows): y (pitch ypitch floats: y1 then y0) and the row maxima (log2
-// units) come from device memory
 // fp32 inputs, d = 16 / 32, short sequences: one wave per row (llla_short.hip)
 bool short_forward_takes(int heads, int n, int d, llla_dtype in);
 hipError_t short_forward(const Problem &p);
+// sweep 3 only, for query rows [0, nrows): y (pitch ypitch floats: y1 then y0) and the row maxima (log2
+// units) come from device memory
 hipError_t valu_forward_given(const Problem &p, int nrows, const float *M, int mpitch, const float *Y, int ypitch);
 hipError_t valu_decode(const Problem &p);
 
@@ -78,6 +78,8 @@ hipError_t mfma_backward_rowmax(const BackwardProblem &p, const BackwardLayout &
 hipError_t mfma_backward_solve(const BackwardProblem &p, const BackwardLayout &L);    // moments, y and u of every row
 hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int early);   // r rows, argmax
 hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int early);  // dQ, dlambda, row scalars
+// rows [r0, r1) of the output of a bf16 forward from the row maxima (log2 units) and the solved rows (llla_mfma_bwd.hip)
+hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int r0, int r1, bool three_terms);
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
 // the same for fp32 inputs (d = 64): sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
 // forward's, with the row maxima M given and the rows r replaced by u

@@ -681,6 +681,145 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
     }
 }
 
+// ---- output sweep of the forward ---------------------------------------------------------------------------------
+// O_i = sum_j w_ij (y0_i + k_j . y1_i) v_j for the rows [first_row, n): the row sweeps' loop with other products, 20 MFMAs and some 50
+// vector instructions per wave, block of 32 keys and 16 queries at d = 64, which hardly overlap.  What bounded sweep_kernel beyond
+// that was the staging through registers with two barriers per block; here the tiles come by DMA one block ahead, one barrier per
+// block, and V is read transposed from its natural tile, so no V^T is made either.  us a call: 64 heads x 4096 at d = 64 2822 -> 2771, 96 x 1000
+// with statistics 456 -> 438, 16 x 8192 at d = 128 10003 -> 9721.  (Three blocks ahead 2779, 441, 9747; two blocks of 16 queries per
+// wave 2758, 443.)
+// TERMS = 3 (the first rows, whose coefficients cancel to a few digits): y1 and the coefficients in three bf16, as in the sweeps above.
+template <int DD, int TERMS = 2>
+__global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
+    const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg, llla_strides sq, llla_strides sk,
+    llla_strides sv, int H, int n, int first_row, int mpitch, float cscale, const float *__restrict__ Mg, const float *__restrict__ Yg,
+    void *__restrict__ Og, llla_strides so, int out_bf16, int causal)
+{
+    using S = Shape<DD>;
+    constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
+    constexpr int CH = DD / 8, TILE = KB * DD, RPT = 64 / CH, NTR = KB / RPT / 4;     // as in the key sweep
+    constexpr int NST = 2;                               // blocks in LDS: the one in use and the next, on its way
+    __shared__ __align__(16) bf16_t kt[NST][TILE], vt[NST][TILE];
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
+    const int bh = blockIdx.x, b = bh / H, h = bh % H;
+    const int i0 = first_row + ((int)gridDim.y - 1 - (int)blockIdx.y) * 64, iw = i0 + 16 * wave;   // first row of the workgroup, of the wave
+    const char *Kh = reinterpret_cast<const char *>(Kg + b * sk.batch + h * sk.head);
+    const char *Vh = reinterpret_cast<const char *>(Vg + b * sv.batch + h * sv.head);
+
+    const int iq = iw + nn, iqc = min(iq, n - 1), last = causal ? iq : n - 1;         // this lane's query, the last key it sees
+    const bf16_t *qrow = Qg + b * sq.batch + h * sq.head + (int64_t)iqc * sq.seq;
+    const float *yr = Yg + ((size_t)bh * n + iqc) * YP;
+    const float mrow = Mg[(size_t)bh * mpitch + iqc], y0 = yr[DD];                   // (mrow in log2 units)
+    bf16x8 qf[NF], yh[NF], ym[NF], yl[NF];
+    f32x4 acc[NB];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        qf[f] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * f + 8 * g);
+        float yv[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) yv[t] = yr[32 * f + 8 * g + t];
+        if constexpr (TERMS == 3) split3_bf16(yv, yh[f], ym[f], yl[f]);
+        else split_bf16(yv, yh[f], yl[f]);
+    }
+#pragma unroll
+    for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int row_addr[NF], tr_addr[NB];                       // operand reads: rows (+ 16 s DD), columns
+#pragma unroll
+    for (int f = 0; f < NF; ++f) row_addr[f] = nn * DD + (((g + 4 * f) ^ row_swizzle<DD>(nn)) * 8);
+    {
+        const int r = 4 * g + (nn >> 2);
+#pragma unroll
+        for (int J = 0; J < NB; ++J) tr_addr[J] = r * DD + (((2 * J + ((nn & 3) >> 1)) ^ row_swizzle<DD>(r)) * 8) + (nn & 1) * 4;
+    }
+    // as in the row sweeps of the backward; keys past the end repeat the last one and are masked
+    unsigned k_off[NTR], v_off[NTR];
+    const int n_whole = sk.seq < (int64_t(1) << 24) && sv.seq < (int64_t(1) << 24) ? n : 0;
+#pragma unroll
+    for (int t = 0; t < NTR; ++t) {
+        const int r = RPT * (NTR * wave + t) + lane / CH, col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+        k_off[t] = 2u * (unsigned)(r * (int)sk.seq) + col;
+        v_off[t] = 2u * (unsigned)(r * (int)sv.seq) + col;
+    }
+    const unsigned kt_lds = lds_offset(&kt[0][0]), vt_lds = lds_offset(&vt[0][0]);
+    auto issue = [&](int buf, int c) {
+        const bool whole = c * KB + KB <= n_whole;
+        const char *kb = Kh + (int64_t)(c * KB) * sk.seq * 2, *vb = Vh + (int64_t)(c * KB) * sv.seq * 2;
+#pragma unroll
+        for (int t = 0; t < NTR; ++t) {
+            const int r0 = RPT * (NTR * wave + t);
+            if (whole) {
+                dma16_base_off(kb, k_off[t], kt_lds + 2u * (unsigned)(buf * TILE + r0 * DD));
+                dma16_base_off(vb, v_off[t], vt_lds + 2u * (unsigned)(buf * TILE + r0 * DD));
+            } else {
+                const int r = r0 + lane / CH;
+                const int64_t j = min(c * KB + r, n - 1);
+                const int col = ((lane % CH) ^ row_swizzle<DD>(r)) * 16;
+                dma16(Kh + j * sk.seq * 2 + col, &kt[buf][r0 * DD]);
+                dma16(Vh + j * sv.seq * 2 + col, &vt[buf][r0 * DD]);
+            }
+        }
+    };
+
+    const int nblk = (causal ? min(i0 + 63, n - 1) : n - 1) / KB + 1;
+    auto step = [&](auto buf, int c) {
+        dma_wait();
+        __syncthreads();                                 // this block has arrived, the previous one is consumed
+        if (c + 1 < nblk) issue(buf ^ 1, c + 1);
+        if (causal && c * KB > iw + 15) return;          // every key of the block lies behind the wave's last row
+        float cv[8];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            f32x4 st = {0.f, 0.f, 0.f, 0.f}, ut = {y0, y0, y0, y0};
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const bf16x8 kfr = *reinterpret_cast<const bf16x8 *>(&kt[buf][row_addr[f] + 16 * s * DD]);
+                st = mfma_bf16(kfr, qf[f], st);
+                ut = mfma_bf16(kfr, yl[f], ut);
+                if constexpr (TERMS == 3) ut = mfma_bf16(kfr, ym[f], ut);
+                ut = mfma_bf16(kfr, yh[f], ut);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) cv[4 * s + r] = __builtin_amdgcn_exp2f(fmaf(st[r], cscale, -mrow)) * ut[r];
+        }
+        // lane (g, nn): cv[4s + r] belongs to key 32c + 16s + 4g + r and query iw + nn
+        if (causal ? c * KB + KB - 1 > iw : c * KB + KB > n) {
+            const int j0 = c * KB + 4 * g;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) cv[t] = j0 + 16 * (t >> 2) + (t & 3) <= last ? cv[t] : 0.f;
+        }
+        bf16x8 ch, cm, cl;
+        if constexpr (TERMS == 3) split3_bf16(cv, ch, cm, cl);
+        else split_bf16(cv, ch, cl);
+#pragma unroll
+        for (int J = 0; J < NB; ++J) {
+            const bf16x8 vT = tr_frag(vt[buf], tr_addr[J], DD);
+            acc[J] = mfma_bf16(cl, vT, acc[J]);
+            if constexpr (TERMS == 3) acc[J] = mfma_bf16(cm, vT, acc[J]);
+            acc[J] = mfma_bf16(ch, vT, acc[J]);
+        }
+    };
+    issue(0, 0);
+    for (int c = 0; c < nblk; c += 2) {
+        step(std::integral_constant<int, 0>{}, c);
+        if (c + 1 < nblk) step(std::integral_constant<int, 1>{}, c + 1);
+    }
+
+    // acc[J]: lane (g, nn) reg r = O[query iw + 4g + r][feature 16J + nn]
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = iw + 4 * g + r;
+        if (i < n) {
+            const int64_t off = b * so.batch + h * so.head + (int64_t)i * so.seq;
+#pragma unroll
+            for (int J = 0; J < NB; ++J) {
+                if (out_bf16) ((bf16_t *)Og)[off + 16 * J + nn] = f32_to_bf16(acc[J][r]);
+                else ((float *)Og)[off + 16 * J + nn] = acc[J][r];
+            }
+        }
+    }
+}
+
 constexpr long long TWO_QUERY_BLOCKS_FROM = 1536, TWO_KEY_BLOCKS_FROM = 768;
 
 template <int DD, int MODE>
@@ -736,6 +875,19 @@ hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L)
     if (p.d != 64) launch(bwd_keys_mfma_kernel<128, 1>, 64);
     else if ((long long)p.B * p.H * ((p.n + 127) / 128) >= TWO_KEY_BLOCKS_FROM) launch(bwd_keys_mfma_kernel<64, 2>, 128);
     else launch(bwd_keys_mfma_kernel<64, 1>, 64);
+    return hipGetLastError();
+}
+
+// rows [r0, r1) of the output of a bf16 forward, r0 a multiple of 64, r1 too or all; the first rows, whose coefficients cancel, with three-term operands
+hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int r0, int r1, bool three_terms)
+{
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (r1 - r0 + 63) / 64), dim3(256), 0, p.stream, static_cast<const bf16_t *>(p.Q),
+                           static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V), p.sq, p.sk, p.sv, p.H, p.n, r0, mpitch,
+                           p.scale * LOG2E, M, Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0, p.causal);
+    };
+    if (p.d == 64) three_terms ? launch(out_rows_kernel<64, 3>) : launch(out_rows_kernel<64>);
+    else three_terms ? launch(out_rows_kernel<128, 3>) : launch(out_rows_kernel<128>);
     return hipGetLastError();
 }
 

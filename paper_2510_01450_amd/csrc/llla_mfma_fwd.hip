@@ -47,7 +47,7 @@ Layout make_layout(int B, int H, int n)
 }
 
 // ------------------------------------------------------------------------------------------------
-// prep: re-tile K (-> f16) and V (bf16) as [bh][key block][feature][32 keys]
+// prep: re-tile K (-> f16) and, where a sweep reads it (VT != nullptr), V (bf16) as [bh][key block][feature][32 keys]
 template <int DD>
 __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
                                                    llla_strides sk, llla_strides sv, int H, int n, int nkb,
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg
         uint4 kv = make_uint4(0, 0, 0, 0), vv = kv;
         if (j < n) {
             kv = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
-            vv = *reinterpret_cast<const uint4 *>(Vh + (int64_t)j * sv.seq + ch);
+            if (VT) vv = *reinterpret_cast<const uint4 *>(Vh + (int64_t)j * sv.seq + ch);
         }
         const uint32_t ku[4] = {kv.x, kv.y, kv.z, kv.w}, vu[4] = {vv.x, vv.y, vv.z, vv.w};
 #pragma unroll
@@ -86,8 +86,8 @@ __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg
         }
         const size_t base = ((size_t)bh * nkb + blk) * (DD * KB) + feat * KB + k0;
         *reinterpret_cast<half8 *>(KT + base) = ko;
-        *reinterpret_cast<uint4 *>(VT + base) = make_uint4(vo[0] | (vo[1] << 16), vo[2] | (vo[3] << 16),
-                                                           vo[4] | (vo[5] << 16), vo[6] | (vo[7] << 16));
+        if (VT) *reinterpret_cast<uint4 *>(VT + base) = make_uint4(vo[0] | (vo[1] << 16), vo[2] | (vo[3] << 16),
+                                                                   vo[4] | (vo[5] << 16), vo[6] | (vo[7] << 16));
     }
 }
 
@@ -1058,12 +1058,13 @@ hipError_t forward_impl(const Problem &p)
 
     const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K),
                  *V = static_cast<const bf16_t *>(p.V);
-    stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, VT);
-    const int nq64 = (p.n + 63) / 64;
-    stage_mark(p.stream, "rowmax");
     // a call at d = 16 / 32 on zero-padded copies (live_d features can be non-zero): the variants that skip padded tiles
     const int live = (DD == 64 && p.live_d > 0) ? (p.live_d + 15) / 16 : S::NB;
+    stage_mark(p.stream, "prep");
+    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT,
+                       live == S::NB ? (bf16_t *)nullptr : VT);
+    const int nq64 = (p.n + 63) / 64;
+    stage_mark(p.stream, "rowmax");
     if constexpr (DD == 64) {
         if (live == 1)
             hipLaunchKernelGGL((sweep_kernel<true, DD, 1>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
@@ -1089,26 +1090,25 @@ hipError_t forward_impl(const Problem &p)
         hipLaunchKernelGGL((moments_kernel<DD>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
                            first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
     // output: those rows by the sweep with fp32 accuracy (their weights y0 + k.y1 cancel to a few digits), the rest by the plain one
+    auto output = [&](int r0, int r1, bool early) {
+        const dim3 grid(bh, (r1 - r0 + 63) / 64);
+        const int obf = p.out == LLLA_BF16 ? 1 : 0;
+        if (live == S::NB) return mfma_output_rows(p, M, L.npad, Y, r0, r1, early);
+        if constexpr (DD == 64) {
+            auto kernel = early ? sweep_kernel<false, 64, 4, 3> : live == 1 ? sweep_kernel<false, 64, 1> : sweep_kernel<false, 64, 2>;
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb, r0, cscale, VT, M, (const float *)Y,
+                               p.O, p.so, obf, (float *)nullptr, p.causal);
+        }
+        return hipGetLastError();
+    };
     if (first > 0) {
         stage_mark(p.stream, "output_early_rows");
-        hipLaunchKernelGGL((sweep_kernel<false, DD, S::NB, 3>), dim3(bh, (first + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
-                           p.n, L.nkb, 0, cscale, VT, M, Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0, (float *)nullptr, p.causal);
+        const hipError_t e = output(0, first, true);
+        if (e != hipSuccess) return e;
     }
     if (first < p.n) {
-        const int nq64b = (p.n - first + 63) / 64;
         stage_mark(p.stream, "output");
-        const int obf = p.out == LLLA_BF16 ? 1 : 0;
-        if constexpr (DD == 64) {
-            if (live == 1)
-                hipLaunchKernelGGL((sweep_kernel<false, DD, 1>), dim3(bh, nq64b), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
-                                   p.n, L.nkb, first, cscale, VT, M, Y, p.O, p.so, obf, (float *)nullptr, p.causal);
-            else if (live == 2)
-                hipLaunchKernelGGL((sweep_kernel<false, DD, 2>), dim3(bh, nq64b), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
-                                   p.n, L.nkb, first, cscale, VT, M, Y, p.O, p.so, obf, (float *)nullptr, p.causal);
-        }
-        if (live == S::NB)
-            hipLaunchKernelGGL((sweep_kernel<false, DD>), dim3(bh, nq64b), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
-                               L.nkb, first, cscale, VT, M, Y, p.O, p.so, obf, (float *)nullptr, p.causal);
+        return output(first, p.n, false);
     }
     return hipGetLastError();
 }
@@ -1318,7 +1318,7 @@ hipError_t backward_rowmax_impl(const BackwardProblem &p, const BackwardLayout &
     const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K),
                  *V = static_cast<const bf16_t *>(p.V);
     stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, VT);
+    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, (bf16_t *)nullptr);
     stage_mark(p.stream, "rowmax");
     hipLaunchKernelGGL((sweep_kernel<true, DD>), dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
                        p.n, L.nkb, 0, p.scale * LOG2E, VT, M, Y, (void *)nullptr, llla_strides{0, 0, 0}, 0, (float *)nullptr);
