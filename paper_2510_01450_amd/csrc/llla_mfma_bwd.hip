@@ -688,15 +688,17 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
 // block, and V is read transposed from its natural tile, so no V^T is made either.  us a call: 64 heads x 4096 at d = 64 2822 -> 2771, 96 x 1000
 // with statistics 456 -> 438, 16 x 8192 at d = 128 10003 -> 9721.  (Three blocks ahead 2779, 441, 9747; two blocks of 16 queries per
 // wave 2758, 443.)
+// LIVE < NB (a d = 16 / 32 call on zero-padded copies): features and value columns from 16 LIVE on are zero and left out.
+// (us a call: 64 heads x 4096 at d = 32 1422 -> 1378, d = 16 1079 -> 1039, 32 x 300 at d = 32 53.9 -> 50.5.)
 // TERMS = 3 (the first rows, whose coefficients cancel to a few digits): y1 and the coefficients in three bf16, as in the sweeps above.
-template <int DD, int TERMS = 2>
+template <int DD, int LIVE = Shape<DD>::NB, int TERMS = 2>
 __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg, llla_strides sq, llla_strides sk,
     llla_strides sv, int H, int n, int first_row, int mpitch, float cscale, const float *__restrict__ Mg, const float *__restrict__ Yg,
     void *__restrict__ Og, llla_strides so, int out_bf16, int causal)
 {
     using S = Shape<DD>;
-    constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
+    constexpr int NF = (16 * LIVE + 31) / 32, NB = LIVE, YP = S::YP;      // feature chunks of 32 and output tiles that are live
     constexpr int CH = DD / 8, TILE = KB * DD, RPT = 64 / CH, NTR = KB / RPT / 4;     // as in the key sweep
     constexpr int NST = 2;                               // blocks in LDS: the one in use and the next, on its way
     __shared__ __align__(16) bf16_t kt[NST][TILE], vt[NST][TILE];
@@ -886,8 +888,11 @@ hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const 
                            static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V), p.sq, p.sk, p.sv, p.H, p.n, r0, mpitch,
                            p.scale * LOG2E, M, Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0, p.causal);
     };
-    if (p.d == 64) three_terms ? launch(out_rows_kernel<64, 3>) : launch(out_rows_kernel<64>);
-    else three_terms ? launch(out_rows_kernel<128, 3>) : launch(out_rows_kernel<128>);
+    const int live = p.d == 64 && p.live_d > 0 ? (p.live_d + 15) / 16 : p.d / 16;
+    if (live == 1) three_terms ? launch(out_rows_kernel<64, 1, 3>) : launch(out_rows_kernel<64, 1>);
+    else if (live == 2) three_terms ? launch(out_rows_kernel<64, 2, 3>) : launch(out_rows_kernel<64, 2>);
+    else if (p.d == 64) three_terms ? launch(out_rows_kernel<64, 4, 3>) : launch(out_rows_kernel<64>);
+    else three_terms ? launch(out_rows_kernel<128, 8, 3>) : launch(out_rows_kernel<128>);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 // Matrix-core (MFMA) forward path of Local Linear Attention for gfx950: bf16 inputs, d = 64 or 128.
 //
 // Stages (all on the caller's stream, workspace holds only Theta(B*H*n*d) data):
-//   prep    K -> f16, V -> bf16, both re-tiled as [key block of 32][feature][key] so that MFMA
+//   prep    K -> f16 (for the approximate mode V too), re-tiled as [key block of 32][feature][key] so that MFMA
 //           operands whose contraction index is the key are 16-byte contiguous;
 //   rowmax  m_i = max_{j<=i} c <q_i,k_j>  (c = scale*log2 e), the exact row maximum that the
 //           running maximum of Algorithm 1 ends at;
@@ -11,7 +11,7 @@
 //           [omega mu~^T; mu~ Sigma~ + lambda I] y = [1; q] by a 16-blocked Cholesky whose block
 //           products run on fp32 MFMA; only y_i (d+1 floats) and m_i leave the chip;
 //   output  s_ij = w_ij (y0_i + k_j . y1_i), O = S V  (Eq. (lla) with y1 = -rho/delta,
-//           y0 = (1 + q.rho)/delta), a flash-style sweep.
+//           y0 = (1 + q.rho)/delta), a flash-style sweep (llla_mfma_bwd.hip).
 // The first 2d rows of every sequence, whose systems are the worst conditioned, take the "precise" variant of the
 // moments kernel (fp32 weights, the scaled operand as two f16 terms) and an output sweep with three-term operands.
 #include <type_traits>
@@ -94,15 +94,12 @@ __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg
 // ------------------------------------------------------------------------------------------------
 // Sweep over S^T = K Q^T for 64 queries per workgroup (16 per wave).
 //   MAXONLY: write the row maxima m_i (in log2 units) -- Algorithm 1's m after its last block.
-//   else   : third loop of Algorithm 1: S = W (y0 + K y1), O = S V.
+//   else   : third loop of Algorithm 1: S = W (y0 + K y1), O = S V, for the approximate mode (the exact forward: out_rows_kernel).
 constexpr int VT_PITCH = KB + 8;     // halves
 
 // LIVE < NB (a d = 16 / 32 call on zero-padded copies): features and value columns from 16 LIVE on are zero, so the
 // contractions over features stop after the chunks that hold live ones and only LIVE output tiles are formed and stored.
-// TERMS = 3 (the first rows, whose coefficients cancel to a few digits): y1 and the coefficients in three bf16 instead of two, i.e. fp32
-// accuracy, since q, k and v are bf16 already.  (On the vector ALU these rows took 26 of 480 us at 96 heads x 1000 rows and 18 at 64 x 4096,
-// all latency; 6 now.)
-template <bool MAXONLY, int DD, int LIVE = Shape<DD>::NB, int TERMS = 2>
+template <bool MAXONLY, int DD, int LIVE = Shape<DD>::NB>
 __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg,
                                                     llla_strides sq, llla_strides sk, int H, int n, int nkb,
                                                     int first_row, float cscale, const bf16_t *__restrict__ VT,
@@ -149,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
     }
 
     float mrow = -INFINITY, y0 = 0.f;
-    bf16x8 yh[NF], ym[NF], yl[NF];
+    bf16x8 yh[NF], yl[NF];
     f32x4 oacc[NB];
     if (!MAXONLY) {
         mrow = Mg[(size_t)bh * (nkb * KB) + iqc];
@@ -160,14 +157,11 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
             float yv[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) yv[t] = yr ? yr[32 * f + 8 * g + t] : 0.f;
-            if constexpr (TERMS == 3) split3_bf16(yv, yh[f], ym[f], yl[f]);
-            else {
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const __bf16 hi = (__bf16)yv[t];
-                    yh[f][t] = hi;
-                    yl[f][t] = (__bf16)(yv[t] - (float)hi);
-                }
+            for (int t = 0; t < 8; ++t) {
+                const __bf16 hi = (__bf16)yv[t];
+                yh[f][t] = hi;
+                yl[f][t] = (__bf16)(yv[t] - (float)hi);
             }
         }
 #pragma unroll
@@ -230,10 +224,6 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                 f32x4 u = {y0, y0, y0, y0};         // y0 + k . y1: the intercept rides in as the accumulator's initial value
 #pragma unroll
                 for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yl[f], u);
-                if constexpr (TERMS == 3) {
-#pragma unroll
-                    for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], ym[f], u);
-                }
 #pragma unroll
                 for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yh[f], u);
                 ut[s] = u;
@@ -257,7 +247,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                     }
             }
         } else {
-            bf16x8 ch, cm, cl;  // output weights as bf16 hi + lo; slot t<4: key 4g+t, t>=4: key 16+4g+t-4
+            bf16x8 ch, cl;      // output weights as bf16 hi + lo; slot t<4: key 4g+t, t>=4: key 16+4g+t-4
             float cv[8];
 #pragma unroll
             for (int s = 0; s < 2; ++s)
@@ -276,15 +266,12 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                 for (int t = 0; t < 8; ++t) csum += cv[t];
             }
             // two values per conversion instruction (v_cvt_pk_bf16_f32)
-            if constexpr (TERMS == 3) split3_bf16(cv, ch, cm, cl);
-            else {
 #pragma unroll
-                for (int t = 0; t < 8; t += 2) {
-                    const bf16x2v hi = __builtin_convertvector(float2v{cv[t], cv[t + 1]}, bf16x2v);
-                    const bf16x2v lo = __builtin_convertvector(float2v{cv[t] - (float)hi[0], cv[t + 1] - (float)hi[1]}, bf16x2v);
-                    ch[t] = hi[0]; ch[t + 1] = hi[1];
-                    cl[t] = lo[0]; cl[t + 1] = lo[1];
-                }
+            for (int t = 0; t < 8; t += 2) {
+                const bf16x2v hi = __builtin_convertvector(float2v{cv[t], cv[t + 1]}, bf16x2v);
+                const bf16x2v lo = __builtin_convertvector(float2v{cv[t] - (float)hi[0], cv[t + 1] - (float)hi[1]}, bf16x2v);
+                ch[t] = hi[0]; ch[t + 1] = hi[1];
+                cl[t] = lo[0]; cl[t + 1] = lo[1];
             }
 #pragma unroll
             for (int J = 0; J < NB; ++J) {
@@ -294,7 +281,6 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
                 const uint4 pk = make_uint4(lo.x, lo.y, hi.x, hi.y);
                 vf = __builtin_bit_cast(bf16x8, pk);
                 oacc[J] = mfma_bf16(cl, vf, oacc[J]);
-                if constexpr (TERMS == 3) oacc[J] = mfma_bf16(cm, vf, oacc[J]);
                 oacc[J] = mfma_bf16(ch, vf, oacc[J]);
             }
         }
@@ -1062,7 +1048,7 @@ hipError_t forward_impl(const Problem &p)
     const int live = (DD == 64 && p.live_d > 0) ? (p.live_d + 15) / 16 : S::NB;
     stage_mark(p.stream, "prep");
     hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT,
-                       live == S::NB ? (bf16_t *)nullptr : VT);
+                       (bf16_t *)nullptr);
     const int nq64 = (p.n + 63) / 64;
     stage_mark(p.stream, "rowmax");
     if constexpr (DD == 64) {
@@ -1090,25 +1076,14 @@ hipError_t forward_impl(const Problem &p)
         hipLaunchKernelGGL((moments_kernel<DD>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
                            first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
     // output: those rows by the sweep with fp32 accuracy (their weights y0 + k.y1 cancel to a few digits), the rest by the plain one
-    auto output = [&](int r0, int r1, bool early) {
-        const dim3 grid(bh, (r1 - r0 + 63) / 64);
-        const int obf = p.out == LLLA_BF16 ? 1 : 0;
-        if (live == S::NB) return mfma_output_rows(p, M, L.npad, Y, r0, r1, early);
-        if constexpr (DD == 64) {
-            auto kernel = early ? sweep_kernel<false, 64, 4, 3> : live == 1 ? sweep_kernel<false, 64, 1> : sweep_kernel<false, 64, 2>;
-            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb, r0, cscale, VT, M, (const float *)Y,
-                               p.O, p.so, obf, (float *)nullptr, p.causal);
-        }
-        return hipGetLastError();
-    };
     if (first > 0) {
         stage_mark(p.stream, "output_early_rows");
-        const hipError_t e = output(0, first, true);
+        const hipError_t e = mfma_output_rows(p, M, L.npad, Y, 0, first, true);
         if (e != hipSuccess) return e;
     }
     if (first < p.n) {
         stage_mark(p.stream, "output");
-        return output(first, p.n, false);
+        return mfma_output_rows(p, M, L.npad, Y, first, p.n, false);
     }
     return hipGetLastError();
 }

@@ -1,0 +1,39 @@
+"""Output sweep of the bf16 forward: lengths around its blocks of 32 keys, its workgroups of 64 rows and the first 2 d rows (three-term
+operands), causal and not, strided operands, both output types, every head dimension.  Gate and oracle as in the other parity tests."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_01450_amd as llla
+from parity import check
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(B, H, n, d, seed):
+    g = torch.Generator(device="cpu").manual_seed(seed)
+    return [torch.randn((B, n, H, d), generator=g).bfloat16().transpose(1, 2) for _ in range(3)]      # [B, n, H, d] in memory
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 127, 128, 129, 160, 161, 193, 256, 257, 289, 321])
+def test_lengths(n, d):
+    Q, K, V = _inputs(1, 2, n, d, 9000 + n + d)
+    scale = 1 / math.sqrt(d)
+    O = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), 1e-2, scale, path="mfma")
+    ref = oracle.forward(Q.contiguous(), K.contiguous(), V.contiguous(), 1e-2, scale)
+    check(O.cpu().numpy(), ref, np.arange(n), d, 2e-2, "n=%d d=%d" % (n, d))
+    half = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), 1e-2, scale, out_dtype=torch.bfloat16, path="mfma")
+    assert torch.equal(half, O.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("d,n", [(16, 130), (32, 100), (64, 33), (64, 129), (64, 161), (128, 256), (128, 300)])
+def test_not_causal(d, n):
+    Q, K, V = _inputs(2, 2, n, d, 9300 + n)
+    O = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), 1e-2, -0.1, causal=False, path="mfma").cpu().numpy()
+    ref = oracle.forward(Q.contiguous(), K.contiguous(), V.contiguous(), 1e-2, -0.1, causal=False)
+    check(O, ref, np.full(n, n - 1), d, 2e-2, "not causal n=%d d=%d" % (n, d))
