@@ -361,14 +361,17 @@ __device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualAr
     for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
     const double u = lane < m ? exp(0.5 * (lg - mx)) : 0.0;
 
-    // row j of G' + lambda I (see dual_row); rows and columns from m on are zero and never become pivots
+    // row j of G' + lambda I (see dual_row); rows and columns from m on are zero and never become pivots.  The rows are selected, not
+    // multiplied by u = 0: lanes m .. mtop - 1 hold keys behind this row, which need not be finite, and what lanes from 16 nb on
+    // find in gram nobody has written in this workgroup.  (With rows of zeros every f, y and u_j t_j from m on is an exact zero.)
     double x[D];
 #pragma unroll
     for (int l = 0; l < D; ++l) {
         x[l] = 0.0;
         if (l < m) {                               // (m is uniform: a scalar branch)
             const double g = ((sm.gram[lane][l] - kq) - lane_value(kq, l)) + qq;
-            x[l] = u * lane_value(u, l) * g + (lane == l ? lam : 0.0);
+            const double v = u * lane_value(u, l) * g + (lane == l ? lam : 0.0);
+            x[l] = lane < m ? v : 0.0;
         }
     }
     double y = u, own = 0.0;

@@ -61,3 +61,41 @@ def test_rows_at_d64_are_exact_to_the_rounding_of_the_result(n):
         err = np.linalg.norm(x - r, axis=-1) / np.maximum(np.linalg.norm(r, axis=-1), 1e-300)
         err[np.linalg.norm(r, axis=-1) == 0] = np.abs(x[np.linalg.norm(r, axis=-1) == 0]).max(initial=0.0)
         assert err.max() < 1e-7, (n, err.max())
+
+
+@pytest.mark.parametrize("n", [17, 49, 64, 70])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_key_behind_a_row_does_not_reach_it(n, bad):
+    """Row i sees keys 0..i.  Four rows share a workgroup and their keys: an entry of key j that is not finite must leave every key-space row
+    before j, those of its own workgroup among them, as it was, bit for bit."""
+    d, B, H = 64, 2, 3
+    g = torch.Generator(device="cpu").manual_seed(7300 + n)
+    Q, K, V = [torch.randn((B, H, n, d), generator=g).to(DEV) for _ in range(3)]
+    clean = llla.llla_forward(Q, K, V, 1e-2, 1 / math.sqrt(d), return_stats=True)
+    for j in sorted({1, 2, 3, 13, n // 2, n - 3, n - 2, n - 1}):
+        Kb = K.clone()
+        Kb[:, :, j, j % d] = bad
+        rows = min(j, 64)
+        for x, r in zip(llla.llla_forward(Q, Kb, V, 1e-2, 1 / math.sqrt(d), return_stats=True), clean):
+            assert torch.isfinite(r).all() and torch.equal(x[:, :, :rows], r[:, :, :rows]), (n, j)
+
+
+@pytest.mark.parametrize("n", [1, 5, 16, 33, 48, 64, 70])
+def test_a_sequence_does_not_depend_on_the_ones_served_before_it(n):
+    """A workgroup's LDS holds what the previous one left there.  A call whose keys are all NaN leaves NaN in the inner products of every
+    compute unit; the sequences of the next call, and those that share a call with such sequences, must not see it."""
+    d, B, H = 64, 32, 16
+    g = torch.Generator(device=DEV).manual_seed(7400 + n)
+    Q, K, V = [torch.randn((B, H, n, d), generator=g, device=DEV) for _ in range(3)]
+    scale = 1 / math.sqrt(d)
+    bad = torch.full((B, H, 64, d), float("nan"), device=DEV)
+    ref = oracle.forward(Q[:1, :2].cpu(), K[:1, :2].cpu(), V[:1, :2].cpu(), 1e-2, scale)
+    before = llla.llla_forward(Q, K, V, 1e-2, scale, return_stats=True)
+    llla.llla_forward(bad, bad, bad, 1e-2, scale)
+    after = llla.llla_forward(Q, K, V, 1e-2, scale, return_stats=True)
+    Kb = K.clone()
+    Kb[1::2] = float("nan")
+    mixed = llla.llla_forward(Q, Kb, V, 1e-2, scale, return_stats=True)
+    check(before[0][:1, :2].cpu().numpy(), ref, np.arange(n), d, 1e-4, "n=%d" % n)
+    for x, y, z in zip(before, after, mixed):
+        assert torch.isfinite(x).all() and torch.equal(x, y) and torch.equal(x[0::2], z[0::2]), n
