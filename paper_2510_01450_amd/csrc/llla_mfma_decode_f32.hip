@@ -17,9 +17,9 @@
 // products instead of eight fp32 ones of twice the cycles.
 //
 // fp32 caches at d = 64 do likewise (compute_roots): 26 tiles of 16x16x4 per four keys were 832 matrix-core cycles for 2 KB of cache, 6 TB/s
-// at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 312.
+// at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 296.
 //
-// What bounds it: HBM at d = 16 / 32; the loads' latency with one wave per SIMD at d = 64 in fp32 (4.7 TB/s at 256 heads x 8192); at d = 128
+// What bounds it: HBM at d = 16 / 32; the loads' latency with one wave per SIMD at d = 64 in fp32 (4.5 TB/s at 256 heads x 8192); at d = 128
 // 100 tiles of 16x16x4 per four keys, 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
 // wave W owns row blocks W and 7 - W, 25 tiles whatever W; every wave loads the whole rows (the first-level cache serves three
 // of the four) and forms the weights for itself, so there is no exchange at all.
@@ -35,8 +35,8 @@ constexpr float REF_SLACK = 8.f;        // the reference exponent moves when a l
 
 // fp32 caches at d = 64: sqrt(w) k and sqrt(w) v in three bf16 on 16-bit MFMA, one workgroup per compute unit (see compute_roots).  Two
 // workgroups on fp32 MFMA overlap one's merge and solve with the other's pass, which wins where there are many heads of few keys
-// (us, fp32 MFMA / roots: 256 heads x 512 42.8 / 28.1, x 1000 59.7 / 40.6; 512 x 128 29 / 35, x 512 56 / 54, x 1000 85 / 78; 384 x 300 43 / 53,
-// 320 x 777 78 / 82; 1024 x 512 100 / 105, x 1000 162 / 153, x 2048 290 / 257).
+// (us, fp32 MFMA / roots: 256 heads x 100 17.3 / 16.9, x 512 40.3 / 26.9, x 1000 56.9 / 39.7; 512 x 128 26.7 / 33.5, x 512 51.5 / 53.0, x 960
+// 80.8 / 77.7; 384 x 300 38 / 50, 320 x 777 75 / 81; 768 x 900 143 / 115; 1024 x 512 97 / 105, x 1000 161 / 156, x 2048 297 / 266).
 inline bool roots_pay(int bh, int L) { return bh <= 256 || L >= 960; }
 
 template <int D>
@@ -187,8 +187,8 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         load_rows(st.k, Kh, krow, koff, s);
         load_rows(st.v, Vh, vrow, voff, s);
     };
-    // logits of a step's 32 keys, the reference exponent, and half the exponents of the weights (ROOTS) or the exponents: e[grp] belongs to
-    // key 4 (n % 4) + g of group grp
+    // logits of a step's 32 keys, the reference exponent, and the exponents of the weights (log2, ROOTS too, which halves them itself): e[grp]
+    // belongs to key 4 (n % 4) + g of group grp
     auto step_exponents = [&](const auto &k, int s, float (&e)[2]) {
         const int j0 = r0 + s * STEP;
         float t[2];
@@ -260,11 +260,14 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         }
     };
     // sqrt(w) k and sqrt(w) v split into three bf16 each, six products per tile of the nine (the rest is below 2^-24), as in the moments
-    // kernel of the forward: 96 matrix-core cycles per tile and 32 keys instead of 256.  One wave per SIMD: with 256 registers 340 are
-    // spilled.  One set of registers for the rows: the next step's keys are requested as soon as these are converted, its values at the end.
-    // 64 heads x 4608 keys: pass 55.7 -> 40.0 us; 256 x 8192: 320 -> 226; 64 heads x 1024 to 8192: call 83.0 -> 64.2.  (Two sets of
-    // registers 66; conversions and products pinned to alternate 66, with two sets 69: part of the registers are then accumulation registers,
-    // read back one by one.)
+    // kernel of the forward: 96 matrix-core cycles per tile and 32 keys instead of 256 (64 in a diagonal tile).  The products of a step
+    // start from zero and are then added to the tile: one rounding of the sum per step, 0.29 ulp rms, instead of six times the 0.58 of an
+    // MFMA.  (Chained onto the sum, errors against fp64 grew with the keys per wave: 32 heads x 32768 unit keys 8.0e-7, 3.5e-7
+    // now, 4.9e-7 on fp32 MFMA; 32 x 8192 3.5e-7, 2.7e-7, 3.2e-7.  64 heads x 1024 to 8192 61.3 -> 61.8 us a call, 256 x 8192 220 -> 241.)
+    // One wave per SIMD: with 256 registers 340 are spilled.  One set of registers for the rows: the next step's keys are requested as soon
+    // as these are converted, its values at the end.  us on fp32 MFMA / here: 64 heads x 1024 to 8192 78 / 62, 256 x 8192 284 / 241.  (With the
+    // products chained: two sets of registers 66 instead of 64; conversions and products pinned to alternate 66, with two sets 69:
+    // part of the registers are then accumulation registers, read back one by one.)
     auto compute_roots = [&](Step &st, int s) {
         float e[2], rt[2];
         step_exponents(st.k, s, e);
@@ -287,13 +290,15 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             split3_bf16(x, r.h, r.m, r.l);
             return r;
         };
-        auto product = [](f32x4 &t, const Split3 &a, const Split3 &b) {
+        auto product = [](f32x4 &sum, const Split3 &a, const Split3 &b) {
+            f32x4 t = {0.f, 0.f, 0.f, 0.f};
             t = mfma_bf16(a.l, b.h, t);
             t = mfma_bf16(a.h, b.l, t);
             t = mfma_bf16(a.m, b.m, t);
             t = mfma_bf16(a.m, b.h, t);
             t = mfma_bf16(a.h, b.m, t);
             t = mfma_bf16(a.h, b.h, t);
+            sum += t;
         };
         Split3 z[NB];
 #pragma unroll
@@ -303,12 +308,13 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
 #pragma unroll
             for (int I = 0; I < J; ++I) product(acc[upper_tile<NB>(I, J)], z[I], z[J]);
             // diagonal: h^T m and m^T h are each other's transposes, and the solve takes (T + T^T) / 2
-            f32x4 &t = acc[upper_tile<NB>(J, J)];
             const bf16x8 h2 = twice_bf16(z[J].h);
+            f32x4 t = {0.f, 0.f, 0.f, 0.f};
             t = mfma_bf16(h2, z[J].l, t);
             t = mfma_bf16(z[J].m, z[J].m, t);
             t = mfma_bf16(h2, z[J].m, t);
             t = mfma_bf16(z[J].h, z[J].h, t);
+            acc[upper_tile<NB>(J, J)] += t;
         }
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
