@@ -55,3 +55,20 @@ def test_both_sides_of_the_rule_agree(d, B, H, n):
     b = llla.llla_forward(*args, 0.25, path="valu").double()
     err = (a - b).norm(dim=-1) / b.norm(dim=-1)
     assert float(err.max()) < 2e-3 and float(err[..., 4 * d:].max() if n > 4 * d else 0) < 2e-4 and float(err.median()) < 1e-5
+
+
+@pytest.mark.parametrize("d,bound", [(16, 6.2), (32, 9.0)])
+def test_errors_of_the_moments(d, bound):
+    """rho of the rows 2 d .. 255, whose systems are well conditioned, so that its error is that of the moments.  Bound on the relative error of all
+    these rows together, in 2^-24: each of four sums of 16 chunks rounds 64 times, one sum of 64 chunks 256 times, which doubles the
+    error of the moments and, with the errors of weights and solve, which both have, makes 1.6 times here (d = 16 / 32: 4.6 / 7.1 with four
+    sums, 7.1 / 11.4 with one, 7.5 to 8.5 / 11.5 to 12.4 on the vector kernels)."""
+    n, H = 256, 8
+    g = torch.Generator(device="cpu").manual_seed(8900 + d)
+    Q, K, V = [torch.randn((1, H, n, d), generator=g) for _ in range(3)]
+    lam = 1e-2 * torch.exp(0.5 * torch.randn((1, H, n), generator=g))
+    rho = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), lam.to(DEV), d ** -0.5, return_stats=True)[1].cpu().double().numpy()[:, :, 2 * d:]
+    ref = oracle.forward_ex(Q, K, V, lam, d ** -0.5)[1][:, :, 2 * d:]
+    err = np.linalg.norm(rho - ref) / np.linalg.norm(ref) * 2 ** 24
+    print("error %.2f x 2^-24" % err)
+    assert err < bound
