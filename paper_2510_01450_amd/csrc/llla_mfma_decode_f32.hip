@@ -31,6 +31,7 @@ namespace {
 using namespace mfma;
 
 constexpr int NT = DEC_NT;
+constexpr float VALUE_SCALE = 0x1p64f, VALUE_SMALL = 0x1p-16f;      // see compute_roots
 constexpr float REF_SLACK = 8.f;        // the reference exponent moves when a logit exceeds it by more than 2^8 (weights stay <= 256)
 
 // fp32 caches at d = 64: sqrt(w) k and sqrt(w) v in three bf16 on 16-bit MFMA, one workgroup per compute unit (see compute_roots).  Two
@@ -170,6 +171,12 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     };
     float om = 0.f, mref = -INFINITY, mtrue = -INFINITY;
 
+    auto unscale_values = [&]() {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) yv[i] *= 1.f / VALUE_SCALE;
+#pragma unroll
+        for (int t = S::NSIG; t < S::NTILES; ++t) acc[t] *= 1.f / VALUE_SCALE;
+    };
     typedef RowFrag<TI, NB> Frag;
     struct Step { Frag k[CH], v[CH]; };
     auto load_rows = [&](Frag (&f)[CH], const char *base, int64_t pitch, unsigned off, int s) {
@@ -268,6 +275,26 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     // as these are converted, its values at the end.  us on fp32 MFMA / here: 64 heads x 1024 to 8192 78 / 62, 256 x 8192 284 / 241.  (With the
     // products chained: two sets of registers 66 instead of 64; conversions and products pinned to alternate 66, with two sets 69:
     // part of the registers are then accumulation registers, read back one by one.)
+    // The third term of a value below 2^-110 would be subnormal, which matrix cores read as zero.  So a stream starts with its values taken
+    // VALUE_SCALE times and goes over to the values as they are at the first one above VALUE_SMALL, ordinarily in its first step (64 heads
+    // x 1024 to 8192 62.6 -> 63.3 us, 16 x 32768 77.9 -> 79.0; values of size 2^-110 3e-7, 2^-124 1.4e-3 off without it, rounding with it).
+    bool small_values = true;
+    auto scale_values = [&](Frag (&f)[CH]) {
+        float top = 0.f;
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) top = fmaxf(top, fabsf(frag_f32<TI, NB>(f[c], i)));
+        if (__builtin_amdgcn_ballot_w64(top > VALUE_SMALL) != 0) {
+            small_values = false;
+            unscale_values();
+        } else {
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) f[c].u[i] = __float_as_uint(VALUE_SCALE * frag_f32<TI, NB>(f[c], i));
+        }
+    };
     auto compute_roots = [&](Step &st, int s) {
         float e[2], rt[2];
         step_exponents(st.k, s, e);
@@ -300,6 +327,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             t = mfma_bf16(a.h, b.h, t);
             sum += t;
         };
+        if (small_values) scale_values(st.v);             // (a scalar branch)
         Split3 z[NB];
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
@@ -392,6 +420,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             load(st, 0);
 #pragma unroll 1
             for (int s = 0; s < nsteps; ++s) compute_roots(st, s);
+            if (small_values) unscale_values();
         }
     } else if (nsteps > 0) {
         Step sa, sb;

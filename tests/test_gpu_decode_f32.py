@@ -135,3 +135,16 @@ def test_errors_do_not_grow_with_the_keys_of_a_wave(B, H, L, values):
     rms = float(np.sqrt(np.mean(err ** 2))) * 2 ** 24
     print("rms error %.2f x 2^-24" % rms)
     assert rms < 8.0
+
+
+@pytest.mark.parametrize("L", [70, 300, 3000])
+def test_values_of_any_size_at_d64(L):
+    """fp32 arithmetic has no value range: the output is linear in V, so values times a power of two give the same bits times it, as long as
+    neither is subnormal; values that are small at first and ordinary later (factors about 2^-18) among them."""
+    g = torch.Generator(device="cpu").manual_seed(2900 + L)
+    q, K, V = [torch.randn(s, generator=g).to(DEV) for s in ((2, 4, 64), (2, 4, L, 64), (2, 4, L, 64))]
+    base = llla.llla_decode(q, K, V, 1e-2, 0.125)
+    assert torch.isfinite(base).all()
+    for k in (-110, -104, -80, -20, -19, -18, -17, -16, -15, 60, 118):
+        got = llla.llla_decode(q, K, V * 2.0 ** k, 1e-2, 0.125)
+        assert torch.equal(got.double(), base.double() * 2.0 ** k), k
