@@ -763,19 +763,15 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
         }
     };
 
-    const int nblk = (causal ? min(i0 + 63, n - 1) : n - 1) / KB + 1;
-    auto step = [&](auto buf, int c) {
-        dma_wait();
-        __syncthreads();                                 // this block has arrived, the previous one is consumed
-        if (c + 1 < nblk) issue(buf ^ 1, c + 1);
-        if (causal && c * KB > iw + 15) return;          // every key of the block lies behind the wave's last row
-        float cv[8];
+    // coefficients of block c: lane (g, nn): cv[4s + r] belongs to key 32c + 16s + 4g + r and query iw + nn.  key_rows(f, s): the operand of
+    // key 16s + nn, features 32f + 8g ..
+    auto coefficients = [&](auto key_rows, int c, float (&cv)[8]) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             f32x4 st = {0.f, 0.f, 0.f, 0.f}, ut = {y0, y0, y0, y0};
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const bf16x8 kfr = *reinterpret_cast<const bf16x8 *>(&kt[buf][row_addr[f] + 16 * s * DD]);
+                const bf16x8 kfr = key_rows(f, s);
                 st = mfma_bf16(kfr, qf[f], st);
                 ut = mfma_bf16(kfr, yl[f], ut);
                 if constexpr (TERMS == 3) ut = mfma_bf16(kfr, ym[f], ut);
@@ -784,12 +780,20 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) cv[4 * s + r] = __builtin_amdgcn_exp2f(fmaf(st[r], cscale, -mrow)) * ut[r];
         }
-        // lane (g, nn): cv[4s + r] belongs to key 32c + 16s + 4g + r and query iw + nn
         if (causal ? c * KB + KB - 1 > iw : c * KB + KB > n) {
             const int j0 = c * KB + 4 * g;
 #pragma unroll
             for (int t = 0; t < 8; ++t) cv[t] = j0 + 16 * (t >> 2) + (t & 3) <= last ? cv[t] : 0.f;
         }
+    };
+    const int nblk = (causal ? min(i0 + 63, n - 1) : n - 1) / KB + 1;
+    auto step = [&](auto buf, int c) {
+        dma_wait();
+        __syncthreads();                                 // this block has arrived, the previous one is consumed
+        if (c + 1 < nblk) issue(buf ^ 1, c + 1);
+        if (causal && c * KB > iw + 15) return;          // every key of the block lies behind the wave's last row
+        float cv[8];
+        coefficients([&](int f, int s) { return *reinterpret_cast<const bf16x8 *>(&kt[buf][row_addr[f] + 16 * s * DD]); }, c, cv);
         bf16x8 ch, cm, cl;
         if constexpr (TERMS == 3) split3_bf16(cv, ch, cm, cl);
         else split_bf16(cv, ch, cl);
@@ -805,6 +809,43 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
     for (int c = 0; c < nblk; c += 2) {
         step(std::integral_constant<int, 0>{}, c);
         if (c + 1 < nblk) step(std::integral_constant<int, 1>{}, c + 1);
+    }
+
+    // The first rows see no later value, one that is not finite included: where a sum has come out so, the wave's rows are summed again with
+    // each key left out of the rows before it instead of multiplied by zero (a scalar branch; no barrier and no LDS in it).
+    if constexpr (TERMS == 3) {
+        bool odd = false;
+#pragma unroll
+        for (int J = 0; J < NB; ++J)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) odd = odd || !(fabsf(acc[J][r]) < INFINITY);
+        if (__any(odd)) {
+#pragma unroll
+            for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int nbw = (causal ? min(iw + 15, n - 1) : n - 1) / KB + 1;
+            for (int c = 0; c < nbw; ++c) {
+                float cv[8];
+                coefficients([&](int f, int s) {
+                    const int64_t j = min(c * KB + 16 * s + nn, n - 1);
+                    return *reinterpret_cast<const bf16x8 *>(Kh + 2 * (j * sk.seq + 32 * f + 8 * g));
+                }, c, cv);
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    for (int gk = 0; gk < 4; ++gk) {     // key j: cv[t] of lanes (gk, query)
+                        const int j = c * KB + 16 * (t >> 2) + 4 * gk + (t & 3);
+                        const bf16_t *vrow = reinterpret_cast<const bf16_t *>(Vh) + (int64_t)min(j, n - 1) * sv.seq + nn;
+                        float w[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) w[r] = __shfl(cv[t], 16 * gk + 4 * g + r);
+#pragma unroll
+                        for (int J = 0; J < NB; ++J) {
+                            const float v = bf16_to_f32(vrow[16 * J]);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) acc[J][r] = j <= (causal ? min(iw + 4 * g + r, n - 1) : n - 1) ? fmaf(w[r], v, acc[J][r]) : acc[J][r];
+                        }
+                    }
+            }
+        }
     }
 
     // acc[J]: lane (g, nn) reg r = O[query iw + 4g + r][feature 16J + nn]

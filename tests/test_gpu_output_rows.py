@@ -37,3 +37,23 @@ def test_not_causal(d, n):
     O = llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), 1e-2, -0.1, causal=False, path="mfma").cpu().numpy()
     ref = oracle.forward(Q.contiguous(), K.contiguous(), V.contiguous(), 1e-2, -0.1, causal=False)
     check(O, ref, np.full(n, n - 1), d, 2e-2, "not causal n=%d d=%d" % (n, d))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_a_value_behind_a_first_row_does_not_reach_it(d, bad):
+    """The first 2 d rows are strictly causal in the values too: an entry of value j that is not finite leaves the rows before j as they
+    were (to the rounding of another order of the sums, 1e-5 of a row), every other column of the rows from j on too, and reaches its own
+    column of those."""
+    n = 2 * d + 37
+    Q, K, V = [t.to(DEV) for t in _inputs(1, 2, n, d, 9500 + d)]
+    scale = 1 / math.sqrt(d)
+    clean = llla.llla_forward(Q, K, V, 1e-2, scale, path="mfma")[0, 1].double()
+    for j in sorted({1, 5, 17, 31, d, 2 * d - 20, 2 * d - 1}):
+        Vb = V.clone()
+        Vb[0, 1, j, d - 3] = bad
+        got = llla.llla_forward(Q, K, Vb, 1e-2, scale, path="mfma")[0, 1].double()
+        other = [c for c in range(d) if c != d - 3]
+        for x, r in ((got[:j], clean[:j]), (got[j:2 * d, other], clean[j:2 * d, other])):
+            assert torch.isfinite(x).all() and float(((x - r).norm(dim=-1) / r.norm(dim=-1)).max()) < 1e-5, (j, bad)
+        assert not torch.isfinite(got[j:2 * d, d - 3]).any(), (j, bad)
