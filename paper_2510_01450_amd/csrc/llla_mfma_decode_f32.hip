@@ -190,9 +190,23 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             for (int c = 0; c < CH; ++c) f[c] = load_frag<TI, NB, !S::TEAM>(base + min(j0 + 4 * c + g, L - 1) * pitch + NB * nn * (int)sizeof(TI));
         }
     };
+    // fp32 at d = 32: keys and values alternate, and the last rows are a choice of addresses instead of a branch (us, as the others / this: 256 heads
+    // x 4096 66.8 / 58.0, 16 x 8192 21.2 / 18.6; bf16 at d = 32, 256 x 4096, 32.7 / 35.3; fp32 at d = 64, 512 x 512, with a branch 51.3 / 52.7).
     auto load = [&](Step &st, int s) {
-        load_rows(st.k, Kh, krow, koff, s);
-        load_rows(st.v, Vh, vrow, voff, s);
+        if constexpr (D != 32 || sizeof(TI) == 2) {
+            load_rows(st.k, Kh, krow, koff, s);
+            load_rows(st.v, Vh, vrow, voff, s);
+        } else {
+            const int j0 = r0 + (s < nsteps ? s : 0) * STEP;
+            const bool whole = j0 + STEP <= L;
+            const char *kb = Kh + j0 * krow + koff, *vb = Vh + j0 * vrow + voff;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int j = min(j0 + 4 * c + g, L - 1), lane_off = NB * nn * (int)sizeof(TI);
+                st.k[c] = load_frag<TI, NB, true>(whole ? kb + 4 * c * krow : Kh + j * krow + lane_off);
+                st.v[c] = load_frag<TI, NB, true>(whole ? vb + 4 * c * vrow : Vh + j * vrow + lane_off);
+            }
+        }
     };
     // logits of a step's 32 keys, the reference exponent, and the exponents of the weights (log2, ROOTS too, which halves them itself): e[grp]
     // belongs to key 4 (n % 4) + g of group grp
