@@ -57,3 +57,27 @@ def test_a_value_behind_a_first_row_does_not_reach_it(d, bad):
         for x, r in ((got[:j], clean[:j]), (got[j:2 * d, other], clean[j:2 * d, other])):
             assert torch.isfinite(x).all() and float(((x - r).norm(dim=-1) / r.norm(dim=-1)).max()) < 1e-5, (j, bad)
         assert not torch.isfinite(got[j:2 * d, d - 3]).any(), (j, bad)
+
+
+@pytest.mark.parametrize("values", ["normal", "regression"])
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_first_rows_are_summed_in_fp32_accuracy(d, values):
+    """The output sweep alone: O of the first 2 d rows against the sum over keys in 64 bits from the call's own rho and delta.  A coefficient
+    w (y0 + k . y1) cancels to a few digits in these rows, so errors are measured against the sum T_i of the sizes of its terms.  Bounds
+    4 x 2^-24 T_i for every row and 0.5 x 2^-24 T_i for the median one: a term has the errors of the logit and the exponential, an ulp or
+    two of its own, and of rho and delta, rounded to fp32 here, at random signs (seen: largest 1.1 to 2.2, median 0.12 to 0.24); two-term
+    operands, 2^-17 of a term at worst, were seen at 5 to 20 and 0.9 to 6.2."""
+    n, scale = 2 * d, 1 / math.sqrt(d)
+    Q, K, V = _inputs(1, 2, n, d, 9700 + d)
+    if values == "regression":
+        V = (K.float() @ (torch.randn((d, d), generator=torch.Generator().manual_seed(d)) / math.sqrt(d)) + 0.1 * V.float()).bfloat16()
+    O, rho, delta = [t.cpu().double() for t in llla.llla_forward(Q.to(DEV), K.to(DEV), V.to(DEV), 1e-2, scale, path="mfma", return_stats=True)]
+    q, k, v = Q.double(), K.double(), V.double()
+    y1, y0 = -rho / delta[..., None], (1 + (q * rho).sum(-1)) / delta
+    lg = (scale * q @ k.transpose(-1, -2)).masked_fill(torch.ones(n, n).triu(1).bool(), -math.inf)
+    w = torch.exp(lg - lg.max(-1, keepdim=True).values)
+    ref = (w * (y0[..., None] + y1 @ k.transpose(-1, -2))) @ v
+    terms = (w * (y0[..., None].abs() + y1.abs() @ k.abs().transpose(-1, -2))) @ v.abs()
+    err = (O - ref).norm(dim=-1) / terms.norm(dim=-1) * 2 ** 24
+    print("largest error %.3f, median %.3f x 2^-24 of the terms" % (float(err.max()), float(err.median())))
+    assert float(err.max()) < 4.0 and float(err.median()) < 0.5
