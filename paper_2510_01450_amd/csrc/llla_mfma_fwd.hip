@@ -30,8 +30,9 @@ struct Layout {
     int nkb, npad;
 };
 
+// with_v: room for V^T, which the approximate mode's sweeps read
 template <int DD>
-Layout make_layout(int B, int H, int n)
+Layout make_layout(int B, int H, int n, bool with_v = false)
 {
     Layout L;
     L.nkb = 2 * ((n + 2 * KB - 1) / (2 * KB));      // 32-key blocks, an even count
@@ -39,7 +40,7 @@ Layout make_layout(int B, int H, int n)
     const size_t bh = (size_t)B * H;
     size_t off = 0;
     L.kt = off; off += round_up(bh * L.npad * DD * 2, 256);
-    L.vt = off; off += round_up(bh * L.npad * DD * 2, 256);
+    L.vt = off; off += with_v ? round_up(bh * L.npad * DD * 2, 256) : 0;
     L.m = off;  off += round_up(bh * L.npad * 4, 256);
     L.y = off;  off += round_up(bh * (size_t)n * Shape<DD>::YP * 4, 256);
     L.total = off;
@@ -47,47 +48,51 @@ Layout make_layout(int B, int H, int n)
 }
 
 // ------------------------------------------------------------------------------------------------
-// prep: re-tile K (-> f16) and, where a sweep reads it (VT != nullptr), V (bf16) as [bh][key block][feature][32 keys]
-template <int DD>
+// prep: re-tile K (-> f16) and, WITH_V, V (bf16) as [bh][key block][feature][32 keys]
+template <int DD, bool WITH_V = false>
 __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
                                                    llla_strides sk, llla_strides sv, int H, int n, int nkb,
                                                    _Float16 *__restrict__ KT, bf16_t *__restrict__ VT)
 {
-    __shared__ bf16_t tile[2][KB][DD + 2];
+    constexpr int NT = WITH_V ? 2 : 1;
+    __shared__ bf16_t tile[NT][KB][DD + 2];
     const int blk = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh % H, tid = threadIdx.x;
-    const bf16_t *Kh = Kg + b * sk.batch + h * sk.head;
-    const bf16_t *Vh = Vg + b * sv.batch + h * sv.head;
+    const bf16_t *head[2] = {Kg + b * sk.batch + h * sk.head, WITH_V ? Vg + b * sv.batch + h * sv.head : nullptr};
+    const int64_t pitch[2] = {sk.seq, sv.seq};
     for (int idx = tid; idx < KB * (DD / 8); idx += 256) {
         const int key = idx / (DD / 8), ch = (idx % (DD / 8)) * 8;
         const int j = blk * KB + key;
-        uint4 kv = make_uint4(0, 0, 0, 0), vv = kv;
-        if (j < n) {
-            kv = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
-            if (VT) vv = *reinterpret_cast<const uint4 *>(Vh + (int64_t)j * sv.seq + ch);
-        }
-        const uint32_t ku[4] = {kv.x, kv.y, kv.z, kv.w}, vu[4] = {vv.x, vv.y, vv.z, vv.w};
+        uint4 x[NT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            tile[0][key][ch + 2 * i] = (bf16_t)(ku[i] & 0xffff);
-            tile[0][key][ch + 2 * i + 1] = (bf16_t)(ku[i] >> 16);
-            tile[1][key][ch + 2 * i] = (bf16_t)(vu[i] & 0xffff);
-            tile[1][key][ch + 2 * i + 1] = (bf16_t)(vu[i] >> 16);
+        for (int m = 0; m < NT; ++m) {
+            x[m] = make_uint4(0, 0, 0, 0);
+            if (j < n) x[m] = *reinterpret_cast<const uint4 *>(head[m] + (int64_t)j * pitch[m] + ch);
+        }
+#pragma unroll
+        for (int m = 0; m < NT; ++m) {
+            const uint32_t u[4] = {x[m].x, x[m].y, x[m].z, x[m].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                tile[m][key][ch + 2 * i] = (bf16_t)(u[i] & 0xffff);
+                tile[m][key][ch + 2 * i + 1] = (bf16_t)(u[i] >> 16);
+            }
         }
     }
     __syncthreads();
     for (int idx = tid; idx < DD * 4; idx += 256) {
         const int feat = idx / 4, k0 = (idx % 4) * 8;
-        half8 ko;
-        uint16_t vo[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            ko[i] = (_Float16)bf16_to_f32(tile[0][k0 + i][feat]);
-            vo[i] = tile[1][k0 + i][feat];
-        }
         const size_t base = ((size_t)bh * nkb + blk) * (DD * KB) + feat * KB + k0;
+        half8 ko;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ko[i] = (_Float16)bf16_to_f32(tile[0][k0 + i][feat]);
         *reinterpret_cast<half8 *>(KT + base) = ko;
-        if (VT) *reinterpret_cast<uint4 *>(VT + base) = make_uint4(vo[0] | (vo[1] << 16), vo[2] | (vo[3] << 16),
-                                                                   vo[4] | (vo[5] << 16), vo[6] | (vo[7] << 16));
+        if constexpr (WITH_V) {
+            uint16_t vo[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vo[i] = tile[1][k0 + i][feat];
+            *reinterpret_cast<uint4 *>(VT + base) = make_uint4(vo[0] | (vo[1] << 16), vo[2] | (vo[3] << 16),
+                                                               vo[4] | (vo[5] << 16), vo[6] | (vo[7] << 16));
+        }
     }
 }
 
@@ -1033,22 +1038,20 @@ hipError_t forward_impl(const Problem &p)
     const Layout L = make_layout<DD>(p.B, p.H, p.n);
     char *ws = static_cast<char *>(p.ws);
     _Float16 *KT = reinterpret_cast<_Float16 *>(ws + L.kt);
-    bf16_t *VT = reinterpret_cast<bf16_t *>(ws + L.vt);
+    const bf16_t *VT = nullptr;                     // the sweep for the maxima reads no values
     float *M = reinterpret_cast<float *>(ws + L.m);
     float *Y = reinterpret_cast<float *>(ws + L.y);
     const int bh = p.B * p.H;
     const float cscale = p.scale * LOG2E;
-    // rows whose visible keys number at most 2 d take the precise moments and the fp32 output sweep: the first 2 d
+    // rows whose visible keys number at most 2 d take the precise moments and the three-term output sweep: the first 2 d
     // rows of a causal call; every row of a non-causal call over at most 2 d keys, none of a longer one
     const int first = p.causal ? (S::EARLY_ROWS < p.n ? S::EARLY_ROWS : p.n) : (p.n <= S::EARLY_ROWS ? p.n : 0);
 
-    const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K),
-                 *V = static_cast<const bf16_t *>(p.V);
+    const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K);
     // a call at d = 16 / 32 on zero-padded copies (live_d features can be non-zero): the variants that skip padded tiles
     const int live = (DD == 64 && p.live_d > 0) ? (p.live_d + 15) / 16 : S::NB;
     stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT,
-                       (bf16_t *)nullptr);
+    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, nullptr, p.sk, p.sk, p.H, p.n, L.nkb, KT, nullptr);
     const int nq64 = (p.n + 63) / 64;
     stage_mark(p.stream, "rowmax");
     if constexpr (DD == 64) {
@@ -1105,7 +1108,7 @@ template <int DD>
 CgLayout make_cg_layout(int B, int H, int n)
 {
     CgLayout C;
-    C.base = make_layout<DD>(B, H, n);
+    C.base = make_layout<DD>(B, H, n, true);
     const size_t bh = (size_t)B * H, rows = bh * (size_t)n;
     size_t off = C.base.total;
     C.ktb = off; off += round_up(bh * C.base.npad * DD * 2, 256);        // K re-tiled as bf16 (tile operand of the sweeps)
@@ -1247,8 +1250,8 @@ hipError_t forward_cg_impl(const Problem &p, int T, float eps, int32_t *iters)
     const dim3 rows_grid((p.n + 3) / 4, bh);
 
     stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, VT);
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, K, p.sk, p.sk, p.H, p.n, L.nkb, KT, KTB);
+    hipLaunchKernelGGL((prep_kernel<DD, true>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, VT);
+    hipLaunchKernelGGL((prep_kernel<DD, true>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, K, p.sk, p.sk, p.H, p.n, L.nkb, KT, KTB);
     stage_mark(p.stream, "rowmax");
     hipLaunchKernelGGL((sweep_kernel<true, DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
                        0, cscale, VT, M, Y, p.O, p.so, 0);
@@ -1286,17 +1289,15 @@ hipError_t backward_rowmax_impl(const BackwardProblem &p, const BackwardLayout &
     const Layout L = make_layout<DD>(p.B, p.H, p.n);
     char *ws = static_cast<char *>(p.ws) + BL.fwd;
     _Float16 *KT = reinterpret_cast<_Float16 *>(ws + L.kt);
-    bf16_t *VT = reinterpret_cast<bf16_t *>(ws + L.vt);
     float *M = reinterpret_cast<float *>(ws + L.m);
     float *Y = reinterpret_cast<float *>(ws + L.y);
     const int bh = p.B * p.H;
-    const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K),
-                 *V = static_cast<const bf16_t *>(p.V);
+    const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K);
     stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, (bf16_t *)nullptr);
+    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, nullptr, p.sk, p.sk, p.H, p.n, L.nkb, KT, nullptr);
     stage_mark(p.stream, "rowmax");
     hipLaunchKernelGGL((sweep_kernel<true, DD>), dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
-                       p.n, L.nkb, 0, p.scale * LOG2E, VT, M, Y, (void *)nullptr, llla_strides{0, 0, 0}, 0, (float *)nullptr);
+                       p.n, L.nkb, 0, p.scale * LOG2E, nullptr, M, Y, (void *)nullptr, llla_strides{0, 0, 0}, 0, (float *)nullptr);
     return hipGetLastError();
 }
 
