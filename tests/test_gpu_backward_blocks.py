@@ -61,3 +61,20 @@ def test_first_rows_have_fp32_accuracy(d, dq_bound, dlam_bound):
     dq, dlam = [np.linalg.norm(got[t].cpu().double().numpy() - ref[t]) / np.linalg.norm(ref[t]) for t in (0, 3)]
     print("dQ %.2e dlambda %.2e" % (dq, dlam))
     assert dq < dq_bound and dlam < dlam_bound
+
+
+@pytest.mark.parametrize("pitch", [2 ** 24 - 8, 2 ** 24, 2 ** 24 + 64])
+def test_rows_far_apart(pitch):
+    """Rows 2^24 elements apart: from there on the sweeps of the forward and the backward form an address per row instead of 32-bit offsets from
+    a common base.  The same bits as from packed tensors (161 rows: both kinds of blocks, first rows and later ones)."""
+    d, H, n = 64, 2, 161
+    g = torch.Generator(device="cpu").manual_seed(161)
+    packed = [torch.randn((1, H, n, d), generator=g).bfloat16().to(DEV) for _ in range(4)]
+    store = torch.empty(n * pitch, dtype=torch.bfloat16, device=DEV)         # 5.4 GB: all four tensors side by side in each row
+    far = [store.as_strided((1, H, n, d), (n * pitch, d, pitch, 1), 2 * H * d * t) for t in range(4)]
+    for x, y in zip(far, packed):
+        x.copy_(y)
+    for a, b in zip(llla.llla_forward(*far[:3], 1e-2, 0.125, return_stats=True), llla.llla_forward(*packed[:3], 1e-2, 0.125, return_stats=True)):
+        assert torch.isfinite(b).all() and torch.equal(a, b)
+    for a, b in zip(llla.llla_backward(*far, 1e-2, 0.125, return_dlambda=True), llla.llla_backward(*packed, 1e-2, 0.125, return_dlambda=True)):
+        assert torch.isfinite(b).all() and torch.equal(a, b)

@@ -88,3 +88,39 @@ def test_forward_replayed(n, d, dtype):
     ref = oracle.forward(Q.cpu(), K.cpu(), V.cpu(), lam, scale)
     tol = 2e-2 if dtype == torch.bfloat16 else 1e-4
     print(check(out.cpu().numpy(), ref, np.arange(n), d, tol, "graph forward n=%d d=%d" % (n, d)))
+
+
+def test_fp32_calls_replayed():
+    """Few short fp32 sequences (one wave per row), the same at d = 64 with its key-space rows, and a decode of an fp32 cache."""
+    B, H = 1, 4
+    lam, scale = 1e-2, 0.2
+    T = {d: [_fresh((B, H, n, d), torch.float32, 40 + d + t) for t in range(3)] for d, n in ((16, 150), (32, 90), (64, 130))}
+    q, Kc, Vc = _fresh((B, H, 64), torch.float32, 140), _fresh((B, H, 3000, 64), torch.float32, 141), _fresh((B, H, 3000, 64), torch.float32, 142)
+    need = max(llla.forward_workspace_bytes(B, H, v[0].shape[2], d, torch.float32) for d, v in T.items())
+    fws = torch.empty(need + 256, dtype=torch.uint8, device=DEV)
+    dws = torch.empty(llla.decode_workspace_bytes(B, H, 3000, 64, torch.float32) + 256, dtype=torch.uint8, device=DEV)
+
+    def step(o):
+        for d in (16, 32):
+            llla.llla_forward(*T[d], lam, scale, workspace=fws, out=o[d])
+        llla.llla_forward(*T[64], lam, scale, workspace=fws, out=o[64])
+        llla.llla_decode(q, Kc, Vc, lam, scale, workspace=dws, out=o[0])
+
+    def outputs():
+        return {**{d: torch.zeros_like(T[d][0]) for d in T}, 0: torch.zeros_like(q)}
+
+    eager, out = outputs(), outputs()
+    step(eager)
+    g = _record(lambda: step(out))
+    for r in range(3):
+        for t in [x for v in T.values() for x in v] + [q, Vc]:
+            t.copy_(_fresh(t.shape, t.dtype, 150 + r))
+        Kc[:, :, r::5].mul_(-1.0)
+        step(eager)
+        torch.cuda.synchronize()
+        for o in out.values():
+            o.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        for k in out:
+            assert torch.isfinite(out[k]).all() and torch.equal(out[k], eager[k]), (r, k)
