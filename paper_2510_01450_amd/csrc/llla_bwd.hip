@@ -536,10 +536,20 @@ size_t backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in, llla_
     return path == LLLA_PATH_MFMA ? m : (m > v ? m : v);
 }
 
+// LLLA_PATH_AUTO and the fp32 matrix-core backward: d = 64 always; d = 16 / 32 from the size on from which its five launches pay.  us, vector
+// kernels vs matrix cores.  d = 32: 4 heads 25 vs 33 at 32 rows, 34 vs 33 at 48, 36 vs 33 at 64, 100 vs 66 at 256; 256 heads 132 vs 58 at 64,
+// 944 vs 304 at 256.  d = 16: 4 heads 33 vs 33 at 64, 45 vs 34 at 96, 192 vs 78 at 512; 256 heads 39 vs 40 at 64, 69 vs 59 at 96, 1006 vs 539
+// at 512.  Errors against fp64 (geometric mean over 8 to 32 heads, 100 to 1500 rows, unit and normal values): d = 32 0.80 to 1.00 times those of
+// the vector kernels, d = 16 0.82 to 1.08.
+static bool takes_backward_f32(int n, int d, llla_dtype in)
+{
+    return mfma_backward_f32_supported(n, d, in) && (d == 64 || n >= (d == 32 ? 64 : 96));
+}
+
 size_t backward_wanted_bytes(int B, int H, int n, int d, llla_dtype in)
 {
     const size_t need = backward_workspace_bytes(B, H, n, d, in, LLLA_PATH_AUTO);
-    const size_t f = mfma_backward_f32_supported(n, d, in) ? mfma_backward_f32_workspace_bytes(B, H, n, d) : 0;
+    const size_t f = takes_backward_f32(n, d, in) ? mfma_backward_f32_workspace_bytes(B, H, n, d) : 0;
     return f > need ? f : need;
 }
 
@@ -549,8 +559,8 @@ hipError_t backward(const BackwardProblem &p, llla_path path)
     const bool use_mfma = path != LLLA_PATH_VALU && mfma_forward_supported(p.d, p.in, true) && (p.n + 63) / 64 <= 65535;
     stage_begin(p.stream);
     hipError_t err;
-    // fp32, d = 64: the vector kernels only on request, or where the caller brought no more workspace than they need
-    const bool use_f32 = path == LLLA_PATH_AUTO && mfma_backward_f32_supported(p.n, p.d, p.in) &&
+    // (the vector kernels on request, or where the caller brought no more workspace than they need)
+    const bool use_f32 = path == LLLA_PATH_AUTO && takes_backward_f32(p.n, p.d, p.in) &&
                          p.ws_bytes >= mfma_backward_f32_workspace_bytes(p.B, p.H, p.n, p.d);
     if (use_f32) err = mfma_backward_f32(p);
     else if (!use_mfma) err = valu_backward(p);

@@ -81,7 +81,7 @@ hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, i
 // rows [r0, r1) of the output of a bf16 forward from the row maxima (log2 units) and the solved rows (llla_mfma_bwd.hip)
 hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int r0, int r1, bool three_terms);
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
-// the same for fp32 inputs (d = 64): sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
+// the same for fp32 inputs (d = 16, 32 and 64): sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
 // forward's, with the row maxima M given and the rows r replaced by u
 bool mfma_backward_f32_supported(int n, int d, llla_dtype in);
 size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d);
@@ -109,6 +109,7 @@ hipError_t padded_forward_cg(const Problem &p, int T, float eps, int32_t *iters)
 bool padded_backward_supported(int d, llla_dtype in);          // bf16 only, like the matrix-core backward itself
 size_t padded_backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in);
 hipError_t padded_backward(const BackwardProblem &p);
+hipError_t pad_queries_keys(const BackwardProblem &p, void *Q, void *K);      // Q and K in rows of 64 features, zero from p.d on
 // approximate mode: T conjugate-gradient steps per row (bf16, d = 64 / 128, causal); iters: [B,H,n] steps done, or nullptr
 size_t mfma_forward_cg_workspace_bytes(int B, int H, int n, int d, llla_dtype in);
 hipError_t mfma_forward_cg(const Problem &p, int T, float eps, int32_t *iters);

@@ -29,16 +29,27 @@ using namespace mfma;
 constexpr int RT = 32;                 // rows per workgroup and rows per step
 constexpr float LAZY_BITS = 64.f;      // as in the forward: the reference exponent moves when a tile exceeds it by more
 
-// 32 rows of DD floats -> LDS, chunk c of row r at c ^ (r & 7); rows past `last` repeat it
+// position of the scalar behind a y, u or r row, and the pitch of the rows: those of the moments kernel, which at d = 16 / 32 runs on
+// copies padded to 64 features
+template <int DD>
+constexpr int SP = DD < 64 ? 64 : DD;
+
+// where 16-byte chunk c of tile row r sits: c ^ swz(r)
+template <int DD>
+__device__ inline int swz(int r) { return DD >= 32 ? r & 7 : (r >> 1) & 3; }
+
+// 32 rows of DD floats -> LDS, chunks swizzled; rows past `last` repeat it
 template <int DD>
 __device__ inline void dma_tile(const float *src, int64_t pitch, int row0, int last, float *dst, int wave, int lane)
 {
-    constexpr int CH = DD / 4, RPT = 64 / CH, NTR = RT / RPT / 4;     // 16-byte chunks per row, rows and number of a wave's transfers
+    constexpr int CH = DD / 4, RPT = 64 / CH, NTR = RT / RPT;         // 16-byte chunks per row, rows of a transfer, transfers
+    constexpr int NW = NTR < 4 ? 1 : NTR / 4;                         // transfers of a wave (d = 16: of the first two)
+    if (NTR < 4 && wave >= NTR) return;
 #pragma unroll
-    for (int t = 0; t < NTR; ++t) {
-        const int r0 = (wave * NTR + t) * RPT, row = r0 + lane / CH;
+    for (int t = 0; t < NW; ++t) {
+        const int r0 = (wave * NW + t) * RPT, row = r0 + lane / CH;
         const int j = min(row0 + row, last);
-        dma16(src + (int64_t)j * pitch + 4 * ((lane % CH) ^ (row & 7)), dst + r0 * DD);
+        dma16(src + (int64_t)j * pitch + 4 * ((lane % CH) ^ swz<DD>(row)), dst + r0 * DD);
     }
 }
 
@@ -71,7 +82,7 @@ static_assert(covered(1) && covered(65535) && block_grid(65535).z == 1 && covere
 template <int DD>
 __device__ inline f32x4 row_chunk(const float *trow, int g, int v, int nn)
 {
-    return *reinterpret_cast<const f32x4 *>(trow + 4 * ((DD / 16 * g + v) ^ (nn & 7)));
+    return *reinterpret_cast<const f32x4 *>(trow + 4 * ((DD / 16 * g + v) ^ swz<DD>(nn)));
 }
 
 // 2^x as the square of its root: the moments kernel works with the roots of the weights, and the sweeps use the same weights to
@@ -105,7 +116,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam, int causal = 1, int skip = 0, void *Og = nullptr,
     llla_strides so = {}, int out_bf16 = 0)
 {
-    constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = Shape<DD>::YP, RP = DD + 4;
+    constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = SP<DD> + 16, RP = DD + 4;
     __shared__ __align__(16) float tiles[2][2][RT * DD];
     __shared__ float rbest[4][16], rref[4][16], rsum[4][16];
     __shared__ int rarg[4][16];
@@ -133,9 +144,9 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     if constexpr (MODE == 1) {
         load_row<DD>(Yg + row * YP, g, yr);
         load_row<DD>(Ug + row * YP, g, ur);
-        y0 = Yg[row * YP + DD];
-        u0 = Ug[row * YP + DD];
-        jstar = __float_as_int(Ug[row * YP + DD + 1]);
+        y0 = Yg[row * YP + SP<DD>];
+        u0 = Ug[row * YP + SP<DD>];
+        jstar = __float_as_int(Ug[row * YP + SP<DD> + 1]);
         mh = Mg[(size_t)bh * npad + iq];
         float dl = 0.f;
 #pragma unroll
@@ -152,7 +163,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     }
     if constexpr (MODE == 2) {
         load_row<DD>(Yg + row * YP, g, yr);
-        y0 = Yg[row * YP + DD];
+        y0 = Yg[row * YP + SP<DD>];
         mh = Mg[(size_t)bh * npad + iq];
     }
     f32x4 acc[NB];
@@ -238,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
             const float *krow = (MODE == 2 ? vt : kt) + kr * DD + (nn & 3);
 #pragma unroll
             for (int J = 0; J < NB; ++J)
-                acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], krow[4 * ((4 * J + (nn >> 2)) ^ (kr & 7))], acc[J], 0, 0, 0);
+                acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], krow[4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))], acc[J], 0, 0, 0);
         }
     }
 
@@ -307,8 +318,8 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
         float r0 = rref[w0][q] == -INFINITY ? 0.f : rsum[w0][q] * __builtin_amdgcn_exp2f(rref[w0][q] - m);
         r0 += rref[w1][q] == -INFINITY ? 0.f : rsum[w1][q] * __builtin_amdgcn_exp2f(rref[w1][q] - m);
         const int a = b1 > b0 || (b1 == b0 && rarg[w1][q] < rarg[w0][q]) ? rarg[w1][q] : rarg[w0][q];
-        Rv[ro * YP + DD] = r0;
-        Rv[ro * YP + DD + 1] = __int_as_float(a);
+        Rv[ro * YP + SP<DD>] = r0;
+        Rv[ro * YP + SP<DD> + 1] = __int_as_float(a);
         Mg[(size_t)bh * npad + i0 + tid] = m;
     }
 }
@@ -317,12 +328,12 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
 // Mirror image: rows of Q, dO, y1, u1 pass through LDS, the keys' rows of K and V stay in registers; the coefficient tiles
 // (lane (g, nn): queries 4g + r, key nn) are the A operands of the products that contract over the queries.
 template <int DD>
-__global__ __launch_bounds__(256, DD == 64 ? 2 : 1) void bwd_keys_f32_kernel(
+__global__ __launch_bounds__(256, DD <= 64 ? 2 : 1) void bwd_keys_f32_kernel(
     const float *__restrict__ Qg, const float *__restrict__ Kg, const float *__restrict__ Vg, const float *__restrict__ Gg,
     llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n, float scale, const float *__restrict__ Yg,
     const float *__restrict__ Ug, const float *__restrict__ Sc, float *__restrict__ dK, float *__restrict__ dV)
 {
-    constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = Shape<DD>::YP, RP = DD + 4;
+    constexpr int NS = DD / 4, NV = DD / 16, NB = DD / 16, YP = SP<DD> + 16, RP = DD + 4;
     __shared__ __align__(16) float tiles[2][4][RT * DD];
     __shared__ __align__(16) float scal[2][RT * 8];
     static_assert(2 * 4 * 16 * RP <= 8 * RT * DD, "the final sums reuse the tiles");
@@ -394,7 +405,7 @@ __global__ __launch_bounds__(256, DD == 64 ? 2 : 1) void bwd_keys_f32_kernel(
             const int qrow = 4 * g + r;
             int off[NB];
 #pragma unroll
-            for (int J = 0; J < NB; ++J) off[J] = qrow * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ (qrow & 7));
+            for (int J = 0; J < NB; ++J) off[J] = qrow * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(qrow));
 #pragma unroll
             for (int J = 0; J < NB; ++J) dv[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cs[r], gt[off[J]], dv[J], 0, 0, 0);
 #pragma unroll
@@ -428,23 +439,27 @@ __global__ __launch_bounds__(256, DD == 64 ? 2 : 1) void bwd_keys_f32_kernel(
 }
 
 struct BwdF32Layout {
-    size_t m, y, ru, sc, total;
+    size_t m, y, ru, sc, q, k, total;
     int npad;
 };
 
 // The rows of r are overwritten by those of u (the workgroup of the moments kernel that reads r_i writes u_i); the scalars
-// of a row follow its vector: r0, later u0, and the key of the row maximum.
+// of a row follow its vector: r0, later u0, and the key of the row maximum.  q, k: at d = 16 / 32 the copies of Q and K, padded to 64
+// features, that the moments kernel works on (see llla_pad.hip); the sweeps read the tensors themselves.
 BwdF32Layout make_bwd_f32_layout(int B, int H, int n, int d)
 {
     BwdF32Layout L{};
     const size_t bh = (size_t)B * H;
-    const int yp = d + 16;
+    const int yp = (d < 64 ? 64 : d) + 16;
     L.npad = (n + 63) / 64 * 64;
     size_t off = 0;
     L.m = off;  off += round_up(bh * L.npad * 4, 256);
     L.y = off;  off += round_up(bh * (size_t)n * yp * 4, 256);
     L.ru = off; off += round_up(bh * (size_t)n * yp * 4, 256);
     L.sc = off; off += round_up(bh * (size_t)n * 8 * 4, 256);
+    const size_t padded = d < 64 ? round_up(bh * (size_t)n * 64 * 4, 256) : 0;
+    L.q = off;  off += padded;
+    L.k = off;  off += padded;
     L.total = off;
     return L;
 }
@@ -475,31 +490,53 @@ hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y,
     return hipGetLastError();
 }
 
-bool mfma_backward_f32_supported(int n, int d, llla_dtype in) { return in == LLLA_F32 && d == 64 && (n + RT - 1) / RT <= 65535; }
+bool mfma_backward_f32_supported(int n, int d, llla_dtype in)
+{
+    return in == LLLA_F32 && (d == 16 || d == 32 || d == 64) && (n + RT - 1) / RT <= 65535;
+}
 
 size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d) { return make_bwd_f32_layout(B, H, n, d).total; }
 
-hipError_t mfma_backward_f32(const BackwardProblem &p)
+namespace {
+
+template <int DD>
+hipError_t launch_backward_f32(const BackwardProblem &p)
 {
-    const BwdF32Layout L = make_bwd_f32_layout(p.B, p.H, p.n, p.d);
+    const BwdF32Layout L = make_bwd_f32_layout(p.B, p.H, p.n, DD);
     char *ws = static_cast<char *>(p.ws);
     const float *Y = reinterpret_cast<const float *>(ws + L.y), *U = reinterpret_cast<const float *>(ws + L.ru);
     const float *Sc = reinterpret_cast<const float *>(ws + L.sc);
     stage_mark(p.stream, "backward_r");
-    hipError_t e = launch_rows<64, 0>(p, L);
+    hipError_t e = launch_rows<DD, 0>(p, L);
     if (e != hipSuccess) return e;
     stage_mark(p.stream, "moments");
-    e = mfma_moments_f32_given(p, L.npad, reinterpret_cast<float *>(ws + L.m), reinterpret_cast<float *>(ws + L.y),
+    BackwardProblem pm = p;
+    if constexpr (DD < 64) {
+        e = pad_queries_keys(p, ws + L.q, ws + L.k);
+        if (e != hipSuccess) return e;
+        pm.Q = ws + L.q;
+        pm.K = ws + L.k;
+        pm.sq = pm.sk = llla_strides{(int64_t)p.H * p.n * 64, (int64_t)p.n * 64, 64};
+        pm.live_d = DD;
+    }
+    e = mfma_moments_f32_given(pm, L.npad, reinterpret_cast<float *>(ws + L.m), reinterpret_cast<float *>(ws + L.y),
                                reinterpret_cast<float *>(ws + L.ru));
     if (e != hipSuccess) return e;
     stage_mark(p.stream, "backward_dq");
-    e = launch_rows<64, 1>(p, L);
+    e = launch_rows<DD, 1>(p, L);
     if (e != hipSuccess) return e;
     stage_mark(p.stream, "backward_keys");
-    hipLaunchKernelGGL((bwd_keys_f32_kernel<64>), dim3(p.B * p.H, (p.n + RT - 1) / RT), dim3(256), 0, p.stream,
+    hipLaunchKernelGGL((bwd_keys_f32_kernel<DD>), dim3(p.B * p.H, (p.n + RT - 1) / RT), dim3(256), 0, p.stream,
                        static_cast<const float *>(p.Q), static_cast<const float *>(p.K), static_cast<const float *>(p.V),
                        static_cast<const float *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, p.scale, Y, U, Sc, p.dK, p.dV);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t mfma_backward_f32(const BackwardProblem &p)
+{
+    return p.d == 16 ? launch_backward_f32<16>(p) : p.d == 32 ? launch_backward_f32<32>(p) : launch_backward_f32<64>(p);
 }
 
 }  // namespace llla

@@ -484,9 +484,14 @@ hipError_t mfma_forward_f32(const Problem &p)
 hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU)
 {
     const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K);
-    hipLaunchKernelGGL((moments_f32_kernel<4, true>), dim3((p.n + Shape<FD>::QB - 1) / Shape<FD>::QB, p.B * p.H), dim3(256), 0,
-                       p.stream, Q, K, p.sq, p.sk, p.H, p.n, npad, p.scale * LOG2E, p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1,
-                       (p.n + Shape<FD>::QB - 1) / Shape<FD>::QB, dual::DualArgs{}, 0);
+    const int nqb = (p.n + Shape<FD>::QB - 1) / Shape<FD>::QB;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nqb, p.B * p.H), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, npad, p.scale * LOG2E,
+                           p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1, nqb, dual::DualArgs{}, 0);
+    };
+    if (p.live_d == 16) launch(moments_f32_kernel<1, true>);
+    else if (p.live_d == 32) launch(moments_f32_kernel<2, true>);
+    else launch(moments_f32_kernel<4, true>);
     return hipGetLastError();
 }
 

@@ -174,6 +174,12 @@ PadBackwardLayout make_pad_backward_layout(int B, int H, int n)
 
 }  // namespace
 
+hipError_t pad_queries_keys(const BackwardProblem &p, void *Q, void *K)
+{
+    const PadSources in = {{pad_source(p.Q, p.sq, Q), pad_source(p.K, p.sk, K)}};
+    return pad_rows(in, 2, Rows{p.B, p.H, p.n, p.d, p.stream}, p.in == LLLA_F32);
+}
+
 bool padded_forward_supported(int d, llla_dtype in)
 {
     if (d != 16 && d != 32) return false;

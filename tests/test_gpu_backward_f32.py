@@ -1,4 +1,4 @@
-"""fp32 backward on the fp32 matrix cores (d = 64): the edges of its 32-row tiles and of the halves they are split into,
+"""fp32 backward on the matrix cores (d = 16, 32 and 64): the edges of its 32-row tiles and of the halves they are split into,
 against the backward oracle, with the fp32 gate of the other backward tests (parity.check_grad, 1e-3)."""
 import numpy as np
 import pytest
@@ -18,6 +18,32 @@ def test_edges_of_the_tiles(n):
     Q, K, V = workloads.make_inputs(w)
     G = _upstream(w, 40 + n)
     _compare(w, _backward(w, Q, K, V, G, w.lam), ob.backward(Q, K, V, G, w.lam, w.scale), "n=%d" % n, _floor(V, G, w.lam))
+
+
+@pytest.mark.parametrize("d,n", [(32, n) for n in (63, 64, 65, 95, 96, 97, 130, 257)] + [(16, n) for n in (95, 96, 97, 127, 128, 130, 257)])
+def test_small_heads(d, n):
+    """d = 16 / 32: sweeps at the head's own dimension, moments on copies padded to 64 features; the sizes on both sides of the rule
+    that takes them."""
+    w = _case(1, 3, n, d, "f32", index=560 + n)
+    Q, K, V = workloads.make_inputs(w)
+    G = _upstream(w, 60 + n)
+    _compare(w, _backward(w, Q, K, V, G, w.lam), ob.backward(Q, K, V, G, w.lam, w.scale), "d=%d n=%d" % (d, n), _floor(V, G, w.lam))
+
+
+@pytest.mark.parametrize("d", [16, 32])
+def test_small_heads_strides_do_not_matter(d):
+    """Heads interleaved with the rows, and rows further apart than they are long: the same bits as contiguous tensors."""
+    w = _case(2, 3, 131, d, "f32", index=570 + d)
+    T = [t.to(DEV) for t in workloads.make_inputs(w)] + [_upstream(w, 70).to(DEV)]
+    want = llla.llla_backward(*T, w.lam, w.scale, return_dlambda=True)
+    rows = [t.transpose(1, 2).contiguous().transpose(1, 2) for t in T]
+    wide = []
+    for t in T:
+        x = torch.full((2, 3, 131, d + 12), float("nan"), device=DEV)
+        x[..., :d] = t
+        wide.append(x[..., :d])
+    for S in (rows, wide):
+        assert all(torch.equal(a, b) for a, b in zip(llla.llla_backward(*S, w.lam, w.scale, return_dlambda=True), want))
 
 
 @pytest.mark.parametrize("factor", [-1.0, 40.0])
@@ -51,9 +77,10 @@ def test_few_keys_small_ridge_features_over_four_decades():
         assert np.linalg.norm(a - b) <= bound * np.linalg.norm(b)
 
 
-def test_workspace_of_the_vector_kernels_is_enough():
+@pytest.mark.parametrize("d,n", [(64, 70), (32, 70), (16, 100)])
+def test_workspace_of_the_vector_kernels_is_enough(d, n):
     """A caller that brings only what the vector kernels need gets their result."""
-    w = _case(1, 2, 70, 64, "f32", index=901)
+    w = _case(1, 2, n, d, "f32", index=901)
     Q, K, V = (t.to(DEV) for t in workloads.make_inputs(w))
     G = _upstream(w, 42).to(DEV)
     small = (w.B * w.H * w.n * (2 * w.d + 8) * 4 + 255) // 256 * 256
