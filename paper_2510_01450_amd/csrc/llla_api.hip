@@ -68,7 +68,8 @@ size_t llla_forward_workspace_bytes(int B, int H, int n, int d, llla_dtype in)
 {
     if (B <= 0 || H <= 0 || n <= 0 || !dim_supported(d) || !dtype_ok(in)) return 0;
     if (llla::padded_forward_supported(d, in)) return llla::padded_forward_workspace_bytes(B, H, n, d, in);
-    if (in == LLLA_F32) return llla::mfma_forward_f32_supported(d, true) ? llla::mfma_forward_f32_workspace_bytes(B, H, n) : 0;
+    if (in == LLLA_F32 && d == 128) return llla::mfma_forward_f32_wide_workspace_bytes(B, H, n);      // (a call with less: vector kernels)
+    if (in == LLLA_F32) return llla::mfma_forward_f32_workspace_bytes(B, H, n);
     return llla::mfma_forward_workspace_bytes(B, H, n, d, in);
 }
 
@@ -107,6 +108,11 @@ llla_status llla_forward_ex(const void *Q, const void *K, const void *V, void *O
         if (st != LLLA_OK) return st;
     }
 
+    // fp32 at d = 128: on the matrix cores where the caller brought the workspace for it.  Calls of key-space rows alone (n <= 64) stay with
+    // the vector path's kernel while those are few: it gives a row a workgroup, here a row is a wave.
+    const bool wide = in == LLLA_F32 && d == 128 && path == LLLA_PATH_AUTO && (n > 64 || (int64_t)B * H * n >= 1024) &&
+                      check_workspace(llla::mfma_forward_f32_wide_workspace_bytes(B, H, n), workspace, workspace_bytes) == LLLA_OK;
+
     Problem p{};
     p.Q = Q; p.K = K; p.V = V; p.O = O;
     p.sq = sq; p.sk = sk; p.sv = sv; p.so = so;
@@ -119,9 +125,10 @@ llla_status llla_forward_ex(const void *Q, const void *K, const void *V, void *O
     p.ws = workspace; p.ws_bytes = workspace_bytes;
     p.stream = static_cast<hipStream_t>(stream);
     llla::stage_begin(p.stream);
-    if (!use_mfma) llla::stage_mark(p.stream, "valu_forward");
+    if (!use_mfma && !wide) llla::stage_mark(p.stream, "valu_forward");
     const bool by_row = path == LLLA_PATH_AUTO && !use_mfma && llla::short_forward_takes(B * H, n, d, in);
-    const hipError_t e = by_row    ? llla::short_forward(p)
+    const hipError_t e = wide        ? llla::mfma_forward_f32_wide(p)
+                         : by_row    ? llla::short_forward(p)
                          : !use_mfma ? llla::valu_forward(p)
                          : padded  ? llla::padded_forward(p)
                          : f32_mfma ? llla::mfma_forward_f32(p) : llla::mfma_forward(p);

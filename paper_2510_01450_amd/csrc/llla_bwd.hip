@@ -543,7 +543,7 @@ size_t backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in, llla_
 // the vector kernels, d = 16 0.82 to 1.08.
 static bool takes_backward_f32(int n, int d, llla_dtype in)
 {
-    return mfma_backward_f32_supported(n, d, in) && (d == 64 || n >= (d == 32 ? 64 : 96));
+    return mfma_backward_f32_supported(n, d, in) && (d >= 64 || n >= (d == 32 ? 64 : 96));
 }
 
 size_t backward_wanted_bytes(int B, int H, int n, int d, llla_dtype in)

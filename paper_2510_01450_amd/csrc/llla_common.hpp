@@ -81,7 +81,7 @@ hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, i
 // rows [r0, r1) of the output of a bf16 forward from the row maxima (log2 units) and the solved rows (llla_mfma_bwd.hip)
 hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int r0, int r1, bool three_terms);
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
-// the same for fp32 inputs (d = 16, 32 and 64): sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
+// the same for fp32 inputs: sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
 // forward's, with the row maxima M given and the rows r replaced by u
 bool mfma_backward_f32_supported(int n, int d, llla_dtype in);
 size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d);
@@ -100,6 +100,10 @@ bool mfma_forward_f32_supported(int d, bool causal);
 size_t mfma_forward_f32_workspace_bytes(int B, int H, int n);
 hipError_t mfma_forward_f32(const Problem &p);
 hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y, int skip);      // its output sweep, rows from skip on
+// and at d = 128: llla_mfma_fwd_f32_128.hip.  The workspace is optional: a call with less runs on the vector kernels.
+size_t mfma_forward_f32_wide_workspace_bytes(int B, int H, int n);
+hipError_t mfma_forward_f32_wide(const Problem &p);
+hipError_t mfma_moments_f32_wide_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU);
 // head dimensions 16 and 32 (bf16 or fp32): the d = 64 matrix-core forward on zero-padded copies (llla_pad.hip)
 bool padded_forward_supported(int d, llla_dtype in);
 size_t padded_forward_workspace_bytes(int B, int H, int n, int d, llla_dtype in);

@@ -275,7 +275,8 @@ __device__ __forceinline__ void dual_forward_row(DualShared<D> &sm, const DualAr
                         a.Delta ? a.Delta + row : nullptr);
 }
 
-// Four consecutive rows of a forward call with fp32 inputs at d = 64, one per wave: rows top - 3 .. top (those below 0 are absent).
+// R consecutive rows of a forward call with fp32 inputs at d = 64 (R = 4) or 128 (R = 8), one per wave: rows top - R + 1 .. top (those
+// below 0 are absent).
 //
 // What bounds dual_row is its chain: two barriers per block step of the factorisation, four roots one after the other in each, a
 // back substitution in one wave, and every row forms the inner products of the same first keys again: some 60 000 cycles of a
@@ -284,10 +285,11 @@ __device__ __forceinline__ void dual_forward_row(DualShared<D> &sm, const DualAr
 // pivot broadcast by v_readlane.  All lanes take part in every update anyway, so the elimination above the diagonal is free and
 // there is no back substitution; the columns move down by one register per step, so that the loop over the pivots need not be unrolled.
 // 16 heads x 1024 rows: moments kernel 415 -> 360 us, the call 418 -> 359.
-struct DualShared4 {
+template <int D, int R>
+struct DualSharedRows {
     double gram[64][65];                           // <k_j, k_l>
-    float ks[64][65];                              // the keys that the rows see, zero beyond
-    float qs[4][64];
+    float ks[64][D + 1];                           // the keys that the rows see, zero beyond
+    float qs[R][D];
 };
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -307,10 +309,10 @@ __device__ inline double wave_sum_f64(double x)
     return x;
 }
 
-template <typename TO>
-__device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualArgs &a, int bh, int top)
+template <int D, int R, typename TO>
+__device__ __forceinline__ void dual_forward_rows(DualSharedRows<D, R> &sm, const DualArgs &a, int bh, int top)
 {
-    constexpr int D = 64;
+    constexpr int MK = 64, NC = D / 64;            // keys at most, columns of a lane: lane + 64 c
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
     const int b = bh / a.H, h = bh % a.H;
     const float *Kh = (const float *)a.K + b * a.sk.batch + h * a.sk.head, *Vh = (const float *)a.V + b * a.sv.batch + h * a.sv.head;
@@ -319,18 +321,22 @@ __device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualAr
     const int i = top - wave, ic = i > 0 ? i : 0;  // this wave's row
     const int m = a.causal ? ic + 1 : a.n;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const int j = 4 * t + wave;
-        const float v = Kh[(int64_t)(j < mtop ? j : mtop - 1) * a.sk.seq + lane];
-        sm.ks[j][lane] = j < mtop ? v : 0.f;
+    for (int t = 0; t < MK / R; ++t) {
+        const int j = R * t + wave;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const float v = Kh[(int64_t)(j < mtop ? j : mtop - 1) * a.sk.seq + lane + 64 * c];
+            sm.ks[j][lane + 64 * c] = j < mtop ? v : 0.f;
+        }
     }
-    sm.qs[wave][lane] = Qh[(int64_t)ic * a.sq.seq + lane];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sm.qs[wave][lane + 64 * c] = Qh[(int64_t)ic * a.sq.seq + lane + 64 * c];
     __syncthreads();
 
     // products of the keys: tiles (I, J), J <= I, of 16 x 16, dealt over the waves; slot g of a chunk of four is feature 4 kc + g
     {
         const int g = lane / 16, nn = lane % 16, nb = (mtop + 15) / 16;
-        for (int tile = wave; tile < nb * (nb + 1) / 2; tile += 4) {
+        for (int tile = wave; tile < nb * (nb + 1) / 2; tile += R) {
             int I = 0;
             while ((I + 1) * (I + 2) / 2 <= tile) ++I;
             const int J = tile - I * (I + 1) / 2;
@@ -354,7 +360,13 @@ __device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualAr
     double kq = 0.0;
 #pragma unroll 8
     for (int c = 0; c < D; ++c) kq = __builtin_fma((double)sm.qs[wave][c], (double)sm.ks[lane][c], kq);
-    const double ql = (double)sm.qs[wave][lane], qq = wave_sum_f64(ql * ql);
+    double ql[NC], qs2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        ql[c] = (double)sm.qs[wave][lane + 64 * c];
+        qs2 = __builtin_fma(ql[c], ql[c], qs2);
+    }
+    const double qq = wave_sum_f64(qs2);
     const double lg = lane < m ? (double)a.scale * kq : -INFINITY;
     double mx = lg;
 #pragma unroll
@@ -364,9 +376,9 @@ __device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualAr
     // row j of G' + lambda I (see dual_row); rows and columns from m on are zero and never become pivots.  The rows are selected, not
     // multiplied by u = 0: lanes m .. mtop - 1 hold keys behind this row, which need not be finite, and what lanes from 16 nb on
     // find in gram nobody has written in this workgroup.  (With rows of zeros every f, y and u_j t_j from m on is an exact zero.)
-    double x[D];
+    double x[MK];
 #pragma unroll
-    for (int l = 0; l < D; ++l) {
+    for (int l = 0; l < MK; ++l) {
         x[l] = 0.0;
         if (l < m) {                               // (m is uniform: a scalar branch)
             const double g = ((sm.gram[lane][l] - kq) - lane_value(kq, l)) + qq;
@@ -381,7 +393,7 @@ __device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualAr
         const double f = lane == k ? 0.0 : -x[0] * r;
         y = __builtin_fma(f, lane_value(y, k), y);
 #pragma unroll
-        for (int c0 = 0; c0 < D; c0 += 8) {
+        for (int c0 = 0; c0 < MK; c0 += 8) {
             if (k + (c0 > 0 ? c0 : 1) < m) {       // scalar branches
 #pragma unroll
                 for (int c = (c0 > 0 ? c0 : 1); c < c0 + 8; ++c) x[c - 1] = __builtin_fma(f, lane_value(x[c], k), x[c]);
@@ -390,22 +402,32 @@ __device__ __forceinline__ void dual_forward_rows4(DualShared4 &sm, const DualAr
     }
     const double ujt = u * (y * own), ut = wave_sum_f64(ujt), inv = 1.0 / ut;     // u_j t_j: output weight s_j = u_j t_j / (u . t)
 
-    double o = 0.0, rh = 0.0;                      // lane c: column c
-    for (int j0 = 0; j0 < m; j0 += 16) {
-        float v[16];
+    double o[NC], rh[NC];                          // columns lane + 64 c
 #pragma unroll
-        for (int t = 0; t < 16; ++t) v[t] = Vh[(int64_t)(j0 + t < m ? j0 + t : m - 1) * a.sv.seq + lane];
+    for (int c = 0; c < NC; ++c) o[c] = rh[c] = 0.0;
+    for (int j0 = 0; j0 < m; j0 += 16) {
+        float v[16][NC];
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[t][c] = Vh[(int64_t)(j0 + t < m ? j0 + t : m - 1) * a.sv.seq + lane + 64 * c];
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
             if (j0 + t < m) {
                 const double w = lane_value(ujt, j0 + t);
-                o = __builtin_fma(w, (double)v[t], o);
-                rh = __builtin_fma(w, (double)sm.ks[j0 + t][lane] - ql, rh);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    o[c] = __builtin_fma(w, (double)v[t][c], o[c]);
+                    rh[c] = __builtin_fma(w, (double)sm.ks[j0 + t][lane + 64 * c] - ql[c], rh[c]);
+                }
             }
         }
     }
-    st_out((TO *)a.O + b * a.so.batch + h * a.so.head + (int64_t)i * a.so.seq + lane, o * inv);
-    if (a.Rho != nullptr) a.Rho[row * D + lane] = (float)rh;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        st_out((TO *)a.O + b * a.so.batch + h * a.so.head + (int64_t)i * a.so.seq + lane + 64 * c, o[c] * inv);
+        if (a.Rho != nullptr) a.Rho[row * D + lane + 64 * c] = (float)rh[c];
+    }
     if (a.Delta != nullptr && lane == 0) a.Delta[row] = (float)(lam * ut);
 }
 

@@ -243,6 +243,32 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
                 cf[r] = j <= iq ? (j == jstar ? pv + corr : pv) : 0.f;
             }
         }
+        if constexpr (MODE == 2 && DD == 128) {
+            // Where not every query of the wave sees every key of the tile the product multiplies values that a row does not see by zero.  If
+            // one of the tile is not finite, they are left out instead, as on the vector kernels that served d = 128 before (a scalar branch;
+            // at d = 64, where the product has always been taken, its 31 registers cost a workgroup per compute unit and 0.8 % of the call).
+            if (jb + 15 > (causal ? min(i0 + 16 * rg, n - 1) : n - 1)) {
+                auto value = [&](int kr, int J) { return vt[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))]; };
+                bool odd = false;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int J = 0; J < NB; ++J) odd = odd || !(fabsf(value(4 * g + r, J)) < INFINITY);
+                if (__any(odd)) {
+                    for (int gk = 0; gk < 4; ++gk)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {          // key 4 gk + r, query 4 g + e
+                                const float w = __shfl(cf[r], 16 * gk + 4 * g + e);
+                                const bool seen = jb + 4 * gk + r <= (causal ? min(i0 + 16 * rg + 4 * g + e, n - 1) : n - 1);
+#pragma unroll
+                                for (int J = 0; J < NB; ++J) acc[J][e] = seen ? fmaf(w, value(4 * gk + r, J), acc[J][e]) : acc[J][e];
+                            }
+                    continue;
+                }
+            }
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int kr = 4 * g + r;
@@ -484,15 +510,19 @@ hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y,
     if (skip >= p.n) return hipSuccess;
     const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K), *V = static_cast<const float *>(p.V);
     const BlockGrid grid = block_grid((p.n - skip + RT - 1) / RT);
-    hipLaunchKernelGGL((bwd_rows_f32_kernel<64, 2>), dim3(p.B * p.H, grid.y, grid.z), dim3(256), 0, p.stream, Q, K, V,
-                       nullptr, p.sq, p.sk, p.sv, llla_strides{}, p.H, p.n, npad, p.scale, 0.f, nullptr, M, Y, nullptr, nullptr, nullptr,
-                       nullptr, nullptr, p.causal, skip, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(p.B * p.H, grid.y, grid.z), dim3(256), 0, p.stream, Q, K, V, nullptr, p.sq, p.sk, p.sv,
+                           llla_strides{}, p.H, p.n, npad, p.scale, 0.f, nullptr, M, Y, nullptr, nullptr, nullptr, nullptr, nullptr,
+                           p.causal, skip, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0);
+    };
+    if (p.d == 128) launch(bwd_rows_f32_kernel<128, 2>);
+    else launch(bwd_rows_f32_kernel<64, 2>);
     return hipGetLastError();
 }
 
 bool mfma_backward_f32_supported(int n, int d, llla_dtype in)
 {
-    return in == LLLA_F32 && (d == 16 || d == 32 || d == 64) && (n + RT - 1) / RT <= 65535;
+    return in == LLLA_F32 && (d == 16 || d == 32 || d == 64 || d == 128) && (n + RT - 1) / RT <= 65535;
 }
 
 size_t mfma_backward_f32_workspace_bytes(int B, int H, int n, int d) { return make_bwd_f32_layout(B, H, n, d).total; }
@@ -519,8 +549,8 @@ hipError_t launch_backward_f32(const BackwardProblem &p)
         pm.sq = pm.sk = llla_strides{(int64_t)p.H * p.n * 64, (int64_t)p.n * 64, 64};
         pm.live_d = DD;
     }
-    e = mfma_moments_f32_given(pm, L.npad, reinterpret_cast<float *>(ws + L.m), reinterpret_cast<float *>(ws + L.y),
-                               reinterpret_cast<float *>(ws + L.ru));
+    float *M = reinterpret_cast<float *>(ws + L.m), *Yw = reinterpret_cast<float *>(ws + L.y), *RU = reinterpret_cast<float *>(ws + L.ru);
+    e = DD == 128 ? mfma_moments_f32_wide_given(pm, L.npad, M, Yw, RU) : mfma_moments_f32_given(pm, L.npad, M, Yw, RU);
     if (e != hipSuccess) return e;
     stage_mark(p.stream, "backward_dq");
     e = launch_rows<DD, 1>(p, L);
@@ -536,7 +566,8 @@ hipError_t launch_backward_f32(const BackwardProblem &p)
 
 hipError_t mfma_backward_f32(const BackwardProblem &p)
 {
-    return p.d == 16 ? launch_backward_f32<16>(p) : p.d == 32 ? launch_backward_f32<32>(p) : launch_backward_f32<64>(p);
+    return p.d == 16 ? launch_backward_f32<16>(p) : p.d == 32 ? launch_backward_f32<32>(p)
+           : p.d == 64 ? launch_backward_f32<64>(p) : launch_backward_f32<128>(p);
 }
 
 }  // namespace llla

@@ -106,11 +106,12 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     if constexpr (!BWD) {
         const int own = nqb - (da.nrows + QB - 1) / QB;
         if (bm.blk >= own) {
-            static_assert(sizeof(dual::DualShared4) <= sizeof(F32Shared), "key-space rows fit the workgroup's LDS");
-            auto &ds = *reinterpret_cast<dual::DualShared4 *>(&sm);
+            using DS = dual::DualSharedRows<FD, 4>;
+            static_assert(sizeof(DS) <= sizeof(F32Shared), "key-space rows fit the workgroup's LDS");
+            auto &ds = *reinterpret_cast<DS *>(&sm);
             const int top = da.nrows - 1 - 4 * (bm.blk - own);
-            if (out_bf16) dual::dual_forward_rows4<bf16_t>(ds, da, bh, top);
-            else dual::dual_forward_rows4<float>(ds, da, bh, top);
+            if (out_bf16) dual::dual_forward_rows<FD, 4, bf16_t>(ds, da, bh, top);
+            else dual::dual_forward_rows<FD, 4, float>(ds, da, bh, top);
             return;
         }
     }
