@@ -180,8 +180,11 @@ def _strides4(*tensors) -> list:
 
 
 def _stream_ptr(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    """The handle of ``stream``, or of the current device's current stream.  The handle is all that is needed: building a torch Stream object
+    for it was a fifth of the host's time of a call (1 head x 128 rows, fp32, d = 16: 14.0 -> 11.3 us a call)."""
+    if stream is not None:
+        return int(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _workspace(nbytes: int, device, workspace):
