@@ -73,7 +73,9 @@ __device__ inline int row_swizzle(int r)
     return ((r & 7) << 1) | ((r >> 3) & 1);
 }
 
-template <int DD, int NK>
+// LIVE < NB (a d = 16 / 32 call on zero-padded copies): features and value columns from 16 LIVE on are zero; the contractions stop after
+// the chunks that hold live ones, and only live columns are formed and stored, in rows of 16 LIVE.  The same in the row sweeps below.
+template <int DD, int NK, int LIVE = Shape<DD>::NB>
 __global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfma_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfm
     float *__restrict__ dK, float *__restrict__ dV)
 {
     using S = Shape<DD>;
-    constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
+    constexpr int NF = (16 * LIVE + 31) / 32, NB = LIVE, YP = S::YP;
     constexpr int CH = DD / 8;                           // 16-byte chunks per row
     constexpr int TILE = QS * DD;                        // halves
     constexpr int NBUF = DD == 64 ? 2 : 1;               // 50 KB per workgroup
@@ -352,7 +354,7 @@ __global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfm
         for (int r = 0; r < 4; ++r) {
             const int key = jw + 16 * k + 4 * g + r;
             if (key < n) {
-                const size_t off = ((size_t)bh * n + key) * DD + nn;
+                const size_t off = ((size_t)bh * n + key) * (16 * LIVE) + nn;
 #pragma unroll
                 for (int J = 0; J < NB; ++J) {
                     dK[off + 16 * J] = dk[k][J][r];
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfm
 // barriers 493 us, one block ahead 480, three 434).  MODE 0, bound by its vector work, has two stages and the loop unrolled
 // over them (341 -> 307; three blocks ahead 319), and NQ = 2 blocks of 16 queries per wave from TWO_QUERY_BLOCKS_FROM workgroups of 128
 // rows on (328 -> 310; 64 x 2048 102 -> 106, 96 x 1000 47 -> 55).
-template <int DD, int MODE, int NQ, int TERMS = 2>
+template <int DD, int MODE, int NQ, int TERMS = 2, int LIVE = Shape<DD>::NB>
 __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
     const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
@@ -390,7 +392,7 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
     float *Yg, float *Ug, float *__restrict__ Rv, float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam)
 {
     using S = Shape<DD>;
-    constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
+    constexpr int NF = (16 * LIVE + 31) / 32, NB = LIVE, YP = S::YP;
     constexpr int CH = DD / 8, TILE = KB * DD, RPT = 64 / CH, NTR = KB / RPT / 4;     // as in the key sweep
     constexpr int NST = MODE == 0 ? 2 : 4;               // blocks in LDS: the one in use and NST - 1 on their way
     __shared__ __align__(16) bf16_t kt[NST][TILE], vt[NST][TILE];
@@ -656,7 +658,7 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
 #pragma unroll
                 for (int J = 0; J < NB; ++J) {
                     if (MODE == 0) Rv[ro * YP + 16 * J + nn] = acc[q][J][r];
-                    else dQ[ro * DD + 16 * J + nn] = fmaf(scale, acc[q][J][r], Ug[ro * YP + 16 * J + nn]);
+                    else dQ[ro * (16 * LIVE) + 16 * J + nn] = fmaf(scale, acc[q][J][r], Ug[ro * YP + 16 * J + nn]);
                 }
             }
         }
@@ -865,7 +867,7 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
 
 constexpr long long TWO_QUERY_BLOCKS_FROM = 1536, TWO_KEY_BLOCKS_FROM = 768;
 
-template <int DD, int MODE>
+template <int DD, int MODE, int LIVE = Shape<DD>::NB>
 hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int early)
 {
     char *base = static_cast<char *>(p.ws);
@@ -881,13 +883,24 @@ hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int ea
                            p.lambda, p.lambda_rows, M, Y, U, R, Sc, p.dQ, p.dlambda);
         return hipGetLastError();
     };
-    const hipError_t e = launch(bwd_rows_mfma_kernel<DD, MODE, 1, 3>, 64, 0, early);
+    const hipError_t e = launch(bwd_rows_mfma_kernel<DD, MODE, 1, 3, LIVE>, 64, 0, early);
     if (e != hipSuccess || early >= p.n) return e;
     if constexpr (DD == 64 && MODE == 0) {
         if ((long long)p.B * p.H * ((p.n - early + 127) / 128) >= TWO_QUERY_BLOCKS_FROM)
-            return launch(bwd_rows_mfma_kernel<64, 0, 2>, 128, early, p.n);
+            return launch(bwd_rows_mfma_kernel<64, 0, 2, 2, LIVE>, 128, early, p.n);
     }
-    return launch(bwd_rows_mfma_kernel<DD, MODE, 1>, 64, early, p.n);
+    return launch(bwd_rows_mfma_kernel<DD, MODE, 1, 2, LIVE>, 64, early, p.n);
+}
+
+// 16-feature blocks that can be non-zero (fewer than d / 16 on the zero-padded copies of a d = 16 / 32 call)
+int live_blocks(int d, int live_d) { return d == 64 && live_d > 0 ? (live_d + 15) / 16 : d / 16; }
+
+template <int MODE>
+hipError_t rows(const BackwardProblem &p, const BackwardLayout &L, int early)
+{
+    if (p.d != 64) return launch_rows<128, MODE>(p, L, early);
+    const int live = live_blocks(p.d, p.live_d);
+    return live == 1 ? launch_rows<64, MODE, 1>(p, L, early) : live == 2 ? launch_rows<64, MODE, 2>(p, L, early) : launch_rows<64, MODE>(p, L, early);
 }
 
 }  // namespace
@@ -895,12 +908,12 @@ hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int ea
 // early: the rows at the beginning that take three-term operands, a multiple of 64 or all
 hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int early)
 {
-    return p.d == 64 ? launch_rows<64, 0>(p, L, early) : launch_rows<128, 0>(p, L, early);
+    return rows<0>(p, L, early);
 }
 
 hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int early)
 {
-    return p.d == 64 ? launch_rows<64, 1>(p, L, early) : launch_rows<128, 1>(p, L, early);
+    return rows<1>(p, L, early);
 }
 
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L)
@@ -915,9 +928,12 @@ hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L)
         hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (p.n + keys - 1) / keys), dim3(256), 0, p.stream, Q, K, V, G, p.sq, p.sk, p.sv, p.sdo,
                            p.H, p.n, p.scale, Y, U, Sc, p.dK, p.dV);
     };
+    const bool two = (long long)p.B * p.H * ((p.n + 127) / 128) >= TWO_KEY_BLOCKS_FROM;
+    const int live = live_blocks(p.d, p.live_d);
     if (p.d != 64) launch(bwd_keys_mfma_kernel<128, 1>, 64);
-    else if ((long long)p.B * p.H * ((p.n + 127) / 128) >= TWO_KEY_BLOCKS_FROM) launch(bwd_keys_mfma_kernel<64, 2>, 128);
-    else launch(bwd_keys_mfma_kernel<64, 1>, 64);
+    else if (live == 1) two ? launch(bwd_keys_mfma_kernel<64, 2, 1>, 128) : launch(bwd_keys_mfma_kernel<64, 1, 1>, 64);
+    else if (live == 2) two ? launch(bwd_keys_mfma_kernel<64, 2, 2>, 128) : launch(bwd_keys_mfma_kernel<64, 1, 2>, 64);
+    else two ? launch(bwd_keys_mfma_kernel<64, 2>, 128) : launch(bwd_keys_mfma_kernel<64, 1>, 64);
     return hipGetLastError();
 }
 
@@ -929,7 +945,7 @@ hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const 
                            static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V), p.sq, p.sk, p.sv, p.H, p.n, r0, mpitch,
                            p.scale * LOG2E, M, Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0, p.causal);
     };
-    const int live = p.d == 64 && p.live_d > 0 ? (p.live_d + 15) / 16 : p.d / 16;
+    const int live = live_blocks(p.d, p.live_d);
     if (live == 1) three_terms ? launch(out_rows_kernel<64, 1, 3>) : launch(out_rows_kernel<64, 1>);
     else if (live == 2) three_terms ? launch(out_rows_kernel<64, 2, 3>) : launch(out_rows_kernel<64, 2>);
     else if (p.d == 64) three_terms ? launch(out_rows_kernel<64, 4, 3>) : launch(out_rows_kernel<64>);

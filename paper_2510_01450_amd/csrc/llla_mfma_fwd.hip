@@ -365,7 +365,7 @@ __device__ inline BlockMap moments_block()
 // returns u = M^{-1} [r0; r1] in Ug, laid out like Yg.
 // LIVE: feature blocks of 16 that can be non-zero (all of them, except for calls at d = 16 / 32 that run here on
 // zero-padded copies: tiles of Sigma~ with a padded block stay at their starting value, 0 or -lambda on the diagonal, so
-// neither their MFMAs nor the scaled operands of padded blocks are issued).
+// neither their MFMAs nor the scaled operands of padded blocks are issued, and rho is written in rows of 16 LIVE).
 template <bool PRECISE, int DD, bool WITH_U = false, int LIVE = Shape<DD>::NB>
 __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t *__restrict__ Qg,
                                              const bf16_t *__restrict__ Kg, llla_strides sq, llla_strides sk, int H,
@@ -918,7 +918,7 @@ __device__ __forceinline__ void moments_body(MomentsShared<DD> &sm, const bf16_t
                     if (delta != nullptr && nn == 0) delta[at] = dl;
                     if (rho != nullptr) {
 #pragma unroll
-                        for (int P = 0; P < NB; ++P) rho[at * DD + 16 * P + nn] = -dl * y1[P];
+                        for (int P = 0; P < LIVE; ++P) rho[at * (16 * LIVE) + 16 * P + nn] = -dl * y1[P];
                     }
                 }
             }
@@ -1296,8 +1296,12 @@ hipError_t backward_rowmax_impl(const BackwardProblem &p, const BackwardLayout &
     stage_mark(p.stream, "prep");
     hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, nullptr, p.sk, p.sk, p.H, p.n, L.nkb, KT, nullptr);
     stage_mark(p.stream, "rowmax");
-    hipLaunchKernelGGL((sweep_kernel<true, DD>), dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H,
-                       p.n, L.nkb, 0, p.scale * LOG2E, nullptr, M, Y, (void *)nullptr, llla_strides{0, 0, 0}, 0, (float *)nullptr);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb, 0, p.scale * LOG2E,
+                           nullptr, M, Y, nullptr, llla_strides{0, 0, 0}, 0, nullptr, 1);
+    };
+    if (DD == 64 && p.live_d > 0 && p.live_d <= 32) launch(sweep_kernel<true, 64, 2>);       // (d = 16: the same chunk of 32 features)
+    else launch(sweep_kernel<true, DD>);
     return hipGetLastError();
 }
 
