@@ -9,6 +9,17 @@
 
 namespace llla {
 
+// The tensors of a d = 16 / 32 call and their copies in rows of 64 features, zero from d on (llla_pad.hip)
+struct PadSource {
+    const char *src;           // [B,H,n,d], strides s in elements
+    uint4 *dst;                // [B*H*n, 64] contiguous
+    llla_strides s;
+};
+struct PadSources {
+    PadSource t[4];            // Q, K, V, dO
+    int count;
+};
+
 // One forward or decode problem, as validated by the C ABI layer.
 struct Problem {
     const void *Q, *K, *V;     // forward: [B,H,n,d]; decode: Q = q [B,H,d], K/V = caches [B,H,n,d]
@@ -19,6 +30,7 @@ struct Problem {
     llla_dtype in, out;
     int causal;
     int live_d;                // forward on zero-padded copies: features [live_d, d) are zero in Q and K; 0 = none are
+    const PadSources *pad;     // bf16: Q, K and V are copies that the call has yet to make from these; or nullptr
     float lambda, scale;
     const float *lambda_rows;  // forward only: [B,H,n] ridge per query row, or nullptr (then `lambda` for all rows)
     float *rho, *delta;        // forward only: optional outputs [B,H,n,d] and [B,H,n] (Eq. (lla)), or nullptr
@@ -35,6 +47,7 @@ struct BackwardProblem {
     float *dlambda;              // [B,H,n] or nullptr
     int B, H, n, d;
     int live_d;                  // on zero-padded copies: features [live_d, d) of Q and K are zero; 0 = none are
+    const PadSources *pad;       // bf16: Q, K, V and dO are copies that the call has yet to make from these; or nullptr
     llla_dtype in;
     float lambda, scale;
     const float *lambda_rows;    // [B,H,n] or nullptr
@@ -166,6 +179,26 @@ __host__ __device__ inline bf16_t f32_to_bf16(float f)
     if ((c.u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((c.u >> 16) | 0x40);
     c.u += 0x7fffu + ((c.u >> 16) & 1u);
     return (bf16_t)(c.u >> 16);
+}
+
+// 16-byte chunk `id` of a padded tensor: chunks inside the original row are copied, the others cleared.  ESZ = bytes per element.
+template <int ESZ>
+__device__ __forceinline__ void pad_chunk(const PadSource &t, size_t id, int H, int n, int d, size_t nchunks)
+{
+    constexpr int CPR = 64 * ESZ / 16;                      // chunks per padded row
+    if (id >= nchunks) return;
+    const size_t row = id / CPR;
+    const int c = (int)(id % CPR);
+    const int i = (int)(row % n);
+    const size_t bh = row / n;
+    const int h = (int)(bh % H);
+    const int64_t b = (int64_t)(bh / H);
+    uint4 v = {0u, 0u, 0u, 0u};
+    if (c * 16 < d * ESZ) {
+        const int64_t e = b * t.s.batch + (int64_t)h * t.s.head + (int64_t)i * t.s.seq;
+        v = *reinterpret_cast<const uint4 *>(t.src + e * ESZ + c * 16);
+    }
+    t.dst[id] = v;
 }
 
 __host__ __device__ inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

@@ -48,15 +48,15 @@ Layout make_layout(int B, int H, int n, bool with_v = false)
 }
 
 // ------------------------------------------------------------------------------------------------
-// prep: re-tile K (-> f16) and, WITH_V, V (bf16) as [bh][key block][feature][32 keys]
+// prep: re-tile K (-> f16) and, WITH_V, V (bf16) as [bh][key block][feature][32 keys]; features from `width` on, which the rows do not
+// have, are zero
 template <int DD, bool WITH_V = false>
-__global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
-                                                   llla_strides sk, llla_strides sv, int H, int n, int nkb,
-                                                   _Float16 *__restrict__ KT, bf16_t *__restrict__ VT)
+__device__ __forceinline__ void prep_block(const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg, llla_strides sk, llla_strides sv,
+                                           int H, int n, int nkb, _Float16 *__restrict__ KT, bf16_t *__restrict__ VT, int width, int blk, int bh)
 {
     constexpr int NT = WITH_V ? 2 : 1;
     __shared__ bf16_t tile[NT][KB][DD + 2];
-    const int blk = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh % H, tid = threadIdx.x;
+    const int b = bh / H, h = bh % H, tid = threadIdx.x;
     const bf16_t *head[2] = {Kg + b * sk.batch + h * sk.head, WITH_V ? Vg + b * sv.batch + h * sv.head : nullptr};
     const int64_t pitch[2] = {sk.seq, sv.seq};
     for (int idx = tid; idx < KB * (DD / 8); idx += 256) {
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg
 #pragma unroll
         for (int m = 0; m < NT; ++m) {
             x[m] = make_uint4(0, 0, 0, 0);
-            if (j < n) x[m] = *reinterpret_cast<const uint4 *>(head[m] + (int64_t)j * pitch[m] + ch);
+            if (j < n && ch < width) x[m] = *reinterpret_cast<const uint4 *>(head[m] + (int64_t)j * pitch[m] + ch);
         }
 #pragma unroll
         for (int m = 0; m < NT; ++m) {
@@ -96,22 +96,29 @@ __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg
     }
 }
 
+template <int DD, bool WITH_V = false>
+__global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
+                                                   llla_strides sk, llla_strides sv, int H, int n, int nkb,
+                                                   _Float16 *__restrict__ KT, bf16_t *__restrict__ VT)
+{
+    prep_block<DD, WITH_V>(Kg, Vg, sk, sv, H, n, nkb, KT, VT, DD, blockIdx.x, blockIdx.y);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Sweep over S^T = K Q^T for 64 queries per workgroup (16 per wave).
 //   MAXONLY: write the row maxima m_i (in log2 units) -- Algorithm 1's m after its last block.
 //   else   : third loop of Algorithm 1: S = W (y0 + K y1), O = S V, for the approximate mode (the exact forward: out_rows_kernel).
 constexpr int VT_PITCH = KB + 8;     // halves
 
-// LIVE < NB (a d = 16 / 32 call on zero-padded copies): features and value columns from 16 LIVE on are zero, so the
-// contractions over features stop after the chunks that hold live ones and only LIVE output tiles are formed and stored.
+// LIVE < NB (MAXONLY, a d = 16 / 32 call): the rows of Q and K have 16 LIVE features, those beyond are zero and not read.
 template <bool MAXONLY, int DD, int LIVE = Shape<DD>::NB>
-__global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg,
-                                                    llla_strides sq, llla_strides sk, int H, int n, int nkb,
-                                                    int first_row, float cscale, const bf16_t *__restrict__ VT,
-                                                    float *__restrict__ Mg, const float *__restrict__ Yg,
-                                                    void *__restrict__ Og, llla_strides so, int out_bf16,
-                                                    float *__restrict__ Csum = nullptr, int causal = 1)
+__device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq, llla_strides sk,
+                                           int H, int n, int nkb, int first_row, float cscale, const bf16_t *__restrict__ VT,
+                                           float *__restrict__ Mg, const float *__restrict__ Yg, void *__restrict__ Og, llla_strides so,
+                                           int out_bf16, float *__restrict__ Csum, int causal, int bh, int yblk, int nqb)
 {
+    static_assert(MAXONLY || LIVE == Shape<DD>::NB, "the padded calls' output sweep is out_rows_kernel");
+    constexpr int WIDTH = 16 * LIVE;
     // !MAXONLY is a general "coefficients times a tile" sweep: O_i = sum_j w_ij (y0_i + k_j . y1_i) t_j with the rows t_j
     // of whatever VT holds (V for the output; K for the first moment and for the matrix-free product of the
     // approximate mode).  Yg == nullptr means y0 = 1, y1 = 0 (plain weights); Csum, if given, receives sum_j of the
@@ -126,9 +133,8 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
     // start first and the short ones fill the tail.  (With the head on y the last head's longest block ran alone at the
     // end; with the XCD-grouped mapping of the moments kernel a head's 64-row blocks all start at once and the XCD
     // waits for the longest: both measured slower.)  Heads that are a multiple of 8 apart share an XCD and its L2.
-    const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int nqb = gridDim.y;
-    const int i0 = first_row + (nqb - 1 - (int)blockIdx.y) * 64;
+    const int b = bh / H, h = bh % H;
+    const int i0 = first_row + (nqb - 1 - yblk) * 64;
     const int iq = i0 + wave * 16 + nn;                                // this lane's query
     const int iqc = min(iq, n - 1);
     const int jlim = causal ? iq : n - 1;                              // last key this lane's query sees
@@ -136,7 +142,11 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
     const bf16_t *qrow = Qg + b * sq.batch + h * sq.head + (int64_t)iqc * sq.seq;
     bf16x8 qf[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) qf[f] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * f + 8 * g);
+    for (int f = 0; f < NF; ++f) {
+        uint4 u = make_uint4(0, 0, 0, 0);
+        if (32 * f + 31 < WIDTH || 32 * f + 8 * g < WIDTH) u = *reinterpret_cast<const uint4 *>(qrow + 32 * f + 8 * g);
+        qf[f] = __builtin_bit_cast(bf16x8, u);
+    }
     // Row maxima: max_j c <q, k_j> = |c| max_j <sign(c) q, k_j>, so the sign of the scale goes into the query operand
     // once (a flip of the bf16 sign bits) and the sweep keeps the maximum of the RAW products, one three-input maximum
     // per two logits; |c| is applied to the result.  (Scaling every logit first was two vector instructions per logit
@@ -193,7 +203,7 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
             const int key = idx / (DD / 8), ch = (idx % (DD / 8)) * 8;
             const int j = c * KB + key;
             kpre[u] = make_uint4(0, 0, 0, 0);
-            if (j < n) kpre[u] = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
+            if (j < n && (WIDTH == DD || ch < WIDTH)) kpre[u] = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
             if (!MAXONLY) {
                 const int feat = idx / 4, k0 = (idx % 4) * 8;
                 vpre[u] = *reinterpret_cast<const uint4 *>(VT + ((size_t)bh * nkb + c) * (DD * KB) + feat * KB + k0);
@@ -317,6 +327,80 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
             }
         }
     }
+}
+
+template <bool MAXONLY, int DD>
+__global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg,
+                                                    llla_strides sq, llla_strides sk, int H, int n, int nkb,
+                                                    int first_row, float cscale, const bf16_t *__restrict__ VT,
+                                                    float *__restrict__ Mg, const float *__restrict__ Yg,
+                                                    void *__restrict__ Og, llla_strides so, int out_bf16,
+                                                    float *__restrict__ Csum = nullptr, int causal = 1)
+{
+    sweep_rows<MAXONLY, DD>(Qg, Kg, sq, sk, H, n, nkb, first_row, cscale, VT, Mg, Yg, Og, so, out_bf16, Csum, causal, blockIdx.x, blockIdx.y,
+                            gridDim.y);
+}
+
+// ------------------------------------------------------------------------------------------------
+// All that a forward or backward call does before its moments, in one launch: row maxima (the first workgroups, longest rows first),
+// K re-tiled, and, in a d = 16 / 32 call, the padded copies, which the sweep and the re-tiling do not wait for: they read the rows
+// of 16 LIVE features themselves.  None reads what another writes.  A launch of a small call costs 3 to 5 us however little it does.
+// us a call, three launches (two at d = 64 / 128) against one: 1 x 12 heads x 157, d = 32, 29.7 and 24.7; 3 x 16 x 1606, d = 32, with statistics
+// 250 and 236; 24 x 4 x 81, d = 32, backward 48.4 and 43.7; 2 x 105, d = 64, 32.2 and 30.4; 96 x 157 with statistics 77.9 and 75.5; 8 x 44,
+// d = 128, 50.6 and 48.0; 64 x 4096 the same.
+struct FrontGrid {
+    long long rowmax, prep, pad, total;      // workgroups of each kind
+    int nq64, npad;                          // row blocks per head; tensors to pad
+    unsigned pad_blocks;                     // workgroups per tensor
+};
+
+template <int DD, int LIVE>
+__global__ __launch_bounds__(256, 2) void front_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq,
+                                                       llla_strides sk, int H, int nbh, int n, int nkb, float cscale, _Float16 *__restrict__ KT,
+                                                       float *__restrict__ Mg, int causal, FrontGrid grid, PadSources pad)
+{
+    long long id = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    if (id < grid.rowmax) {
+        sweep_rows<true, DD, LIVE>(Qg, Kg, sq, sk, H, n, nkb, 0, cscale, nullptr, Mg, nullptr, nullptr, llla_strides{}, 0, nullptr, causal,
+                                   (int)(id % nbh), (int)(id / nbh), grid.nq64);
+        return;
+    }
+    id -= grid.rowmax;
+    if (id < grid.prep) {
+        prep_block<DD>(Kg, nullptr, sk, sk, H, n, nkb, KT, nullptr, 16 * LIVE, (int)(id % nkb), (int)(id / nkb));
+        return;
+    }
+    id -= grid.prep;
+    if constexpr (LIVE < Shape<DD>::NB) {
+        if (id < grid.pad) pad_chunk<2>(pad.t[id / grid.pad_blocks], (size_t)(id % grid.pad_blocks) * 256 + threadIdx.x, H, n, 16 * LIVE, (size_t)nbh * n * (DD / 8));
+    }
+}
+
+// p: Problem or BackwardProblem
+template <int DD, typename P>
+hipError_t launch_front(const P &p, int nkb, _Float16 *KT, float *M, int causal)
+{
+    const int bh = p.B * p.H, count = p.pad ? p.pad->count : 0;
+    FrontGrid g{};
+    g.nq64 = (p.n + 63) / 64;
+    g.rowmax = (long long)bh * g.nq64;
+    g.prep = (long long)bh * nkb;
+    g.pad_blocks = (unsigned)(((size_t)bh * p.n * (DD / 8) + 255) / 256);
+    g.pad = (long long)count * g.pad_blocks;
+    g.total = g.rowmax + g.prep + g.pad;
+    const long long width = g.total < (1 << 20) ? g.total : 1 << 20;
+    const dim3 grid((unsigned)width, (unsigned)((g.total + width - 1) / width));
+    const PadSources none{}, &pad = p.pad ? *p.pad : none;
+    const bf16_t *Q = static_cast<const bf16_t *>(p.pad ? pad.t[0].src : p.Q), *K = static_cast<const bf16_t *>(p.pad ? pad.t[1].src : p.K);
+    const llla_strides sq = p.pad ? pad.t[0].s : p.sq, sk = p.pad ? pad.t[1].s : p.sk;
+    stage_mark(p.stream, "front");
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, p.stream, Q, K, sq, sk, p.H, bh, p.n, nkb, p.scale * LOG2E, KT, M, causal, g, pad);
+    };
+    if (p.pad && p.live_d == 16) launch(front_kernel<64, 1>);
+    else if (p.pad) launch(front_kernel<64, 2>);
+    else launch(front_kernel<DD, Shape<DD>::NB>);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1038,7 +1122,6 @@ hipError_t forward_impl(const Problem &p)
     const Layout L = make_layout<DD>(p.B, p.H, p.n);
     char *ws = static_cast<char *>(p.ws);
     _Float16 *KT = reinterpret_cast<_Float16 *>(ws + L.kt);
-    const bf16_t *VT = nullptr;                     // the sweep for the maxima reads no values
     float *M = reinterpret_cast<float *>(ws + L.m);
     float *Y = reinterpret_cast<float *>(ws + L.y);
     const int bh = p.B * p.H;
@@ -1050,21 +1133,8 @@ hipError_t forward_impl(const Problem &p)
     const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K);
     // a call at d = 16 / 32 on zero-padded copies (live_d features can be non-zero): the variants that skip padded tiles
     const int live = (DD == 64 && p.live_d > 0) ? (p.live_d + 15) / 16 : S::NB;
-    stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, nullptr, p.sk, p.sk, p.H, p.n, L.nkb, KT, nullptr);
-    const int nq64 = (p.n + 63) / 64;
-    stage_mark(p.stream, "rowmax");
-    if constexpr (DD == 64) {
-        if (live == 1)
-            hipLaunchKernelGGL((sweep_kernel<true, DD, 1>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
-                               L.nkb, 0, cscale, VT, M, Y, p.O, p.so, 0, (float *)nullptr, p.causal);
-        else if (live == 2)
-            hipLaunchKernelGGL((sweep_kernel<true, DD, 2>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
-                               L.nkb, 0, cscale, VT, M, Y, p.O, p.so, 0, (float *)nullptr, p.causal);
-    }
-    if (live == S::NB)
-        hipLaunchKernelGGL((sweep_kernel<true, DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
-                           0, cscale, VT, M, Y, p.O, p.so, 0, (float *)nullptr, p.causal);
+    const hipError_t e = launch_front<DD>(p, L.nkb, KT, M, p.causal);
+    if (e != hipSuccess) return e;
     const int nqb = (p.n + S::QB - 1) / S::QB;
     stage_mark(p.stream, "moments");
     if constexpr (DD == 64) {
@@ -1288,21 +1358,7 @@ hipError_t backward_rowmax_impl(const BackwardProblem &p, const BackwardLayout &
 {
     const Layout L = make_layout<DD>(p.B, p.H, p.n);
     char *ws = static_cast<char *>(p.ws) + BL.fwd;
-    _Float16 *KT = reinterpret_cast<_Float16 *>(ws + L.kt);
-    float *M = reinterpret_cast<float *>(ws + L.m);
-    float *Y = reinterpret_cast<float *>(ws + L.y);
-    const int bh = p.B * p.H;
-    const bf16_t *Q = static_cast<const bf16_t *>(p.Q), *K = static_cast<const bf16_t *>(p.K);
-    stage_mark(p.stream, "prep");
-    hipLaunchKernelGGL((prep_kernel<DD>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, nullptr, p.sk, p.sk, p.H, p.n, L.nkb, KT, nullptr);
-    stage_mark(p.stream, "rowmax");
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(bh, (p.n + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb, 0, p.scale * LOG2E,
-                           nullptr, M, Y, nullptr, llla_strides{0, 0, 0}, 0, nullptr, 1);
-    };
-    if (DD == 64 && p.live_d > 0 && p.live_d <= 32) launch(sweep_kernel<true, 64, 2>);       // (d = 16: the same chunk of 32 features)
-    else launch(sweep_kernel<true, DD>);
-    return hipGetLastError();
+    return launch_front<DD>(p, L.nkb, reinterpret_cast<_Float16 *>(ws + L.kt), reinterpret_cast<float *>(ws + L.m), 1);
 }
 
 template <int DD>

@@ -43,39 +43,14 @@ PadLayout make_pad_layout(int B, int H, int n, llla_dtype in, bool cg = false)
     return L;
 }
 
-// One thread per 16-byte chunk of a padded row, blockIdx.y the tensor: chunks inside the original row are copied, the others cleared.
-// src: [B,H,n,d] with strides (elements); dst: [B*H*n, PD] contiguous.  ESZ = bytes per element.
-//
+// One thread per 16-byte chunk of a padded row, blockIdx.y the tensor.
 // All tensors of a call in one launch, on the way in and on the way out: a copy of a small call takes 5 us, nearly all of it the
-// launch.  60 heads x 68 rows, d = 32, bf16, forward: 37.3 -> 29.4 us a call; 4 heads x 1871, d = 16, backward: 265 -> 255.
-struct PadSource {
-    const char *src;
-    uint4 *dst;
-    llla_strides s;
-};
-struct PadSources {
-    PadSource t[4];
-};
-
+// launch.  60 heads x 68 rows, d = 32, bf16, forward: 37.3 -> 29.4 us a call; 4 heads x 1871, d = 16, backward: 265 -> 255.  (The exact
+// bf16 calls make theirs in the launch that forms the row maxima.)
 template <int ESZ>
 __global__ __launch_bounds__(256) void pad_rows_kernel(PadSources a, int H, int n, int d, size_t nchunks)
 {
-    constexpr int CPR = PD * ESZ / 16;                      // chunks per padded row
-    const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= nchunks) return;
-    const PadSource &t = a.t[blockIdx.y];
-    const size_t row = id / CPR;
-    const int c = (int)(id % CPR);
-    const int i = (int)(row % n);
-    const size_t bh = row / n;
-    const int h = (int)(bh % H);
-    const int64_t b = (int64_t)(bh / H);
-    uint4 v = {0u, 0u, 0u, 0u};
-    if (c * 16 < d * ESZ) {
-        const int64_t e = b * t.s.batch + (int64_t)h * t.s.head + (int64_t)i * t.s.seq;
-        v = *reinterpret_cast<const uint4 *>(t.src + e * ESZ + c * 16);
-    }
-    t.dst[id] = v;
+    pad_chunk<ESZ>(a.t[blockIdx.y], (size_t)blockIdx.x * 256 + threadIdx.x, H, n, d, nchunks);
 }
 
 // The first d elements of every padded row back into a strided [B,H,n,d] tensor, one 16-byte chunk per thread.  A destination whose
@@ -119,10 +94,10 @@ struct Rows {
     hipStream_t stream;
 };
 
-hipError_t pad_rows(const PadSources &a, int count, const Rows &r, bool f32)
+hipError_t pad_rows(const PadSources &a, const Rows &r, bool f32)
 {
     const size_t rows = (size_t)r.B * r.H * r.n, nch = rows * (PD * (f32 ? 4 : 2) / 16);
-    const dim3 grid((unsigned)((nch + 255) / 256), count);
+    const dim3 grid((unsigned)((nch + 255) / 256), a.count);
     if (f32) pad_rows_kernel<4><<<grid, dim3(256), 0, r.stream>>>(a, r.H, r.n, r.d, nch);
     else pad_rows_kernel<2><<<grid, dim3(256), 0, r.stream>>>(a, r.H, r.n, r.d, nch);
     return hipGetLastError();
@@ -177,8 +152,8 @@ PadBackwardLayout make_pad_backward_layout(int B, int H, int n)
 
 hipError_t pad_queries_keys(const BackwardProblem &p, void *Q, void *K)
 {
-    const PadSources in = {{pad_source(p.Q, p.sq, Q), pad_source(p.K, p.sk, K)}};
-    return pad_rows(in, 2, Rows{p.B, p.H, p.n, p.d, p.stream}, p.in == LLLA_F32);
+    const PadSources in = {{pad_source(p.Q, p.sq, Q), pad_source(p.K, p.sk, K)}, 2};
+    return pad_rows(in, Rows{p.B, p.H, p.n, p.d, p.stream}, p.in == LLLA_F32);
 }
 
 bool padded_forward_supported(int d, llla_dtype in)
@@ -200,12 +175,7 @@ hipError_t padded_forward(const Problem &p)
     char *ws = static_cast<char *>(p.ws);
     const llla_strides sp = {(int64_t)p.H * p.n * PD, (int64_t)p.n * PD, (int64_t)PD};
 
-    const Rows r{p.B, p.H, p.n, p.d, p.stream};
-    stage_mark(p.stream, "pad");
-    const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v)}};
-    hipError_t e = pad_rows(in, 3, r, p.in == LLLA_F32);
-    if (e != hipSuccess) return e;
-
+    const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v)}, 3};
     Problem q = p;
     q.Q = ws + L.q; q.K = ws + L.k; q.V = ws + L.v;
     q.sq = q.sk = q.sv = sp;
@@ -213,7 +183,14 @@ hipError_t padded_forward(const Problem &p)
     q.live_d = p.d;
     q.ws = ws + L.inner;
     q.ws_bytes = L.total - L.inner;
-    if (p.in != LLLA_F32) return mfma_forward(q);
+    if (p.in != LLLA_F32) {
+        q.pad = &in;
+        return mfma_forward(q);
+    }
+    const Rows r{p.B, p.H, p.n, p.d, p.stream};
+    stage_mark(p.stream, "pad");
+    hipError_t e = pad_rows(in, r, true);
+    if (e != hipSuccess) return e;
     q.O = ws + L.o;
     q.so = sp;
     q.rho = p.rho ? reinterpret_cast<float *>(ws + L.rho) : nullptr;
@@ -239,8 +216,8 @@ hipError_t padded_forward_cg(const Problem &p, int T, float eps, int32_t *iters)
     char *ws = static_cast<char *>(p.ws);
     const llla_strides sp = {(int64_t)p.H * p.n * PD, (int64_t)p.n * PD, (int64_t)PD};
     const Rows r{p.B, p.H, p.n, p.d, p.stream};
-    const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v)}};
-    hipError_t e = pad_rows(in, 3, r, false);
+    const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v)}, 3};
+    hipError_t e = pad_rows(in, r, false);
     if (e != hipSuccess) return e;
     Problem q = p;
     q.Q = ws + L.q; q.K = ws + L.k; q.V = ws + L.v; q.O = ws + L.o;
@@ -273,18 +250,15 @@ hipError_t padded_backward(const BackwardProblem &p)
     const PadBackwardLayout L = make_pad_backward_layout(p.B, p.H, p.n);
     char *ws = static_cast<char *>(p.ws);
     const llla_strides sp = {(int64_t)p.H * p.n * PD, (int64_t)p.n * PD, (int64_t)PD};
-    const Rows r{p.B, p.H, p.n, p.d, p.stream};
-
     const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v),
-                            pad_source(p.dO, p.sdo, ws + L.g)}};
-    hipError_t e = pad_rows(in, 4, r, false);
-    if (e != hipSuccess) return e;
+                            pad_source(p.dO, p.sdo, ws + L.g)}, 4};
 
     BackwardProblem q = p;
     q.Q = ws + L.q; q.K = ws + L.k; q.V = ws + L.v; q.dO = ws + L.g;
     q.sq = q.sk = q.sv = q.sdo = sp;
     q.d = PD;
     q.live_d = p.d;
+    q.pad = &in;
     q.ws = ws + L.inner;
     q.ws_bytes = L.total - L.inner;
     return backward(q, LLLA_PATH_MFMA);
