@@ -91,8 +91,8 @@ hipError_t mfma_backward_rowmax(const BackwardProblem &p, const BackwardLayout &
 hipError_t mfma_backward_solve(const BackwardProblem &p, const BackwardLayout &L);    // moments, y and u of every row
 hipError_t mfma_backward_r(const BackwardProblem &p, const BackwardLayout &L, int early);   // r rows, argmax
 hipError_t mfma_backward_dq(const BackwardProblem &p, const BackwardLayout &L, int early);  // dQ, dlambda, row scalars
-// rows [r0, r1) of the output of a bf16 forward from the row maxima (log2 units) and the solved rows (llla_mfma_bwd.hip)
-hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int r0, int r1, bool three_terms);
+// output of a bf16 forward from the row maxima (log2 units) and the solved rows (llla_mfma_bwd.hip); early: rows with three-term operands
+hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int early);
 hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L);     // dK, dV from y, u and the row scalars
 // the same for fp32 inputs: sweeps on the fp32 matrix cores (llla_mfma_bwd_f32.hip); its moments kernel is the
 // forward's, with the row maxima M given and the rows r replaced by u

@@ -384,23 +384,31 @@ __global__ __launch_bounds__(256, DD == 64 && NK == 1 ? 3 : 2) void bwd_keys_mfm
 // barriers 493 us, one block ahead 480, three 434).  MODE 0, bound by its vector work, has two stages and the loop unrolled
 // over them (341 -> 307; three blocks ahead 319), and NQ = 2 blocks of 16 queries per wave from TWO_QUERY_BLOCKS_FROM workgroups of 128
 // rows on (328 -> 310; 64 x 2048 102 -> 106, 96 x 1000 47 -> 55).
-template <int DD, int MODE, int NQ, int TERMS = 2, int LIVE = Shape<DD>::NB>
-__global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
-    const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
+template <int DD, int MODE>
+struct RowTiles {
+    static constexpr int NST = MODE == 0 ? 2 : 4;        // blocks in LDS: the one in use and NST - 1 on their way
+    bf16_t kt[NST][KB * DD], vt[NST][KB * DD];
+};
+
+// (row block yblk of ny, from first_row on)
+template <int DD, int MODE, int NQ, int TERMS, int LIVE>
+__device__ __forceinline__ void bwd_rows_body(
+    RowTiles<DD, MODE> &tiles, const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
     const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n,
-    int first_row, int mpitch, float scale, float lambda, const float *__restrict__ LamRows, const float *__restrict__ Mg,
+    int first_row, int yblk, int ny, int mpitch, float scale, float lambda, const float *__restrict__ LamRows, const float *__restrict__ Mg,
     float *Yg, float *Ug, float *__restrict__ Rv, float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam)
 {
     using S = Shape<DD>;
     constexpr int NF = (16 * LIVE + 31) / 32, NB = LIVE, YP = S::YP;
     constexpr int CH = DD / 8, TILE = KB * DD, RPT = 64 / CH, NTR = KB / RPT / 4;     // as in the key sweep
-    constexpr int NST = MODE == 0 ? 2 : 4;               // blocks in LDS: the one in use and NST - 1 on their way
-    __shared__ __align__(16) bf16_t kt[NST][TILE], vt[NST][TILE];
+    constexpr int NST = RowTiles<DD, MODE>::NST;
+    auto &kt = tiles.kt;
+    auto &vt = tiles.vt;
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     // head on blockIdx.x (dispatched fastest), row block on y, longest rows first: see bwd_keys_mfma_kernel
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int i0 = first_row + ((int)gridDim.y - 1 - (int)blockIdx.y) * (64 * NQ), iw = i0 + 16 * NQ * wave;   // first row of the workgroup, of the wave
+    const int i0 = first_row + (ny - 1 - yblk) * (64 * NQ), iw = i0 + 16 * NQ * wave;   // first row of the workgroup, of the wave
     const char *Kh = reinterpret_cast<const char *>(Kg + b * sk.batch + h * sk.head);
     const char *Vh = reinterpret_cast<const char *>(Vg + b * sv.batch + h * sv.head);
     // MODE 0 compares raw products with the maximum, so the sign of the scale goes into the query operand
@@ -683,6 +691,30 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
     }
 }
 
+// TERMS = 0: rows [0, early) with three terms and those behind them with two, in one launch (the last early / 64 row blocks).
+template <int DD, int MODE, int NQ, int TERMS, int LIVE = Shape<DD>::NB>
+__global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
+    const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg,
+    const bf16_t *__restrict__ Gg, llla_strides sq, llla_strides sk, llla_strides sv, llla_strides sg, int H, int n, int early,
+    int first_row, int mpitch, float scale, float lambda, const float *__restrict__ LamRows, const float *__restrict__ Mg,
+    float *Yg, float *Ug, float *__restrict__ Rv, float *__restrict__ Sc, float *__restrict__ dQ, float *__restrict__ dLam)
+{
+    __shared__ __align__(16) RowTiles<DD, MODE> tiles;
+    const int yblk = blockIdx.y, ny = gridDim.y;
+    if constexpr (TERMS == 0) {
+        const int late = ny - early / 64;
+        if (yblk < late)
+            bwd_rows_body<DD, MODE, NQ, 2, LIVE>(tiles, Qg, Kg, Vg, Gg, sq, sk, sv, sg, H, n, early, yblk, late, mpitch, scale, lambda, LamRows, Mg,
+                                                 Yg, Ug, Rv, Sc, dQ, dLam);
+        else
+            bwd_rows_body<DD, MODE, NQ, 3, LIVE>(tiles, Qg, Kg, Vg, Gg, sq, sk, sv, sg, H, n, 0, yblk - late, ny - late, mpitch, scale, lambda,
+                                                 LamRows, Mg, Yg, Ug, Rv, Sc, dQ, dLam);
+    } else {
+        bwd_rows_body<DD, MODE, NQ, TERMS, LIVE>(tiles, Qg, Kg, Vg, Gg, sq, sk, sv, sg, H, n, first_row, yblk, ny, mpitch, scale, lambda, LamRows, Mg,
+                                                 Yg, Ug, Rv, Sc, dQ, dLam);
+    }
+}
+
 // ---- output sweep of the forward ---------------------------------------------------------------------------------
 // O_i = sum_j w_ij (y0_i + k_j . y1_i) v_j for the rows [first_row, n): the row sweeps' loop with other products, 20 MFMAs and some 50
 // vector instructions per wave, block of 32 keys and 16 queries at d = 64, which hardly overlap.  What bounded sweep_kernel beyond
@@ -693,21 +725,21 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void bwd_rows_mfma_kernel(
 // LIVE < NB (a d = 16 / 32 call on zero-padded copies): features and value columns from 16 LIVE on are zero and left out.
 // (us a call: 64 heads x 4096 at d = 32 1422 -> 1378, d = 16 1079 -> 1039, 32 x 300 at d = 32 53.9 -> 50.5.)
 // TERMS = 3 (the first rows, whose coefficients cancel to a few digits): y1 and the coefficients in three bf16, as in the sweeps above.
-template <int DD, int LIVE = Shape<DD>::NB, int TERMS = 2>
-__global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
-    const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg, llla_strides sq, llla_strides sk,
-    llla_strides sv, int H, int n, int first_row, int mpitch, float cscale, const float *__restrict__ Mg, const float *__restrict__ Yg,
-    void *__restrict__ Og, llla_strides so, int out_bf16, int causal)
+template <int DD, int LIVE, int TERMS>
+__device__ __forceinline__ void out_rows_body(
+    RowTiles<DD, 0> &tiles, const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg, llla_strides sq,
+    llla_strides sk, llla_strides sv, int H, int n, int first_row, int yblk, int ny, int mpitch, float cscale, const float *__restrict__ Mg,
+    const float *__restrict__ Yg, void *__restrict__ Og, llla_strides so, int out_bf16, int causal)
 {
     using S = Shape<DD>;
     constexpr int NF = (16 * LIVE + 31) / 32, NB = LIVE, YP = S::YP;      // feature chunks of 32 and output tiles that are live
     constexpr int CH = DD / 8, TILE = KB * DD, RPT = 64 / CH, NTR = KB / RPT / 4;     // as in the key sweep
-    constexpr int NST = 2;                               // blocks in LDS: the one in use and the next, on its way
-    __shared__ __align__(16) bf16_t kt[NST][TILE], vt[NST][TILE];
+    auto &kt = tiles.kt;                                 // two blocks: the one in use and the next, on its way
+    auto &vt = tiles.vt;
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
-    const int i0 = first_row + ((int)gridDim.y - 1 - (int)blockIdx.y) * 64, iw = i0 + 16 * wave;   // first row of the workgroup, of the wave
+    const int i0 = first_row + (ny - 1 - yblk) * 64, iw = i0 + 16 * wave;   // first row of the workgroup, of the wave
     const char *Kh = reinterpret_cast<const char *>(Kg + b * sk.batch + h * sk.head);
     const char *Vh = reinterpret_cast<const char *>(Vg + b * sv.batch + h * sv.head);
 
@@ -865,7 +897,38 @@ __global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
     }
 }
 
+// TERMS = 0: as in the row sweeps
+template <int DD, int LIVE, int TERMS>
+__global__ __launch_bounds__(256, TERMS == 3 ? 1 : 2) void out_rows_kernel(
+    const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, const bf16_t *__restrict__ Vg, llla_strides sq, llla_strides sk,
+    llla_strides sv, int H, int n, int early, int first_row, int mpitch, float cscale, const float *__restrict__ Mg, const float *__restrict__ Yg,
+    void *__restrict__ Og, llla_strides so, int out_bf16, int causal)
+{
+    __shared__ __align__(16) RowTiles<DD, 0> tiles;
+    const int yblk = blockIdx.y, ny = gridDim.y;
+    if constexpr (TERMS == 0) {
+        const int late = ny - early / 64;
+        if (yblk < late)
+            out_rows_body<DD, LIVE, 2>(tiles, Qg, Kg, Vg, sq, sk, sv, H, n, early, yblk, late, mpitch, cscale, Mg, Yg, Og, so, out_bf16, causal);
+        else
+            out_rows_body<DD, LIVE, 3>(tiles, Qg, Kg, Vg, sq, sk, sv, H, n, 0, yblk - late, ny - late, mpitch, cscale, Mg, Yg, Og, so, out_bf16, causal);
+    } else {
+        out_rows_body<DD, LIVE, TERMS>(tiles, Qg, Kg, Vg, sq, sk, sv, H, n, first_row, yblk, ny, mpitch, cscale, Mg, Yg, Og, so, out_bf16, causal);
+    }
+}
+
 constexpr long long TWO_QUERY_BLOCKS_FROM = 1536, TWO_KEY_BLOCKS_FROM = 768;
+
+// The first rows (three terms) and the others in one launch.  A launch of the first rows alone is a few workgroups' latency, 5 to 30 us; the
+// price is the registers of three terms for all, i.e. fewer resident workgroups.  us a call, two launches and one: 4 heads x 400 41.2 and
+// 35.1, backward 4 x 300 90.8 and 75.1, 96 x 157 with statistics 74.6 and 69.1, backward 8 x 961 at d = 128 435 and 403, 16 x 1000
+// 108 and 102, 96 x 1000 (1344 workgroups) 445 and 438, backward 681 and 668, 64 x 2048 (1920) 840 and 829; but 64 x 3000 at d = 16 (2880)
+// 583 and 592, backward 64 x 4096 (3968) 4275 and 4333.
+constexpr long long ONE_LAUNCH_UP_TO = 2048;
+bool one_launch(int heads, int n, int early)
+{
+    return early > 0 && early < n && early % 64 == 0 && (long long)heads * ((n - early + 63) / 64) <= ONE_LAUNCH_UP_TO;
+}
 
 template <int DD, int MODE, int LIVE = Shape<DD>::NB>
 hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int early)
@@ -879,10 +942,11 @@ hipError_t launch_rows(const BackwardProblem &p, const BackwardLayout &L, int ea
     auto launch = [&](auto kernel, int rows, int r0, int r1) {        // rows [r0, r1) in blocks of `rows`; r1 a multiple of 64 or n
         hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (r1 - r0 + rows - 1) / rows), dim3(256), 0, p.stream,
                            static_cast<const bf16_t *>(p.Q), static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V),
-                           static_cast<const bf16_t *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, r0, L.npad, p.scale,
+                           static_cast<const bf16_t *>(p.dO), p.sq, p.sk, p.sv, p.sdo, p.H, p.n, early, r0, L.npad, p.scale,
                            p.lambda, p.lambda_rows, M, Y, U, R, Sc, p.dQ, p.dlambda);
         return hipGetLastError();
     };
+    if (one_launch(p.B * p.H, p.n, early)) return launch(bwd_rows_mfma_kernel<DD, MODE, 1, 0, LIVE>, 64, 0, p.n);
     const hipError_t e = launch(bwd_rows_mfma_kernel<DD, MODE, 1, 3, LIVE>, 64, 0, early);
     if (e != hipSuccess || early >= p.n) return e;
     if constexpr (DD == 64 && MODE == 0) {
@@ -937,19 +1001,36 @@ hipError_t mfma_backward_keys(const BackwardProblem &p, const BackwardLayout &L)
     return hipGetLastError();
 }
 
-// rows [r0, r1) of the output of a bf16 forward, r0 a multiple of 64, r1 too or all; the first rows, whose coefficients cancel, with three-term operands
-hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int r0, int r1, bool three_terms)
+// output of a bf16 forward; rows [0, early), whose coefficients cancel, with three-term operands: a multiple of 64, or all
+hipError_t mfma_output_rows(const Problem &p, const float *M, int mpitch, const float *Y, int early)
 {
-    auto launch = [&](auto kernel) {
+    auto launch = [&](auto kernel, int r0, int r1) {
         hipLaunchKernelGGL(kernel, dim3(p.B * p.H, (r1 - r0 + 63) / 64), dim3(256), 0, p.stream, static_cast<const bf16_t *>(p.Q),
-                           static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V), p.sq, p.sk, p.sv, p.H, p.n, r0, mpitch,
+                           static_cast<const bf16_t *>(p.K), static_cast<const bf16_t *>(p.V), p.sq, p.sk, p.sv, p.H, p.n, early, r0, mpitch,
                            p.scale * LOG2E, M, Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0, p.causal);
     };
+    auto sweep = [&](auto dtag, auto livetag) {
+        constexpr int DD = decltype(dtag)::value, LIVE = decltype(livetag)::value;
+        if (one_launch(p.B * p.H, p.n, early)) {
+            stage_mark(p.stream, "output");
+            launch(out_rows_kernel<DD, LIVE, 0>, 0, p.n);
+            return;
+        }
+        if (early > 0) {
+            stage_mark(p.stream, "output_early_rows");
+            launch(out_rows_kernel<DD, LIVE, 3>, 0, early);
+        }
+        if (early < p.n) {
+            stage_mark(p.stream, "output");
+            launch(out_rows_kernel<DD, LIVE, 2>, early, p.n);
+        }
+    };
+    using std::integral_constant;
     const int live = live_blocks(p.d, p.live_d);
-    if (live == 1) three_terms ? launch(out_rows_kernel<64, 1, 3>) : launch(out_rows_kernel<64, 1>);
-    else if (live == 2) three_terms ? launch(out_rows_kernel<64, 2, 3>) : launch(out_rows_kernel<64, 2>);
-    else if (p.d == 64) three_terms ? launch(out_rows_kernel<64, 4, 3>) : launch(out_rows_kernel<64>);
-    else three_terms ? launch(out_rows_kernel<128, 8, 3>) : launch(out_rows_kernel<128>);
+    if (p.d != 64) sweep(integral_constant<int, 128>{}, integral_constant<int, 8>{});
+    else if (live == 1) sweep(integral_constant<int, 64>{}, integral_constant<int, 1>{});
+    else if (live == 2) sweep(integral_constant<int, 64>{}, integral_constant<int, 2>{});
+    else sweep(integral_constant<int, 64>{}, integral_constant<int, 4>{});
     return hipGetLastError();
 }
 

@@ -1149,16 +1149,8 @@ hipError_t forward_impl(const Problem &p)
         hipLaunchKernelGGL((moments_kernel<DD>), dim3(nqb, bh), dim3(S::NT), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
                            first, cscale, p.lambda, p.lambda_rows, KT, M, Y, p.causal, p.rho, p.delta);
     // output: those rows by the sweep with fp32 accuracy (their weights y0 + k.y1 cancel to a few digits), the rest by the plain one
-    if (first > 0) {
-        stage_mark(p.stream, "output_early_rows");
-        const hipError_t e = mfma_output_rows(p, M, L.npad, Y, 0, first, true);
-        if (e != hipSuccess) return e;
-    }
-    if (first < p.n) {
-        stage_mark(p.stream, "output");
-        return mfma_output_rows(p, M, L.npad, Y, first, p.n, false);
-    }
-    return hipGetLastError();
+    const hipError_t launched = hipGetLastError();
+    return launched != hipSuccess ? launched : mfma_output_rows(p, M, L.npad, Y, first);
 }
 
 
