@@ -349,7 +349,7 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
                 }
             }
             float low = INFINITY;
-            factorise_one<NB, true>(acc, scratch, g, nn, floor, &low);
+            factorise_one<NB, true, false, false>(acc, scratch, g, nn, floor, &low);
             float tv[1][NB];                                  // -q_c, U^{-T} q_c, its negative
 #pragma unroll
             for (int P = 0; P < NB; ++P) {

@@ -152,6 +152,42 @@ __device__ inline f32x4 tile_atb(f32x4 c, f32x4 a, f32x4 b)
     return c;
 }
 
+// The same on 16-bit MFMA from operands in three bf16 (see split3_bf16): a tile's terms m, h, l lie side by side, so (m, h) and (h, l)
+// are operands whose two halves are the same sixteen rows in two terms, and three MFMAs are the six products that count --
+// hm + lh, mh + hl, mm + hh; what is left out is below 2^-24 of the result.  48 cycles of the matrix cores instead of 128, for 14
+// vector instructions per operand tile.
+typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
+typedef unsigned u32x6 __attribute__((ext_vector_type(6)));
+__device__ inline u32x6 split_tile(f32x4 x)
+{
+    unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
+    asm("" : "+s"(lo), "+s"(hi));
+    const bf16x2v first = __builtin_bit_cast(bf16x2v, lo), second = __builtin_bit_cast(bf16x2v, hi);
+    u32x6 r;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const bf16x2v a = __builtin_convertvector(float2v{x[2 * t], x[2 * t + 1]}, bf16x2v);
+        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, first, x[2 * t], false), r1 = __builtin_amdgcn_fdot2_f32_bf16(a, second, x[2 * t + 1], false);
+        const bf16x2v b = __builtin_convertvector(float2v{r0, r1}, bf16x2v);
+        const bf16x2v c = __builtin_convertvector(float2v{__builtin_amdgcn_fdot2_f32_bf16(b, first, r0, false),
+                                                          __builtin_amdgcn_fdot2_f32_bf16(b, second, r1, false)}, bf16x2v);
+        r[t] = __builtin_bit_cast(unsigned, b);
+        r[2 + t] = __builtin_bit_cast(unsigned, a);
+        r[4 + t] = __builtin_bit_cast(unsigned, c);
+    }
+    return r;
+}
+__device__ inline f32x4 split_atb(f32x4 c, const u32x6 &a, const u32x6 &b)
+{
+    const bf16x8 amh = __builtin_bit_cast(bf16x8, (u32x4v)__builtin_shufflevector(a, a, 0, 1, 2, 3));
+    const bf16x8 ahl = __builtin_bit_cast(bf16x8, (u32x4v)__builtin_shufflevector(a, a, 2, 3, 4, 5));
+    const bf16x8 bmh = __builtin_bit_cast(bf16x8, (u32x4v)__builtin_shufflevector(b, b, 0, 1, 2, 3));
+    const bf16x8 bhl = __builtin_bit_cast(bf16x8, (u32x4v)__builtin_shufflevector(b, b, 2, 3, 4, 5));
+    c = mfma_bf16(ahl, bmh, c);
+    c = mfma_bf16(amh, bhl, c);
+    return mfma_bf16(amh, bmh, c);
+}
+
 constexpr int SC_PITCH = 20;         // floats per row of a 16x16 scratch tile
 
 // ---- diagonal tiles -----------------------------------------------------------------------------------------------------------
@@ -399,7 +435,14 @@ __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I *
 // inverse diagonal factors (N_P), and, in the substitutions, the partial right-hand sides; no tile is ever negated on
 // the vector ALU.
 // LOW: low as in eliminate16, over all pivots.
-template <int NB, bool LOW = false, bool DROP = false>
+// SPLIT: the block products on 16-bit MFMA from operands in three bf16.  fp32 MFMA and vector instructions of the two waves of a SIMD do not
+// overlap, and 112 tile products at d = 128 are a third of the solve.  Each product starts from zero and is added to its tile on the vector
+// ALU: chained onto the tile its three MFMAs left errors of up to 1.09 times those of fp32 MFMA, which rounds at each of a product's sixteen
+// rows; so they are 0.80 to 0.99 times those (O, dQ, dK, dV; 140 to 400 rows, bf16 and fp32).  us a call, fp32 MFMA and split: 16 heads x
+// 2048 1049 and 1012, 16 x 8192 9674 and 9613, 8 x 44 46.7 and 43.8, backward 8 x 961 402 and 386; fp32 64 x 700 2413 and 2357.  Decode,
+// one solve per compute unit, gains nothing (224 heads of up to 589 keys 54.7 and 55.6), nor do four systems per wave at d = 64 (64 x 4096 bf16
+// 2829 and 2916, 16 x 1024 fp32 346 and 352).
+template <int NB, bool LOW = false, bool DROP = false, bool SPLIT = true>
 __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor, float *low = nullptr)
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -423,13 +466,28 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
         // N_P replaces the consumed diagonal tile; U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
         const f32x4 ui = invert16_quarter(nl, ndinv, nn, g);
         acc[upper_tile<NB>(P, P)] = ui;
+        if constexpr (!SPLIT) {
 #pragma unroll
-        for (int J = P + 1; J < NB; ++J) acc[upper_tile<NB>(P, J)] = tile_atb(zero, ui, acc[upper_tile<NB>(P, J)]);
+            for (int J = P + 1; J < NB; ++J) acc[upper_tile<NB>(P, J)] = tile_atb(zero, ui, acc[upper_tile<NB>(P, J)]);
 #pragma unroll
-        for (int I = P + 1; I < NB; ++I)
+            for (int I = P + 1; I < NB; ++I)
 #pragma unroll
-            for (int J = I; J < NB; ++J)
-                acc[upper_tile<NB>(I, J)] = tile_atb(acc[upper_tile<NB>(I, J)], acc[upper_tile<NB>(P, I)], acc[upper_tile<NB>(P, J)]);
+                for (int J = I; J < NB; ++J)
+                    acc[upper_tile<NB>(I, J)] = tile_atb(acc[upper_tile<NB>(I, J)], acc[upper_tile<NB>(P, I)], acc[upper_tile<NB>(P, J)]);
+        } else if (P + 1 < NB) {
+            const u32x6 us = split_tile(ui);
+            u32x6 row[NB];
+#pragma unroll
+            for (int J = P + 1; J < NB; ++J) {
+                f32x4 &u = acc[upper_tile<NB>(P, J)];
+                u = split_atb(zero, us, split_tile(u));
+                row[J] = split_tile(u);
+            }
+#pragma unroll
+            for (int I = P + 1; I < NB; ++I)
+#pragma unroll
+                for (int J = I; J < NB; ++J) acc[upper_tile<NB>(I, J)] += split_atb(zero, row[I], row[J]);
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
