@@ -105,97 +105,67 @@ __global__ __launch_bounds__(256) void prep_kernel(const bf16_t *__restrict__ Kg
 }
 
 // ------------------------------------------------------------------------------------------------
-// Sweep over S^T = K Q^T for 64 queries per workgroup (16 per wave).
-//   MAXONLY: write the row maxima m_i (in log2 units) -- Algorithm 1's m after its last block.
-//   else   : third loop of Algorithm 1: S = W (y0 + K y1), O = S V, for the approximate mode (the exact forward: out_rows_kernel).
+// Sweep over S^T = K Q^T for 64 queries per workgroup (16 per wave): third loop of Algorithm 1, S = W (y0 + K y1), O = S V, for the approximate mode
+// (the exact forward: out_rows_kernel).
 constexpr int VT_PITCH = KB + 8;     // halves
 
-// LIVE < NB (MAXONLY, a d = 16 / 32 call): the rows of Q and K have 16 LIVE features, those beyond are zero and not read.
-template <bool MAXONLY, int DD, int LIVE = Shape<DD>::NB>
-__device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq, llla_strides sk,
-                                           int H, int n, int nkb, int first_row, float cscale, const bf16_t *__restrict__ VT,
-                                           float *__restrict__ Mg, const float *__restrict__ Yg, void *__restrict__ Og, llla_strides so,
-                                           int out_bf16, float *__restrict__ Csum, int causal, int bh, int yblk, int nqb)
+template <int DD>
+__global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq,
+                                                       llla_strides sk, int H, int n, int nkb, int first_row, float cscale,
+                                                       const bf16_t *__restrict__ VT, const float *__restrict__ Mg, const float *__restrict__ Yg,
+                                                       void *__restrict__ Og, llla_strides so, int out_bf16, float *__restrict__ Csum)
 {
-    static_assert(MAXONLY || LIVE == Shape<DD>::NB, "the padded calls' output sweep is out_rows_kernel");
-    constexpr int WIDTH = 16 * LIVE;
-    // !MAXONLY is a general "coefficients times a tile" sweep: O_i = sum_j w_ij (y0_i + k_j . y1_i) t_j with the rows t_j
+    // a general "coefficients times a tile" sweep: O_i = sum_j w_ij (y0_i + k_j . y1_i) t_j with the rows t_j
     // of whatever VT holds (V for the output; K for the first moment and for the matrix-free product of the
     // approximate mode).  Yg == nullptr means y0 = 1, y1 = 0 (plain weights); Csum, if given, receives sum_j of the
     // coefficients of every row.
     using S = Shape<DD>;
-    constexpr int NF = (16 * LIVE + 31) / 32, NB = LIVE, YP = S::YP;     // feature chunks of 32 and output tiles that are live
+    constexpr int NF = S::NF, NB = S::NB, YP = S::YP;
     constexpr int KN_PITCH = DD + 16;    // halves; rows of the natural K tile stay 16-byte aligned (measured 2-3 % faster than DD + 8)
     __shared__ __align__(16) bf16_t kn[KB * KN_PITCH];
-    __shared__ __align__(16) bf16_t vt[MAXONLY ? 8 : DD * VT_PITCH];
+    __shared__ __align__(16) bf16_t vt[DD * VT_PITCH];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     // head on blockIdx.x (dispatched fastest), query block on y, longest rows first: every head's longest blocks
     // start first and the short ones fill the tail.  (With the head on y the last head's longest block ran alone at the
     // end; with the XCD-grouped mapping of the moments kernel a head's 64-row blocks all start at once and the XCD
     // waits for the longest: both measured slower.)  Heads that are a multiple of 8 apart share an XCD and its L2.
-    const int b = bh / H, h = bh % H;
-    const int i0 = first_row + (nqb - 1 - yblk) * 64;
-    const int iq = i0 + wave * 16 + nn;                                // this lane's query
+    const int bh = blockIdx.x, b = bh / H, h = bh % H;
+    const int i0 = first_row + ((int)gridDim.y - 1 - (int)blockIdx.y) * 64;
+    const int iq = i0 + wave * 16 + nn;                                // this lane's query, and the last key it sees
     const int iqc = min(iq, n - 1);
-    const int jlim = causal ? iq : n - 1;                              // last key this lane's query sees
     const bf16_t *Kh = Kg + b * sk.batch + h * sk.head;
     const bf16_t *qrow = Qg + b * sq.batch + h * sq.head + (int64_t)iqc * sq.seq;
     bf16x8 qf[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        uint4 u = make_uint4(0, 0, 0, 0);
-        if (32 * f + 31 < WIDTH || 32 * f + 8 * g < WIDTH) u = *reinterpret_cast<const uint4 *>(qrow + 32 * f + 8 * g);
-        qf[f] = __builtin_bit_cast(bf16x8, u);
-    }
-    // Row maxima: max_j c <q, k_j> = |c| max_j <sign(c) q, k_j>, so the sign of the scale goes into the query operand
-    // once (a flip of the bf16 sign bits) and the sweep keeps the maximum of the RAW products, one three-input maximum
-    // per two logits; |c| is applied to the result.  (Scaling every logit first was two vector instructions per logit
-    // in a sweep that the vector ALU bounds.)
-    if (MAXONLY && cscale < 0.f) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            uint4 u = __builtin_bit_cast(uint4, qf[f]);
-            u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u;
-            qf[f] = __builtin_bit_cast(bf16x8, u);
-        }
-    }
+    for (int f = 0; f < NF; ++f) qf[f] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * f + 8 * g);
 
-    float mrow = -INFINITY, y0 = 0.f;
+    const float mrow = Mg[(size_t)bh * (nkb * KB) + iqc];
+    const float *yr = Yg ? Yg + ((size_t)bh * n + iqc) * YP : nullptr;
+    const float y0 = yr ? yr[DD] : 1.f;
     bf16x8 yh[NF], yl[NF];
     f32x4 oacc[NB];
-    if (!MAXONLY) {
-        mrow = Mg[(size_t)bh * (nkb * KB) + iqc];
-        const float *yr = Yg ? Yg + ((size_t)bh * n + iqc) * YP : nullptr;
-        y0 = yr ? yr[DD] : 1.f;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            float yv[8];
+    for (int f = 0; f < NF; ++f) {
+        float yv[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) yv[t] = yr ? yr[32 * f + 8 * g + t] : 0.f;
+        for (int t = 0; t < 8; ++t) yv[t] = yr ? yr[32 * f + 8 * g + t] : 0.f;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const __bf16 hi = (__bf16)yv[t];
-                yh[f][t] = hi;
-                yl[f][t] = (__bf16)(yv[t] - (float)hi);
-            }
+        for (int t = 0; t < 8; ++t) {
+            const __bf16 hi = (__bf16)yv[t];
+            yh[f][t] = hi;
+            yl[f][t] = (__bf16)(yv[t] - (float)hi);
         }
-#pragma unroll
-        for (int J = 0; J < NB; ++J) oacc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float mx[2][4];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mx[s][r] = -INFINITY;
+    for (int J = 0; J < NB; ++J) oacc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
     float csum = 0.f;
 
     const int ilast = min(i0 + 63, n - 1);
-    const int nblk = causal ? ilast / KB + 1 : (n + KB - 1) / KB;
+    const int nblk = ilast / KB + 1;
     // The K (natural) and V^T tiles of block c + 1 are fetched into registers while block c is computed, and written
-    // to LDS at the top of the next iteration: the global-memory latency is off the path between the two barriers
-    // (the row-maximum sweep has four MFMAs of work per block and was waiting for memory most of the time).
+    // to LDS at the top of the next iteration: the global-memory latency is off the path between the two barriers.
     constexpr int NLD = DD / 64;         // 16-byte pieces per thread and tile
-    uint4 kpre[NLD], vpre[MAXONLY ? 1 : NLD];
+    uint4 kpre[NLD], vpre[NLD];
     auto fetch = [&](int c) {
 #pragma unroll
         for (int u = 0; u < NLD; ++u) {
@@ -203,11 +173,9 @@ __device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const 
             const int key = idx / (DD / 8), ch = (idx % (DD / 8)) * 8;
             const int j = c * KB + key;
             kpre[u] = make_uint4(0, 0, 0, 0);
-            if (j < n && (WIDTH == DD || ch < WIDTH)) kpre[u] = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
-            if (!MAXONLY) {
-                const int feat = idx / 4, k0 = (idx % 4) * 8;
-                vpre[u] = *reinterpret_cast<const uint4 *>(VT + ((size_t)bh * nkb + c) * (DD * KB) + feat * KB + k0);
-            }
+            if (j < n) kpre[u] = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
+            const int feat = idx / 4, k0 = (idx % 4) * 8;
+            vpre[u] = *reinterpret_cast<const uint4 *>(VT + ((size_t)bh * nkb + c) * (DD * KB) + feat * KB + k0);
         }
     };
     fetch(0);
@@ -218,10 +186,8 @@ __device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const 
             const int idx = tid + 256 * u;
             const int key = idx / (DD / 8), ch = (idx % (DD / 8)) * 8;
             *reinterpret_cast<uint4 *>(&kn[key * KN_PITCH + ch]) = kpre[u];
-            if (!MAXONLY) {
-                const int feat = idx / 4, k0 = (idx % 4) * 8;
-                *reinterpret_cast<uint4 *>(&vt[feat * VT_PITCH + k0]) = vpre[u];
-            }
+            const int feat = idx / 4, k0 = (idx % 4) * 8;
+            *reinterpret_cast<uint4 *>(&vt[feat * VT_PITCH + k0]) = vpre[u];
         }
         if (c + 1 < nblk) fetch(c + 1);
         __syncthreads();
@@ -235,33 +201,18 @@ __device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const 
 #pragma unroll
             for (int f = 0; f < NF; ++f) z = mfma_bf16(kf[f], qf[f], z);
             st[s] = z;
-            if (!MAXONLY) {
-                f32x4 u = {y0, y0, y0, y0};         // y0 + k . y1: the intercept rides in as the accumulator's initial value
+            f32x4 u = {y0, y0, y0, y0};             // y0 + k . y1: the intercept rides in as the accumulator's initial value
 #pragma unroll
-                for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yl[f], u);
+            for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yl[f], u);
 #pragma unroll
-                for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yh[f], u);
-                ut[s] = u;
-            }
+            for (int f = 0; f < NF; ++f) u = mfma_bf16(kf[f], yh[f], u);
+            ut[s] = u;
         }
         // lane (g, nn): st[s][r] = <k_j, q_iq> for key j = 32c + 16s + 4g + r.  Only the blocks that reach past the
         // wave's first query need the causal mask (a scalar condition): the others skip the compares and selects,
         // which are most of the vector work of this sweep.
-        const bool masked = causal ? (c * KB + KB - 1 > i0 + wave * 16) : (c * KB + KB > n);
-        if (MAXONLY) {
-            if (!masked) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) mx[0][r] = __builtin_fmaxf(__builtin_fmaxf(mx[0][r], st[0][r]), st[1][r]);   // v_max3_f32
-            } else {
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int j = c * KB + 16 * s + 4 * g + r;
-                        mx[0][r] = (j <= jlim) ? fmaxf(mx[0][r], st[s][r]) : mx[0][r];
-                    }
-            }
-        } else {
+        const bool masked = c * KB + KB - 1 > i0 + wave * 16;
+        {
             bf16x8 ch, cl;      // output weights as bf16 hi + lo; slot t<4: key 4g+t, t>=4: key 16+4g+t-4
             float cv[8];
 #pragma unroll
@@ -273,7 +224,7 @@ __device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const 
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const int j = c * KB + 16 * (t >> 2) + 4 * g + (t & 3);
-                    cv[t] = (j <= jlim) ? cv[t] : 0.f;
+                    cv[t] = (j <= iq) ? cv[t] : 0.f;
                 }
             }
             if (Csum != nullptr) {                                   // a scalar branch: the plain output call skips the sums
@@ -301,44 +252,137 @@ __device__ __forceinline__ void sweep_rows(const bf16_t *__restrict__ Qg, const 
         }
     }
 
-    if (MAXONLY) {
-        float m = fmaxf(fmaxf(mx[0][0], mx[0][1]), fmaxf(mx[0][2], mx[0][3]));
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        // every row sees at least its own key, so m is finite; a zero scale gives 0 (not 0 times a product)
-        if (g == 0 && iq < n) Mg[(size_t)bh * (nkb * KB) + iq] = cscale == 0.f ? 0.f : m * fabsf(cscale);
-    } else {
-        if (Csum != nullptr) {      // lanes (g, nn), g = 0..3, hold the coefficients of query nn for disjoint keys
-            csum += __shfl_xor(csum, 16);
-            csum += __shfl_xor(csum, 32);
-            if (g == 0 && iq < n) Csum[(size_t)bh * n + iq] = csum;
-        }
-        // oacc[J]: lane (g, nn) reg r = O[query i0 + 16 wave + 4g + r][feature 16J + nn]
+    if (Csum != nullptr) {          // lanes (g, nn), g = 0..3, hold the coefficients of query nn for disjoint keys
+        csum += __shfl_xor(csum, 16);
+        csum += __shfl_xor(csum, 32);
+        if (g == 0 && iq < n) Csum[(size_t)bh * n + iq] = csum;
+    }
+    // oacc[J]: lane (g, nn) reg r = O[query i0 + 16 wave + 4g + r][feature 16J + nn]
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = i0 + wave * 16 + 4 * g + r;
-            if (i < n) {
-                const int64_t off = b * so.batch + h * so.head + (int64_t)i * so.seq;
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + wave * 16 + 4 * g + r;
+        if (i < n) {
+            const int64_t off = b * so.batch + h * so.head + (int64_t)i * so.seq;
 #pragma unroll
-                for (int J = 0; J < NB; ++J) {
-                    if (out_bf16) ((bf16_t *)Og)[off + 16 * J + nn] = f32_to_bf16(oacc[J][r]);
-                    else ((float *)Og)[off + 16 * J + nn] = oacc[J][r];
-                }
+            for (int J = 0; J < NB; ++J) {
+                if (out_bf16) ((bf16_t *)Og)[off + 16 * J + nn] = f32_to_bf16(oacc[J][r]);
+                else ((float *)Og)[off + 16 * J + nn] = oacc[J][r];
             }
         }
     }
 }
 
-template <bool MAXONLY, int DD>
-__global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg,
-                                                    llla_strides sq, llla_strides sk, int H, int n, int nkb,
-                                                    int first_row, float cscale, const bf16_t *__restrict__ VT,
-                                                    float *__restrict__ Mg, const float *__restrict__ Yg,
-                                                    void *__restrict__ Og, llla_strides so, int out_bf16,
-                                                    float *__restrict__ Csum = nullptr, int causal = 1)
+// ------------------------------------------------------------------------------------------------
+// Row maxima m_i (log2 units) of the rows (nqb - 1 - yblk) 64 NQ ..: S^T = K Q^T, 16 NQ queries per wave -- Algorithm 1's m after its last block.
+// With one block of 16 queries per wave a wave reads 2 KB of LDS per 16 x 16 logits, which is what bounds the sweep; NQ blocks share every key
+// fragment: NQ = 2 where that leaves WIDE_ROWMAX_FROM workgroups (us a call, NQ = 1, 2, 4: 64 heads x 4096 2800, 2779, 2775, 64 x 2048 at
+// d = 16 314, 308, 314; but 16 x 4000 at d = 32 370, 379, 394, 16 x 1024 100, 103, 109).
+// K goes through two LDS buffers in blocks of 64 keys, one barrier per block: block c + 1 is fetched into registers while block c is computed.  (Blocks
+// of 32 keys in one buffer with two barriers: 16 x 4000, d = 32, 372 instead of 363; 8 x 3483 with statistics 325 instead of 321; d = 128 the same.)
+// LIVE < NB (a d = 16 / 32 call): the rows of Q and K have 16 LIVE features, those beyond are zero and not read.
+template <int DD, int LIVE, int NQ>
+__device__ __forceinline__ void rowmax_rows(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq, llla_strides sk, int H,
+                                            int n, int mpitch, float cscale, float *__restrict__ Mg, int causal, int bh, int yblk, int nqb)
 {
-    sweep_rows<MAXONLY, DD>(Qg, Kg, sq, sk, H, n, nkb, first_row, cscale, VT, Mg, Yg, Og, so, out_bf16, Csum, causal, blockIdx.x, blockIdx.y,
-                            gridDim.y);
+    constexpr int WIDTH = 16 * LIVE, NF = (WIDTH + 31) / 32, RB = 64;      // features; chunks of 32 of them; keys per block
+    constexpr int PITCH = 32 * NF + 16, CH = 4 * NF, NLD = RB * CH / 256;                   // halves; 16-byte pieces per row, per thread
+    __shared__ __align__(16) bf16_t kn[2][RB * PITCH];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
+    const int b = bh / H, h = bh % H;
+    const int i0 = (nqb - 1 - yblk) * (64 * NQ), iw = i0 + 16 * NQ * wave;
+    const bf16_t *Kh = Kg + b * sk.batch + h * sk.head, *Qh = Qg + b * sq.batch + h * sq.head;
+    // max_j c <q, k_j> = |c| max_j <sign(c) q, k_j>: the sign of the scale goes into the query operand once (a flip of the bf16 sign bits) and
+    // the sweep keeps the maximum of the raw products, one three-input maximum per two of them
+    const unsigned flip = cscale < 0.f ? 0x80008000u : 0u;
+    bf16x8 qf[NQ][NF];
+    float mx[NQ][4];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const bf16_t *qrow = Qh + (int64_t)min(iw + 16 * q + nn, n - 1) * sq.seq;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            uint4 u = make_uint4(0, 0, 0, 0);
+            if (32 * f + 31 < WIDTH || 32 * f + 8 * g < WIDTH) u = *reinterpret_cast<const uint4 *>(qrow + 32 * f + 8 * g);
+            u.x ^= flip; u.y ^= flip; u.z ^= flip; u.w ^= flip;
+            qf[q][f] = __builtin_bit_cast(bf16x8, u);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx[q][r] = -INFINITY;
+    }
+    const int nblk = (causal ? min(i0 + 64 * NQ - 1, n - 1) : n - 1) / RB + 1;
+    uint4 next[NLD];
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < NLD; ++u) {
+            const int idx = tid + 256 * u, ch = (idx % CH) * 8, j = c * RB + idx / CH;
+            next[u] = make_uint4(0, 0, 0, 0);
+            if (j < n && (WIDTH == 32 * NF || ch < WIDTH)) next[u] = *reinterpret_cast<const uint4 *>(Kh + (int64_t)j * sk.seq + ch);
+        }
+    };
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < NLD; ++u) {
+            const int idx = tid + 256 * u;
+            *reinterpret_cast<uint4 *>(&kn[buf][(idx / CH) * PITCH + (idx % CH) * 8]) = next[u];
+        }
+    };
+    fetch(0);
+    put(0);
+    __syncthreads();
+    for (int c = 0; c < nblk; ++c) {
+        if (c + 1 < nblk) fetch(c + 1);
+        const bf16_t *kt = kn[c & 1];
+#pragma unroll
+        for (int s = 0; s < RB / 16; s += 2) {           // 2 x 16 keys
+            const int j0 = c * RB + 16 * s;
+            if (causal && j0 > iw + 16 * NQ - 1) continue;                  // all behind the wave's last query (a scalar branch)
+            bf16x8 kf[2][NF];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) kf[t][f] = *reinterpret_cast<const bf16x8 *>(&kt[(16 * (s + t) + nn) * PITCH + 32 * f + 8 * g]);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                f32x4 z[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    z[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) z[t] = mfma_bf16(kf[t][f], qf[q][f], z[t]);
+                }
+                // lane (g, nn): z[t][r] = <k_j, q> for key j = j0 + 16 t + 4 g + r and query iw + 16 q + nn.  Only blocks that reach past
+                // the first of the queries need the mask (a scalar condition).
+                if (causal ? j0 + 31 <= iw + 16 * q : j0 + 32 <= n) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mx[q][r] = __builtin_fmaxf(__builtin_fmaxf(mx[q][r], z[0][r]), z[1][r]);      // v_max3_f32
+                } else {
+                    const int jlim = causal ? iw + 16 * q + nn : n - 1;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) mx[q][r] = j0 + 16 * t + 4 * g + r <= jlim ? fmaxf(mx[q][r], z[t][r]) : mx[q][r];
+                }
+            }
+        }
+        if (c + 1 < nblk) put((c + 1) & 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        float m = fmaxf(fmaxf(mx[q][0], mx[q][1]), fmaxf(mx[q][2], mx[q][3]));
+        m = fmaxf(m, __shfl_xor(m, 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        // every row sees at least its own key, so m is finite; a zero scale gives 0 (not 0 times a product)
+        const int iq = iw + 16 * q + nn;
+        if (g == 0 && iq < n) Mg[(size_t)bh * mpitch + iq] = cscale == 0.f ? 0.f : m * fabsf(cscale);
+    }
+}
+
+template <int DD>
+__global__ __launch_bounds__(256, 2) void rowmax_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq, llla_strides sk,
+                                                        int H, int n, int mpitch, float cscale, float *__restrict__ Mg)
+{
+    rowmax_rows<DD, Shape<DD>::NB, 1>(Qg, Kg, sq, sk, H, n, mpitch, cscale, Mg, 1, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -350,19 +394,18 @@ __global__ __launch_bounds__(256, 2) void sweep_kernel(const bf16_t *__restrict_
 // d = 128, 50.6 and 48.0; 64 x 4096 the same.
 struct FrontGrid {
     long long rowmax, prep, pad, total;      // workgroups of each kind
-    int nq64, npad;                          // row blocks per head; tensors to pad
+    int nrb;                                 // row blocks per head
     unsigned pad_blocks;                     // workgroups per tensor
 };
 
-template <int DD, int LIVE>
+template <int DD, int LIVE, int NQ>
 __global__ __launch_bounds__(256, 2) void front_kernel(const bf16_t *__restrict__ Qg, const bf16_t *__restrict__ Kg, llla_strides sq,
                                                        llla_strides sk, int H, int nbh, int n, int nkb, float cscale, _Float16 *__restrict__ KT,
                                                        float *__restrict__ Mg, int causal, FrontGrid grid, PadSources pad)
 {
     long long id = (long long)blockIdx.y * gridDim.x + blockIdx.x;
     if (id < grid.rowmax) {
-        sweep_rows<true, DD, LIVE>(Qg, Kg, sq, sk, H, n, nkb, 0, cscale, nullptr, Mg, nullptr, nullptr, llla_strides{}, 0, nullptr, causal,
-                                   (int)(id % nbh), (int)(id / nbh), grid.nq64);
+        rowmax_rows<DD, LIVE, NQ>(Qg, Kg, sq, sk, H, n, nkb * KB, cscale, Mg, causal, (int)(id % nbh), (int)(id / nbh), grid.nrb);
         return;
     }
     id -= grid.rowmax;
@@ -376,14 +419,18 @@ __global__ __launch_bounds__(256, 2) void front_kernel(const bf16_t *__restrict_
     }
 }
 
+constexpr long long WIDE_ROWMAX_FROM = 1024;      // workgroups of 128 rows from which two blocks of queries per wave pay (see rowmax_rows)
+
 // p: Problem or BackwardProblem
 template <int DD, typename P>
 hipError_t launch_front(const P &p, int nkb, _Float16 *KT, float *M, int causal)
 {
     const int bh = p.B * p.H, count = p.pad ? p.pad->count : 0;
     FrontGrid g{};
-    g.nq64 = (p.n + 63) / 64;
-    g.rowmax = (long long)bh * g.nq64;
+    auto row_blocks = [&](int nq) { return (p.n + 64 * nq - 1) / (64 * nq); };
+    const int nq = bh * (long long)row_blocks(2) >= WIDE_ROWMAX_FROM ? 2 : 1;
+    g.nrb = row_blocks(nq);
+    g.rowmax = (long long)bh * g.nrb;
     g.prep = (long long)bh * nkb;
     g.pad_blocks = (unsigned)(((size_t)bh * p.n * (DD / 8) + 255) / 256);
     g.pad = (long long)count * g.pad_blocks;
@@ -397,9 +444,14 @@ hipError_t launch_front(const P &p, int nkb, _Float16 *KT, float *M, int causal)
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, p.stream, Q, K, sq, sk, p.H, bh, p.n, nkb, p.scale * LOG2E, KT, M, causal, g, pad);
     };
-    if (p.pad && p.live_d == 16) launch(front_kernel<64, 1>);
-    else if (p.pad) launch(front_kernel<64, 2>);
-    else launch(front_kernel<DD, Shape<DD>::NB>);
+    auto launch_nq = [&](auto live) {
+        constexpr int LIVE = decltype(live)::value, D = LIVE < 4 ? 64 : DD;
+        if (nq == 2) launch(front_kernel<D, LIVE, 2>);
+        else launch(front_kernel<D, LIVE, 1>);
+    };
+    if (p.pad && p.live_d == 16) launch_nq(std::integral_constant<int, 1>{});
+    else if (p.pad) launch_nq(std::integral_constant<int, 2>{});
+    else launch_nq(std::integral_constant<int, Shape<DD>::NB>{});
     return hipGetLastError();
 }
 
@@ -1315,16 +1367,15 @@ hipError_t forward_cg_impl(const Problem &p, int T, float eps, int32_t *iters)
     hipLaunchKernelGGL((prep_kernel<DD, true>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, V, p.sk, p.sv, p.H, p.n, L.nkb, KT, VT);
     hipLaunchKernelGGL((prep_kernel<DD, true>), dim3(L.nkb, bh), dim3(256), 0, p.stream, K, K, p.sk, p.sk, p.H, p.n, L.nkb, KT, KTB);
     stage_mark(p.stream, "rowmax");
-    hipLaunchKernelGGL((sweep_kernel<true, DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
-                       0, cscale, VT, M, Y, p.O, p.so, 0);
+    hipLaunchKernelGGL(rowmax_kernel<DD>, dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad, cscale, M);
     stage_mark(p.stream, "first_moment");       // omega = sum w, mu~ = sum w k: plain weights times the K tile
-    hipLaunchKernelGGL((sweep_kernel<false, DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
+    hipLaunchKernelGGL((sweep_kernel<DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.nkb,
                        0, cscale, KTB, M, (const float *)nullptr, (void *)MUt, dense, 0, OM);
     hipLaunchKernelGGL((cg_rows_kernel<DD, 0>), rows_grid, dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, p.lambda, eps, MUt, OM,
                        X, R, P, SP, RR, IT, Y, p.rho, p.delta, iters);
     stage_mark(p.stream, "cg_steps");
     for (int t = 0; t < T; ++t) {
-        hipLaunchKernelGGL((sweep_kernel<false, DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
+        hipLaunchKernelGGL((sweep_kernel<DD>), dim3(bh, nq64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n,
                            L.nkb, 0, cscale, KTB, M, (const float *)P, (void *)SP, dense, 0, (float *)nullptr);
         hipLaunchKernelGGL((cg_rows_kernel<DD, 1>), rows_grid, dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, p.lambda, eps, MUt,
                            OM, X, R, P, SP, RR, IT, Y, p.rho, p.delta, iters);
@@ -1338,7 +1389,7 @@ hipError_t forward_cg_impl(const Problem &p, int T, float eps, int32_t *iters)
     if (e != hipSuccess) return e;
     if (first < p.n) {
         stage_mark(p.stream, "output");
-        hipLaunchKernelGGL((sweep_kernel<false, DD>), dim3(bh, (p.n - first + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk,
+        hipLaunchKernelGGL((sweep_kernel<DD>), dim3(bh, (p.n - first + 63) / 64), dim3(256), 0, p.stream, Q, K, p.sq, p.sk,
                            p.H, p.n, L.nkb, first, cscale, VT, M, (const float *)Y, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0,
                            (float *)nullptr);
     }

@@ -398,7 +398,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     }
     // (pivots below half the ridge are dropped, not raised: 500 rows with a common offset of 30 in all features, ridge 10^-2, had NaN in 832
     // rows of dK and in 18 of O)
-    solve_wave_q4<BWD, LIVE, true>(acc, tmu, tq, te, r0, 1.f, &sm.sc[wave][0][0], g, nn, pivot_floor, y1, y0, u1, u0);
+    solve_wave_q4<BWD, LIVE, true, false>(acc, tmu, tq, te, r0, 1.f, &sm.sc[wave][0][0], g, nn, pivot_floor, y1, y0, u1, u0);
     {
         float my = 0.f, mu = 0.f;
 #pragma unroll

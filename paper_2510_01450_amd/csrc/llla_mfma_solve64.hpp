@@ -171,10 +171,12 @@ __device__ inline float row_transpose_sum(const float (&p)[16], int nn)
 //        scw               >= 4 * 16 * SC_PITCH floats of LDS owned by this wave; pivot_floor, DROP as in eliminate16
 //   out: y1[P] = y1_q[16P + r] in lane (q, r), y0 of the lane's query in every lane;  WITH_U: u1[P], u0 likewise
 // with [omega mu~^T; mu~ Sigma~ + lambda I] [y0; y1] = [1; q] and, WITH_U, the same matrix times [u0; u1] = [r0; r1].
+// AUGMENTED = false: (Sigma~ + lambda I) [y1 u1] = [q r1] instead (the fp32 kernels, which have eliminated the intercept); tmu, r0, omega, y0, u0
+// take no part.  (With a zero mu~ carried along: 160 more multiply-adds of some 2300 instructions; 16 x 1024 346.1 instead of 345.3 us.)
 // LIVE < 4 (a call at d = 16 / 32 on zero-padded copies): feature blocks LIVE..3 of every key and query are zero, the
 // matrix is block diagonal with lambda I in those blocks and their right-hand sides are zero, so the solution vanishes
 // there and only blocks 0..LIVE-1 are factorised and substituted.
-template <bool WITH_U, int LIVE = 4, bool DROP = false>
+template <bool WITH_U, int LIVE = 4, bool DROP = false, bool AUGMENTED = true>
 __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[4], float (&tq)[4], float (&te)[4], float r0,
                                               float omega, float *scw, int g, int nn, float pivot_floor, float (&y1)[4],
                                               float &y0, float (&u1)[4], float &u0)
@@ -248,41 +250,54 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
     for (int P = 0; P < NB; ++P) {
         const int dt = S::tix(P, P);
         float am = 0.f, aq = 0.f, ae = 0.f;
-        if constexpr (WITH_U) dot16_bcast3(am, aq, ae, tmu[P], tq[P], te[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
-        else dot16_bcast2(am, aq, tmu[P], tq[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
-        tmu[P] = am; tq[P] = aq;
+        if constexpr (WITH_U && AUGMENTED) dot16_bcast3(am, aq, ae, tmu[P], tq[P], te[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
+        else if constexpr (WITH_U) dot16_bcast2(aq, ae, tq[P], te[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
+        else if constexpr (AUGMENTED) dot16_bcast2(am, aq, tmu[P], tq[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
+        else dot16_bcast1(aq, tq[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
+        if constexpr (AUGMENTED) tmu[P] = am;
+        tq[P] = aq;
         if constexpr (WITH_U) te[P] = ae;
 #pragma unroll
         for (int I = P + 1; I < NB; ++I) {
             const int ot = S::tix(P, I);
-            if constexpr (WITH_U) dot16_bcast3(tmu[I], tq[I], te[I], am, aq, ae, acc[0][ot], acc[1][ot], acc[2][ot], acc[3][ot]);
-            else dot16_bcast2(tmu[I], tq[I], am, aq, acc[0][ot], acc[1][ot], acc[2][ot], acc[3][ot]);
+            if constexpr (WITH_U && AUGMENTED) dot16_bcast3(tmu[I], tq[I], te[I], am, aq, ae, acc[0][ot], acc[1][ot], acc[2][ot], acc[3][ot]);
+            else if constexpr (WITH_U) dot16_bcast2(tq[I], te[I], aq, ae, acc[0][ot], acc[1][ot], acc[2][ot], acc[3][ot]);
+            else if constexpr (AUGMENTED) dot16_bcast2(tmu[I], tq[I], am, aq, acc[0][ot], acc[1][ot], acc[2][ot], acc[3][ot]);
+            else dot16_bcast1(tq[I], aq, acc[0][ot], acc[1][ot], acc[2][ot], acc[3][ot]);
         }
     }
 
     // tmu = a = U^{-T} mu~, tq = c = U^{-T} q (te = e = U^{-T} r1).  Schur step on the intercept:
     // y0 = (1 - a.c) / (omega - a.a), then y1 = U^{-1} (c - a y0), started as z = a y0 - c (the factors N_P are negated)
-    float saa = 0.f, sac = 0.f, sae = 0.f;
-#pragma unroll
-    for (int P = 0; P < NB; ++P) {
-        saa = fmaf(tmu[P], tmu[P], saa);
-        sac = fmaf(tmu[P], tq[P], sac);
-        if constexpr (WITH_U) sae = fmaf(tmu[P], te[P], sae);
-    }
-    saa = row_allsum(saa);
-    sac = row_allsum(sac);
-    const float dinv = 1.f / (omega - saa);
-    y0 = (1.f - sac) * dinv;
     float z[4], zu[4];
 #pragma unroll
     for (int P = NB; P < 4; ++P) { y1[P] = 0.f; u1[P] = 0.f; }
+    if constexpr (AUGMENTED) {
+        float saa = 0.f, sac = 0.f, sae = 0.f;
 #pragma unroll
-    for (int P = 0; P < NB; ++P) z[P] = tmu[P] * y0 - tq[P];
-    if constexpr (WITH_U) {
-        sae = row_allsum(sae);
-        u0 = (r0 - sae) * dinv;
+        for (int P = 0; P < NB; ++P) {
+            saa = fmaf(tmu[P], tmu[P], saa);
+            sac = fmaf(tmu[P], tq[P], sac);
+            if constexpr (WITH_U) sae = fmaf(tmu[P], te[P], sae);
+        }
+        saa = row_allsum(saa);
+        sac = row_allsum(sac);
+        const float dinv = 1.f / (omega - saa);
+        y0 = (1.f - sac) * dinv;
 #pragma unroll
-        for (int P = 0; P < NB; ++P) zu[P] = tmu[P] * u0 - te[P];
+        for (int P = 0; P < NB; ++P) z[P] = tmu[P] * y0 - tq[P];
+        if constexpr (WITH_U) {
+            sae = row_allsum(sae);
+            u0 = (r0 - sae) * dinv;
+#pragma unroll
+            for (int P = 0; P < NB; ++P) zu[P] = tmu[P] * u0 - te[P];
+        }
+    } else {
+#pragma unroll
+        for (int P = 0; P < NB; ++P) {
+            z[P] = -tq[P];
+            if constexpr (WITH_U) zu[P] = -te[P];
+        }
     }
 
     // ---- back substitution, block rows 3..0: x_P = N_P (z_P + sum_{J>P} U(P,J) x_J), outer-product form --------------
