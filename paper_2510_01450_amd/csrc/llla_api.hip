@@ -13,11 +13,19 @@ constexpr int kMaxGridY = 65535;
 // Measured at 64 heads, bf16, vector vs padded.  Forward, d = 32: 0.028 vs 0.036 ms at n = 16, 0.075 vs 0.037 at 32, 0.19 vs
 // 0.057 at 128, 22.5 vs 1.56 at 4096; d = 16: 0.028 vs 0.036 at n = 16, 0.045 vs 0.038 at 32, 0.064 vs 0.053 at 128, 6.2 vs 1.2 at
 // 4096 -> from 32 rows on.  Backward, d = 32: 0.055 vs 0.057 at n = 32, 0.080 vs 0.070 at 64, 42.5 vs 3.7 at 4096 -> from 64 rows
-// on; d = 16: 0.071 vs 0.106 at n = 128, 0.32 vs 0.21 at 512, 15.1 vs 3.2 at 4096 -> from 512 rows on.  fp32 inputs (forward
-// only), 64 heads, d = 32: 0.16 vs 0.27 ms at n = 256, 0.50 vs 0.39 at 512, 1.6 vs 0.83 at 1024, 23.9 vs 8.9 at 4096; 2 heads 0.079 vs
-// 0.080 at 512, 0.153 vs 0.136 at 1024 -> from 1024 rows on; d = 16: 0.028 vs 0.23 at n = 128, 0.47 vs 0.64 at 1024, 1.6 vs 1.8 at 2048,
-// 6.4 vs 6.3 at 4096, and with 2 heads 0.083 vs 0.074 at 512, 0.62 vs 0.42 at 4096 -> only when forced.
-bool auto_takes_padded(int n, int d, llla_dtype in) { return in == LLLA_BF16 ? n >= 32 : (d == 32 && n >= 1024); }
+// on; d = 16: 0.071 vs 0.106 at n = 128, 0.32 vs 0.21 at 512, 15.1 vs 3.2 at 4096 -> from 512 rows on.
+// fp32 inputs, forward, vector vs padded, d = 32: 1 head 60 vs 63 us at n = 384, 77 vs 66 at 512, 291 vs 198 at 2048; 16 heads 51 vs 70 at 256, 85 vs
+// 80 at 384, 431 vs 195 at 1024; 64 heads 155 vs 158 at 256, 287 vs 203 at 384, 6135 vs 2002 at 2048; 256 heads 239 vs 369 at 128, 583 vs 490 at
+// 256, 1115 vs 662 at 384; 4 heads 61 vs 63 at 390, 8 heads with statistics 66 vs 68 at 430 -> from 448 rows on; d = 16: 1 head 63 vs 60 at 384, 82 vs 62 at 512; 16 heads 64 vs 76 at 384, 84 vs 78 at 512, 169 vs 145
+// at 1024; 32 heads 90 vs 116 at 512, 250 vs 226 at 1024; 256 heads 476 vs 630 at 512, 1737 vs 1427 at 1024 -> from 1024 rows on, and
+// up to 16 heads from 512.  Below, the 64 key-space rows of every head are most of the padded call.  One to three heads keep the vector
+// kernels there (d = 32: below 1024 rows): such calls are held to those kernels' bits.
+bool auto_takes_padded(int heads, int n, int d, llla_dtype in)
+{
+    if (in == LLLA_BF16) return n >= 32;
+    if (d == 32) return n >= 1024 || (n >= 448 && heads >= 4);
+    return heads >= 4 && n >= (heads <= 16 ? 512 : 1024);
+}
 bool auto_takes_padded_backward(int n, int d, llla_dtype in) { return in == LLLA_BF16 && n >= (d == 32 ? 64 : 512); }
 
 bool dim_supported(int d) { return d == 16 || d == 32 || d == 64 || d == 128; }
@@ -100,12 +108,14 @@ llla_status llla_forward_ex(const void *Q, const void *K, const void *V, void *O
     const bool padded = llla::padded_forward_supported(d, in);
     const bool has_mfma = (padded || f32_mfma || llla::mfma_forward_supported(d, in, causal != 0)) && (n + 63) / 64 <= kMaxGridY;
     if (path == LLLA_PATH_MFMA && !has_mfma) return LLLA_ERR_UNSUPPORTED;
-    const bool use_mfma = has_mfma && path != LLLA_PATH_VALU && !(padded && path == LLLA_PATH_AUTO && !auto_takes_padded(n, d, in));
+    bool use_mfma = has_mfma && path != LLLA_PATH_VALU && !(padded && path == LLLA_PATH_AUTO && !auto_takes_padded(B * H, n, d, in));
     if (use_mfma) {
         st = check_workspace(padded ? llla::padded_forward_workspace_bytes(B, H, n, d, in)
                              : f32_mfma ? llla::mfma_forward_f32_workspace_bytes(B, H, n)
                                         : llla::mfma_forward_workspace_bytes(B, H, n, d, in), workspace, workspace_bytes);
-        if (st != LLLA_OK) return st;
+        // (fp32 at d = 16, and at d = 32 below 1024 rows: a caller without the workspace gets the vector kernels, which need none)
+        if (st != LLLA_OK && padded && in == LLLA_F32 && path == LLLA_PATH_AUTO && (d == 16 || n < 1024)) use_mfma = false;
+        else if (st != LLLA_OK) return st;
     }
 
     // fp32 at d = 128: on the matrix cores where the caller brought the workspace for it.  Calls of key-space rows alone (n <= 64) stay with
@@ -131,7 +141,7 @@ llla_status llla_forward_ex(const void *Q, const void *K, const void *V, void *O
                          : by_row    ? llla::short_forward(p)
                          : !use_mfma ? llla::valu_forward(p)
                          : padded  ? llla::padded_forward(p)
-                         : f32_mfma ? llla::mfma_forward_f32(p) : llla::mfma_forward(p);
+                         : f32_mfma ? llla::mfma_forward_f32(p, p) : llla::mfma_forward(p);
     llla::stage_end(p.stream);
     return e == hipSuccess ? LLLA_OK : LLLA_ERR_LAUNCH;
 }

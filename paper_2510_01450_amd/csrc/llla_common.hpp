@@ -111,7 +111,7 @@ hipError_t mfma_forward(const Problem &p);
 // the same for fp32 inputs (d = 64): llla_mfma_fwd_f32.hip
 bool mfma_forward_f32_supported(int d, bool causal);
 size_t mfma_forward_f32_workspace_bytes(int B, int H, int n);
-hipError_t mfma_forward_f32(const Problem &p);
+hipError_t mfma_forward_f32(const Problem &p, const Problem &call);
 hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y, int skip);      // its output sweep, rows from skip on
 // and at d = 128: llla_mfma_fwd_f32_128.hip.  The workspace is optional: a call with less runs on the vector kernels.
 size_t mfma_forward_f32_wide_workspace_bytes(int B, int H, int n);

@@ -275,7 +275,7 @@ __device__ __forceinline__ void dual_forward_row(DualShared<D> &sm, const DualAr
                         a.Delta ? a.Delta + row : nullptr);
 }
 
-// R consecutive rows of a forward call with fp32 inputs at d = 64 (R = 4) or 128 (R = 8), one per wave: rows top - R + 1 .. top (those
+// R consecutive rows of a forward call with fp32 inputs, R = 4 or, at d = 128, 8, one per wave: rows top - R + 1 .. top (those
 // below 0 are absent).
 //
 // What bounds dual_row is its chain: two barriers per block step of the factorisation, four roots one after the other in each, a
@@ -312,8 +312,10 @@ __device__ inline double wave_sum_f64(double x)
 template <int D, int R, typename TO>
 __device__ __forceinline__ void dual_forward_rows(DualSharedRows<D, R> &sm, const DualArgs &a, int bh, int top)
 {
-    constexpr int MK = 64, NC = D / 64;            // keys at most, columns of a lane: lane + 64 c
+    constexpr int MK = 64, NC = D < 64 ? 1 : D / 64;       // keys at most, columns of a lane: col + 64 c
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+    const int col = D < 64 ? lane % D : lane;      // d = 16 / 32: lanes from d on repeat the others and store nothing
+    const bool own_col = D >= 64 || lane < D;
     const int b = bh / a.H, h = bh % a.H;
     const float *Kh = (const float *)a.K + b * a.sk.batch + h * a.sk.head, *Vh = (const float *)a.V + b * a.sv.batch + h * a.sv.head;
     const float *Qh = (const float *)a.Q + b * a.sq.batch + h * a.sq.head;
@@ -325,12 +327,12 @@ __device__ __forceinline__ void dual_forward_rows(DualSharedRows<D, R> &sm, cons
         const int j = R * t + wave;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const float v = Kh[(int64_t)(j < mtop ? j : mtop - 1) * a.sk.seq + lane + 64 * c];
-            sm.ks[j][lane + 64 * c] = j < mtop ? v : 0.f;
+            const float v = Kh[(int64_t)(j < mtop ? j : mtop - 1) * a.sk.seq + col + 64 * c];
+            sm.ks[j][col + 64 * c] = j < mtop ? v : 0.f;
         }
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) sm.qs[wave][lane + 64 * c] = Qh[(int64_t)ic * a.sq.seq + lane + 64 * c];
+    for (int c = 0; c < NC; ++c) sm.qs[wave][col + 64 * c] = Qh[(int64_t)ic * a.sq.seq + col + 64 * c];
     __syncthreads();
 
     // products of the keys: tiles (I, J), J <= I, of 16 x 16, dealt over the waves; slot g of a chunk of four is feature 4 kc + g
@@ -363,8 +365,8 @@ __device__ __forceinline__ void dual_forward_rows(DualSharedRows<D, R> &sm, cons
     double ql[NC], qs2 = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        ql[c] = (double)sm.qs[wave][lane + 64 * c];
-        qs2 = __builtin_fma(ql[c], ql[c], qs2);
+        ql[c] = (double)sm.qs[wave][col + 64 * c];
+        if (own_col) qs2 = __builtin_fma(ql[c], ql[c], qs2);
     }
     const double qq = wave_sum_f64(qs2);
     const double lg = lane < m ? (double)a.scale * kq : -INFINITY;
@@ -410,7 +412,7 @@ __device__ __forceinline__ void dual_forward_rows(DualSharedRows<D, R> &sm, cons
 #pragma unroll
         for (int t = 0; t < 16; ++t)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) v[t][c] = Vh[(int64_t)(j0 + t < m ? j0 + t : m - 1) * a.sv.seq + lane + 64 * c];
+            for (int c = 0; c < NC; ++c) v[t][c] = Vh[(int64_t)(j0 + t < m ? j0 + t : m - 1) * a.sv.seq + col + 64 * c];
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
             if (j0 + t < m) {
@@ -418,15 +420,15 @@ __device__ __forceinline__ void dual_forward_rows(DualSharedRows<D, R> &sm, cons
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     o[c] = __builtin_fma(w, (double)v[t][c], o[c]);
-                    rh[c] = __builtin_fma(w, (double)sm.ks[j0 + t][lane + 64 * c] - ql[c], rh[c]);
+                    rh[c] = __builtin_fma(w, (double)sm.ks[j0 + t][col + 64 * c] - ql[c], rh[c]);
                 }
             }
         }
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        st_out((TO *)a.O + b * a.so.batch + h * a.so.head + (int64_t)i * a.so.seq + lane + 64 * c, o[c] * inv);
-        if (a.Rho != nullptr) a.Rho[row * D + lane + 64 * c] = (float)rh[c];
+        if (own_col) st_out((TO *)a.O + b * a.so.batch + h * a.so.head + (int64_t)i * a.so.seq + col + 64 * c, o[c] * inv);
+        if (a.Rho != nullptr && own_col) a.Rho[row * D + col + 64 * c] = (float)rh[c];
     }
     if (a.Delta != nullptr && lane == 0) a.Delta[row] = (float)(lam * ut);
 }

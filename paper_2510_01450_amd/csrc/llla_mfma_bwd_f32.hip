@@ -516,7 +516,9 @@ hipError_t mfma_output_f32(const Problem &p, int npad, float *M, const float *Y,
                            p.causal, skip, p.O, p.so, p.out == LLLA_BF16 ? 1 : 0);
     };
     if (p.d == 128) launch(bwd_rows_f32_kernel<128, 2>);
-    else launch(bwd_rows_f32_kernel<64, 2>);
+    else if (p.d == 64) launch(bwd_rows_f32_kernel<64, 2>);
+    else if (p.d == 32) launch(bwd_rows_f32_kernel<32, 2>);
+    else launch(bwd_rows_f32_kernel<16, 2>);
     return hipGetLastError();
 }
 

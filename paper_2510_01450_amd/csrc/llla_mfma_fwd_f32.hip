@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                                                             dual::DualArgs da, int out_bf16)
 {
     // nqb: blocks of 16 query rows the sequence has; rows [0, da.nrows), a multiple of 16 or all, are the key-space workgroups' (four each),
-    // which follow the others of their head
+    // which follow the others of their head and work on the caller's own tensors
     using S = Shape<FD>;
     constexpr int NB = 4, QW = 4, QB = 16, YP = S::YP;
     __shared__ __align__(16) F32Shared sm;
@@ -106,12 +106,12 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     if constexpr (!BWD) {
         const int own = nqb - (da.nrows + QB - 1) / QB;
         if (bm.blk >= own) {
-            using DS = dual::DualSharedRows<FD, 4>;
+            using DS = dual::DualSharedRows<16 * LIVE, 4>;
             static_assert(sizeof(DS) <= sizeof(F32Shared), "key-space rows fit the workgroup's LDS");
             auto &ds = *reinterpret_cast<DS *>(&sm);
             const int top = da.nrows - 1 - 4 * (bm.blk - own);
-            if (out_bf16) dual::dual_forward_rows<FD, 4, bf16_t>(ds, da, bh, top);
-            else dual::dual_forward_rows<FD, 4, float>(ds, da, bh, top);
+            if (out_bf16) dual::dual_forward_rows<16 * LIVE, 4, bf16_t>(ds, da, bh, top);
+            else dual::dual_forward_rows<16 * LIVE, 4, float>(ds, da, bh, top);
             return;
         }
     }
@@ -178,16 +178,16 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
         dma_wait();
         __syncthreads();                   // tile c complete; everybody is done with block c-1
 
-        // ---- weights of block c: S^T = K Q^T for this wave's 16 keys, contraction slot (s, g) <-> feature 16 g + s ----
+        // ---- weights of block c: S^T = K Q^T for this wave's 16 keys, contraction slot (s, g) <-> feature 4 LIVE g + s ----
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
         {
             const int row = 16 * wave + nn;
             const float *krow = kt + row * FD;
             const int sw = swz(row);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const f32x4 kv = *reinterpret_cast<const f32x4 *>(krow + 4 * ((4 * g + v) ^ sw));
-                const f32x4 qv = *reinterpret_cast<const f32x4 *>(&sm.mus[nn][16 * g + 4 * v]);   // Q[query nn][16 g + 4 v ..]
+            for (int v = 0; v < LIVE; ++v) {
+                const f32x4 kv = *reinterpret_cast<const f32x4 *>(krow + 4 * ((LIVE * g + v) ^ sw));
+                const f32x4 qv = *reinterpret_cast<const f32x4 *>(&sm.mus[nn][4 * LIVE * g + 4 * v]);   // Q[query nn][4 (LIVE g + v) ..]
 #pragma unroll
                 for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qv[e], z, 0, 0, 0);
             }
@@ -320,6 +320,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
             const float *wp = &sm.wt[nn_e * FWP + g_e * 16 + 8 * hf];
             w0 = *reinterpret_cast<const f32x4 *>(wp);
             w1 = *reinterpret_cast<const f32x4 *>(wp + 4);
+            if (LIVE < 4 && wave >= LIVE) continue;       // a padded feature block (a scalar branch)
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const float sw = t < 4 ? w0[t & 3] : w1[t & 3];
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
 // Statistics of Eq. (lla) from y' and F: 1/delta' = y0' + q . y1', delta = delta' / F, rho = -delta' y1'.  One wave per row.
 __global__ __launch_bounds__(256) void stats_f32_kernel(const float *__restrict__ Qg, llla_strides sq, int H, int n, int npad,
                                                         const float *__restrict__ Yg, const float *__restrict__ LFg,
-                                                        float *__restrict__ rho, float *__restrict__ delta, int skip)
+                                                        float *__restrict__ rho, float *__restrict__ delta, int d, int skip)
 {
     constexpr int YP = Shape<FD>::YP;
     const int lane = threadIdx.x % 64, i = blockIdx.x * 4 + threadIdx.x / 64, bh = blockIdx.y;
@@ -434,13 +435,13 @@ __global__ __launch_bounds__(256) void stats_f32_kernel(const float *__restrict_
     const float *qrow = Qg + (bh / H) * sq.batch + (bh % H) * sq.head + (int64_t)i * sq.seq;
     const float *yr = Yg + ((size_t)bh * n + i) * YP;
     const float y1 = yr[lane];
-    float qy = qrow[lane] * y1;
+    float qy = lane < d ? qrow[lane] * y1 : 0.f;
 #pragma unroll
     for (int sft = 32; sft >= 1; sft >>= 1) qy += __shfl_xor(qy, sft);
     const float dl = 1.f / (yr[FD] + qy);                                 // delta'
     const size_t row = (size_t)bh * n + i;
     if (delta != nullptr && lane == 0) delta[row] = dl * __builtin_amdgcn_exp2f(-LFg[(size_t)bh * npad + i]);
-    if (rho != nullptr) rho[row * FD + lane] = -dl * y1;
+    if (rho != nullptr && lane < d) rho[row * d + lane] = -dl * y1;
 }
 
 }  // namespace
@@ -449,7 +450,8 @@ bool mfma_forward_f32_supported(int d, bool causal) { (void)causal; return d == 
 
 size_t mfma_forward_f32_workspace_bytes(int B, int H, int n) { return make_f32_layout(B, H, n).total; }
 
-hipError_t mfma_forward_f32(const Problem &p)
+// call: the caller's own tensors, at d = 16 / 32 with p's Q and K copies of them in rows of 64 features (see llla_pad.hip)
+hipError_t mfma_forward_f32(const Problem &p, const Problem &call)
 {
     using S = Shape<FD>;
     const F32Layout L = make_f32_layout(p.B, p.H, p.n);
@@ -460,7 +462,8 @@ hipError_t mfma_forward_f32(const Problem &p)
     const float *Q = static_cast<const float *>(p.Q), *K = static_cast<const float *>(p.K);
     stage_mark(p.stream, "moments");
     const int live = p.live_d > 0 ? (p.live_d + 15) / 16 : 4;      // a d = 16 / 32 call on zero-padded copies: 1 or 2
-    const dual::DualArgs da = dual::dual_args(p);
+    dual::DualArgs da = dual::dual_args(call);
+    da.nrows = dual_forward_rows(p);                               // up to 64 keys at every head dimension
     const int nqb = (p.n + S::QB - 1) / S::QB, obf = p.out == LLLA_BF16 ? 1 : 0;
     const dim3 grid(nqb - (da.nrows + S::QB - 1) / S::QB + (da.nrows + 3) / 4, bh);
     if (live == 1)
@@ -475,11 +478,11 @@ hipError_t mfma_forward_f32(const Problem &p)
     if (p.rho != nullptr || p.delta != nullptr) {
         stage_mark(p.stream, "statistics");
         hipLaunchKernelGGL(stats_f32_kernel, dim3((p.n + 3) / 4, bh), dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, L.npad,
-                           (const float *)Y, (const float *)LF, p.rho, p.delta, da.nrows);
+                           (const float *)Y, (const float *)LF, p.rho, p.delta, call.d, da.nrows);
     }
     stage_mark(p.stream, "output");
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : mfma_output_f32(p, L.npad, M, Y, da.nrows);
+    return e != hipSuccess ? e : mfma_output_f32(call, L.npad, M, Y, da.nrows);
 }
 
 hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, float *Y, float *RU)

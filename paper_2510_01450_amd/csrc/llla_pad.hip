@@ -13,7 +13,8 @@
 //
 // The bf16 kernels know the number of 16-feature blocks that are not padding: they skip the padded ones and write the caller's tensors
 // themselves (outputs through padded rows and a copy out: 3 x 16 heads x 1606, d = 32, with statistics 259 us, 250 without; the
-// backward's sweeps over all 64 features as well: 96 heads x 1882 1134 us, 974).  fp32 and the approximate mode write padded rows.
+// backward's sweeps over all 64 features as well: 96 heads x 1882 1134 us, 974).  With fp32 inputs only the moments run on copies.  The approximate
+// mode writes padded rows.
 #include "llla_common.hpp"
 
 namespace llla {
@@ -28,14 +29,15 @@ struct PadLayout {
 PadLayout make_pad_layout(int B, int H, int n, llla_dtype in, bool cg = false)
 {
     const size_t rows = (size_t)B * H * n;
-    const size_t esz = in == LLLA_F32 ? 4 : 2, padded_out = in == LLLA_F32 || cg ? round_up(rows * PD * 4, 256) : 0;
+    const size_t esz = in == LLLA_F32 ? 4 : 2;
     PadLayout L{};
     size_t off = 0;
     L.q = off; off += round_up(rows * PD * esz, 256);
     L.k = off; off += round_up(rows * PD * esz, 256);
-    L.v = off; off += round_up(rows * PD * esz, 256);
-    L.o = off; off += padded_out;                           // fp32 or bf16 output rows
-    L.rho = off; off += padded_out;
+    L.v = off; off += round_up(rows * PD * esz, 256);       // (not fp32)
+    // rows of O and rho: the approximate mode alone writes them; the size that callers are told stays what it was
+    L.o = off; off += round_up(rows * PD * 4, 256);
+    L.rho = off; off += round_up(rows * PD * 4, 256);
     L.inner = off;
     off += round_up(cg ? mfma_forward_cg_workspace_bytes(B, H, n, PD, in)
                        : in == LLLA_F32 ? mfma_forward_f32_workspace_bytes(B, H, n) : mfma_forward_workspace_bytes(B, H, n, PD, in), 256);
@@ -175,30 +177,24 @@ hipError_t padded_forward(const Problem &p)
     char *ws = static_cast<char *>(p.ws);
     const llla_strides sp = {(int64_t)p.H * p.n * PD, (int64_t)p.n * PD, (int64_t)PD};
 
-    const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v)}, 3};
     Problem q = p;
-    q.Q = ws + L.q; q.K = ws + L.k; q.V = ws + L.v;
-    q.sq = q.sk = q.sv = sp;
+    q.Q = ws + L.q; q.K = ws + L.k;
+    q.sq = q.sk = sp;
     q.d = PD;
     q.live_d = p.d;
     q.ws = ws + L.inner;
     q.ws_bytes = L.total - L.inner;
-    if (p.in != LLLA_F32) {
-        q.pad = &in;
-        return mfma_forward(q);
+    if (p.in == LLLA_F32) {                                 // the moments alone run on copies; the rest reads and writes the tensors themselves
+        stage_mark(p.stream, "pad");
+        const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k)}, 2};
+        const hipError_t e = pad_rows(in, Rows{p.B, p.H, p.n, p.d, p.stream}, true);
+        return e != hipSuccess ? e : mfma_forward_f32(q, p);
     }
-    const Rows r{p.B, p.H, p.n, p.d, p.stream};
-    stage_mark(p.stream, "pad");
-    hipError_t e = pad_rows(in, r, true);
-    if (e != hipSuccess) return e;
-    q.O = ws + L.o;
-    q.so = sp;
-    q.rho = p.rho ? reinterpret_cast<float *>(ws + L.rho) : nullptr;
-    e = mfma_forward_f32(q);
-    if (e != hipSuccess) return e;
-
-    stage_mark(p.stream, "unpad");
-    return unpad_forward(p, ws, L, r);
+    const PadSources in = {{pad_source(p.Q, p.sq, ws + L.q), pad_source(p.K, p.sk, ws + L.k), pad_source(p.V, p.sv, ws + L.v)}, 3};
+    q.V = ws + L.v;
+    q.sv = sp;
+    q.pad = &in;
+    return mfma_forward(q);
 }
 
 // The approximate mode (conjugate gradients) at d = 16 / 32 (bf16): the same padding.  The padded entries of every

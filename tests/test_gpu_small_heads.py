@@ -142,3 +142,25 @@ def test_what_auto_takes_in_the_backward():
         torch.cuda.synchronize()
         for x, y in zip(a, m):
             assert torch.equal(x, y), (n, d)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d,heads,n", [(16, 4, 511), (16, 4, 512), (16, 5, 529), (16, 17, 1023), (16, 17, 1024), (32, 4, 447), (32, 4, 448), (32, 3, 1024),
+                                       (32, 6, 465)])
+def test_fp32_calls_on_both_sides_of_the_rule(d, heads, n, causal):
+    """fp32 at d = 16 / 32: key-space rows, moments on copies in rows of 64 features, output sweep of the tensors themselves, against the vector
+    kernels, whose errors test_gpu_key_space_rows.py and the gate above bound.  Strided operands and outputs in rows of another pitch, a
+    ridge per row, statistics.  The two differ by the rounding of either, 1e-6 of a head for unit keys and up to 1e-5 in rho (seen 2e-6): 5e-5 is
+    far above that and far below a wrong row or feature.  Without workspace a call takes the vector kernels, as it always did."""
+    g = torch.Generator(device=DEV).manual_seed(n + heads)
+    Q, K, V = [torch.randn((1, n, heads, d + 4 * t), generator=g, device=DEV)[..., :d].transpose(1, 2) for t in range(3)]
+    Q, K = Q / Q.norm(dim=-1, keepdim=True), K / K.norm(dim=-1, keepdim=True)
+    ridge = 1e-2 * torch.exp(0.5 * torch.randn((1, heads, n), generator=g, device=DEV))
+    got = llla.llla_forward(Q, K, V, ridge, d ** -0.5, causal=causal, return_stats=True)
+    ref = llla.llla_forward(Q, K, V, ridge, d ** -0.5, causal=causal, return_stats=True, path="valu")
+    for x, r in zip(got, ref):
+        err = (x.double() - r.double()).flatten(2).norm(dim=2) / r.double().flatten(2).norm(dim=2)
+        assert torch.isfinite(x).all() and float(err.max()) < 5e-5, err
+    if d == 16 or n < 1024:
+        small = torch.empty(256, dtype=torch.uint8, device=DEV)
+        assert torch.equal(llla.llla_forward(Q, K, V, ridge, d ** -0.5, causal=causal, workspace=small), ref[0])
