@@ -1,6 +1,6 @@
 // Matrix-core (MFMA) forward path of Local Linear Attention for gfx950: bf16 inputs, d = 64 or 128.
 //
-// Stages (all on the caller's stream, workspace holds only Theta(B*H*n*d) data):
+// Stages (all on the caller's stream, workspace holds only Theta(B*H*n*d) data; the first two are one launch):
 //   prep    K -> f16 (for the approximate mode V too), re-tiled as [key block of 32][feature][key] so that MFMA
 //           operands whose contraction index is the key are 16-byte contiguous;
 //   rowmax  m_i = max_{j<=i} c <q_i,k_j>  (c = scale*log2 e), the exact row maximum that the
@@ -9,7 +9,7 @@
 //           omega_i, mu~_i, Sigma~_i of Eq. (tilded_form) accumulated ON CHIP as MFMA accumulators
 //           (Sigma~_i: upper triangle of 16x16 tiles), then the exact per-query solve of
 //           [omega mu~^T; mu~ Sigma~ + lambda I] y = [1; q] by a 16-blocked Cholesky whose block
-//           products run on fp32 MFMA; only y_i (d+1 floats) and m_i leave the chip;
+//           products run on the matrix cores; only y_i (d+1 floats) and m_i leave the chip;
 //   output  s_ij = w_ij (y0_i + k_j . y1_i), O = S V  (Eq. (lla) with y1 = -rho/delta,
 //           y0 = (1 + q.rho)/delta), a flash-style sweep (llla_mfma_bwd.hip).
 // The first 2d rows of every sequence, whose systems are the worst conditioned, take the "precise" variant of the
