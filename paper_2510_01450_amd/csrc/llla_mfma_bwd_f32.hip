@@ -169,8 +169,13 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     f32x4 acc[NB];
 #pragma unroll
     for (int J = 0; J < NB; ++J) acc[J] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float csum = 0.f, best = -INFINITY;
+    float csum = 0.f, best = -INFINITY, cf[4] = {0.f, 0.f, 0.f, 0.f};
     int arg = 0;
+    // Where not every query of the wave sees every key of a tile, the products multiply what a row does not see by zero.  If one of the
+    // tile's keys (MODE 2: values) is not finite they are left out instead, as on the vector kernels, and formed after the loop, where
+    // nothing else is in registers: rows before such a key keep their results.
+    constexpr bool GUARD = MODE == 2;
+    bool odd = false;
 
     const int nblk = (MODE == 2 && !causal ? n - 1 : min(i0 + RT - 1, n - 1)) / RT + 1;
     auto issue = [&](int c) {
@@ -201,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
                 }
             }
         }
-        float zs[4], cf[4];
+        float zs[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) zs[r] = z[r] * cscale;
         if constexpr (MODE == 0) {
@@ -243,39 +248,44 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
                 cf[r] = j <= iq ? (j == jstar ? pv + corr : pv) : 0.f;
             }
         }
-        if constexpr (MODE == 2 && DD == 128) {
-            // Where not every query of the wave sees every key of the tile the product multiplies values that a row does not see by zero.  If
-            // one of the tile is not finite, they are left out instead, as on the vector kernels that served d = 128 before (a scalar branch;
-            // at d = 64, where the product has always been taken, its 31 registers cost a workgroup per compute unit and 0.8 % of the call).
-            if (jb + 15 > (causal ? min(i0 + 16 * rg, n - 1) : n - 1)) {
-                auto value = [&](int kr, int J) { return vt[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))]; };
-                bool odd = false;
+        const float *tile = MODE == 2 ? vt : kt;             // what the coefficients multiply: keys or values, key row kr, feature 16 J + nn
+        auto value = [&](int kr, int J) { return tile[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))]; };
+        if constexpr (GUARD) {
+            if (jb + 15 > (causal ? min(i0 + 16 * rg, n - 1) : n - 1)) {        // (a scalar branch, in the last step)
+                float zero = 0.f;                            // 0 times every element
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int J = 0; J < NB; ++J) odd = odd || !(fabsf(value(4 * g + r, J)) < INFINITY);
-                if (__any(odd)) {
-                    for (int gk = 0; gk < 4; ++gk)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {          // key 4 gk + r, query 4 g + e
-                                const float w = __shfl(cf[r], 16 * gk + 4 * g + e);
-                                const bool seen = jb + 4 * gk + r <= (causal ? min(i0 + 16 * rg + 4 * g + e, n - 1) : n - 1);
-#pragma unroll
-                                for (int J = 0; J < NB; ++J) acc[J][e] = seen ? fmaf(w, value(4 * gk + r, J), acc[J][e]) : acc[J][e];
-                            }
-                    continue;
-                }
+                    for (int J = 0; J < NB; ++J) zero = fmaf(value(4 * g + r, J), 0.f, zero);
+                odd = __any(!(zero == 0.f));
+                asm volatile("" ::: "memory");               // (read again for the products: kept, they cost registers in every step)
+                if (odd) continue;
             }
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int kr = 4 * g + r;
-            const float *krow = (MODE == 2 ? vt : kt) + kr * DD + (nn & 3);
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int J = 0; J < NB; ++J)
-                acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], krow[4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))], acc[J], 0, 0, 0);
+            for (int J = 0; J < NB; ++J) acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], value(4 * g + r, J), acc[J], 0, 0, 0);
+    }
+    if constexpr (GUARD) {
+        if (odd) {                                           // the wave's share of the last step, which is still in LDS, without what a row does not see
+            const int c = nblk - 1, jb = c * RT + 16 * ks;
+            const float *tile = &tiles[c & 1][MODE == 2 ? 1 : 0][16 * ks * DD];
+#pragma unroll 1
+            for (int gk = 0; gk < 4; ++gk)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {            // key 4 gk + r, query 4 g + e
+                        const int kr = 4 * gk + r;
+                        const float w = __shfl(cf[r], 16 * gk + 4 * g + e);
+                        const bool seen = jb + kr <= (causal ? min(i0 + 16 * rg + 4 * g + e, n - 1) : n - 1);
+#pragma unroll
+                        for (int J = 0; J < NB; ++J) {
+                            const float v = tile[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))];
+                            acc[J][e] = seen ? fmaf(w, v, acc[J][e]) : acc[J][e];
+                        }
+                    }
         }
     }
 

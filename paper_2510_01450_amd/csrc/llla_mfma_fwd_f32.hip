@@ -228,6 +228,20 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
             }
             om_part += (wf[0] + wf[1]) + (wf[2] + wf[3]);
         }
+        // The last block holds keys behind the workgroup's first query, whose weight 0 must stay 0 in the products below: an element that is not
+        // finite is cleared, now that its logits are formed (rows that see it have a weight that is not a number).  Each wave has read
+        // only its own 16 rows so far.  (Once per workgroup; a select or a check in the products' loop cost 1 to 3 % of a d = 16 / 32 call.)
+        if (c == nblk - 1) {
+            float *krow = sm.kt[c & 1] + (16 * wave + nn) * FD;
+#pragma unroll
+            for (int v = 0; v < LIVE; ++v) {
+                f32x4 *kv = reinterpret_cast<f32x4 *>(krow + 4 * ((LIVE * g + v) ^ swz(16 * wave + nn)));
+                f32x4 x = *kv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = fabsf(x[e]) < INFINITY ? x[e] : 0.f;
+                *kv = x;
+            }
+        }
         __syncthreads();                   // weights and rescale factors of block c visible
         if (c + 1 < nblk) issue_dma(c + 1);
 

@@ -164,3 +164,23 @@ def test_fp32_calls_on_both_sides_of_the_rule(d, heads, n, causal):
     if d == 16 or n < 1024:
         small = torch.empty(256, dtype=torch.uint8, device=DEV)
         assert torch.equal(llla.llla_forward(Q, K, V, ridge, d ** -0.5, causal=causal, workspace=small), ref[0])
+
+
+@pytest.mark.parametrize("what", ["keys", "values"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,n,path", [(16, 512, "auto"), (16, 545, "auto"), (32, 448, "auto"), (32, 471, "auto"), (16, 150, "mfma"), (32, 150, "mfma"), (64, 143, "auto"),
+                                      (64, 160, "auto")])
+def test_a_row_does_not_see_what_is_behind_it(d, n, path, bad, what):
+    """fp32: keys or values that are not finite from a row on (a sequence padded with whatever its buffer holds) leave the rows before it as the
+    sequence without them gives them: the oracle's rows, in the gate of the other tests.  Rows on both sides of the blocks of 16 queries, of 32
+    keys and of 64, and the last one alone."""
+    w = _case("behind", 1, 4, n, d, "f32", index=490 + d + n)
+    Q, K, V = [t.to(DEV) for t in workloads.make_inputs(w)]
+    ref = np.asarray(oracle.forward(Q.cpu(), K.cpu(), V.cpu(), w.lam, w.scale))
+    for first in (65, 97, 111, n - 33, n - 17, n - 16, n - 5, n - 1):
+        T = {"keys": K.clone(), "values": V.clone()}
+        T[what][:, :, first:] = bad
+        O, rho, delta = llla.llla_forward(Q, T["keys"], T["values"], w.lam, w.scale, path=path, return_stats=True)
+        check(O[:, :, :first].cpu().numpy(), ref[:, :, :first], np.arange(first), d, w.tol, "%s from %d" % (what, first))
+        assert not bool(torch.isfinite(O[:, :, first:]).any())
+        assert bool(torch.isfinite(rho[:, :, :first]).all()) and bool(torch.isfinite(delta[:, :, :first]).all())
