@@ -174,7 +174,6 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
     // Where not every query of the wave sees every key of a tile, the products multiply what a row does not see by zero.  If one of the
     // tile's keys (MODE 2: values) is not finite they are left out instead, as on the vector kernels, and formed after the loop, where
     // nothing else is in registers: rows before such a key keep their results.
-    constexpr bool GUARD = MODE == 2;
     bool odd = false;
 
     const int nblk = (MODE == 2 && !causal ? n - 1 : min(i0 + RT - 1, n - 1)) / RT + 1;
@@ -250,43 +249,39 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
         }
         const float *tile = MODE == 2 ? vt : kt;             // what the coefficients multiply: keys or values, key row kr, feature 16 J + nn
         auto value = [&](int kr, int J) { return tile[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))]; };
-        if constexpr (GUARD) {
-            if (jb + 15 > (causal ? min(i0 + 16 * rg, n - 1) : n - 1)) {        // (a scalar branch, in the last step)
-                float zero = 0.f;                            // 0 times every element
+        if (jb + 15 > (causal ? min(i0 + 16 * rg, n - 1) : n - 1)) {        // (a scalar branch, in the last step)
+            float zero = 0.f;                                // 0 times every element
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int J = 0; J < NB; ++J) zero = fmaf(value(4 * g + r, J), 0.f, zero);
-                odd = __any(!(zero == 0.f));
-                asm volatile("" ::: "memory");               // (read again for the products: kept, they cost registers in every step)
-                if (odd) continue;
-            }
+                for (int J = 0; J < NB; ++J) zero = fmaf(value(4 * g + r, J), 0.f, zero);
+            odd = __any(!(zero == 0.f));
+            asm volatile("" ::: "memory");                   // (read again for the products: kept, they cost registers in every step)
+            if (odd) continue;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int J = 0; J < NB; ++J) acc[J] = __builtin_amdgcn_mfma_f32_16x16x4f32(cf[r], value(4 * g + r, J), acc[J], 0, 0, 0);
     }
-    if constexpr (GUARD) {
-        if (odd) {                                           // the wave's share of the last step, which is still in LDS, without what a row does not see
-            const int c = nblk - 1, jb = c * RT + 16 * ks;
-            const float *tile = &tiles[c & 1][MODE == 2 ? 1 : 0][16 * ks * DD];
+    if (odd) {                                               // the wave's share of the last step, which is still in LDS, without what a row does not see
+        const int c = nblk - 1, jb = c * RT + 16 * ks;
+        const float *tile = &tiles[c & 1][MODE == 2 ? 1 : 0][16 * ks * DD];
 #pragma unroll 1
-            for (int gk = 0; gk < 4; ++gk)
+        for (int gk = 0; gk < 4; ++gk)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {            // key 4 gk + r, query 4 g + e
-                        const int kr = 4 * gk + r;
-                        const float w = __shfl(cf[r], 16 * gk + 4 * g + e);
-                        const bool seen = jb + kr <= (causal ? min(i0 + 16 * rg + 4 * g + e, n - 1) : n - 1);
+                for (int e = 0; e < 4; ++e) {                // key 4 gk + r, query 4 g + e
+                    const int kr = 4 * gk + r;
+                    const float w = __shfl(cf[r], 16 * gk + 4 * g + e);
+                    const bool seen = jb + kr <= (causal ? min(i0 + 16 * rg + 4 * g + e, n - 1) : n - 1);
 #pragma unroll
-                        for (int J = 0; J < NB; ++J) {
-                            const float v = tile[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))];
-                            acc[J][e] = seen ? fmaf(w, v, acc[J][e]) : acc[J][e];
-                        }
+                    for (int J = 0; J < NB; ++J) {
+                        const float v = tile[kr * DD + (nn & 3) + 4 * ((4 * J + (nn >> 2)) ^ swz<DD>(kr))];
+                        acc[J][e] = seen ? fmaf(w, v, acc[J][e]) : acc[J][e];
                     }
-        }
+                }
     }
 
     // ---- the two halves of a row's keys meet in LDS ---------------------------------------------------------------

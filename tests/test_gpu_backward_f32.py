@@ -1,4 +1,4 @@
-"""fp32 backward on the matrix cores (d = 16, 32 and 64): the edges of its 32-row tiles and of the halves they are split into,
+"""fp32 backward on the matrix cores: the edges of its 32-row tiles and of the halves they are split into,
 against the backward oracle, with the fp32 gate of the other backward tests (parity.check_grad, 1e-3)."""
 import numpy as np
 import pytest
@@ -7,6 +7,7 @@ import torch
 import paper_2510_01450_amd as llla
 import workloads
 from oracle import backward as ob
+from parity import check_grad
 from test_gpu_backward import DEV, _backward, _case, _compare, _floor, _upstream
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +102,24 @@ def test_common_offset_stays_finite(n, offset):
     Q, K = Q + offset, K + offset
     for x in (llla.llla_forward(Q, K, V, 1e-2, 1 / 8.0),) + llla.llla_backward(Q, K, V, G, 1e-2, 1 / 8.0, return_dlambda=True):
         assert bool(torch.isfinite(x).all())
+
+
+@pytest.mark.parametrize("what", ["keys", "values"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d,n", [(16, 100), (16, 143), (32, 64), (32, 111), (64, 40), (64, 111), (128, 40), (128, 143)])
+def test_a_row_does_not_see_what_is_behind_it(d, n, bad, what):
+    """Keys or values that are not finite from a row on leave dQ and dlambda of the rows before it as the sequence without them gives
+    them.  (dK and dV of the keys before it are sums over all later rows.)  Rows on both sides of the tiles of 16 and the blocks of 32."""
+    w = _case(1, 4, n, d, "f32", index=580 + d + n)
+    Q, K, V = workloads.make_inputs(w)
+    G = _upstream(w, 90 + n)
+    floor = _floor(V, G, w.lam)
+    full = ob.backward(Q, K, V, G, w.lam, w.scale)
+    for first in (5, 17, n - 33, n - 16, n - 7, n - 1):
+        T = {"keys": K.clone(), "values": V.clone()}
+        T[what][:, :, first:] = bad
+        got = _backward(w, Q, T["keys"], T["values"], G, w.lam)
+        for name, t in (("dQ", 0), ("dlambda", 3)):
+            ref = np.asarray(full[t])[:, :, :first]
+            print(name, check_grad(got[t][:, :, :first], ref, d, w.tol, "%s from %d: %s" % (what, first, name), floor=floor[name]))
+            assert not np.isfinite(got[t][:, :, first:]).any()
