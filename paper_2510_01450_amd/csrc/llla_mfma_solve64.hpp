@@ -101,6 +101,19 @@ __device__ inline void dot16_bcast3(float &a0, float &a1, float &a2, float s0, f
 #undef L
 }
 
+// x, y <- L^-1 x, L^-1 y for the unit lower triangular L of eliminate16, nl[k] = -L[r][k] in lane r: element k, final at step k, into all below.
+__device__ inline void substitute16(float &x, float &y, const float (&nl)[16])
+{
+#define L(K)                                                                                     \
+    "v_fmac_f32_dpp %[x], %[x], %[n" #K "]" LLLA_DPP(K) "v_fmac_f32_dpp %[y], %[y], %[n" #K "]" LLLA_DPP(K) "s_nop 0\n\t"
+#define N(K) [n##K] "v"(nl[K])
+    asm volatile("s_nop 1\n\t" L(0) L(1) L(2) L(3) L(4) L(5) L(6) L(7) L(8) L(9) L(10) L(11) L(12) L(13) L(14)
+                 : [x] "+v"(x), [y] "+v"(y)
+                 : N(0), N(1), N(2), N(3), N(4), N(5), N(6), N(7), N(8), N(9), N(10), N(11), N(12), N(13), N(14));
+#undef N
+#undef L
+}
+
 // Sum of x over the 16 lanes of the caller's row, in every lane of the row.
 __device__ inline float row_allsum(float x)
 {
@@ -185,6 +198,12 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
     constexpr int QW = 4, NB = LIVE;       // blocks LIVE..3 are lambda I with zero right-hand sides (see above): y1 = u1 = 0 there
     static_assert(LIVE >= 1 && LIVE <= 4, "four 16-wide blocks");
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // The fp32 backward at d = 16 / 32 keeps L of the diagonal tiles (16 registers each, which d = 64 does not have) for the forward substitution:
+    // r1 - mu~ r0 / omega of a row with fewer keys than features lies in the span of its centred keys, and L^-1 formed first and then multiplied
+    // loses there what substitution keeps (u1 of rows 1 to 8 at d = 16, normal keys, ridge 10^-4: errors 1.2 to 1.6 times those of the vector
+    // kernels; y1, whose right-hand side q is not in that span, 0.8 to 1.0).
+    constexpr bool KEEP_L = WITH_U && !AUGMENTED && LIVE < 4;
+    float lower[KEEP_L ? NB : 1][16], nroot[KEEP_L ? NB : 1];
 
     // ---- factorisation (as in factorise_one): acc(P,J), P < J, becomes U(P,J); acc(P,P) becomes N_P = -U(P,P)^{-1}, by columns -----
 #pragma unroll
@@ -209,6 +228,11 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
         wave_sync();
         eliminate16<false, DROP>(a, nl, ndinv, nn, pivot_floor, nullptr);
         invert16(nl, ndinv, nn, li);
+        if constexpr (KEEP_L) {
+#pragma unroll
+            for (int k = 0; k < 15; ++k) lower[P][k] = nl[k];
+            nroot[P] = ndinv;
+        }
         if (P + 1 < NB) {
             float *my = scw + g * 16 * SC_PITCH;
 #pragma unroll
@@ -250,7 +274,11 @@ __device__ __forceinline__ void solve_wave_q4(f32x4 (&acc)[4][10], float (&tmu)[
     for (int P = 0; P < NB; ++P) {
         const int dt = S::tix(P, P);
         float am = 0.f, aq = 0.f, ae = 0.f;
-        if constexpr (WITH_U && AUGMENTED) dot16_bcast3(am, aq, ae, tmu[P], tq[P], te[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
+        if constexpr (KEEP_L) {
+            substitute16(tq[P], te[P], lower[P]);
+            aq = tq[P] * nroot[P];
+            ae = te[P] * nroot[P];
+        } else if constexpr (WITH_U && AUGMENTED) dot16_bcast3(am, aq, ae, tmu[P], tq[P], te[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
         else if constexpr (WITH_U) dot16_bcast2(aq, ae, tq[P], te[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
         else if constexpr (AUGMENTED) dot16_bcast2(am, aq, tmu[P], tq[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);
         else dot16_bcast1(aq, tq[P], acc[0][dt], acc[1][dt], acc[2][dt], acc[3][dt]);

@@ -139,3 +139,17 @@ def test_small_heads_with_a_common_offset(d, n):
     ratio = float(np.exp(np.mean(np.log(err[0] / err[1]))))
     print("ratio %.3f" % ratio)
     assert ratio < 0.8
+
+
+@pytest.mark.parametrize("d,n,bound", [(16, 120, 0.95), (32, 90, 1.1)])
+def test_small_heads_few_keys_and_a_small_ridge(d, n, bound):
+    """|k|^2 / ridge = 1.6e5 and 3.2e5: what the solve for u1 loses in rows with fewer keys than features is most of the error of dQ.  Geometric
+    mean of the heads' errors against the vector kernels': seen 0.91 and 1.03, with L^-1 formed first 1.23 and 1.13."""
+    w = _case(1, 48, n, d, "f32", values="normal", index=596 + d, lam=1e-4)
+    Q, K, V = workloads.make_inputs(w)
+    G = _upstream(w, 97 + d)
+    ref = np.asarray(ob.backward(Q, K, V, G, w.lam, w.scale)[0])
+    err = [np.linalg.norm((_backward(w, Q, K, V, G, w.lam, path)[0] - ref).reshape(48, -1), axis=1) for path in ("auto", "valu")]
+    ratio = float(np.exp(np.mean(np.log(err[0] / err[1]))))
+    print("ratio %.3f" % ratio)
+    assert ratio < bound, ratio
