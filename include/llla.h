@@ -31,6 +31,8 @@
  *   - tensors are [batch, head, seq, d] with the innermost (d) stride equal to 1; the other strides
  *     are given in elements in an llla_strides;
  *   - inputs are never modified, outputs are fully overwritten, results are deterministic;
+ *   - causal fp32 calls: a key or value that is not finite reaches only the rows that see it (in the backward pass dQ and
+ *     dlambda of those rows, and every dK and dV that sums over them);
  *   - arguments are validated on the host before anything is enqueued; on error nothing has been
  *     launched and the outputs are untouched (LLLA_ERR_LAUNCH excepted);
  *   - `workspace` is scratch of at least the size the matching *_workspace_bytes() call returns
@@ -108,8 +110,10 @@ llla_status llla_forward(const void *Q, const void *K, const void *V, void *O,
  * kernels wherever they exist, except where the vector kernels measured faster: bf16 inputs with d = 16 / 32 and fewer
  * than 32 rows; fp32 inputs with d = 32 below 1024 rows (below 448 from four heads on) and with d = 16 below 1024 rows (below 512
  * up to 16 heads) or fewer than four heads.  Of those fp32 calls it runs few sequences of at most 256 rows one wave
- * per row, in fp32 too.  fp32 calls with d = 16, with d = 32 and fewer than 1024 rows, and with d = 128 run on the vector
- * kernels where the workspace is missing or too small.  bf16 inputs on the matrix cores are subject to the f16 value
+ * per row, in fp32 too.  fp32 inputs with d = 128 take matrix-core kernels of their own, which LLLA_PATH_MFMA does not reach
+ * (calls of at most 64 rows only from 1024 rows of all heads together on).  fp32 calls with d = 16, with d = 32 and fewer than
+ * 1024 rows, and with d = 128 run on the vector kernels where the workspace is missing or too small.  As the choice looks at B * H, the last
+ * bits of a sequence's result can depend on how many others the call holds.  bf16 inputs on the matrix cores are subject to the f16 value
  * range stated at the top of this file. */
 llla_status llla_forward_path(const void *Q, const void *K, const void *V, void *O,
                               llla_strides sq, llla_strides sk, llla_strides sv, llla_strides so,
@@ -174,9 +178,10 @@ llla_status llla_forward_cg(const void *Q, const void *K, const void *V, void *O
  *                 sweeps around it run on the bf16 matrix cores from split operands.  bf16 inputs with d = 16 or 32 run it at d = 64 on
  *                 zero-padded copies, as the forward does (the gradient of a padded feature is zero and is dropped);
  *                 LLLA_PATH_AUTO takes that route for d = 32 from 64 rows on, and for d = 16 from 512 rows on.
- *                 LLLA_PATH_AUTO runs fp32 inputs with d = 64 on the fp32 matrix cores (fp32 arithmetic; the second moment
- *                 from operands split into three bf16, 24 significant bits), or on the vector path when the workspace is too small
- *                 for that but large enough for the vector path.
+ *                 LLLA_PATH_AUTO runs fp32 inputs on the fp32 matrix cores (fp32 arithmetic; the second moment from operands
+ *                 split into three bf16, 24 significant bits): d = 64 and 128 always, d = 32 from 64 rows on, d = 16 from 96;
+ *                 or on the vector path when the workspace is smaller than llla_backward_workspace_bytes but large enough for
+ *                 that path (2 d + 8 floats a row).
  * Causal only.  Workspace: llla_backward_workspace_bytes (Theta(B H n d); enough for every path).
  */
 size_t llla_backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in);

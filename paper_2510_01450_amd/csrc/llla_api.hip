@@ -16,10 +16,11 @@ constexpr int kMaxGridY = 65535;
 // on; d = 16: 0.071 vs 0.106 at n = 128, 0.32 vs 0.21 at 512, 15.1 vs 3.2 at 4096 -> from 512 rows on.
 // fp32 inputs, forward, vector vs padded, d = 32: 1 head 60 vs 63 us at n = 384, 77 vs 66 at 512, 291 vs 198 at 2048; 16 heads 51 vs 70 at 256, 85 vs
 // 80 at 384, 431 vs 195 at 1024; 64 heads 155 vs 158 at 256, 287 vs 203 at 384, 6135 vs 2002 at 2048; 256 heads 239 vs 369 at 128, 583 vs 490 at
-// 256, 1115 vs 662 at 384; 4 heads 61 vs 63 at 390, 8 heads with statistics 66 vs 68 at 430 -> from 448 rows on; d = 16: 1 head 63 vs 60 at 384, 82 vs 62 at 512; 16 heads 64 vs 76 at 384, 84 vs 78 at 512, 169 vs 145
-// at 1024; 32 heads 90 vs 116 at 512, 250 vs 226 at 1024; 256 heads 476 vs 630 at 512, 1737 vs 1427 at 1024 -> from 1024 rows on, and
-// up to 16 heads from 512.  Below, the 64 key-space rows of every head are most of the padded call.  One to three heads keep the vector
-// kernels there (d = 32: below 1024 rows): such calls are held to those kernels' bits.
+// 256, 1115 vs 662 at 384; 4 heads 61 vs 63 at 390, 8 heads with statistics 66 vs 68 at 430 -> from 448 rows on; d = 16: 1 head 63 vs 60 at 384,
+// 82 vs 62 at 512; 16 heads 64 vs 76 at 384, 84 vs 78 at 512, 169 vs 145 at 1024; 32 heads 90 vs 116 at 512, 250 vs 226 at 1024; 256 heads 476 vs
+// 630 at 512, 1737 vs 1427 at 1024 -> from 1024 rows on, and up to 16 heads from 512.  Below, the 64 key-space rows of every head are most
+// of the padded call.  One to three heads stay on the vector kernels (d = 32: below 1024 rows) not because those are faster -- from 512 rows on they are
+// not, 2 heads x 4096 at d = 16 take 614 us there -- but because the results of such calls are fixed to those kernels' bits (test_what_auto_takes).
 bool auto_takes_padded(int heads, int n, int d, llla_dtype in)
 {
     if (in == LLLA_BF16) return n >= 32;

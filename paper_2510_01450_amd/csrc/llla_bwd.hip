@@ -537,10 +537,9 @@ size_t backward_workspace_bytes(int B, int H, int n, int d, llla_dtype in, llla_
 }
 
 // LLLA_PATH_AUTO and the fp32 matrix-core backward: d = 64 always; d = 16 / 32 from the size on from which its five launches pay.  us, vector
-// kernels vs matrix cores.  d = 32: 4 heads 25 vs 33 at 32 rows, 34 vs 33 at 48, 36 vs 33 at 64, 100 vs 66 at 256; 256 heads 132 vs 58 at 64,
-// 944 vs 304 at 256.  d = 16: 4 heads 33 vs 33 at 64, 45 vs 34 at 96, 192 vs 78 at 512; 256 heads 39 vs 40 at 64, 69 vs 59 at 96, 1006 vs 539
-// at 512.  Errors against fp64 (geometric mean over 8 to 32 heads, 100 to 1500 rows, unit and normal values): d = 32 0.80 to 1.00 times those of
-// the vector kernels, d = 16 0.82 to 1.08.
+// kernels vs matrix cores.  d = 32: 4 heads 25 vs 33 at 32 rows, 34 vs 33 at 48, 35 vs 32 at 64, 100 vs 64 at 256; 256 heads 131 vs 57 at 64,
+// 944 vs 293 at 256.  d = 16: 4 heads 33 vs 33 at 64, 44 vs 31 at 96, 191 vs 73 at 512; 256 heads 39 vs 40 at 64, 67 vs 55 at 96, 1003 vs 467
+// at 512.  Errors against fp64: see llla_mfma_bwd_f32.hip.
 static bool takes_backward_f32(int n, int d, llla_dtype in)
 {
     return mfma_backward_f32_supported(n, d, in) && (d >= 64 || n >= (d == 32 ? 64 : 96));

@@ -923,7 +923,9 @@ constexpr long long TWO_QUERY_BLOCKS_FROM = 1536, TWO_KEY_BLOCKS_FROM = 768;
 // price is the registers of three terms for all, i.e. fewer resident workgroups.  us a call, two launches and one: 4 heads x 400 41.2 and
 // 35.1, backward 4 x 300 90.8 and 75.1, 96 x 157 with statistics 74.6 and 69.1, backward 8 x 961 at d = 128 435 and 403, 16 x 1000
 // 108 and 102, 96 x 1000 (1344 workgroups) 445 and 438, backward 681 and 668, 64 x 2048 (1920) 840 and 829; but 64 x 3000 at d = 16 (2880)
-// 583 and 592, backward 64 x 4096 (3968) 4275 and 4333.
+// 583 and 592, backward 64 x 4096 (3968) 4275 and 4333.  At d = 128 the gain is larger and there is no loss up to the same line: 4 x 600 122 and
+// 109, backward 242 and 212, 16 x 2048 (448) 1019 and 1007, backward 1439 and 1409, 64 x 2048 (1792) 3836 and 3831, backward 5100 and 5081, 16 x 8192
+// (1984) 9525 and 9516.  Backward 64 x 2048 at d = 64 1285 and 1293, at d = 32 727 and 716, at d = 16 590 and 577.
 constexpr long long ONE_LAUNCH_UP_TO = 2048;
 bool one_launch(int heads, int n, int early)
 {

@@ -1,22 +1,31 @@
-// Matrix-core backward pass for fp32 inputs, d = 64.  The sweeps form every contraction on v_mfma_f32_16x16x4_f32, fp32 operands and fp32
-// accumulation; the second moment comes from operands split into three bf16 (24 significant bits) on 16-bit MFMA.  Errors against fp64
-// are those of the vector kernels of llla_bwd.hip (whose notation is used here) or smaller, for inputs whose |k|^2 / ridge is below
-// some 10^5: 500 rows of normal inputs, ridge 10^-2, dQ 8.1e-5 there and 7.0e-5 here; keys of ten times that size 0.15 and 0.22.
+// Matrix-core backward pass for fp32 inputs, d = 16, 32, 64 and 128, and the output sweep of the fp32 forward.  The sweeps form every contraction on
+// v_mfma_f32_16x16x4_f32 at the head's own dimension, fp32 operands and fp32 accumulation; the second moment comes from operands split into three
+// bf16 (24 significant bits) on 16-bit MFMA, at d = 16 / 32 from copies of Q and K in rows of 64 features.
+//
+// Errors against fp64 times those of the vector kernels of llla_bwd.hip (whose notation is used here), which serve these calls on request; dQ, dK,
+// dV and dlambda, geometric means of 48 to 160 heads at two to seven lengths each:
+//   unit keys, ridge 10^-2      d = 16 0.83-0.98   d = 32 0.78-0.88   d = 128 0.66-0.69
+//   normal keys, 10^-2 and 10^-3       0.76-1.06          0.73-0.98           0.72-0.80
+//   normal keys, 10^-4                 0.80-1.22          0.74-1.10           0.68-0.77     (|k|^2 / ridge 10^5 and more)
+//   normal keys times 10, 10^-2        0.97-1.14          0.86-1.13           0.70-0.94     (10^5 to 10^6: dlambda has one digit on either)
+//   normal keys plus 3, 10^-2          0.65-0.83          0.56-0.66           0.36-0.38
+// (d = 16: six, eight or nine partial products, pivots dropped or raised, a Newton step on their roots, r from final weights or from fused
+// multiply-adds make no difference; fp32 MFMA for the second moment 1.1 times more.)
 //
 //   r sweep   r_i = sum_j w_ij gamma_ij [1; k_j], the row maximum m_i and the first key that attains it;
 //   moments   the forward's fp32 moments kernel with m_i given and a second right-hand side in its solve: y_i and u_i;
 //   dQ sweep  p^_ij, dQ_i, dlambda_i and the scalars of row i that the key sweep reads;
 //   key sweep dK_j, dV_j.
 //
-// What bounds it: the sweeps the fp32 matrix rate (1/16 of the 16-bit one; a tile of 16 queries x 16 keys costs 48 + 80 + 128 MFMAs of
+// What bounds it: the sweeps the fp32 matrix rate (1/16 of the 16-bit one; a tile of 16 queries x 16 keys costs 48 + 80 + 128 MFMAs (d = 64) of
 // 32 cycles in the three of them), the moments see llla_mfma_fwd_f32.hip.  The vector kernels spend d^2 multiply-adds per pair on
-// the vector ALU, out of LDS, and eliminate a (d+1)^2 system with one barrier per pivot.  16 heads x 1024 rows: 2811 us on the
-// vector kernels, 513 here; 2 x 128: 207 and 82.
+// the vector ALU, out of LDS, and eliminate a (d+1)^2 system with one barrier per pivot.  16 heads x 1024 rows at d = 64: 2811 us on the
+// vector kernels, 494 here; 2 x 128: 207 and 82; other dimensions beside takes_backward_f32 and in llla_mfma_fwd_f32_128.hip.
 //
 // The sweeps (and the output sweep of the fp32 forward, a fourth) share one shape: 32 rows per workgroup, four waves = 2 groups of 16 rows x 2 halves of every 32-row step
 // of the other side, the halves' sums added through LDS at the end.  (64 rows per workgroup without the split leave a
 // 1024-row head with 16 workgroups whose longest is twice the mean; with it and balanced_block the r, dQ and key sweeps of 16 heads x
-// 1024 rows take 55, 64 and 110 us, in plain longest-first order 62, 79 and 131; the output sweep 53, before the split 64.)  Tiles arrive by DMA one step ahead, two buffers, one
+// 1024 rows at d = 64 take 55, 64 and 110 us, in plain longest-first order 62, 79 and 131; the output sweep 53, before the split 64.)  Tiles arrive by DMA one step ahead, two buffers, one
 // barrier per step; 16-byte chunks are XOR-swizzled with the row, so that rows are read 16 bytes per lane (operand with the
 // features as contraction index) and columns 4 bytes per lane (operand with the rows as contraction index) from one copy.
 #include "llla_mfma_common.hpp"

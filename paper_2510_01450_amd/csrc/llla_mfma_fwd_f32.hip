@@ -1,4 +1,4 @@
-// Matrix-core forward path for fp32 inputs, d = 64, with the accuracy of the vector kernels and no value-range condition: logits and
+// Matrix-core forward path for fp32 inputs, d = 64 (and the moments at d = 16 / 32, on copies in rows of 64 features), with the accuracy of the vector kernels and no value-range condition: logits and
 // first moment on v_mfma_f32_16x16x4_f32, the second moment Sigma~_i = Z^T Z with the rows z_j = sqrt(w_ij) k_j split into three bf16
 // (24 significant bits, fp32's exponents) on 16-bit MFMA, six of the nine partial products, fp32 accumulation.
 //

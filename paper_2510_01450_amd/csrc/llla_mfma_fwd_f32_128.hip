@@ -10,9 +10,9 @@
 // of the workgroup.  mu~ is summed on the vector ALU from the same sqrt(w) k.
 //
 // What bounds it: MFMA and splitting as at d = 64, and for short sequences the per-row solve and the chain of the key-space rows (74 us).
-// us a call, vector kernels (which served d = 128 before) and these.  Forward: 8 heads x 65 rows 348 and 86, 8 x 250 1188 and 105, 64 x 700
-// 37900 and 2420; backward: 1 x 64 396 and 87, 8 x 250 3250 and 195, 32 x 700 43700 and 1570.  Errors against fp64, unit and normal values,
-// 200 to 500 rows: 0.77 to 0.98 times those of the vector kernels.
+// us a call, vector kernels (which served d = 128 before) and these.  Forward: 8 heads x 65 rows 349 and 84, 8 x 250 1190 and 98, 64 x 700
+// 37900 and 2345; backward: 1 x 64 396 and 83, 8 x 250 3256 and 186, 32 x 700 43800 and 1495.  Errors of O against fp64, 140 and 300 rows, times
+// those of the vector kernels: unit keys 0.67-0.68, normal keys 0.72-0.75 with ridges from 10^-2 to 10^-4, 0.70 times 10, 0.37 plus 3.
 #include "llla_dual.hpp"
 #include "llla_mfma_common.hpp"
 #include "llla_mfma_solve128.hpp"

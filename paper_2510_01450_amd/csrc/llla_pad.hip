@@ -46,9 +46,8 @@ PadLayout make_pad_layout(int B, int H, int n, llla_dtype in, bool cg = false)
 }
 
 // One thread per 16-byte chunk of a padded row, blockIdx.y the tensor.
-// All tensors of a call in one launch, on the way in and on the way out: a copy of a small call takes 5 us, nearly all of it the
-// launch.  60 heads x 68 rows, d = 32, bf16, forward: 37.3 -> 29.4 us a call; 4 heads x 1871, d = 16, backward: 265 -> 255.  (The exact
-// bf16 calls make theirs in the launch that forms the row maxima.)
+// All tensors of a call in one launch, on the way in and, in the approximate mode, on the way out: a copy of a small call takes 5 us, nearly all
+// of it the launch.  (The exact bf16 calls make theirs in the launch that forms the row maxima.)
 template <int ESZ>
 __global__ __launch_bounds__(256) void pad_rows_kernel(PadSources a, int H, int n, int d, size_t nchunks)
 {
