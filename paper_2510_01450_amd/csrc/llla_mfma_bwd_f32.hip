@@ -5,10 +5,12 @@
 // Errors against fp64 times those of the vector kernels of llla_bwd.hip (whose notation is used here), which serve these calls on request; dQ, dK,
 // dV and dlambda, geometric means of 48 to 160 heads at two to seven lengths each:
 //   unit keys, ridge 10^-2      d = 16 0.83-0.98   d = 32 0.78-0.88   d = 128 0.66-0.69
-//   normal keys, 10^-2 and 10^-3       0.76-1.06          0.73-0.98           0.72-0.80
-//   normal keys, 10^-4                 0.80-1.22          0.74-1.10           0.68-0.77     (|k|^2 / ridge 10^5 and more)
-//   normal keys times 10, 10^-2        0.97-1.14          0.86-1.13           0.70-0.94     (10^5 to 10^6: dlambda has one digit on either)
-//   normal keys plus 3, 10^-2          0.65-0.83          0.56-0.66           0.36-0.38
+//   normal keys, 10^-2 and 10^-3       0.76-1.06          0.73-0.98           0.71-0.78
+//   normal keys, 10^-4                 0.80-1.22          0.74-1.10           0.65-0.78     (|k|^2 / ridge 10^5 and more)
+//   normal keys times 10, 10^-2        0.97-1.14          0.86-1.13           0.70-0.91     (10^5 to 10^6: dlambda has one digit on either)
+//   normal keys plus 3, 10^-2          0.65-0.83          0.56-0.66           0.35-0.38
+// Large logits, dK at d = 128 (normal keys, ridge 0.05, 40 to 300 rows, logits of standard deviation 8 / 16 / 32 / 64): 0.66-0.96 / 1.0-1.2 / 1.3-1.4 / 1.6-1.9;
+// where moments and sweeps sum the logits in different orders 1.8-3.3 / 3.1-4.1 / 4.5-5.0 / 5.9-7.4.
 // (d = 16: six, eight or nine partial products, pivots dropped or raised, a Newton step on their roots, r from final weights or from fused
 // multiply-adds make no difference; fp32 MFMA for the second moment 1.1 times more.)
 //
@@ -87,11 +89,16 @@ static_assert(covered(1) && covered(65535) && block_grid(65535).z == 1 && covere
               "row blocks of the longest forward call: 64 x 65535 rows");
 
 // C += T R^T over the features: T = 16 rows of a tile (tile row nn of the lane), R = a row per lane in registers; contraction
-// slot (s, g) stands for feature DD/4 g + s on both sides
+// slot (s, g) stands for feature DD/4 g + s on both sides, at d = 128 for 64 (s / 16) + 16 g + s % 16: chunk v of lane group g.
+// Logits are to have the bits that the moments kernels give them (see weight() below), so at d = 128 they are the sum of two
+// halves of the features, as there.
+template <int DD>
+__device__ inline int chunk_of(int g, int v) { return DD == 128 ? 16 * (v >> 2) + 4 * g + (v & 3) : DD / 16 * g + v; }
+
 template <int DD>
 __device__ inline f32x4 row_chunk(const float *trow, int g, int v, int nn)
 {
-    return *reinterpret_cast<const f32x4 *>(trow + 4 * ((DD / 16 * g + v) ^ swz<DD>(nn)));
+    return *reinterpret_cast<const f32x4 *>(trow + 4 * (chunk_of<DD>(g, v) ^ swz<DD>(nn)));
 }
 
 // 2^x as the square of its root: the moments kernel works with the roots of the weights, and the sweeps use the same weights to
@@ -107,7 +114,7 @@ __device__ inline void load_row(const float *row, int g, float (&x)[DD / 4])
 {
 #pragma unroll
     for (int v = 0; v < DD / 16; ++v) {
-        const f32x4 a = *reinterpret_cast<const f32x4 *>(row + DD / 4 * g + 4 * v);
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(row + 4 * chunk_of<DD>(g, v));
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[4 * v + e] = a[e];
     }
@@ -198,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
         const int jb = c * RT + 16 * ks;
         if (jb > wlast) continue;                            // no query of this wave sees these keys
         const float *kt = &tiles[c & 1][0][16 * ks * DD], *vt = &tiles[c & 1][1][16 * ks * DD];
-        f32x4 z = {0.f, 0.f, 0.f, 0.f}, gm = z, at = {y0, y0, y0, y0}, bt = {u0, u0, u0, u0};
+        f32x4 z = {0.f, 0.f, 0.f, 0.f}, zb = z, gm = z, at = {y0, y0, y0, y0}, bt = {u0, u0, u0, u0};
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const f32x4 kv = row_chunk<DD>(kt + nn * DD, g, v, nn);
@@ -206,7 +213,8 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
             if constexpr (MODE < 2) vv = row_chunk<DD>(vt + nn * DD, g, v, nn);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                z = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qr[4 * v + e], z, 0, 0, 0);
+                f32x4 &zv = DD == 128 && v >= 4 ? zb : z;
+                zv = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qr[4 * v + e], zv, 0, 0, 0);
                 if constexpr (MODE < 2) gm = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], gr[4 * v + e], gm, 0, 0, 0);
                 if constexpr (MODE >= 1) at = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], yr[4 * v + e], at, 0, 0, 0);
                 if constexpr (MODE == 1) {
@@ -214,6 +222,7 @@ __global__ __launch_bounds__(256, 2) void bwd_rows_f32_kernel(
                 }
             }
         }
+        if constexpr (DD == 128) z += zb;
         float zs[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) zs[r] = z[r] * cscale;
@@ -412,19 +421,21 @@ __global__ __launch_bounds__(256, DD <= 64 ? 2 : 1) void bwd_keys_f32_kernel(
         const float *qt = &tiles[c & 1][0][16 * qs * DD], *gt = &tiles[c & 1][1][16 * qs * DD];
         const float *yt = &tiles[c & 1][2][16 * qs * DD], *ut = &tiles[c & 1][3][16 * qs * DD];
         const float *st = &scal[c & 1][16 * qs * 8];
-        f32x4 z = {0.f, 0.f, 0.f, 0.f}, gm = z, at = z, bt = z;
+        f32x4 z = {0.f, 0.f, 0.f, 0.f}, zb = z, gm = z, at = z, bt = z;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const f32x4 qv = row_chunk<DD>(qt + nn * DD, g, v, nn), gv = row_chunk<DD>(gt + nn * DD, g, v, nn);
             const f32x4 yv = row_chunk<DD>(yt + nn * DD, g, v, nn), uv = row_chunk<DD>(ut + nn * DD, g, v, nn);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                z = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[e], kr[4 * v + e], z, 0, 0, 0);
+                f32x4 &zv = DD == 128 && v >= 4 ? zb : z;
+                zv = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[e], kr[4 * v + e], zv, 0, 0, 0);
                 gm = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[e], vr[4 * v + e], gm, 0, 0, 0);
                 at = __builtin_amdgcn_mfma_f32_16x16x4f32(yv[e], kr[4 * v + e], at, 0, 0, 0);
                 bt = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[e], kr[4 * v + e], bt, 0, 0, 0);
             }
         }
+        if constexpr (DD == 128) z += zb;
         float cs[4], ce[4], cp[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

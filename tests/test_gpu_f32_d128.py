@@ -121,3 +121,18 @@ def test_backward_edges(n):
     Q, K, V = workloads.make_inputs(w)
     G = _upstream(w, 80 + n)
     _compare(w, _backward(w, Q, K, V, G, w.lam), ob.backward(Q, K, V, G, w.lam, w.scale), "n=%d" % n, _floor(V, G, w.lam))
+
+
+def test_moments_and_sweeps_see_the_same_logits():
+    """Logits of some eight standard deviations of 1: a weight of the moments kernel and of a sweep that differ by the rounding of two orders of
+    summation leave e_ij = w_ij (gamma_ij - b_ij) of that size behind, which y1 multiplies by |q| / ridge.  Geometric mean of the heads' errors of
+    dK against the vector kernels', whose sweeps share one order: seen WITH, in two orders WITHOUT."""
+    w = _backward_case(1, 16, 70, D, "f32", values="normal", index=699)
+    Q, K, V = workloads.make_inputs(w)
+    Q = 8 * Q
+    G = _upstream(w, 99)
+    ref = np.asarray(ob.backward(Q, K, V, G, w.lam, w.scale)[1])
+    err = [np.linalg.norm((_backward(w, Q, K, V, G, w.lam, path)[1] - ref).reshape(16, -1), axis=1) for path in ("auto", "valu")]
+    ratio = float(np.exp(np.mean(np.log(err[0] / err[1]))))
+    print("ratio %.3f" % ratio)
+    assert ratio < 1.25, ratio
