@@ -11,7 +11,7 @@
 //
 // What bounds it: MFMA and splitting as at d = 64, and for short sequences the per-row solve and the chain of the key-space rows (74 us).
 // us a call, vector kernels (which served d = 128 before) and these.  Forward: 8 heads x 65 rows 349 and 84, 8 x 250 1190 and 98, 64 x 700
-// 37900 and 2345; backward: 1 x 64 396 and 83, 8 x 250 3256 and 186, 32 x 700 43800 and 1495.  Errors of O against fp64, 140 and 300 rows, times
+// 37900 and 2345; backward: 1 x 64 396 and 83, 8 x 250 3256 and 189, 32 x 700 43800 and 1510.  Errors of O against fp64, 140 and 300 rows, times
 // those of the vector kernels: unit keys 0.67-0.68, normal keys 0.72-0.75 with ridges from 10^-2 to 10^-4, 0.70 times 10, 0.37 plus 3.
 #include "llla_dual.hpp"
 #include "llla_mfma_common.hpp"
