@@ -19,7 +19,7 @@
 // fp32 caches at d = 64 do likewise (compute_roots): 26 tiles of 16x16x4 per four keys were 832 matrix-core cycles for 2 KB of cache, 6 TB/s
 // at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 296.
 //
-// What bounds it: HBM at d = 16 / 32; the loads' latency with one wave per SIMD at d = 64 in fp32 (4.5 TB/s at 256 heads x 8192); at d = 128
+// What bounds it: HBM at d = 16 / 32; matrix and vector work of two waves per SIMD at d = 64 in fp32 (4.9 TB/s at 256 heads x 8192); at d = 128
 // 100 tiles of 16x16x4 per four keys, 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
 // wave W owns row blocks W and 7 - W, 25 tiles whatever W; every wave loads the whole rows (the first-level cache serves three
 // of the four) and forms the weights for itself, so there is no exchange at all.
@@ -31,14 +31,9 @@ namespace {
 using namespace mfma;
 
 constexpr int NT = DEC_NT;
+constexpr int ROOT_STAGE_B = 16384;     // by roots: a wave's LDS stage, 32 keys and 32 values of 64 floats
 constexpr float VALUE_SCALE = 0x1p64f, VALUE_SMALL = 0x1p-16f;      // see compute_roots
 constexpr float REF_SLACK = 8.f;        // the reference exponent moves when a logit exceeds it by more than 2^8 (weights stay <= 256)
-
-// fp32 caches at d = 64: sqrt(w) k and sqrt(w) v in three bf16 on 16-bit MFMA, one workgroup per compute unit (see compute_roots).  Two
-// workgroups on fp32 MFMA overlap one's merge and solve with the other's pass, which wins where there are many heads of few keys
-// (us, fp32 MFMA / roots: 256 heads x 100 17.3 / 16.9, x 512 40.3 / 26.9, x 1000 56.9 / 39.7; 512 x 128 26.7 / 33.5, x 512 51.5 / 53.0, x 960
-// 80.8 / 77.7; 384 x 300 38 / 50, 320 x 777 75 / 81; 768 x 900 143 / 115; 1024 x 512 97 / 105, x 1000 161 / 156, x 2048 297 / 266).
-inline bool roots_pay(int bh, int L) { return bh <= 256 || L >= 960; }
 
 template <int D>
 struct F32Shape : DecShape<D> {
@@ -125,8 +120,9 @@ struct F32Args {
 
 // The stream of one wave and what becomes of its moments.  W: the wave's share of the tiles (TEAM), else 0.
 // FUSED: one workgroup per head; it solves and writes the output itself.
+// stages (ROOTS): the LDS stages of the four waves and, behind them, a kilobyte per wave for the query; the merge reuses them.
 template <int D, typename TI, bool FUSED, bool ROOTS, int W, class Lds>
-__device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece &pc, Lds &lds, int wave, int lane)
+__device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece &pc, Lds &lds, unsigned char *stages, int wave, int lane)
 {
     using S = F32Shape<D>;
     constexpr bool SPLIT = sizeof(TI) == 2 && D <= 32;    // w k in three bf16 on 16-bit MFMA, eight chunks at a time
@@ -145,7 +141,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     const unsigned koff = (unsigned)(g * (int)krow + NB * nn * (int)sizeof(TI)), voff = (unsigned)(g * (int)vrow + NB * nn * (int)sizeof(TI));
 
     float q[NB];
-    {
+    if constexpr (!ROOTS) {
         const TI *qp = static_cast<const TI *>(a.out.q) + (size_t)bh * D + NB * nn;
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -285,70 +281,124 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     // start from zero and are then added to the tile: one rounding of the sum per step, 0.29 ulp rms, instead of six times the 0.58 of an
     // MFMA.  (Chained onto the sum, errors against fp64 grew with the keys per wave: 32 heads x 32768 unit keys 8.0e-7, 3.5e-7
     // now, 4.9e-7 on fp32 MFMA; 32 x 8192 3.5e-7, 2.7e-7, 3.2e-7.  64 heads x 1024 to 8192 61.3 -> 61.8 us a call, 256 x 8192 220 -> 241.)
-    // One wave per SIMD: with 256 registers 340 are spilled.  One set of registers for the rows: the next step's keys are requested as soon
-    // as these are converted, its values at the end.  us on fp32 MFMA / here: 64 heads x 1024 to 8192 78 / 62, 256 x 8192 284 / 241.  (With the
-    // products chained: two sets of registers 66 instead of 64; conversions and products pinned to alternate 66, with two sets 69:
-    // part of the registers are then accumulation registers, read back one by one.)
+    // Two waves per SIMD.  The rows come by DMA into LDS, and a conversion reads the two feature blocks it needs; kept in registers, with sums put off
+    // by the compiler until after the next branch (their terms kept until then), a wave took 430 registers, was alone on its SIMD and
+    // waited for its values.  249 now; the conversion of the next block is pinned to alternate with the products of this one.  us, one wave with
+    // rows in registers / one with two LDS stages / two waves: 256 heads x 8192 234 / 215 / 212, 512 x 1000 79 / 74 / 66, 1024 x 2000 260 / 243 / 220.  On fp32 MFMA, also two waves: 512 x 100 25.7 (22.1 here), 512 x 512
+    // 51.4 (42.3), 384 x 300 38.0 (30.9), 320 x 777 74.0 (60.0), 1024 x 800 137 (108).
     // The third term of a value below 2^-110 would be subnormal, which matrix cores read as zero.  So a stream starts with its values taken
     // VALUE_SCALE times and goes over to the values as they are at the first one above VALUE_SMALL, ordinarily in its first step (64 heads
     // x 1024 to 8192 62.6 -> 63.3 us, 16 x 32768 77.9 -> 79.0; values of size 2^-110 3e-7, 2^-124 1.4e-3 off without it, rounding with it).
     bool small_values = true;
-    auto scale_values = [&](Frag (&f)[CH]) {
-        float top = 0.f;
+    // Rows of a step by DMA, a wave's own stages: lane l's 16 bytes of a chunk land at 16 l of its kilobyte, which is where the lane reads
+    // them, so there is no swizzle, no bank conflict and no barrier.  tile: 0 keys, 1 values.
+    unsigned char *const mine = stages + wave * ROOT_STAGE_B;
+    auto fetch_rows = [&](int tile, int s) {
+        const char *base = tile ? Vh : Kh;
+        const int64_t pitch = tile ? vrow : krow;
+        const unsigned dst = lds_offset(mine) + (unsigned)(tile * (ROOT_STAGE_B / 2));
+        const int j0 = r0 + s * STEP;
+        if (j0 + STEP <= L) {
+            const char *p = base + j0 * pitch;
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+            for (int c = 0; c < CH; ++c) {
+                dma16_base_nt_off(p, tile ? voff : koff, dst + 1024u * c);
+                p += 4 * pitch;
+                asm volatile("" : "+s"(p));               // (kept as sixteen hoisted bases: 44 spilled scalar registers)
+            }
+        } else {                                          // rows beyond the sequence: its last row (their weights are 0)
 #pragma unroll
-            for (int i = 0; i < NB; ++i) top = fmaxf(top, fabsf(frag_f32<TI, NB>(f[c], i)));
-        if (__builtin_amdgcn_ballot_w64(top > VALUE_SMALL) != 0) {
-            small_values = false;
-            unscale_values();
-        } else {
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int i = 0; i < NB; ++i) f[c].u[i] = __float_as_uint(VALUE_SCALE * frag_f32<TI, NB>(f[c], i));
+            for (int c = 0; c < CH; ++c) dma16_nt_off(base + min(j0 + 4 * c + g, L - 1) * pitch + 16 * nn, dst + 1024u * c);
         }
     };
-    auto compute_roots = [&](Step &st, int s) {
+    // features 2 half and 2 half + 1 of the lane's rows
+    auto read_half = [&](float (&f)[2][CH], int tile, int half) {
+        const float2v *p = reinterpret_cast<const float2v *>(mine + tile * (ROOT_STAGE_B / 2)) + 2 * lane + half;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const float2v v = p[128 * c];
+            f[0][c] = v[0];
+            f[1][c] = v[1];
+        }
+    };
+    auto compute_roots = [&](auto s) {               // (generic: instantiated only where it is called)
+        const bool more = s + 1 < nsteps;
+        dma_wait_but<CH>();                               // all but the values of this step
         float e[2], rt[2];
-        step_exponents(st.k, s, e);
+        {
+            Frag k[CH];
+            const uint4v *p = reinterpret_cast<const uint4v *>(mine) + lane;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const uint4v v = p[64 * c];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) k[c].u[t] = v[t];
+            }
+            step_exponents(k, s, e);
+        }
 #pragma unroll
         for (int grp = 0; grp < 2; ++grp) {
             rt[grp] = __builtin_amdgcn_exp2f(0.5f * e[grp]);          // exp2(-inf) = 0 masks the tail
             om = fmaf(rt[grp], rt[grp], om);
         }
+        asm volatile("" : "+v"(om), "+v"(mtrue));
         const float rc[8] = {row_bcast<0>(rt[0]), row_bcast<1>(rt[0]), row_bcast<2>(rt[0]), row_bcast<3>(rt[0]),
                              row_bcast<0>(rt[1]), row_bcast<1>(rt[1]), row_bcast<2>(rt[1]), row_bcast<3>(rt[1])};
         struct Split3 { bf16x8 h, m, l; };
-        auto scaled = [&](const Frag (&f)[CH], int I, float &sum) {
+        auto scaled = [&](const float (&f)[CH], float &sum) {
             float x[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                x[c] = rc[c] * frag_f32<TI, NB>(f[c], I);
+                x[c] = rc[c] * f[c];
                 sum = fmaf(rc[c], x[c], sum);
             }
+            asm volatile("" : "+v"(sum));                 // (summed here: not put off, with the terms kept in registers)
             Split3 r;
             split3_bf16(x, r.h, r.m, r.l);
             return r;
         };
-        auto product = [](f32x4 &sum, const Split3 &a, const Split3 &b) {
-            f32x4 t = {0.f, 0.f, 0.f, 0.f};
-            t = mfma_bf16(a.l, b.h, t);
-            t = mfma_bf16(a.h, b.l, t);
-            t = mfma_bf16(a.m, b.m, t);
-            t = mfma_bf16(a.m, b.h, t);
-            t = mfma_bf16(a.h, b.m, t);
-            t = mfma_bf16(a.h, b.h, t);
-            sum += t;
+        // a vector instruction of the next conversion behind every product
+        auto alternate = [](auto n, auto each) {
+#pragma unroll
+            for (int i = 0; i < decltype(n)::value; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, decltype(each)::value, 0);
+            }
         };
-        if (small_values) scale_values(st.v);             // (a scalar branch)
-        Split3 z[NB];
+        // tiles z[0..N-1] x b from zero, added to the sums; the chains of the tiles alternate
+        auto products = [&](auto n, auto keys, auto jtag, const Split3 (&z)[NB], const Split3 &b) {
+            constexpr int N = decltype(n)::value, J = decltype(jtag)::value;
+            f32x4 t[N > 0 ? N : 1];
 #pragma unroll
-        for (int J = 0; J < NB; ++J) {
-            z[J] = scaled(st.k, J, mu[J]);
-            if (J == NB - 1) load_rows(st.k, Kh, krow, koff, s + 1);
+            for (int I = 0; I < N; ++I) t[I] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int I = 0; I < J; ++I) product(acc[upper_tile<NB>(I, J)], z[I], z[J]);
+            for (int I = 0; I < N; ++I) t[I] = mfma_bf16(z[I].l, b.h, t[I]);
+#pragma unroll
+            for (int I = 0; I < N; ++I) t[I] = mfma_bf16(z[I].h, b.l, t[I]);
+#pragma unroll
+            for (int I = 0; I < N; ++I) t[I] = mfma_bf16(z[I].m, b.m, t[I]);
+#pragma unroll
+            for (int I = 0; I < N; ++I) t[I] = mfma_bf16(z[I].m, b.h, t[I]);
+#pragma unroll
+            for (int I = 0; I < N; ++I) t[I] = mfma_bf16(z[I].h, b.m, t[I]);
+#pragma unroll
+            for (int I = 0; I < N; ++I) t[I] = mfma_bf16(z[I].h, b.h, t[I]);
+#pragma unroll
+            for (int I = 0; I < N; ++I) acc[decltype(keys)::value ? upper_tile<NB>(I, J) : S::NSIG + NB * I + J] += t[I];
+#pragma unroll
+            for (int I = 0; I < N; ++I) asm volatile("" : "+v"(acc[decltype(keys)::value ? upper_tile<NB>(I, J) : S::NSIG + NB * I + J]));
+        };
+        asm volatile("" ::: "memory");                    // the rows are read again, not kept
+        Split3 z[NB], v;
+        float raw[2][CH];
+        read_half(raw, 0, 0);
+        z[0] = scaled(raw[0], mu[0]);
+        auto key_block = [&](auto jtag) {
+            constexpr int J = decltype(jtag)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (J + 1 < NB) z[J + 1] = scaled(raw[(J + 1) & 1], mu[J + 1]);
+            else v = scaled(raw[0], yv[0]);
+            products(jtag, std::true_type{}, jtag, z, z[J]);
             // diagonal: h^T m and m^T h are each other's transposes, and the solve takes (T + T^T) / 2
             const bf16x8 h2 = twice_bf16(z[J].h);
             f32x4 t = {0.f, 0.f, 0.f, 0.f};
@@ -357,14 +407,62 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             t = mfma_bf16(h2, z[J].m, t);
             t = mfma_bf16(z[J].h, z[J].h, t);
             acc[upper_tile<NB>(J, J)] += t;
+            asm volatile("" : "+v"(acc[upper_tile<NB>(J, J)]));
+            alternate(std::integral_constant<int, 6 * J + 4>{}, std::integral_constant<int, J == 0 ? 8 : J == 1 ? 6 : J == 2 ? 5 : 4>{});
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        key_block(std::integral_constant<int, 0>{});
+        read_half(raw, 0, 1);
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // read before the transfer that overwrites them is requested
+            fetch_rows(0, s + 1);
         }
+        key_block(std::integral_constant<int, 1>{});
+        key_block(std::integral_constant<int, 2>{});
+        if (more) dma_wait_but<CH>();                     // all but the next step's keys
+        else dma_wait_but<0>();
+        if (small_values) {                               // (a scalar branch)
+            float top = 0.f;
 #pragma unroll
-        for (int J = 0; J < NB; ++J) {
-            const Split3 v = scaled(st.v, J, yv[J]);
-            if (J == NB - 1) load_rows(st.v, Vh, vrow, voff, s + 1);
+            for (int half = 0; half < 2; ++half) {
+                read_half(raw, 1, half);
 #pragma unroll
-            for (int I = 0; I < NB; ++I) product(acc[S::NSIG + NB * I + J], z[I], v);
+                for (int c = 0; c < CH; ++c) top = fmaxf(top, fmaxf(fabsf(raw[0][c]), fabsf(raw[1][c])));
+            }
+            if (__builtin_amdgcn_ballot_w64(top > VALUE_SMALL) != 0) {
+                small_values = false;
+                unscale_values();
+            }
         }
+        auto read_values = [&](int half) {
+            read_half(raw, 1, half);
+            if (half && more) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                fetch_rows(1, s + 1);
+            }
+            if (small_values) {
+#pragma unroll
+                for (int c = 0; c < CH; ++c) { raw[0][c] *= VALUE_SCALE; raw[1][c] *= VALUE_SCALE; }
+            }
+        };
+        asm volatile("" ::: "memory");
+        read_values(0);
+        key_block(std::integral_constant<int, 3>{});
+        auto value_block = [&](auto jtag) {
+            constexpr int J = decltype(jtag)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            Split3 next = v;
+            if constexpr (J + 1 < NB) next = scaled(raw[(J + 1) & 1], yv[J + 1]);
+            products(std::integral_constant<int, NB>{}, std::false_type{}, jtag, z, v);
+            v = next;
+            alternate(std::integral_constant<int, 6 * NB>{}, std::integral_constant<int, 4>{});
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        value_block(std::integral_constant<int, 0>{});
+        read_values(1);
+        value_block(std::integral_constant<int, 1>{});
+        value_block(std::integral_constant<int, 2>{});
+        value_block(std::integral_constant<int, 3>{});
     };
     auto compute_f32 = [&](const Step &st, int s) {
         const int j0 = r0 + s * STEP;
@@ -429,13 +527,22 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         else compute_f32(st, s);
     };
     if constexpr (ROOTS) {
+        static_assert(CH * 1024 == ROOT_STAGE_B / 2, "a transfer of one kilobyte per chunk");
+        // the query comes the same way, in front of the rows: a load of its own would be waited for with all transfers behind it
+        unsigned char *const qs = stages + 4 * ROOT_STAGE_B + 1024 * wave;
         if (nsteps > 0) {
-            Step st;
-            load(st, 0);
-#pragma unroll 1
-            for (int s = 0; s < nsteps; ++s) compute_roots(st, s);
-            if (small_values) unscale_values();
+            dma16(static_cast<const char *>(a.out.q) + ((size_t)bh * D + NB * nn) * sizeof(TI), qs);
+            fetch_rows(0, 0);
+            fetch_rows(1, 0);
+            dma_wait_but<2 * CH>();
+            const f32x4 v = reinterpret_cast<const f32x4 *>(qs)[lane];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) q[i] = v[i] * a.cscale;
         }
+#pragma unroll 1
+        for (int s = 0; s < nsteps; ++s) compute_roots(s);
+        if (nsteps > 0 && small_values) unscale_values();
+        __syncthreads();                                  // the stages of all waves are dead
     } else if (nsteps > 0) {
         Step sa, sb;
         load(sa, 0);
@@ -480,7 +587,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
 // Two waves per SIMD for the split form at d = 32: four leave 128 registers, 24 too few, and three are still slower (256 heads x 4096
 // keys: 53.9, 38.4 and 35.9 us with 1024, 768 and 512 workgroups; on fp32 MFMA 52.6; 512 x 16384: 254, 201, 191 and 303).
 template <int D, typename TI, bool FUSED, bool ROOTS>
-__global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : ROOTS || (D == 128 && FUSED) ? 1 : 2) void decode_f32_kernel(F32Args a)
+__global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : (D == 128 && FUSED) ? 1 : 2) void decode_f32_kernel(F32Args a)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     using S = F32Shape<D>;
@@ -489,14 +596,17 @@ __global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : 
         __shared__ __align__(16) unsigned char raw[FUSED ? sizeof(HeadLds<D, 1, 1>) : 16];
         HeadLds<D, 1, 1> &lds = *reinterpret_cast<HeadLds<D, 1, 1> *>(raw);
         for_pieces<FUSED>(a.split, [&](const DecPiece &pc) {
-            if (wave == 0) decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, wave, piece_lane());
-            else if (wave == 1) decode_f32_body<D, TI, FUSED, ROOTS, 1>(a, pc, lds, wave, piece_lane());
-            else if (wave == 2) decode_f32_body<D, TI, FUSED, ROOTS, 2>(a, pc, lds, wave, piece_lane());
-            else decode_f32_body<D, TI, FUSED, ROOTS, 3>(a, pc, lds, wave, piece_lane());
+            if (wave == 0) decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, nullptr, wave, piece_lane());
+            else if (wave == 1) decode_f32_body<D, TI, FUSED, ROOTS, 1>(a, pc, lds, nullptr, wave, piece_lane());
+            else if (wave == 2) decode_f32_body<D, TI, FUSED, ROOTS, 2>(a, pc, lds, nullptr, wave, piece_lane());
+            else decode_f32_body<D, TI, FUSED, ROOTS, 3>(a, pc, lds, nullptr, wave, piece_lane());
         });
     } else {
-        __shared__ __align__(16) HeadLds<D, S::NBUF, 4> lds;
-        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, wave, piece_lane()); });
+        using Lds = HeadLds<D, S::NBUF, 4>;
+        constexpr size_t STAGES_B = ROOTS ? 4 * (ROOT_STAGE_B + 1024) : 0;
+        __shared__ __align__(16) unsigned char raw[STAGES_B > sizeof(Lds) ? STAGES_B : sizeof(Lds)];
+        Lds &lds = *reinterpret_cast<Lds *>(raw);
+        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, raw, wave, piece_lane()); });
     }
 }
 
@@ -545,10 +655,14 @@ hipError_t f32_launch(const Problem &p)
     // a caller without the scratch that the records need gets one workgroup per head
     const size_t records = f32_records<D>(p.B, p.H, p.n);
     const bool scratch = p.ws != nullptr && (reinterpret_cast<uintptr_t>(p.ws) & 255u) == 0 && p.ws_bytes >= records * S::REC_F * sizeof(float);
-    // (by roots a compute unit holds one workgroup; the records' room is that of the other types)
-    constexpr int slots = ROOTS ? 256 : S::SLOTS;
-    const int ns = scratch ? f32_nsplit<D>(bh, p.n, ROOTS ? records * S::REC_F * sizeof(float) : MAX_RECORD_BYTES, slots) : 1;
-    a.split = choose_split(p, ns, scratch ? records : 0, slots, ROOTS ? 128 : 4 * S::STEP, S::KEYS_MIN, S::MAX_SPLIT);
+    // By roots the even cut counts one workgroup per compute unit, although two fit: on one each they run almost twice as fast, and half the records
+    // are left to merge; two from 4096 keys per workgroup on (us with 256 / 512 counted: 256 heads x 512 26 / 34, x 1024 38 / 45, x 8192 231 / 220;
+    // 64 x 4096 43.5 / 45.9, 16 x 32768 72 / 74).  The flat cut counts both, in units of 256 keys (128: 64 heads of 1024 to 8192 63.7 instead of
+    // 61.7, 32 of 3750 to 30 000 97.0 instead of 94.2, 256 of 256 to 2048 53.4 instead of 55.4).
+    const size_t room = ROOTS ? records * S::REC_F * sizeof(float) : MAX_RECORD_BYTES;
+    int ns = scratch ? f32_nsplit<D>(bh, p.n, room, ROOTS ? 256 : S::SLOTS) : 1;
+    if (ROOTS && scratch && p.n >= 4096 * ns && 2 * bh * ns <= S::SLOTS && 2 * ns <= S::MAX_SPLIT && (size_t)bh * 2 * ns <= records) ns *= 2;
+    a.split = choose_split(p, ns, scratch ? records : 0, S::SLOTS, ROOTS ? 256 : 4 * S::STEP, S::KEYS_MIN, S::MAX_SPLIT);
     a.out = HeadOut{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
     a.cscale = p.scale * LOG2E;
     a.parts = static_cast<float *>(p.ws);
@@ -577,9 +691,11 @@ template <int D>
 hipError_t f32_by_dtype(const Problem &p)
 {
     if constexpr (D == 64) {
-        if (p.in == LLLA_F32 && roots_pay(p.B * p.H, p.n)) return f32_launch<D, float, true>(p);
+        if (p.in == LLLA_F32) return f32_launch<D, float, true>(p);
+    } else {
+        if (p.in == LLLA_F32) return f32_launch<D, float, false>(p);
     }
-    return p.in == LLLA_F32 ? f32_launch<D, float, false>(p) : f32_launch<D, bf16_t, false>(p);
+    return f32_launch<D, bf16_t, false>(p);
 }
 
 }  // namespace

@@ -1,0 +1,35 @@
+"""fp32 caches at d = 64: rows staged in LDS by DMA, one step of 32 keys ahead.  Lengths that leave the four waves of a workgroup no step, one, two
+and several, whole last steps and partial ones; more heads than the GPU holds at once; the even cut at 4095 and 4096 keys, where a head's
+workgroups double.  Rows 2 d apart, everything beyond the sequence NaN."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_01450_amd as llla
+import workloads
+from parity import check
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("B,H,L", [(2, 2, 66), (2, 2, 96), (2, 2, 128), (2, 3, 129), (2, 2, 250), (3, 2, 256), (1, 2, 385), (70, 8, 70), (70, 8, 300),
+                                   (43, 3, 4095), (43, 3, 4096)])
+def test_steps_and_cuts(B, H, L):
+    d = 64
+    w = workloads.C5.with_shape(name="stages", B=B, H=H, n=L, d=d, dtype="f32", index=2800 + L, values="l2", tol=1e-4, scale=d ** -0.5)
+    q, Kc, Vc = workloads.make_inputs(w)
+    nb = min(B, 2)
+    ref = oracle.decode(q[:nb], Kc[:nb], Vc[:nb], w.lam, w.scale)
+    buf = torch.full((2, B, H, L + 3, 2 * d), float("nan"), device=DEV)
+    buf[0, :, :, :L, :d] = Kc.to(DEV)
+    buf[1, :, :, :L, d:] = Vc.to(DEV)
+    got = llla.llla_decode(q.to(DEV), buf[0, :, :, :L, :d], buf[1, :, :, :L, d:], w.lam, w.scale)
+    assert torch.isfinite(got).all()
+    # (the gate: 24-bit operands and fp32 sums leave some 2^-24 sqrt(L) of the moments, times a condition number of about 4, and more below 4 d keys)
+    check(got[:nb].cpu().numpy()[:, :, None], ref[:, :, None], np.array([L - 1]), d, 1e-5 if L >= 256 else 1e-4, "L=%d heads %d" % (L, B * H))
+    # the same keys as the first L of longer caches
+    lens = torch.full((B,), L, dtype=torch.int32, device=DEV)
+    again = llla.llla_decode(q.to(DEV), buf[0, ..., :d], buf[1, ..., d:], w.lam, w.scale, seqlens=lens)
+    check(again[:nb].cpu().numpy()[:, :, None], ref[:, :, None], np.array([L - 1]), d, 1e-5 if L >= 256 else 1e-4, "lengths, L=%d" % L)
