@@ -26,7 +26,7 @@ constexpr int D = S64::D, NT = DEC_NT;
 __host__ __device__ constexpr int tix(int I, int J) { return S64::tix(I, J); }
 
 constexpr int STEP = 32;                       // keys per MFMA step
-constexpr int NSTAGE = 2;                      // LDS stages per wave; NSTAGE-1 are in flight
+constexpr int NSTAGE = 2;                      // LDS stages per wave
 constexpr int TILE_H = STEP * D;               // halves of one natural [32 keys][64] tile (4 KB)
 constexpr int STAGE_H = 2 * TILE_H;            // K tile + V tile
 constexpr int DMA_PER_STAGE = 8;
@@ -152,7 +152,7 @@ __device__ __forceinline__ void decode_partial_body(unsigned char *smem, const D
     auto issue_dma = [&](int step) {
         // (LDS destinations as byte offsets: a generic pointer costs four scalar instructions per transfer to turn back)
         const unsigned dst = lds_offset(mystage) + 2u * (unsigned)((step % NSTAGE) * STAGE_H);
-        const int j0 = r0 + step_pos(step < nsteps ? step : 0) * STEP;
+        const int j0 = r0 + step_pos(step) * STEP;
         if (j0 + STEP <= L) {
             const bf16_t *kb = Kh + (int64_t)j0 * sk.seq, *vb = Vh + (int64_t)j0 * sv.seq;
 #pragma unroll
@@ -170,13 +170,18 @@ __device__ __forceinline__ void decode_partial_body(unsigned char *smem, const D
         }
     };
 
-    // NSTAGE-1 stages in flight; every step issues exactly one more stage (clamped past the end) so
-    // that "vmcnt <= 8 (NSTAGE-1)" always means "the oldest stage has landed"
-#pragma unroll
-    for (int st = 0; st < NSTAGE - 1; ++st) issue_dma(st);
+    // One stage in flight behind the one in use, and none past the last step: a wave with a few steps paid a stage's traffic for it and waited for it in
+    // front of the merge (us: 128 heads of 256 to 2048 keys 34.3 -> 32.7, 256 x 700 23.3 -> 22.6, 16 x 1024 18.3 -> 17.9, 64 x 32768 100.7 -> 99.7).
+    // (Four stages where a workgroup has a compute unit to itself: 16 x 4096 25.5 instead of 23.7, 256 x 700 26.3.)
+    static_assert(NSTAGE == 2, "the waits count one stage");
+    if (nsteps > 0) issue_dma(0);
     for (int s = 0; s < nsteps; ++s) {
-        issue_dma(s + NSTAGE - 1);
-        dma_wait_pending<DMA_PER_STAGE *(NSTAGE - 1)>();
+        if (s + 1 < nsteps) {
+            issue_dma(s + 1);
+            dma_wait_pending<DMA_PER_STAGE>();
+        } else {
+            dma_wait_pending<0>();
+        }
         const bf16_t *kt = mystage + (s % NSTAGE) * STAGE_H;
         const bf16_t *vt = kt + TILE_H;
         const int j0 = r0 + step_pos(s) * STEP;
@@ -279,7 +284,6 @@ __device__ __forceinline__ void decode_partial_body(unsigned char *smem, const D
             bcast_mfmas(wl);
         }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // drain the clamped tail DMAs before the wave ends
 
     om = rows_allsum(om);
     float mu[4], yv[4];
