@@ -232,7 +232,7 @@ struct HeadLds {
     float tiles[NBUF][DecShape<D>::NTILES * 256];
     float mu[NW][D], yv[NW][D];
     float mw[4], om[4];
-    float sc[D == 128 ? 16 * SC_PITCH + D + 4 : DecShape<D>::NB * 16 * SC_PITCH];
+    float sc[D == 128 ? 16 * SC_PITCH + D + 4 : 4];
 };
 
 // The ridge of attempt a at a solve: lambda + eta S~_ii.  The centred matrix carries the rounding of moments of the size of |k|^2: some
@@ -242,6 +242,26 @@ struct HeadLds {
 // feature; the last one dominates any.  All arithmetic before the first such pivot is that of lambda alone.
 constexpr int SOLVE_TRIES = 5;
 __device__ inline float noise_ridge(int attempt) { return attempt == 0 ? 0.f : __builtin_ldexpf(1.f, 6 * attempt - 28); }
+
+// What a lane needs of the head's query (features 16 P + 4 g + t; at d = 128 16 P + n), requested by the caller long before the solve: a trip to memory is a tenth of it.
+template <int D>
+struct QueryPart { static constexpr int PER = D == 128 ? 1 : 4; float v[D / 16][PER]; };
+template <int D, typename TI, bool PERM>
+__device__ __forceinline__ QueryPart<D> load_query(const HeadOut &out, int bh, int lane)
+{
+    constexpr int NB = D / 16;
+    const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
+    constexpr int PER = QueryPart<D>::PER;
+    QueryPart<D> q;
+#pragma unroll
+    for (int i = 0; i < PER * NB; ++i) {
+        const int P = i / PER, n = PER == 1 ? lane % 16 : 4 * (lane / 16) + i % PER;
+        const TI v = qp[PERM ? NB * n + P : 16 * P + n];
+        if constexpr (sizeof(TI) == 2) q.v[P][i % PER] = bf16_to_f32(v);
+        else q.v[P][i % PER] = v;
+    }
+    return q;
+}
 
 // Solve and output of one head whose merged moments lie in lds.tiles[0], lds.mu[0], lds.yv[0], lds.om[0].  Called by all four
 // waves after a barrier.
@@ -255,8 +275,13 @@ __device__ inline float noise_ridge(int attempt) { return attempt == 0 ? 0.f : _
 // of tiles would cost the barriers that this saves).  What bounds it is the serial chain of the diagonal tiles.  One wave with both
 // substitutions on the vector ALU: 64 heads of 1024 to 8192 fp32 keys, d = 64, 86.7 instead of 81.2 us; 256 heads x 4096 bf16
 // keys, d = 32, 53.7 instead of 51.5.
+// Of 15 500 cycles at d = 64 the diagonal tiles were 2300 each (on the way through LDS and back 500, elimination 1420, inverse 320), the products 4700,
+// loading and the query's trip to memory 1200.  Now tiles are symmetric as loaded and become rows by lane exchanges (230), products run on
+// 16-bit MFMA from operands in three bf16, and the query is on its way while the records are merged: us, 16 heads x 4096 bf16 keys 23.7 -> 23.4,
+// 16 x 512 (one workgroup per head) 17.4 -> 16.3, 512 x 700 30.4 -> 28.7; fp32 16 x 4096 29.8 -> 28.7; errors 0.6 to 1.0 times those before.
+// (The columns dealt over the four waves, tiles handed on through LDS with two barriers per step: 23.9, 17.2, 28.5, 29.2; d = 128 53.7 -> 56.3.)
 template <int D, typename TI, bool PERM, class Lds>
-__device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
+__device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, const QueryPart<D> &q, int bh, int wave, int lane)
 {
     using S = DecShape<D>;
     constexpr int NB = S::NB;
@@ -264,7 +289,6 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
     const int g = lane / 16, nn = lane % 16;
     if (wave >= NB) return;                               // (scalar branches: what follows contains MFMAs)
     const float oinv = 1.f / lds.om[0], yc = lds.yv[0][16 * wave + nn], floor = 0.5f * out.lambda;
-    const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
     float o = 0.f;
     for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
         asm volatile("" ::: "memory");                    // (the moments are read again: not kept in registers for a second attempt)
@@ -279,29 +303,39 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
             const f32x4 gt = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][(S::NSIG + NB * P + wave) * 256 + lane * 4]);
 #pragma unroll
             for (int J = P; J < NB; ++J) {
-                const f32x4 st = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][upper_tile<NB>(P, J) * 256 + lane * 4]);
+                const float *tile = &lds.tiles[0][upper_tile<NB>(P, J) * 256];
+                const f32x4 st = *reinterpret_cast<const f32x4 *>(tile + lane * 4);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     float v = fmaf(mr[t], mc[J], -st[t]);
-                    if (J == P) v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                    if (J == P) {                         // symmetrised: element [nn][4 g + t] beside [4 g + t][nn]
+                        const float other = fmaf(oinv * mc[J], lds.mu[0][16 * P + 4 * g + t], -tile[(16 * (nn >> 2) + 4 * g + t) * 4 + (nn & 3)]);
+                        v = 0.5f * (v + other);
+                        v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                    }
                     acc[upper_tile<NB>(P, J)][t] = v;
                 }
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 x[0][P][t] = fmaf(mr[t], yc, -gt[t]);
-                const TI qv = qp[PERM ? NB * (4 * g + t) + P : 16 * P + 4 * g + t];
-                float q;
-                if constexpr (sizeof(TI) == 2) q = bf16_to_f32(qv);
-                else q = qv;
-                x[1][P][t] = nn == 0 ? mr[t] - q : 0.f;
+                x[1][P][t] = nn == 0 ? mr[t] - q.v[P][t] : 0.f;
             }
         }
-        const float low = factorise_columns<NB, 2>(acc, lds.sc + wave * 16 * SC_PITCH, g, nn, floor, x);
+        // the column of G_c times a power of two, which takes it out of the way of three bf16 at both ends of the range (the third term of a value
+        // below 2^-110 is subnormal, which matrix cores read as zero; the first of one above 2^127.99 infinite)
+        float top = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4 * NB; ++i) top = fmaxf(top, fabsf(x[0][i / 4][i % 4]));
+        const int e = max(min(__builtin_amdgcn_frexp_expf(wave_max_dpp(top)), 120), -120);      // (0 for 0 and infinity)
+        const float scale = __builtin_ldexpf(1.f, -e);
+#pragma unroll
+        for (int I = 0; I < NB; ++I) x[0][I] *= scale;
+        const float low = factorise_columns<NB, 2>(acc, g, nn, floor, x);
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[0][i / 4][i % 4], row_bcast<0>(x[1][i / 4][i % 4]), s);
-        s = rows_allsum(s);
+        s = __builtin_ldexpf(rows_allsum(s), e);
         o = fmaf(oinv, yc, s);
         if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;      // (at the end: nothing but o outlives an attempt)
     }
@@ -316,7 +350,7 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, in
 // 49): one wave factorises and substitutes on the vector ALU, all waves form the output as y0 sum w v + G~^T y1, y0 = (1 - mu~ . y1) /
 // omega.
 template <int D, typename TI, bool PERM, class Lds>
-__device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
+__device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out, const QueryPart<D> &q, int bh, int wave, int lane)
 {
     using S = DecShape<D>;
     constexpr int NB = S::NB;
@@ -324,7 +358,6 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
     float *scratch = lds.sc, *ys = scratch + 16 * SC_PITCH;
     if (wave == 0) {                                      // scalar branch: the block contains MFMAs
         const float oinv = 1.f / lds.om[0], floor = 0.5f * out.lambda;
-        const TI *qp = static_cast<const TI *>(out.q) + (size_t)bh * D;
         for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
             int lane_e = lane;                            // an attempt keeps nothing for the next: neither the moments nor what follows
             asm volatile("" : "+v"(lane_e) :: "memory");  // from the lane index (registers for both cost 0.5 us)
@@ -339,25 +372,26 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
                 const f32x4 mr = oinv * *reinterpret_cast<const f32x4 *>(&lds.mu[0][16 * P + 4 * g]);
 #pragma unroll
                 for (int J = P; J < NB; ++J) {
-                    const f32x4 st = *reinterpret_cast<const f32x4 *>(&lds.tiles[0][upper_tile<NB>(P, J) * 256 + lane_e * 4]);
+                    const float *tile = &lds.tiles[0][upper_tile<NB>(P, J) * 256];
+                    const f32x4 st = *reinterpret_cast<const f32x4 *>(tile + lane_e * 4);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         float v = fmaf(mr[t], mc[J], -st[t]);
-                        if (J == P) v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                        if (J == P) {                     // symmetrised, as above
+                            const float other = fmaf(oinv * mc[J], lds.mu[0][16 * P + 4 * g + t], -tile[(16 * (nn >> 2) + 4 * g + t) * 4 + (nn & 3)]);
+                            v = 0.5f * (v + other);
+                            v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                        }
                         acc[upper_tile<NB>(P, J)][t] = v;
                     }
                 }
             }
             float low = INFINITY;
-            factorise_one<NB, true, false, false>(acc, scratch, g, nn, floor, &low);
+            factorise_one<NB, true, false, false, true>(acc, scratch, g, nn, floor, &low);
             float tv[1][NB];                                  // -q_c, U^{-T} q_c, its negative
 #pragma unroll
             for (int P = 0; P < NB; ++P) {
-                const TI v = qp[PERM ? NB * nn + P : 16 * P + nn];
-                float q;
-                if constexpr (sizeof(TI) == 2) q = bf16_to_f32(v);
-                else q = v;
-                tv[0][P] = fmaf(lds.mu[0][16 * P + nn], oinv, -q);
+                tv[0][P] = fmaf(lds.mu[0][16 * P + nn], oinv, -q.v[P][0]);
             }
             substitute_forward<NB, 1>(acc, tv, scratch, g, nn);
 #pragma unroll
@@ -401,10 +435,10 @@ __device__ __forceinline__ void solve_and_store_128(Lds &lds, const HeadOut &out
 }
 
 template <int D, typename TI, bool PERM, class Lds>
-__device__ __forceinline__ void solve_head(Lds &lds, const HeadOut &out, int bh, int wave, int lane)
+__device__ __forceinline__ void solve_head(Lds &lds, const HeadOut &out, const QueryPart<D> &q, int bh, int wave, int lane)
 {
-    if constexpr (D == 128) solve_and_store_128<D, TI, PERM>(lds, out, bh, wave, lane);
-    else solve_and_store<D, TI, PERM>(lds, out, bh, wave, lane);
+    if constexpr (D == 128) solve_and_store_128<D, TI, PERM>(lds, out, q, bh, wave, lane);
+    else solve_and_store<D, TI, PERM>(lds, out, q, bh, wave, lane);
 }
 
 // The four waves of a workgroup, each with moments of its own share of the keys, become one set of moments: in the workgroup's
@@ -456,12 +490,14 @@ __device__ __forceinline__ void finish_workgroup(Lds &lds, f32x4 (&acc)[DecShape
         if constexpr (FUSED) src[0] = v;
         else R[64 + tid] = v;
     }
+    QueryPart<D> q;
+    if constexpr (FUSED) q = load_query<D, TI, PERM>(out, bh, lane);
     const float oall = (lds.om[0] + lds.om[1]) + (lds.om[2] + lds.om[3]);
     if constexpr (FUSED) {
         __syncthreads();
         if (tid == 0) lds.om[0] = oall;
         __syncthreads();
-        solve_head<D, TI, PERM>(lds, out, bh, wave, lane);
+        solve_head<D, TI, PERM>(lds, out, q, bh, wave, lane);
     } else if (tid == 0) {
         R[0] = mall;
         R[1] = oall;
@@ -496,6 +532,7 @@ __global__ __launch_bounds__(DEC_NT, D == 128 ? 1 : 2) void decode_merge_kernel(
     }
     HeadLds<D, 1, 1> &lds = *reinterpret_cast<HeadLds<D, 1, 1> *>(raw);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, bh = blockIdx.x;
+    const QueryPart<D> q = load_query<D, TI, PERM>(out, bh, lane);
     const DecRecords rec = dec_records(split, bh);
     const int np = rec.count;
     const float *P0 = parts + (size_t)rec.first * S::REC_F;
@@ -554,7 +591,7 @@ __global__ __launch_bounds__(DEC_NT, D == 128 ? 1 : 2) void decode_merge_kernel(
     if (tid < 2 * D) (tid < D ? lds.mu[0] : lds.yv[0])[tid & (D - 1)] = hv;
     if (tid == 0) lds.om[0] = om;
     __syncthreads();
-    solve_head<D, TI, PERM>(lds, out, bh, wave, lane);
+    solve_head<D, TI, PERM>(lds, out, q, bh, wave, lane);
 }
 
 }  // namespace mfma

@@ -423,6 +423,36 @@ __device__ inline void dma_wait_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"
 template <int NB>
 __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I * (I - 1) / 2 + (J - I); }
 
+// A symmetric tile from the accumulator layout to one row per lane: a[c] = X[n][c] in lane (g, n), four copies.  Column n is what the four lanes
+// (g, n) hold between them, so the four 16-lane rows exchange their registers (inline assembly and its s_nop: see rows_transpose4); through
+// LDS, a write and a read in a chain, it took three times as long.
+__device__ __forceinline__ void symmetric_rows(const f32x4 &x, float (&a)[16])
+{
+    float e0 = x[0], e1 = x[1], e2 = x[2], e3 = x[3], f0 = e0, f1 = e1, f2 = e2, f3 = e3;
+    asm volatile("s_nop 1\n\t"
+                 "v_permlane16_swap_b32 %0, %4\n\t"
+                 "v_permlane16_swap_b32 %1, %5\n\t"
+                 "v_permlane16_swap_b32 %2, %6\n\t"
+                 "v_permlane16_swap_b32 %3, %7"
+                 : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3), "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3));      // rows 0 0 2 2 and 1 1 3 3
+    float g0 = e0, g1 = e1, g2 = e2, g3 = e3, h0 = f0, h1 = f1, h2 = f2, h3 = f3;
+    asm volatile("s_nop 1\n\t"
+                 "v_permlane32_swap_b32 %0, %8\n\t"
+                 "v_permlane32_swap_b32 %1, %9\n\t"
+                 "v_permlane32_swap_b32 %2, %10\n\t"
+                 "v_permlane32_swap_b32 %3, %11\n\t"
+                 "v_permlane32_swap_b32 %4, %12\n\t"
+                 "v_permlane32_swap_b32 %5, %13\n\t"
+                 "v_permlane32_swap_b32 %6, %14\n\t"
+                 "v_permlane32_swap_b32 %7, %15"
+                 : "+v"(e0), "+v"(e1), "+v"(e2), "+v"(e3), "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3),
+                   "+v"(h0), "+v"(h1), "+v"(h2), "+v"(h3));
+    a[0] = e0; a[1] = e1; a[2] = e2; a[3] = e3;
+    a[4] = f0; a[5] = f1; a[6] = f2; a[7] = f3;
+    a[8] = g0; a[9] = g1; a[10] = g2; a[11] = g3;
+    a[12] = h0; a[13] = h1; a[14] = h2; a[15] = h3;
+}
+
 // Blocked factorisation of ONE system per wave, all in registers / wave-private LDS scratch (the first half of solve_one;
 // solve_wave_q4 has its own for four systems at d = 64):
 //   in : acc[upper_tile(I,J)]  upper-triangular 16x16 tiles of T = -(Sigma~ + lambda I) (MFMA accumulator layout)
@@ -442,26 +472,31 @@ __host__ __device__ constexpr int upper_tile(int I, int J) { return I * NB - I *
 // 2048 1049 and 1012, 16 x 8192 9674 and 9613, 8 x 44 46.7 and 43.8, backward 8 x 961 402 and 386; fp32 64 x 700 2413 and 2357.  Decode,
 // one solve per compute unit, gains nothing (224 heads of up to 589 keys 54.7 and 55.6), nor do four systems per wave at d = 64 (64 x 4096 bf16
 // 2829 and 2916, 16 x 1024 fp32 346 and 352).
-template <int NB, bool LOW = false, bool DROP = false, bool SPLIT = true>
+// SYMMETRIC: the diagonal tiles come in symmetric to the last bit, and the factorisation takes one triangle of them (symmetric_rows); otherwise it takes
+// the mean of the two.
+template <int NB, bool LOW = false, bool DROP = false, bool SPLIT = true, bool SYMMETRIC = false>
 __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor, float *low = nullptr)
 {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
-        // diagonal tile -> one row per lane, symmetrised
-#pragma unroll
-        for (int t = 0; t < 4; ++t) scw[(4 * g + t) * SC_PITCH + nn] = acc[upper_tile<NB>(P, P)][t];
-        wave_sync();
         float a[16], nl[16], ndinv;
+        if constexpr (SYMMETRIC) {
+            symmetric_rows(-acc[upper_tile<NB>(P, P)], a);
+        } else {                                          // one row per lane, symmetrised
 #pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-            const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
+            for (int t = 0; t < 4; ++t) scw[(4 * g + t) * SC_PITCH + nn] = acc[upper_tile<NB>(P, P)][t];
+            wave_sync();
 #pragma unroll
-            for (int t = 0; t < 4; ++t) a[4 * c4 + t] = v[t];
+            for (int c4 = 0; c4 < 4; ++c4) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) a[4 * c4 + t] = v[t];
+            }
+#pragma unroll
+            for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
+            wave_sync();
         }
-#pragma unroll
-        for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
-        wave_sync();
         eliminate16<LOW, DROP>(a, nl, ndinv, nn, pivot_floor, low);
         // N_P replaces the consumed diagonal tile; U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
         const f32x4 ui = invert16_quarter(nl, ndinv, nn, g);
@@ -495,53 +530,38 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 // The same with further block columns (the decode tail's solve at d <= 64):
 //   in : x[v][P]               NX further block columns, negated right-hand sides -B in the same layout
 //   out: x = U^{-T} B; returns the smallest pivot before it was raised to the floor
-// The next diagonal tile is updated first and on its way through LDS while the other products issue.
+// Diagonal tiles come in symmetric (only their products are added to them here).
 template <int NB, int NX>
-__device__ __forceinline__ float factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor,
-                                                   f32x4 (&x)[NX][NB])
+__device__ __forceinline__ float factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2], int g, int nn, float pivot_floor, f32x4 (&x)[NX][NB])
 {
     float low = INFINITY;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    auto put_diagonal = [&](int P) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) scw[(4 * g + t) * SC_PITCH + nn] = acc[upper_tile<NB>(P, P)][t];
-        wave_sync();
-    };
-    put_diagonal(0);
 #pragma unroll
     for (int P = 0; P < NB; ++P) {
-        // diagonal tile -> one row per lane, symmetrised
         float a[16], nl[16], ndinv;
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-            const f32x4 v = *reinterpret_cast<const f32x4 *>(scw + nn * SC_PITCH + 4 * c4);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) a[4 * c4 + t] = v[t];
-        }
-#pragma unroll
-        for (int c = 0; c < 16; ++c) a[c] = -0.5f * (a[c] + scw[c * SC_PITCH + nn]);    // -T, symmetrised
-        wave_sync();
+        symmetric_rows(-acc[upper_tile<NB>(P, P)], a);
         eliminate16<true, false>(a, nl, ndinv, nn, pivot_floor, &low);
         // N_P replaces the consumed diagonal tile; U(P,J) = N_P^T T(P,J), and the trailing tiles take T(I,J) += U(P,I)^T U(P,J)
         const f32x4 ui = invert16_quarter(nl, ndinv, nn, g);
-        acc[upper_tile<NB>(P, P)] = ui;
-        if (P + 1 < NB) {
-            f32x4 &u = acc[upper_tile<NB>(P, P + 1)], &d = acc[upper_tile<NB>(P + 1, P + 1)];
-            u = tile_atb(zero, ui, u);
-            d = tile_atb(d, u, u);
-            put_diagonal(P + 1);
+        const u32x6 us = split_tile(ui);
+        u32x6 row[NB], xs[NX];
+#pragma unroll
+        for (int J = P + 1; J < NB; ++J) {
+            f32x4 &u = acc[upper_tile<NB>(P, J)];
+            u = split_atb(zero, us, split_tile(u));
+            row[J] = split_tile(u);
         }
 #pragma unroll
-        for (int J = P + 2; J < NB; ++J) acc[upper_tile<NB>(P, J)] = tile_atb(zero, ui, acc[upper_tile<NB>(P, J)]);
-#pragma unroll
-        for (int v = 0; v < NX; ++v) x[v][P] = tile_atb(zero, ui, x[v][P]);
+        for (int v = 0; v < NX; ++v) {
+            x[v][P] = split_atb(zero, us, split_tile(x[v][P]));
+            if (P + 1 < NB) xs[v] = split_tile(x[v][P]);
+        }
 #pragma unroll
         for (int I = P + 1; I < NB; ++I) {
 #pragma unroll
-            for (int J = I == P + 1 ? I + 1 : I; J < NB; ++J)
-                acc[upper_tile<NB>(I, J)] = tile_atb(acc[upper_tile<NB>(I, J)], acc[upper_tile<NB>(P, I)], acc[upper_tile<NB>(P, J)]);
+            for (int J = I; J < NB; ++J) acc[upper_tile<NB>(I, J)] += split_atb(zero, row[I], row[J]);
 #pragma unroll
-            for (int v = 0; v < NX; ++v) x[v][I] = tile_atb(x[v][I], acc[upper_tile<NB>(P, I)], x[v][P]);
+            for (int v = 0; v < NX; ++v) x[v][I] += split_atb(zero, row[I], xs[v]);
         }
         __builtin_amdgcn_sched_barrier(0);
     }

@@ -578,8 +578,9 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
             else { R[0] = mtrue; R[1] = f * om; }
         }
         if constexpr (FUSED) {
+            const QueryPart<D> query = load_query<D, TI, true>(a.out, bh, lane);
             __syncthreads();
-            solve_head<D, TI, true>(lds, a.out, bh, wave, lane);
+            solve_head<D, TI, true>(lds, a.out, query, bh, wave, lane);
         }
     }
 }

@@ -33,3 +33,17 @@ def test_steps_and_cuts(B, H, L):
     lens = torch.full((B,), L, dtype=torch.int32, device=DEV)
     again = llla.llla_decode(q.to(DEV), buf[0, ..., :d], buf[1, ..., d:], w.lam, w.scale, seqlens=lens)
     check(again[:nb].cpu().numpy()[:, :, None], ref[:, :, None], np.array([L - 1]), d, 1e-5 if L >= 256 else 1e-4, "lengths, L=%d" % L)
+
+
+@pytest.mark.parametrize("d", [16, 32])
+@pytest.mark.parametrize("L", [40, 700])
+def test_values_of_any_size(d, L):
+    """The output is linear in V, so values times a power of two give the same bits times it, as long as neither is subnormal: the solve takes the
+    value moments' columns in three bf16, whose third term would be lost from 2^-110 on and whose first overflows at 2^127.99."""
+    g = torch.Generator(device="cpu").manual_seed(3000 + L + d)
+    q, K, V = [torch.randn(s, generator=g).to(DEV) for s in ((2, 3, d), (2, 3, L, d), (2, 3, L, d))]
+    base = llla.llla_decode(q, K, V, 1e-2, d ** -0.5)
+    assert torch.isfinite(base).all()
+    for k in (-110, -100, -60, 60, 110):
+        got = llla.llla_decode(q, K, V * 2.0 ** k, 1e-2, d ** -0.5)
+        assert torch.equal(got.double(), base.double() * 2.0 ** k), k
