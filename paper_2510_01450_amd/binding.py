@@ -1,8 +1,11 @@
-"""ctypes binding of libllla.so -- argument marshalling only."""
+"""Binding of libllla.so -- argument marshalling only: ctypes, and for the ordinary forms of a forward or decode call a native extension
+(csrc/host/llla_host.cpp) that does the same with less of the host's time."""
 from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -104,6 +107,32 @@ def _load(measure: bool):
     return L
 
 
+_host = None
+_entries = {}
+
+
+def _load_host():
+    """The native host extension, rebuilt first if it is missing or not of the tree's sources and this torch."""
+    global _host
+    if _host is None:
+        from . import build as _build
+        if not _build.host_is_current():
+            _build.build_host()
+        loader = importlib.machinery.ExtensionFileLoader("llla_host", _build.LIB_HOST)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("llla_host", loader))
+        loader.exec_module(module)
+        _host = module
+    return _host
+
+
+def _entry_points(measure: bool):
+    """Addresses of the C ABI's functions that the host extension calls, of the library in use."""
+    L = _load(measure)
+    _entries[measure] = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.llla_forward_ex, L.llla_forward_workspace_bytes, L.llla_decode_path, L.llla_decode_workspace_bytes))
+    return _entries[measure]
+
+
 def lib():
     """The loaded C-ABI library (the production one unless use_measure_library(True) is in effect)."""
     return _load(_use_measure)
@@ -179,12 +208,14 @@ def _strides4(*tensors) -> list:
     return out
 
 
+def _current_stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream_ptr(stream) -> int:
     """The handle of ``stream``, or of the current device's current stream.  The handle is all that is needed: building a torch Stream object
     for it was a fifth of the host's time of a call (1 head x 128 rows, fp32, d = 16: 14.0 -> 11.3 us a call)."""
-    if stream is not None:
-        return int(stream.cuda_stream)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream) if stream is not None else _current_stream()
 
 
 def _workspace(nbytes: int, device, workspace):
@@ -214,6 +245,14 @@ def llla_forward(Q, K, V, lam, scale: float, causal: bool = True, out_dtype=None
     """O = LLA(Q, K, V) for [B, H, n, d] device tensors (f32 or bf16).  ``lam`` is a float or a device float32
     tensor [B, H, n] (one ridge per query row).  Returns O ([B, H, n, d]), or (O, rho, delta) with the per-row
     statistics of Eq. (lla) when ``return_stats`` is set."""
+    # the ordinary forms, natively (1 head x 128 rows at d = 16 in fp32 11.7 -> 8.1 us a call); NotImplemented: not one of them, nothing done
+    fn = _entries.get(_use_measure) or _entry_points(_use_measure)
+    r = (_host or _load_host()).forward(fn[0], fn[1], Q, K, V, lam, scale, causal, out_dtype, PATHS.get(path, -1), workspace, out, return_stats,
+                                        _current_stream if stream is None else int(stream.cuda_stream))
+    if r is not NotImplemented:
+        if type(r) is int:
+            raise LlaError(r, "llla_forward")
+        return r
     if not (Q.is_cuda and K.is_cuda and V.is_cuda):
         raise ValueError("llla_forward needs device tensors; this library has no CPU path")
     if not (Q.dtype == K.dtype == V.dtype) or Q.dtype not in _DTYPES:
@@ -334,6 +373,13 @@ def llla_backward(Q, K, V, dO, lam, scale: float, path: str = "auto", workspace=
 def llla_decode(q, Kc, Vc, lam: float, scale: float, seqlens=None, out_dtype=None, path: str = "auto",
                 workspace=None, out=None, stream=None):
     """One query per (batch, head) against [B, H, L_max, d] caches.  q: [B, H, d].  Returns [B, H, d]."""
+    fn = _entries.get(_use_measure) or _entry_points(_use_measure)
+    r = (_host or _load_host()).decode(fn[2], fn[3], q, Kc, Vc, lam, scale, seqlens, out_dtype, PATHS.get(path, -1), workspace, out,
+                                       _current_stream if stream is None else int(stream.cuda_stream))
+    if r is not NotImplemented:
+        if type(r) is int:
+            raise LlaError(r, "llla_decode")
+        return r
     if not (q.is_cuda and Kc.is_cuda and Vc.is_cuda):
         raise ValueError("llla_decode needs device tensors; this library has no CPU path")
     if not (q.dtype == Kc.dtype == Vc.dtype) or q.dtype not in _DTYPES:

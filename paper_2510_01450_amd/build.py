@@ -1,9 +1,10 @@
 """Builds the C-ABI library from csrc/*.hip with hipcc for gfx950, in-tree.
 
-Two artefacts from the same sources:
+Two artefacts from the same sources, and one of the host's:
   libllla.so          the production library (include/llla.h);
   libllla_measure.so  the same sources compiled with -DLLLA_MEASURE (kernel launchers record HIP events) plus
                       csrc/measure/*.hip (include/llla_measure.h) -- loaded by the benchmark only.
+  llla_host.so        csrc/host/llla_host.cpp, the host side of a call as a Python extension (torch's headers, the C++ compiler).
 Each gets a stamp file holding a hash of the sources it was built from; the binding compares it before loading.
 """
 from __future__ import annotations
@@ -19,6 +20,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libllla.so")
 LIB_MEASURE = os.path.join(HERE, "libllla_measure.so")
+LIB_HOST = os.path.join(HERE, "llla_host.so")
+HOST_SOURCE = os.path.join(CSRC, "host", "llla_host.cpp")
+CXX = os.environ.get("CXX", "g++")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -88,8 +92,54 @@ def _build_one(lib: str, measure: bool, verbose: bool, extra) -> str:
     return lib
 
 
+def host_command(out: str) -> list:
+    """The compiler's command line for the host extension.  torch's libraries are linked by name only: the process has them loaded."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    return [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+            "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], HOST_SOURCE, "-o", out,
+            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
+def host_hash() -> str:
+    """Hash of what the host extension is compiled from and against."""
+    import sys
+    import torch
+    h = hashlib.sha256()
+    for f in (HOST_SOURCE, os.path.join(ROOT, "include", "llla.h")):
+        with open(f, "rb") as fh:
+            h.update(fh.read())
+    h.update(("%s %s" % (torch.__version__, sys.version)).encode())
+    return h.hexdigest()
+
+
+def host_is_current() -> bool:
+    try:
+        with open(stamp_path(LIB_HOST)) as fh:
+            return os.path.exists(LIB_HOST) and fh.read().strip() == host_hash()
+    except OSError:
+        return False
+
+
+def build_host(verbose: bool = False) -> str:
+    tmp = LIB_HOST + ".tmp.%d" % os.getpid()
+    cmd = host_command(tmp)
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, LIB_HOST)
+    with open(stamp_path(LIB_HOST), "w") as fh:
+        fh.write(host_hash() + "\n")
+    return LIB_HOST
+
+
 def build(verbose: bool = False, extra=(), measure: bool = True) -> str:
-    """Compile every HIP source into libllla.so (and libllla_measure.so).  Always recompiles."""
+    """Compile every HIP source into libllla.so (and libllla_measure.so), and the host extension.  Always recompiles."""
+    build_host(verbose)
     _build_one(LIB, False, verbose, extra)
     if measure:
         _build_one(LIB_MEASURE, True, verbose, extra)
