@@ -114,22 +114,39 @@ typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 // remainders x - h are v_dot2_f32_bf16 with (-1, 0) and (0, -1), exact like the subtractions they stand for: one instruction per value
 // instead of an unpacking and a subtraction.  (The two constants come in scalar registers: as a literal the compiler encodes (-1, 0)
 // as the inline constant -1.0, which this instruction reads as the fp32 bit pattern, i.e. (0, -1); seen with ROCm 7.2.)
+// The stages of the eight values are kept apart (the empty statements): a vector instruction that reads the result of v_dot2_f32_bf16 less than three
+// instructions later is held up, and the scheduler, left to itself, put the two next to each other.
+__device__ inline void tie8(float (&x)[8])
+{
+    asm("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
+}
 __device__ inline void split3_bf16(const float (&x)[8], bf16x8 &h, bf16x8 &m, bf16x8 &l)
 {
     unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
     asm("" : "+s"(lo), "+s"(hi));
     const bf16x2v first = __builtin_bit_cast(bf16x2v, lo), second = __builtin_bit_cast(bf16x2v, hi);
+    float r[8];
+    auto terms = [&](const float (&v)[8], bf16x8 &o) {
 #pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-        const bf16x2v a = __builtin_convertvector(float2v{x[t], x[t + 1]}, bf16x2v);
-        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, first, x[t], false), r1 = __builtin_amdgcn_fdot2_f32_bf16(a, second, x[t + 1], false);
-        const bf16x2v b = __builtin_convertvector(float2v{r0, r1}, bf16x2v);
-        const bf16x2v c = __builtin_convertvector(float2v{__builtin_amdgcn_fdot2_f32_bf16(b, first, r0, false),
-                                                          __builtin_amdgcn_fdot2_f32_bf16(b, second, r1, false)}, bf16x2v);
-        h[t] = a[0]; h[t + 1] = a[1];
-        m[t] = b[0]; m[t + 1] = b[1];
-        l[t] = c[0]; l[t + 1] = c[1];
-    }
+        for (int t = 0; t < 8; t += 2) {
+            const bf16x2v a = __builtin_convertvector(float2v{v[t], v[t + 1]}, bf16x2v);
+            o[t] = a[0]; o[t + 1] = a[1];
+        }
+    };
+    auto remainders = [&](const bf16x8 &o, const float (&v)[8]) {
+#pragma unroll
+        for (int t = 0; t < 8; t += 2) {
+            const bf16x2v a = {o[t], o[t + 1]};
+            r[t] = __builtin_amdgcn_fdot2_f32_bf16(a, first, v[t], false);
+            r[t + 1] = __builtin_amdgcn_fdot2_f32_bf16(a, second, v[t + 1], false);
+        }
+        tie8(r);
+    };
+    terms(x, h);
+    remainders(h, x);
+    terms(r, m);
+    remainders(m, r);
+    terms(r, l);
 }
 
 // 2 x for finite x of at least 2^-126 in absolute value, by the exponent field (a smaller x becomes x +- 2^-126; infinities are not kept)

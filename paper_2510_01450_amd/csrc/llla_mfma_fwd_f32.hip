@@ -351,10 +351,14 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
             w0 = *reinterpret_cast<const f32x4 *>(wp);
             w1 = *reinterpret_cast<const f32x4 *>(wp + 4);
             if (LIVE < 4 && wave >= LIVE) continue;       // a padded feature block (a scalar branch)
+            // (this wave's two addresses as offsets: chosen among the four pointers they were loads through the generic address space, each waited for by
+            // itself and for the transfers of the next block with it)
+            const int row0 = (32 * hf + g_e) * FD + (nn_e & 3), blk = 4 * ((wave & 1) ^ (g_e & 1));
+            const int at[2] = {row0 + 4 * (blk + (c4 ^ (g_e >> 1))) + 32 * (wave >> 1), row0 + 4 * (blk + (c4 ^ (2 + (g_e >> 1)))) + 32 * (wave >> 1)};
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const float sw = t < 4 ? w0[t & 3] : w1[t & 3];
-                const float kmu = ka[t & 1][wave & 1][4 * t * FD + 32 * (wave >> 1)];
+                const float kmu = kt[at[t & 1] + 4 * t * FD];
                 mu_acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-sw * sw, kmu, mu_acc, 0, 0, 0);   // -mu~'[query 4g+r][16 wave + nn]
             }
         }
