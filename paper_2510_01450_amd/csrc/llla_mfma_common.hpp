@@ -44,16 +44,17 @@ struct Shape {
 // workgroup, hundreds of workgroups per head).  The 64-row sweeps do not use it: all blocks of a head fit an XCD at
 // once, they would start together and the XCD would wait for the longest; those kernels put the head on blockIdx.x.
 struct BlockMap { int bh, blk; };
-__device__ inline BlockMap xcd_block_map()
+// (32 bits: a call has fewer than 2^31 rows, and a division of 64 costs a workgroup some hundred instructions)
+__device__ inline int linear_block() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+// workgroup `lin` (in dispatch order) of nblk blocks of nbh heads
+__device__ inline BlockMap xcd_block_map(int lin, int nblk, int nbh)
 {
-    const int nblk = (int)gridDim.x, nbh = (int)gridDim.y;
-    const long long lin = (long long)blockIdx.y * nblk + blockIdx.x;
-    const long long grouped = (long long)(nbh & ~7) * nblk;
-    if (lin >= grouped) return BlockMap{(int)blockIdx.y, (int)blockIdx.x};
-    const int xcd = (int)(lin & 7);
-    const long long k = lin >> 3;
-    return BlockMap{(int)(k / nblk) * 8 + xcd, (int)(k % nblk)};
+    const unsigned l = (unsigned)lin, nb = (unsigned)nblk;
+    if (l >= (unsigned)(nbh & ~7) * nb) return BlockMap{(int)(l / nb), (int)(l % nb)};
+    const unsigned k = l >> 3;
+    return BlockMap{(int)(k / nb * 8 + (l & 7)), (int)(k % nb)};
 }
+__device__ inline BlockMap xcd_block_map() { return xcd_block_map(linear_block(), (int)gridDim.x, (int)gridDim.y); }
 
 // Row broadcasts across the 16-lane rows of a wave: rows 1 and 3 receive lane 15 of rows 0 and 2 (the other rows
 // keep x); rows 2 and 3 receive lane 31, the last lane of row 1 (rows 0 and 1 keep x).

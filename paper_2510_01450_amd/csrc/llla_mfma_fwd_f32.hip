@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                                                             dual::DualArgs da, int out_bf16)
 {
     // nqb: blocks of 16 query rows the sequence has; rows [0, da.nrows), a multiple of 16 or all, are the key-space workgroups' (four each),
-    // which follow the others of their head and work on the caller's own tensors
+    // which follow all others and work on the caller's own tensors
     using S = Shape<FD>;
     constexpr int NB = 4, QW = 4, QB = 16, YP = S::YP;
     // The backward at d = 16 / 32 sums mu~ and omega on the vector ALU, from the same rounded sqrt(w) k that Sigma~ is formed of, which leaves
@@ -106,20 +106,26 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     constexpr bool MU_VALU = BWD && LIVE < 4;
     __shared__ __align__(16) F32Shared sm;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
-    const BlockMap bm = xcd_block_map();
-    const int bh = bm.bh, b = bh / H, h = bh % H;
+    const int own = BWD ? nqb : nqb - (da.nrows + QB - 1) / QB;      // blocks of a head here
+    const int lin = linear_block();
     if constexpr (!BWD) {
-        const int own = nqb - (da.nrows + QB - 1) / QB;
-        if (bm.blk >= own) {
+        // Behind the blocks of all heads.  Behind those of their own head they held up the longest blocks of the heads that come next on the same XCD.
+        // us a call so / here: 16 heads x 1024 342 / 331, 12 x 800 263 / 215, 24 x 400 144 / 128, 64 x 128 136 / 95, 64 x 500 438 / 383, 16 x 256
+        // 80 / 69, 16 x 500 138 / 140; after the first 256 workgroups 331, 246, 147, 95, 414, 83, 142; in front of all 331, 250, 146, 116, 417, 83, 143.
+        const int at = lin - own * (int)gridDim.y;
+        if (at >= 0) {
+            const int bh = (int)((unsigned)at % gridDim.y), part = (int)((unsigned)at / gridDim.y);
             using DS = dual::DualSharedRows<16 * LIVE, 4>;
             static_assert(sizeof(DS) <= sizeof(F32Shared), "key-space rows fit the workgroup's LDS");
             auto &ds = *reinterpret_cast<DS *>(&sm);
-            const int top = da.nrows - 1 - 4 * (bm.blk - own);
+            const int top = da.nrows - 1 - 4 * part;
             if (out_bf16) dual::dual_forward_rows<16 * LIVE, 4, bf16_t>(ds, da, bh, top);
             else dual::dual_forward_rows<16 * LIVE, 4, float>(ds, da, bh, top);
             return;
         }
     }
+    const BlockMap bm = xcd_block_map(lin, own, (int)gridDim.y);
+    const int bh = bm.bh, b = bh / H, h = bh % H;
     const int i0 = (nqb - 1 - bm.blk) * QB;                           // long rows first
     const int ilast = min(i0 + QB - 1, n - 1);
     const int nblk = causal ? ilast / FKB + 1 : (n + FKB - 1) / FKB;
