@@ -182,16 +182,19 @@ __device__ inline u32x6 split_tile(f32x4 x)
     asm("" : "+s"(lo), "+s"(hi));
     const bf16x2v first = __builtin_bit_cast(bf16x2v, lo), second = __builtin_bit_cast(bf16x2v, hi);
     u32x6 r;
+    float v[4] = {x[0], x[1], x[2], x[3]};
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const bf16x2v a = __builtin_convertvector(float2v{x[2 * t], x[2 * t + 1]}, bf16x2v);
-        const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, first, x[2 * t], false), r1 = __builtin_amdgcn_fdot2_f32_bf16(a, second, x[2 * t + 1], false);
-        const bf16x2v b = __builtin_convertvector(float2v{r0, r1}, bf16x2v);
-        const bf16x2v c = __builtin_convertvector(float2v{__builtin_amdgcn_fdot2_f32_bf16(b, first, r0, false),
-                                                          __builtin_amdgcn_fdot2_f32_bf16(b, second, r1, false)}, bf16x2v);
-        r[t] = __builtin_bit_cast(unsigned, b);
-        r[2 + t] = __builtin_bit_cast(unsigned, a);
-        r[4 + t] = __builtin_bit_cast(unsigned, c);
+    for (int term = 0; term < 3; ++term) {                // h, m, l; the stages kept apart as in split3_bf16
+        const int at = term == 0 ? 2 : term == 1 ? 0 : 4;
+        const bf16x2v a = __builtin_convertvector(float2v{v[0], v[1]}, bf16x2v), b = __builtin_convertvector(float2v{v[2], v[3]}, bf16x2v);
+        r[at] = __builtin_bit_cast(unsigned, a);
+        r[at + 1] = __builtin_bit_cast(unsigned, b);
+        if (term == 2) break;
+        v[0] = __builtin_amdgcn_fdot2_f32_bf16(a, first, v[0], false);
+        v[1] = __builtin_amdgcn_fdot2_f32_bf16(a, second, v[1], false);
+        v[2] = __builtin_amdgcn_fdot2_f32_bf16(b, first, v[2], false);
+        v[3] = __builtin_amdgcn_fdot2_f32_bf16(b, second, v[3], false);
+        asm("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
     }
     return r;
 }

@@ -104,20 +104,23 @@ __global__ __launch_bounds__(WNT, 1) void moments_f32_wide_kernel(
 {
     __shared__ __align__(16) WideShared sm;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
-    const BlockMap bm = xcd_block_map();
-    const int bh = bm.bh, b = bh / H, h = bh % H;
+    const int own = BWD ? nqb : nqb - (da.nrows + WQB - 1) / WQB;      // blocks of a head here
+    const int lin = linear_block();
     if constexpr (!BWD) {
-        const int own = nqb - (da.nrows + WQB - 1) / WQB;
-        if (bm.blk >= own) {
+        const int at = lin - own * (int)gridDim.y;         // behind the blocks of all heads, as in moments_f32_kernel
+        if (at >= 0) {
+            const int bh = (int)((unsigned)at % gridDim.y), part = (int)((unsigned)at / gridDim.y);
             using DS = dual::DualSharedRows<WD, WQB>;
             static_assert(sizeof(DS) <= sizeof(WideShared), "key-space rows fit the workgroup's LDS");
             auto &ds = *reinterpret_cast<DS *>(&sm);
-            const int top = da.nrows - 1 - WQB * (bm.blk - own);
+            const int top = da.nrows - 1 - WQB * part;
             if (out_bf16) dual::dual_forward_rows<WD, WQB, bf16_t>(ds, da, bh, top);
             else dual::dual_forward_rows<WD, WQB, float>(ds, da, bh, top);
             return;
         }
     }
+    const BlockMap bm = xcd_block_map(lin, own, (int)gridDim.y);
+    const int bh = bm.bh, b = bh / H, h = bh % H;
     const int i0 = (nqb - 1 - bm.blk) * WQB;                           // long rows first
     const int ilast = min(i0 + WQB - 1, n - 1);
     const int nblk = causal ? ilast / WKB + 1 : (n + WKB - 1) / WKB;
