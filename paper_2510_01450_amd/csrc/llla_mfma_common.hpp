@@ -490,8 +490,8 @@ __device__ __forceinline__ void symmetric_rows(const f32x4 &x, float (&a)[16])
 // overlap, and 112 tile products at d = 128 are a third of the solve.  Each product starts from zero and is added to its tile on the vector
 // ALU: chained onto the tile its three MFMAs left errors of up to 1.09 times those of fp32 MFMA, which rounds at each of a product's sixteen
 // rows; so they are 0.80 to 0.99 times those (O, dQ, dK, dV; 140 to 400 rows, bf16 and fp32).  us a call, fp32 MFMA and split: 16 heads x
-// 2048 1049 and 1012, 16 x 8192 9674 and 9613, 8 x 44 46.7 and 43.8, backward 8 x 961 402 and 386; fp32 64 x 700 2413 and 2357.  Decode,
-// one solve per compute unit, gains nothing (224 heads of up to 589 keys 54.7 and 55.6), nor do four systems per wave at d = 64 (64 x 4096 bf16
+// 2048 1049 and 1012, 16 x 8192 9674 and 9613, 8 x 44 46.7 and 43.8, backward 8 x 961 402 and 386; fp32 64 x 700 2413 and 2357.  Decode at
+// d = 128, one solve per compute unit, gains nothing (224 heads of up to 589 keys 54.7 and 55.6), nor do four systems per wave at d = 64 (64 x 4096 bf16
 // 2829 and 2916, 16 x 1024 fp32 346 and 352).
 // SYMMETRIC: the diagonal tiles come in symmetric to the last bit, and the factorisation takes one triangle of them (symmetric_rows); otherwise it takes
 // the mean of the two.
@@ -551,7 +551,9 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 // The same with further block columns (the decode tail's solve at d <= 64):
 //   in : x[v][P]               NX further block columns, negated right-hand sides -B in the same layout
 //   out: x = U^{-T} B; returns the smallest pivot before it was raised to the floor
-// Diagonal tiles come in symmetric (only their products are added to them here).
+// Diagonal tiles come in symmetric (only their products are added to them here).  What bounds it is one chain per head: per diagonal tile rows, 1400
+// cycles of elimination, 300 of inversion, products.  Rows by lane exchanges and products in three bf16, against a way through LDS and fp32 MFMA, with the
+// query's early request: us a call, 16 heads x 4096 23.7 -> 23.4, 16 x 512 (solved by the pass) 17.4 -> 16.3; errors 0.6 to 1.0 times the former.
 template <int NB, int NX>
 __device__ __forceinline__ float factorise_columns(f32x4 (&acc)[NB * (NB + 1) / 2], int g, int nn, float pivot_floor, f32x4 (&x)[NX][NB])
 {

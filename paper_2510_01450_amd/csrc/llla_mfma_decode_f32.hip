@@ -187,7 +187,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         }
     };
     // fp32 at d = 32: keys and values alternate, and the last rows are a choice of addresses instead of a branch (us, as the others / this: 256 heads
-    // x 4096 66.8 / 58.0, 16 x 8192 21.2 / 18.6; bf16 at d = 32, 256 x 4096, 32.7 / 35.3; fp32 at d = 64, 512 x 512, with a branch 51.3 / 52.7).
+    // x 4096 66.8 / 58.0, 16 x 8192 21.2 / 18.6; bf16 at d = 32, 256 x 4096, 32.7 / 35.3).
     auto load = [&](Step &st, int s) {
         if constexpr (D != 32 || sizeof(TI) == 2) {
             load_rows(st.k, Kh, krow, koff, s);

@@ -5,7 +5,7 @@
 // and output weights); the moments go through v_mfma_f32_16x16x4_f32 with the key as contraction index, lane (g, n) holding feature n of
 // key 4 c + g; the system is solved by the wave as in the fp32 matrix-core forward: the intercept eliminated first, pivots that are noise
 // dropped (llla_mfma_fwd_f32.hip).  Rows that see at most d keys are served in key space by further workgroups (dual_row).
-// 1 head x 128 rows at d = 16: 24 us (the vector kernel alone) -> 8.2 on the GPU; a call from Python takes 14.
+// 1 head x 128 rows at d = 16: 24 us (the vector kernel alone) -> 8.1 on the GPU, which is what such calls take one after the other.
 #include "llla_decode_tail.hpp"
 
 namespace llla {
