@@ -7,6 +7,7 @@ import functools
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -111,23 +112,40 @@ _host = None
 _entries = {}
 
 
+class _PythonHost:
+    """In place of a host extension that can be neither loaded nor built: leaves every call to the code of this module."""
+
+    @staticmethod
+    def forward(*args):
+        return NotImplemented
+
+    decode = forward
+
+
 def _load_host():
-    """The native host extension, rebuilt first if it is missing or not of the tree's sources and this torch."""
+    """The native host extension, rebuilt first if it is missing or not of the tree's sources and this torch.  It only saves host time, so
+    a machine that has no compiler, headers or writable tree for it is told once and works without."""
     global _host
     if _host is None:
         from . import build as _build
-        if not _build.host_is_current():
-            _build.build_host()
-        loader = importlib.machinery.ExtensionFileLoader("llla_host", _build.LIB_HOST)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("llla_host", loader))
-        loader.exec_module(module)
-        _host = module
+        try:
+            if not _build.host_is_current():
+                _build.build_host()
+            loader = importlib.machinery.ExtensionFileLoader("llla_host", _build.LIB_HOST)
+            module = importlib.util.module_from_spec(importlib.util.spec_from_loader("llla_host", loader))
+            loader.exec_module(module)
+            _host = module
+        except Exception as e:      # noqa: BLE001 (no compiler, no headers, a tree that cannot be written, another Python's binary ..)
+            warnings.warn("llla_host.so cannot be built or loaded (%s: %s); calls are marshalled in Python, some 4 us more of the host's "
+                          "time each" % (type(e).__name__, e), RuntimeWarning, stacklevel=3)
+            _host = _PythonHost()
     return _host
 
 
 def _entry_points(measure: bool):
     """Addresses of the C ABI's functions that the host extension calls, of the library in use."""
     L = _load(measure)
+    _load_host()
     _entries[measure] = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.llla_forward_ex, L.llla_forward_workspace_bytes, L.llla_decode_path, L.llla_decode_workspace_bytes))
     return _entries[measure]
@@ -247,8 +265,9 @@ def llla_forward(Q, K, V, lam, scale: float, causal: bool = True, out_dtype=None
     statistics of Eq. (lla) when ``return_stats`` is set."""
     # the ordinary forms, natively (1 head x 128 rows at d = 16 in fp32 11.7 -> 8.1 us a call); NotImplemented: not one of them, nothing done
     fn = _entries.get(_use_measure) or _entry_points(_use_measure)
-    r = (_host or _load_host()).forward(fn[0], fn[1], Q, K, V, lam, scale, causal, out_dtype, PATHS.get(path, -1), workspace, out, return_stats,
-                                        _current_stream if stream is None else int(stream.cuda_stream))
+    r = _host.forward(
+        fn[0], fn[1], Q, K, V, lam, scale, causal, out_dtype, PATHS.get(path, -1), workspace, out, return_stats,
+        _current_stream if stream is None else int(stream.cuda_stream))
     if r is not NotImplemented:
         if type(r) is int:
             raise LlaError(r, "llla_forward")
@@ -374,8 +393,9 @@ def llla_decode(q, Kc, Vc, lam: float, scale: float, seqlens=None, out_dtype=Non
                 workspace=None, out=None, stream=None):
     """One query per (batch, head) against [B, H, L_max, d] caches.  q: [B, H, d].  Returns [B, H, d]."""
     fn = _entries.get(_use_measure) or _entry_points(_use_measure)
-    r = (_host or _load_host()).decode(fn[2], fn[3], q, Kc, Vc, lam, scale, seqlens, out_dtype, PATHS.get(path, -1), workspace, out,
-                                       _current_stream if stream is None else int(stream.cuda_stream))
+    r = _host.decode(
+        fn[2], fn[3], q, Kc, Vc, lam, scale, seqlens, out_dtype, PATHS.get(path, -1), workspace, out,
+        _current_stream if stream is None else int(stream.cuda_stream))
     if r is not NotImplemented:
         if type(r) is int:
             raise LlaError(r, "llla_decode")

@@ -1,0 +1,42 @@
+"""The host extension is an aid: without it, and without what it takes to build it, every call still goes through binding.py's own code."""
+import warnings
+
+import pytest
+
+from paper_2510_01450_amd import binding
+from paper_2510_01450_amd import build
+
+
+@pytest.fixture
+def unloaded(monkeypatch):
+    """A process that has made no call yet."""
+    monkeypatch.setattr(binding, "_host", None)
+    monkeypatch.setattr(binding, "_entries", {})
+
+
+def _missing(monkeypatch, how, tmp_path):
+    if how == "no compiler":
+        monkeypatch.setattr(build, "host_is_current", lambda: False)
+        monkeypatch.setattr(build, "CXX", str(tmp_path / "no-such-compiler"))
+    elif how == "compiler fails":
+        monkeypatch.setattr(build, "host_is_current", lambda: False)
+        monkeypatch.setattr(build, "CXX", "false")
+    elif how == "tree not writable":
+        monkeypatch.setattr(build, "host_is_current", lambda: False)
+        monkeypatch.setattr(build, "build_host", lambda verbose=False: open(str(tmp_path / "no-such-folder" / "llla_host.so"), "wb"))
+    else:                                                      # a file that cannot be loaded
+        bad = tmp_path / "llla_host.so"
+        bad.write_bytes(b"not a library")
+        monkeypatch.setattr(build, "host_is_current", lambda: True)
+        monkeypatch.setattr(build, "LIB_HOST", str(bad))
+
+
+@pytest.mark.parametrize("how", ["no compiler", "compiler fails", "tree not writable", "not a library"])
+def test_calls_do_without_it(monkeypatch, unloaded, how, tmp_path):
+    _missing(monkeypatch, how, tmp_path)
+    with pytest.warns(RuntimeWarning, match="llla_host.so"):
+        host = binding._load_host()
+    assert host.forward(*range(14)) is NotImplemented and host.decode(*range(13)) is NotImplemented
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")                         # told once, tried once
+        assert binding._load_host() is host
