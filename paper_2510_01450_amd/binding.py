@@ -142,8 +142,12 @@ def _load_host():
     return _host
 
 
-def _entry_points(measure: bool):
-    """Addresses of the C ABI's functions that the host extension calls, of the library in use."""
+def _entry_points(*tensors):
+    """Addresses of the C ABI's functions that the host extension calls, of the library in use; kept in _entries.  None, with nothing loaded or
+    built, while a call's tensors are not all on the GPU: the caller's own checks word that mistake."""
+    if not all(torch.is_tensor(t) and t.is_cuda for t in tensors):
+        return None
+    measure = _use_measure
     L = _load(measure)
     _load_host()
     _entries[measure] = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (
@@ -264,8 +268,8 @@ def llla_forward(Q, K, V, lam, scale: float, causal: bool = True, out_dtype=None
     tensor [B, H, n] (one ridge per query row).  Returns O ([B, H, n, d]), or (O, rho, delta) with the per-row
     statistics of Eq. (lla) when ``return_stats`` is set."""
     # the ordinary forms, natively (1 head x 128 rows at d = 16 in fp32 11.7 -> 8.1 us a call); NotImplemented: not one of them, nothing done
-    fn = _entries.get(_use_measure) or _entry_points(_use_measure)
-    r = _host.forward(
+    fn = _entries.get(_use_measure) or _entry_points(Q, K, V)
+    r = NotImplemented if fn is None else _host.forward(
         fn[0], fn[1], Q, K, V, lam, scale, causal, out_dtype, PATHS.get(path, -1), workspace, out, return_stats,
         _current_stream if stream is None else int(stream.cuda_stream))
     if r is not NotImplemented:
@@ -392,8 +396,8 @@ def llla_backward(Q, K, V, dO, lam, scale: float, path: str = "auto", workspace=
 def llla_decode(q, Kc, Vc, lam: float, scale: float, seqlens=None, out_dtype=None, path: str = "auto",
                 workspace=None, out=None, stream=None):
     """One query per (batch, head) against [B, H, L_max, d] caches.  q: [B, H, d].  Returns [B, H, d]."""
-    fn = _entries.get(_use_measure) or _entry_points(_use_measure)
-    r = _host.decode(
+    fn = _entries.get(_use_measure) or _entry_points(q, Kc, Vc)
+    r = NotImplemented if fn is None else _host.decode(
         fn[2], fn[3], q, Kc, Vc, lam, scale, seqlens, out_dtype, PATHS.get(path, -1), workspace, out,
         _current_stream if stream is None else int(stream.cuda_stream))
     if r is not NotImplemented:

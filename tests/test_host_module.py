@@ -2,7 +2,9 @@
 import warnings
 
 import pytest
+import torch
 
+import paper_2510_01450_amd as llla
 from paper_2510_01450_amd import binding
 from paper_2510_01450_amd import build
 
@@ -40,3 +42,15 @@ def test_calls_do_without_it(monkeypatch, unloaded, how, tmp_path):
     with warnings.catch_warnings():
         warnings.simplefilter("error")                         # told once, tried once
         assert binding._load_host() is host
+
+
+def test_mistakes_load_nothing(monkeypatch, unloaded):
+    def loads(*args):
+        raise AssertionError("loaded for a call that is refused")
+    monkeypatch.setattr(binding, "_load", loads)
+    monkeypatch.setattr(binding, "_load_host", loads)
+    t, q = torch.zeros(1, 1, 8, 16), torch.zeros(1, 1, 16)
+    with pytest.raises(ValueError, match="device tensors"):
+        llla.llla_forward(t, t, t, 0.1, 1.0)
+    with pytest.raises(ValueError, match="device tensors"):
+        llla.llla_decode(q, t, t, 0.1, 1.0)
