@@ -7,6 +7,7 @@ import functools
 import importlib.machinery
 import importlib.util
 import os
+import threading
 import warnings
 
 import torch
@@ -16,6 +17,7 @@ _LIB_PATH = os.path.join(_HERE, "libllla.so")
 _MEASURE_PATH = os.path.join(_HERE, "libllla_measure.so")
 _libs = {}
 _use_measure = False
+_load_lock = threading.RLock()          # of two threads that make the first call one loads (and builds, if need be)
 
 PATHS = {"auto": 0, "valu": 1, "mfma": 2}
 _DTYPES = {torch.float32: 0, torch.bfloat16: 1}
@@ -98,13 +100,16 @@ def _load(measure: bool):
         return _libs[measure]
     from . import build as _build
     path = _MEASURE_PATH if measure else _LIB_PATH
-    if not _build.is_current(path, measure):
-        if not os.path.exists(_build.HIPCC):
-            raise RuntimeError("%s is missing or older than its sources and there is no hipcc to rebuild it" % path)
-        _build._build_one(path, measure, False, ())
-    L = ctypes.CDLL(path)
-    _declare(L, measure)
-    _libs[measure] = L
+    with _load_lock:
+        if measure in _libs:
+            return _libs[measure]
+        if not _build.is_current(path, measure):
+            if not os.path.exists(_build.HIPCC):
+                raise RuntimeError("%s is missing or older than its sources and there is no hipcc to rebuild it" % path)
+            _build._build_one(path, measure, False, ())
+        L = ctypes.CDLL(path)
+        _declare(L, measure)
+        _libs[measure] = L
     return L
 
 
@@ -126,19 +131,20 @@ def _load_host():
     """The native host extension, rebuilt first if it is missing or not of the tree's sources and this torch.  It only saves host time, so
     a machine that has no compiler, headers or writable tree for it is told once and works without."""
     global _host
-    if _host is None:
-        from . import build as _build
-        try:
-            if not _build.host_is_current():
-                _build.build_host()
-            loader = importlib.machinery.ExtensionFileLoader("llla_host", _build.LIB_HOST)
-            module = importlib.util.module_from_spec(importlib.util.spec_from_loader("llla_host", loader))
-            loader.exec_module(module)
-            _host = module
-        except Exception as e:      # noqa: BLE001 (no compiler, no headers, a tree that cannot be written, another Python's binary ..)
-            warnings.warn("llla_host.so cannot be built or loaded (%s: %s); calls are marshalled in Python, some 4 us more of the host's "
-                          "time each" % (type(e).__name__, e), RuntimeWarning, stacklevel=3)
-            _host = _PythonHost()
+    with _load_lock:
+        if _host is None:
+            from . import build as _build
+            try:
+                if not _build.host_is_current():
+                    _build.build_host()
+                loader = importlib.machinery.ExtensionFileLoader("llla_host", _build.LIB_HOST)
+                module = importlib.util.module_from_spec(importlib.util.spec_from_loader("llla_host", loader))
+                loader.exec_module(module)
+                _host = module
+            except Exception as e:      # noqa: BLE001 (no compiler, no headers, a tree that cannot be written, another Python's binary ..)
+                warnings.warn("llla_host.so cannot be built or loaded (%s: %s); calls are marshalled in Python, some 4 us more of the host's "
+                              "time each" % (type(e).__name__, e), RuntimeWarning, stacklevel=3)
+                _host = _PythonHost()
     return _host
 
 

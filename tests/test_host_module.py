@@ -1,4 +1,6 @@
 """The host extension is an aid: without it, and without what it takes to build it, every call still goes through binding.py's own code."""
+import threading
+import time
 import warnings
 
 import pytest
@@ -54,3 +56,23 @@ def test_mistakes_load_nothing(monkeypatch, unloaded):
         llla.llla_forward(t, t, t, 0.1, 1.0)
     with pytest.raises(ValueError, match="device tensors"):
         llla.llla_decode(q, t, t, 0.1, 1.0)
+
+
+def test_threads_build_it_once(monkeypatch, unloaded):
+    built = []
+
+    def slow_build(verbose=False):
+        built.append(1)
+        time.sleep(0.2)
+        raise OSError("no compiler")
+    monkeypatch.setattr(build, "host_is_current", lambda: False)
+    monkeypatch.setattr(build, "build_host", slow_build)
+    got = []
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        threads = [threading.Thread(target=lambda: got.append(binding._load_host())) for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    assert len(built) == 1 and len(got) == 4 and all(h is got[0] for h in got)
