@@ -23,6 +23,8 @@ LIB_MEASURE = os.path.join(HERE, "libllla_measure.so")
 LIB_HOST = os.path.join(HERE, "llla_host.so")
 HOST_SOURCE = os.path.join(CSRC, "host", "llla_host.cpp")
 CXX = os.environ.get("CXX", "g++")
+HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall"]
+HOST_LIBS = ["-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -98,22 +100,22 @@ def host_command(out: str) -> list:
     import torch
     root = os.path.dirname(torch.__file__)
     inc = os.path.join(root, "include")
-    return [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+    return [CXX, *HOST_FLAGS, "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
             "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
             "-isystem", sysconfig.get_paths()["include"], HOST_SOURCE, "-o", out,
-            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+            "-L" + os.path.join(root, "lib"), *HOST_LIBS]
 
 
 def host_hash() -> str:
-    """Hash of what the host extension is compiled from and against."""
+    """Hash of what the host extension is compiled from, with and against (without the paths, which differ between machines; which compiler it
+    was does not matter to a module that loads)."""
     import sys
     import torch
     h = hashlib.sha256()
     for f in (HOST_SOURCE, os.path.join(ROOT, "include", "llla.h")):
         with open(f, "rb") as fh:
             h.update(fh.read())
-    h.update(("%s %s" % (torch.__version__, sys.version)).encode())
+    h.update(("%s %s %s" % (" ".join(HOST_FLAGS + HOST_LIBS), torch.__version__, sys.version)).encode())
     return h.hexdigest()
 
 

@@ -76,3 +76,9 @@ def test_threads_build_it_once(monkeypatch, unloaded):
         for t in threads:
             t.join()
     assert len(built) == 1 and len(got) == 4 and all(h is got[0] for h in got)
+
+
+def test_stamp_covers_the_flags(monkeypatch):
+    before = build.host_hash()
+    monkeypatch.setattr(build, "HOST_FLAGS", [f.replace("-O2", "-O3") for f in build.HOST_FLAGS])
+    assert build.host_hash() != before
