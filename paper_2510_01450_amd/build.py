@@ -141,10 +141,10 @@ def build_host(verbose: bool = False) -> str:
 
 def build(verbose: bool = False, extra=(), measure: bool = True) -> str:
     """Compile every HIP source into libllla.so (and libllla_measure.so), and the host extension.  Always recompiles."""
-    build_host(verbose)
     _build_one(LIB, False, verbose, extra)
     if measure:
         _build_one(LIB_MEASURE, True, verbose, extra)
+    build_host(verbose)
     return LIB
 
 

@@ -82,3 +82,11 @@ def test_stamp_covers_the_flags(monkeypatch):
     before = build.host_hash()
     monkeypatch.setattr(build, "HOST_FLAGS", [f.replace("-O2", "-O3") for f in build.HOST_FLAGS])
     assert build.host_hash() != before
+
+
+def test_kernels_are_built_before_it(monkeypatch):
+    order = []
+    monkeypatch.setattr(build, "_build_one", lambda lib, *a: order.append(lib))
+    monkeypatch.setattr(build, "build_host", lambda verbose=False: order.append(build.LIB_HOST))
+    build.build()
+    assert order == [build.LIB, build.LIB_MEASURE, build.LIB_HOST]
