@@ -70,19 +70,17 @@ struct Scratch {
     size_t bytes;
 };
 
-bool scratch(PyObject *o, size_t need, const at::Device &device, Scratch &s)
+// the caller's scratch, or without any `need` bytes from torch's allocator
+Scratch scratch(const at::Tensor *given, size_t need, const at::Device &device)
 {
-    if (o == Py_None) {
+    Scratch s;
+    if (given == nullptr) {
         s.own = at::empty({(int64_t)(need < 256 ? 256 : need)}, at::TensorOptions().dtype(at::kByte).device(device));
-        s.ptr = s.own.data_ptr();
-        s.bytes = (size_t)s.own.numel();
-        return true;
+        given = &s.own;
     }
-    if (!is_tensor(o)) return false;
-    const at::Tensor &t = THPVariable_Unpack(o);
-    s.ptr = t.data_ptr();
-    s.bytes = (size_t)t.numel() * t.element_size();
-    return true;
+    s.ptr = given->data_ptr();
+    s.bytes = (size_t)given->numel() * given->element_size();
+    return s;
 }
 
 PyObject *not_implemented() { Py_RETURN_NOTIMPLEMENTED; }
@@ -98,15 +96,12 @@ void *stream_of(PyObject *o)
     return s;
 }
 
-// The C ABI neither needs nor touches Python, and a launch can wait for room in the queue: other threads go on meanwhile, as under ctypes.
-template <class Call>
-llla_status without_gil(Call call)
-{
+// Other threads go on while torch allocates (which can wait for the GPU, or free what it holds and try again) and while the C ABI is called (a launch
+// can wait for room in the queue), as they do where Python makes these calls.  Taken back on the way out, exceptions included.
+struct WithoutGil {
     PyThreadState *state = PyEval_SaveThread();
-    const llla_status st = call();
-    PyEval_RestoreThread(state);
-    return st;
-}
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
 
 // forward(llla_forward_ex, llla_forward_workspace_bytes, Q, K, V, lam, scale, causal, out_dtype, path, workspace, out, return_stats, stream)
 PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n_args)
@@ -142,32 +137,31 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     if (path < 0) return not_implemented();
     if (a[10] != Py_None && !is_tensor(a[10])) return not_implemented();
 
-    const at::TensorOptions options = at::TensorOptions().device(Q.device()).dtype(at::kFloat);
-    at::Tensor O, rho, delta;
-    if (a[11] != Py_None) {
-        O = THPVariable_Unpack(a[11]);
-    } else {
-        O = at::empty({B, H, n, d}, options.dtype(out_type));
-        dtype_of(out_type, out);
-        so = llla_strides{O.stride(0), O.stride(1), O.stride(2)};
-    }
-    if (stats) {
-        rho = at::empty({B, H, n, d}, options);
-        delta = at::empty({B, H, n}, options);
-    }
-    const SizeFn size = reinterpret_cast<SizeFn>(PyLong_AsVoidPtr(a[1]));
-    Scratch ws;
-    if (!scratch(a[10], size((int)B, (int)H, (int)n, (int)d, in), Q.device(), ws)) return not_implemented();
-    const ForwardFn call = reinterpret_cast<ForwardFn>(PyLong_AsVoidPtr(a[0]));
     void *stream = stream_of(a[13]);
     if (PyErr_Occurred()) return nullptr;
-    const void *qp = Q.data_ptr(), *kp = K.data_ptr(), *vp = V.data_ptr();
-    void *op = O.data_ptr();
-    float *rp = stats ? static_cast<float *>(rho.data_ptr()) : nullptr, *dp = stats ? static_cast<float *>(delta.data_ptr()) : nullptr;
-    const llla_status st = without_gil([&] {
-        return call(qp, kp, vp, op, sq, sk, sv, so, (int)B, (int)H, (int)n, (int)d, in, out, causal, (float)lambda, lam_rows, (float)scale, rp, dp,
-                    (llla_path)path, ws.ptr, ws.bytes, stream);
-    });
+    const ForwardFn call = reinterpret_cast<ForwardFn>(PyLong_AsVoidPtr(a[0]));
+    const SizeFn size = reinterpret_cast<SizeFn>(PyLong_AsVoidPtr(a[1]));
+    const at::Tensor *given = a[10] == Py_None ? nullptr : &THPVariable_Unpack(a[10]);
+    at::Tensor O, rho, delta;
+    if (a[11] != Py_None) O = THPVariable_Unpack(a[11]);
+    llla_status st;
+    {
+        WithoutGil released;
+        const at::TensorOptions options = at::TensorOptions().device(Q.device()).dtype(at::kFloat);
+        if (!O.defined()) {
+            O = at::empty({B, H, n, d}, options.dtype(out_type));
+            dtype_of(out_type, out);
+            so = llla_strides{O.stride(0), O.stride(1), O.stride(2)};
+        }
+        if (stats) {
+            rho = at::empty({B, H, n, d}, options);
+            delta = at::empty({B, H, n}, options);
+        }
+        const Scratch ws = scratch(given, given ? 0 : size((int)B, (int)H, (int)n, (int)d, in), Q.device());
+        st = call(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), sq, sk, sv, so, (int)B, (int)H, (int)n, (int)d, in, out, causal, (float)lambda,
+                  lam_rows, (float)scale, stats ? static_cast<float *>(rho.data_ptr()) : nullptr,
+                  stats ? static_cast<float *>(delta.data_ptr()) : nullptr, (llla_path)path, ws.ptr, ws.bytes, stream);
+    }
     if (st != LLLA_OK) return PyLong_FromLong(st);
     PyObject *result;
     if (a[11] != Py_None) {
@@ -216,25 +210,24 @@ PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     if (path < 0) return not_implemented();
     if (a[10] != Py_None && !is_tensor(a[10])) return not_implemented();
 
-    at::Tensor o;
-    if (a[11] != Py_None) {
-        o = THPVariable_Unpack(a[11]);
-    } else {
-        o = at::empty({B, H, d}, at::TensorOptions().device(q.device()).dtype(out_type));
-        dtype_of(out_type, out);
-    }
-    const SizeFn size = reinterpret_cast<SizeFn>(PyLong_AsVoidPtr(a[1]));
-    Scratch ws;
-    if (!scratch(a[10], a[10] == Py_None ? size((int)B, (int)H, (int)n, (int)d, in) : 0, q.device(), ws)) return not_implemented();
-    const DecodeFn call = reinterpret_cast<DecodeFn>(PyLong_AsVoidPtr(a[0]));
     void *stream = stream_of(a[12]);
     if (PyErr_Occurred()) return nullptr;
-    const void *qp = q.data_ptr(), *kp = K.data_ptr(), *vp = V.data_ptr();
-    void *op = o.data_ptr();
-    const llla_status st = without_gil([&] {
-        return call(qp, kp, vp, op, sk, sv, lens, (int)B, (int)H, (int)n, (int)d, in, out, (float)lambda, (float)scale, (llla_path)path, ws.ptr, ws.bytes,
-                    stream);
-    });
+    const DecodeFn call = reinterpret_cast<DecodeFn>(PyLong_AsVoidPtr(a[0]));
+    const SizeFn size = reinterpret_cast<SizeFn>(PyLong_AsVoidPtr(a[1]));
+    const at::Tensor *given = a[10] == Py_None ? nullptr : &THPVariable_Unpack(a[10]);
+    at::Tensor o;
+    if (a[11] != Py_None) o = THPVariable_Unpack(a[11]);
+    llla_status st;
+    {
+        WithoutGil released;
+        if (!o.defined()) {
+            o = at::empty({B, H, d}, at::TensorOptions().device(q.device()).dtype(out_type));
+            dtype_of(out_type, out);
+        }
+        const Scratch ws = scratch(given, given ? 0 : size((int)B, (int)H, (int)n, (int)d, in), q.device());
+        st = call(q.data_ptr(), K.data_ptr(), V.data_ptr(), o.data_ptr(), sk, sv, lens, (int)B, (int)H, (int)n, (int)d, in, out, (float)lambda, (float)scale,
+                  (llla_path)path, ws.ptr, ws.bytes, stream);
+    }
     if (st != LLLA_OK) return PyLong_FromLong(st);
     if (a[11] != Py_None) {
         Py_INCREF(a[11]);

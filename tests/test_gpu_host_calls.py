@@ -1,6 +1,9 @@
 """The native host side of a call (csrc/host/llla_host.cpp) against the Python one: the same bits for every form that it takes, and the same
 errors for what it leaves to the other."""
 import itertools
+import sys
+import threading
+import time
 
 import pytest
 import torch
@@ -89,3 +92,53 @@ def test_integers_and_scalars_serve_as_numbers(monkeypatch):
     t = torch.randn(1, 2, 40, 16, device=DEV)
     want = llla.llla_forward(t, t, t, 1.0, 1.0)
     assert torch.equal(want, llla.llla_forward(t, t, t, 1, np.float64(1.0), causal=1))
+
+
+def _try_to_allocate(call, tries):
+    """Whether another thread gets to run while `call` fails to allocate; Python itself switches threads only where one gives way."""
+    ran, stop = [0], threading.Event()
+
+    def other():
+        while not stop.is_set():
+            ran[0] += 1
+            time.sleep(1e-4)
+    thread = threading.Thread(target=other)
+    interval = sys.getswitchinterval()
+    thread.start()
+    try:
+        sys.setswitchinterval(1000.)
+        before = ran[0]
+        for _ in range(tries):
+            try:
+                call()
+            except torch.cuda.OutOfMemoryError:
+                pass
+            else:
+                raise AssertionError("there was room")
+            if ran[0] != before:
+                return True
+        return False
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        thread.join()
+
+
+def test_allocation_holds_up_no_other_thread():
+    """torch's allocator can take its time (it synchronises and frees what it caches before it gives up, as here under a limit): Python's lock
+    is not held meanwhile."""
+    t = torch.zeros(1, 1, 1 << 20, 16, device=DEV)
+    q, cache = torch.zeros(4, 8, 128, device=DEV), torch.zeros(4, 8, 2048, 128, device=DEV)
+    assert llla.decode_workspace_bytes(4, 8, 2048, 128, torch.float32) > 32 << 20
+    calls = [lambda: llla.llla_forward(t, t, t, 0.1, 1.0), lambda: llla.llla_decode(q, cache, cache, 0.1, 1.0)]
+    small = torch.zeros(1, 1, 40, 16, device=DEV)
+    llla.llla_forward(small, small, small, 0.1, 1.0)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+    try:
+        for i, call in enumerate(calls):
+            assert _try_to_allocate(call, 200), i
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
