@@ -1,6 +1,6 @@
 """fp32 caches at d = 64: rows staged in LDS by DMA, one step of 32 keys ahead.  Lengths that leave the four waves of a workgroup no step, one, two
-and several, whole last steps and partial ones; more heads than the GPU holds at once; the even cut at 4095 and 4096 keys, where a head's
-workgroups double.  Rows 2 d apart, everything beyond the sequence NaN."""
+and several, whole last steps and partial ones; more heads than the GPU holds at once; the flat cut of 129 heads of 4095 and 4096 keys; the even cut
+of 256 heads of as many, which from 4096 on get two workgroups each.  Rows 2 d apart, everything beyond the sequence NaN."""
 import numpy as np
 import pytest
 import torch
@@ -15,7 +15,7 @@ DEV = "cuda"
 
 
 @pytest.mark.parametrize("B,H,L", [(2, 2, 66), (2, 2, 96), (2, 2, 128), (2, 3, 129), (2, 2, 250), (3, 2, 256), (1, 2, 385), (70, 8, 70), (70, 8, 300),
-                                   (43, 3, 4095), (43, 3, 4096)])
+                                   (43, 3, 4095), (43, 3, 4096), (16, 16, 4095), (16, 16, 4096)])
 def test_steps_and_cuts(B, H, L):
     d = 64
     w = workloads.C5.with_shape(name="stages", B=B, H=H, n=L, d=d, dtype="f32", index=2800 + L, values="l2", tol=1e-4, scale=d ** -0.5)
