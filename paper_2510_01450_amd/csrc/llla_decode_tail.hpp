@@ -322,20 +322,24 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, co
                 x[1][P][t] = nn == 0 ? mr[t] - q.v[P][t] : 0.f;
             }
         }
-        // the column of G_c times a power of two, which takes it out of the way of three bf16 at both ends of the range (the third term of a value
-        // below 2^-110 is subnormal, which matrix cores read as zero; the first of one above 2^127.99 infinite)
-        float top = 0.f;
+        // Every column of G_c, and q_c, times a power of two of its own, which takes it out of the way of three bf16 at both ends of the range (the
+        // third term of a value below 2^-110 is subnormal, which matrix cores read as zero; the first of one above 2^127.99 infinite): as on
+        // fp32 MFMA, what one value feature holds is nothing to the others.
+        auto column_exponent = [&](const f32x4 (&c)[NB]) {
+            float top = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4 * NB; ++i) top = fmaxf(top, fabsf(x[0][i / 4][i % 4]));
-        const int e = max(min(__builtin_amdgcn_frexp_expf(wave_max_dpp(top)), 120), -120);      // (0 for 0 and infinity)
-        const float scale = __builtin_ldexpf(1.f, -e);
+            for (int i = 0; i < 4 * NB; ++i) top = fmaxf(top, fabsf(c[i / 4][i % 4]));
+            return max(min(__builtin_amdgcn_frexp_expf(rows_allmax(top)), 120), -120);      // (0 for 0 and infinity)
+        };
+        const int eg = column_exponent(x[0]), eq = column_exponent(x[1]);
+        const float sg = __builtin_ldexpf(1.f, -eg), sq = __builtin_ldexpf(1.f, -eq);
 #pragma unroll
-        for (int I = 0; I < NB; ++I) x[0][I] *= scale;
+        for (int I = 0; I < NB; ++I) { x[0][I] *= sg; x[1][I] *= sq; }
         const float low = factorise_columns<NB, 2>(acc, g, nn, floor, x);
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < 4 * NB; ++i) s = fmaf(x[0][i / 4][i % 4], row_bcast<0>(x[1][i / 4][i % 4]), s);
-        s = __builtin_ldexpf(rows_allsum(s), e);
+        s = __builtin_ldexpf(rows_allsum(s), eg + __builtin_amdgcn_update_dpp(0, eq, 0x150, 0xf, 0xf, true));      // (eq of lane 0 of the row)
         o = fmaf(oinv, yc, s);
         if (__builtin_amdgcn_ballot_w64(low < floor) == 0) break;      // (at the end: nothing but o outlives an attempt)
     }

@@ -35,6 +35,16 @@ __device__ inline float rows_allsum(float x)
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
     return a + b;
 }
+// the largest instead of the sum (a NaN is passed over)
+__device__ inline float rows_allmax(float x)
+{
+    float a = x, b = x;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    a = fmaxf(a, b);
+    b = a;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return fmaxf(a, b);
+}
 
 // C -> R and R -> C for NV vectors at once through the scratch tile (vector v at scw + 16 v)
 template <int NV>

@@ -47,3 +47,31 @@ def test_values_of_any_size(d, L):
     for k in (-110, -100, -60, 60, 110):
         got = llla.llla_decode(q, K, V * 2.0 ** k, 1e-2, d ** -0.5)
         assert torch.equal(got.double(), base.double() * 2.0 ** k), k
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 16), (torch.float32, 32), (torch.bfloat16, 16), (torch.bfloat16, 32)])
+@pytest.mark.parametrize("L", [80, 700, 3000])
+def test_value_features_of_different_sizes(dtype, d, L):
+    """The same with a power of two of its own for every feature of V: no feature of the output hangs on the size of another."""
+    g = torch.Generator(device="cpu").manual_seed(3100 + L + d)
+    q, K, V = [torch.randn(s, generator=g).to(dtype).to(DEV) for s in ((2, 3, d), (2, 3, L, d), (2, 3, L, d))]
+    k = [-110, 110, 0, -60, 60, -100, 0, -85] * (d // 8)
+    size = torch.tensor([2.0 ** k[i] for i in torch.randperm(d, generator=g)], dtype=torch.float64).to(DEV)
+    base = llla.llla_decode(q, K, V, 1e-2, d ** -0.5)
+    got = llla.llla_decode(q, K, (V.double() * size).to(dtype), 1e-2, d ** -0.5)
+    assert torch.isfinite(base).all() and torch.equal(got.double(), base.double() * size)
+
+
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_queries_of_any_size(d):
+    """Keys and values in pairs of opposite sign have no mean, and queries so small that all weights are one then give an output that is linear in
+    them: the same bits times the power of two."""
+    g = torch.Generator(device="cpu").manual_seed(3200 + d)
+    L = 640
+    q, K, V = [torch.randn(s, generator=g) for s in ((2, 3, d), (2, 3, L // 2, d), (2, 3, L // 2, d))]
+    K, V = [torch.stack((x, -x), dim=3).reshape(2, 3, L, d).to(DEV) for x in (K, V)]
+    q = q.to(DEV)
+    base = llla.llla_decode(q * 2.0 ** -60, K, V, 1e-2, d ** -0.5)
+    assert torch.isfinite(base).all() and (base != 0).any()
+    for k in (-112, -90):
+        assert torch.equal(llla.llla_decode(q * 2.0 ** k, K, V, 1e-2, d ** -0.5).double(), base.double() * 2.0 ** (k + 60)), k
