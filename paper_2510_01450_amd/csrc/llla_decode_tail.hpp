@@ -243,6 +243,26 @@ struct HeadLds {
 constexpr int SOLVE_TRIES = 5;
 __device__ inline float noise_ridge(int attempt) { return attempt == 0 ? 0.f : __builtin_ldexpf(1.f, 6 * attempt - 28); }
 
+// Second moments of 2^-102 and less have terms that matrix cores read as zero where they are taken in three bf16.  That matters where the ridge is
+// no larger: then keys and query are taken 2^r times, which brings the largest second moment to about one and leaves the output as it is.
+// (32 fp32 features of size 2^-60, 100 keys: 2.7e-5 off without it, 1e-7 with it and on fp32 MFMA.)  In LDS, in front of the solve: a choice between the
+// loads and the factorisation held up every call by 0.2 us, here it is 0.1 (16 heads x 4096 bf16 keys).
+constexpr float RIDGE_SMALL = 0x1p-80f;
+template <int D, class Lds>
+__device__ __forceinline__ int enlarge_keys(Lds &lds, int wave, int lane)      // (all four waves)
+{
+    using S = DecShape<D>;
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4 * S::NB; ++i) top = fmaxf(top, fabsf(lds.tiles[0][upper_tile<S::NB>(i / 4, i / 4) * 256 + lane * 4 + i % 4]));
+    const int r = max(-__builtin_amdgcn_frexp_expf(wave_max_dpp(top)) / 2, 0), tid = wave * 64 + lane;
+    __syncthreads();
+    for (int i = tid; i < S::NTILES * 256; i += DEC_NT) lds.tiles[0][i] = __builtin_ldexpf(lds.tiles[0][i], i < S::NSIG * 256 ? 2 * r : r);
+    if (tid < D) lds.mu[0][tid] = __builtin_ldexpf(lds.mu[0][tid], r);
+    __syncthreads();
+    return r;
+}
+
 // What a lane needs of the head's query (features 16 P + 4 g + t; at d = 128 16 P + n), requested by the caller long before the solve: a trip to memory is a tenth of it.
 template <int D>
 struct QueryPart { static constexpr int PER = D == 128 ? 1 : 4; float v[D / 16][PER]; };
@@ -281,14 +301,21 @@ __device__ __forceinline__ QueryPart<D> load_query(const HeadOut &out, int bh, i
 // 16 x 512 (one workgroup per head) 17.4 -> 16.3, 512 x 700 30.4 -> 28.7; fp32 16 x 4096 29.8 -> 28.7; errors 0.6 to 1.0 times those before.
 // (The columns dealt over the four waves, tiles handed on through LDS with two barriers per step: 23.9, 17.2, 28.5, 29.2; d = 128 53.7 -> 56.3.)
 template <int D, typename TI, bool PERM, class Lds>
-__device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, const QueryPart<D> &q, int bh, int wave, int lane)
+__device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, QueryPart<D> q, int bh, int wave, int lane)
 {
     using S = DecShape<D>;
     constexpr int NB = S::NB;
     static_assert(NB <= 4, "a column of G_c per wave");
     const int g = lane / 16, nn = lane % 16;
+    float lambda = out.lambda;
+    if (lambda < RIDGE_SMALL) {                           // (a scalar branch)
+        const int r = enlarge_keys<D>(lds, wave, lane);
+        lambda = __builtin_ldexpf(lambda, 2 * r);
+#pragma unroll
+        for (int i = 0; i < 4 * NB; ++i) q.v[i / 4][i % 4] = __builtin_ldexpf(q.v[i / 4][i % 4], r);
+    }
     if (wave >= NB) return;                               // (scalar branches: what follows contains MFMAs)
-    const float oinv = 1.f / lds.om[0], yc = lds.yv[0][16 * wave + nn], floor = 0.5f * out.lambda;
+    const float oinv = 1.f / lds.om[0], yc = lds.yv[0][16 * wave + nn], floor = 0.5f * lambda;
     float o = 0.f;
     for (int attempt = 0; attempt < SOLVE_TRIES; ++attempt) {
         asm volatile("" ::: "memory");                    // (the moments are read again: not kept in registers for a second attempt)
@@ -311,7 +338,7 @@ __device__ __forceinline__ void solve_and_store(Lds &lds, const HeadOut &out, co
                     if (J == P) {                         // symmetrised: element [nn][4 g + t] beside [4 g + t][nn]
                         const float other = fmaf(oinv * mc[J], lds.mu[0][16 * P + 4 * g + t], -tile[(16 * (nn >> 2) + 4 * g + t) * 4 + (nn & 3)]);
                         v = 0.5f * (v + other);
-                        v -= (nn == 4 * g + t) ? fmaf(eta, st[t], out.lambda) : 0.f;
+                        v -= (nn == 4 * g + t) ? fmaf(eta, st[t], lambda) : 0.f;
                     }
                     acc[upper_tile<NB>(P, J)][t] = v;
                 }

@@ -75,3 +75,16 @@ def test_queries_of_any_size(d):
     assert torch.isfinite(base).all() and (base != 0).any()
     for k in (-112, -90):
         assert torch.equal(llla.llla_decode(q * 2.0 ** k, K, V, 1e-2, d ** -0.5).double(), base.double() * 2.0 ** (k + 60)), k
+
+
+@pytest.mark.parametrize("dtype,d,H,e", [(torch.float32, 16, 3, 58), (torch.float32, 32, 3, 54), (torch.float32, 32, 3, 58), (torch.bfloat16, 32, 3, 54),
+                                         (torch.float32, 64, 3, 52), (torch.float32, 64, 150, 52)])
+@pytest.mark.parametrize("L", [100, 700])
+def test_keys_and_ridges_of_any_size(dtype, d, H, e, L):
+    """Query and keys times 2^-e, the scale times 2^2e and the ridge times 2^-2e are the same problem: the same bits, as long as the moments that the
+    matrix cores sum are not subnormal (fp32 caches at d = 64, whose products are taken of three bf16 terms: from 2^-54 on)."""
+    g = torch.Generator(device="cpu").manual_seed(3300 + d + L)
+    q, K, V = [torch.randn(s, generator=g).to(dtype).to(DEV) for s in ((2, H, d), (2, H, L, d), (2, H, L, d))]
+    base = llla.llla_decode(q, K, V, 1e-2, d ** -0.5)
+    s = 2.0 ** -e
+    assert torch.isfinite(base).all() and torch.equal(llla.llla_decode(q * s, K * s, V, 1e-2 * s * s, d ** -0.5 / (s * s)), base)
