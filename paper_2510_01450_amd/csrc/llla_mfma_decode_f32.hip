@@ -167,11 +167,19 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     };
     float om = 0.f, mref = -INFINITY, mtrue = -INFINITY;
 
-    auto unscale_values = [&]() {
+    // by roots, value features taken VALUE_SCALE times (all to begin with): bit 16 i + n is feature NB n + i
+    unsigned long long small = ~0ull;
+    auto value_scale = [&](unsigned long long which, int i, float s) {       // s for the lane's feature i if it is among them, else 1
+        return ((unsigned)(which >> (i & 2) * 16) >> (16 * (i & 1) + nn)) & 1 ? s : 1.f;
+    };
+    auto unscale_values = [&](unsigned long long which) {
 #pragma unroll
-        for (int i = 0; i < NR; ++i) yv[i] *= 1.f / VALUE_SCALE;
+        for (int i = 0; i < NR; ++i) {
+            const float f = value_scale(which, i, 1.f / VALUE_SCALE);
+            yv[i] *= f;
 #pragma unroll
-        for (int t = S::NSIG; t < S::NTILES; ++t) acc[t] *= 1.f / VALUE_SCALE;
+            for (int I = 0; I < NB; ++I) acc[S::NSIG + NB * I + i] *= f;
+        }
     };
     typedef RowFrag<TI, NB> Frag;
     struct Step { Frag k[CH], v[CH]; };
@@ -287,9 +295,10 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     // rows in registers / one with two LDS stages / two waves: 256 heads x 8192 234 / 215 / 212, 512 x 1000 79 / 74 / 66, 1024 x 2000 260 / 243 / 220.  On fp32 MFMA, also two waves: 512 x 100 25.7 (22.1 here), 512 x 512
     // 51.4 (42.3), 384 x 300 38.0 (30.9), 320 x 777 74.0 (60.0), 1024 x 800 137 (108).
     // The third term of a value below 2^-110 would be subnormal, which matrix cores read as zero.  So a stream starts with its values taken
-    // VALUE_SCALE times and goes over to the values as they are at the first one above VALUE_SMALL, ordinarily in its first step (64 heads
-    // x 1024 to 8192 62.6 -> 63.3 us, 16 x 32768 77.9 -> 79.0; values of size 2^-110 3e-7, 2^-124 1.4e-3 off without it, rounding with it).
-    bool small_values = true;
+    // VALUE_SCALE times and goes over to the values as they are, feature by feature, at the first one above VALUE_SMALL, ordinarily in its first
+    // step (64 heads x 1024 to 8192 62.6 -> 63.3 us, 16 x 32768 77.9 -> 79.0; values of size 2^-110 3e-7, 2^-124 1.4e-3 off without it, rounding
+    // with it).  A feature that stays below, of zeros for instance, costs its stream the choice in every step: 256 heads x 8192 with a quarter of the
+    // features zero 208 -> 214 us, as long as with none (213).
     // Rows of a step by DMA, a wave's own stages: lane l's 16 bytes of a chunk land at 16 l of its kilobyte, which is where the lane reads
     // them, so there is no swizzle, no bank conflict and no barrier.  tile: 0 keys, 1 values.
     unsigned char *const mine = stages + wave * ROOT_STAGE_B;
@@ -421,28 +430,34 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         key_block(std::integral_constant<int, 2>{});
         if (more) dma_wait_but<CH>();                     // all but the next step's keys
         else dma_wait_but<0>();
-        if (small_values) {                               // (a scalar branch)
-            float top = 0.f;
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                read_half(raw, 1, half);
-#pragma unroll
-                for (int c = 0; c < CH; ++c) top = fmaxf(top, fmaxf(fabsf(raw[0][c]), fabsf(raw[1][c])));
-            }
-            if (__builtin_amdgcn_ballot_w64(top > VALUE_SMALL) != 0) {
-                small_values = false;
-                unscale_values();
-            }
-        }
         auto read_values = [&](int half) {
             read_half(raw, 1, half);
             if (half && more) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 fetch_rows(1, s + 1);
             }
-            if (small_values) {
+            if (small != 0) {                             // (a scalar branch)
+                unsigned long long large = 0;
 #pragma unroll
-                for (int c = 0; c < CH; ++c) { raw[0][c] *= VALUE_SCALE; raw[1][c] *= VALUE_SCALE; }
+                for (int i = 0; i < 2; ++i) {
+                    float top = 0.f;
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) top = fmaxf(top, fabsf(raw[i][c]));
+                    unsigned long long m = __builtin_amdgcn_ballot_w64(top > VALUE_SMALL);
+                    m |= m >> 32;
+                    m |= m >> 16;
+                    large |= (m & 0xffff) << (32 * half + 16 * i);
+                }
+                if ((large & small) != 0) {
+                    unscale_values(large & small);
+                    small &= ~large;
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float f = value_scale(small, 2 * half + i, VALUE_SCALE);
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) raw[i][c] *= f;
+                }
             }
         };
         asm volatile("" ::: "memory");
@@ -541,7 +556,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
         }
 #pragma unroll 1
         for (int s = 0; s < nsteps; ++s) compute_roots(s);
-        if (nsteps > 0 && small_values) unscale_values();
+        if (small != 0) unscale_values(small);            // (nothing, where there was no step)
         __syncthreads();                                  // the stages of all waves are dead
     } else if (nsteps > 0) {
         Step sa, sb;

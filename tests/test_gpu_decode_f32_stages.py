@@ -49,7 +49,7 @@ def test_values_of_any_size(d, L):
         assert torch.equal(got.double(), base.double() * 2.0 ** k), k
 
 
-@pytest.mark.parametrize("dtype,d", [(torch.float32, 16), (torch.float32, 32), (torch.bfloat16, 16), (torch.bfloat16, 32)])
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 16), (torch.float32, 32), (torch.float32, 64), (torch.bfloat16, 16), (torch.bfloat16, 32)])
 @pytest.mark.parametrize("L", [80, 700, 3000])
 def test_value_features_of_different_sizes(dtype, d, L):
     """The same with a power of two of its own for every feature of V: no feature of the output hangs on the size of another."""
@@ -60,6 +60,22 @@ def test_value_features_of_different_sizes(dtype, d, L):
     base = llla.llla_decode(q, K, V, 1e-2, d ** -0.5)
     got = llla.llla_decode(q, K, (V.double() * size).to(dtype), 1e-2, d ** -0.5)
     assert torch.isfinite(base).all() and torch.equal(got.double(), base.double() * size)
+
+
+@pytest.mark.parametrize("H", [3, 300])
+def test_value_features_that_grow(H):
+    """Features of V that are zero, or as good as zero, up to some key and of ordinary size from there on, another one after every wave's first step."""
+    d, L = 64, 900
+    w = workloads.C5.with_shape(name="grow", B=2, H=H, n=L, d=d, dtype="f32", index=3150 + H, values="l2", tol=1e-4, scale=d ** -0.5)
+    q, K, V = workloads.make_inputs(w)
+    from_key = torch.arange(d) * 13                            # feature 0 is whole, feature 63 begins at key 819
+    before = (torch.arange(L)[:, None] < from_key).to(V.dtype)
+    zero, tiny = V * (1 - before), V * (1 - before) + V * before * 2.0 ** -100
+    ref = oracle.decode(q[:1, :3], K[:1, :3], zero[:1, :3], w.lam, w.scale)
+    for x in (zero, tiny):
+        got = llla.llla_decode(q.to(DEV), K.to(DEV), x.to(DEV), w.lam, w.scale)
+        # (24-bit operands and fp32 sums, as in test_steps_and_cuts)
+        check(got[:1, :3].cpu().numpy()[:, :, None], ref[:, :, None], np.array([L - 1]), d, 1e-5, "H=%d" % H)
 
 
 @pytest.mark.parametrize("d", [16, 32, 64])
