@@ -493,8 +493,8 @@ __device__ __forceinline__ void symmetric_rows(const f32x4 &x, float (&a)[16])
 // 2048 1049 and 1012, 16 x 8192 9674 and 9613, 8 x 44 46.7 and 43.8, backward 8 x 961 402 and 386; fp32 64 x 700 2413 and 2357.  Decode at
 // d = 128, one solve per compute unit, gains nothing (224 heads of up to 589 keys 54.7 and 55.6), nor do four systems per wave at d = 64 (64 x 4096 bf16
 // 2829 and 2916, 16 x 1024 fp32 346 and 352).
-// SYMMETRIC: the diagonal tiles come in symmetric to the last bit, and the factorisation takes one triangle of them (symmetric_rows); otherwise it takes
-// the mean of the two.
+// SYMMETRIC: the diagonal tiles come in symmetric to the last bit and stay so under their updates (fp32 products u^T u, with SPLIT = false), and the
+// factorisation takes one triangle of them (symmetric_rows); otherwise it takes the mean of the two.
 template <int NB, bool LOW = false, bool DROP = false, bool SPLIT = true, bool SYMMETRIC = false>
 __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], float *scw, int g, int nn, float pivot_floor, float *low = nullptr)
 {
@@ -551,7 +551,8 @@ __device__ __forceinline__ void factorise_one(f32x4 (&acc)[NB * (NB + 1) / 2], f
 // The same with further block columns (the decode tail's solve at d <= 64):
 //   in : x[v][P]               NX further block columns, negated right-hand sides -B in the same layout
 //   out: x = U^{-T} B; returns the smallest pivot before it was raised to the floor
-// Diagonal tiles come in symmetric (only their products are added to them here).  What bounds it is one chain per head: per diagonal tile rows, 1400
+// Diagonal tiles come in symmetric; their updates in three bf16 add the mixed terms [i][j] and [j][i] in another order each and leave them up to a rounding
+// apart, and the elimination takes one triangle, the lower.  What bounds it is one chain per head: per diagonal tile rows, 1400
 // cycles of elimination, 300 of inversion, products.  Rows by lane exchanges and products in three bf16, against a way through LDS and fp32 MFMA, with the
 // query's early request: us a call, 16 heads x 4096 23.7 -> 23.4, 16 x 512 (solved by the pass) 17.4 -> 16.3; errors 0.6 to 1.0 times the former.
 template <int NB, int NX>

@@ -1,10 +1,10 @@
 // fp32 matrix-core decode for gfx950: fp32 caches at every d, bf16 caches at d = 16 / 32 and at any d below the capacity from
-// which the 16-bit kernels serve.  All arithmetic in fp32 (bf16 is widened exactly), as in the vector kernels, on
-// v_mfma_f32_16x16x4_f32; one pass over the cache, the method of llla_mfma_decode.hip: each wave accumulates, relative to a
+// which the 16-bit kernels serve.  The precision of fp32 (bf16 is widened exactly), as in the vector kernels: on v_mfma_f32_16x16x4_f32, or, fp32
+// caches at d = 64 and bf16 ones at d = 16 / 32, on 16-bit matrix instructions with operands in three bf16 (below).  One pass over the cache, the method of llla_mfma_decode.hip: each wave accumulates, relative to a
 // running reference exponent, omega, mu~, Sigma~ and the value moments sum w v and G~ = sum w k v^T, and the solved system gives
 // o = y0 * sum w v + G~^T y1.
 //
-// No LDS and no data movement in the loop.  An MFMA with the key as contraction index wants lane (g, n) to hold element n of
+// No LDS and no data movement in the loop, but for fp32 rows at d = 64.  An MFMA with the key as contraction index wants lane (g, n) to hold element n of
 // key g; the features may be numbered in any order, so lane (g, n) owns features NB n .. NB n + NB - 1 (NB = d / 16) of key g: one
 // vector load per lane and four keys, fully coalesced (the wave reads four whole rows), and register I is directly the A operand
 // (times w) of row block I and the B operand of column block I of every tile product.  Feature NB n + I is element n of block I in
@@ -17,7 +17,7 @@
 // products instead of eight fp32 ones of twice the cycles.
 //
 // fp32 caches at d = 64 do likewise (compute_roots): 26 tiles of 16x16x4 per four keys were 832 matrix-core cycles for 2 KB of cache, 6 TB/s
-// at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 296.
+// at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 296.  Their rows pass through LDS stages of the wave's own.
 //
 // What bounds it: HBM at d = 16 / 32; matrix and vector work of two waves per SIMD at d = 64 in fp32 (4.9 TB/s at 256 heads x 8192); at d = 128
 // 100 tiles of 16x16x4 per four keys, 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
@@ -291,7 +291,7 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     // now, 4.9e-7 on fp32 MFMA; 32 x 8192 3.5e-7, 2.7e-7, 3.2e-7.  64 heads x 1024 to 8192 61.3 -> 61.8 us a call, 256 x 8192 220 -> 241.)
     // Two waves per SIMD.  The rows come by DMA into LDS, and a conversion reads the two feature blocks it needs; kept in registers, with sums put off
     // by the compiler until after the next branch (their terms kept until then), a wave took 430 registers, was alone on its SIMD and
-    // waited for its values.  249 now; the conversion of the next block is pinned to alternate with the products of this one.  us, one wave with
+    // waited for its values.  246 to 249 now; the conversion of the next block is pinned to alternate with the products of this one.  us, one wave with
     // rows in registers / one with two LDS stages / two waves: 256 heads x 8192 234 / 215 / 212, 512 x 1000 79 / 74 / 66, 1024 x 2000 260 / 243 / 220.  On fp32 MFMA, also two waves: 512 x 100 25.7 (22.1 here), 512 x 512
     // 51.4 (42.3), 384 x 300 38.0 (30.9), 320 x 777 74.0 (60.0), 1024 x 800 137 (108).
     // The third term of a value below 2^-110 would be subnormal, which matrix cores read as zero.  So a stream starts with its values taken

@@ -305,8 +305,8 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                     w0 = *reinterpret_cast<const f32x4 *>(wp);
                     w1 = *reinterpret_cast<const f32x4 *>(wp + 4);
                 }
-                // read again for every query: 32 registers for the keys of a half would push accumulators into scratch memory (some
-                // 30 registers are spilled as it is, around this loop; nothing inside it touches scratch memory)
+                // read again for every query: 32 registers for the keys of a half would push accumulators into scratch memory (as it is,
+                // 37 are spilled around this loop; nothing inside it touches scratch memory)
                 asm volatile("" ::: "memory");
                 float x[8];
 #pragma unroll
