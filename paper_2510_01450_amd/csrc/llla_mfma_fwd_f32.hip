@@ -21,6 +21,7 @@
 // moment is F_i times the max-normalised one, so the system solved is the max-normalised one times F_i:
 // [omega' mu~'^T; mu~' Sigma~' + lambda F I] y' = [1; q], and the output weights w'_ij (y0' + k_j . y1') equal those of
 // Eq. (lla).  mh_i and y'_i go to the output sweep; delta_i = delta'_i / F_i (rho_i needs no correction).
+#include <algorithm>
 #include "llla_dual.hpp"
 #include "llla_mfma_common.hpp"
 #include "llla_mfma_solve64.hpp"
@@ -93,10 +94,10 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
                                                             float cscale, float lambda, const float *__restrict__ lam_rows,
                                                             float *__restrict__ Mg, float *__restrict__ LFg,
                                                             float *__restrict__ Yg, float *__restrict__ RUg, int causal, int nqb,
-                                                            dual::DualArgs da, int out_bf16)
+                                                            dual::DualArgs da, int rows_at, int mixed, int out_bf16)
 {
     // nqb: blocks of 16 query rows the sequence has; rows [0, da.nrows), a multiple of 16 or all, are the key-space workgroups' (four each),
-    // which follow all others and work on the caller's own tensors
+    // which start after rows_at others and work on the caller's own tensors (mixed: see block_order)
     using S = Shape<FD>;
     constexpr int NB = 4, QW = 4, QB = 16, YP = S::YP;
     // The backward at d = 16 / 32 sums mu~ and omega on the vector ALU, from the same rounded sqrt(w) k that Sigma~ is formed of, which leaves
@@ -108,13 +109,13 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, g = lane / 16, nn = lane % 16;
     const int own = BWD ? nqb : nqb - (da.nrows + QB - 1) / QB;      // blocks of a head here
     const int lin = linear_block();
-    if constexpr (!BWD) {
-        // Behind the blocks of all heads.  Behind those of their own head they held up the longest blocks of the heads that come next on the same XCD.
-        // us a call so / here: 16 heads x 1024 342 / 331, 12 x 800 263 / 215, 24 x 400 144 / 128, 64 x 128 136 / 95, 64 x 500 438 / 383, 16 x 256
-        // 80 / 69, 16 x 500 138 / 140; after the first 256 workgroups 331, 246, 147, 95, 414, 83, 142; in front of all 331, 250, 146, 116, 417, 83, 143.
-        const int at = lin - own * (int)gridDim.y;
-        if (at >= 0) {
-            const int bh = (int)((unsigned)at % gridDim.y), part = (int)((unsigned)at / gridDim.y);
+    BlockMap bm;
+    if constexpr (BWD) {
+        bm = xcd_block_map(lin, own, (int)gridDim.y);
+    } else {
+        const int heads = (int)gridDim.y, parts = ((int)gridDim.x - own) * heads, at = lin - rows_at;
+        if (__builtin_expect((unsigned)at < (unsigned)parts, 0)) {
+            const int bh = (int)((unsigned)at % (unsigned)heads), part = (int)((unsigned)at / (unsigned)heads);
             using DS = dual::DualSharedRows<16 * LIVE, 4>;
             static_assert(sizeof(DS) <= sizeof(F32Shared), "key-space rows fit the workgroup's LDS");
             auto &ds = *reinterpret_cast<DS *>(&sm);
@@ -123,8 +124,9 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
             else dual::dual_forward_rows<16 * LIVE, 4, float>(ds, da, bh, top);
             return;
         }
+        const int l = at < 0 ? lin : lin - parts;
+        bm = mixed ? BlockMap{(int)((unsigned)l % (unsigned)heads), (int)((unsigned)l / (unsigned)heads)} : xcd_block_map(l, own, heads);
     }
-    const BlockMap bm = xcd_block_map(lin, own, (int)gridDim.y);
     const int bh = bm.bh, b = bh / H, h = bh % H;
     const int i0 = (nqb - 1 - bm.blk) * QB;                           // long rows first
     const int ilast = min(i0 + QB - 1, n - 1);
@@ -479,6 +481,29 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
     }
 }
 
+// The order in which the workgroups of a launch start: `rows_at` blocks of query rows, then all key-space workgroups, then the other blocks; mixed: the
+// longest block of every head, then the second longest ..., else head by head, a head's blocks on one XCD (xcd_block_map).
+// A launch of some 500 workgroups, what the GPU holds at once, is as long as its worst compute unit, and which two workgroups share one follows from the
+// order: neighbours go round the XCDs, and on an XCD the 33rd joins the first.  Head by head, the longest block of a head joins one of the next head
+// that is nearly as long, and a further workgroup waits for the shader engine whose turn it is.  Mixed, the first 256 are the longest of the call, each
+// on a compute unit of its own; then come the short key-space workgroups (all else at d = 64 is longer), and short blocks at the end fill what is left.
+// us a call, head by head with the key-space workgroups behind their own head's blocks / behind all blocks / this, d = 64: 4 x 1500 325 / 366 / 268,
+// 12 x 500 138 / 145 / 107, 16 x 500 139 / 140 / 112, 16 x 600 160 / 172 / 144, 16 x 1000 332 / 324 / 314, 64 x 1000 1224 / 1115 / 1089.
+// Where a head has fewer than 24 blocks for its 16 key-space workgroups they are no small part of the call any more and go last (mixed, 48 x 300 153 ->
+// 161, 16 x 350 93 -> 96); with more than 16 heads the same holds up to 28 blocks (40 x 480 221 -> 229).
+// At d = 16 / 32 a block is hardly longer than a key-space workgroup.  In front of all else they pay while they are few, four on ten compute units
+// (d = 16, 4 x 1100 86 -> 75, behind 256 blocks 88), behind 256 blocks where the blocks alone fill the GPU nearly twice (16 x 600 92 -> 74; 8 x 900, 424
+// blocks, 76 -> 83).
+struct BlockOrder { int rows_at, mixed; };
+inline BlockOrder block_order(int live, int heads, int own, int parts)
+{
+    const int blocks = own * heads;
+    if (parts == 0) return BlockOrder{blocks, 0};
+    if (live == 4) return own >= (heads <= 16 ? 24 : 28) ? BlockOrder{std::min(blocks, 256), 1} : BlockOrder{blocks, 0};
+    if (blocks > 256 && parts * heads <= 96) return BlockOrder{0, 1};
+    return blocks >= 480 ? BlockOrder{256, 1} : BlockOrder{blocks, 0};
+}
+
 // Statistics of Eq. (lla) from y' and F: 1/delta' = y0' + q . y1', delta = delta' / F, rho = -delta' y1'.  One wave per row.
 __global__ __launch_bounds__(256) void stats_f32_kernel(const float *__restrict__ Qg, llla_strides sq, int H, int n, int npad,
                                                         const float *__restrict__ Yg, const float *__restrict__ LFg,
@@ -520,16 +545,18 @@ hipError_t mfma_forward_f32(const Problem &p, const Problem &call)
     dual::DualArgs da = dual::dual_args(call);
     da.nrows = dual_forward_rows(p);                               // up to 64 keys at every head dimension
     const int nqb = (p.n + S::QB - 1) / S::QB, obf = p.out == LLLA_BF16 ? 1 : 0;
-    const dim3 grid(nqb - (da.nrows + S::QB - 1) / S::QB + (da.nrows + 3) / 4, bh);
+    const int own = nqb - (da.nrows + S::QB - 1) / S::QB, parts = (da.nrows + 3) / 4;
+    const dim3 grid(own + parts, bh);
+    const BlockOrder order = block_order(live, bh, own, parts);
     if (live == 1)
         hipLaunchKernelGGL(moments_f32_kernel<1>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, order.rows_at, order.mixed, obf);
     else if (live == 2)
         hipLaunchKernelGGL(moments_f32_kernel<2>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, order.rows_at, order.mixed, obf);
     else
         hipLaunchKernelGGL(moments_f32_kernel<4>, grid, dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, L.npad,
-                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, obf);
+                           p.scale * LOG2E, p.lambda, p.lambda_rows, M, LF, Y, nullptr, p.causal, nqb, da, order.rows_at, order.mixed, obf);
     if (p.rho != nullptr || p.delta != nullptr) {
         stage_mark(p.stream, "statistics");
         hipLaunchKernelGGL(stats_f32_kernel, dim3((p.n + 3) / 4, bh), dim3(256), 0, p.stream, Q, p.sq, p.H, p.n, L.npad,
@@ -546,7 +573,7 @@ hipError_t mfma_moments_f32_given(const BackwardProblem &p, int npad, float *M, 
     const int nqb = (p.n + Shape<FD>::QB - 1) / Shape<FD>::QB;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(nqb, p.B * p.H), dim3(256), 0, p.stream, Q, K, p.sq, p.sk, p.H, p.n, npad, p.scale * LOG2E,
-                           p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1, nqb, dual::DualArgs{}, 0);
+                           p.lambda, p.lambda_rows, M, nullptr, Y, RU, 1, nqb, dual::DualArgs{}, 0, 0, 0);
     };
     if (p.live_d == 16) launch(moments_f32_kernel<1, true>);
     else if (p.live_d == 32) launch(moments_f32_kernel<2, true>);

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(WNT, 1) void moments_f32_wide_kernel(
     const int own = BWD ? nqb : nqb - (da.nrows + WQB - 1) / WQB;      // blocks of a head here
     const int lin = linear_block();
     if constexpr (!BWD) {
-        const int at = lin - own * (int)gridDim.y;         // behind the blocks of all heads, as in moments_f32_kernel
+        const int at = lin - own * (int)gridDim.y;         // behind the blocks of all heads (us so / behind their own head's: 16 x 500 364 / 375)
         if (at >= 0) {
             const int bh = (int)((unsigned)at % gridDim.y), part = (int)((unsigned)at / gridDim.y);
             using DS = dual::DualSharedRows<WD, WQB>;
