@@ -117,9 +117,10 @@ __device__ inline FlatPlan flat_plan(const DecSplit &s, int &b_of, Pos pos)
 }
 
 // Calls body(piece) for every piece of this workgroup's share, with a barrier between two of them (the body owns the workgroup's
-// LDS).  Everything that decides the control flow is wave-uniform and the same in all waves.  ONE: even cut, one piece.
+// LDS).  Everything that decides the control flow is wave-uniform and the same in all waves.  ONE: even cut, one piece.  heads_first: flat, in a grid
+// (H, slots) instead of (slots, H).
 template <bool ONE, class Body>
-__device__ __forceinline__ void for_pieces(const DecSplit &s, Body body)
+__device__ __forceinline__ void for_pieces(const DecSplit &s, Body body, bool heads_first = false)
 {
     DecPiece pc;
     const bool flat = !ONE && s.slots != 0;
@@ -134,11 +135,12 @@ __device__ __forceinline__ void for_pieces(const DecSplit &s, Body body)
         pc.k1 = min(pc.k0 + part, pc.L);
         pc.rec = pc.bh * s.nsplit + blockIdx.x;
     } else {
+        const int x = (int)(heads_first ? blockIdx.y : blockIdx.x), y = (int)(heads_first ? blockIdx.x : blockIdx.y);
         int b = -1;
-        const FlatPlan plan = flat_plan(s, b, [](int share) { return (int)blockIdx.x * share; });
+        const FlatPlan plan = flat_plan(s, b, [x](int share) { return x * share; });
         pc.b = __builtin_amdgcn_readfirstlane(b);
-        pc.h = blockIdx.y;
-        const int share = __builtin_amdgcn_readfirstlane(plan.share), at = (int)blockIdx.x * share;
+        pc.h = y;
+        const int share = __builtin_amdgcn_readfirstlane(plan.share), at = x * share;
         end = min(at + share, __builtin_amdgcn_readfirstlane(plan.total));
         if (at >= end) return;
         start = __builtin_amdgcn_readfirstlane(plan.start);
@@ -147,7 +149,7 @@ __device__ __forceinline__ void for_pieces(const DecSplit &s, Body body)
         pc.k0 = (at - start) * s.unit;
         pc.k1 = min((stop - start) * s.unit, pc.L);
         pc.bh = pc.b * s.H + pc.h;
-        pc.rec = (int)blockIdx.y * (s.slots + s.B) + (int)blockIdx.x + pc.b;
+        pc.rec = y * (s.slots + s.B) + x + pc.b;
     }
     for (;;) {
         body(pc);

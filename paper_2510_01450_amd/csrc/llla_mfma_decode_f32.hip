@@ -116,6 +116,7 @@ struct F32Args {
     HeadOut out;
     float cscale;
     float *parts;
+    int heads_first;       // flat cut by roots: grid (H, slots)
 };
 
 // The stream of one wave and what becomes of its moments.  W: the wave's share of the tiles (TEAM), else 0.
@@ -622,7 +623,8 @@ __global__ __launch_bounds__(NT, D == 32 && sizeof(TI) == 2 ? 2 : D <= 32 ? 4 : 
         constexpr size_t STAGES_B = ROOTS ? 4 * (ROOT_STAGE_B + 1024) : 0;
         __shared__ __align__(16) unsigned char raw[STAGES_B > sizeof(Lds) ? STAGES_B : sizeof(Lds)];
         Lds &lds = *reinterpret_cast<Lds *>(raw);
-        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, raw, wave, piece_lane()); });
+        for_pieces<FUSED>(a.split, [&](const DecPiece &pc) { decode_f32_body<D, TI, FUSED, ROOTS, 0>(a, pc, lds, raw, wave, piece_lane()); },
+                          ROOTS && a.heads_first != 0);
     }
 }
 
@@ -679,6 +681,11 @@ hipError_t f32_launch(const Problem &p)
     int ns = scratch ? f32_nsplit<D>(bh, p.n, room, ROOTS ? 256 : S::SLOTS) : 1;
     if (ROOTS && scratch && p.n >= 4096 * ns && 2 * bh * ns <= S::SLOTS && 2 * ns <= S::MAX_SPLIT && (size_t)bh * 2 * ns <= records) ns *= 2;
     a.split = choose_split(p, ns, scratch ? records : 0, S::SLOTS, ROOTS ? 256 : 4 * S::STEP, S::KEYS_MIN, S::MAX_SPLIT);
+    // Two workgroups of a flat cut share a compute unit only where there are more than compute units: neighbours in the grid go round them, so shares
+    // that hold keys come first, all heads' first ones, where a part of the slots stays empty (at most two units of keys per slot, were all sequences
+    // as long as the cache).  us, a head's shares together / this: 2 sequences x 16 heads of up to 500 keys 27.3 / 22.4, of up to 5000 36.8 / 33.5, 16 x 16 of up
+    // to 900 43.9 / 40.3; with fuller slots it changes little (4 x 16 of up to 8192 59.9 / 60.8, 8 x 16 of up to 8192 89.3 / 87.9).
+    a.heads_first = ROOTS && a.split.slots != 0 && (long long)bh * ((p.n + 255) / 256) <= 2 * S::SLOTS ? 1 : 0;
     a.out = HeadOut{p.Q, p.O, p.out == LLLA_BF16 ? 1 : 0, p.lambda};
     a.cscale = p.scale * LOG2E;
     a.parts = static_cast<float *>(p.ws);
@@ -690,8 +697,8 @@ hipError_t f32_launch(const Problem &p)
         return e != hipSuccess || p.seqlens == nullptr ? e : dual_decode(p);
     } else {
         stage_mark(p.stream, "decode_partial");
-        hipLaunchKernelGGL((decode_f32_kernel<D, TI, false, ROOTS>), a.split.slots ? dim3(a.split.slots, p.H) : dim3(a.split.nsplit, bh), dim3(NT),
-                           0, p.stream, a);
+        hipLaunchKernelGGL((decode_f32_kernel<D, TI, false, ROOTS>), !a.split.slots ? dim3(a.split.nsplit, bh) : a.heads_first ? dim3(p.H, a.split.slots) : dim3(a.split.slots, p.H),
+                           dim3(NT), 0, p.stream, a);
         stage_mark(p.stream, "decode_merge");
         if (p.seqlens == nullptr)
             hipLaunchKernelGGL((decode_merge_kernel<D, TI, true>), dim3(bh), dim3(NT), 0, p.stream, a.split, a.out, (const float *)a.parts,

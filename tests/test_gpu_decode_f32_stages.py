@@ -104,3 +104,19 @@ def test_keys_and_ridges_of_any_size(dtype, d, H, e, L):
     base = llla.llla_decode(q, K, V, 1e-2, d ** -0.5)
     s = 2.0 ** -e
     assert torch.isfinite(base).all() and torch.equal(llla.llla_decode(q * s, K * s, V, 1e-2 * s * s, d ** -0.5 / (s * s)), base)
+
+
+@pytest.mark.parametrize("B,H,L", [(16, 16, 1024), (4, 3, 21760), (5, 12, 4352)])
+def test_order_of_shares(B, H, L):
+    """Sequences of lengths of their own: up to two units of 256 keys of full caches per slot (the capacities here, to within a unit) the heads' first
+    shares start first, beyond it a head's shares together.  The shares are the same, and so are the bits."""
+    d = 64
+    g = torch.Generator(device="cpu").manual_seed(3400 + L)
+    units = 1024 // (B * H)
+    assert L == 256 * units
+    q, K, V = [torch.randn(s, generator=g).to(DEV) for s in ((B, H, d), (B, H, L + 1, d), (B, H, L + 1, d))]
+    lens = torch.randint(1, L + 1, (B,), generator=g, dtype=torch.int32)
+    lens[B - 1] = L
+    lens = lens.to(DEV)
+    got = llla.llla_decode(q, K[:, :, :L], V[:, :, :L], 1e-2, d ** -0.5, seqlens=lens)
+    assert torch.isfinite(got).all() and torch.equal(got, llla.llla_decode(q, K, V, 1e-2, d ** -0.5, seqlens=lens))
