@@ -19,7 +19,8 @@
 // fp32 caches at d = 64 do likewise (compute_roots): 26 tiles of 16x16x4 per four keys were 832 matrix-core cycles for 2 KB of cache, 6 TB/s
 // at 2.4 GHz and 2.7 reached; both operands in three bf16, as sqrt(w) k and sqrt(w) v, take 296.  Their rows pass through LDS stages of the wave's own.
 //
-// What bounds it: HBM at d = 16 / 32; matrix and vector work of two waves per SIMD at d = 64 in fp32 (4.9 TB/s at 256 heads x 8192); at d = 128
+// What bounds it: HBM at d = 16 / 32; at d = 64 in fp32 nearly HBM (194 us = 5.5 TB/s of 6.6 at 256 heads x 8192) and nearly the two waves of a SIMD, matrix cores 36 % and
+// vector port 45 % busy, and in short calls latency (64 heads of 1024 to 8192 keys, six steps a wave: 3.6 TB/s, 19 and 28 %); at d = 128
 // 100 tiles of 16x16x4 per four keys, 3 TB/s: the matrix cores.  There the accumulators of a stream (400 registers) are dealt over the four waves of a workgroup:
 // wave W owns row blocks W and 7 - W, 25 tiles whatever W; every wave loads the whole rows (the first-level cache serves three
 // of the four) and forms the weights for itself, so there is no exchange at all.
@@ -301,7 +302,8 @@ __device__ __forceinline__ void decode_f32_body(const F32Args &a, const DecPiece
     // with it).  A feature that stays below, of zeros for instance, costs its stream the choice in every step: 256 heads x 8192 with a quarter of the
     // features zero 208 -> 214 us, as long as with none (213).
     // Rows of a step by DMA, a wave's own stages: lane l's 16 bytes of a chunk land at 16 l of its kilobyte, which is where the lane reads
-    // them, so there is no swizzle, no bank conflict and no barrier.  tile: 0 keys, 1 values.
+    // them, so there is no swizzle and no barrier, and the 16-byte reads have no bank conflicts; those of a half, 8 bytes at a distance of 16, have
+    // (43 % of LDS cycles, which are 18 % of all).  tile: 0 keys, 1 values.
     unsigned char *const mine = stages + wave * ROOT_STAGE_B;
     auto fetch_rows = [&](int tile, int s) {
         const char *base = tile ? Vh : Kh;

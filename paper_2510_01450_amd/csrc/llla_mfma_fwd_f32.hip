@@ -491,16 +491,16 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
 // 12 x 500 138 / 145 / 107, 16 x 500 139 / 140 / 112, 16 x 600 160 / 172 / 144, 16 x 1000 332 / 324 / 314, 64 x 1000 1224 / 1115 / 1089.
 // Where a head has fewer than 24 blocks for its 16 key-space workgroups they are no small part of the call any more and go last (mixed, 48 x 300 153 ->
 // 161, 16 x 350 93 -> 96); with more than 16 heads the same holds up to 28 blocks (40 x 480 221 -> 229).
-// At d = 16 / 32 a block is hardly longer than a key-space workgroup.  In front of all else they pay while they are few, four on ten compute units
-// (d = 16, 4 x 1100 86 -> 75, behind 256 blocks 88), behind 256 blocks where the blocks alone fill the GPU nearly twice (16 x 600 92 -> 74; 8 x 900, 424
-// blocks, 76 -> 83).
+// At d = 16 / 32 a block is hardly longer than a key-space workgroup.  In front of all else, where they meet the longest blocks, they pay while they are few, three for
+// eight compute units, or while all start at once (d = 16, 4 x 1100 86 -> 75, behind 256 blocks 88; d = 32, 10 x 500 82 -> 77; d = 16, 10 x 600, 500 workgroups,
+// 69 -> 72), behind 256 blocks where the blocks alone fill the GPU nearly twice (d = 16, 16 x 600 92 -> 73; 8 x 900, 424 blocks, 76 -> 83).
 struct BlockOrder { int rows_at, mixed; };
 inline BlockOrder block_order(int live, int heads, int own, int parts)
 {
     const int blocks = own * heads;
     if (parts == 0) return BlockOrder{blocks, 0};
     if (live == 4) return own >= (heads <= 16 ? 24 : 28) ? BlockOrder{std::min(blocks, 256), 1} : BlockOrder{blocks, 0};
-    if (blocks > 256 && parts * heads <= 96) return BlockOrder{0, 1};
+    if (blocks > 256 && (parts * heads <= 96 || blocks + parts * heads <= 480)) return BlockOrder{0, 1};
     return blocks >= 480 ? BlockOrder{256, 1} : BlockOrder{blocks, 0};
 }
 
