@@ -41,24 +41,24 @@ CSRC = os.path.join(ROOT, "paper_2510_01450_amd", "csrc")
 # scaled with a copy kernel of known size.  Each entry names the summary it was taken from and the hash of the kernel's
 # source file at the time: when the source has changed since, the figure is not reported (traffic = null).
 MEASURED_TRAFFIC = {
-    ("C3_prefill_bf16_n4096_d64", "moments"): {"fetch_bytes": 1.058e+08, "write_bytes": 8.109e+07, "source": "profiles/forward_C3_C3b_moments_kernel_mfma_counters.md",
+    ("C3_prefill_bf16_n4096_d64", "moments"): {"fetch_bytes": 1.040e+08, "write_bytes": 8.099e+07, "source": "profiles/forward_C3_C3b_moments_kernel_mfma_counters.md",
         "kernel_files": ["llla_mfma_fwd.hip", "llla_mfma_common.hpp", "llla_mfma_solve64.hpp"],
-        "kernel_sha16": "1554a82e8fa01087,d7714e9175e4ad38,f43966e0f1d3ccb1"},
-    ("C3b_prefill_bf16_n8192_d64", "moments"): {"fetch_bytes": 1.074e+08, "write_bytes": 8.581e+07, "source": "profiles/forward_C3_C3b_moments_kernel_mfma_counters.md",
+        "kernel_sha16": "1554a82e8fa01087,3a3dd57a2532c062,f43966e0f1d3ccb1"},
+    ("C3b_prefill_bf16_n8192_d64", "moments"): {"fetch_bytes": 1.066e+08, "write_bytes": 8.582e+07, "source": "profiles/forward_C3_C3b_moments_kernel_mfma_counters.md",
         "kernel_files": ["llla_mfma_fwd.hip", "llla_mfma_common.hpp", "llla_mfma_solve64.hpp"],
-        "kernel_sha16": "1554a82e8fa01087,d7714e9175e4ad38,f43966e0f1d3ccb1"},
+        "kernel_sha16": "1554a82e8fa01087,3a3dd57a2532c062,f43966e0f1d3ccb1"},
     ("C5_decode_bf16_L32768_d64", "decode_partial"): {"fetch_bytes": 4.296e+09, "write_bytes": 1.311e+05, "source": "profiles/decode_C5_bf16_L32768_d64_hbm_traffic.md",
         "kernel_files": ["llla_mfma_decode.hip", "llla_decode_tail.hpp", "llla_mfma_common.hpp"],
-        "kernel_sha16": "5bc82355d8460a21,3c0ff26e455c60b0,d7714e9175e4ad38"},
+        "kernel_sha16": "5bc82355d8460a21,44b08eb93375a9d5,3a3dd57a2532c062"},
     ("C5d128_decode_bf16_L32768_d128", "decode_partial"): {"fetch_bytes": 4.296e+09, "write_bytes": 5.297e+07, "source": "profiles/decode_C5d128_bf16_L32768_d128_hbm_traffic.md",
         "kernel_files": ["llla_mfma_decode128.hip", "llla_decode_tail.hpp", "llla_mfma_common.hpp"],
-        "kernel_sha16": "61808e2a8149462b,3c0ff26e455c60b0,d7714e9175e4ad38"},
-    ("C4_longctx_bf16_n8192_d128", "moments"): {"fetch_bytes": 9.204e+08, "write_bytes": 8.598e+07, "source": "profiles/forward_C4_bf16_n8192_d128_hbm_traffic.md",
+        "kernel_sha16": "61808e2a8149462b,44b08eb93375a9d5,3a3dd57a2532c062"},
+    ("C4_longctx_bf16_n8192_d128", "moments"): {"fetch_bytes": 9.235e+08, "write_bytes": 8.598e+07, "source": "profiles/forward_C4_bf16_n8192_d128_hbm_traffic.md",
         "kernel_files": ["llla_mfma_fwd.hip", "llla_mfma_common.hpp", "llla_mfma_solve128.hpp"],
-        "kernel_sha16": "1554a82e8fa01087,d7714e9175e4ad38,c536f4c1342b1f30"},
-    ("C2_f32_n1024_d64", "moments"): {"fetch_bytes": 1.893e+07, "write_bytes": 2.161e+07, "source": "profiles/forward_C2_f32_n1024_d64_counters.md",
+        "kernel_sha16": "1554a82e8fa01087,3a3dd57a2532c062,645315b670a2d65a"},
+    ("C2_f32_n1024_d64", "moments"): {"fetch_bytes": 1.890e+07, "write_bytes": 2.289e+07, "source": "profiles/forward_C2_f32_n1024_d64_counters.md",
         "kernel_files": ["llla_mfma_fwd_f32.hip", "llla_mfma_common.hpp", "llla_mfma_solve64.hpp"],
-        "kernel_sha16": "f0c696b63899cb4e,d7714e9175e4ad38,f43966e0f1d3ccb1"},
+        "kernel_sha16": "9c7301ec93319db5,3a3dd57a2532c062,f43966e0f1d3ccb1"},
 }
 
 
