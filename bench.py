@@ -58,7 +58,7 @@ MEASURED_TRAFFIC = {
         "kernel_sha16": "1554a82e8fa01087,3a3dd57a2532c062,645315b670a2d65a"},
     ("C2_f32_n1024_d64", "moments"): {"fetch_bytes": 1.890e+07, "write_bytes": 2.289e+07, "source": "profiles/forward_C2_f32_n1024_d64_counters.md",
         "kernel_files": ["llla_mfma_fwd_f32.hip", "llla_mfma_common.hpp", "llla_mfma_solve64.hpp"],
-        "kernel_sha16": "9c7301ec93319db5,3a3dd57a2532c062,f43966e0f1d3ccb1"},
+        "kernel_sha16": "c07eb41c81ad849d,3a3dd57a2532c062,f43966e0f1d3ccb1"},
 }
 
 

@@ -492,7 +492,7 @@ __global__ __launch_bounds__(256, 2) void moments_f32_kernel(const float *__rest
 // Where a head has fewer than 24 blocks for its 16 key-space workgroups they are no small part of the call any more and go last (mixed, 48 x 300 153 ->
 // 161, 16 x 350 93 -> 96); with more than 16 heads the same holds up to 28 blocks (40 x 480 221 -> 229).
 // At d = 16 / 32 a block is hardly longer than a key-space workgroup.  In front of all else, where they meet the longest blocks, they pay while they are few, three for
-// eight compute units, or while all start at once (d = 16, 4 x 1100 86 -> 75, behind 256 blocks 88; d = 32, 10 x 500 82 -> 77; d = 16, 10 x 600, 500 workgroups,
+// eight compute units, or while all start at once (d = 16, 4 x 1100 86 -> 75, behind 256 blocks 88; d = 32, 10 x 500 82 -> 76; d = 16, 10 x 600, 500 workgroups,
 // 69 -> 72), behind 256 blocks where the blocks alone fill the GPU nearly twice (d = 16, 16 x 600 92 -> 73; 8 x 900, 424 blocks, 76 -> 83).
 struct BlockOrder { int rows_at, mixed; };
 inline BlockOrder block_order(int live, int heads, int own, int parts)
